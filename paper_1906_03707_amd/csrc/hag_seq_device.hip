@@ -8,13 +8,12 @@
 // forest is cut into PATHS: every state hands its running (h, c) on to one continuation (its
 // largest subtree, or one node's private remainder) without a trip through memory, and is written
 // to memory only if something else needs it (another path starts there, or it is some a_v).  A path
-// that starts from a written state is one level above the path that wrote it; one launch runs all
-// paths of a level, 64 per workgroup, each step a gathered matrix product on the matrix cores:
-//     gates^T [4H, paths] = Wp [4H, D+H] . Z^T [D+H, paths],    Z[j] = (x[in_j], h_j),
-// 32 gate rows x 32 paths per wavefront tile with v_mfma_f32_32x32x2_f32 (fp32 in, fp32 out).  The rows of
-// Wp are ordered (hidden unit, gate), so a lane ends up holding all four gates of its hidden units
-// for its path and the cell's element-wise part runs in registers.  A wavefront keeps its slice of
-// Wp in registers for the whole launch; the operand rows of a tile of paths are staged in LDS.
+// that starts from a written state is one level above the path that wrote it; paths run 64 per workgroup, each step a
+// matrix product on the matrix cores.  The half of the gates that depends on the input row only, W_ih x + b, is computed once
+// per node (a node occurs in many lists); a step adds to it
+//     gates^T [4H, paths] += W_hh [4H, H] . H^T [H, paths],
+// with fp32 operands cut into three bf16 pieces.  The rows of W_hh are ordered so that a lane ends up holding all four gates
+// of its hidden units for its path and the cell's element-wise part runs in registers.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -50,11 +49,12 @@ struct hag_seq {
     // for the backward pass: per step where its h_{t-1} lives (>= 0: that step's tape row, -1: the zero state,
     // <= -2: state row -(value) - 2), and the steps grouped by the input row they read (for the gradient of x)
     std::vector<int32_t> step_prev, xt_ptr, xt_idx;
+    std::vector<int32_t> used, step_g;   // the nodes that occur in a list, ascending; per step the place of its input row among them
     std::vector<int32_t> pending_init;   // per state: the paths that start from it
     int32_t *d_step_prev = nullptr, *d_xt_ptr = nullptr, *d_xt_idx = nullptr, *d_pending_init = nullptr;
+    int32_t *d_used = nullptr, *d_step_g = nullptr;
     int64_t resident_reverse[3] = {0, 0, 0};   // reverse kernel variants <false,1>, <false,2>, <true,2>
-    int64_t resident[6] = {0, 0, 0, 0, 0, 0};
-    int64_t resident_tape[6] = {0, 0, 0, 0, 0, 0};   // likewise for the variants that write the tape   // per kernel variant: workgroups the device holds at once (set by hag_seq_upload)
+    int64_t resident[3] = {0, 0, 0}, resident_tape[3] = {0, 0, 0};   // forward kernel variants, without and with the tape: workgroups the device holds at once (set by hag_seq_upload)
     int32_t *d_gave_up = nullptr;     // set by a wait that gave up; read and cleared by hag_seq_check
     int device = -1;
 };
@@ -62,34 +62,123 @@ struct hag_seq {
 namespace hag {
 
 constexpr int kSeqJobs = 64;      // paths per tile
-constexpr int kSeqMaxK = 256;     // D + H at most (128 for the variants that hold Wp in registers)
+constexpr int kSeqMaxK = 256;     // D + H at most
 
-// Wp / bp from the usual layout: w_ih [4H, D], w_hh [4H, H], b [4H], gate-major rows (input, forget,
-// cell, output gate).
-__global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
-                                                      const float *__restrict__ b, float *__restrict__ wp,
-                                                      float *__restrict__ bp, int d, int hidden, int kp, int operand_order,
-                                                      int32_t *__restrict__ flags, int64_t n_flags) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t total = (int64_t)4 * hidden * kp;
-    // the "state is written" flags of this pass start at zero
-    for (int64_t f = i; f < n_flags; f += (int64_t)gridDim.x * 256) flags[f] = 0;
-    if (i >= total) return;
-    int r = (int)(i / kp), k = (int)(i % kp);
-    if (operand_order) {
-        // the kernel that streams Wp reads it in the order its matrix instructions consume it:
-        // [gate tile][4 k-steps][lane][step in the group], lane l supplying row l % 32 and column 2 * step + l / 32
-        const int per_tile = 32 * kp, tile = (int)(i / per_tile), rest = (int)(i % per_tile);
-        const int q = rest / 256, lane = (rest % 256) / 4, step = 4 * q + (rest & 3);
-        r = tile * 32 + (lane & 31);
-        k = 2 * step + (lane >> 5);
+typedef float seq_acc_t __attribute__((ext_vector_type(16)));
+typedef __bf16 seq_b8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 seq_b2_t __attribute__((ext_vector_type(2)));
+typedef float seq_f2_t __attribute__((ext_vector_type(2)));
+typedef unsigned int seq_u2_t __attribute__((ext_vector_type(2)));
+
+// An fp32 number as the sum of three bf16 numbers: 8 + 8 + 8 significant bits hold the 24 of an fp32 exactly, so a product
+// of two such sums loses only the terms mid * lo, lo * mid and lo * lo, about 2^-26 of the product and of either sign
+// (round to nearest at every cut), which is below the rounding of the fp32 accumulator.  Two numbers at a time,
+// packed as the low and the high half of each word.
+__device__ __forceinline__ void seq_split2(float a, float b, uint32_t (&p)[3]) {
+#pragma clang fp contract(off)   // the pieces are those of the rounded number, however it was computed
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const seq_f2_t v = {a, b};
+        p[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, seq_b2_t));
+        if (k < 2) { a -= __uint_as_float(p[k] << 16); b -= __uint_as_float(p[k] & 0xffff0000u); }
     }
-    const int unit = r >> 2, gate = r & 3, src_row = gate * hidden + unit;
-    float v = 0.f;
-    if (k < d) v = w_ih[(size_t)src_row * d + k];
-    else if (k < d + hidden) v = w_hh[(size_t)src_row * hidden + (k - d)];
-    wp[i] = v;
-    if (k == 0) bp[r] = b[src_row];                        // (every row has exactly one element with k == 0 in either order)
+}
+
+// Weights in the forms the kernels read, from the usual layout (w_ih [4H, D], w_hh [4H, H], b [4H], gate-major rows: input,
+// forget, cell, output gate):
+//   wx: W_ih for the product over input rows, fp32, [gate tile][dp / 8 groups of four k-steps][lane][4]; lane l supplies
+//       column l % 32 of the tile (gate row tile * 32 + l % 32 in (unit, gate) order) and k = 2 * step + l / 32;
+//   wq: W_hh for the recurrent product, three bf16 pieces, [gate tile][ks steps of 16][piece][lane][8]; lane l supplies row
+//       l % 32 of the tile, k = 16 * step + 8 * (l / 32) + 0..7.  Row 8 m + 4 p + gate of a tile is that gate of hidden unit
+//       8 * tile + 4 p + m, so that lane l of the product ends up with all gates of four CONSECUTIVE units;
+//   bp: the bias in (unit, gate) order.
+// The "state is written" counters of the pass start at zero.
+__global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
+                                                      const float *__restrict__ b, float *__restrict__ wx,
+                                                      uint16_t *__restrict__ wq, float *__restrict__ bp, int d, int dp,
+                                                      int hidden, int ks, int32_t *__restrict__ flags, int64_t n_flags) {
+    const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
+    for (int64_t f = first; f < n_flags; f += stride) flags[f] = 0;
+    for (int64_t i = first; i < (int64_t)4 * hidden; i += stride) bp[i] = b[(i & 3) * hidden + (i >> 2)];
+    for (int64_t i = first; i < (int64_t)4 * hidden * dp; i += stride) {
+        const int per_tile = 32 * dp, tile = (int)(i / per_tile), rest = (int)(i % per_tile);
+        const int q = rest / 256, lane = (rest % 256) / 4, step = 4 * q + (rest & 3);
+        const int r = tile * 32 + (lane & 31), k = 2 * step + (lane >> 5);
+        wx[i] = k < d ? w_ih[(size_t)((r & 3) * hidden + (r >> 2)) * d + k] : 0.f;
+    }
+    for (int64_t i = first; i < (int64_t)(hidden / 8) * ks * 512; i += stride) {
+        const int tile = (int)(i / (ks * 512)), step = (int)(i / 512) % ks, lane = (int)(i % 512) / 8;
+        const int row = lane & 31, unit = tile * 8 + ((row >> 2) & 1) * 4 + (row >> 3), gate = row & 3;
+        const int k = 16 * step + 8 * (lane >> 5) + (int)(i & 7);
+        float v = k < hidden ? w_hh[(size_t)(gate * hidden + unit) * hidden + k] : 0.f;
+        uint32_t p[3];
+        seq_split2(v, 0.f, p);
+        if ((p[0] & 0x7fffu) == 0x7f80u && fabsf(v) < INFINITY) {   // rounded up past the largest bf16: cut the first piece instead
+            p[0] = __float_as_uint(v) >> 16;
+            uint32_t rest[3];
+            seq_split2(v - __uint_as_float(p[0] << 16), 0.f, rest);
+            p[1] = rest[0]; p[2] = rest[1];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) wq[((int64_t)(tile * ks + step) * 3 + c) * 512 + (i % 512)] = (uint16_t)(p[c] & 0xffffu);
+    }
+}
+
+// The input half of the gates, once per node that occurs in a list instead of once per cell that reads it:
+//     gx[i] = b + W_ih x[used[i]]   ([n_used, 4H], (unit, gate) order),
+// 64 nodes per workgroup against all gate rows, fp32 matrix-core products, nodes as rows so that a store instruction writes
+// 128 contiguous bytes of two rows.  On the lists of the benchmark every row serves 6 to 16 cells; the sums start from the
+// bias and take the columns in order, as a product over (x, h) in one piece would.
+__global__ __launch_bounds__(256) void seq_input_gates_kernel(const float *__restrict__ x, const int32_t *__restrict__ used, int64_t n_used,
+                                                             const float *__restrict__ wx, const float *__restrict__ bp,
+                                                             float *__restrict__ gx, int d, int dp, int hidden) {
+    extern __shared__ float xs[];                          // [64][dp + 2]: rows 2 banks apart
+    const int zs = dp + 2, n_tiles = hidden / 8, rows4 = 4 * hidden;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t blocks = (n_used + 63) / 64;
+    for (int64_t bt = blockIdx.x; bt < blocks; bt += gridDim.x) {
+        {
+            const int row = threadIdx.x >> 2;
+            const int64_t at = bt * 64 + row;
+            const int u = at < n_used ? used[at] : -1;
+            for (int k = (threadIdx.x & 3) * 4; k < dp; k += 16) {
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (u >= 0 && k < d) v = *reinterpret_cast<const float4 *>(x + (size_t)u * d + k);
+                *reinterpret_cast<float2 *>(&xs[row * zs + k]) = make_float2(v.x, v.y);
+                *reinterpret_cast<float2 *>(&xs[row * zs + k + 2]) = make_float2(v.z, v.w);
+            }
+        }
+        __syncthreads();
+        for (int tile = wave; tile < n_tiles; tile += 4) {
+            const float bias = bp[tile * 32 + (lane & 31)];
+            seq_acc_t acc[2];
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[g][r] = bias;
+            const float4 *wq = reinterpret_cast<const float4 *>(wx) + (size_t)tile * (dp / 8) * 64 + lane;
+            const float *xl = &xs[(lane & 31) * zs + (lane >> 5)];
+            float4 wa = wq[0];
+            for (int q = 0; q < dp / 8; ++q) {
+                const float4 wn = wq[(q + 1 < dp / 8 ? q + 1 : q) * 64];
+                const float w4[4] = {wa.x, wa.y, wa.z, wa.w};
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int g = 0; g < 2; ++g)
+                        acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(xl[g * 32 * zs + 2 * (4 * q + r)], w4[r], acc[g], 0, 0, 0);
+                wa = wn;
+            }
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t at = bt * 64 + g * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
+                    if (at < n_used) gx[(size_t)at * rows4 + tile * 32 + (lane & 31)] = acc[g][r];
+                }
+        }
+        __syncthreads();
+    }
 }
 
 // Gate functions on the hardware's exp2 and reciprocal: absolute error of a few 1e-7 on outputs in (0, 1) and
@@ -101,22 +190,21 @@ __device__ __forceinline__ float seq_tanh(float z) {
     return copysignf((1.f - e) * __builtin_amdgcn_rcpf(1.f + e), z);
 }
 
-typedef float seq_acc_t __attribute__((ext_vector_type(16)));
-
 struct SeqChainArgs {
     const int32_t *chains;   // paths, 4 per path, in tiles of 64 (padded with empty paths), longest first within a level
     int64_t n_path_tiles;
-    int32_t *flags;          // per state row: set once the row is written (NULL: every start state was written by an earlier launch)
+    int32_t *flags;          // per state row: the wavefronts that have written their part of it (NULL: every start state was written by an earlier launch)
     int32_t *gave_up;        // set by a wait that gives up
     int32_t spin_limit;      // polls of a flag before giving up
     int32_t publish;         // 0 in a test of the time-out: no flag is ever set
-    const int32_t *step_x;   // per step: input row
+    const int32_t *step_g;   // per step: row of gx
     const int32_t *step_out; // per step: state row to write, or -1
-    const float *x, *wp, *bp;
+    const float *gx;         // the input half of the gates, [n_used, 4H] in (unit, gate) order
+    const uint16_t *wq;      // W_hh in bf16 pieces, see seq_pack_kernel
     float *h, *c;            // [n_states, H]: read where a path starts (written by a lower level), written where a step says so
     float *a_out;            // [n, H]
     float *tape_g, *tape_c, *tape_h;   // training: per step the activated gates [H][4], the new c [H] and the new h [H] (NULL: inference)
-    int32_t d, hidden;
+    int32_t hidden;
 };
 
 // State rows that another workgroup of the same launch reads, possibly on another XCD: device-scope accesses,
@@ -138,60 +226,64 @@ __device__ __forceinline__ void seq_st4_device(float *p, float4 v) {
 // instead of being held in a register across the products.
 __device__ __forceinline__ int seq_opaque(int v) { asm volatile("" : "+v"(v)); return v; }
 
-// One level of paths.  A workgroup of 8 wavefronts takes tiles of 64 paths and walks ALL their steps:
-// the running states never leave the compute unit (h in the staged operand rows, c beside them in LDS),
-// so a step costs one input row of global traffic, plus the two state rows where something else needs
-// them.  Paths are sorted by length, so the paths of a tile end within a step or two of each other; a
-// path that has ended keeps its state while the others finish.  KSTEPS = KP / 2 matrix-core steps per
-// 32 x 32 product.  WIDE (hidden > 32, up to 8 gate tiles of 8 hidden units): wavefront w holds gate
-// tile w and multiplies it with both halves of the path tile; otherwise (up to 4 gate tiles) wavefront w
-// holds gate tile w % 4 and takes the half w / 4 of the path tile.  Either way a wavefront keeps one gate
-// tile of Wp in registers (64 of the 128 it may use at four wavefronts per SIMD, 32 more for the
-// accumulators), so the staging and element-wise phases of one workgroup hide behind the products of the other.
+// Paths of one level, or of all.  A workgroup takes tiles of 64 paths and walks ALL their steps; the running states never leave
+// the compute unit: c in registers, h in LDS as the operand of the next step's product.  A step reads one row of gx per path
+// (the accumulators start from it), multiplies W_hh with the 64 h rows, runs the element-wise part on the result in
+// registers and writes the new h to the other of two LDS buffers, so that a step has one barrier.  Paths are sorted by length, so
+// the paths of a tile end within a step or two of each other; a path that has ended keeps quiet while the others finish.
 //
-// BIG (hidden up to 128, D + H up to 256): 16 wavefronts, wavefront w takes gate tile w and both halves of the
-// path tile; Wp no longer fits the registers of a compute unit, so every wavefront streams its gate tile,
-// stored in the order the matrix instructions consume it, from the L2 cache once per step (16-byte loads, one
-// group of four k-steps ahead): 4H (D + H) * 4 bytes per 64 cells, against 2 * 4H (D + H) * 64 flops.
-template <int KSTEPS, bool WIDE, bool BIG, bool TAPE>
-__global__ __launch_bounds__(BIG ? 1024 : 512, (TAPE && !BIG) ? 2 : 4) void seq_chain_kernel(SeqChainArgs A) {
-    static_assert(!BIG || WIDE, "the streamed variant uses the wide tiling");
-    constexpr int KP = 2 * KSTEPS, ZS = KP + 2;
-    constexpr int HMAX = BIG ? 128 : (WIDE ? 64 : 32);
-    constexpr int HS = HMAX + 1, JG = WIDE ? 2 : 1;
-    constexpr int TPP = BIG ? 16 : 8;                      // threads per path in the staging phases
-    __shared__ float z[kSeqJobs * ZS];
-    __shared__ float cs[kSeqJobs * HS];
-    __shared__ __align__(16) float sb[4 * (BIG ? 128 : 64)];
+// The product runs in bf16 pieces (seq_split2): six v_mfma_f32_32x32x16_bf16 per 16 columns cost 192 cycles against 512 for
+// fp32 ones.
+// Measured (370 k nodes, hidden = d = 64, prefix HAG with 3.35 M cells): 0.85 ms + 0.06 ms for gx, against 1.9 ms with fp32
+// products over (x, h) in every cell; what is left is the element-wise part and the gx rows.
+// A gate tile is 32 gate rows = 8 hidden units; lane l of the product holds, for path l % 32 of its half of the tile, the four
+// gates of units 8 * tile + 4 * (l / 32) + 0..3.
+//   HMAX 64 (hidden 33..64): 8 wavefronts, wavefront w holds gate tile w in registers and takes both halves of the paths;
+//   HMAX 32: wavefront w holds gate tile w % 4 and takes half w / 4;
+//   HMAX 128: 16 wavefronts, wavefront w streams gate tile w (3 KB per 16 columns) from the L2 cache once per step for both
+//   halves: the pieces of a whole tile would be 96 of the 128 registers there are at four wavefronts per SIMD.
+template <int HMAX, bool TAPE>
+__global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(SeqChainArgs A) {
+    constexpr bool BIG = HMAX == 128, WIDE = HMAX >= 64, C_LDS = HMAX == 64;
+    constexpr int KS = HMAX / 16, ZS = HMAX + 8, JG = WIDE ? 2 : 1;
+    __shared__ __align__(16) uint16_t z[2][3][kSeqJobs][ZS];   // h of every path in bf16 pieces: this step's and the next step's
+    // c: in registers, except where those are too short (rows 4 banks apart: conflict-free 16-byte accesses)
+    __shared__ __align__(16) float cs[C_LDS ? kSeqJobs : 1][HMAX + 4];
     __shared__ int32_t sdesc[kSeqJobs * 4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int hidden = A.hidden, d = A.d, n_tiles = hidden / 8;
+    __shared__ int32_t spend[2][kSeqJobs];                 // per path: the state row that a step wrote, to be announced a step later
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+    const int hidden = A.hidden, n_tiles = hidden / 8, ks = BIG ? (hidden + 15) / 16 : KS;
     const int tile = WIDE ? wave : (wave & 3), group0 = WIDE ? 0 : (wave >> 2);
-    float wreg[BIG ? 1 : KSTEPS];
+    const bool on = tile < n_tiles;                        // wavefronts beyond the hidden size only keep the barriers
+    seq_b8_t wreg[BIG ? 1 : KS][3];
+    const seq_b8_t *wl = reinterpret_cast<const seq_b8_t *>(A.wq) + (size_t)tile * ks * 3 * 64 + lane;
     if constexpr (!BIG) {
+        if (on) {
 #pragma unroll
-        for (int s = 0; s < KSTEPS; ++s)
-            wreg[s] = tile < n_tiles ? A.wp[(size_t)(tile * 32 + (lane & 31)) * KP + 2 * s + (lane >> 5)] : 0.f;
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) wreg[s][p] = wl[(s * 3 + p) * 64];
+        }
     }
-    if ((int)threadIdx.x < 4 * hidden) sb[threadIdx.x] = A.bp[threadIdx.x];
-    constexpr int ZV = KP / (4 * TPP);
+    // columns from `hidden` on stay zero in both buffers
+    for (int i = threadIdx.x; i < (int)(sizeof(z) / 4); i += blockDim.x) reinterpret_cast<uint32_t *>(&z[0][0][0][0])[i] = 0;
     for (int64_t ct = blockIdx.x; ct < A.n_path_tiles; ct += gridDim.x) {
         {
-            const int tid0 = seq_opaque(threadIdx.x);
-            if (tid0 < kSeqJobs * 4) sdesc[tid0] = A.chains[ct * (kSeqJobs * 4) + tid0];
+            const int tid = seq_opaque(threadIdx.x);
+            if (tid < kSeqJobs * 4) sdesc[tid] = A.chains[ct * (kSeqJobs * 4) + tid];
         }
         __syncthreads();
         if (A.flags) {
             // All levels in one launch: wait until the states this tile's paths start from are written.  They
             // belong to tiles with a smaller index, which this or another resident workgroup finishes without
             // waiting for this one, so the wait ends; it is bounded all the same, and a time-out is recorded.
-            const int tid0 = seq_opaque(threadIdx.x);
-            if (tid0 < kSeqJobs) {
-                const int start = sdesc[tid0 * 4];
+            const int tid = seq_opaque(threadIdx.x);
+            if (tid < kSeqJobs) {
+                const int start = sdesc[tid * 4];
                 if (start >= 0) {
                     bool ready = false;
                     for (int spin = 0; spin < A.spin_limit; ++spin) {
-                        if (__hip_atomic_load(A.flags + start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) { ready = true; break; }
+                        if (__hip_atomic_load(A.flags + start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= n_tiles) { ready = true; break; }
                         // once any wait of the pass has given up its output is void: the others do not sit theirs out
                         if (__hip_atomic_load(A.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
                         __builtin_amdgcn_s_sleep(16);
@@ -204,168 +296,169 @@ __global__ __launch_bounds__(BIG ? 1024 : 512, (TAPE && !BIG) ? 2 : 4) void seq_
             // cache is invalidated here; the fence keeps those loads behind the polls
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         }
-        // (thread indices are derived again in every phase, and the descriptor is re-read from LDS where it is needed rather than held in registers, which are short)
         const int steps = sdesc[2];                        // the tile's first path is its longest
-        // the state the path starts from, the first input row, zero padding
-        {
-            const int tid = seq_opaque(threadIdx.x), sj = tid / TPP, part = tid % TPP;
-            const int start = sdesc[sj * 4], beg = sdesc[sj * 4 + 1], len = sdesc[sj * 4 + 2];
-            const int row0 = len > 0 ? A.step_x[beg] : -1;
-#pragma unroll 1                                           // (one vector in flight: this runs once per tile, and registers are short)
-            for (int i = 0; i < ZV; ++i) {
-                const int k = part * 4 + 4 * TPP * i;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (k < d) { if (row0 >= 0) v = *reinterpret_cast<const float4 *>(A.x + (size_t)row0 * d + k); }
-                else if (k < d + hidden && start >= 0)
-                    v = A.flags ? seq_ld4_device(A.h + (size_t)start * hidden + (k - d)) : *reinterpret_cast<const float4 *>(A.h + (size_t)start * hidden + (k - d));
-                *reinterpret_cast<float2 *>(&z[sj * ZS + k]) = make_float2(v.x, v.y);
-                *reinterpret_cast<float2 *>(&z[sj * ZS + k + 2]) = make_float2(v.z, v.w);
-            }
-            for (int u = part * 4; u < hidden; u += 4 * TPP) {
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (start >= 0) v = A.flags ? seq_ld4_device(A.c + (size_t)start * hidden + u) : *reinterpret_cast<const float4 *>(A.c + (size_t)start * hidden + u);
-                cs[sj * HS + u] = v.x; cs[sj * HS + u + 1] = v.y; cs[sj * HS + u + 2] = v.z; cs[sj * HS + u + 3] = v.w;
-            }
-        }
-        __syncthreads();
-        for (int t = 0; t < steps; ++t) {
-            // the next step's input row is requested before this step's products and lands in LDS after them
-            // (its first 64 columns, that is: holding more across the products would spill registers)
-            constexpr int ZE = ZV < 2 ? ZV : 2;
-            float4 xr[ZE];
-            const int tid = seq_opaque(threadIdx.x), sj = tid / TPP, part = tid % TPP;
-            const int len = sdesc[sj * 4 + 2], at = sdesc[sj * 4 + 1] + t;
-            const int row1 = t + 1 < len ? A.step_x[at + 1] : -1;
-#pragma unroll
-            for (int i = 0; i < ZE; ++i) {
-                const int k = part * 4 + 4 * TPP * i;
-                xr[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (k < d && row1 >= 0) xr[i] = *reinterpret_cast<const float4 *>(A.x + (size_t)row1 * d + k);
-            }
-            seq_acc_t acc[JG];
+        int row[JG], keep[JG];                             // (begin and length are read from LDS where they are needed: registers are short)
+        float4 creg[C_LDS ? 1 : JG];
+        seq_acc_t acc[JG];
+        auto load_gates = [&](int g, int unit0) {          // the accumulators of the next step start from this row of gx
+            const float *p = A.gx + (size_t)row[g] * (4 * hidden) + unit0 * 4;
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                const float4 bias = tile < n_tiles ? *reinterpret_cast<const float4 *>(&sb[(tile * 8 + 2 * m + (lane >> 5)) * 4])
-                                                   : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                for (int g = 0; g < JG; ++g) { acc[g][4 * m] = bias.x; acc[g][4 * m + 1] = bias.y; acc[g][4 * m + 2] = bias.z; acc[g][4 * m + 3] = bias.w; }
+                const float4 v = *reinterpret_cast<const float4 *>(p + 4 * m);
+                acc[g][4 * m] = v.x; acc[g][4 * m + 1] = v.y; acc[g][4 * m + 2] = v.z; acc[g][4 * m + 3] = v.w;
             }
-            const float *zl = &z[(group0 * 32 + (lane & 31)) * ZS + (lane >> 5)];
-            if constexpr (!BIG) {
+        };
+        auto put_h = [&](int buf, int j, int unit0, const float (&h)[4]) {
+            uint32_t a[3], b[3];
+            seq_split2(h[0], h[1], a);
+            seq_split2(h[2], h[3], b);
 #pragma unroll
-                for (int s = 0; s < KSTEPS; ++s) {
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2 *>(&z[buf][p][j][unit0]) = make_uint2(a[p], b[p]);
+        };
 #pragma unroll
-                    for (int g = 0; g < JG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(wreg[s], zl[g * 32 * ZS + 2 * s], acc[g], 0, 0, 0);
+        for (int g = 0; g < JG; ++g) {
+            const int l = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (l >> 5) * 4, j = (group0 + g) * 32 + (l & 31), start = sdesc[j * 4];
+            const int beg = sdesc[j * 4 + 1], len = on ? sdesc[j * 4 + 2] : 0;
+            row[g] = 0; keep[g] = -1;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[g][r] = 0.f;
+            if (len > 0) {
+                row[g] = A.step_g[beg];
+                keep[g] = A.step_out[beg];
+                float h[4] = {0.f, 0.f, 0.f, 0.f};
+                float4 cv = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (start >= 0) {
+                    const size_t o = (size_t)start * hidden + unit0;
+                    const float4 hv = A.flags ? seq_ld4_device(A.h + o) : *reinterpret_cast<const float4 *>(A.h + o);
+                    cv = A.flags ? seq_ld4_device(A.c + o) : *reinterpret_cast<const float4 *>(A.c + o);
+                    h[0] = hv.x; h[1] = hv.y; h[2] = hv.z; h[3] = hv.w;
                 }
-            } else if (tile < n_tiles) {                   // (a wavefront without a gate tile has nothing to stream)
-                const float4 *wq = reinterpret_cast<const float4 *>(A.wp) + (size_t)tile * (KSTEPS / 4) * 64 + lane;
-                float4 wa = wq[0];
-                constexpr int UNR = KSTEPS == 96 ? 12 : 16;   // a divisor of the trip count: how far the loads run ahead within the registers there are
-#pragma unroll UNR
-                for (int q = 0; q < KSTEPS / 4; ++q) {
-                    const float4 wn = wq[(q + 1 < KSTEPS / 4 ? q + 1 : q) * 64];
-                    const float w4[4] = {wa.x, wa.y, wa.z, wa.w};
+                if constexpr (C_LDS) *reinterpret_cast<float4 *>(&cs[j][unit0]) = cv;
+                else creg[g] = cv;
+                put_h(0, j, unit0, h);
+                load_gates(g, unit0);
+                if (len > 1) row[g] = A.step_g[beg + 1];
+            }
+        }
+        {
+            const int tid = seq_opaque(threadIdx.x);
+            if (tid < 2 * kSeqJobs) (&spend[0][0])[tid] = -1;
+        }
+        __syncthreads();
+        // counts this wavefront off for the states it wrote a step ago: their stores are older than the rows of gx that the
+        // product just used, so they have long completed
+        auto publish = [&](int par) {
+            if (!A.flags) return;
+            int pend[JG];
+            bool any = false;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
+            for (int g = 0; g < JG; ++g) { pend[g] = spend[par][(group0 + g) * 32 + (lane & 31)]; any |= pend[g] >= 0; }
+            if (!__any(any)) return;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-                        for (int g = 0; g < JG; ++g)
-                            acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(w4[r], zl[g * 32 * ZS + 2 * (4 * q + r)], acc[g], 0, 0, 0);
+            for (int g = 0; g < JG; ++g)
+                if (pend[g] >= 0 && half == 0 && A.publish) __hip_atomic_fetch_add(A.flags + pend[g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        auto product = [&](int cur, int g, seq_acc_t &a, const seq_b8_t (&w)[3], int s) {
+            seq_b8_t zb[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                zb[p] = *reinterpret_cast<const seq_b8_t *>(&z[cur][p][(group0 + g) * 32 + (lane & 31)][16 * s + 8 * half]);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[2], zb[0], a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], zb[2], a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[1], zb[1], a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[1], zb[0], a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], zb[1], a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], zb[0], a, 0, 0, 0);
+        };
+        for (int t = 0; t < steps; ++t) {
+            const int cur = t & 1;
+            if (on) {
+                if constexpr (BIG) {
+                    seq_b8_t wa[3], wn[3];
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) wa[p] = wl[p * 64];
+                    for (int s = 0; s < ks; ++s) {
+                        const int sn = s + 1 < ks ? s + 1 : s;
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) wn[p] = wl[(sn * 3 + p) * 64];
+#pragma unroll
+                        for (int g = 0; g < JG; ++g) product(cur, g, acc[g], wa, s);
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) wa[p] = wn[p];
                     }
-                    wa = wn;
                 }
-            }
-            __syncthreads();                               // every product has read z
-            // the state row this step writes, if any: asked for now, used after the next barrier
-            int keep = -1;
-            {
-                const int tid1 = seq_opaque(threadIdx.x), sj1 = tid1 / TPP;
-                if (t < sdesc[sj1 * 4 + 2]) keep = A.step_out[sdesc[sj1 * 4 + 1] + t];
-            }
-            // element-wise part: lane l holds, for path l % 32 of its half, gate rows 8 * (r / 4) + 4 * (l / 32) + r % 4 of the
-            // gate tile, i.e. the four gates (r % 4) of hidden units 2 * (r / 4) + l / 32 of the tile; the new h goes straight
-            // into the operand rows of the next step
-            if (tile < n_tiles) {
 #pragma unroll
                 for (int g = 0; g < JG; ++g) {
-                    const int j = (group0 + g) * 32 + (lane & 31);
-                    if (t < sdesc[j * 4 + 2]) {
+                    if constexpr (!BIG) {
+#pragma unroll
+                        for (int s = 0; s < KS; ++s) product(cur, g, acc[g], wreg[s], s);
+                    }
+                    if (g == 0) publish(cur ^ 1);
+                    const int l = seq_opaque(threadIdx.x) & 63, half = l >> 5, unit0 = tile * 8 + half * 4, j = (group0 + g) * 32 + (l & 31);
+                    const int beg = sdesc[j * 4 + 1], len = sdesc[j * 4 + 2];
+                    if (A.flags && half == 0) spend[cur][j] = t < len ? keep[g] : -1;
+                    if (t < len) {
+                        float4 cv;
+                        if constexpr (C_LDS) cv = *reinterpret_cast<const float4 *>(&cs[j][unit0]);
+                        else cv = creg[g];
+                        float h[4], c[4] = {cv.x, cv.y, cv.z, cv.w};
 #pragma unroll
                         for (int m = 0; m < 4; ++m) {
-                            const int unit = tile * 8 + 2 * m + (lane >> 5);
-                            const float c_new = seq_sigmoid(acc[g][4 * m + 1]) * cs[j * HS + unit] +
-                                                seq_sigmoid(acc[g][4 * m + 0]) * seq_tanh(acc[g][4 * m + 2]);
-                            cs[j * HS + unit] = c_new;
-                            if constexpr (TAPE) {
-                                // what the backward pass needs of this cell, indexed by the step
-                                const float gi = seq_sigmoid(acc[g][4 * m + 0]), gf = seq_sigmoid(acc[g][4 * m + 1]);
-                                const float gg = seq_tanh(acc[g][4 * m + 2]), go = seq_sigmoid(acc[g][4 * m + 3]);
-                                const float h_new = go * seq_tanh(c_new);
-                                const size_t cell = (size_t)(sdesc[j * 4 + 1] + t) * hidden + unit;
-                                *reinterpret_cast<float4 *>(A.tape_g + cell * 4) = make_float4(gi, gf, gg, go);
-                                z[j * ZS + d + unit] = h_new;              // (c and h go to the tape as whole rows, below)
-                                continue;
-                            }
-                            z[j * ZS + d + unit] = seq_sigmoid(acc[g][4 * m + 3]) * seq_tanh(c_new);
+                            const float gi = seq_sigmoid(acc[g][4 * m]), gf = seq_sigmoid(acc[g][4 * m + 1]);
+                            const float gg = seq_tanh(acc[g][4 * m + 2]), go = seq_sigmoid(acc[g][4 * m + 3]);
+                            c[m] = fmaf(gf, c[m], gi * gg);             // (spelled out: one rounding, the same in every copy of this code)
+                            h[m] = go * seq_tanh(c[m]);
+                            if constexpr (TAPE) { acc[g][4 * m] = gi; acc[g][4 * m + 1] = gf; acc[g][4 * m + 2] = gg; acc[g][4 * m + 3] = go; }
                         }
-                    }
-                }
-            }
-            {
-                const int tid2 = seq_opaque(threadIdx.x), sj2 = tid2 / TPP, part2 = tid2 % TPP;
-                if (row1 >= 0) {
+                        put_h(cur ^ 1, j, unit0, h);
+                        const float4 h4 = make_float4(h[0], h[1], h[2], h[3]), c4 = make_float4(c[0], c[1], c[2], c[3]);
+                        if constexpr (C_LDS) *reinterpret_cast<float4 *>(&cs[j][unit0]) = c4;
+                        else creg[g] = c4;
+                        if constexpr (TAPE) {
+                            // what the backward pass needs of this cell, indexed by the step.  Lanes l and l + 32 (the same path) swap
+                            // half of their units, so that together they write 32 contiguous bytes of the gates per store.
+                            const size_t cell = (size_t)(beg + t) * hidden;
 #pragma unroll
-                    for (int i = 0; i < ZV; ++i) {
-                        const int k = part2 * 4 + 4 * TPP * i;
-                        if (k < d) {
-                            const float4 v = i < ZE ? xr[i < ZE ? i : 0] : *reinterpret_cast<const float4 *>(A.x + (size_t)row1 * d + k);
-                            *reinterpret_cast<float2 *>(&z[sj2 * ZS + k]) = make_float2(v.x, v.y);
-                            *reinterpret_cast<float2 *>(&z[sj2 * ZS + k + 2]) = make_float2(v.z, v.w);
+                            for (int q = 0; q < 2; ++q) {
+                                float lo[4], hi[4];
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    const seq_u2_t v = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[g][8 * q + e]), __float_as_uint(acc[g][8 * q + 4 + e]), false, false);
+                                    lo[e] = __uint_as_float(v.x); hi[e] = __uint_as_float(v.y);
+                                }
+                                float *p = A.tape_g + (cell + tile * 8 + 2 * q + half) * 4;
+                                *reinterpret_cast<float4 *>(p) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+                                *reinterpret_cast<float4 *>(p + 16) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+                            }
+                            *reinterpret_cast<float4 *>(A.tape_h + cell + unit0) = h4;
+                            *reinterpret_cast<float4 *>(A.tape_c + cell + unit0) = c4;
+                        }
+                        if (keep[g] >= 0) {                // a state that another path starts from, or some a_v
+                            const size_t o = (size_t)keep[g] * hidden + unit0;
+                            if (A.flags) {
+                                seq_st4_device(A.h + o, h4);
+                                seq_st4_device(A.c + o, c4);
+                            } else {
+                                *reinterpret_cast<float4 *>(A.h + o) = h4;
+                                *reinterpret_cast<float4 *>(A.c + o) = c4;
+                            }
+                        }
+                        if (t + 1 == len) {
+                            // a_v = the last h of the path, where the path ends a node's list
+                            const int node = sdesc[j * 4 + 3];
+                            if (node >= 0) *reinterpret_cast<float4 *>(A.a_out + (size_t)node * hidden + unit0) = h4;
+                        } else {
+                            keep[g] = A.step_out[beg + t + 1];
+                            load_gates(g, unit0);
+                            if (t + 2 < len) row[g] = A.step_g[beg + t + 2];
                         }
                     }
                 }
             }
-            __syncthreads();                               // the operand rows and cell states of the next step are complete
-            if constexpr (TAPE) {
-                // the step's c and h rows of the tape, from LDS: whole rows, a few lines per path instead of one request per element
-                const int tid4 = seq_opaque(threadIdx.x), sj4 = tid4 / TPP, part4 = tid4 % TPP;
-                if (t < sdesc[sj4 * 4 + 2]) {
-                    const size_t row = (size_t)(sdesc[sj4 * 4 + 1] + t) * hidden;
-                    for (int u = part4 * 4; u < hidden; u += 4 * TPP) {
-                        const float *ph = &z[sj4 * ZS + d + u], *pc = &cs[sj4 * HS + u];
-                        *reinterpret_cast<float4 *>(A.tape_h + row + u) = make_float4(ph[0], ph[1], ph[2], ph[3]);
-                        *reinterpret_cast<float4 *>(A.tape_c + row + u) = make_float4(pc[0], pc[1], pc[2], pc[3]);
-                    }
-                }
-            }
-            if (keep >= 0) {                               // a state that another path starts from, or some a_v
-                const int tid3 = seq_opaque(threadIdx.x), sj3 = tid3 / TPP, part3 = tid3 % TPP;
-                for (int u = part3 * 4; u < hidden; u += 4 * TPP) {
-                    const float *ph = &z[sj3 * ZS + d + u], *pc = &cs[sj3 * HS + u];
-                    if (A.flags) {
-                        seq_st4_device(A.h + (size_t)keep * hidden + u, make_float4(ph[0], ph[1], ph[2], ph[3]));
-                        seq_st4_device(A.c + (size_t)keep * hidden + u, make_float4(pc[0], pc[1], pc[2], pc[3]));
-                    } else {
-                        *reinterpret_cast<float4 *>(A.h + (size_t)keep * hidden + u) = make_float4(ph[0], ph[1], ph[2], ph[3]);
-                        *reinterpret_cast<float4 *>(A.c + (size_t)keep * hidden + u) = make_float4(pc[0], pc[1], pc[2], pc[3]);
-                    }
-                }
-                if (A.flags) {
-                    // the threads of a path are adjacent lanes of one wavefront: once the wavefront has seen its stores complete,
-                    // the whole row is out, and one of them sets the state's flag
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                    if (A.publish && part3 == 0) __hip_atomic_store(A.flags + keep, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
+            __syncthreads();                               // the h rows of the next step are complete, this step's have been read
         }
-        // a_v = the last h of the path, where the path ends a node's list
-        const int tid = seq_opaque(threadIdx.x), sj = tid / TPP, part = tid % TPP;
-        const int node = sdesc[sj * 4 + 3];
-        if (node >= 0) {
-            for (int u = part * 4; u < hidden; u += 4 * TPP) {
-                const float *ph = &z[sj * ZS + d + u];
-                *reinterpret_cast<float4 *>(A.a_out + (size_t)node * hidden + u) = make_float4(ph[0], ph[1], ph[2], ph[3]);
-            }
-        }
+        if (on) publish((steps - 1) & 1);
         __syncthreads();
     }
 }
@@ -905,6 +998,11 @@ int hag_seq_create(int64_t n, const int64_t *rowptr, const int32_t *col, int64_t
             for (int64_t a2 = 0; a2 < cells; ++a2) ++h->xt_ptr[(size_t)h->step_x[a2] + 1];
             for (int64_t u = 0; u < n; ++u) h->xt_ptr[(size_t)u + 1] += h->xt_ptr[u];
             h->xt_idx.resize((size_t)cells);
+            std::vector<int32_t> place((size_t)n, 0);
+            for (int64_t u = 0; u < n; ++u)
+                if (h->xt_ptr[(size_t)u + 1] > h->xt_ptr[u]) { place[u] = (int32_t)h->used.size(); h->used.push_back((int32_t)u); }
+            h->step_g.resize((size_t)cells);
+            for (int64_t a2 = 0; a2 < cells; ++a2) h->step_g[a2] = place[h->step_x[a2]];
             std::vector<int32_t> at(h->xt_ptr.begin(), h->xt_ptr.end() - 1);
             for (int64_t a2 = 0; a2 < cells; ++a2) h->xt_idx[(size_t)at[h->step_x[a2]]++] = (int32_t)a2;
         }
@@ -925,6 +1023,8 @@ void hag_seq_free(hag_seq_t *h) {
     if (h->d_paths) (void)hipFree(h->d_paths);
     if (h->d_paths_by_depth) (void)hipFree(h->d_paths_by_depth);
     if (h->d_step_prev) (void)hipFree(h->d_step_prev);
+    if (h->d_used) (void)hipFree(h->d_used);
+    if (h->d_step_g) (void)hipFree(h->d_step_g);
     if (h->d_xt_ptr) (void)hipFree(h->d_xt_ptr);
     if (h->d_xt_idx) (void)hipFree(h->d_xt_idx);
     if (h->d_pending_init) (void)hipFree(h->d_pending_init);
@@ -943,23 +1043,20 @@ int64_t hag_seq_launches(const hag_seq_t *h) {
 }
 int64_t hag_seq_merges(const hag_seq_t *h) { return h ? h->n_merges : 0; }
 
-// Padded D + H, which also names the kernel variant: 64 and 128 hold Wp in registers (hidden <= 64), 192 and 256 stream it.
+// Forward kernel variants: hidden up to 32, 64, 128.
+static int seq_variant(int64_t hidden) { return hidden <= 32 ? 0 : hidden <= 64 ? 1 : 2; }
+typedef void (*seq_kernel_t)(SeqChainArgs);
+static const seq_kernel_t kSeqVariants[3] = {seq_chain_kernel<32, false>, seq_chain_kernel<64, false>, seq_chain_kernel<128, false>};
+// the same with the tape written (training)
+static const seq_kernel_t kSeqTapeVariants[3] = {seq_chain_kernel<32, true>, seq_chain_kernel<64, true>, seq_chain_kernel<128, true>};
+static unsigned seq_block(int variant) { return variant == 2 ? 1024 : 512; }
+// D + H padded to the column tiles of the backward kernels
 static int64_t seq_kp(int64_t d, int64_t hidden) {
     if (hidden <= 64 && d + hidden <= 128) return d + hidden <= 64 ? 64 : 128;
     return d + hidden <= 192 ? 192 : 256;
 }
-// Index into hag_seq::resident / the variant table below.
-static int seq_variant(int64_t kp, int64_t hidden) { return kp > 128 ? (kp == 192 ? 4 : 5) : (kp == 64 ? 0 : 2) + (hidden > 32 ? 1 : 0); }
-typedef void (*seq_kernel_t)(SeqChainArgs);
-static const seq_kernel_t kSeqVariants[6] = {seq_chain_kernel<32, false, false, false>, seq_chain_kernel<32, true, false, false>,
-                                             seq_chain_kernel<64, false, false, false>, seq_chain_kernel<64, true, false, false>,
-                                             seq_chain_kernel<96, true, true, false>,   seq_chain_kernel<128, true, true, false>};
 typedef void (*seq_reverse_t)(SeqRevArgs);
 static const seq_reverse_t kSeqReverseVariants[3] = {seq_reverse_kernel<false, 1>, seq_reverse_kernel<false, 2>, seq_reverse_kernel<true, 2>};
-// the same with the tape written (training)
-static const seq_kernel_t kSeqTapeVariants[6] = {seq_chain_kernel<32, false, false, true>, seq_chain_kernel<32, true, false, true>,
-                                                 seq_chain_kernel<64, false, false, true>, seq_chain_kernel<64, true, false, true>,
-                                                 seq_chain_kernel<96, true, true, true>,   seq_chain_kernel<128, true, true, true>};
 
 int hag_seq_get_plan(const hag_seq_t *h, int32_t order, int64_t *n_states, int64_t *n_paths, const int32_t **paths,
                      const int32_t **step_x, const int32_t **step_out, int64_t *n_levels, const int64_t **level_ptr,
@@ -1003,6 +1100,8 @@ int hag_seq_upload(hag_seq_t *h) {
     HIP_TRY(put(&h->d_step_x, h->step_x));
     HIP_TRY(put(&h->d_step_out, h->step_out));
     HIP_TRY(put(&h->d_step_prev, h->step_prev));
+    HIP_TRY(put(&h->d_used, h->used));
+    HIP_TRY(put(&h->d_step_g, h->step_g));
     HIP_TRY(put(&h->d_xt_ptr, h->xt_ptr));
     HIP_TRY(put(&h->d_xt_idx, h->xt_idx));
     HIP_TRY(put(&h->d_pending_init, h->pending_init));
@@ -1012,16 +1111,14 @@ int hag_seq_upload(hag_seq_t *h) {
         // kernel is tuned for): the grid of a one-launch pass
         int cus = 0;
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device));
-        for (int k = 0; k < 6; ++k) {
+        for (int k = 0; k < 3; ++k) {
             int per_cu = 0;
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqVariants[k], k >= 4 ? 1024 : 512, 0));
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqVariants[k], (int)seq_block(k), 0));
             h->resident[k] = (int64_t)std::min(per_cu, 2) * cus;
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqTapeVariants[k], k >= 4 ? 1024 : 512, 0));
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqTapeVariants[k], (int)seq_block(k), 0));
             h->resident_tape[k] = (int64_t)std::min(per_cu, 2) * cus;
-            if (k < 3) {
-                HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqReverseVariants[k], 512, 0));
-                h->resident_reverse[k] = (int64_t)std::min(per_cu, k == 2 ? 1 : 2) * cus;
-            }
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqReverseVariants[k], 512, 0));
+            h->resident_reverse[k] = (int64_t)std::min(per_cu, k == 2 ? 1 : 2) * cus;
         }
     }
     HIP_TRY(put(&h->d_final, h->final_state));
@@ -1052,13 +1149,28 @@ int hag_seq_check(const hag_seq_t *h, void *stream) {
     return HAG_ETIMEOUT;
 }
 
+// Layout of the forward workspace, in bytes.
+struct SeqLayout { int64_t dp, ks; size_t wx, wq, bp, h, c, flags, gx, total; };
+static SeqLayout seq_layout(const hag_seq_t *h, int64_t d, int64_t hidden) {
+    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const size_t states = (size_t)std::max<int64_t>(h->n_states, 1), H = (size_t)hidden, f = sizeof(float);
+    SeqLayout L;
+    L.dp = (d + 7) / 8 * 8;
+    L.ks = hidden > 64 ? (hidden + 15) / 16 : hidden > 32 ? 4 : 2;
+    size_t at = 0;
+    L.wx = at; at += up(4 * H * (size_t)L.dp * f);
+    L.wq = at; at += up((H / 8) * (size_t)L.ks * 3 * 512 * sizeof(uint16_t));
+    L.bp = at; at += up(4 * H * f);
+    L.h = at; at += up(states * H * f);
+    L.c = at; at += up(states * H * f);
+    L.flags = at; at += up(states * sizeof(int32_t));
+    L.gx = at; at += up(h->used.size() * 4 * H * f);
+    L.total = at;
+    return L;
+}
 size_t hag_seq_workspace_bytes(const hag_seq_t *h, int64_t d, int64_t hidden) {
     if (!h || d <= 0 || hidden <= 0) return 0;
-    const size_t states = (size_t)std::max<int64_t>(h->n_states, 1) * (size_t)hidden * sizeof(float);
-    const size_t wp = (size_t)4 * hidden * seq_kp(d, hidden) * sizeof(float), bp = (size_t)4 * hidden * sizeof(float);
-    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const size_t flags = (size_t)std::max<int64_t>(h->n_states, 1) * sizeof(int32_t);
-    return up(wp) + up(bp) + 2 * up(states) + up(flags);
+    return seq_layout(h, d, hidden).total;
 }
 
 static int seq_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const float *x, const float *w_ih, const float *w_hh,
@@ -1073,24 +1185,24 @@ static int seq_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const floa
     if (!x || !w_ih || !w_hh || !b || !a_out || !workspace) { set_error("NULL pointer"); return HAG_EINVAL; }
     if (((uintptr_t)x | (uintptr_t)workspace | (uintptr_t)a_out) & 15) { set_error("x, a_out and workspace must be 16-byte aligned"); return HAG_EINVAL; }
     hipStream_t s = (hipStream_t)stream;
-    const int kp = (int)seq_kp(d, hidden);
-    auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    const SeqLayout L = seq_layout(h, d, hidden);
     char *w = (char *)workspace;
-    float *wp = (float *)w; w += up((size_t)4 * hidden * kp * sizeof(float));
-    float *bp = (float *)w; w += up((size_t)4 * hidden * sizeof(float));
-    const size_t states = up((size_t)std::max<int64_t>(h->n_states, 1) * (size_t)hidden * sizeof(float));
-    float *hst = (float *)w; w += states;
-    float *cst = (float *)w; w += states;
-    int32_t *flags = (int32_t *)w;                          // [n_states]
+    float *wx = (float *)(w + L.wx), *bp = (float *)(w + L.bp), *hst = (float *)(w + L.h), *cst = (float *)(w + L.c), *gx = (float *)(w + L.gx);
+    uint16_t *wq = (uint16_t *)(w + L.wq);
+    int32_t *flags = (int32_t *)(w + L.flags);              // [n_states]
     {
-        const int64_t total = (int64_t)4 * hidden * kp;
-        hipLaunchKernelGGL(seq_pack_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, w_ih, w_hh, b, wp, bp, (int)d,
-                           (int)hidden, kp, kp > 128 ? 1 : 0, flags, h->n_states);
+        const int64_t total = std::max<int64_t>({4 * hidden * L.dp, hidden / 8 * L.ks * 512, std::min<int64_t>(h->n_states, 1 << 20)});
+        hipLaunchKernelGGL(seq_pack_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, w_ih, w_hh, b, wx, wq, bp, (int)d,
+                           (int)L.dp, (int)hidden, (int)L.ks, flags, h->n_states);
+        HIP_TRY(hipGetLastError());
+    }
+    if (const int64_t n_used = (int64_t)h->used.size(); n_used > 0) {
+        hipLaunchKernelGGL(seq_input_gates_kernel, dim3((unsigned)std::min<int64_t>((n_used + 63) / 64, 1 << 20)), dim3(256),
+                           (size_t)64 * (size_t)(L.dp + 2) * sizeof(float), s, x, h->d_used, n_used, wx, bp, gx, (int)d, (int)L.dp, (int)hidden);
         HIP_TRY(hipGetLastError());
     }
     const int64_t levels = (int64_t)h->tile_ptr.size() - 1;
-    const int variant = seq_variant(kp, hidden);
-    const bool big = variant >= 4;
+    const int variant = seq_variant(hidden);
     const int64_t resident = tape_g ? h->resident_tape[variant] : h->resident[variant];
     const bool fused = levels > 1 && h->one_launch && resident > 0;
     for (int64_t l = 0; l < (fused ? 1 : levels); ++l) {
@@ -1102,12 +1214,12 @@ static int seq_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const floa
         c.spin_limit = h->spin_limit;
         c.publish = h->wait_unreachable ? 0 : 1;
         c.gave_up = h->d_gave_up;
-        c.step_x = h->d_step_x; c.step_out = h->d_step_out;
-        c.x = x; c.wp = wp; c.bp = bp; c.h = hst; c.c = cst; c.a_out = a_out;
+        c.step_g = h->d_step_g; c.step_out = h->d_step_out;
+        c.gx = gx; c.wq = wq; c.h = hst; c.c = cst; c.a_out = a_out;
         c.tape_g = tape_g; c.tape_c = tape_c; c.tape_h = tape_h;
-        c.d = (int32_t)d; c.hidden = (int32_t)hidden;
+        c.hidden = (int32_t)hidden;
         if (c.n_path_tiles <= 0) continue;
-        const dim3 grid((unsigned)std::min<int64_t>(c.n_path_tiles, fused ? resident : (big ? 256 : 512))), block(big ? 1024 : 512);
+        const dim3 grid((unsigned)std::min<int64_t>(c.n_path_tiles, fused ? resident : (variant == 2 ? 256 : 512))), block(seq_block(variant));
         hipLaunchKernelGGL(tape_g ? kSeqTapeVariants[variant] : kSeqVariants[variant], grid, block, 0, s, c);
         HIP_TRY(hipGetLastError());
     }
@@ -1186,12 +1298,9 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
     hipStream_t s = (hipStream_t)stream;
     const int kp = (int)seq_kp(d, hidden);
     const SeqTrainLayout L = seq_train_layout(h, d, hidden);
-    auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
     char *w = (char *)workspace;
-    // the forward workspace as seq_forward laid it out: packed weights, packed bias, h rows, c rows
-    const size_t states = up((size_t)std::max<int64_t>(h->n_states, 1) * (size_t)hidden * sizeof(float));
-    const float *hst = (const float *)(w + up((size_t)4 * hidden * kp * sizeof(float)) + up((size_t)4 * hidden * sizeof(float)));
-    const float *cst = (const float *)((const char *)hst + states);
+    const SeqLayout F = seq_layout(h, d, hidden);           // the forward pass left its state rows there
+    const float *hst = (const float *)(w + F.h), *cst = (const float *)(w + F.c);
     float *tape_g = (float *)(w + L.tape_g), *tape_c = (float *)(w + L.tape_c), *tape_h = (float *)(w + L.tape_h);
     float *dx = (float *)(w + L.dx), *gh = (float *)(w + L.gh), *gc = (float *)(w + L.gc), *wqt = (float *)(w + L.wqt);
     float *partial = (float *)(w + L.partial);

@@ -47,13 +47,14 @@ struct hag_seq {
     int32_t *d_final = nullptr, *d_paths = nullptr, *d_step_x = nullptr, *d_step_out = nullptr;   // d_paths: padded to whole tiles per level
     int32_t *d_paths_by_depth = nullptr;                    // likewise per depth group
     // for the backward pass: per step where its h_{t-1} lives (>= 0: that step's tape row, -1: the zero state,
-    // <= -2: state row -(value) - 2), and the steps grouped by the input row they read (for the gradient of x)
-    std::vector<int32_t> step_prev, xt_ptr, xt_idx;
+    // <= -2: state row -(value) - 2); all three in the order of the input row that the steps read: the steps, their step_prev, the
+    // place of the input row among the used ones
+    std::vector<int32_t> xt_idx, xt_prev, xt_seg;
     std::vector<int32_t> used, step_g;   // the nodes that occur in a list, ascending; per step the place of its input row among them
     std::vector<int32_t> pending_init;   // per state: the paths that start from it
-    int32_t *d_step_prev = nullptr, *d_xt_ptr = nullptr, *d_xt_idx = nullptr, *d_pending_init = nullptr;
+    int32_t *d_xt_idx = nullptr, *d_xt_prev = nullptr, *d_xt_seg = nullptr, *d_pending_init = nullptr;
     int32_t *d_used = nullptr, *d_step_g = nullptr;
-    int64_t resident_reverse[3] = {0, 0, 0};   // reverse kernel variants <false,1>, <false,2>, <true,2>
+    int64_t resident_reverse[3] = {0, 0, 0};   // reverse kernel variants: hidden up to 32, 64, 128
     int64_t resident[3] = {0, 0, 0}, resident_tape[3] = {0, 0, 0};   // forward kernel variants, without and with the tape: workgroups the device holds at once (set by hag_seq_upload)
     int32_t *d_gave_up = nullptr;     // set by a wait that gave up; read and cleared by hag_seq_check
     int device = -1;
@@ -226,6 +227,55 @@ __device__ __forceinline__ void seq_st4_device(float *p, float4 v) {
 // instead of being held in a register across the products.
 __device__ __forceinline__ int seq_opaque(int v) { asm volatile("" : "+v"(v)); return v; }
 
+// The 128 bytes that one path has of a gate tile (eight units, four gates) are held by lanes l and l + 32, four float4 each (unit
+// 4 * (l / 32) + m).  Moved to memory as they are, an instruction would touch 16 or 32 bytes of 64 or 32 rows, which a streaming
+// kernel moves at 2.9 TB/s here; exchanged between the rows of 16 lanes first, it touches 64 bytes of 16 paths (5.0 TB/s).  After
+// seq_to_pieces lane l holds, of path l % 16 in v[0] and v[1] and of path 16 + l % 16 in v[2] and v[3], unit piece(l) and unit 4 + piece(l).
+// All 64 lanes take part.
+__device__ __forceinline__ int seq_piece(int lane) { return ((lane >> 5) & 1) | (((lane >> 4) & 1) << 1); }
+__device__ __forceinline__ void seq_swap32(float &a, float &b) {
+    const seq_u2_t v = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(v.x); b = __uint_as_float(v.y);
+}
+__device__ __forceinline__ void seq_swap16(float &a, float &b) {
+    const seq_u2_t v = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(v.x); b = __uint_as_float(v.y);
+}
+// v: sixteen values, (m, gate); V is indexable (an array or an accumulator)
+template <typename V>
+__device__ __forceinline__ void seq_to_pieces(V &v, float4 (&p)[4]) {
+    float r[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) r[e] = v[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        seq_swap32(r[e], r[4 + e]);           // -> units {0, 1} and {4, 5}
+        seq_swap32(r[8 + e], r[12 + e]);      // -> units {2, 3} and {6, 7}
+        seq_swap16(r[e], r[8 + e]);
+        seq_swap16(r[4 + e], r[12 + e]);
+    }
+    p[0] = make_float4(r[0], r[1], r[2], r[3]);
+    p[1] = make_float4(r[4], r[5], r[6], r[7]);
+    p[2] = make_float4(r[8], r[9], r[10], r[11]);
+    p[3] = make_float4(r[12], r[13], r[14], r[15]);
+}
+// the reverse, in place: v holds the float4 p[0], p[1], ... as seq_to_pieces leaves them
+template <typename V>
+__device__ __forceinline__ void seq_from_pieces(V &v) {
+    float r[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) r[e] = v[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        seq_swap16(r[e], r[8 + e]);
+        seq_swap16(r[4 + e], r[12 + e]);
+        seq_swap32(r[e], r[4 + e]);
+        seq_swap32(r[8 + e], r[12 + e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = r[e];
+}
+
 // Paths of one level, or of all.  A workgroup takes tiles of 64 paths and walks ALL their steps; the running states never leave
 // the compute unit: c in registers, h in LDS as the operand of the next step's product.  A step reads one row of gx per path
 // (the accumulators start from it), multiplies W_hh with the 64 h rows, runs the element-wise part on the result in
@@ -300,12 +350,18 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
         int row[JG], keep[JG];                             // (begin and length are read from LDS where they are needed: registers are short)
         float4 creg[C_LDS ? 1 : JG];
         seq_acc_t acc[JG];
-        auto load_gates = [&](int g, int unit0) {          // the accumulators of the next step start from this row of gx
-            const float *p = A.gx + (size_t)row[g] * (4 * hidden) + unit0 * 4;
+        auto load_gates = [&](int g) {                     // the accumulators of the next step start from these rows of gx (row -1: the path has ended); the pieces are put in place by seq_from_pieces when they are used, so that nothing waits for them here
+            const seq_u2_t rows = __builtin_amdgcn_permlane16_swap((unsigned)row[g], (unsigned)row[g], false, false);   // of paths l % 16 and 16 + l % 16
+            const int l = seq_opaque(threadIdx.x) & 63;
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const float4 v = *reinterpret_cast<const float4 *>(p + 4 * m);
-                acc[g][4 * m] = v.x; acc[g][4 * m + 1] = v.y; acc[g][4 * m + 2] = v.z; acc[g][4 * m + 3] = v.w;
+            for (int q = 0; q < 2; ++q) {
+                const int r = (int)(q ? rows.y : rows.x);
+                if (r >= 0) {
+                    const float *p = A.gx + ((size_t)r * hidden + tile * 8 + seq_piece(l)) * 4;
+                    const float4 v = *reinterpret_cast<const float4 *>(p), w = *reinterpret_cast<const float4 *>(p + 16);
+                    acc[g][8 * q] = v.x; acc[g][8 * q + 1] = v.y; acc[g][8 * q + 2] = v.z; acc[g][8 * q + 3] = v.w;
+                    acc[g][8 * q + 4] = w.x; acc[g][8 * q + 5] = w.y; acc[g][8 * q + 6] = w.z; acc[g][8 * q + 7] = w.w;
+                }
             }
         };
         auto put_h = [&](int buf, int j, int unit0, const float (&h)[4]) {
@@ -318,8 +374,8 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
 #pragma unroll
         for (int g = 0; g < JG; ++g) {
             const int l = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (l >> 5) * 4, j = (group0 + g) * 32 + (l & 31), start = sdesc[j * 4];
-            const int beg = sdesc[j * 4 + 1], len = on ? sdesc[j * 4 + 2] : 0;
-            row[g] = 0; keep[g] = -1;
+            const int beg = sdesc[j * 4 + 1], len = on ? sdesc[j * 4 + 2] : 0;   // (the path's row of gx for the next step is asked for a step ahead)
+            row[g] = -1; keep[g] = -1;
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[g][r] = 0.f;
             if (len > 0) {
@@ -336,9 +392,9 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                 if constexpr (C_LDS) *reinterpret_cast<float4 *>(&cs[j][unit0]) = cv;
                 else creg[g] = cv;
                 put_h(0, j, unit0, h);
-                load_gates(g, unit0);
-                if (len > 1) row[g] = A.step_g[beg + 1];
             }
+            if (on) load_gates(g);
+            row[g] = len > 1 ? A.step_g[beg + 1] : -1;
         }
         {
             const int tid = seq_opaque(threadIdx.x);
@@ -375,6 +431,8 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
             const int cur = t & 1;
             if (on) {
                 if constexpr (BIG) {
+#pragma unroll
+                    for (int g = 0; g < JG; ++g) seq_from_pieces(acc[g]);
                     seq_b8_t wa[3], wn[3];
 #pragma unroll
                     for (int p = 0; p < 3; ++p) wa[p] = wl[p * 64];
@@ -391,6 +449,7 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
 #pragma unroll
                 for (int g = 0; g < JG; ++g) {
                     if constexpr (!BIG) {
+                        seq_from_pieces(acc[g]);
 #pragma unroll
                         for (int s = 0; s < KS; ++s) product(cur, g, acc[g], wreg[s], s);
                     }
@@ -415,25 +474,8 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                         const float4 h4 = make_float4(h[0], h[1], h[2], h[3]), c4 = make_float4(c[0], c[1], c[2], c[3]);
                         if constexpr (C_LDS) *reinterpret_cast<float4 *>(&cs[j][unit0]) = c4;
                         else creg[g] = c4;
-                        if constexpr (TAPE) {
-                            // what the backward pass needs of this cell, indexed by the step.  Lanes l and l + 32 (the same path) swap
-                            // half of their units, so that together they write 32 contiguous bytes of the gates per store.
-                            const size_t cell = (size_t)(beg + t) * hidden;
-#pragma unroll
-                            for (int q = 0; q < 2; ++q) {
-                                float lo[4], hi[4];
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) {
-                                    const seq_u2_t v = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[g][8 * q + e]), __float_as_uint(acc[g][8 * q + 4 + e]), false, false);
-                                    lo[e] = __uint_as_float(v.x); hi[e] = __uint_as_float(v.y);
-                                }
-                                float *p = A.tape_g + (cell + tile * 8 + 2 * q + half) * 4;
-                                *reinterpret_cast<float4 *>(p) = make_float4(lo[0], lo[1], lo[2], lo[3]);
-                                *reinterpret_cast<float4 *>(p + 16) = make_float4(hi[0], hi[1], hi[2], hi[3]);
-                            }
-                            *reinterpret_cast<float4 *>(A.tape_h + cell + unit0) = h4;
-                            *reinterpret_cast<float4 *>(A.tape_c + cell + unit0) = c4;
-                        }
+                        // (the gates and h leave further down, in larger pieces)
+                        if constexpr (TAPE) *reinterpret_cast<float4 *>(A.tape_c + (size_t)(beg + t) * hidden + unit0) = c4;
                         if (keep[g] >= 0) {                // a state that another path starts from, or some a_v
                             const size_t o = (size_t)keep[g] * hidden + unit0;
                             if (A.flags) {
@@ -448,15 +490,52 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                             // a_v = the last h of the path, where the path ends a node's list
                             const int node = sdesc[j * 4 + 3];
                             if (node >= 0) *reinterpret_cast<float4 *>(A.a_out + (size_t)node * hidden + unit0) = h4;
+                            row[g] = -1;
                         } else {
                             keep[g] = A.step_out[beg + t + 1];
-                            load_gates(g, unit0);
-                            if (t + 2 < len) row[g] = A.step_g[beg + t + 2];
                         }
                     }
+                    if constexpr (TAPE) {
+                        // the activated gates, for the backward pass, indexed by the step
+                        float4 v[4];
+                        seq_to_pieces(acc[g], v);
+                        const int l = seq_opaque(threadIdx.x) & 63;
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            const int jj = (group0 + g) * 32 + 16 * q + (l & 15);
+                            if (t < sdesc[jj * 4 + 2]) {
+                                float *p = A.tape_g + ((size_t)(sdesc[jj * 4 + 1] + t) * hidden + tile * 8 + seq_piece(l)) * 4;
+                                *reinterpret_cast<float4 *>(p) = v[2 * q];
+                                *reinterpret_cast<float4 *>(p + 16) = v[2 * q + 1];
+                            }
+                        }
+                    }
+                    load_gates(g);
+                    if (t + 2 < len) row[g] = A.step_g[beg + t + 2];
                 }
             }
             __syncthreads();                               // the h rows of the next step are complete, this step's have been read
+            if constexpr (TAPE) {
+                // h of the step as whole rows out of the operand buffer (the three pieces add up to it exactly), which is not
+                // written again before the barrier of the next step
+                const int tid = seq_opaque(threadIdx.x), j = tid / (HMAX / 8), part = tid % (HMAX / 8);
+                if (j < kSeqJobs && t < sdesc[j * 4 + 2]) {
+                    const size_t cell = (size_t)(sdesc[j * 4 + 1] + t) * hidden;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const int u = part * 4 + i * (HMAX / 2);
+                        if (u >= hidden) continue;
+                        float h[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) {
+                            const uint2 w = *reinterpret_cast<const uint2 *>(&z[cur ^ 1][p][j][u]);
+                            h[0] += __uint_as_float(w.x << 16); h[1] += __uint_as_float(w.x & 0xffff0000u);
+                            h[2] += __uint_as_float(w.y << 16); h[3] += __uint_as_float(w.y & 0xffff0000u);
+                        }
+                        *reinterpret_cast<float4 *>(A.tape_h + cell + u) = make_float4(h[0], h[1], h[2], h[3]);
+                    }
+                }
+            }
         }
         if (on) publish((steps - 1) & 1);
         __syncthreads();
@@ -477,8 +556,10 @@ __global__ __launch_bounds__(256) void seq_output_kernel(const int32_t *__restri
 // ---------------------------------------------------------------------------------------------------------
 // Backward pass (backpropagation through time along the same paths, last step first).  For the cell of a step,
 // with the gradients dh, dc of its outputs:  t = tanh(c'),  d_o = dh t,  dc += dh o (1 - t^2),
-//   d(pre-activations) = (dc g i(1-i),  dc c f(1-f),  dc i (1-g^2),  d_o o(1-o)),   dc_prev = dc f,
-//   (dx, dh_prev) = Wp^T d(pre-activations),   dWp += d(pre-activations) (x, h_prev)^T,   db += d(pre-activations).
+//   dG = d(pre-activations) = (dc g i(1-i),  dc c f(1-f),  dc i (1-g^2),  d_o o(1-o)),   dc_prev = dc f,
+//   dh_prev = W_hh^T dG,   dW_hh += dG h_prev^T;
+// what depends on the input row x[u] goes through the sum of dG over the steps that read it, once per node:
+//   s[u] = sum of dG,   g_x[u] = W_ih^T s[u],   dW_ih = sum over u of s[u] x[u]^T,   db = sum over u of s[u].
 // A state that other paths start from (or that is some a_v) collects their gradients in its row of gh / gc; levels
 // run last to first, so a path finds those rows complete when it reaches the step that wrote the state.
 
@@ -486,46 +567,57 @@ struct SeqRevArgs {
     const int32_t *paths;    // this level's paths in tiles of 64
     int64_t n_path_tiles;
     const int32_t *step_out;
-    const float *wqt;        // Wp^T in the order the matrix instructions consume it
+    const float *wqt;        // W_hh^T in the order the matrix instructions consume it, see seq_pack_transposed_kernel
     float *tape_g;           // in: the activated gates of every step; out: the gradients of its pre-activations
     const float *tape_c;     // c' of every step
     const float *c_state;    // c rows of the kept states
     const float *g_a;        // [n, H]
     float *gh, *gc;          // [n_states, H]
-    float *dx;               // [cells, d]: every step's gradient of its input row
-    // all levels in one launch (NULL: one launch per level): per kept state the number of paths that start from it and
-    // have not sent their gradients yet; tiles are taken last first
+    // all levels in one launch (NULL: one launch per level): per kept state what is still to come from the paths that start
+    // from it (one count per path, or per path and wavefront, see seq_reverse_counts); tiles are taken last first
     int32_t *pending;
     int32_t *gave_up;
     int32_t spin_limit, reversed;
     int32_t publish;         // 0 in a test of the time-out: no path is ever counted off
-    int32_t d, hidden, kp;
+    int32_t hidden;
 };
 
 
-__global__ __launch_bounds__(256) void seq_copy_i32_kernel(const int32_t *__restrict__ src, int32_t *__restrict__ dst, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) dst[i] = src[i];
+__global__ __launch_bounds__(256) void seq_scale_i32_kernel(const int32_t *__restrict__ src, int32_t *__restrict__ dst, int64_t n, int32_t factor) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) dst[i] = src[i] * factor;
 }
 
 __global__ __launch_bounds__(256) void seq_fill_kernel(float *p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0.f;
 }
 
-// Wp^T for the backward product, from the usual layout: [kp / 32 row tiles][4H / 8 groups of four k-steps][64 lanes][4];
-// lane l supplies row (tile * 32 + l % 32) of Wp^T, i.e. column z of Wp = (w_ih | w_hh | 0), and Wp's row 2 * step + l / 32,
-// rows of Wp being ordered (unit, gate).
+// The weights of the backward products, from the usual layout.
+//   wqt, hidden <= 64: [gate tile][m_tiles of 32 hidden units][16][lane]; lane l supplies output unit 32 * mt + l % 32, and as k
+//       value e = 4 m + gate the gate row of unit 8 * tile + 4 * (l / 32) + m: the order in which the lanes hold dG;
+//   wqt, hidden > 64: [m_tiles][4H / 8 groups of four k-steps][lane][4]; lane l supplies unit 32 * mt + l % 32, k-step q the gate
+//       rows 2 q + l / 32 in (unit, gate) order;
+//   wxt: W_ih^T for g_x: [d tiles of 32 columns][4H / 8 groups of four k-steps][lane][4]; lane l supplies column 32 * tile + l % 32,
+//       k-step q the gate rows 2 q + l / 32.
 __global__ __launch_bounds__(256) void seq_pack_transposed_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
-                                                                 float *__restrict__ wqt, int d, int hidden, int kp) {
-    const int64_t total = (int64_t)kp * 4 * hidden;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const int per_tile = 32 * 4 * hidden, tile = (int)(i / per_tile), rest = (int)(i % per_tile);
-        const int q = rest / 256, lane = (rest % 256) / 4, step = 4 * q + (rest & 3);
-        const int r = 2 * step + (lane >> 5), z = tile * 32 + (lane & 31);
-        const int row = (r & 3) * hidden + (r >> 2);
-        float v = 0.f;
-        if (z < d) v = w_ih[(size_t)row * d + z];
-        else if (z < d + hidden) v = w_hh[(size_t)row * hidden + (z - d)];
-        wqt[i] = v;
+                                                                 float *__restrict__ wqt, float *__restrict__ wxt, int d, int hidden) {
+    const int m_tiles = (hidden + 31) / 32, d_tiles = (d + 31) / 32, rows = 4 * hidden;
+    const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
+    for (int64_t i = first; i < (int64_t)m_tiles * 32 * rows; i += stride) {
+        int unit, gate, z;
+        if (hidden <= 64) {
+            const int lane = (int)(i & 63), e = (int)(i >> 6) & 15, mt = (int)(i >> 10) % m_tiles, tile = (int)(i >> 10) / m_tiles;
+            unit = tile * 8 + (lane >> 5) * 4 + (e >> 2); gate = e & 3; z = mt * 32 + (lane & 31);
+        } else {
+            const int mt = (int)(i / (32 * rows)), rest = (int)(i % (32 * rows)), q = rest / 256, lane = (rest % 256) / 4;
+            const int r = 2 * (4 * q + (rest & 3)) + (lane >> 5);
+            unit = r >> 2; gate = r & 3; z = mt * 32 + (lane & 31);
+        }
+        wqt[i] = z < hidden ? w_hh[(size_t)(gate * hidden + unit) * hidden + z] : 0.f;
+    }
+    for (int64_t i = first; i < (int64_t)d_tiles * 32 * rows; i += stride) {
+        const int tile = (int)(i / (32 * rows)), rest = (int)(i % (32 * rows)), q = rest / 256, lane = (rest % 256) / 4;
+        const int r = 2 * (4 * q + (rest & 3)) + (lane >> 5), z = tile * 32 + (lane & 31);
+        wxt[i] = z < d ? w_ih[(size_t)((r & 3) * hidden + (r >> 2)) * d + z] : 0.f;
     }
 }
 
@@ -538,17 +630,204 @@ __global__ __launch_bounds__(256) void seq_final_grad_kernel(const int32_t *__re
     }
 }
 
-// WIDE_H: hidden above 64 (up to 128): rows of 4 * 128 + 2 staged gradients, one workgroup per compute unit.
-template <bool WIDE_H, int NPI>
-__global__ __launch_bounds__(512, WIDE_H ? 2 : 4) void seq_reverse_kernel(SeqRevArgs A) {
-    constexpr int ZG = 4 * (WIDE_H ? 128 : 64) + 2, IT = WIDE_H ? 4 : 2;
+// Waits (bounded) until everything that continues from a kept state has sent its gradients.  One launch for all levels: the paths
+// that start from the state belong to tiles taken before this one, which never wait for it, so the count reaches zero.
+__device__ __forceinline__ void seq_wait_pending(const SeqRevArgs &A, int keep) {
+    bool ready = false;
+    for (int spin = 0; spin < A.spin_limit; ++spin) {
+        if (__hip_atomic_load(A.pending + keep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= 0) { ready = true; break; }
+        if (__hip_atomic_load(A.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
+        __builtin_amdgcn_s_sleep(16);
+    }
+    if (!ready) __hip_atomic_store(A.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");       // the sums are then read with device-scope loads
+}
+
+// Hidden sizes up to 64 (HMAX 32 or 64).  Lanes and wavefronts are those of the forward kernel: a lane holds (path, four units of
+// gate tile w), their running dh and dc and, per step, the sixteen dG.  The k index of dh_prev = W_hh^T dG can be taken in any order, so the
+// dG are the product's operand where they are, in the registers of the lane that made them: wavefront w multiplies the 32 gate
+// rows of its own tile and leaves its part of dh_prev for all units in LDS; after a barrier every lane adds the parts
+// for its own units, in a fixed order.  The gates of the next step are requested before the product, and with one workgroup per compute
+// unit (139 KB of LDS, 256 registers) about 80 KB of tape are in flight: the kernel is bound by the tape (read gates and c, write dG: 36 H bytes
+// per cell).
+template <int HMAX>
+__global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
+    constexpr int MT = HMAX / 32, JG = HMAX / 32, NT = HMAX / 8, RS = HMAX + 4;
+    __shared__ __align__(16) float red[NT][kSeqJobs][RS];
+    __shared__ int32_t sdesc[kSeqJobs * 4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+    const int hidden = A.hidden, n_tiles = hidden / 8, m_tiles = (hidden + 31) / 32;
+    const int tile = HMAX == 64 ? wave : (wave & 3), group0 = HMAX == 64 ? 0 : (wave >> 2);
+    const bool on = tile < n_tiles;
+    const int unit0 = tile * 8 + half * 4;
+    float wt[MT][16];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) wt[mt][e] = on && mt < m_tiles ? A.wqt[(((size_t)tile * m_tiles + mt) * 16 + e) * 64 + lane] : 0.f;
+    for (int64_t ci = blockIdx.x; ci < A.n_path_tiles; ci += gridDim.x) {
+        const int64_t ct = A.reversed ? A.n_path_tiles - 1 - ci : ci;
+        if (threadIdx.x < kSeqJobs * 4) sdesc[threadIdx.x] = A.paths[ct * (kSeqJobs * 4) + threadIdx.x];
+        __syncthreads();
+        const int steps = sdesc[2];
+        float dh[JG][4], dc[JG][4];
+        float dg[JG][16], gates[JG][16];                   // gates: requested a step ahead, in pieces (see seq_to_pieces)
+        float4 c_now[JG], c_prev[JG];                      // c_prev is the next step's c_now
+        int keep[JG];
+        auto load_step = [&](int g, int t) {               // the tape of step t, where the paths have one
+            const int l = seq_opaque(threadIdx.x) & 63, half = l >> 5, unit0 = tile * 8 + half * 4;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int jj = (group0 + g) * 32 + 16 * q + (l & 15);
+                if (t < sdesc[jj * 4 + 2]) {
+                    const float *p = A.tape_g + ((size_t)(sdesc[jj * 4 + 1] + t) * hidden + tile * 8 + seq_piece(l)) * 4;
+                    const float4 v = *reinterpret_cast<const float4 *>(p), w = *reinterpret_cast<const float4 *>(p + 16);
+                    gates[g][8 * q] = v.x; gates[g][8 * q + 1] = v.y; gates[g][8 * q + 2] = v.z; gates[g][8 * q + 3] = v.w;
+                    gates[g][8 * q + 4] = w.x; gates[g][8 * q + 5] = w.y; gates[g][8 * q + 6] = w.z; gates[g][8 * q + 7] = w.w;
+                }
+            }
+            const int j = (group0 + g) * 32 + (l & 31), start = sdesc[j * 4], len = sdesc[j * 4 + 2];
+            if (t < len) {
+                const size_t cell = (size_t)sdesc[j * 4 + 1] + t;
+                keep[g] = A.step_out[cell];
+                c_prev[g] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (t > 0) c_prev[g] = *reinterpret_cast<const float4 *>(A.tape_c + (cell - 1) * hidden + unit0);
+                else if (start >= 0) c_prev[g] = *reinterpret_cast<const float4 *>(A.c_state + (size_t)start * hidden + unit0);
+            }
+        };
+        auto sum_parts = [&](int g, int j) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int w = 0; w < NT; ++w) {
+                if (w >= n_tiles) break;
+                const float4 q = *reinterpret_cast<const float4 *>(&red[w][j][unit0]);
+                v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+            }
+            dh[g][0] = v.x; dh[g][1] = v.y; dh[g][2] = v.z; dh[g][3] = v.w;
+        };
+#pragma unroll
+        for (int g = 0; g < JG; ++g) {
+            const int j = (group0 + g) * 32 + (lane & 31), len = sdesc[j * 4 + 2], node = sdesc[j * 4 + 3];
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (on && node >= 0) v = *reinterpret_cast<const float4 *>(A.g_a + (size_t)node * hidden + unit0);
+            dh[g][0] = v.x; dh[g][1] = v.y; dh[g][2] = v.z; dh[g][3] = v.w;
+            dc[g][0] = dc[g][1] = dc[g][2] = dc[g][3] = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) dg[g][e] = gates[g][e] = 0.f;
+            keep[g] = -1;
+            c_now[g] = c_prev[g] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (on && len > 0) c_now[g] = *reinterpret_cast<const float4 *>(A.tape_c + ((size_t)sdesc[j * 4 + 1] + len - 1) * hidden + unit0);
+            if (on) load_step(g, steps - 1);
+        }
+        for (int t = steps - 1; t >= 0; --t) {
+#pragma unroll
+            for (int g = 0; g < JG; ++g) {
+                if (!on) break;                            // (wavefronts beyond the hidden size only keep the barriers)
+                const int j = (group0 + g) * 32 + (lane & 31), len = sdesc[j * 4 + 2];
+                seq_from_pieces(gates[g]);
+                if (t < len) {
+                    if (t + 1 < len) sum_parts(g, j);      // dh_prev of the step before is this step's dh
+                    if (keep[g] >= 0) {                    // what the other users of this state sent back
+                        if (A.pending) seq_wait_pending(A, keep[g]);
+                        const size_t o = (size_t)keep[g] * hidden + unit0;
+                        const float4 a = A.pending ? seq_ld4_device(A.gh + o) : *reinterpret_cast<const float4 *>(A.gh + o);
+                        const float4 b = A.pending ? seq_ld4_device(A.gc + o) : *reinterpret_cast<const float4 *>(A.gc + o);
+                        dh[g][0] += a.x; dh[g][1] += a.y; dh[g][2] += a.z; dh[g][3] += a.w;
+                        dc[g][0] += b.x; dc[g][1] += b.y; dc[g][2] += b.z; dc[g][3] += b.w;
+                    }
+                    const float cn[4] = {c_now[g].x, c_now[g].y, c_now[g].z, c_now[g].w}, cp[4] = {c_prev[g].x, c_prev[g].y, c_prev[g].z, c_prev[g].w};
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const float4 g4 = make_float4(gates[g][4 * m], gates[g][4 * m + 1], gates[g][4 * m + 2], gates[g][4 * m + 3]);   // i, f, g, o
+                        const float tc = seq_tanh(cn[m]);
+                        const float d_o = dh[g][m] * tc;
+                        const float dcc = dc[g][m] + dh[g][m] * g4.w * (1.f - tc * tc);
+                        dg[g][4 * m] = dcc * g4.z * g4.x * (1.f - g4.x);
+                        dg[g][4 * m + 1] = dcc * cp[m] * g4.y * (1.f - g4.y);
+                        dg[g][4 * m + 2] = dcc * g4.x * (1.f - g4.z * g4.z);
+                        dg[g][4 * m + 3] = d_o * g4.w * (1.f - g4.w);
+                        dc[g][m] = dcc * g4.y;
+                    }
+                    c_now[g] = c_prev[g];
+                }
+                // dG replaces the gates on the tape
+                float4 v[4];
+                seq_to_pieces(dg[g], v);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int jj = (group0 + g) * 32 + 16 * q + (lane & 15);
+                    if (t < sdesc[jj * 4 + 2]) {
+                        float *p = A.tape_g + ((size_t)(sdesc[jj * 4 + 1] + t) * hidden + tile * 8 + seq_piece(lane)) * 4;
+                        *reinterpret_cast<float4 *>(p) = v[2 * q];
+                        *reinterpret_cast<float4 *>(p + 16) = v[2 * q + 1];
+                    }
+                }
+                if (t > 0) load_step(g, t - 1);
+            }
+            __syncthreads();                               // every lane has read the parts of the step before
+            if (on) {
+#pragma unroll
+                for (int g = 0; g < JG; ++g) {
+                    seq_acc_t acc[MT];
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(wt[mt][e], dg[g][e], acc[mt], 0, 0, 0);
+                    const int j = (group0 + g) * 32 + (lane & 31);
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            *reinterpret_cast<float4 *>(&red[tile][j][mt * 32 + 8 * q + 4 * half]) =
+                                make_float4(acc[mt][4 * q], acc[mt][4 * q + 1], acc[mt][4 * q + 2], acc[mt][4 * q + 3]);
+                }
+            }
+            __syncthreads();                               // the parts of dh_prev are complete
+        }
+        // what is left: the gradient of the state the path started from
+        if (on) {
+            bool sent = false;
+#pragma unroll
+            for (int g = 0; g < JG; ++g) {
+                const int j = (group0 + g) * 32 + (lane & 31), start = sdesc[j * 4], len = sdesc[j * 4 + 2];
+                if (len > 0 && start >= 0) {
+                    sum_parts(g, j);
+                    sent = true;
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        __hip_atomic_fetch_add(A.gh + (size_t)start * hidden + unit0 + m, dh[g][m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_fetch_add(A.gc + (size_t)start * hidden + unit0 + m, dc[g][m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+            }
+            if (A.pending && __any(sent)) {
+                // once the wavefront has seen its atomics complete, the path is counted off for this wavefront
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int g = 0; g < JG; ++g) {
+                    const int j = (group0 + g) * 32 + (lane & 31), start = sdesc[j * 4], len = sdesc[j * 4 + 2];
+                    if (len > 0 && start >= 0 && half == 0 && A.publish) __hip_atomic_fetch_sub(A.pending + start, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Hidden sizes from 72 to 128: eight threads per path run the element-wise part, dG is staged as rows of 4 * 128 + 2 in LDS (131 KB, one
+// workgroup per compute unit) and every wavefront multiplies one 32-unit tile of W_hh^T, streamed from the L2 cache, with one half of the paths.
+__global__ __launch_bounds__(512, 2) void seq_reverse_wide_kernel(SeqRevArgs A) {
+    constexpr int ZG = 4 * 128 + 2, IT = 4;
     // per path: the pre-activation gradients of the current step (the product's operand), then the product's result
-    // (dx, dh_prev); the running dh and dc themselves stay in the registers of the path's eight threads
+    // dh_prev; the running dh and dc themselves stay in the registers of the path's eight threads
     __shared__ __align__(16) float zg[kSeqJobs * ZG];
     __shared__ int32_t sdesc[kSeqJobs * 4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int hidden = A.hidden, d = A.d, n_rt = A.kp / 32;          // 2 or 4 row tiles of the product
-    // the product has n_rt row tiles x 2 halves of the paths; wavefront w takes pairs w and, with more than 8 (NPI = 2), w + 8
+    const int hidden = A.hidden, n_rt = (hidden + 31) / 32;          // 3 or 4 row tiles of the product
     const int sj = threadIdx.x >> 3, part = threadIdx.x & 7;         // element-wise phases: 8 threads per path, all in one wavefront
     for (int64_t ci = blockIdx.x; ci < A.n_path_tiles; ci += gridDim.x) {
         const int64_t ct = A.reversed ? A.n_path_tiles - 1 - ci : ci;
@@ -569,35 +848,19 @@ __global__ __launch_bounds__(512, WIDE_H ? 2 : 4) void seq_reverse_kernel(SeqRev
             if (t < len) {
                 const size_t cell = (size_t)beg + t;
                 if (t + 1 < len) {
-                    // the product of the step before left (dx, dh_prev) of this path in its row: dx goes out, dh_prev is this
-                    // step's dh.  Only this path's own lanes touch the row between the barriers, and they read it before
-                    // they overwrite it below (one wavefront, program order).
-                    for (int k = part * 4; k < d; k += 32) {
-                        const float *pz = &zg[sj * ZG + k];
-                        *reinterpret_cast<float4 *>(A.dx + (cell + 1) * d + k) = make_float4(pz[0], pz[1], pz[2], pz[3]);
-                    }
+                    // the product of the step before left dh_prev of this path in its row: this step's dh.  Only this path's own
+                    // lanes touch the row between the barriers, and they read it before they overwrite it below (one wavefront,
+                    // program order).
 #pragma unroll
                     for (int it = 0; it < IT; ++it) {
                         const int u = part * 4 + 32 * it;
                         if (u >= hidden) continue;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) dhv[it][e] = zg[sj * ZG + d + u + e];
+                        for (int e = 0; e < 4; ++e) dhv[it][e] = zg[sj * ZG + u + e];
                     }
                 }
                 const int keep = A.step_out[cell];
-                if (A.pending && keep >= 0) {
-                    // One launch for all levels: the paths that start from this state belong to tiles taken before this one,
-                    // which never wait for it, so the count reaches zero; the wait is bounded all the same.  Their sums are
-                    // then read with device-scope loads.
-                    bool ready = false;
-                    for (int spin = 0; spin < A.spin_limit; ++spin) {
-                        if (__hip_atomic_load(A.pending + keep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= 0) { ready = true; break; }
-                        if (__hip_atomic_load(A.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
-                        __builtin_amdgcn_s_sleep(16);
-                    }
-                    if (!ready) __hip_atomic_store(A.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                }
+                if (A.pending && keep >= 0) seq_wait_pending(A, keep);
 #pragma unroll
                 for (int it = 0; it < IT; ++it) {
                     const int u = part * 4 + 32 * it;
@@ -634,177 +897,199 @@ __global__ __launch_bounds__(512, WIDE_H ? 2 : 4) void seq_reverse_kernel(SeqRev
                 }
             }
             __syncthreads();
-            // (dx, dh_prev)^T [kp, paths] = Wp^T [kp, 4H] . dG^T [4H, paths]
-            seq_acc_t acc[NPI];
+            // dh_prev^T [units, paths] = W_hh^T . dG^T [4H, paths]
+            seq_acc_t acc;
 #pragma unroll
-            for (int pi = 0; pi < NPI; ++pi) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[pi][r] = 0.f;
-                const int pair = wave + 8 * pi;
-                if (pair >= 2 * n_rt) continue;
-                const int rt = pair % n_rt, grp = pair / n_rt;
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+            const bool has_pair = wave < 2 * n_rt;
+            const int rt = wave % n_rt, grp = wave / n_rt;
+            if (has_pair) {
                 const float4 *wq = reinterpret_cast<const float4 *>(A.wqt) + (size_t)rt * (hidden / 2) * 64 + lane;
                 const float *zl = &zg[(grp * 32 + (lane & 31)) * ZG + (lane >> 5)];
                 float4 wa = wq[0];
                 for (int q = 0; q < hidden / 2; ++q) {
                     const float4 wn = wq[(q + 1 < hidden / 2 ? q + 1 : q) * 64];
-                    acc[pi] = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.x, zl[2 * (4 * q + 0)], acc[pi], 0, 0, 0);
-                    acc[pi] = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.y, zl[2 * (4 * q + 1)], acc[pi], 0, 0, 0);
-                    acc[pi] = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.z, zl[2 * (4 * q + 2)], acc[pi], 0, 0, 0);
-                    acc[pi] = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.w, zl[2 * (4 * q + 3)], acc[pi], 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.x, zl[2 * (4 * q + 0)], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.y, zl[2 * (4 * q + 1)], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.z, zl[2 * (4 * q + 2)], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.w, zl[2 * (4 * q + 3)], acc, 0, 0, 0);
                     wa = wn;
                 }
             }
             __syncthreads();                               // every product has read the staged gradients
-#pragma unroll
-            for (int pi = 0; pi < NPI; ++pi) {
-                const int pair = wave + 8 * pi;
-                if (pair >= 2 * n_rt) continue;
-                const int rt = pair % n_rt, grp = pair / n_rt;
+            if (has_pair) {
                 const int j = grp * 32 + (lane & 31);
                 if (t < sdesc[j * 4 + 2]) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int row = rt * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-                        if (row < d + hidden) zg[j * ZG + row] = acc[pi][r];
+                        if (row < hidden) zg[j * ZG + row] = acc[r];
                     }
                 }
             }
             __syncthreads();
         }
-        // the first step's dx, and what is left: the gradient of the state the path started from
-        if (len > 0) {
-            for (int k = part * 4; k < d; k += 32) {
-                const float *pz = &zg[sj * ZG + k];
-                *reinterpret_cast<float4 *>(A.dx + (size_t)beg * d + k) = make_float4(pz[0], pz[1], pz[2], pz[3]);
+        // what is left: the gradient of the state the path started from
+        if (len > 0 && start >= 0) {
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const int u = part * 4 + 32 * it;
+                if (u >= hidden) continue;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    __hip_atomic_fetch_add(A.gh + (size_t)start * hidden + u + e, zg[sj * ZG + u + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(A.gc + (size_t)start * hidden + u + e, dcv[it][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
-            if (start >= 0) {
-#pragma unroll
-                for (int it = 0; it < IT; ++it) {
-                    const int u = part * 4 + 32 * it;
-                    if (u >= hidden) continue;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        __hip_atomic_fetch_add(A.gh + (size_t)start * hidden + u + e, zg[sj * ZG + d + u + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        __hip_atomic_fetch_add(A.gc + (size_t)start * hidden + u + e, dcv[it][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                }
-                if (A.pending) {
-                    // the eight threads of the path are lanes of one wavefront: once it has seen its atomics complete, one
-                    // of them counts the path off
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                    if (part == 0 && A.publish) __hip_atomic_fetch_sub(A.pending + start, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
+            if (A.pending) {
+                // the eight threads of the path are lanes of one wavefront: once it has seen its atomics complete, one
+                // of them counts the path off
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                if (part == 0 && A.publish) __hip_atomic_fetch_sub(A.pending + start, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         __syncthreads();
     }
 }
 
-// g_x[u] = the sum of the dx rows of the steps that read x[u]; one thread per (u, four columns)
-__global__ __launch_bounds__(256) void seq_input_grad_kernel(const int32_t *__restrict__ xt_ptr, const int32_t *__restrict__ xt_idx,
-                                                            const float *__restrict__ dx, float *__restrict__ g_x, int64_t n, int d) {
-    const int q = d / 4;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n * q; i += (int64_t)gridDim.x * 256) {
-        const int64_t u = i / q;
-        const int k = (int)(i % q) * 4;
-        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int32_t e = xt_ptr[u]; e < xt_ptr[u + 1]; ++e) {
-            const float4 v = *reinterpret_cast<const float4 *>(dx + (size_t)xt_idx[e] * d + k);
-            sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
-        }
-        *reinterpret_cast<float4 *>(g_x + (size_t)u * d + k) = sum;
-    }
-}
-
-// dWp [4H, kp] = sum over steps of dG[step] (x[in], h_prev)^T and dbp = sum of dG[step], on the matrix cores: the sum over
-// steps is the contraction.  A workgroup of 8 wavefronts stages 32 steps at a time in LDS (their dG rows and their
-// gathered (x[in], h_prev) rows), wavefront w accumulates row tile w of dWp (32 rows of dG) against all column tiles
-// (kp / 32, 16 registers each); every workgroup ends with its own partial sums, which a second kernel adds up in a
-// fixed order (so the weight gradients do not depend on timing) and writes in the layout of w_ih, w_hh and b.
+// Weight gradients: a contraction over many rows on the matrix cores, dW [4H, columns] = sum over rows of dG[row] z[row]^T.  A
+// workgroup of 8 wavefronts stages 32 rows at a time in LDS, wavefront w accumulates 32 rows of dW (tile w) against all
+// column tiles; every workgroup ends with its own partial sums, which a second kernel adds up in a fixed order (so the weight
+// gradients do not depend on timing).  blockIdx.y selects a slab of 256 rows of dW (hidden > 64 has two).
+//
+// SEG: the rows are cells, taken in the order of the input row they read (`at`, ascending `seg`), z is h_prev, and while a row of dG is in LDS
+// it is also added to s[seg], the sum of dG over the cells that read one node: dG is read once for both.  A workgroup takes a
+// contiguous range of rows; the part of a node that an earlier range began goes to edge_first, the part of one that a later range
+// goes on with to edge_last, and seq_edges_kernel adds those up in order.
+// Without SEG the rows are the nodes themselves: dG is s, z is x, and the column sums are the gradient of the bias.
 struct SeqWgradArgs {
-    const float *dg, *x, *tape_h, *h_state;
-    const int32_t *step_x, *step_prev;
-    int64_t cells;
-    int32_t d, hidden, kp;
-    float *partial;          // [gridDim.x][4H * kp + 4H]
+    const float *dg;         // [rows, 4H]
+    const float *z, *z2;     // SEG: tape_h and h_state; else x, z2 unused
+    const int32_t *at, *prev, *seg;   // SEG: cell, where its h_prev lives (>= 0: that tape row, -1: zero, <= -2: state row -(value) - 2), node; else at = used
+    int64_t rows, range;     // range: rows per workgroup, a multiple of the 32 staged at a time
+    int32_t cols, hidden;    // columns of z
+    float *partial;          // [gridDim.x][4H * 32 * column tiles + 4H]
+    float *s, *edge_first, *edge_last;   // SEG: [nodes, 4H], [gridDim.x, 4H] twice
 };
-constexpr int kSeqWgradCells = 32;
+constexpr int kSeqWgradRows = 32;
 constexpr int kSeqWgradGroups = 768;        // workgroups along x at most (three per compute unit)
 constexpr int64_t kSeqWgradPartialFloats = 64 << 20;   // and no more partial sums than this many floats
 
-// NCT: column tiles of 32 (kp / 32 rounded up to 4 or 8).  blockIdx.y selects a slab of 256 rows of dWp (hidden > 64 has two).
-template <int NCT, bool SLABS>
-__global__ __launch_bounds__(512, 2) void seq_weight_grad_kernel(SeqWgradArgs A) {
-    constexpr int CK = kSeqWgradCells, ZW = NCT * 32, RZ = NCT / 2;
+// NCT: column tiles of 32, rounded up to 1, 2, 4 or 8.
+template <int NCT, bool SEG>
+__global__ __launch_bounds__(512, NCT <= 4 ? 4 : 2) void seq_weight_grad_kernel(SeqWgradArgs A) {
+    constexpr int CK = kSeqWgradRows, ZW = NCT * 32, RZ = (CK * ZW / 4 + 511) / 512;
     __shared__ __align__(16) float sdg[CK][256];
     __shared__ __align__(16) float sz[CK][ZW];
+    __shared__ int32_t sseg[CK + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int rows = 4 * A.hidden, d = A.d, hidden = A.hidden, kp = A.kp;
-    const int row0 = SLABS ? blockIdx.y * 256 : 0, n_rt = (rows - row0 < 256 ? rows - row0 : 256) / 32, n_ct = kp / 32;
+    const int rows4 = 4 * A.hidden, cols = A.cols;
+    const int row0 = blockIdx.y * 256, n_rt = (rows4 - row0 < 256 ? rows4 - row0 : 256) / 32, n_ct = (cols + 31) / 32;
     seq_acc_t acc[NCT];
 #pragma unroll
     for (int c = 0; c < NCT; ++c)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
-    float accb = 0.f;                                      // thread i < 256: the sum of dG[.][row0 + i]
-    const int64_t chunks = (A.cells + CK - 1) / CK;
-    // the next 32 steps' rows are requested into registers before the products of the current ones
+    float sum = 0.f;                                       // thread i < 256: the running sum of dG[.][row0 + i]
+    const int64_t first = (int64_t)blockIdx.x * A.range, last = first + A.range < A.rows ? first + A.range : A.rows;
+    bool begun_before = false;                             // SEG: the running sum belongs to a node that an earlier range began
+    if (SEG && first > 0 && first < last) begun_before = A.seg[first - 1] == A.seg[first];
+    // the next 32 rows are requested into registers before the products of the current ones
     float4 rg[4], rz[RZ];
-    auto request = [&](int64_t ch) {
-        const int64_t c0 = ch * CK;
+    int32_t rs = -1, ig[4], iz[RZ];                        // and the places of those rows a chunk before that
+    auto request_ids = [&](int64_t c0) {
+        const int tid = seq_opaque(threadIdx.x), wave = tid >> 6;   // (indices are derived again in every phase: registers are short)
 #pragma unroll
         for (int v4 = 0; v4 < 4; ++v4) {
-            const int i = threadIdx.x + 512 * v4, c = i / 64, k = (i % 64) * 4;
-            rg[v4] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ch < chunks && c0 + c < A.cells && row0 + k < rows) rg[v4] = *reinterpret_cast<const float4 *>(A.dg + (size_t)(c0 + c) * rows + row0 + k);
+            const int64_t at = c0 + wave + 8 * v4;
+            ig[v4] = at < last ? (SEG ? A.at[at] : 0) : -1;
         }
 #pragma unroll
         for (int v4 = 0; v4 < RZ; ++v4) {
-            const int i = threadIdx.x + 512 * v4, c = i / (ZW / 4), k = (i % (ZW / 4)) * 4;
+            const int i = tid + 512 * v4, c = i / (ZW / 4);
+            iz[v4] = c < CK && c0 + c < last ? (SEG ? A.prev[c0 + c] : A.at[c0 + c]) : -1;
+        }
+    };
+    auto request = [&](int64_t c0) {
+        const int tid = seq_opaque(threadIdx.x), wave = tid >> 6, lane = tid & 63;
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+            const int c = wave + 8 * v4, k = lane * 4;     // a wavefront moves whole slabs of rows
+            rg[v4] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (ig[v4] >= 0 && row0 + k < rows4) {
+                const size_t row = SEG ? (size_t)ig[v4] : (size_t)(c0 + c);
+                rg[v4] = *reinterpret_cast<const float4 *>(A.dg + row * rows4 + row0 + k);
+            }
+        }
+#pragma unroll
+        for (int v4 = 0; v4 < RZ; ++v4) {
+            const int i = tid + 512 * v4, k = (i % (ZW / 4)) * 4, pv = iz[v4];
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ch < chunks && c0 + c < A.cells) {
-                if (k < d) v = *reinterpret_cast<const float4 *>(A.x + (size_t)A.step_x[c0 + c] * d + k);
-                else if (k < d + hidden) {
-                    const int pv = A.step_prev[c0 + c];
-                    if (pv >= 0) v = *reinterpret_cast<const float4 *>(A.tape_h + (size_t)pv * hidden + (k - d));
-                    else if (pv <= -2) v = *reinterpret_cast<const float4 *>(A.h_state + (size_t)(-pv - 2) * hidden + (k - d));
-                }
+            if (k < cols) {
+                if (pv >= 0) v = *reinterpret_cast<const float4 *>(A.z + (size_t)pv * cols + k);
+                else if (SEG && pv <= -2) v = *reinterpret_cast<const float4 *>(A.z2 + (size_t)(-pv - 2) * cols + k);
             }
             rz[v4] = v;
         }
+        if (SEG && tid <= CK) rs = c0 + tid < A.rows ? A.seg[c0 + tid] : -1;   // one more than the chunk: where the last row's node ends
     };
-    request(blockIdx.x);
-    for (int64_t ch = blockIdx.x; ch < chunks; ch += gridDim.x) {
+    if (first < last) {
+        request_ids(first);
+        request(first);
+        request_ids(first + CK);
+    }
+    for (int64_t c0 = first; c0 < last; c0 += CK) {
+        const int tid = seq_opaque(threadIdx.x), lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-            const int i = threadIdx.x + 512 * v4;
-            *reinterpret_cast<float4 *>(&sdg[i / 64][(i % 64) * 4]) = rg[v4];
-        }
+        for (int v4 = 0; v4 < 4; ++v4) *reinterpret_cast<float4 *>(&sdg[wave + 8 * v4][lane * 4]) = rg[v4];
 #pragma unroll
         for (int v4 = 0; v4 < RZ; ++v4) {
-            const int i = threadIdx.x + 512 * v4;
-            *reinterpret_cast<float4 *>(&sz[i / (ZW / 4)][(i % (ZW / 4)) * 4]) = rz[v4];
+            const int i = tid + 512 * v4;
+            if (i / (ZW / 4) < CK) *reinterpret_cast<float4 *>(&sz[i / (ZW / 4)][(i % (ZW / 4)) * 4]) = rz[v4];
         }
+        if (SEG && tid <= CK) sseg[tid] = rs;
         __syncthreads();
-        request(ch + gridDim.x);
+        if (c0 + CK < last) {
+            request(c0 + CK);
+            request_ids(c0 + 2 * CK);
+        }
         if (wave < n_rt) {
-#pragma unroll
+            constexpr int UNR = NCT == 4 ? 2 : 4;          // (unrolled further the operands of many steps are read at once, and spill)
+#pragma unroll UNR
             for (int st = 0; st < CK / 2; ++st) {
                 const int c = 2 * st + (lane >> 5);
                 const float a = sdg[c][wave * 32 + (lane & 31)];
 #pragma unroll
                 for (int ct = 0; ct < NCT; ++ct)
-                    if (ct < n_ct) acc[ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, sz[c][ct * 32 + (lane & 31)], acc[ct], 0, 0, 0);
+                    acc[ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, sz[c][ct * 32 + (lane & 31)], acc[ct], 0, 0, 0);
             }
         }
-        if ((int)threadIdx.x < 32 * n_rt) {
-#pragma unroll
-            for (int c = 0; c < CK; ++c) accb += sdg[c][threadIdx.x];
+        if (tid < 32 * n_rt) {
+            if (SEG) {
+                // bit c: the node of row c ends there, or the range does
+                const int here = last - c0 < CK ? (int)(last - c0) : CK;
+                const bool ends = lane < here && (sseg[lane & (CK - 1)] != sseg[(lane & (CK - 1)) + 1] || lane + 1 + c0 == last);
+                const uint32_t stops = (uint32_t)__ballot(ends);
+                const bool goes_on = here > 0 && c0 + here == last && sseg[here - 1] == sseg[here];   // the last row's node, beyond this range
+#pragma unroll 8
+                for (int c = 0; c < CK; ++c) {
+                    sum += sdg[c][tid];            // (rows past the end were staged as zeros)
+                    if (!((stops >> c) & 1)) continue;
+                    float *out = begun_before ? A.edge_first + (size_t)blockIdx.x * rows4
+                               : goes_on && c == here - 1 ? A.edge_last + (size_t)blockIdx.x * rows4 : A.s + (size_t)sseg[c] * rows4;
+                    out[row0 + tid] = sum;
+                    sum = 0.f;
+                    begun_before = false;
+                }
+            } else {
+#pragma unroll 8
+                for (int c = 0; c < CK; ++c) sum += sdg[c][tid];   // (rows past the end were staged as zeros)
+            }
         }
         __syncthreads();
     }
-    float *out = A.partial + (size_t)blockIdx.x * ((size_t)rows * kp + rows);
+    const int kp = NCT * 32;
+    float *out = A.partial + (size_t)blockIdx.x * ((size_t)rows4 * kp + rows4);
     if (wave < n_rt) {
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct) {
@@ -816,28 +1101,136 @@ __global__ __launch_bounds__(512, 2) void seq_weight_grad_kernel(SeqWgradArgs A)
             }
         }
     }
-    if ((int)threadIdx.x < 32 * n_rt) out[(size_t)rows * kp + row0 + threadIdx.x] = accb;
+    if (!SEG && (int)threadIdx.x < 32 * n_rt) out[(size_t)rows4 * kp + row0 + threadIdx.x] = sum;
 }
 
-// adds the workgroups' partial sums in index order and writes the usual layout: rows (unit, gate) -> gate-major rows,
-// columns split into the input and the hidden part
-__global__ __launch_bounds__(256) void seq_weight_grad_reduce_kernel(const float *__restrict__ partial, int groups, float *__restrict__ g_w_ih,
-                                                                    float *__restrict__ g_w_hh, float *__restrict__ g_b, int d, int hidden,
-                                                                    int kp) {
-    const int64_t per = (int64_t)4 * hidden * kp + 4 * hidden;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < per; i += (int64_t)gridDim.x * 256) {
-        float sum = 0.f;
-        for (int g = 0; g < groups; ++g) sum += partial[(size_t)g * per + i];
-        if (i < (int64_t)4 * hidden * kp) {
-            const int r = (int)(i / kp), k = (int)(i % kp);
-            const int row = (r & 3) * hidden + (r >> 2);
-            if (k < d) g_w_ih[(size_t)row * d + k] = sum;
-            else if (k < d + hidden) g_w_hh[(size_t)row * hidden + (k - d)] = sum;
-        } else {
-            const int r = (int)(i - (int64_t)4 * hidden * kp);
-            g_b[(r & 3) * hidden + (r >> 2)] = sum;
-        }
+// s of the nodes that several ranges share: the part of the range that begins the node, then those of the ranges that go on with
+// it, in order.  One workgroup per range whose last node goes on.
+__global__ __launch_bounds__(256) void seq_edges_kernel(const int32_t *__restrict__ seg, int64_t rows, int64_t range, const float *__restrict__ edge_first,
+                                                       const float *__restrict__ edge_last, float *__restrict__ s, int rows4) {
+    const int64_t first = (int64_t)blockIdx.x * range, last = first + range;
+    if (last >= rows) return;                              // the last range: nothing goes on
+    const int node = seg[last - 1];
+    if (seg[last] != node || (first > 0 && seg[first - 1] == node)) return;   // ends here, or began before this range
+    for (int k = threadIdx.x; k < rows4; k += 256) {
+        float sum = edge_last[(size_t)blockIdx.x * rows4 + k];
+        for (int64_t b = blockIdx.x + 1; b * range < rows && seg[b * range] == node; ++b) sum += edge_first[(size_t)b * rows4 + k];
+        s[(size_t)node * rows4 + k] = sum;
     }
+}
+
+// adds the workgroups' partial sums in a fixed order (eight interleaved sums, then those) and writes gate-major rows; `g_b` is NULL where
+// the column sums are not wanted.  32 outputs per workgroup, eight threads each.
+__global__ __launch_bounds__(256) void seq_weight_grad_reduce_kernel(const float *__restrict__ partial, int groups, float *__restrict__ g_w,
+                                                                    float *__restrict__ g_b, int cols, int hidden, int kp) {
+    __shared__ float part[8][32];
+    const int64_t per = (int64_t)4 * hidden * kp + 4 * hidden, wanted = g_b ? per : per - 4 * hidden;
+    const int o = threadIdx.x & 31, p = threadIdx.x >> 5;
+    const int64_t i = (int64_t)blockIdx.x * 32 + o;
+    const bool in_use = i < wanted && (i >= (int64_t)4 * hidden * kp || (int)(i % kp) < cols);   // (padding columns were never written)
+    float sum = 0.f;
+    if (in_use)
+        for (int g = p; g < groups; g += 8) sum += partial[(size_t)g * per + i];
+    part[p][o] = sum;
+    __syncthreads();
+    if (p != 0 || !in_use) return;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) sum += part[k][o];
+    if (i < (int64_t)4 * hidden * kp) {
+        const int r = (int)(i / kp), k = (int)(i % kp);
+        g_w[(size_t)((r & 3) * hidden + (r >> 2)) * cols + k] = sum;
+    } else {
+        const int r = (int)(i - (int64_t)4 * hidden * kp);
+        g_b[(r & 3) * hidden + (r >> 2)] = sum;
+    }
+}
+
+// g_x[used[i]] = W_ih^T s[i]: 64 nodes per workgroup, the gate rows in chunks of 128 through LDS, wavefront w taking column tiles w and w + 4.
+__global__ __launch_bounds__(256) void seq_input_grad_kernel(const float *__restrict__ s, const int32_t *__restrict__ used, int64_t n_used,
+                                                            const float *__restrict__ wxt, float *__restrict__ g_x, int d, int hidden) {
+    constexpr int KC = 128, ZS = KC + 2;
+    __shared__ __align__(16) float sh[64 * ZS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rows4 = 4 * hidden, n_dt = (d + 31) / 32;
+    const int64_t blocks = (n_used + 63) / 64;
+    for (int64_t bt = blockIdx.x; bt < blocks; bt += gridDim.x) {
+        seq_acc_t acc[2][2];                               // [column tile][half of the nodes]
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[a][g][r] = 0.f;
+        for (int k0 = 0; k0 < rows4; k0 += KC) {
+            const int kc = rows4 - k0 < KC ? rows4 - k0 : KC;   // a multiple of 32
+            __syncthreads();
+            for (int i = threadIdx.x; i < 64 * (KC / 4); i += 256) {
+                const int row = i / (KC / 4), k = (i % (KC / 4)) * 4;
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (bt * 64 + row < n_used && k < kc) v = *reinterpret_cast<const float4 *>(s + (size_t)(bt * 64 + row) * rows4 + k0 + k);
+                *reinterpret_cast<float2 *>(&sh[row * ZS + k]) = make_float2(v.x, v.y);
+                *reinterpret_cast<float2 *>(&sh[row * ZS + k + 2]) = make_float2(v.z, v.w);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const int tile = wave + 4 * a;
+                if (tile >= n_dt) continue;
+                const float4 *wq = reinterpret_cast<const float4 *>(wxt) + ((size_t)tile * (rows4 / 8) + k0 / 8) * 64 + lane;
+                const float *zl = &sh[(lane & 31) * ZS + (lane >> 5)];
+                for (int q = 0; q < kc / 8; ++q) {
+                    const float4 w = wq[q * 64];
+                    const float w4[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int g = 0; g < 2; ++g)
+                            acc[a][g] = __builtin_amdgcn_mfma_f32_32x32x2f32(zl[g * 32 * ZS + 2 * (4 * q + r)], w4[r], acc[a][g], 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            const int col = (wave + 4 * a) * 32 + (lane & 31);
+            if (col >= d) continue;
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t at = bt * 64 + g * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
+                    if (at < n_used) g_x[(size_t)used[at] * d + col] = acc[a][g][r];
+                }
+        }
+        __syncthreads();
+    }
+}
+
+// The two weight-gradient contractions: column tiles (as the kernel rounds them), floats of one workgroup's partial sums,
+// workgroups along x and rows per workgroup (a multiple of the rows staged at a time).
+struct SeqWgradShape { int nct; int64_t per, groups, range; };
+static SeqWgradShape seq_wgrad_shape(int64_t rows, int64_t cols, int64_t hidden) {
+    SeqWgradShape w;
+    const int64_t ct = (cols + 31) / 32;
+    w.nct = ct <= 1 ? 1 : ct <= 2 ? 2 : ct <= 4 ? 4 : 8;
+    w.per = 4 * hidden * 32 * w.nct + 4 * hidden;
+    const int64_t most = std::max<int64_t>(std::min<int64_t>(kSeqWgradGroups, kSeqWgradPartialFloats / w.per), 1);
+    const int64_t chunks = (rows + kSeqWgradRows - 1) / kSeqWgradRows;
+    const int64_t each = std::max<int64_t>((chunks + most - 1) / most, 1);
+    w.range = each * kSeqWgradRows;
+    w.groups = std::max<int64_t>((chunks + each - 1) / each, 1);
+    return w;
+}
+
+template <bool SEG>
+static int launch_wgrad(const SeqWgradArgs &g, const SeqWgradShape &w, int64_t hidden, hipStream_t s) {
+    const dim3 grid((unsigned)w.groups, (unsigned)((4 * hidden + 255) / 256)), block(512);
+    switch (w.nct) {
+        case 1: hipLaunchKernelGGL((seq_weight_grad_kernel<1, SEG>), grid, block, 0, s, g); break;
+        case 2: hipLaunchKernelGGL((seq_weight_grad_kernel<2, SEG>), grid, block, 0, s, g); break;
+        case 4: hipLaunchKernelGGL((seq_weight_grad_kernel<4, SEG>), grid, block, 0, s, g); break;
+        default: hipLaunchKernelGGL((seq_weight_grad_kernel<8, false>), grid, block, 0, s, g); break;   // (hidden has at most four column tiles)
+    }
+    HIP_TRY(hipGetLastError());
+    return HAG_OK;
 }
 
 }  // namespace hag
@@ -987,24 +1380,27 @@ int hag_seq_create(int64_t n, const int64_t *rowptr, const int32_t *col, int64_t
         }
         {
             const int64_t cells = (int64_t)h->step_x.size(), np = (int64_t)(h->paths.size() / 4);
-            h->step_prev.assign((size_t)cells, -1);
+            std::vector<int32_t> step_prev((size_t)cells, -1);
             h->pending_init.assign((size_t)std::max<int64_t>(h->n_states, 1), 0);
             for (int64_t i = 0; i < np; ++i) {
                 const int32_t start = h->paths[i * 4], beg = h->paths[i * 4 + 1], len = h->paths[i * 4 + 2];
                 if (start >= 0 && len > 0) ++h->pending_init[start];
-                for (int32_t t = 0; t < len; ++t) h->step_prev[(size_t)beg + t] = t > 0 ? beg + t - 1 : (start >= 0 ? -start - 2 : -1);
+                for (int32_t t = 0; t < len; ++t) step_prev[(size_t)beg + t] = t > 0 ? beg + t - 1 : (start >= 0 ? -start - 2 : -1);
             }
-            h->xt_ptr.assign((size_t)n + 1, 0);
-            for (int64_t a2 = 0; a2 < cells; ++a2) ++h->xt_ptr[(size_t)h->step_x[a2] + 1];
-            for (int64_t u = 0; u < n; ++u) h->xt_ptr[(size_t)u + 1] += h->xt_ptr[u];
+            std::vector<int32_t> xt_ptr((size_t)n + 1, 0);
+            for (int64_t a2 = 0; a2 < cells; ++a2) ++xt_ptr[(size_t)h->step_x[a2] + 1];
+            for (int64_t u = 0; u < n; ++u) xt_ptr[(size_t)u + 1] += xt_ptr[u];
             h->xt_idx.resize((size_t)cells);
             std::vector<int32_t> place((size_t)n, 0);
             for (int64_t u = 0; u < n; ++u)
-                if (h->xt_ptr[(size_t)u + 1] > h->xt_ptr[u]) { place[u] = (int32_t)h->used.size(); h->used.push_back((int32_t)u); }
+                if (xt_ptr[(size_t)u + 1] > xt_ptr[u]) { place[u] = (int32_t)h->used.size(); h->used.push_back((int32_t)u); }
             h->step_g.resize((size_t)cells);
             for (int64_t a2 = 0; a2 < cells; ++a2) h->step_g[a2] = place[h->step_x[a2]];
-            std::vector<int32_t> at(h->xt_ptr.begin(), h->xt_ptr.end() - 1);
+            std::vector<int32_t> at(xt_ptr.begin(), xt_ptr.end() - 1);
             for (int64_t a2 = 0; a2 < cells; ++a2) h->xt_idx[(size_t)at[h->step_x[a2]]++] = (int32_t)a2;
+            h->xt_prev.resize((size_t)cells);
+            h->xt_seg.resize((size_t)cells);
+            for (int64_t k = 0; k < cells; ++k) { h->xt_prev[k] = step_prev[h->xt_idx[k]]; h->xt_seg[k] = h->step_g[h->xt_idx[k]]; }
         }
         *out = h;
         return HAG_OK;
@@ -1022,10 +1418,10 @@ void hag_seq_free(hag_seq_t *h) {
     if (h->d_final) (void)hipFree(h->d_final);
     if (h->d_paths) (void)hipFree(h->d_paths);
     if (h->d_paths_by_depth) (void)hipFree(h->d_paths_by_depth);
-    if (h->d_step_prev) (void)hipFree(h->d_step_prev);
+    if (h->d_xt_prev) (void)hipFree(h->d_xt_prev);
+    if (h->d_xt_seg) (void)hipFree(h->d_xt_seg);
     if (h->d_used) (void)hipFree(h->d_used);
     if (h->d_step_g) (void)hipFree(h->d_step_g);
-    if (h->d_xt_ptr) (void)hipFree(h->d_xt_ptr);
     if (h->d_xt_idx) (void)hipFree(h->d_xt_idx);
     if (h->d_pending_init) (void)hipFree(h->d_pending_init);
     if (h->d_step_x) (void)hipFree(h->d_step_x);
@@ -1050,13 +1446,10 @@ static const seq_kernel_t kSeqVariants[3] = {seq_chain_kernel<32, false>, seq_ch
 // the same with the tape written (training)
 static const seq_kernel_t kSeqTapeVariants[3] = {seq_chain_kernel<32, true>, seq_chain_kernel<64, true>, seq_chain_kernel<128, true>};
 static unsigned seq_block(int variant) { return variant == 2 ? 1024 : 512; }
-// D + H padded to the column tiles of the backward kernels
-static int64_t seq_kp(int64_t d, int64_t hidden) {
-    if (hidden <= 64 && d + hidden <= 128) return d + hidden <= 64 ? 64 : 128;
-    return d + hidden <= 192 ? 192 : 256;
-}
 typedef void (*seq_reverse_t)(SeqRevArgs);
-static const seq_reverse_t kSeqReverseVariants[3] = {seq_reverse_kernel<false, 1>, seq_reverse_kernel<false, 2>, seq_reverse_kernel<true, 2>};
+static const seq_reverse_t kSeqReverseVariants[3] = {seq_reverse_kernel<32>, seq_reverse_kernel<64>, seq_reverse_wide_kernel};
+// how often a path that starts from a state is counted off: once per wavefront that sends a part of its gradients, or once
+static int32_t seq_reverse_counts(int64_t hidden) { return hidden > 64 ? 1 : (int32_t)(hidden / 8); }
 
 int hag_seq_get_plan(const hag_seq_t *h, int32_t order, int64_t *n_states, int64_t *n_paths, const int32_t **paths,
                      const int32_t **step_x, const int32_t **step_out, int64_t *n_levels, const int64_t **level_ptr,
@@ -1099,10 +1492,10 @@ int hag_seq_upload(hag_seq_t *h) {
     }
     HIP_TRY(put(&h->d_step_x, h->step_x));
     HIP_TRY(put(&h->d_step_out, h->step_out));
-    HIP_TRY(put(&h->d_step_prev, h->step_prev));
+    HIP_TRY(put(&h->d_xt_prev, h->xt_prev));
+    HIP_TRY(put(&h->d_xt_seg, h->xt_seg));
     HIP_TRY(put(&h->d_used, h->used));
     HIP_TRY(put(&h->d_step_g, h->step_g));
-    HIP_TRY(put(&h->d_xt_ptr, h->xt_ptr));
     HIP_TRY(put(&h->d_xt_idx, h->xt_idx));
     HIP_TRY(put(&h->d_pending_init, h->pending_init));
     HIP_TRY(put(&h->d_gave_up, std::vector<int32_t>(1, 0)));
@@ -1118,7 +1511,7 @@ int hag_seq_upload(hag_seq_t *h) {
             HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqTapeVariants[k], (int)seq_block(k), 0));
             h->resident_tape[k] = (int64_t)std::min(per_cu, 2) * cus;
             HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqReverseVariants[k], 512, 0));
-            h->resident_reverse[k] = (int64_t)std::min(per_cu, k == 2 ? 1 : 2) * cus;
+            h->resident_reverse[k] = (int64_t)std::min(per_cu, 2) * cus;
         }
     }
     HIP_TRY(put(&h->d_final, h->final_state));
@@ -1237,27 +1630,30 @@ int hag_seq_lstm_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const fl
     return seq_forward(h, d, hidden, x, w_ih, w_hh, b, a_out, workspace, stream, nullptr, nullptr, nullptr);
 }
 
-// workgroups (along x) of the weight-gradient kernel at most: each leaves one set of partial sums
-static int64_t seq_wgrad_groups(size_t per) { return std::max<int64_t>(std::min<int64_t>(kSeqWgradGroups, kSeqWgradPartialFloats / (int64_t)per), 1); }
-
 // Layout of the training workspace: the forward workspace, then the tape and the backward pass's own buffers.
-struct SeqTrainLayout { size_t fwd, tape_g, tape_c, tape_h, dx, gh, gc, pending, wqt, partial, total; };
+struct SeqTrainLayout { SeqWgradShape hh, ih; size_t fwd, tape_g, tape_c, tape_h, gh, gc, pending, wqt, wxt, s, edge_first, edge_last, partial_hh, partial_ih, total; };
 static SeqTrainLayout seq_train_layout(const hag_seq_t *h, int64_t d, int64_t hidden) {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t cells = std::max<size_t>(h->step_x.size(), 1), states = (size_t)std::max<int64_t>(h->n_states, 1);
-    const size_t kp = (size_t)seq_kp(d, hidden), H = (size_t)hidden, f = sizeof(float);
+    const size_t H = (size_t)hidden, f = sizeof(float), used = std::max<size_t>(h->used.size(), 1);
     SeqTrainLayout L;
+    L.hh = seq_wgrad_shape((int64_t)h->step_x.size(), hidden, hidden);
+    L.ih = seq_wgrad_shape((int64_t)h->used.size(), d, hidden);
     size_t at = up(hag_seq_workspace_bytes(h, d, hidden));
     L.fwd = 0;
     L.tape_g = at; at += up(cells * 4 * H * f);
     L.tape_c = at; at += up(cells * H * f);
     L.tape_h = at; at += up(cells * H * f);
-    L.dx = at; at += up(cells * (size_t)d * f);
     L.gh = at; at += up(states * H * f);
     L.gc = at; at += up(states * H * f);
     L.pending = at; at += up(states * sizeof(int32_t));
-    L.wqt = at; at += up(kp * 4 * H * f);
-    L.partial = at; at += up((size_t)seq_wgrad_groups(4 * H * kp + 4 * H) * (4 * H * kp + 4 * H) * f);
+    L.wqt = at; at += up((H + 31) / 32 * 32 * 4 * H * f);
+    L.wxt = at; at += up(((size_t)d + 31) / 32 * 32 * 4 * H * f);
+    L.s = at; at += up(used * 4 * H * f);
+    L.edge_first = at; at += up((size_t)L.hh.groups * 4 * H * f);
+    L.edge_last = at; at += up((size_t)L.hh.groups * 4 * H * f);
+    L.partial_hh = at; at += up((size_t)L.hh.groups * (size_t)L.hh.per * f);
+    L.partial_ih = at; at += up((size_t)L.ih.groups * (size_t)L.ih.per * f);
     L.total = at;
     return L;
 }
@@ -1296,37 +1692,39 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
     if (!x || !w_ih || !w_hh || !g_a || !g_x || !g_w_ih || !g_w_hh || !g_b || !workspace) { set_error("NULL pointer"); return HAG_EINVAL; }
     if (((uintptr_t)x | (uintptr_t)workspace | (uintptr_t)g_a | (uintptr_t)g_x) & 15) { set_error("x, g_a, g_x and workspace must be 16-byte aligned"); return HAG_EINVAL; }
     hipStream_t s = (hipStream_t)stream;
-    const int kp = (int)seq_kp(d, hidden);
     const SeqTrainLayout L = seq_train_layout(h, d, hidden);
     char *w = (char *)workspace;
     const SeqLayout F = seq_layout(h, d, hidden);           // the forward pass left its state rows there
     const float *hst = (const float *)(w + F.h), *cst = (const float *)(w + F.c);
     float *tape_g = (float *)(w + L.tape_g), *tape_c = (float *)(w + L.tape_c), *tape_h = (float *)(w + L.tape_h);
-    float *dx = (float *)(w + L.dx), *gh = (float *)(w + L.gh), *gc = (float *)(w + L.gc), *wqt = (float *)(w + L.wqt);
-    float *partial = (float *)(w + L.partial);
-    const int64_t cells = (int64_t)h->step_x.size();
+    float *gh = (float *)(w + L.gh), *gc = (float *)(w + L.gc), *wqt = (float *)(w + L.wqt), *wxt = (float *)(w + L.wxt), *sums = (float *)(w + L.s);
+    const int64_t cells = (int64_t)h->step_x.size(), n_used = (int64_t)h->used.size();
     auto blocks = [](int64_t total) { return dim3((unsigned)std::min<int64_t>((total + 255) / 256, 65535 * 16)); };
-    // gradient rows of the kept states start at zero (gh and gc are adjacent)
+    // gradient rows of the kept states start at zero (gh and gc are adjacent); nodes that no list names have no gradient
     {
         const int64_t total = (int64_t)((L.pending - L.gh) / sizeof(float));
         hipLaunchKernelGGL(seq_fill_kernel, blocks(total), dim3(256), 0, s, gh, total);
         HIP_TRY(hipGetLastError());
+        if (n_used < h->n) {
+            hipLaunchKernelGGL(seq_fill_kernel, blocks(h->n * d), dim3(256), 0, s, g_x, h->n * d);
+            HIP_TRY(hipGetLastError());
+        }
     }
     {
-        const int64_t total = (int64_t)kp * 4 * hidden;
-        hipLaunchKernelGGL(seq_pack_transposed_kernel, blocks(total), dim3(256), 0, s, w_ih, w_hh, wqt, (int)d, (int)hidden, kp);
+        const int64_t total = 4 * hidden * std::max((hidden + 31) / 32, (d + 31) / 32) * 32;
+        hipLaunchKernelGGL(seq_pack_transposed_kernel, blocks(total), dim3(256), 0, s, w_ih, w_hh, wqt, wxt, (int)d, (int)hidden);
         HIP_TRY(hipGetLastError());
         const int64_t nh = h->n * hidden;
         hipLaunchKernelGGL(seq_final_grad_kernel, blocks(nh), dim3(256), 0, s, h->d_final, g_a, gh, h->n, (int)hidden);
         HIP_TRY(hipGetLastError());
     }
     const int64_t levels = (int64_t)h->tile_ptr.size() - 1;
-    const int rv = hidden > 64 ? 2 : (kp > 128 ? 1 : 0);
+    const int rv = seq_variant(hidden);
     const int64_t resident = h->resident_reverse[rv];
     const bool fused = levels > 1 && h->one_launch && resident > 0;
     int32_t *pending = (int32_t *)(w + L.pending);
     if (fused) {
-        hipLaunchKernelGGL(seq_copy_i32_kernel, blocks(h->n_states), dim3(256), 0, s, h->d_pending_init, pending, h->n_states);
+        hipLaunchKernelGGL(seq_scale_i32_kernel, blocks(h->n_states), dim3(256), 0, s, h->d_pending_init, pending, h->n_states, seq_reverse_counts(hidden));
         HIP_TRY(hipGetLastError());
     }
     for (int64_t l = fused ? 0 : levels - 1; l >= 0; --l) {
@@ -1340,33 +1738,43 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
         r.spin_limit = h->spin_limit;
         r.publish = h->wait_unreachable ? 0 : 1;
         r.step_out = h->d_step_out;
-        r.wqt = wqt; r.tape_g = tape_g; r.tape_c = tape_c; r.c_state = cst; r.g_a = g_a; r.gh = gh; r.gc = gc; r.dx = dx;
-        r.d = (int32_t)d; r.hidden = (int32_t)hidden; r.kp = kp;
+        r.wqt = wqt; r.tape_g = tape_g; r.tape_c = tape_c; r.c_state = cst; r.g_a = g_a; r.gh = gh; r.gc = gc;
+        r.hidden = (int32_t)hidden;
         if (r.n_path_tiles <= 0) continue;
-        const int64_t cap = fused ? resident : (rv == 2 ? 256 : 512);
+        const int64_t cap = fused ? resident : 512;
         hipLaunchKernelGGL(kSeqReverseVariants[rv], dim3((unsigned)std::min<int64_t>(r.n_path_tiles, cap)), dim3(512), 0, s, r);
         HIP_TRY(hipGetLastError());
     }
     {
-        const int64_t total = h->n * (d / 4);
-        hipLaunchKernelGGL(seq_input_grad_kernel, blocks(total), dim3(256), 0, s, h->d_xt_ptr, h->d_xt_idx, dx, g_x, h->n, (int)d);
+        // recurrent weights and the per-node sums of dG, over the cells
+        SeqWgradArgs g{};
+        g.dg = tape_g; g.z = tape_h; g.z2 = hst; g.at = h->d_xt_idx; g.prev = h->d_xt_prev; g.seg = h->d_xt_seg;
+        g.rows = cells; g.range = L.hh.range; g.cols = (int32_t)hidden; g.hidden = (int32_t)hidden;
+        g.partial = (float *)(w + L.partial_hh); g.s = sums; g.edge_first = (float *)(w + L.edge_first); g.edge_last = (float *)(w + L.edge_last);
+        if (int rc = launch_wgrad<true>(g, L.hh, hidden, s)) return rc;
+        if (L.hh.groups > 1) {
+            hipLaunchKernelGGL(seq_edges_kernel, dim3((unsigned)L.hh.groups), dim3(256), 0, s, h->d_xt_seg, cells, L.hh.range, g.edge_first, g.edge_last,
+                               sums, (int)(4 * hidden));
+            HIP_TRY(hipGetLastError());
+        }
+        hipLaunchKernelGGL(seq_weight_grad_reduce_kernel, dim3((unsigned)((L.hh.per + 31) / 32)), dim3(256), 0, s, g.partial, (int)L.hh.groups, g_w_hh,
+                           (float *)nullptr, (int)hidden, (int)hidden, 32 * L.hh.nct);
         HIP_TRY(hipGetLastError());
     }
     {
-        SeqWgradArgs g;
-        g.dg = tape_g; g.x = x; g.tape_h = tape_h; g.h_state = hst; g.step_x = h->d_step_x; g.step_prev = h->d_step_prev;
-        g.cells = cells; g.d = (int32_t)d; g.hidden = (int32_t)hidden; g.kp = kp; g.partial = partial;
-        const int64_t chunks = (cells + kSeqWgradCells - 1) / kSeqWgradCells;
-        const int64_t per = (int64_t)4 * hidden * kp + 4 * hidden;
-        const int groups = (int)std::max<int64_t>(std::min<int64_t>(chunks, seq_wgrad_groups((size_t)per)), 1);
-        const dim3 grid((unsigned)groups, (unsigned)((4 * hidden + 255) / 256));
-        if (hidden > 64) hipLaunchKernelGGL((seq_weight_grad_kernel<8, true>), grid, dim3(512), 0, s, g);
-        else if (kp > 128) hipLaunchKernelGGL((seq_weight_grad_kernel<8, false>), grid, dim3(512), 0, s, g);
-        else hipLaunchKernelGGL((seq_weight_grad_kernel<4, false>), grid, dim3(512), 0, s, g);
+        // input weights, bias and g_x, over the nodes
+        SeqWgradArgs g{};
+        g.dg = sums; g.z = x; g.at = h->d_used;
+        g.rows = n_used; g.range = L.ih.range; g.cols = (int32_t)d; g.hidden = (int32_t)hidden; g.partial = (float *)(w + L.partial_ih);
+        if (int rc = launch_wgrad<false>(g, L.ih, hidden, s)) return rc;
+        hipLaunchKernelGGL(seq_weight_grad_reduce_kernel, dim3((unsigned)((L.ih.per + 31) / 32)), dim3(256), 0, s, g.partial, (int)L.ih.groups, g_w_ih, g_b,
+                           (int)d, (int)hidden, 32 * L.ih.nct);
         HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(seq_weight_grad_reduce_kernel, blocks(per), dim3(256), 0, s, partial, groups, g_w_ih, g_w_hh, g_b, (int)d,
-                           (int)hidden, kp);
-        HIP_TRY(hipGetLastError());
+        if (n_used > 0) {
+            hipLaunchKernelGGL(seq_input_grad_kernel, dim3((unsigned)std::min<int64_t>((n_used + 63) / 64, 1 << 20)), dim3(256), 0, s, sums, h->d_used, n_used,
+                               wxt, g_x, (int)d, (int)hidden);
+            HIP_TRY(hipGetLastError());
+        }
     }
     return HAG_OK;
 }

@@ -475,7 +475,7 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                         if constexpr (C_LDS) *reinterpret_cast<float4 *>(&cs[j][unit0]) = c4;
                         else creg[g] = c4;
                         // (the gates and h leave further down, in larger pieces)
-                        if constexpr (TAPE) *reinterpret_cast<float4 *>(A.tape_c + (size_t)(beg + t) * hidden + unit0) = c4;
+                        if constexpr (TAPE) st4_stream(A.tape_c + (size_t)(beg + t) * hidden + unit0, c4);
                         if (keep[g] >= 0) {                // a state that another path starts from, or some a_v
                             const size_t o = (size_t)keep[g] * hidden + unit0;
                             if (A.flags) {
@@ -505,8 +505,8 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                             const int jj = (group0 + g) * 32 + 16 * q + (l & 15);
                             if (t < sdesc[jj * 4 + 2]) {
                                 float *p = A.tape_g + ((size_t)(sdesc[jj * 4 + 1] + t) * hidden + tile * 8 + seq_piece(l)) * 4;
-                                *reinterpret_cast<float4 *>(p) = v[2 * q];
-                                *reinterpret_cast<float4 *>(p + 16) = v[2 * q + 1];
+                                st4_stream(p, v[2 * q]);   // (streaming stores: nothing reads the tape before the backward pass)
+                                st4_stream(p + 16, v[2 * q + 1]);
                             }
                         }
                     }
@@ -532,7 +532,7 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                             h[0] += __uint_as_float(w.x << 16); h[1] += __uint_as_float(w.x & 0xffff0000u);
                             h[2] += __uint_as_float(w.y << 16); h[3] += __uint_as_float(w.y & 0xffff0000u);
                         }
-                        *reinterpret_cast<float4 *>(A.tape_h + cell + u) = make_float4(h[0], h[1], h[2], h[3]);
+                        st4_stream(A.tape_h + cell + u, make_float4(h[0], h[1], h[2], h[3]));
                     }
                 }
             }
@@ -573,8 +573,8 @@ struct SeqRevArgs {
     const float *c_state;    // c rows of the kept states
     const float *g_a;        // [n, H]
     float *gh, *gc;          // [n_states, H]
-    // all levels in one launch (NULL: one launch per level): per kept state what is still to come from the paths that start
-    // from it (one count per path, or per path and wavefront, see seq_reverse_counts); tiles are taken last first
+    // all levels in one launch (NULL: one launch per level): per kept state the number of paths that start from it
+    // and have not sent their gradients yet; tiles are taken last first
     int32_t *pending;
     int32_t *gave_up;
     int32_t spin_limit, reversed;
@@ -583,8 +583,8 @@ struct SeqRevArgs {
 };
 
 
-__global__ __launch_bounds__(256) void seq_scale_i32_kernel(const int32_t *__restrict__ src, int32_t *__restrict__ dst, int64_t n, int32_t factor) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) dst[i] = src[i] * factor;
+__global__ __launch_bounds__(256) void seq_copy_i32_kernel(const int32_t *__restrict__ src, int32_t *__restrict__ dst, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) dst[i] = src[i];
 }
 
 __global__ __launch_bounds__(256) void seq_fill_kernel(float *p, int64_t n) {
@@ -788,30 +788,42 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
             }
             __syncthreads();                               // the parts of dh_prev are complete
         }
-        // what is left: the gradient of the state the path started from
-        if (on) {
-            bool sent = false;
+        // What is left: the gradient of the state the path started from, as rows in LDS first, so that one atomic instruction
+        // covers a row of 256 contiguous bytes (issued by the lanes that hold the values, four bytes of each of 64 rows per
+        // instruction, they took most of the kernel's time: the memory side does about 17 such requests per ns).
+        bool any = false;
+        if (threadIdx.x < kSeqJobs) any = sdesc[threadIdx.x * 4] >= 0;
+        if (__syncthreads_or(any)) {
+            float4 rows[JG];
 #pragma unroll
             for (int g = 0; g < JG; ++g) {
-                const int j = (group0 + g) * 32 + (lane & 31), start = sdesc[j * 4], len = sdesc[j * 4 + 2];
-                if (len > 0 && start >= 0) {
-                    sum_parts(g, j);
-                    sent = true;
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        __hip_atomic_fetch_add(A.gh + (size_t)start * hidden + unit0 + m, dh[g][m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        __hip_atomic_fetch_add(A.gc + (size_t)start * hidden + unit0 + m, dc[g][m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                }
+                const int j = (group0 + g) * 32 + (lane & 31);
+                if (on) sum_parts(g, j);
+                rows[g] = make_float4(dh[g][0], dh[g][1], dh[g][2], dh[g][3]);
             }
-            if (A.pending && __any(sent)) {
-                // once the wavefront has seen its atomics complete, the path is counted off for this wavefront
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (on) {
 #pragma unroll
                 for (int g = 0; g < JG; ++g) {
-                    const int j = (group0 + g) * 32 + (lane & 31), start = sdesc[j * 4], len = sdesc[j * 4 + 2];
-                    if (len > 0 && start >= 0 && half == 0 && A.publish) __hip_atomic_fetch_sub(A.pending + start, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int j = (group0 + g) * 32 + (lane & 31);
+                    *reinterpret_cast<float4 *>(&red[0][j][unit0]) = rows[g];
+                    *reinterpret_cast<float4 *>(&red[1][j][unit0]) = make_float4(dc[g][0], dc[g][1], dc[g][2], dc[g][3]);
                 }
+            }
+            __syncthreads();
+            for (int j = wave; j < kSeqJobs; j += 8) {
+                const int start = sdesc[j * 4];
+                if (start < 0) continue;                   // (the same for the whole wavefront; an empty path starts nowhere)
+                if (lane < hidden) {
+                    __hip_atomic_fetch_add(A.gh + (size_t)start * hidden + lane, red[0][j][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(A.gc + (size_t)start * hidden + lane, red[1][j][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+            if (A.pending) {
+                // once the wavefront has seen its atomics complete, its paths are counted off
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                const int start = lane < 8 ? sdesc[(wave + 8 * lane) * 4] : -1;
+                if (start >= 0 && A.publish) __hip_atomic_fetch_sub(A.pending + start, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         __syncthreads();
@@ -929,23 +941,30 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_wide_kernel(SeqRevArgs A) 
             }
             __syncthreads();
         }
-        // what is left: the gradient of the state the path started from
-        if (len > 0 && start >= 0) {
+        // what is left: the gradient of the state the path started from, dh beside dc in the path's row, added by whole wavefronts so
+        // that an atomic instruction covers contiguous bytes
+        if (__syncthreads_or(start >= 0)) {
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
                 const int u = part * 4 + 32 * it;
                 if (u >= hidden) continue;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    __hip_atomic_fetch_add(A.gh + (size_t)start * hidden + u + e, zg[sj * ZG + u + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_fetch_add(A.gc + (size_t)start * hidden + u + e, dcv[it][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int e = 0; e < 4; ++e) zg[sj * ZG + 128 + u + e] = dcv[it][e];
+            }
+            __syncthreads();
+            for (int j = wave; j < kSeqJobs; j += 8) {
+                const int from = sdesc[j * 4];
+                if (from < 0) continue;
+                for (int u = lane; u < hidden; u += 64) {
+                    __hip_atomic_fetch_add(A.gh + (size_t)from * hidden + u, zg[j * ZG + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(A.gc + (size_t)from * hidden + u, zg[j * ZG + 128 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
             if (A.pending) {
-                // the eight threads of the path are lanes of one wavefront: once it has seen its atomics complete, one
-                // of them counts the path off
+                // once the wavefront has seen its atomics complete, its paths are counted off
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                if (part == 0 && A.publish) __hip_atomic_fetch_sub(A.pending + start, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int from = lane < 8 ? sdesc[(wave + 8 * lane) * 4] : -1;
+                if (from >= 0 && A.publish) __hip_atomic_fetch_sub(A.pending + from, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         __syncthreads();
@@ -1448,8 +1467,6 @@ static const seq_kernel_t kSeqTapeVariants[3] = {seq_chain_kernel<32, true>, seq
 static unsigned seq_block(int variant) { return variant == 2 ? 1024 : 512; }
 typedef void (*seq_reverse_t)(SeqRevArgs);
 static const seq_reverse_t kSeqReverseVariants[3] = {seq_reverse_kernel<32>, seq_reverse_kernel<64>, seq_reverse_wide_kernel};
-// how often a path that starts from a state is counted off: once per wavefront that sends a part of its gradients, or once
-static int32_t seq_reverse_counts(int64_t hidden) { return hidden > 64 ? 1 : (int32_t)(hidden / 8); }
 
 int hag_seq_get_plan(const hag_seq_t *h, int32_t order, int64_t *n_states, int64_t *n_paths, const int32_t **paths,
                      const int32_t **step_x, const int32_t **step_out, int64_t *n_levels, const int64_t **level_ptr,
@@ -1724,7 +1741,7 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
     const bool fused = levels > 1 && h->one_launch && resident > 0;
     int32_t *pending = (int32_t *)(w + L.pending);
     if (fused) {
-        hipLaunchKernelGGL(seq_scale_i32_kernel, blocks(h->n_states), dim3(256), 0, s, h->d_pending_init, pending, h->n_states, seq_reverse_counts(hidden));
+        hipLaunchKernelGGL(seq_copy_i32_kernel, blocks(h->n_states), dim3(256), 0, s, h->d_pending_init, pending, h->n_states);
         HIP_TRY(hipGetLastError());
     }
     for (int64_t l = fused ? 0 : levels - 1; l >= 0; --l) {

@@ -15,7 +15,7 @@ SOURCES = [os.path.join(HERE, "csrc", f) for f in (
     # the gather and component kernels are instantiated for many widths and roles: one unit per
     # element type (and reduction) so that they compile side by side
     "hag_gather_f32_sum.hip", "hag_gather_f32_max.hip", "hag_gather_i32_sum.hip", "hag_gather_i32_max.hip",
-    "hag_component_f32.hip", "hag_component_i32.hip")]
+    "hag_component_f32.hip", "hag_component_i32.hip", "hag_dense.hip")]
 HEADERS = [os.path.join(HERE, "csrc", f) for f in ("hag_internal.hpp", "hag_device_common.hpp", "hag_gather.inc",
                                                    "hag_component.inc")] + [os.path.join(ROOT, "include", "hag.h")]
 

@@ -318,6 +318,18 @@ struct CompArgs {
     int32_t stream_out;          // output rows are written with streaming stores
 };
 
+// Product of a component's adjacency bits with its feature rows (hag_dense.hip).
+struct DenseArgs {
+    const int32_t *meta;         // per component: first node, #nodes, first word of its bits, 0
+    const uint32_t *bits;        // per component: row r is ceil(#nodes / 32) words, bit k of them set if k is summed into r
+    const float *in;
+    float *out;
+    const float *scale_in, *scale_out;
+    int32_t add_self;            // gcn: the node's own row (scaled like the others) is added
+    int32_t d, count;
+    int32_t m_chunks, f_chunks;  // set by launch_dense: wavefronts per component, along its rows and its feature columns
+};
+
 static inline int hip_fail(hipError_t e, const char *what) {
     set_error(std::string(what) + ": " + hipGetErrorString(e));
     return HAG_EHIP;
@@ -348,5 +360,8 @@ int launch_fused(const FusedArgs<T> &a, hipStream_t s);
 template <typename T>
 int launch_component_kernel(const CompArgs<T> &a, int role, int64_t d, unsigned components, unsigned column_parts,
                             size_t lds_bytes, hipStream_t s);
+
+// role: as launch_component_kernel
+int launch_dense(DenseArgs a, int role, int max_nodes, hipStream_t s);
 
 }  // namespace hag

@@ -977,6 +977,40 @@ static void build_components(hag_handle *h) {
         c.meta[4 * k + 2] = c.agg_ptr[k];
         c.meta[4 * k + 3] = (c.agg_ptr[k + 1] - c.agg_ptr[k]) | ((int32_t)c.n_stages[k] << 16);
     }
+    // Adjacency bits for the dense form, unless one of the knobs of the list form is given (HAG_COMPONENT_DENSE: 0 never, 1 by the rule of
+    // dense_applies, 2 always)
+    const bool list_knob = env_i64("HAG_COMPONENT_EXPAND", -1) != -1 || env_i64("HAG_COMPONENT_PAD", 0) != 0 ||
+                           env_i64("HAG_COMPONENT_EXTRA_LDS", 0) != 0 || env_i64("HAG_STREAM_OUTPUT", 0) != 0;
+    const int64_t want = env_i64("HAG_COMPONENT_DENSE", list_knob ? 0 : 1);
+    if (c.max_nodes <= kDenseMaxNodes && want != 0) {
+        int64_t words = 0;
+        c.dense_meta.resize(4 * (size_t)c.count);
+        for (int32_t k = 0; k < c.count; ++k) {
+            const int32_t nv = c.node_ptr[k + 1] - c.node_ptr[k];
+            c.dense_meta[4 * k + 0] = c.node_ptr[k];
+            c.dense_meta[4 * k + 1] = nv;
+            c.dense_meta[4 * k + 2] = (int32_t)words;
+            c.dense_meta[4 * k + 3] = 0;
+            words += (int64_t)nv * ((nv + 31) / 32);
+            if (words >= (int64_t)INT32_MAX) { c.dense_meta.clear(); break; }
+        }
+        if (!c.dense_meta.empty()) {
+            c.dense_fwd.assign((size_t)words, 0);
+            c.dense_bwd.assign((size_t)words, 0);
+            for (int32_t k = 0; k < c.count; ++k) {
+                const int32_t v0 = c.node_ptr[k], nv = c.node_ptr[k + 1] - v0, kw = (nv + 31) / 32;
+                uint32_t *f = c.dense_fwd.data() + c.dense_meta[4 * k + 2], *b = c.dense_bwd.data() + c.dense_meta[4 * k + 2];
+                for (int32_t r = 0; r < nv; ++r)
+                    for (int64_t i = h->g.ptr[v0 + r]; i < h->g.ptr[v0 + r + 1]; ++i) {
+                        const int32_t u = h->g.col[i] - v0;
+                        f[r * kw + u / 32] |= 1u << (u & 31);
+                        b[u * kw + r / 32] |= 1u << (r & 31);
+                    }
+            }
+            c.dense = true;
+            c.dense_always = want == 2;
+        }
+    }
     c.enabled = true;
 }
 

@@ -69,6 +69,7 @@ struct LocalLists {
     int32_t *d_items = nullptr;
     int32_t *d_split = nullptr;
 };
+constexpr int32_t kDenseMaxNodes = 256;
 struct Components {
     bool enabled = false;
     bool expanded = false;                   // aggregation lists are expressed over original rows (one stage)
@@ -88,6 +89,13 @@ struct Components {
     // first the split[k] rows that no aggregation node consumes, then the others.
     LocalLists bwd_all;
     LocalLists nfwd, nbwd;                   // the input graph and its transpose (naive baseline)
+    // Adjacency bits of every component (rows: destinations; transposed: sources), see hag_dense.hip; used for f32 sums when no
+    // component has more than kDenseMaxNodes nodes
+    bool dense = false, dense_always = false;
+    std::vector<uint32_t> dense_fwd, dense_bwd;
+    std::vector<int32_t> dense_meta;         // [4*count] first node, #nodes, first word of its bits, 0
+    uint32_t *d_dense_fwd = nullptr, *d_dense_bwd = nullptr;
+    int32_t *d_dense_meta = nullptr;
     std::vector<int32_t> meta;               // [4*count] first node, #nodes, first slot, #agg | #stages << 16
     int32_t *d_meta = nullptr;
     uint8_t *d_stage = nullptr;

@@ -157,6 +157,7 @@ class Hag:
     def __init__(self, handle):
         self._h = ctypes.c_void_p(handle)
         self._ws = {}
+        self._shapes = {}
         self._n = None
 
     def __del__(self):
@@ -213,17 +214,6 @@ class Hag:
     def workspace_bytes(self, op, dtype_code, d) -> int:
         return int(lib().hag_workspace_bytes(self._h, OPS[op], dtype_code, int(d)))
 
-    def _workspace(self, op, t):
-        import torch
-        nbytes = self.workspace_bytes(op, _dtype_code(t), t.shape[1])
-        # one buffer per (device, stream): calls enqueued on different streams may overlap
-        key = (t.device.index, torch.cuda.current_stream(t.device).cuda_stream)
-        ws = self._ws.get(key)
-        if ws is None or ws.numel() < nbytes:
-            ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=t.device)
-            self._ws[key] = ws
-        return ws
-
     def _check_args(self, what, a, op, out, argmax, workspace, needs_argmax):
         """Everything the C ABI cannot check from raw pointers: the library takes no row count, so a
         matrix with too few rows, a narrower dtype or a short workspace would make a kernel read or
@@ -251,29 +241,57 @@ class Hag:
             if have < need or workspace.device != a.device:
                 raise ValueError(f"workspace holds {have} bytes on {workspace.device}, {need} needed on {a.device}")
 
-    def _fwd(self, fn, x, op, y, argmax, workspace, *extra):
+    def _shape(self, what, a, op):
+        """(op code, dtype code, d, workspace bytes) of a call on a matrix of a's shape and dtype; raises what _check_args
+        raises for `a`.  Looked up by value: a handle's sizes never change, so neither do the answers."""
+        key = (op, a.dtype, a.shape)
+        got = self._shapes.get(key)
+        if got is None:
+            self._check_args(what, a, op, None, None, None, False)
+            code, d = _dtype_code(a), int(a.shape[1])
+            got = (OPS[op], code, d, self.workspace_bytes(op, code, d))
+            if len(self._shapes) >= 256:
+                self._shapes.clear()
+            self._shapes[key] = got
+        return got
+
+    def _launch(self, fn, what, a, op, out, argmax, workspace, needs_argmax, backward, extra):
+        # A call on a small graph takes about as long as preparing it, so everything that depends on sizes only is looked up, and
+        # the stream is asked for once.
         import torch
-        self._check_args("x", x, op, y, argmax, workspace, False)
-        n, d = x.shape
-        if y is None:
-            y = torch.empty_like(x)
+        op_code, code, d, nbytes = self._shape(what, a, op)
+        if out is not None or argmax is not None or workspace is not None or needs_argmax:
+            self._check_args(what, a, op, out, argmax, workspace, needs_argmax)
+        if not a.is_cuda or not a.is_contiguous():
+            raise ValueError("device tensors must be contiguous and on the GPU")
+        if out is None:
+            out = torch.empty_like(a)
         if op == "max" and argmax is None:
-            argmax = torch.empty((n, d), dtype=torch.int32, device=x.device)
-        ws = workspace if workspace is not None else self._workspace(op, x)
-        _check(fn(self._h, OPS[op], _dtype_code(x), d, _dev_ptr(x), _dev_ptr(y), _dev_ptr(argmax), _dev_ptr(ws),
-                  _stream_ptr(), *extra))
+            argmax = torch.empty_like(a, dtype=torch.int32)
+        device = torch._C._cuda_getDevice()
+        stream = torch._C._cuda_getCurrentRawStream(device)
+        if workspace is None:
+            # one buffer per (device, stream): calls enqueued on different streams may overlap
+            index = a.get_device()
+            key = (index, stream if index == device else torch._C._cuda_getCurrentRawStream(index))
+            workspace = self._ws.get(key)
+            if workspace is None or workspace.numel() < nbytes:
+                workspace = self._ws[key] = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=a.device)
+        rest = (argmax, out) if backward else (out, argmax)
+        for t in (out, argmax, workspace):
+            if t is not None and (not t.is_cuda or not t.is_contiguous()):
+                raise ValueError("device tensors must be contiguous and on the GPU")
+        rc = fn(self._h, op_code, code, d, a.data_ptr(), *(None if t is None else t.data_ptr() for t in rest), workspace.data_ptr(), stream, *extra)
+        if rc != 0:
+            _check(rc)
+        return out, argmax
+
+    def _fwd(self, fn, x, op, y, argmax, workspace, *extra):
+        y, argmax = self._launch(fn, "x", x, op, y, argmax, workspace, False, False, extra)
         return (y, argmax) if op == "max" else y
 
     def _bwd(self, fn, gy, op, argmax, gx, workspace, *extra):
-        import torch
-        self._check_args("gy", gy, op, gx, argmax, workspace, op == "max")
-        n, d = gy.shape
-        if gx is None:
-            gx = torch.empty_like(gy)
-        ws = workspace if workspace is not None else self._workspace(op, gy)
-        _check(fn(self._h, OPS[op], _dtype_code(gy), d, _dev_ptr(gy), _dev_ptr(argmax), _dev_ptr(gx), _dev_ptr(ws),
-                  _stream_ptr(), *extra))
-        return gx
+        return self._launch(fn, "gy", gy, op, gx, argmax, workspace, op == "max", True, extra)[0]
 
     def forward(self, x, op="sum", y=None, argmax=None, workspace=None):
         return self._fwd(lib().hag_forward, x, op, y, argmax, workspace)

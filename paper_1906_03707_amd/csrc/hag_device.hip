@@ -153,7 +153,7 @@ static int run_fused(const hag_handle *h, const std::vector<const Plan *> &plans
                      hipStream_t s) {
     FusedArgs<T> f{};
     const int lpr = pick_lpr(base.d);
-    const int64_t per_block = (kBlock / kWave) * (kWave / lpr);
+    const int64_t per_block = kBlock / item_lanes(lpr);
     int64_t blocks = 0;
     const int np = (int)plans.size();
     for (int k = 0; k < np; ++k) {

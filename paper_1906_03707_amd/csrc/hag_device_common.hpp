@@ -348,6 +348,12 @@ static inline int pick_lpr(int64_t d) {
     return l;
 }
 
+// Lanes that share one short item of a gather: at least 16, so that narrow rows (4 or 8 lanes each) are read by 4 or 2 streams of lanes
+// side by side.  With one stream per item an item of 16 columns was a chain of one id load and four row loads per four entries, and took
+// longer than one of 64 columns.  Forward sum over 8.4 M edges (65536 nodes, mean degree 128): d = 16 142 -> 56 us, d = 32 95 -> 73 us (d = 64:
+// 117 us); over 26 M edges (131072 nodes): 244 -> 150 and 198 -> 194 us; max at d = 16 192 -> 86 us.
+constexpr int item_lanes(int lpr) { return lpr < 16 ? 16 : lpr; }
+
 // Defined in the gather units (one per element type and reduction), used by hag_device.hip.
 template <typename T, int RED, int ROLE>
 int launch_gather(const GatherArgs<T> &a, hipStream_t s);

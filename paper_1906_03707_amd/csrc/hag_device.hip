@@ -122,7 +122,7 @@ static Workspace carve(const hag_handle *h, hag_op_t op, int64_t d, void *base) 
 // Longest item that a single sub-group of lanes takes; longer ones get a whole workgroup.
 static int64_t block_threshold(const hag_handle *h, const Plan &p, int64_t d) {
     const int64_t sub_max = h->knobs.sub_max;
-    const int64_t nsg = kBlock / pick_lpr(d);
+    const int64_t nsg = kBlock / gather_lpr(d, p.np);
     // A launch too small to fill the device with one sub-group per row (the stages of
     // a small HAG) lasts as long as its longest single-sub-group row: there a row gets
     // a workgroup much sooner.

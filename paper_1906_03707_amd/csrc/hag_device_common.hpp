@@ -348,6 +348,11 @@ static inline int pick_lpr(int64_t d) {
     return l;
 }
 
+// The same for a gather over np source classes: at most 32 lanes (128 columns) where the launch is cut by source, so that wide rows are gathered
+// in more column chunks, one after the other, each with a smaller share of the matrix per XCD
+// (forward sum over 26 M edges, 131072 nodes: d = 256 1425 -> 1341 us, d = 512 2838 -> 2676 us; narrower chunks gain nothing, the list work per byte grows).
+static inline int gather_lpr(int64_t d, int np) { return np > 1 ? std::min(pick_lpr(d), 32) : pick_lpr(d); }
+
 // Lanes that share one short item of a gather: at least 16, so that narrow rows (4 or 8 lanes each) are read by 4 or 2 streams of lanes
 // side by side.  With one stream per item an item of 16 columns was a chain of one id load and four row loads per four entries, and took
 // longer than one of 64 columns.  Forward sum over 8.4 M edges (65536 nodes, mean degree 128): d = 16 142 -> 56 us, d = 32 95 -> 73 us (d = 64:

@@ -381,9 +381,23 @@ static int run_dense(const hag_handle *h, bool naive, bool backward, hag_op_t op
     return launch_dense(a, (naive ? 2 : 0) + (backward ? 1 : 0), h->comp.max_nodes, s);
 }
 
+// Whether a whole pass over the input graph's own lists is expected to be faster than the pass over the HAG, which aggregates the same (the
+// two are equivalent graphs).  The HAG's aggregation nodes cost launches of their own and 25 to 60 MB more rows that compete for the L2s, and what it
+// saves are mostly rows that hit there.  Measured, plain lists against HAG (forward; transposed pass), d = 128:
+//   1025 and 4096 nodes, 5 to 8 % fewer row reads:            14 / 17 us;    14 / 17 us (launches)
+//   power-law graph, 1.6 M edges, 2 to 4 % fewer:             88 / 98 us;    88 / 96 us
+//   65536 nodes, 8.4 M edges, 9 to 15 % fewer:               213 / 210 us;  213 / 227 us; d = 512: 846 / 842 us; 846 / 897 us
+//   131072 nodes, 26 M edges, 10 to 15 % fewer:              650 / 625 us;  645 / 625 us
+// and a max gains nothing at any of these sizes (934 / 927 us in the last, 272 / 286 us in the one before).
+static bool plain_lists_are_faster(const hag_handle *h, hag_op_t op) {
+    if (h->a == 0 || !h->knobs.route || h->knobs.fuse_max_items > 0) return false;
+    return op == HAG_MAX || h->e < 16000000 || (double)(h->st.h + 2 * h->a) > 0.92 * (double)h->e;
+}
+
 template <typename T, int RED>
 static int forward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d, const T *x, T *y, int32_t *argmax,
                         void *ws, hipStream_t s, uint32_t phases) {
+    naive = naive || (phases == HAG_PHASE_ALL && plain_lists_are_faster(h, op));
     // a batch of small graphs: the whole pass is one launch, on the matrix cores or out of LDS
     if constexpr (std::is_same<T, float>::value && RED == R_SUM)
         if (phases == HAG_PHASE_ALL && dense_applies(h, op, d)) return run_dense(h, naive, false, op, d, x, y, s);
@@ -458,6 +472,7 @@ template <typename T>
 static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d, const T *gy, const int32_t *argmax,
                          T *gx, void *ws, hipStream_t s, uint32_t phases) {
     const int32_t n = (int32_t)h->n;
+    naive = naive || (phases == HAG_PHASE_ALL && op != HAG_MAX && plain_lists_are_faster(h, op));   // (a max looks at no list here)
     if (op == HAG_MAX && h->knobs.deterministic_max_backward) {
         // gx[u, f] = sum over the consumers v of u of gy[v, f] where argmax[v, f] == u: a gather over the
         // transposed input graph in a fixed order (no atomics), at the price of reading the argmax row
@@ -692,7 +707,7 @@ int hag_forward_static_scratch(const hag_t *h, hag_op_t op, hag_dtype_t dt, int6
 int hag_set_option(hag_t *h, int32_t option, int64_t value) {
     if (!h) { set_error("handle is NULL"); return HAG_EINVAL; }
     switch (option) {
-        case HAG_OPT_ONE_LAUNCH_MAX_ITEMS: h->knobs.fuse_max_items = std::max<int64_t>(value, 0); return HAG_OK;
+        case HAG_OPT_ONE_LAUNCH_MAX_ITEMS: h->knobs.fuse_max_items = std::max<int64_t>(value, 0); if (value > 0) h->knobs.route = false; return HAG_OK;
         case HAG_OPT_SPIN_LIMIT: h->knobs.spin_limit = std::max<int64_t>(value, 1); return HAG_OK;
         case HAG_OPT_TEST_WAIT_UNREACHABLE: h->knobs.wait_unreachable = value != 0; return HAG_OK;
         case HAG_OPT_DETERMINISTIC_MAX_BACKWARD: h->knobs.deterministic_max_backward = value != 0; return HAG_OK;

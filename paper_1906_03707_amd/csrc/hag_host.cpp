@@ -1034,6 +1034,8 @@ static int finalize_from_builder(hag_handle *h, Builder &b) {
         k.part_shift = (int32_t)(env_i64("HAG_PART_SHIFT", 0) & 7);
         k.fuse_max_items = env_i64("HAG_FUSE_MAX_ITEMS", 0);   // off: measured slower than one launch per stage
         k.spin_limit = env_i64("HAG_SPIN_LIMIT", 1 << 18);
+        // (a knob that shapes the pass over the HAG asks for that pass)
+        k.route = env_i64("HAG_ROUTE", std::getenv("HAG_STAGE_EXTRA_ROWS") || std::getenv("HAG_FUSE_MAX_ITEMS") ? 0 : 1) != 0;
     }
     // depth(original) = 0, depth(w) = 1 + max over its inputs; creation order is topological
     std::vector<int32_t> order(a);

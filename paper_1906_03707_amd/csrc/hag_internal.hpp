@@ -139,6 +139,7 @@ struct hag_knobs {
     int64_t spin_limit = 0;     // HAG_SPIN_LIMIT: polls a wavefront of the one-launch pass waits for earlier phases
     bool wait_unreachable = false;      // test only: the awaited count can never be reached, so every wait gives up
     bool deterministic_max_backward = false;
+    bool route = true;          // HAG_ROUTE: whole passes may run over the input graph's lists where those are faster
     int32_t part_shift = 0;     // HAG_PART_SHIFT: workgroup b of a partitioned launch takes the sources of class (b + shift) mod 8
 };
 

@@ -855,67 +855,76 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_wide_kernel(SeqRevArgs A) 
         __syncthreads();
         const int steps = sdesc[2];
         const int start = sdesc[sj * 4], beg = sdesc[sj * 4 + 1], len = sdesc[sj * 4 + 2], node = sdesc[sj * 4 + 3];
-        float dhv[IT][4], dcv[IT][4];                        // units part * 4 + 32 * it + e
+        // unit 32 * it + 8 * e + part: the eight threads of a path move 128 contiguous bytes of its gates per instruction
+        float dhv[IT][4], dcv[IT][4];
+        // the tape of a step is requested while the product of the one after it runs (one workgroup per compute unit: there are registers)
+        float4 gates[IT][4];
+        float c_now[IT][4], c_prev[IT][4];                   // c_prev is the next step's c_now
+        int keep = -1;
+        auto load_step = [&](int t) {
+            const size_t cell = (size_t)beg + t;
+            keep = A.step_out[cell];
+            const float *before = t > 0 ? A.tape_c + (cell - 1) * hidden : start >= 0 ? A.c_state + (size_t)start * hidden : nullptr;
 #pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            const int u = part * 4 + 32 * it;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (node >= 0 && u < hidden) v = *reinterpret_cast<const float4 *>(A.g_a + (size_t)node * hidden + u);
-            dhv[it][0] = v.x; dhv[it][1] = v.y; dhv[it][2] = v.z; dhv[it][3] = v.w;
-            dcv[it][0] = dcv[it][1] = dcv[it][2] = dcv[it][3] = 0.f;
-        }
+            for (int it = 0; it < IT; ++it)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int u = 32 * it + 8 * e + part;
+                    if (u >= hidden) continue;
+                    gates[it][e] = *reinterpret_cast<const float4 *>(A.tape_g + (cell * hidden + u) * 4);
+                    c_prev[it][e] = before ? before[u] : 0.f;
+                }
+        };
+#pragma unroll
+        for (int it = 0; it < IT; ++it)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int u = 32 * it + 8 * e + part;
+                dhv[it][e] = node >= 0 && u < hidden ? A.g_a[(size_t)node * hidden + u] : 0.f;
+                dcv[it][e] = c_prev[it][e] = 0.f;
+                gates[it][e] = make_float4(0.f, 0.f, 0.f, 0.f);
+                c_now[it][e] = len > 0 && u < hidden ? A.tape_c[((size_t)beg + len - 1) * hidden + u] : 0.f;
+            }
+        if (len > 0 && len == steps) load_step(steps - 1);
         for (int t = steps - 1; t >= 0; --t) {
             if (t < len) {
                 const size_t cell = (size_t)beg + t;
-                if (t + 1 < len) {
-                    // the product of the step before left dh_prev of this path in its row: this step's dh.  Only this path's own
-                    // lanes touch the row between the barriers, and they read it before they overwrite it below (one wavefront,
-                    // program order).
-#pragma unroll
-                    for (int it = 0; it < IT; ++it) {
-                        const int u = part * 4 + 32 * it;
-                        if (u >= hidden) continue;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) dhv[it][e] = zg[sj * ZG + u + e];
-                    }
-                }
-                const int keep = A.step_out[cell];
                 if (A.pending && keep >= 0) seq_wait_pending(A, keep);
+                // the product of the step before left dh_prev of this path in its row: this step's dh.  Only this path's own
+                // lanes touch the row between the barriers, and they read all of it before they overwrite it below (one wavefront,
+                // program order).
+                if (t + 1 < len) {
 #pragma unroll
-                for (int it = 0; it < IT; ++it) {
-                    const int u = part * 4 + 32 * it;
-                    if (u >= hidden) continue;
-                    float cn[4], cp[4];
-                    if (keep >= 0) {                       // what the other users of this state sent back
-                        const float4 a = A.pending ? seq_ld4_device(A.gh + (size_t)keep * hidden + u) : *reinterpret_cast<const float4 *>(A.gh + (size_t)keep * hidden + u);
-                        const float4 b = A.pending ? seq_ld4_device(A.gc + (size_t)keep * hidden + u) : *reinterpret_cast<const float4 *>(A.gc + (size_t)keep * hidden + u);
-                        dhv[it][0] += a.x; dhv[it][1] += a.y; dhv[it][2] += a.z; dhv[it][3] += a.w;
-                        dcv[it][0] += b.x; dcv[it][1] += b.y; dcv[it][2] += b.z; dcv[it][3] += b.w;
-                    }
-                    {
-                        const float4 a = *reinterpret_cast<const float4 *>(A.tape_c + cell * hidden + u);
-                        cn[0] = a.x; cn[1] = a.y; cn[2] = a.z; cn[3] = a.w;
-                        float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (t > 0) b = *reinterpret_cast<const float4 *>(A.tape_c + (cell - 1) * hidden + u);
-                        else if (start >= 0) b = *reinterpret_cast<const float4 *>(A.c_state + (size_t)start * hidden + u);
-                        cp[0] = b.x; cp[1] = b.y; cp[2] = b.z; cp[3] = b.w;
-                    }
+                    for (int it = 0; it < IT; ++it)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (32 * it + 8 * e < hidden) dhv[it][e] = zg[sj * ZG + 32 * it + 8 * e + part];
+                }
+#pragma unroll
+                for (int it = 0; it < IT; ++it)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        float4 *pg = reinterpret_cast<float4 *>(A.tape_g + (cell * hidden + u + e) * 4);
-                        const float4 g4 = *pg;             // i, f, g, o
-                        const float tc = seq_tanh(cn[e]);
+                        const int u = 32 * it + 8 * e + part;
+                        if (u >= hidden) continue;
+                        if (keep >= 0) {                   // what the other users of this state sent back
+                            const float *h = A.gh + (size_t)keep * hidden + u, *c = A.gc + (size_t)keep * hidden + u;
+                            dhv[it][e] += A.pending ? __hip_atomic_load(h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *h;
+                            dcv[it][e] += A.pending ? __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *c;
+                        }
+                        const float4 g4 = gates[it][e];    // i, f, g, o
+                        const float tc = seq_tanh(c_now[it][e]);
                         const float d_o = dhv[it][e] * tc;
                         const float dcc = dcv[it][e] + dhv[it][e] * g4.w * (1.f - tc * tc);
-                        const float4 dg = make_float4(dcc * g4.z * g4.x * (1.f - g4.x), dcc * cp[e] * g4.y * (1.f - g4.y),
+                        const float4 dg = make_float4(dcc * g4.z * g4.x * (1.f - g4.x), dcc * c_prev[it][e] * g4.y * (1.f - g4.y),
                                                       dcc * g4.x * (1.f - g4.z * g4.z), d_o * g4.w * (1.f - g4.w));
-                        *pg = dg;                          // kept for the weight gradients
-                        *reinterpret_cast<float2 *>(&zg[sj * ZG + (u + e) * 4]) = make_float2(dg.x, dg.y);
-                        *reinterpret_cast<float2 *>(&zg[sj * ZG + (u + e) * 4 + 2]) = make_float2(dg.z, dg.w);
                         dcv[it][e] = dcc * g4.y;
+                        c_now[it][e] = c_prev[it][e];
+                        *reinterpret_cast<float4 *>(A.tape_g + (cell * hidden + u) * 4) = dg;   // kept for the weight gradients
+                        *reinterpret_cast<float2 *>(&zg[sj * ZG + u * 4]) = make_float2(dg.x, dg.y);
+                        *reinterpret_cast<float2 *>(&zg[sj * ZG + u * 4 + 2]) = make_float2(dg.z, dg.w);
                     }
-                }
             }
+            if (t > 0 && t - 1 < len) load_step(t - 1);
             __syncthreads();
             // dh_prev^T [units, paths] = W_hh^T . dG^T [4H, paths]
             seq_acc_t acc;
@@ -953,12 +962,10 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_wide_kernel(SeqRevArgs A) 
         // that an atomic instruction covers contiguous bytes
         if (__syncthreads_or(start >= 0)) {
 #pragma unroll
-            for (int it = 0; it < IT; ++it) {
-                const int u = part * 4 + 32 * it;
-                if (u >= hidden) continue;
+            for (int it = 0; it < IT; ++it)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) zg[sj * ZG + 128 + u + e] = dcv[it][e];
-            }
+                for (int e = 0; e < 4; ++e)
+                    if (32 * it + 8 * e < hidden) zg[sj * ZG + 128 + 32 * it + 8 * e + part] = dcv[it][e];
             __syncthreads();
             for (int j = wave; j < kSeqJobs; j += 8) {
                 const int from = sdesc[j * 4];

@@ -1,0 +1,76 @@
+"""LSTM aggregator: sizes at the edges of the kernels' tiles and inputs with values that do not split into bf16 pieces.
+
+Forward: gate tiles of 8 hidden units, 16 columns per product step, variants for hidden up to 32, 64 and 128; the input half of the gates runs
+over 64 nodes at a time, d padded to 8.  Backward: node sums over ranges of cells that cut through a node's cells (one node in every list)."""
+import numpy as np
+import pytest
+
+from oracle import lstm
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1906_03707_amd import binding
+    binding.lib()
+    return binding
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+
+
+def lists(n, seed, hub=False):
+    rng = np.random.default_rng(seed)
+    rows = [rng.integers(0, n, int(k)) for k in rng.integers(0, 7, n)]
+    if hub:
+        rows = [np.concatenate([[3], r]) for r in rows]       # node 3 starts every list: its cells fill many ranges of the node sums
+    rowptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+    return rowptr, np.concatenate(rows).astype(np.int32)
+
+
+@pytest.mark.parametrize("d,hidden", [(4, 8), (12, 24), (20, 32), (8, 40), (248, 8), (188, 64), (60, 56), (8, 72), (132, 88), (12, 120), (128, 128)])
+@pytest.mark.parametrize("hub", [False, True])
+def test_sizes(B, d, hidden, hub):
+    n = 700 if hub else 131
+    rowptr, col = lists(n, d + hidden, hub)
+    rng = np.random.default_rng(hidden)
+    x, w_ih, w_hh, b, g = (dev(rng.normal(0, s, shape)) for s, shape in ((1, (n, d)), (0.3, (4 * hidden, d)), (0.3, (4 * hidden, hidden)), (0.3, 4 * hidden), (1, (n, hidden))))
+    f64 = lambda t: t.cpu().numpy().astype(np.float64)
+    want_a, _ = lstm.naive_aggregate(rowptr, col, f64(x), f64(w_ih), f64(w_hh), f64(b))
+    want = lstm.naive_aggregate_backward(rowptr, col, f64(x), f64(w_ih), f64(w_hh), f64(b), f64(g))
+    for cap in (0, int(col.size)):
+        h = B.SeqHag(rowptr, col, cap).upload()
+        # pre-activations of up to 256 terms of size 1 carry 256 * 2^-24 = 1.5e-5 at most, the gates' slopes are below 1
+        assert np.abs(f64(h.lstm_forward(x, w_ih, w_hh, b)) - want_a).max() <= 1.5e-5
+        a, ws = h.lstm_forward_train(x, w_ih, w_hh, b)
+        for got, ref in zip(h.lstm_backward(x, w_ih, w_hh, g, ws), want):
+            # norm-wise, the bar of the other gradient tests
+            assert np.linalg.norm(f64(got) - ref) <= 2e-5 * max(np.linalg.norm(ref), 1e-30)
+        h.check()
+
+
+def test_infinite_and_nan_features_stay_with_their_readers(B):
+    # an infinite feature saturates the gates of the cells that read it, a NaN spreads to the lists that hold it, and to nobody else
+    n, d, hidden = 200, 16, 40
+    rowptr, col = lists(n, 5)
+    rng = np.random.default_rng(6)
+    x, w_ih, w_hh, b = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden)
+    h = B.SeqHag(rowptr, col, int(col.size)).upload()
+    clean = h.lstm_forward(dev(x), dev(w_ih), dev(w_hh), dev(b)).cpu().numpy()
+    x[7, 2], x[9, 0] = np.inf, np.nan
+    got = h.lstm_forward(dev(x), dev(w_ih), dev(w_hh), dev(b)).cpu().numpy()
+    x32 = [a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b)]
+    with np.errstate(all="ignore"):
+        want, _ = lstm.naive_aggregate(rowptr, col, *x32)
+    holds = lambda u: np.array([u in col[rowptr[v]:rowptr[v + 1]] for v in range(n)])   # noqa: E731
+    assert holds(7).any() and holds(9).any()
+    assert np.array_equal(np.isnan(got).any(1), holds(9))
+    untouched = ~holds(7) & ~holds(9)
+    assert np.array_equal(got[untouched], clean[untouched])
+    fine = holds(7) & ~holds(9)
+    assert np.abs(got[fine] - want[fine]).max() <= 1e-5

@@ -244,25 +244,26 @@ __device__ __forceinline__ void lazy_max4(V &v, int4 &vi, const V &w, int wi, co
     max_first4(v, vi, w, wi);   // a tie keeps the accumulator, whose id is settled above
 }
 // (value, id) max of partial results whose ids may still be aggregation ids (>= split) standing for the
-// winner stored in `late`: a tie between two such partial results is settled on the original ids
-template <typename S>
+// winner stored in `late`: a tie between two such partial results is settled on the original ids.
+// COH: `late` was written by an earlier phase of the same launch, possibly on another XCD
+template <bool COH, typename S>
 __device__ __forceinline__ void late_max1(S &v, int &vi, S w, int wi, const int32_t *late, int split, size_t d, int col) {
     if (wi < 0) return;
     if (vi >= 0 && w == v && (wi >= split || vi >= split)) {   // rare
-        if (wi >= split) wi = late[(size_t)(wi - split) * d + col];
-        if (vi >= split) vi = late[(size_t)(vi - split) * d + col];
+        if (wi >= split) wi = ld1_id<COH>(late + (size_t)(wi - split) * d + col);
+        if (vi >= split) vi = ld1_id<COH>(late + (size_t)(vi - split) * d + col);
     }
     const bool take = vi < 0 || w > v || (w == v && wi < vi);
     v = take ? w : v;
     vi = take ? wi : vi;
 }
-template <typename V>
+template <bool COH, typename V>
 __device__ __forceinline__ void late_max4(V &v, int4 &vi, const V &w, const int4 &wi, const int32_t *late, int split,
                                           size_t d, int cb) {
-    late_max1(v.x, vi.x, w.x, wi.x, late, split, d, cb);
-    late_max1(v.y, vi.y, w.y, wi.y, late, split, d, cb + 1);
-    late_max1(v.z, vi.z, w.z, wi.z, late, split, d, cb + 2);
-    late_max1(v.w, vi.w, w.w, wi.w, late, split, d, cb + 3);
+    late_max1<COH>(v.x, vi.x, w.x, wi.x, late, split, d, cb);
+    late_max1<COH>(v.y, vi.y, w.y, wi.y, late, split, d, cb + 1);
+    late_max1<COH>(v.z, vi.z, w.z, wi.z, late, split, d, cb + 2);
+    late_max1<COH>(v.w, vi.w, w.w, wi.w, late, split, d, cb + 3);
 }
 // replace aggregation ids left in acc_id by the original ids they stand for
 template <bool COH>

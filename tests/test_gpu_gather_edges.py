@@ -81,3 +81,26 @@ def test_both_graphs_give_the_same(B, d, monkeypatch):
     for phase in (B.HAG_PHASE_LEVELS, B.HAG_PHASE_GATHER, B.HAG_PHASE_FOLD):   # phase by phase: over the HAG
         h.forward_phases(x, phase, "sum", y=out)
     assert torch.equal(out, over_hag.forward(x, "sum"))
+
+
+@pytest.mark.parametrize("d", [4, 16, 32])
+def test_one_launch_max_with_ties(B, d, monkeypatch):
+    # several dependent phases in one launch: an item's streams settle their ties on winners that an earlier phase of the launch wrote,
+    # whose narrow rows share cache lines with rows that are written later
+    monkeypatch.setenv("HAG_FUSE_MAX_ITEMS", "262144")
+    monkeypatch.setenv("HAG_STAGE_EXTRA_ROWS", "-1000000")            # one phase per level
+    rowptr, col = synth.sbm(n_blocks=4, block=60, p_in=0.5, p_out=0.02, seed=82)
+    n = rowptr.size - 1
+    h = B.hag_search(rowptr, col, n).upload()
+    assert 3 <= h.stats()["stages"] == h.stats()["levels"] <= 7
+    for seed in range(6):
+        x = np.random.default_rng(seed).integers(0, 2 + seed, (n, d)).astype(np.float32)
+        want, _, am = oracle.naive_forward(rowptr, col, x, "max")
+        xd = torch.from_numpy(x).cuda()
+        for _ in range(3):
+            y, who = h.forward(xd, "max")
+            assert np.array_equal(y.cpu().numpy(), want) and np.array_equal(who.cpu().numpy(), am), seed
+            gy = synth.features_f32(n, d, seed)
+            gw, gs = oracle.naive_backward(rowptr, col, gy, "max", am)
+            assert np.all(np.abs(h.backward(torch.from_numpy(gy).cuda(), "max", argmax=who).cpu().numpy() - gw) <= 1e-5 * gs)
+        h.check()                                                     # no wait gave up

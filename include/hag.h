@@ -282,6 +282,18 @@ int hag_forward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d,
 int hag_backward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d,
                  const void *gy, const int32_t *argmax, void *gx, void *workspace, void *stream);
 
+/* The way hag_forward (backward = 0) or hag_backward (1) takes with these arguments, or a negative status.  Host state only; hag_upload
+ * need not have been called:
+ *   HAG_ROUTE_HAG              Algorithm 2 over the HAG: a launch per stage of aggregation nodes, then the gather over V;
+ *   HAG_ROUTE_LISTS            the input graph's own lists (max, backward: the fixed-order gather of HAG_OPT_DETERMINISTIC_MAX_BACKWARD);
+ *   HAG_ROUTE_COMPONENT_HAG, HAG_ROUTE_COMPONENT_LISTS   a batch of small graphs, one launch out of LDS, over the HAG or the lists;
+ *   HAG_ROUTE_DENSE            a batch of small graphs as products with their adjacency matrices;
+ *   HAG_ROUTE_ONE_LAUNCH       the one-launch schedule below, over the HAG;
+ *   HAG_ROUTE_SCATTER          max, backward: every gradient is added to its winner. */
+enum { HAG_ROUTE_HAG = 0, HAG_ROUTE_LISTS = 1, HAG_ROUTE_COMPONENT_HAG = 2, HAG_ROUTE_COMPONENT_LISTS = 3, HAG_ROUTE_DENSE = 4,
+       HAG_ROUTE_ONE_LAUNCH = 5, HAG_ROUTE_SCATTER = 6 };
+int hag_route(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d, int32_t backward);
+
 /* The one-launch schedule (optional, off by default).  hag_forward and hag_backward can run
  * Algorithm 2's loop over V_A and its final loop (resp. their transposes) as ONE kernel launch:
  * workgroups draw units of work, phase by phase, from a device-wide ticket counter, and a unit of

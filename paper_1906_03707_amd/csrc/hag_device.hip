@@ -135,7 +135,7 @@ static int64_t block_threshold(const hag_handle *h, const Plan &p, int64_t d) {
 // HAG whose launches are short against the gaps between them, no row cut into pieces (the fold
 // of partial rows would be one more phase per launch), feature columns in one chunk.
 static bool fusable(const hag_handle *h, int64_t d, const std::vector<const Plan *> &plans) {
-    if (h->knobs.fuse_max_items <= 0 || !h->d_sync || h->a == 0 || d > 256) return false;
+    if (h->knobs.fuse_max_items <= 0 || h->a == 0 || d > 256) return false;
     if ((int)plans.size() > kMaxPhases || plans.size() < 2) return false;
     int64_t items = 0;
     for (const Plan *p : plans) {
@@ -289,7 +289,7 @@ struct CompLayout {
 static CompLayout component_layout(const hag_handle *h, bool naive, bool backward, hag_op_t op, int64_t d) {
     CompLayout L;
     const Components &c = h->comp;
-    if (!c.enabled || !h->comp_uploaded) return L;
+    if (!c.enabled) return L;
     // sums only.  Max stays on the generic kernels: their ordered comparison path is cheaper
     // per element than a (value, id) comparison for every LDS row (measured: the LDS variant
     // was the slower one), and its backward pass is a scatter, not a gather.
@@ -362,7 +362,7 @@ static int launch_component(const hag_handle *h, bool naive, hag_op_t op, int64_
 // degree 2.5 on the list's side (39 against 33 us): about the cube of the largest graph's nodes, as its work per node grows with their square.
 static bool dense_applies(const hag_handle *h, hag_op_t op, int64_t d) {
     const Components &c = h->comp;
-    if (!c.dense || !h->comp_uploaded || op == HAG_MAX) return false;
+    if (!c.dense || op == HAG_MAX) return false;
     const double nodes = (double)c.max_nodes;
     return c.dense_always || d > 32 || (double)h->e * 417000.0 >= nodes * nodes * nodes * (double)h->n;
 }
@@ -394,35 +394,55 @@ static bool plain_lists_are_faster(const hag_handle *h, hag_op_t op) {
     return op == HAG_MAX || h->e < 16000000 || (double)(h->st.h + 2 * h->a) > 0.92 * (double)h->e;
 }
 
+// The plans of a pass over the HAG in execution order, and the column array of each.
+struct PassPlans { std::vector<const Plan *> plans; std::vector<const int32_t *> cols; };
+static PassPlans hag_pass(const hag_handle *h, bool backward) {
+    PassPlans p;
+    for (int32_t k = 0; k < h->stages; ++k) {
+        const int32_t st = backward ? h->stages - 1 - k : k;
+        p.plans.push_back(backward ? &h->p_bwd_stage[st] : &h->p_fwd_stage[st]);
+        p.cols.push_back(backward ? h->d_tcol : h->d_ecol);
+    }
+    p.plans.push_back(backward ? &h->p_bwd_src : &h->p_fwd);
+    p.cols.push_back(backward ? h->d_tcol : h->d_hcol);
+    return p;
+}
+
+// The way a pass takes (HAG_ROUTE_*): the one place where it is decided.
+static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases) {
+    if (op == HAG_MAX && backward) return h->knobs.deterministic_max_backward ? HAG_ROUTE_LISTS : HAG_ROUTE_SCATTER;   // looks at no list of the HAG
+    const bool whole = phases == HAG_PHASE_ALL;
+    naive = naive || (whole && plain_lists_are_faster(h, op));
+    // a batch of small graphs: the whole pass is one launch, on the matrix cores or out of LDS
+    if (whole && dt == HAG_F32 && dense_applies(h, op, d)) return HAG_ROUTE_DENSE;
+    if (whole && component_layout(h, naive, backward, op, d).total > 0) return naive ? HAG_ROUTE_COMPONENT_LISTS : HAG_ROUTE_COMPONENT_HAG;
+    if (naive) return HAG_ROUTE_LISTS;
+    // a small HAG: aggregation-node stages and the gather over V as one launch
+    return whole && fusable(h, d, hag_pass(h, backward).plans) ? HAG_ROUTE_ONE_LAUNCH : HAG_ROUTE_HAG;
+}
+
 template <typename T, int RED>
 static int forward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d, const T *x, T *y, int32_t *argmax,
                         void *ws, hipStream_t s, uint32_t phases) {
-    naive = naive || (phases == HAG_PHASE_ALL && plain_lists_are_faster(h, op));
-    // a batch of small graphs: the whole pass is one launch, on the matrix cores or out of LDS
+    const int route = route_of(h, naive, false, op, std::is_same<T, float>::value ? HAG_F32 : HAG_I32, d, phases);
     if constexpr (std::is_same<T, float>::value && RED == R_SUM)
-        if (phases == HAG_PHASE_ALL && dense_applies(h, op, d)) return run_dense(h, naive, false, op, d, x, y, s);
-    if (phases == HAG_PHASE_ALL && component_layout(h, naive, false, op, d).total > 0)
-        return launch_component<T, false>(h, naive, op, d, x, y, s);
+        if (route == HAG_ROUTE_DENSE) return run_dense(h, naive, false, op, d, x, y, s);
+    if (route == HAG_ROUTE_COMPONENT_HAG || route == HAG_ROUTE_COMPONENT_LISTS)
+        return launch_component<T, false>(h, route == HAG_ROUTE_COMPONENT_LISTS, op, d, x, y, s);
+    naive = route == HAG_ROUTE_LISTS;
     Workspace w = carve(h, op, d, ws);
     const int32_t n = (int32_t)h->n;
-    if (!naive && phases == HAG_PHASE_ALL) {
-        // a small HAG: aggregation-node stages and the gather over V as one launch
-        std::vector<const Plan *> plans;
-        std::vector<const int32_t *> cols;
-        for (int32_t st = 0; st < h->stages; ++st) { plans.push_back(&h->p_fwd_stage[st]); cols.push_back(h->d_ecol); }
-        plans.push_back(&h->p_fwd);
-        cols.push_back(h->d_hcol);
-        if (fusable(h, d, plans)) {
-            GatherArgs<T> b{};
-            b.src_lo = x;
-            b.src_hi = (const T *)w.agg;
-            b.id_hi = (const int32_t *)w.agg_id;
-            b.split = n;
-            b.d = (int32_t)d;
-            b.out_scale = op == HAG_MEAN ? h->d_inv_deg : op == HAG_GCN ? h->d_inv_deg1 : nullptr;
-            b.self = op == HAG_GCN ? x : nullptr;
-            return run_fused<T, RED, G_HAG_FWD>(h, plans, cols, b, (T *)w.agg, (int32_t *)w.agg_id, y, argmax, s);
-        }
+    if (route == HAG_ROUTE_ONE_LAUNCH) {
+        const PassPlans p = hag_pass(h, false);
+        GatherArgs<T> b{};
+        b.src_lo = x;
+        b.src_hi = (const T *)w.agg;
+        b.id_hi = (const int32_t *)w.agg_id;
+        b.split = n;
+        b.d = (int32_t)d;
+        b.out_scale = op == HAG_MEAN ? h->d_inv_deg : op == HAG_GCN ? h->d_inv_deg1 : nullptr;
+        b.self = op == HAG_GCN ? x : nullptr;
+        return run_fused<T, RED, G_HAG_FWD>(h, p.plans, p.cols, b, (T *)w.agg, (int32_t *)w.agg_id, y, argmax, s);
     }
     if (!naive && (phases & HAG_PHASE_LEVELS)) {
         for (int32_t st = 0; st < h->stages; ++st) {
@@ -472,8 +492,8 @@ template <typename T>
 static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d, const T *gy, const int32_t *argmax,
                          T *gx, void *ws, hipStream_t s, uint32_t phases) {
     const int32_t n = (int32_t)h->n;
-    naive = naive || (phases == HAG_PHASE_ALL && op != HAG_MAX && plain_lists_are_faster(h, op));   // (a max looks at no list here)
-    if (op == HAG_MAX && h->knobs.deterministic_max_backward) {
+    const int route = route_of(h, naive, true, op, std::is_same<T, float>::value ? HAG_F32 : HAG_I32, d, phases);
+    if (op == HAG_MAX && route == HAG_ROUTE_LISTS) {
         // gx[u, f] = sum over the consumers v of u of gy[v, f] where argmax[v, f] == u: a gather over the
         // transposed input graph in a fixed order (no atomics), at the price of reading the argmax row
         // of every consumer: about as much traffic as a forward pass
@@ -489,7 +509,7 @@ static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d
         a.out_off = 0;
         return run_plan<T, R_SUMIF, G_NAIVE_BWD>(h, h->p_naive_bwd, h->d_gtcol, a, w, s, phases);
     }
-    if (op == HAG_MAX) {
+    if (route == HAG_ROUTE_SCATTER) {
         int64_t total = h->n * d;
         if (total == 0 || !(phases & HAG_PHASE_GATHER)) return HAG_OK;
         hipLaunchKernelGGL((fill_zero_kernel<T>), dim3((unsigned)((total / 4 + kBlock - 1) / kBlock)), dim3(kBlock), 0,
@@ -501,9 +521,10 @@ static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d
         return HAG_OK;
     }
     if constexpr (std::is_same<T, float>::value)
-        if (phases == HAG_PHASE_ALL && dense_applies(h, op, d)) return run_dense(h, naive, true, op, d, gy, gx, s);
-    if (phases == HAG_PHASE_ALL && component_layout(h, naive, true, op, d).total > 0)
-        return launch_component<T, true>(h, naive, op, d, gy, gx, s);
+        if (route == HAG_ROUTE_DENSE) return run_dense(h, naive, true, op, d, gy, gx, s);
+    if (route == HAG_ROUTE_COMPONENT_HAG || route == HAG_ROUTE_COMPONENT_LISTS)
+        return launch_component<T, true>(h, route == HAG_ROUTE_COMPONENT_LISTS, op, d, gy, gx, s);
+    naive = route == HAG_ROUTE_LISTS;
     Workspace w = carve(h, op, d, ws);
     GatherArgs<T> a{};
     a.src_lo = gy;
@@ -520,17 +541,11 @@ static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d
         if (!(phases & (HAG_PHASE_GATHER | HAG_PHASE_FOLD))) return HAG_OK;
         return run_plan<T, R_SUM, G_NAIVE_BWD>(h, h->p_naive_bwd, h->d_gtcol, a, w, s, phases);
     }
-    if (phases == HAG_PHASE_ALL) {
-        std::vector<const Plan *> plans;
-        std::vector<const int32_t *> cols;
-        for (int32_t st = h->stages - 1; st >= 0; --st) { plans.push_back(&h->p_bwd_stage[st]); cols.push_back(h->d_tcol); }
-        plans.push_back(&h->p_bwd_src);
-        cols.push_back(h->d_tcol);
-        if (fusable(h, d, plans)) {
-            GatherArgs<T> b = a;
-            if (op == HAG_GCN) { b.self = gy; b.self_scale = h->d_inv_deg1; }
-            return run_fused<T, R_SUM, G_HAG_BWD_SRC>(h, plans, cols, b, (T *)w.agg, nullptr, gx, nullptr, s);
-        }
+    if (route == HAG_ROUTE_ONE_LAUNCH) {
+        const PassPlans p = hag_pass(h, true);
+        GatherArgs<T> b = a;
+        if (op == HAG_GCN) { b.self = gy; b.self_scale = h->d_inv_deg1; }
+        return run_fused<T, R_SUM, G_HAG_BWD_SRC>(h, p.plans, p.cols, b, (T *)w.agg, nullptr, gx, nullptr, s);
     }
     // deepest stage first: its consumers are destinations only; an earlier stage may also be
     // consumed by aggregation nodes of later stages, whose gradient rows are complete by then
@@ -576,7 +591,6 @@ void free_device(hag_handle *h) {
     }
     h->d_allocs.clear();
     h->uploaded = false;
-    h->comp_uploaded = false;
 }
 
 }  // namespace hag
@@ -636,7 +650,6 @@ int hag_upload(hag_t *h, void *stream) {
             if ((rc = upload_array(h, l->col, &l->d_col, s))) goto bad;
             if ((rc = upload_array(h, l->items, &l->d_items, s))) goto bad;
         }
-        h->comp_uploaded = true;
     }
     {
         hipError_t e = hipStreamSynchronize(s);  // host vectors (slots) must outlive the copies
@@ -704,10 +717,18 @@ int hag_forward_static_scratch(const hag_t *h, hag_op_t op, hag_dtype_t dt, int6
     if (!ws) { set_error("static scratch of the handle's device was not set up"); return HAG_ESTATE; }
     return forward_entry(h, false, op, dt, d, x, y, argmax, ws, stream, HAG_PHASE_ALL);
 }
+int hag_route(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d, int32_t backward) {
+    if (!h) { set_error("handle is NULL"); return HAG_EINVAL; }
+    if (op != HAG_SUM && op != HAG_MEAN && op != HAG_MAX && op != HAG_GCN) { set_error("unknown op"); return HAG_EINVAL; }
+    if (dt != HAG_F32 && dt != HAG_I32) { set_error("unknown dtype"); return HAG_EINVAL; }
+    if ((op == HAG_MEAN || op == HAG_GCN) && dt != HAG_F32) { set_error("mean and gcn are defined for f32 only"); return HAG_EINVAL; }
+    if (d <= 0 || d % 4 != 0 || d > (1 << 20)) { set_error("d must be a positive multiple of 4, at most 2^20"); return HAG_EINVAL; }
+    return route_of(h, false, backward != 0, op, dt, d, HAG_PHASE_ALL);
+}
 int hag_set_option(hag_t *h, int32_t option, int64_t value) {
     if (!h) { set_error("handle is NULL"); return HAG_EINVAL; }
     switch (option) {
-        case HAG_OPT_ONE_LAUNCH_MAX_ITEMS: h->knobs.fuse_max_items = std::max<int64_t>(value, 0); if (value > 0) h->knobs.route = false; return HAG_OK;
+        case HAG_OPT_ONE_LAUNCH_MAX_ITEMS: h->knobs.fuse_max_items = std::max<int64_t>(value, 0); return HAG_OK;
         case HAG_OPT_SPIN_LIMIT: h->knobs.spin_limit = std::max<int64_t>(value, 1); return HAG_OK;
         case HAG_OPT_TEST_WAIT_UNREACHABLE: h->knobs.wait_unreachable = value != 0; return HAG_OK;
         case HAG_OPT_DETERMINISTIC_MAX_BACKWARD: h->knobs.deterministic_max_backward = value != 0; return HAG_OK;

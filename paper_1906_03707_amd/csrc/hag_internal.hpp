@@ -181,7 +181,7 @@ struct hag_handle {
     hag::Components comp;
 
     // device copies
-    bool uploaded = false, comp_uploaded = false;
+    bool uploaded = false;
     int device = -1;
     int32_t *d_left = nullptr, *d_right = nullptr;
     int32_t *d_hcol = nullptr, *d_tcol = nullptr, *d_gcol = nullptr, *d_gtcol = nullptr, *d_ecol = nullptr;

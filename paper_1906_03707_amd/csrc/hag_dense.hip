@@ -24,8 +24,6 @@ typedef unsigned int dense_u4_t __attribute__((ext_vector_type(4)));
 //
 // Features that the pieces cannot hold (infinities, NaN, |x| above 2^118, nonzero |x| below 2^-100) would also reach rows they are no neighbour of
 // (0 * inf); a wavefront that has loaded one redoes its rows by adding the neighbours one by one.
-constexpr int kDenseTiles = 5;   // MT
-
 __device__ __forceinline__ void dense_split2(float a, float b, uint32_t &p0, uint32_t &p1, uint32_t &p2) {
     // cut, not rounded: no piece can overflow, and the three still hold all 24 bits
     uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
@@ -185,8 +183,12 @@ static int launch_dense_vec(DenseArgs a, int role, hipStream_t s) {
 }
 
 int launch_dense(DenseArgs a, int role, int max_nodes, hipStream_t s) {
-    a.m_chunks = ((max_nodes + 15) / 16 + kDenseTiles - 1) / kDenseTiles;
-    return a.d <= 16 ? launch_dense_vec<1>(a, role, s) : a.d <= 32 ? launch_dense_vec<2>(a, role, s) : launch_dense_vec<4>(a, role, s);
+    a.m_chunks = dense_row_chunks(max_nodes);
+    switch (dense_vec(a.d)) {
+        case 1: return launch_dense_vec<1>(a, role, s);
+        case 2: return launch_dense_vec<2>(a, role, s);
+        default: return launch_dense_vec<4>(a, role, s);
+    }
 }
 
 }  // namespace hag

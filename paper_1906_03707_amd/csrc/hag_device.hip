@@ -119,18 +119,6 @@ static Workspace carve(const hag_handle *h, hag_op_t op, int64_t d, void *base) 
     return w;
 }
 
-// Longest item that a single sub-group of lanes takes; longer ones get a whole workgroup.
-static int64_t block_threshold(const hag_handle *h, const Plan &p, int64_t d) {
-    const int64_t sub_max = h->knobs.sub_max;
-    const int64_t nsg = kBlock / gather_lpr(d, p.np);
-    // A launch too small to fill the device with one sub-group per row (the stages of
-    // a small HAG) lasts as long as its longest single-sub-group row: there a row gets
-    // a workgroup much sooner.
-    const int64_t n_all = p.part_begin[p.np] - p.part_begin[0];
-    const bool small_launch = n_all <= 256 * 8 * nsg;
-    return sub_max > 0 ? sub_max : small_launch ? 16 : std::max<int64_t>(64, 8 * nsg);
-}
-
 // Whether a pass over `plans` (its phases in execution order) can run as one launch: a small
 // HAG whose launches are short against the gaps between them, no row cut into pieces (the fold
 // of partial rows would be one more phase per launch), feature columns in one chunk.
@@ -162,7 +150,7 @@ static int run_fused(const hag_handle *h, const std::vector<const Plan *> &plans
         ph.items = p.d_items;
         ph.col = cols[k];
         ph.n_items = (int64_t)p.items.size();
-        ph.n_block = long_items(p, 0, block_threshold(h, p, base.d));
+        ph.n_block = long_items(p, 0, block_threshold(h->knobs.sub_max, p, gather_lpr(base.d, p.np)));
         const bool last = k == np - 1;
         ph.out = last ? final_out : agg_out;
         ph.out_id = last ? final_out_id : agg_out_id;
@@ -218,7 +206,7 @@ static int run_plan(const hag_handle *h, const Plan &p, const int32_t *d_col, Ga
     // A row is worth a whole workgroup when each of its 256/LPR sub-groups still gets about
     // eight neighbours, and needs one when a single sub-group would walk it for too long.
     {
-        const int64_t threshold = block_threshold(h, p, a.d);
+        const int64_t threshold = block_threshold(h->knobs.sub_max, p, gather_lpr(a.d, p.np));
         for (int k = 0; k < p.np; ++k) {
             a.seg[k].begin = p.part_begin[k];
             a.seg[k].n_items = p.part_begin[k + 1] - p.part_begin[k];
@@ -356,16 +344,6 @@ static int launch_component(const hag_handle *h, bool naive, hag_op_t op, int64_
 }
 
 // The batch of small graphs as dense products (f32 sums); the workspace, the lists and the aggregation nodes are not needed.
-// Its time depends on the graphs' sizes and hardly on their edges; the list form's depends on the edges.  Above 32 columns the dense form won
-// everywhere (1500 graphs of 250 nodes, mean degree 5, d = 64: 138 against 169 us for both passes); at up to 32 columns the two meet at a mean degree
-// of about 37 for 250 nodes (d = 8: 62 and 61 us) and below 1 for 74 (degree 3.7, d = 20: 45 against 62 us), with 128 nodes of
-// degree 2.5 on the list's side (39 against 33 us): about the cube of the largest graph's nodes, as its work per node grows with their square.
-static bool dense_applies(const hag_handle *h, hag_op_t op, int64_t d) {
-    const Components &c = h->comp;
-    if (!c.dense || op == HAG_MAX) return false;
-    const double nodes = (double)c.max_nodes;
-    return c.dense_always || d > 32 || (double)h->e * 417000.0 >= nodes * nodes * nodes * (double)h->n;
-}
 static int run_dense(const hag_handle *h, bool naive, bool backward, hag_op_t op, int64_t d, const float *in, float *out, hipStream_t s) {
     DenseArgs a{};
     a.meta = h->comp.d_dense_meta;
@@ -379,19 +357,6 @@ static int run_dense(const hag_handle *h, bool naive, bool backward, hag_op_t op
     a.d = (int32_t)d;
     a.count = h->comp.count;
     return launch_dense(a, (naive ? 2 : 0) + (backward ? 1 : 0), h->comp.max_nodes, s);
-}
-
-// Whether a whole pass over the input graph's own lists is expected to be faster than the pass over the HAG, which aggregates the same (the
-// two are equivalent graphs).  The HAG's aggregation nodes cost launches of their own and 25 to 60 MB more rows that compete for the L2s, and what it
-// saves are mostly rows that hit there.  Measured, plain lists against HAG (forward; transposed pass), d = 128:
-//   1025 and 4096 nodes, 5 to 8 % fewer row reads:            14 / 17 us;    14 / 17 us (launches)
-//   power-law graph, 1.6 M edges, 2 to 4 % fewer:             88 / 98 us;    88 / 96 us
-//   65536 nodes, 8.4 M edges, 9 to 15 % fewer:               213 / 210 us;  213 / 227 us; d = 512: 846 / 842 us; 846 / 897 us
-//   131072 nodes, 26 M edges, 10 to 15 % fewer:              650 / 625 us;  645 / 625 us
-// and a max gains nothing at any of these sizes (934 / 927 us in the last, 272 / 286 us in the one before).
-static bool plain_lists_are_faster(const hag_handle *h, hag_op_t op) {
-    if (h->a == 0 || !h->knobs.route || h->knobs.fuse_max_items > 0) return false;
-    return op == HAG_MAX || h->e < 16000000 || (double)(h->st.h + 2 * h->a) > 0.92 * (double)h->e;
 }
 
 // The plans of a pass over the HAG in execution order, and the column array of each.
@@ -408,17 +373,28 @@ static PassPlans hag_pass(const hag_handle *h, bool backward) {
     return p;
 }
 
-// The way a pass takes (HAG_ROUTE_*): the one place where it is decided.
+// The way a pass takes (HAG_ROUTE_*): the one place where it is decided, from sizes and knobs alone.  The pass over the HAG, the pass over the input
+// graph's own lists and, for a batch of small graphs, the dense products aggregate the same; a whole pass takes the one expected to be fastest (see hag_cost.cpp).
 static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases) {
     if (op == HAG_MAX && backward) return h->knobs.deterministic_max_backward ? HAG_ROUTE_LISTS : HAG_ROUTE_SCATTER;   // looks at no list of the HAG
-    const bool whole = phases == HAG_PHASE_ALL;
-    naive = naive || (whole && plain_lists_are_faster(h, op));
-    // a batch of small graphs: the whole pass is one launch, on the matrix cores or out of LDS
-    if (whole && dt == HAG_F32 && dense_applies(h, op, d)) return HAG_ROUTE_DENSE;
-    if (whole && component_layout(h, naive, backward, op, d).total > 0) return naive ? HAG_ROUTE_COMPONENT_LISTS : HAG_ROUTE_COMPONENT_HAG;
-    if (naive) return HAG_ROUTE_LISTS;
+    if (phases != HAG_PHASE_ALL) return naive ? HAG_ROUTE_LISTS : HAG_ROUTE_HAG;
+    const bool one_launch = h->knobs.fuse_max_items > 0;
+    const CompLayout on_hag = component_layout(h, false, backward, op, d), on_lists = component_layout(h, true, backward, op, d);
+    FormQuery q{};
+    q.max = op == HAG_MAX;
+    q.backward = backward;
+    q.hag_allowed = !naive;
+    q.lists_allowed = naive || (h->a > 0 && h->knobs.route && !one_launch);
+    q.dense_allowed = h->comp.dense && dt == HAG_F32 && op != HAG_MAX && !h->comp.dense_always;
+    q.d = d;
+    q.component_lds[0] = on_hag.total * on_hag.parts;     // (priced with its columns in one piece: the pieces are a knob for experiments)
+    q.component_lds[1] = on_lists.total * on_lists.parts;
+    const int form = h->comp.dense_always && dt == HAG_F32 && op != HAG_MAX ? kFormDense : cheapest_form(h, q);
+    if (form == kFormDense) return HAG_ROUTE_DENSE;
+    if (form == kFormLists) return on_lists.total > 0 ? HAG_ROUTE_COMPONENT_LISTS : HAG_ROUTE_LISTS;
+    if (on_hag.total > 0) return HAG_ROUTE_COMPONENT_HAG;
     // a small HAG: aggregation-node stages and the gather over V as one launch
-    return whole && fusable(h, d, hag_pass(h, backward).plans) ? HAG_ROUTE_ONE_LAUNCH : HAG_ROUTE_HAG;
+    return one_launch && fusable(h, d, hag_pass(h, backward).plans) ? HAG_ROUTE_ONE_LAUNCH : HAG_ROUTE_HAG;
 }
 
 template <typename T, int RED>

@@ -13,9 +13,6 @@
 
 namespace hag {
 
-constexpr int kBlock = 256;  // 4 wavefronts of 64 lanes
-constexpr int kWave = 64;
-
 // R_SUMIF: sum of the rows' elements whose entry in a second, int32 matrix (GatherArgs::filter, same
 // shape and row index as src_lo) equals the id of the output row: the backward pass of max as a
 // gather, gx[u, f] = sum over consumers v of u of gy[v, f] where argmax[v, f] == u, in a fixed order
@@ -340,25 +337,6 @@ static inline int hip_fail(hipError_t e, const char *what) {
         hipError_t _e = (expr);                         \
         if (_e != hipSuccess) return hip_fail(_e, #expr); \
     } while (0)
-
-// lanes that share one feature row: the power of two that covers d/4 float4 columns, 4..64
-static inline int pick_lpr(int64_t d) {
-    int64_t q = d / 4;
-    int l = 4;
-    while (l < 64 && l < q) l <<= 1;
-    return l;
-}
-
-// The same for a gather over np source classes: at most 32 lanes (128 columns) where the launch is cut by source, so that wide rows are gathered
-// in more column chunks, one after the other, each with a smaller share of the matrix per XCD
-// (forward sum over 26 M edges, 131072 nodes: d = 256 1425 -> 1341 us, d = 512 2838 -> 2676 us; narrower chunks gain nothing, the list work per byte grows).
-static inline int gather_lpr(int64_t d, int np) { return np > 1 ? std::min(pick_lpr(d), 32) : pick_lpr(d); }
-
-// Lanes that share one short item of a gather: at least 16, so that narrow rows (4 or 8 lanes each) are read by 4 or 2 streams of lanes
-// side by side.  With one stream per item an item of 16 columns was a chain of one id load and four row loads per four entries, and took
-// longer than one of 64 columns.  Forward sum over 8.4 M edges (65536 nodes, mean degree 128): d = 16 142 -> 56 us, d = 32 95 -> 73 us (d = 64:
-// 117 us); over 26 M edges (131072 nodes): 244 -> 150 and 198 -> 194 us; max at d = 16 192 -> 86 us.
-constexpr int item_lanes(int lpr) { return lpr < 16 ? 16 : lpr; }
 
 // Defined in the gather units (one per element type and reduction), used by hag_device.hip.
 template <typename T, int RED, int ROLE>

@@ -743,6 +743,17 @@ int64_t long_items(const Plan &p, int k, int64_t threshold) {
     return (int64_t)(it - b);
 }
 
+// Longest item that a single sub-group of lanes takes; longer ones get a whole workgroup.
+int64_t block_threshold(int64_t sub_max, const Plan &p, int lpr) {
+    const int64_t nsg = kBlock / lpr;
+    // A launch too small to fill the device with one sub-group per row (the stages of
+    // a small HAG) lasts as long as its longest single-sub-group row: there a row gets
+    // a workgroup much sooner.
+    const int64_t n_all = p.part_begin[p.np] - p.part_begin[0];
+    const bool small_launch = n_all <= 256 * 8 * nsg;
+    return sub_max > 0 ? sub_max : small_launch ? 16 : std::max<int64_t>(64, 8 * nsg);
+}
+
 // ------------------------------------------------------------------------------------------
 // finalisation: levels, level-ordered forward form, transposes, schedules, statistics
 // ------------------------------------------------------------------------------------------
@@ -977,6 +988,14 @@ static void build_components(hag_handle *h) {
         c.meta[4 * k + 2] = c.agg_ptr[k];
         c.meta[4 * k + 3] = (c.agg_ptr[k + 1] - c.agg_ptr[k]) | ((int32_t)c.n_stages[k] << 16);
     }
+    for (int i = 0; i < 2; ++i) {
+        const LocalLists &over_hag = i ? c.bwd_all : c.fwd, &plain = i ? c.nbwd : c.nfwd;
+        c.entries[0][i] = (double)(i ? c.bwd_agg : c.fwd_agg).col.size();
+        for (size_t k = 1; k < over_hag.items.size(); k += 2) c.entries[0][i] += over_hag.items[k] & 0xffff;
+        c.entries[1][i] = (double)plain.col.size();
+    }
+    c.steps = 0;
+    for (uint8_t v : c.n_stages) c.steps += v;
     // Adjacency bits for the dense form, unless one of the knobs of the list form is given (HAG_COMPONENT_DENSE: 0 never, 1 by the rule of
     // dense_applies, 2 always)
     const bool list_knob = env_i64("HAG_COMPONENT_EXPAND", -1) != -1 || env_i64("HAG_COMPONENT_PAD", 0) != 0 ||
@@ -1035,7 +1054,7 @@ static int finalize_from_builder(hag_handle *h, Builder &b) {
         k.fuse_max_items = env_i64("HAG_FUSE_MAX_ITEMS", 0);   // off: measured slower than one launch per stage
         k.spin_limit = env_i64("HAG_SPIN_LIMIT", 1 << 18);
         // (a knob that shapes the pass over the HAG asks for that pass)
-        k.route = env_i64("HAG_ROUTE", std::getenv("HAG_STAGE_EXTRA_ROWS") || std::getenv("HAG_FUSE_MAX_ITEMS") ? 0 : 1) != 0;
+        k.route = env_i64("HAG_ROUTE", std::getenv("HAG_STAGE_EXTRA_ROWS") || std::getenv("HAG_FUSE_MAX_ITEMS") || std::getenv("HAG_COMPONENT_EXPAND") ? 0 : 1) != 0;
     }
     // depth(original) = 0, depth(w) = 1 + max over its inputs; creation order is topological
     std::vector<int32_t> order(a);
@@ -1173,6 +1192,17 @@ static int finalize_from_builder(hag_handle *h, Builder &b) {
     for (auto &p : h->p_bwd_stage) h->max_slots = std::max(h->max_slots, p.n_slots);
     for (auto &p : h->p_fwd_stage) h->max_slots = std::max(h->max_slots, p.n_slots);
     build_components(h);
+    for (auto &form : h->cost) for (PassCost &c : form) c = PassCost{};
+    if (a > 0 || h->comp.dense) {
+        PassCost part[2 * 2 * kWidths];
+        parallel_for(2 * 2 * kWidths, h->e > 200000 ? host_threads() : 1, [&](int64_t i, unsigned) { estimate_pass(h, i & 1, (i >> 1) & 1, (int)(i >> 2), part[i]); });
+        for (int i = 0; i < 2 * 2 * kWidths; ++i) {
+            PassCost &c = h->cost[i & 1][(i >> 1) & 1];
+            if (i < 4) c = part[i];
+            c.miss[i >> 2] = part[i].miss[i >> 2];
+            c.fold[i >> 2] = part[i].fold[i >> 2];
+        }
+    }
     // statistics (Section 4.1: k in-neighbours cost k-1 binary aggregations; Section 5.4: one
     // row transfer per aggregated neighbour)
     hag_stats_t &s = h->st;

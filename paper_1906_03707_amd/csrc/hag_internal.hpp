@@ -1,5 +1,6 @@
 // Internal layout of a HAG handle: host arrays, launch schedules, device copies.
 #pragma once
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -29,6 +30,8 @@ constexpr int64_t kItemDependsBit = (int64_t)1 << 62;
 
 // Schedule of one gather launch (plus the optional second launch that folds the
 // partial slots of split rows).
+constexpr int kBlock = 256;      // threads of a workgroup: 4 wavefronts of 64 lanes
+constexpr int kWave = 64;
 constexpr int kPartitions = 8;   // XCDs of the device; workgroups b of one residue mod 8 share an XCD
 
 struct Plan {
@@ -47,6 +50,37 @@ struct Plan {
     // device copies
     Item *d_items = nullptr;
     Item *d_combine = nullptr;
+};
+
+// lanes that share one feature row: the power of two that covers d/4 float4 columns, 4..64
+static inline int pick_lpr(int64_t d) {
+    int64_t q = d / 4;
+    int l = 4;
+    while (l < 64 && l < q) l <<= 1;
+    return l;
+}
+
+// The same for a gather over np source classes: at most 32 lanes (128 columns) where the launch is cut by source, so that wide rows are gathered
+// in more column chunks, one after the other, each with a smaller share of the matrix per XCD
+// (forward sum over 26 M edges, 131072 nodes: d = 256 1425 -> 1341 us, d = 512 2838 -> 2676 us; narrower chunks gain nothing, the list work per byte grows).
+static inline int gather_lpr(int64_t d, int np) { return np > 1 ? std::min(pick_lpr(d), 32) : pick_lpr(d); }
+
+// Lanes that share one short item of a gather: at least 16, so that narrow rows (4 or 8 lanes each) are read by 4 or 2 streams of lanes
+// side by side.  With one stream per item an item of 16 columns was a chain of one id load and four row loads per four entries, and took
+// longer than one of 64 columns.  Forward sum over 8.4 M edges (65536 nodes, mean degree 128): d = 16 142 -> 56 us, d = 32 95 -> 73 us (d = 64:
+// 117 us); over 26 M edges (131072 nodes): 244 -> 150 and 198 -> 194 us; max at d = 16 192 -> 86 us.
+constexpr int item_lanes(int lpr) { return lpr < 16 ? 16 : lpr; }
+
+// What decides how long a pass over the lists of a graph or a HAG takes (hag_cost.cpp), summed over its launches.  Entry w of an array is
+// for rows that 4 << w lanes share.
+constexpr int kWidths = 5;
+struct PassCost {
+    double launches = 0;
+    double reads[2] = {0, 0};        // rows gathered, by launches over all sources and by launches cut by source
+    double rows = 0;                 // rows written
+    double slots = 0;                // partial rows written and folded
+    double miss[kWidths] = {};       // rows fetched into an L2 rather than found there, per column chunk
+    double fold[kWidths] = {};       // partial sums that whole-workgroup items fold through LDS, per column chunk
 };
 
 // Component-local form of a graph made of many small connected components with contiguous
@@ -70,6 +104,9 @@ struct LocalLists {
     int32_t *d_split = nullptr;
 };
 constexpr int32_t kDenseMaxNodes = 256;
+constexpr int kDenseTiles = 5;   // 16-row tiles of a wavefront of the dense form
+static inline int dense_vec(int64_t d) { return d <= 16 ? 1 : d <= 32 ? 2 : 4; }   // feature columns per lane
+static inline int dense_row_chunks(int32_t max_nodes) { return ((max_nodes + 15) / 16 + kDenseTiles - 1) / kDenseTiles; }
 struct Components {
     bool enabled = false;
     bool expanded = false;                   // aggregation lists are expressed over original rows (one stage)
@@ -96,6 +133,8 @@ struct Components {
     std::vector<int32_t> dense_meta;         // [4*count] first node, #nodes, first word of its bits, 0
     uint32_t *d_dense_fwd = nullptr, *d_dense_bwd = nullptr;
     int32_t *d_dense_meta = nullptr;
+    double entries[2][2] = {};               // list entries a pass walks, [over the HAG, over the plain lists][forward, backward]
+    double steps = 0;                        // stages of aggregation nodes, all components together
     std::vector<int32_t> meta;               // [4*count] first node, #nodes, first slot, #agg | #stages << 16
     int32_t *d_meta = nullptr;
     uint8_t *d_stage = nullptr;
@@ -177,6 +216,7 @@ struct hag_handle {
     std::vector<hag::Plan> p_bwd_stage;    // [stages]; rows of ht that belong to the stage
     hag::Plan p_bwd_src;                   // rows 0..n-1 of ht
     hag::Plan p_naive_fwd, p_naive_bwd;
+    hag::PassCost cost[2][2];              // [over the HAG, over the plain lists][forward, backward]; empty if a == 0
     int64_t max_slots = 0;
     hag::Components comp;
 
@@ -197,6 +237,13 @@ int finalize(hag_handle *h, uint32_t flags);  // levels, forward form, transpose
 void build_plan(const Csr &c, std::vector<int32_t> &dcol, int64_t row_begin, int64_t row_end, Plan &p, bool partition,
                 int64_t split);
 int64_t long_items(const Plan &p, int k, int64_t threshold);
+int64_t block_threshold(int64_t sub_max, const Plan &p, int lpr);
+// hag_cost.cpp
+void estimate_pass(const hag_handle *h, bool lists, bool backward, int w, PassCost &c);
+// The form of a whole pass, by expected time.  component_lds: LDS bytes of the component pass over [the HAG, the lists], 0 where it does not apply.
+enum { kFormHag = 0, kFormLists = 1, kFormDense = 2 };
+struct FormQuery { bool max, backward, hag_allowed, lists_allowed, dense_allowed; int64_t d; size_t component_lds[2]; };
+int cheapest_form(const hag_handle *h, const FormQuery &q);
 // hag_device.hip
 void free_device(hag_handle *h);
 }  // namespace hag

@@ -1,4 +1,5 @@
 """Which way a pass takes (hag_route): a host decision, checked without a GPU."""
+import numpy as np
 import pytest
 
 from paper_1906_03707_amd import binding as B
@@ -30,3 +31,85 @@ def test_route_refuses_what_the_calls_refuse():
     assert h.route("max", backward=True) == "scatter"
     h.set_option(B.HAG_OPT_DETERMINISTIC_MAX_BACKWARD, 1)
     assert h.route("max", backward=True) == "lists"
+
+
+def dense_groups(n, size, cross, seed):
+    """Complete groups of `size` consecutive nodes and `cross` random edges: a HAG of |V| nodes saves nearly every row read."""
+    rng = np.random.default_rng(seed)
+    g = np.arange(n) // size
+    rows = np.repeat(np.arange(n), size)
+    cols = np.repeat(g * size, size) + np.tile(np.arange(size), n)
+    a, b = rng.integers(0, n, cross), rng.integers(0, n, cross)
+    keys = np.unique(np.concatenate([rows, a, b]).astype(np.int64) * n + np.concatenate([cols, b, a]))
+    r, c = keys // n, keys % n
+    r, c = r[r != c], c[r != c]
+    return np.concatenate([[0], np.cumsum(np.bincount(r, minlength=n))]).astype(np.int64), c.astype(np.int32)
+
+
+def ways(h, op="sum", dtype=B.HAG_F32, widths=(16, 64, 128, 512)):
+    return [[h.route(op, dtype, d, back) for back in (False, True)] for d in widths]
+
+
+def test_a_hag_that_saves_most_rows_is_used_whatever_the_graph_size():
+    # 2 M edges, 95 % fewer row reads; measured on a graph of twice the size, d = 128: 25 against 83 us for a sum, 35 against 114 us for a max
+    rowptr, col = dense_groups(10000, 200, 10000, 3)
+    h = B.hag_search(rowptr, col, 10000)
+    st = h.stats()
+    assert st["e"] < 16_000_000 and st["h"] + 2 * st["a"] < 0.1 * st["e"]
+    assert ways(h, widths=(64, 128, 512)) == [["hag", "hag"]] * 3
+    assert ways(h, dtype=B.HAG_I32, widths=(64, 128, 512)) == [["hag", "hag"]] * 3
+    assert ways(h, "max", widths=(64, 128, 512)) == [["hag", "scatter"]] * 3
+    few = h.prefix(600)                                     # 6 % fewer: 82 against 82 us forward, 90 against 82 transposed, at d = 128
+    assert few.stats()["h"] > 0.9 * st["e"] and ways(few)[2][1] == "lists"
+
+
+def test_a_hag_that_saves_little_of_a_small_graph_is_not():
+    # launches: 10 against 7 us (1025 nodes); rows that miss either way: 105 against 88 us (57 k nodes, 6 % fewer reads)
+    for rowptr, col in (synth.sbm(25, 41, 0.2, 0.001, seed=101), synth.holme_kim(6000, 14, 0.5, seed=102)):
+        h = B.hag_search(rowptr, col, (rowptr.size - 1) // 4)
+        assert {w[0] for w in ways(h)} == {w[1] for w in ways(h)} == {"lists"}
+
+
+def test_batches():
+    # time of both passes, us: dense products, LDS lists over the HAG, over the plain lists
+    def batch(count, size, density, frac):
+        rowptr, col, gp = synth.er_batch(count, size, density, seed=104)
+        return B.hag_search_batched(rowptr, col, gp, frac)
+    full = batch(1500, 74, 0.9, 1.0)
+    assert ways(full, widths=(64,)) == [["dense", "dense"]]                                    # 31, 72, 64
+    assert ways(full, dtype=B.HAG_I32, widths=(20,)) == [["component_hag", "component_hag"]]   # -, 38, 61
+    sparse = batch(100, 250, 0.02, 0.25)
+    # few large sparse graphs: at d = 128 no form fits in LDS; 37, 32 (over the HAG, from L2), 23
+    assert ways(sparse, widths=(128,)) == [["lists", "lists"]]
+    assert "dense" not in ways(sparse, widths=(64,))[0]                                        # 35, 22, 38
+    few = batch(200, 128, 0.04, 0.25)
+    assert ways(few, widths=(64, 128, 256)) == [["dense", "dense"]] * 3                        # 22, 27, 23; 24, 34, 24; 34, 54, 42
+
+
+def test_knobs_that_shape_a_form_keep_it(monkeypatch):
+    rowptr, col, gp = synth.er_batch(150, 40, 0.6, seed=5)
+    search = lambda: B.hag_search_batched(rowptr, col, gp, 0.25)   # noqa: E731
+    for expand in ("0", "1"):
+        monkeypatch.setenv("HAG_COMPONENT_EXPAND", expand)
+        assert ways(search(), widths=(16, 64)) == [["component_hag"] * 2] * 2
+    monkeypatch.delenv("HAG_COMPONENT_EXPAND")
+    want = ways(search(), widths=(32, 64, 128))
+    monkeypatch.setenv("HAG_COMPONENT_PARTS", "2")
+    assert ways(search(), widths=(32, 64, 128)) == want
+    monkeypatch.setenv("HAG_ROUTE", "0")
+    monkeypatch.setenv("HAG_COMPONENT_DENSE", "0")
+    assert ways(search(), widths=(32, 64, 128)) == [["component_hag"] * 2] * 3
+    monkeypatch.delenv("HAG_COMPONENT_PARTS")
+    monkeypatch.delenv("HAG_COMPONENT_DENSE")
+    rowptr, col = synth.holme_kim(2000, 8, 0.5, seed=6)
+    h = B.hag_search(rowptr, col, 500)
+    assert ways(h) == [["hag", "hag"]] * 4 and ways(h, "max") == [["hag", "scatter"]] * 4
+
+
+def test_the_way_depends_on_the_handle_alone():
+    rowptr, col = dense_groups(1000, 50, 500, 7)
+    h = B.hag_search(rowptr, col, 1000)
+    left, right, _ = h.get_merges()
+    again = B.hag_from_merges(rowptr, col, left, right)
+    for op in ("sum", "max", "gcn"):
+        assert ways(h, op, widths=range(4, 300, 28)) == ways(again, op, widths=range(4, 300, 28)) == ways(h.prefix(left.size), op, widths=range(4, 300, 28))

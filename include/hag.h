@@ -25,7 +25,9 @@
  * Semantics taken where the paper is silent:
  *   empty N(v): sum 0, mean 0, max 0 with argmax -1 (and no gradient);
  *   mean = sum / |N(v)| with the degree of the INPUT graph (not of the HAG);
- *   max ties go to the smallest original node id; argmax holds original ids.
+ *   max ties go to the smallest original node id; argmax holds original ids;
+ *   NaN: sums propagate it to the nodes that aggregate it and to no other; max is defined for numbers (infinities
+ *   included) only: with a NaN among the neighbours the result is one of them, which one depends on the form that runs.
  *
  * Ownership.  The library owns hag_t and every array returned by a getter (valid
  * until hag_free).  The caller owns all arrays it passes in; host arrays are

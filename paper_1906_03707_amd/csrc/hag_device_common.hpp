@@ -181,6 +181,12 @@ __device__ __forceinline__ void add4(int4 &a, const int4 &b) {
 __device__ __forceinline__ void scale4(float4 &a, float s) { a.x *= s; a.y *= s; a.z *= s; a.w *= s; }
 __device__ __forceinline__ void scale4(int4 &, float) {}
 
+// NaN as the smallest value there is
+__device__ __forceinline__ void not_nan4(float4 &v) {
+    v.x = v.x == v.x ? v.x : -INFINITY; v.y = v.y == v.y ? v.y : -INFINITY;
+    v.z = v.z == v.z ? v.z : -INFINITY; v.w = v.w == v.w ? v.w : -INFINITY;
+}
+__device__ __forceinline__ void not_nan4(int4 &) {}
 // (value, id) max with ties to the smaller id; id < 0 means "nothing yet"
 template <typename S>
 __device__ __forceinline__ void max1(S &v, int &vi, S w, int wi) {

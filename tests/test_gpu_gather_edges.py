@@ -104,3 +104,26 @@ def test_one_launch_max_with_ties(B, d, monkeypatch):
             gw, gs = oracle.naive_backward(rowptr, col, gy, "max", am)
             assert np.all(np.abs(h.backward(torch.from_numpy(gy).cuda(), "max", argmax=who).cpu().numpy() - gw) <= 1e-5 * gs)
         h.check()                                                     # no wait gave up
+
+
+@pytest.mark.parametrize("d", [4, 16, 32, 64])
+def test_max_passes_over_nan_in_short_lists(B, d):
+    # the scan takes the first entry and then whatever is greater: a NaN stays if it comes first and hides nothing anywhere else, however many
+    # streams of lanes share the list
+    rng = np.random.default_rng(d)
+    n = 400
+    rows = [np.sort(rng.choice(n, k, replace=False)) for k in rng.integers(1, 16, n)]
+    rowptr, col = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64), np.concatenate(rows).astype(np.int32)
+    h = B.hag_search(rowptr, col, 0).upload()
+    x = rng.integers(-3, 4, (n, d)).astype(np.float32)
+    x[rng.random((n, d)) < 0.3] = np.nan
+    x[rng.random((n, d)) < 0.2] = -np.inf
+    want, who = np.empty_like(x), np.empty((n, d), np.int32)
+    for v, r in enumerate(rows):
+        best, at = x[r[0]].copy(), np.full(d, r[0])
+        for u in r[1:]:
+            take = x[u] > best                              # (False beside a NaN)
+            best, at = np.where(take, x[u], best), np.where(take, u, at)
+        want[v], who[v] = best, at
+    y, am = h.forward(torch.from_numpy(x).cuda(), "max")
+    assert np.array_equal(y.cpu().numpy(), want, equal_nan=True) and np.array_equal(am.cpu().numpy(), who)

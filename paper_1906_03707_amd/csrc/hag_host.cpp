@@ -1195,7 +1195,7 @@ static int finalize_from_builder(hag_handle *h, Builder &b) {
     for (auto &form : h->cost) for (PassCost &c : form) c = PassCost{};
     if (a > 0 || h->comp.dense) {
         PassCost part[2 * 2 * kWidths];
-        parallel_for(2 * 2 * kWidths, h->e > 200000 ? host_threads() : 1, [&](int64_t i, unsigned) { estimate_pass(h, i & 1, (i >> 1) & 1, (int)(i >> 2), part[i]); });
+        parallel_for(2 * 2 * kWidths, h->e > 4000000 ? host_threads() : 1, [&](int64_t i, unsigned) { estimate_pass(h, i & 1, (i >> 1) & 1, (int)(i >> 2), part[i]); });
         for (int i = 0; i < 2 * 2 * kWidths; ++i) {
             PassCost &c = h->cost[i & 1][(i >> 1) & 1];
             if (i < 4) c = part[i];

@@ -97,3 +97,26 @@ def test_list_form(B, parts, monkeypatch):
         gx, gs = oracle.naive_backward(rowptr, col, x, op)
         assert np.all(np.abs(h.forward(xd, op).cpu().numpy() - y) <= 1e-5 * s), op
         assert np.all(np.abs(h.backward(xd, op).cpu().numpy() - gx) <= 1e-5 * gs), op
+
+
+@pytest.mark.parametrize("d", [12, 64])
+def test_small_values_are_summed_like_any_other(B, d, monkeypatch):
+    # features and gradients that have underflowed partly or all the way (down to the smallest subnormal) beside ordinary ones
+    rowptr, col, gp = directed_batch([5, 40, 70, 256] * 20, 0.3, seed=6)
+    monkeypatch.setenv("HAG_COMPONENT_DENSE", "2")
+    h = B.hag_search_batched(rowptr, col, gp, 0.0).upload()
+    rng = np.random.default_rng(7)
+    n = rowptr.size - 1
+    ordinary = synth.features_f32(n, d, 8)
+    spread = (rng.normal(size=(n, d)) * 2.0 ** rng.integers(-149, 1, (n, d))).astype(np.float32)
+    below = (rng.integers(-5, 6, (n, d)) * 2.0 ** -149).astype(np.float32)
+    assert np.count_nonzero(below) > 0 and h.route("sum", d=d) == "dense"
+    for x in (spread, np.where(rng.random((n, d)) < 0.1, below, ordinary), below):
+        xd = torch.from_numpy(x).cuda()
+        for op in ("sum", "mean", "gcn"):
+            y, s, _ = oracle.naive_forward(rowptr, col, x, op)
+            gx, gs = oracle.naive_backward(rowptr, col, x, op)
+            # fp32 rounding as in the other tests; below 2^-126 fp32 has units of 2^-149, so there a rounding is off by up to half of that: one for the
+            # sum and one for its factor going forward, one per factor times gradient (257 terms at most) and one for the sum going back
+            assert np.all(np.abs(h.forward(xd, op).cpu().numpy() - y) <= 1e-5 * s + 1.01 * 2.0 ** -149), op
+            assert np.all(np.abs(h.backward(xd, op).cpu().numpy() - gx) <= 1e-5 * gs + 258 * 2.0 ** -150), op

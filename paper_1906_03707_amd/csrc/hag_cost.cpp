@@ -8,11 +8,12 @@
 namespace hag {
 
 // Misses are those of one XCD's L2 under the plan's own order, a first-in first-out cache of this many bytes (of the 4 MB, some holds ids and
-// results): misses per row read, from a run of at most kSampleReads reads at the start of the plan and one in its middle.
+// results): misses per row read, from a run of at most kSampleReads reads at the start of the plan and one in its middle (in a batch of small graphs
+// every stretch is like any other: shorter runs).
 constexpr double kCacheBytes = 3e6;
-constexpr int64_t kSampleReads = 1 << 20;
+constexpr int64_t kSampleReads = 1 << 20, kSampleReadsBatch = 1 << 14;
 
-static double miss_rate(const Plan &p, const std::vector<int32_t> &col, int64_t n_ids, int lpr, int64_t n_long, double plan_reads) {
+static double miss_rate(const Plan &p, const std::vector<int32_t> &col, int64_t n_ids, int lpr, int64_t n_long, double plan_reads, int64_t sample) {
     const int64_t cap = (int64_t)(kCacheBytes / (16 * lpr)), n_all = p.part_begin[1];
     if (n_ids <= cap) return std::min(1., (double)n_ids / std::max(1., plan_reads / kPartitions));   // every row once
     std::vector<int32_t> seen((size_t)n_ids, INT32_MIN);
@@ -21,7 +22,7 @@ static double miss_rate(const Plan &p, const std::vector<int32_t> &col, int64_t 
     int64_t misses = 0, reads = 0, counted = 0, counted_misses = 0;
     for (const int64_t from : {(int64_t)0, n_groups / 2 / step * step}) {
         // what was cached before a run counts as gone; a run counts from when its cache is full
-        const int64_t gone = misses + cap, stop = reads + kSampleReads;
+        const int64_t gone = misses + cap, stop = reads + sample;
         int64_t start_reads = -1, start_misses = 0;
         misses = gone;
         const int64_t first_read = reads;
@@ -56,7 +57,7 @@ static void add_plan(const hag_handle *h, const Plan &p, const std::vector<int32
     }
     double reads = 0;
     for (const Item &it : p.items) reads += it.cnt;
-    c.miss[w] += reads * miss_rate(p, col, h->n + h->a, lpr, long0, reads);
+    c.miss[w] += reads * miss_rate(p, col, h->n + h->a, lpr, long0, reads, h->comp.enabled ? kSampleReadsBatch : kSampleReads);
     c.fold[w] += (double)n_long * (kBlock / lpr);
     if (w > 0) return;
     c.launches += p.combine.empty() ? 1 : 2;

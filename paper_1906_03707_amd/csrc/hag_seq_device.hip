@@ -891,14 +891,16 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_wide_kernel(SeqRevArgs A) 
                 const size_t cell = (size_t)beg + t;
                 if (A.pending && keep >= 0) seq_wait_pending(A, keep);
                 // the product of the step before left dh_prev of this path in its row: this step's dh.  Only this path's own
-                // lanes touch the row between the barriers, and they read all of it before they overwrite it below (one wavefront,
-                // program order).
+                // lanes touch the row between the barriers, and they read all of it before any of them overwrites it below: one
+                // wavefront, whose LDS accesses take effect in program order, and the fence keeps the compiler to that order.
                 if (t + 1 < len) {
 #pragma unroll
                     for (int it = 0; it < IT; ++it)
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
                             if (32 * it + 8 * e < hidden) dhv[it][e] = zg[sj * ZG + 32 * it + 8 * e + part];
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
                 }
 #pragma unroll
                 for (int it = 0; it < IT; ++it)

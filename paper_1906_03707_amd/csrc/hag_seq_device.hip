@@ -44,7 +44,7 @@ struct hag_seq {
     bool one_launch = true;           // HAG_SEQ_ONE_LAUNCH (default 1): all levels in one launch, paths waiting for the states they start from
     int32_t spin_limit = 1 << 21;     // HAG_SPIN_LIMIT: polls (about half a microsecond apart) after which such a wait gives up
     bool wait_unreachable = false;    // tests only: flags are never set, so every wait gives up
-    int32_t *d_final = nullptr, *d_paths = nullptr, *d_step_x = nullptr, *d_step_out = nullptr;   // d_paths: padded to whole tiles per level
+    int32_t *d_final = nullptr, *d_paths = nullptr, *d_step_out = nullptr;   // d_paths: padded to whole tiles per level
     int32_t *d_paths_by_depth = nullptr;                    // likewise per depth group
     // for the backward pass: per step where its h_{t-1} lives (>= 0: that step's tape row, -1: the zero state,
     // <= -2: state row -(value) - 2); all three in the order of the input row that the steps read: the steps, their step_prev, the
@@ -1460,7 +1460,6 @@ void hag_seq_free(hag_seq_t *h) {
     if (h->d_step_g) (void)hipFree(h->d_step_g);
     if (h->d_xt_idx) (void)hipFree(h->d_xt_idx);
     if (h->d_pending_init) (void)hipFree(h->d_pending_init);
-    if (h->d_step_x) (void)hipFree(h->d_step_x);
     if (h->d_step_out) (void)hipFree(h->d_step_out);
     if (h->d_gave_up) (void)hipFree(h->d_gave_up);
     delete h;
@@ -1524,7 +1523,6 @@ int hag_seq_upload(hag_seq_t *h) {
         HIP_TRY(put(&h->d_paths, padded(h->paths, h->level_ptr, h->tile_ptr)));
         HIP_TRY(put(&h->d_paths_by_depth, padded(h->paths_by_depth, h->depth_ptr, h->depth_tile_ptr)));
     }
-    HIP_TRY(put(&h->d_step_x, h->step_x));
     HIP_TRY(put(&h->d_step_out, h->step_out));
     HIP_TRY(put(&h->d_xt_prev, h->xt_prev));
     HIP_TRY(put(&h->d_xt_seg, h->xt_seg));

@@ -140,6 +140,20 @@ def _dtype_code(t):
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
+_torch_calls = None
+
+
+def _resolve_torch_calls():
+    """(current_device, current raw stream of a device): torch's short forms where this build of it has them, else the public ones, which
+    take 0.2 us and 0.6 us more (a Stream object is built first)."""
+    import torch
+    global _torch_calls
+    device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+    stream = getattr(torch._C, "_cuda_getCurrentRawStream", lambda index: torch.cuda.current_stream(index).cuda_stream)
+    _torch_calls = device, stream
+    return _torch_calls
+
+
 def _stream_ptr():
     import torch
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
@@ -277,12 +291,13 @@ class Hag:
             out = torch.empty_like(a)
         if op == "max" and argmax is None:
             argmax = torch.empty_like(a, dtype=torch.int32)
-        device = torch._C._cuda_getDevice()
-        stream = torch._C._cuda_getCurrentRawStream(device)
+        current_device, raw_stream = _torch_calls or _resolve_torch_calls()
+        device = current_device()
+        stream = raw_stream(device)
         if workspace is None:
             # one buffer per (device, stream): calls enqueued on different streams may overlap
             index = a.get_device()
-            key = (index, stream if index == device else torch._C._cuda_getCurrentRawStream(index))
+            key = (index, stream if index == device else raw_stream(index))
             workspace = self._ws.get(key)
             if workspace is None or workspace.numel() < nbytes:
                 workspace = self._ws[key] = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=a.device)

@@ -512,3 +512,25 @@ def test_deterministic_max_backward_is_bit_reproducible_and_matches_oracle(B, mo
                 else:
                     assert_close(det[0], gx_ref, gs, f"deterministic f32 d={d}")
                     assert_close(atomic, gx_ref, gs, f"atomic f32 d={d}")
+
+
+@pytest.mark.parametrize("short_form", [True, False])
+def test_calls_run_on_the_current_stream(B, monkeypatch, short_form):
+    # whichever way the stream is asked for: work queued on a side stream behind a long kernel is ordered with it
+    if not short_form:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+        monkeypatch.setattr(B, "_torch_calls", None)            # put back, resolved anew, after the test
+        B._resolve_torch_calls()
+    rowptr, col = synth.random_graph(300, 0.1, seed=5)
+    h = B.hag_search(rowptr, col, 75).upload()
+    x = dev(synth.features_f32(300, 64, 6))
+    want = h.forward(x, "sum").clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        late = torch.zeros_like(x)
+        torch.cuda._sleep(20_000_000)
+        late.copy_(x)
+        got = h.forward(late, "sum")
+    side.synchronize()
+    assert torch.equal(got, want)

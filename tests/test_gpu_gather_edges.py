@@ -41,7 +41,28 @@ def test_list_lengths(B, d, route, monkeypatch):
     monkeypatch.setenv("HAG_ROUTE", route)
     rowptr, col = edge_graph(d)
     h = B.hag_search(rowptr, col, 130).upload()
-    assert h.stats()["a"] > 20
+    assert h.stats()["a"] > 20 and h.route("sum", d=d) == h.route("max", d=d) == ("lists" if route == "1" else "hag")
+    check_against_oracle(h, rowptr, col, d)
+
+
+@pytest.mark.parametrize("d", [4, 16, 32, 128, 132, 256, 260])
+@pytest.mark.parametrize("route", ["0", "1"])
+def test_rows_cut_by_source(B, d, route, monkeypatch):
+    # every row of 8 and more entries cut into the eight source classes, wide rows in chunks of 128 columns: pieces of one entry, folds of partial rows
+    # whose winners may still be aggregation nodes
+    for k, v in dict(HAG_PARTITION_MIN_ROWS="0", HAG_PART_MIN="8", HAG_PART_SHARE_PCT="0", HAG_PART_MEAN_MIN="0", HAG_ROUTE=route).items():
+        monkeypatch.setenv(k, v)
+    rowptr, col = edge_graph(d)
+    h = B.hag_search(rowptr, col, 130).upload()
+    monkeypatch.setenv("HAG_PARTITION", "0")
+    whole = B.hag_search(rowptr, col, 130)
+    assert h.workspace_bytes("sum", 0, d) > whole.workspace_bytes("sum", 0, d)       # the cut is in effect: partial rows
+    if route == "0":
+        assert h.route("sum", d=d) == h.route("max", d=d) == "hag"
+    check_against_oracle(h, rowptr, col, d)
+
+
+def check_against_oracle(h, rowptr, col, d):
     n = rowptr.size - 1
     real, ties = synth.features_f32(n, d, 1), np.random.default_rng(2).integers(-2, 3, (n, d)).astype(np.float32)
     ints = synth.features_i32(n, d, 3)

@@ -35,8 +35,13 @@ def rel(a, ref):
 
 def graphs(B):
     rowptr, col = synth.holme_kim(5000, 10, 0.5, seed=91)
-    yield "power-law", rowptr, col, B.hag_search(rowptr, col, 1250).upload()
-    rowptr, col, gp = synth.er_batch(n_graphs=80, size=30, p=0.6, seed=92)     # runs the component-local pass
+    yield "power-law", rowptr, col, B.hag_search(rowptr, col, 1250).upload()       # runs over the plain lists
+    with pytest.MonkeyPatch.context() as mp:
+        mp.setenv("HAG_ROUTE", "0")
+        h = B.hag_search(rowptr, col, 1250).upload()
+    assert h.route("gcn", d=16) == h.route("max", d=16) == "hag"
+    yield "power-law, over the HAG", rowptr, col, h
+    rowptr, col, gp = synth.er_batch(n_graphs=80, size=30, p=0.6, seed=92)     # sums run as dense products
     yield "graph batch", rowptr, col, B.hag_search_batched(rowptr, col, gp, 0.25).upload()
 
 

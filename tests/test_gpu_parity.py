@@ -28,6 +28,16 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
+def over_the_hag(h, widths, ops=("sum", "max"), dtypes=(0, 1), component=False):
+    """Asserts that whole passes of this handle run over the HAG, not over the plain lists or as dense products."""
+    for d in widths:
+        for dt in dtypes:
+            for op in ops:
+                way = "component_hag" if component and op != "max" else "hag"
+                assert h.route(op, dt, d) == way and h.route(op, dt, d, backward=True) == ("scatter" if op == "max" else way), (d, dt, op)
+    return h
+
+
 def assert_close(gpu, ref, s, what):
     gpu = gpu.cpu().numpy().astype(np.float64)
     err = np.abs(gpu - ref)
@@ -84,9 +94,10 @@ def run_all_ops(B, h, rowptr, col, d, seed, ops=("sum", "mean", "max", "gcn"), d
     (777, 0.05, 64, False), (1000, 0.04, 128, True), (301, 0.2, 100, False), (150, 0.3, 260, True),
     (260, 0.2, 512, False), (129, 0.25, 1028, False),
 ])
-def test_random_graphs_all_ops(B, n, p, d, directed):
+def test_random_graphs_all_ops(B, n, p, d, directed, monkeypatch):
+    monkeypatch.setenv("HAG_ROUTE", "0")
     rowptr, col = synth.random_graph(n, p, seed=n + d, directed=directed)
-    h = B.hag_search(rowptr, col, n // 2)
+    h = over_the_hag(B.hag_search(rowptr, col, n // 2), (d,))
     assert h.stats()["a"] > 0
     run_all_ops(B, h, rowptr, col, d, seed=7 * n + d)
 
@@ -94,15 +105,16 @@ def test_random_graphs_all_ops(B, n, p, d, directed):
 def test_fused_and_unfused_stages(B, monkeypatch):
     # levels are fused into stages (one launch each) when that costs few extra row reads; both the
     # fused form and the one-launch-per-level form must match the oracle
+    monkeypatch.setenv("HAG_ROUTE", "0")
     rowptr, col = synth.sbm(n_blocks=3, block=60, p_in=0.5, p_out=0.02, seed=31)
     n = rowptr.size - 1
     fused = B.hag_search(rowptr, col, n)
     assert fused.stats()["levels"] >= 3 and fused.stats()["stages"] < fused.stats()["levels"]
-    run_all_ops(B, fused, rowptr, col, 32, seed=32)
+    run_all_ops(B, over_the_hag(fused, (32,)), rowptr, col, 32, seed=32)
     monkeypatch.setenv("HAG_STAGE_EXTRA_ROWS", "-1000000")
     unfused = B.hag_search(rowptr, col, n)
     assert unfused.stats()["stages"] == unfused.stats()["levels"]
-    run_all_ops(B, unfused, rowptr, col, 32, seed=32)
+    run_all_ops(B, over_the_hag(unfused, (32,)), rowptr, col, 32, seed=32)
 
 
 @pytest.mark.parametrize("offset64", [False, True])
@@ -110,6 +122,7 @@ def test_source_partitioned_schedule(B, monkeypatch, offset64):
     # rows cut by source id into per-XCD segments with partial rows folded afterwards: forced on
     # for a small graph (by default only large graphs use it), incl. hubs that are also split;
     # once more with the 64-bit row addressing that matrices of 4 GiB and more take
+    monkeypatch.setenv("HAG_ROUTE", "0")
     if offset64:
         monkeypatch.setenv("HAG_OFFSET64", "1")
     monkeypatch.setenv("HAG_PARTITION_MIN_ROWS", "0")
@@ -120,7 +133,7 @@ def test_source_partitioned_schedule(B, monkeypatch, offset64):
     rowptr, col = synth.holme_kim(1500, 9, 0.5, seed=41)
     n = rowptr.size - 1
     assert np.diff(rowptr).max() > 100
-    h = B.hag_search(rowptr, col, n // 4)
+    h = over_the_hag(B.hag_search(rowptr, col, n // 4), (16, 64))
     run_all_ops(B, h, rowptr, col, 64, seed=42)
     # the cut is really in effect: its partial rows make the workspace larger than without it
     monkeypatch.setenv("HAG_PARTITION", "0")
@@ -138,6 +151,8 @@ def test_component_local_pass_with_feature_columns_cut_in_parts(B, parts, monkey
     # the component pass with each component handled by 2 or 4 workgroups, one per part of the feature
     # columns (chosen by occupancy in real runs, forced here), must agree with the oracle and, bit for
     # bit, with the uncut pass
+    monkeypatch.setenv("HAG_ROUTE", "0")
+    monkeypatch.setenv("HAG_COMPONENT_DENSE", "0")
     sizes = np.random.default_rng(64).integers(1, 41, size=150)
     rowptr, col, gp = ragged_batch(sizes, 0.6, seed=65)
     whole = B.hag_search_batched(rowptr, col, gp, 0.25).upload()
@@ -145,6 +160,8 @@ def test_component_local_pass_with_feature_columns_cut_in_parts(B, parts, monkey
     cut = B.hag_search_batched(rowptr, col, gp, 0.25).upload()
     monkeypatch.delenv("HAG_COMPONENT_PARTS")
     assert cut.stats()["components"] >= 64
+    over_the_hag(cut, (32, 64, 128), component=True)
+    over_the_hag(whole, (32, 64, 128), component=True)
     for d in (32, 64, 128):
         run_all_ops(B, cut, rowptr, col, d, seed=66 + d, ops=("sum", "mean", "gcn"))
         x = dev(synth.features_f32(rowptr.size - 1, d, 67))
@@ -183,6 +200,7 @@ def test_component_local_pass_on_graph_batches(B, d, expand, monkeypatch):
     h = B.hag_search_batched(rowptr, col, gp, 0.25)
     assert h.stats()["a"] > 100 and h.stats()["levels"] >= 2
     assert h.stats()["components"] >= 64            # the component-local pass is the one that runs
+    over_the_hag(h, (d,), component=True)
     run_all_ops(B, h, rowptr, col, d, seed=63 + d)
     # streaming stores of the output rows (a knob read when a handle is built) change nothing but
     # the cache policy
@@ -196,6 +214,7 @@ def test_component_local_pass_on_graph_batches(B, d, expand, monkeypatch):
     monkeypatch.setenv("HAG_COMPONENT", "0")
     g = B.hag_search_batched(rowptr, col, gp, 0.25).upload()
     x = dev(synth.features_i32(rowptr.size - 1, d, 5))
+    over_the_hag(g, (d,))
     assert torch.equal(h.forward(x, "sum"), g.forward(x, "sum"))
     assert torch.equal(h.backward(x, "sum"), g.backward(x, "sum"))
     ya, aa = h.forward(x, "max")
@@ -212,9 +231,10 @@ def test_capacity_zero_is_the_gnn_graph(B):
     assert torch.equal(h.backward(x, "sum"), h.naive_backward(x, "sum"))
 
 
-def test_split_rows_hubs_and_isolated_nodes(B):
+def test_split_rows_hubs_and_isolated_nodes(B, monkeypatch):
     # a few hubs with thousands of neighbours (rows split across items and folded in a second
     # launch), many leaves, some isolated nodes; unsymmetric
+    monkeypatch.setenv("HAG_ROUTE", "0")
     n, d = 6000, 64
     rng = np.random.default_rng(11)
     rows, cols = [], []
@@ -233,14 +253,15 @@ def test_split_rows_hubs_and_isolated_nodes(B):
     rowptr = np.concatenate([[0], np.cumsum(np.bincount(r, minlength=n))]).astype(np.int64)
     col = c.astype(np.int32)
     assert np.diff(rowptr)[-50:].max() == 0 and np.diff(rowptr).max() == 5000
-    h = B.hag_search(rowptr, col, n // 4)
+    h = over_the_hag(B.hag_search(rowptr, col, n // 4), (16, d))
     run_all_ops(B, h, rowptr, col, d, seed=12)
     run_all_ops(B, h, rowptr, col, 16, seed=13, ops=("sum", "max"), dtypes=("f32",))
 
 
-def test_self_loops_and_dedup(B):
+def test_self_loops_and_dedup(B, monkeypatch):
     # a node may be its own neighbour (source and destination roles are distinct); duplicates are
     # dropped on request
+    monkeypatch.setenv("HAG_ROUTE", "0")
     n = 200
     rowptr, col = synth.random_graph(n, 0.08, seed=51, directed=True)
     rows = np.repeat(np.arange(n), np.diff(rowptr))
@@ -256,15 +277,20 @@ def test_self_loops_and_dedup(B):
     r2, c2 = keys // n, (keys % n).astype(np.int32)
     rp2 = np.concatenate([[0], np.cumsum(np.bincount(r2, minlength=n))]).astype(np.int64)
     assert h.stats()["e"] == c2.size and np.any(r2 == c2)
-    run_all_ops(B, h, rp2, c2, 32, seed=52)
+    run_all_ops(B, over_the_hag(h, (32,)), rp2, c2, 32, seed=52)
 
 
-@pytest.mark.parametrize("kind", ["power_law", "graph_batch"])
-def test_forward_backward_inside_a_hip_graph(B, kind):
+@pytest.mark.parametrize("kind", ["power_law", "graph_batch", "power_law_hag", "graph_batch_hag"])
+def test_forward_backward_inside_a_hip_graph(B, kind, monkeypatch):
     # the device entry points allocate nothing, never synchronise and clear memory with kernels, so a
     # whole step can be captured once and replayed; every replay must reproduce the eager result
-    # (graph_batch: sum / mean run as the one-launch component-local pass, max on the generic kernels)
-    if kind == "power_law":
+    # (graph_batch: sum / mean run in one launch, as dense products or, "_hag", out of LDS over the HAG; max on the generic kernels)
+    if kind.endswith("_hag"):
+        monkeypatch.setenv("HAG_ROUTE", "0")
+        monkeypatch.setenv("HAG_COMPONENT_DENSE", "0")
+    if kind == "graph_batch":
+        monkeypatch.setenv("HAG_COMPONENT_DENSE", "2")
+    if kind.startswith("power_law"):
         rowptr, col = synth.holme_kim(3000, 8, 0.5, seed=71)
         n = rowptr.size - 1
         h = B.hag_search(rowptr, col, n // 4).upload()
@@ -276,6 +302,10 @@ def test_forward_backward_inside_a_hip_graph(B, kind):
         assert h.stats()["components"] >= 64
     d = 64
     assert h.stats()["levels"] >= 2
+    if kind.endswith("_hag"):
+        over_the_hag(h, (d,), component=kind == "graph_batch_hag")
+    else:
+        assert h.route("sum", d=d) == ("lists" if kind == "power_law" else "dense")
     x = dev(synth.features_f32(n, d, 72))
     gy = dev(synth.features_f32(n, d, 73))
     y, gx = torch.empty_like(x), torch.empty_like(x)
@@ -312,11 +342,12 @@ def test_forward_backward_inside_a_hip_graph(B, kind):
         assert torch.allclose(gm, want_gm, rtol=1e-5, atol=1e-5)   # atomics: order not fixed
 
 
-def test_max_ties_bit_exact(B):
+def test_max_ties_bit_exact(B, monkeypatch):
     # few distinct values -> many exact ties; argmax must be the smallest original id
+    monkeypatch.setenv("HAG_ROUTE", "0")
     n, d = 600, 32
     rowptr, col = synth.random_graph(n, 0.1, seed=21)
-    h = B.hag_search(rowptr, col, n // 2).upload()
+    h = over_the_hag(B.hag_search(rowptr, col, n // 2), (d,)).upload()
     x = np.random.default_rng(22).integers(0, 3, size=(n, d)).astype(np.float32)
     y_ref, _, am_ref = oracle.naive_forward(rowptr, col, x, "max")
     for fwd in (h.forward, h.naive_forward):
@@ -334,11 +365,12 @@ def test_max_ties_bit_exact(B):
 def test_max_ties_through_aggregation_rows(B, monkeypatch, knobs):
     # fp32 max looks up the winner stored beside an aggregation row only when a tie needs it: ties
     # between original rows and aggregation rows, and between aggregation rows, in every schedule
+    monkeypatch.setenv("HAG_ROUTE", "0")
     for k, v in knobs.items():
         monkeypatch.setenv(k, v)
     rowptr, col = synth.holme_kim(2500, 12, 0.6, seed=23)
     n = rowptr.size - 1
-    h = B.hag_search(rowptr, col, n // 2).upload()
+    h = over_the_hag(B.hag_search(rowptr, col, n // 2), (8, 64, 132)).upload()
     assert h.stats()["levels"] >= 2
     rng = np.random.default_rng(24)
     for d, levels_of_value in ((8, 2), (64, 4), (132, 50)):
@@ -381,14 +413,15 @@ def test_device_argument_errors(B):
         h.forward(x8, "sum", y=x8)               # aliasing
 
 
-def test_config1_sbm_sum_f32_and_i32(B):
+def test_config1_sbm_sum_f32_and_i32(B, monkeypatch):
+    monkeypatch.setenv("HAG_ROUTE", "0")
     rowptr, col = synth.sbm()
     n = rowptr.size - 1
     h = B.hag_search(rowptr, col, n // 4)
     ref = oracle.search(rowptr, col, n // 4)     # canonical search parity at full config-1 size
     l, r, red = h.get_merges()
     assert np.array_equal(l, ref.left) and np.array_equal(r, ref.right) and np.array_equal(red, ref.red)
-    run_all_ops(B, h, rowptr, col, 64, seed=synth.SEED_BASE + 1001, ops=("sum",))
+    run_all_ops(B, over_the_hag(h, (64,)), rowptr, col, 64, seed=synth.SEED_BASE + 1001, ops=("sum",))
 
 
 # ------------------------------------------------------------------------------------------------

@@ -1,7 +1,7 @@
 """Seeded random sweep of the device path: random graphs of three families (G(n,p) directed or not,
 power-law cluster graphs, ragged batches of small graphs), random feature widths, random schedule
 knobs (rows cut by source id, split rows, sub-group / workgroup threshold, unfused levels), every op
-and dtype, HAG path and naive-CSR baseline, forward and backward, against the CPU oracle.
+and dtype, HAG path (every second graph; the others the form the handle chooses) and naive-CSR baseline, forward and backward, against the CPU oracle.
 
 Bars as everywhere: int32 and max (values, argmax) bit-exact, fp32 sums within 1e-5 * sum|terms|.
 Half of the max cases use quantised features, so that ties between original rows and aggregation
@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 TOL = 1e-5
 KNOBS = ("HAG_PARTITION_MIN_ROWS", "HAG_PART_MIN", "HAG_PART_SHARE_PCT", "HAG_PART_MEAN_MIN", "HAG_PART_CLASS_SHIFT",
-         "HAG_PART_SHIFT", "HAG_BLOCK_MAX", "HAG_SUB_MAX", "HAG_STAGE_EXTRA_ROWS")
+         "HAG_PART_SHIFT", "HAG_BLOCK_MAX", "HAG_SUB_MAX", "HAG_STAGE_EXTRA_ROWS", "HAG_ROUTE", "HAG_COMPONENT_DENSE")
 
 
 @pytest.fixture(scope="module")
@@ -83,6 +83,9 @@ def test_random_graphs_widths_and_schedules(B, monkeypatch, chunk):
             env["HAG_SUB_MAX"] = str(rng.choice([4, 16, 100]))
         if rng.random() < 0.3:
             env["HAG_STAGE_EXTRA_ROWS"] = "-1000000"
+        # every second graph by the handle's own choice of form, the others over the HAG (batches out of LDS instead of as dense products)
+        if it % 2 == 0:
+            env.update(HAG_ROUTE="0", HAG_COMPONENT_DENSE="0")
         for k, v in env.items():
             monkeypatch.setenv(k, v)
         d = int(rng.choice([4, 8, 12, 16, 36, 64, 100, 128, 260]))
@@ -112,4 +115,6 @@ def test_random_graphs_widths_and_schedules(B, monkeypatch, chunk):
             h = B.hag_search_batched(rowptr, col, graph_ptr, float(rng.choice([0.25, 0.5])))
         st = h.stats()
         tag = f"chunk {chunk} case {it} family {kind} n={st['n']} e={st['e']} a={st['a']} levels={st['levels']} d={d} {env}"
+        if it % 2 == 0:
+            assert {h.route(op, dt, d) for op, dt in (("sum", 0), ("max", 0), ("sum", 1))} <= {"hag", "component_hag"}
         check_all(h, rowptr, col, d, int(rng.integers(1 << 30)), tag)

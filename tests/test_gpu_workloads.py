@@ -89,19 +89,21 @@ def check_columns(h, rowptr, col, d, op, cols, seed, check_naive=True):
         del y, gx
 
 
-def test_config2_holme_kim_sum_and_mean(B):
+def test_config2_holme_kim_sum_and_mean(B, monkeypatch):
+    monkeypatch.setenv("HAG_ROUTE", "0")                     # the form chosen by itself is the plain lists: the "naive" half
     rowptr, col = synth.holme_kim()
     n = rowptr.size - 1
     h = B.hag_search(rowptr, col, n // 4).upload()
     st = h.stats()
     assert st["a"] == n // 4 and st["aggr_hag"] < st["aggr_naive"]
     assert oracle.cover_check(rowptr, col, oracle_view(h)) == 0          # Theorem 2
+    assert h.route("sum", d=128) == h.route("sum", d=128, backward=True) == "hag"
     cols = np.arange(128)
     for op in ("sum", "mean", "gcn"):
         check_columns(h, rowptr, col, 128, op, cols, synth.SEED_BASE + 2 + 1000)
 
 
-def test_config4_graph_batch_sum(B):
+def test_config4_graph_batch_sum(B, monkeypatch):
     rowptr, col, gp = synth.er_batch()
     n = rowptr.size - 1
     h = B.hag_search_batched(rowptr, col, gp, 0.25).upload()
@@ -120,6 +122,14 @@ def test_config4_graph_batch_sum(B):
     assert np.array_equal(orig_of[f["hcol"]], rows // 74)
     check_columns(h, rowptr, col, 64, "sum", np.arange(64), synth.SEED_BASE + 4 + 1000)
     check_columns(h, rowptr, col, 64, "gcn", np.arange(64), synth.SEED_BASE + 4 + 1000)
+    assert h.route("sum", d=64) == "dense"
+    # and out of LDS, over the HAG and over the plain lists
+    monkeypatch.setenv("HAG_ROUTE", "0")
+    monkeypatch.setenv("HAG_COMPONENT_DENSE", "0")
+    left, right, _ = h.get_merges()
+    lists = B.hag_from_merges(rowptr, col, left, right).upload()
+    assert lists.route("sum", d=64) == lists.route("sum", d=64, backward=True) == "component_hag"
+    check_columns(lists, rowptr, col, 64, "sum", np.arange(64), synth.SEED_BASE + 4 + 1000)
 
 
 # ------------------------------------------------------------------------------------------------
@@ -158,10 +168,13 @@ def big_hags(request, B, big_graph):
         "merge-list cache for the 114M-edge graph is missing or short: run " \
         "`python -m paper_1906_03707_amd.workloads --make-cache 3` (about an hour of CPU time)"
     hags = {}
-    for cap in (0, n // 8, n // 4, n // 2):
-        progress(request, f"replaying {cap} merges (hag_from_merges) ...")
-        hags[cap] = workloads.build_hag(3, rowptr, col, capacity=cap)
-        assert hags[cap].stats()["a"] == cap
+    with pytest.MonkeyPatch.context() as mp:
+        mp.setenv("HAG_ROUTE", "0")                          # every pass over the HAG, max too
+        for cap in (0, n // 8, n // 4, n // 2):
+            progress(request, f"replaying {cap} merges (hag_from_merges) ...")
+            hags[cap] = workloads.build_hag(3, rowptr, col, capacity=cap)
+            assert hags[cap].stats()["a"] == cap
+            assert {hags[cap].route(op, 0, d) for op in ("sum", "max") for d in (16, 128, 512)} == {"hag"}
     progress(request, "HAGs built")
     return hags
 

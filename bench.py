@@ -25,8 +25,9 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 # Limits derived from the chip's unit counts and clock (8 XCDs, 256 compute units, 2.4 GHz):
 #   L2 -> compute units: 16 channels x 128 B/clk per XCD; the vector L1s take 64 B/clk per
-#   compute unit, which is the same 39.3 TB/s.
+#   compute unit, which is the same 39.3 TB/s;  LDS: 64 banks x 4 B per clock and compute unit.
 L2_PEAK_GBS = 8 * 16 * 128 * 2.4
+LDS_PEAK_GBS = 256 * 64 * 4 * 2.4
 
 # L2 fills + write-backs per launch of the dominant kernel, from separate rocprofv3 --pmc runs of this
 # file (FETCH_SIZE, WRITE_SIZE, scaled by what the same counters read for --copy-calibration's
@@ -69,18 +70,21 @@ def time_steps(torch, fn, steps, warmup):
     return statistics.median(a.elapsed_time(b) for a, b in ev), wall
 
 
-def time_interleaved(torch, fn_a, fn_b, steps, warmup, blocks=4):
-    """Per-step event times of two paths measured alternately: after `warmup` untimed steps of each, `steps`
+def time_interleaved(torch, *fns, steps, warmup, blocks=4, before=None):
+    """Per-step event times of several paths measured alternately: after `warmup` untimed steps of each, `steps`
     timed steps of each in `blocks` alternating runs (a, b, a, b, ...), so that a slow drift of the machine (clocks,
-    what else shares it) lands on both.  Returns ((median_a, wall_mean_a), (median_b, wall_mean_b)) in ms."""
-    for _ in range(warmup):
-        fn_a()
-    for _ in range(warmup):
-        fn_b()
+    what else shares it) lands on all.  before[i], if given, runs before path i is switched to.
+    Returns ((median_a, wall_mean_a), (median_b, wall_mean_b), ...) in ms."""
+    before = before or [lambda: None] * len(fns)
+    for switch, fn in zip(before, fns):
+        switch()
+        for _ in range(warmup):
+            fn()
     per = [steps // blocks + (1 if i < steps % blocks else 0) for i in range(blocks)]
-    samples, wall = ([], []), [0.0, 0.0]
+    samples, wall = [[] for _ in fns], [0.0] * len(fns)
     for n_block in per:
-        for which, fn in ((0, fn_a), (1, fn_b)):
+        for which, fn in enumerate(fns):
+            before[which]()
             fn()                                   # one untimed step after the switch of paths
             ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(n_block)]
             torch.cuda.synchronize()
@@ -92,7 +96,21 @@ def time_interleaved(torch, fn_a, fn_b, steps, warmup, blocks=4):
             torch.cuda.synchronize()
             wall[which] += time.perf_counter() - t0
             samples[which].extend(a.elapsed_time(b) for a, b in ev)
-    return tuple((statistics.median(samples[w]), wall[w] / steps * 1e3) for w in (0, 1))
+    return tuple((statistics.median(s), w / steps * 1e3) for s, w in zip(samples, wall))
+
+
+def forms(h, op, d):
+    """The form that forward and backward of a handle run in (binding.ROUTES), for the figures' labels."""
+    return {"forward": h.route(op, d=d), "backward": h.route(op, d=d, backward=True)}
+
+
+def three_legs(torch, binding, h, step, step_naive, steps, warmup, blocks=4):
+    """A step as a user calls it (the form that is expected to be fastest), the same over the HAG and the baseline over the plain lists, the last two
+    in list form (no dense products), timed alternately."""
+    pick = lambda v: lambda: h.set_option(binding.HAG_OPT_LIST_FORMS, v)   # noqa: E731
+    legs = time_interleaved(torch, step, step, step_naive, steps=steps, warmup=warmup, blocks=blocks, before=[pick(0), pick(1), pick(1)])
+    h.set_option(binding.HAG_OPT_LIST_FORMS, 0)
+    return legs
 
 
 def time_kernel(torch, pre, fn, post, steps, warmup):
@@ -267,7 +285,7 @@ def sage_pool_epoch_ms(torch, h, x, hidden, classes, steps, warmup, naive):
     return time_steps(torch, epoch, steps, warmup)[0]
 
 
-def sweep_config5(torch, synth, workloads, steps, warmup):
+def sweep_config5(torch, binding, synth, workloads, steps, warmup):
     """benchmark config 5: the 232,965-node graph over capacity {0, |V|/8, |V|/4, |V|/2} x feature
     dim {16, 128, 512} x {max, sum}, forward + backward.  One JSON line per point on stdout."""
     rowptr, col, _ = synth.graph_for_config(5)
@@ -276,7 +294,7 @@ def sweep_config5(torch, synth, workloads, steps, warmup):
     hags = {}
     for cap in (0, n // 8, n // 4, n // 2):
         hags[cap] = workloads.build_hag(5, rowptr, col, None, cap, log=lambda m: log("[bench] " + m)).upload()
-    log("[bench] capacity      d  op    hag ms   naive ms  speedup  aggregations fewer")
+    log("[bench] capacity      d  op   call ms    hag ms   naive ms  hag speedup  call speedup  aggregations fewer")
     for d in (16, 128, 512):
         x = torch.from_numpy(synth.features_f32(n, d, synth.SEED_BASE + 5 + 1000 + d)).cuda()
         gy = torch.from_numpy(synth.features_f32(n, d, synth.SEED_BASE + 5 + 2000 + d)).cuda()
@@ -287,7 +305,7 @@ def sweep_config5(torch, synth, workloads, steps, warmup):
                 st = h.stats()
                 a = am if op == "max" else None
 
-                def step_hag():
+                def step():
                     h.forward(x, op, y=y, argmax=a)
                     h.backward(gy, op, argmax=a, gx=gx)
 
@@ -295,12 +313,13 @@ def sweep_config5(torch, synth, workloads, steps, warmup):
                     h.naive_forward(x, op, y=y, argmax=a)
                     h.naive_backward(gy, op, argmax=a, gx=gx)
 
-                (ms_h, _), (ms_n, _) = time_interleaved(torch, step_hag, step_naive, steps, warmup, blocks=2)
+                (ms_c, _), (ms_h, _), (ms_n, _) = three_legs(torch, binding, h, step, step_naive, steps, warmup, blocks=2)
                 red = st["aggr_naive"] / max(st["aggr_hag"], 1)
-                log(f"[bench] {cap:8d} {d:6d}  {op:4s} {ms_h:8.3f}  {ms_n:8.3f}  {ms_n / ms_h:6.3f}x  {red:6.3f}x")
-                print(json.dumps({"workload": "config5:dcsbm232965_sweep", "capacity": cap, "feature_dim": d, "op": op,
-                                  "ms_per_step": ms_h, "naive_ms_per_step": ms_n, "speedup_vs_naive": ms_n / ms_h,
-                                  "value": 2.0 * st["e"] * d / (ms_h * 1e-3), "unit": "feature-elems/s",
+                log(f"[bench] {cap:8d} {d:6d}  {op:4s} {ms_c:8.3f} {ms_h:8.3f}  {ms_n:8.3f}  {ms_n / ms_h:6.3f}x  {ms_n / ms_c:6.3f}x  {red:6.3f}x")
+                print(json.dumps({"workload": "config5:dcsbm232965_sweep", "capacity": cap, "feature_dim": d, "op": op, "form": forms(h, op, d),
+                                  "ms_per_step": ms_c, "hag_ms_per_step": ms_h, "naive_ms_per_step": ms_n, "hag_speedup_vs_naive": ms_n / ms_h,
+                                  "speedup_vs_naive": ms_n / ms_c,
+                                  "value": 2.0 * st["e"] * d / (ms_c * 1e-3), "unit": "feature-elems/s",
                                   "aggregation_reduction": red, "levels": st["levels"], "stages": st["stages"]}),
                       flush=True)
         del x, gy, y, gx, am
@@ -351,7 +370,7 @@ def seq_lstm_bench(torch, binding, synth, cfg, first_k, d, hidden, steps, warmup
             ms, _ = time_steps(torch, fn, steps, warmup)
             ms_base = ms if name == "lists" else float("nan")
         else:
-            (ms, _), (ms_base, _) = time_interleaved(torch, fn, base, steps, warmup)
+            (ms, _), (ms_base, _) = time_interleaved(torch, fn, base, steps=steps, warmup=warmup)
         tf = p.cells * flops_per_cell / (ms * 1e-3) / 1e12
         res["plans"][name] = {"cells": p.cells, "aggregation_nodes": p.merges, "launches": p.launches, "levels": int(p.plan()[4].size - 1), "longest_chain": p.ranks, "ms_per_pass": ms,
                               "lists_ms_per_pass": ms_base, "speedup_vs_lists": ms_base / ms,
@@ -399,7 +418,7 @@ def seq_lstm_bench(torch, binding, synth, cfg, first_k, d, hidden, steps, warmup
             ms, _ = time_steps(torch, fn, steps, warmup)
             ms_base = ms if name == "lists" else float("nan")
         else:
-            (ms, _), (ms_base, _) = time_interleaved(torch, fn, infer["lists"], steps, warmup)
+            (ms, _), (ms_base, _) = time_interleaved(torch, fn, infer["lists"], steps=steps, warmup=warmup)
         res["plans"][name]["sage_lstm2_inference_ms"] = ms
         res["plans"][name]["sage_lstm2_inference_speedup_vs_lists"] = ms_base / ms
         log(f"[bench] 2-layer GraphSAGE-LSTM inference, {name}: {ms:.3f} ms ({ms_base / ms:.2f}x the plain lists' speed)")
@@ -423,7 +442,7 @@ def seq_lstm_bench(torch, binding, synth, cfg, first_k, d, hidden, steps, warmup
 
 
 def short_workload(torch, binding, synth, workloads, cfg, steps, warmup):
-    """Forward + backward of one of the smaller configs, HAG against the naive-CSR kernels: the figures
+    """Forward + backward of one of the smaller configs, as called, over the HAG and with the naive-CSR kernels: the figures
     that ride along with the main workload's line."""
     rowptr, col, h, d = build_workload(cfg, None, workloads, synth)
     st = h.stats()
@@ -434,7 +453,7 @@ def short_workload(torch, binding, synth, workloads, cfg, steps, warmup):
     gy = torch.from_numpy(synth.features_f32(n, d, seed + 2000)).cuda()
     y, gx = torch.empty_like(x), torch.empty_like(x)
 
-    def step_hag():
+    def step():
         h.forward(x, "sum", y=y)
         h.backward(gy, "sum", gx=gx)
 
@@ -442,14 +461,15 @@ def short_workload(torch, binding, synth, workloads, cfg, steps, warmup):
         h.naive_forward(x, "sum", y=y)
         h.naive_backward(gy, "sum", gx=gx)
 
-    (ms_h, _), (ms_n, _) = time_interleaved(torch, step_hag, step_naive, steps, warmup)
+    (ms_c, _), (ms_h, _), (ms_n, _) = three_legs(torch, binding, h, step, step_naive, steps, warmup)
     red = st["aggr_naive"] / max(st["aggr_hag"], 1)
-    log(f"[bench] config {cfg} (d={d}, sum): hag {ms_h:.4f} ms  naive {ms_n:.4f} ms  speedup {ms_n / ms_h:.3f}x  "
-        f"(aggregations {red:.3f}x fewer)")
-    return {"feature_dim": d, "nodes": n, "edges": st["e"], "capacity": st["a"], "ms_per_step": ms_h,
-            "naive_ms_per_step": ms_n, "speedup_vs_naive": ms_n / ms_h, "aggregation_reduction": red,
+    form = forms(h, "sum", d)
+    log(f"[bench] config {cfg} (d={d}, sum): as called ({form['forward']} / {form['backward']}) {ms_c:.4f} ms  over the HAG {ms_h:.4f} ms  "
+        f"naive {ms_n:.4f} ms  speedup {ms_n / ms_c:.3f}x, of the HAG {ms_n / ms_h:.3f}x  (aggregations {red:.3f}x fewer)")
+    return {"feature_dim": d, "nodes": n, "edges": st["e"], "capacity": st["a"], "form": form, "ms_per_step": ms_c, "hag_ms_per_step": ms_h,
+            "naive_ms_per_step": ms_n, "speedup_vs_naive": ms_n / ms_c, "hag_speedup_vs_naive": ms_n / ms_h, "aggregation_reduction": red,
             "transfer_reduction": st["xfer_naive"] / max(st["xfer_hag"], 1),
-            "feature_elems_per_s": 2.0 * st["e"] * d / (ms_h * 1e-3), "levels": st["levels"], "stages": st["stages"]}
+            "feature_elems_per_s": 2.0 * st["e"] * d / (ms_c * 1e-3), "levels": st["levels"], "stages": st["stages"]}
 
 
 def main():
@@ -514,7 +534,7 @@ def main():
                           "config": res}), flush=True)
         return
     if cfg == 5:
-        sweep_config5(torch, synth, workloads, max(min(args.steps, 10), 3), 2)
+        sweep_config5(torch, binding, synth, workloads, max(min(args.steps, 10), 3), 2)
         return
     rowptr, col, h, d = build_workload(cfg, None if args.capacity < 0 else args.capacity, workloads, synth,
                                        device_search=args.device_search)
@@ -541,12 +561,17 @@ def main():
         del a, b
 
     def step_hag():
+        # as a user calls it: in the form that is expected to be fastest (`form`), for this workload by default the pass over the HAG
         h.forward(x, op, y=y, argmax=am)
         h.backward(gy, op, argmax=am, gx=gx)
 
     def step_naive():
         h.naive_forward(x, op, y=y, argmax=am)
         h.naive_backward(gy, op, argmax=am, gx=gx)
+
+    form = forms(h, op, d)
+    over_hag = form["forward"] in ("hag", "one_launch", "component_hag") and form["backward"] in ("hag", "one_launch", "component_hag", "scatter")
+    naive_form = {"forward": h.route(op, d=d, naive=True), "backward": h.route(op, d=d, backward=True, naive=True)}
 
     def time_cold(fn, reps=5):
         """One step right after a write sweep over 1 GiB (larger than L2 + the 256 MB Infinity Cache)."""
@@ -562,9 +587,14 @@ def main():
 
     # the timed region: exactly `steps` steps after `warmup` untimed ones, in four runs that alternate with the
     # baseline's (the machine's clocks drift by a few per cent over seconds: both paths get the same share of it)
-    (ms_hag, ms_hag_wall), (ms_naive, ms_naive_wall) = time_interleaved(torch, step_hag, step_naive, args.steps, args.warmup)
+    (ms_hag, ms_hag_wall), (ms_naive, ms_naive_wall) = time_interleaved(torch, step_hag, step_naive, steps=args.steps, warmup=args.warmup)
+    list_legs = None
+    if not (over_hag and naive_form["forward"] in ("lists", "component_lists")):
+        # the call does not compare the HAG with the plain lists: time those two apart
+        _, (ms_list_hag, _), (ms_list_naive, _) = three_legs(torch, binding, h, step_hag, step_naive, args.steps, args.warmup)
+        list_legs = {"hag_ms_per_step": ms_list_hag, "naive_ms_per_step": ms_list_naive, "hag_speedup_vs_naive": ms_list_naive / ms_list_hag}
     (ms_fwd, _), (ms_nfwd, _) = time_interleaved(torch, lambda: h.forward(x, op, y=y, argmax=am),
-                                                 lambda: h.naive_forward(x, op, y=y, argmax=am), args.steps, args.warmup)
+                                                 lambda: h.naive_forward(x, op, y=y, argmax=am), steps=args.steps, warmup=args.warmup)
 
     def capture(fn):
         """The same step captured once into a HIP graph (replayed without per-launch host work)."""
@@ -579,7 +609,7 @@ def main():
         return g
 
     g_hag, g_naive = capture(step_hag), capture(step_naive)
-    (ms_hag_graph, _), (ms_naive_graph, _) = time_interleaved(torch, g_hag.replay, g_naive.replay, args.steps, args.warmup)
+    (ms_hag_graph, _), (ms_naive_graph, _) = time_interleaved(torch, g_hag.replay, g_naive.replay, steps=args.steps, warmup=args.warmup)
     del g_hag, g_naive
     ms_hag_cold = time_cold(step_hag)
     ms_naive_cold = time_cold(step_naive)
@@ -589,12 +619,22 @@ def main():
     P = binding
     row = 4 * d
     lpr = min(64, max(4, 1 << (max(d // 4, 1) - 1).bit_length()))
-    component_pass = st.get("components", 0) > 0 and op != "max" and os.environ.get("HAG_COMPONENT", "1") != "0"
-    if component_pass:
+    # a row read per entry of the lists that are walked; the dense products walk none: rows in, rows out and the adjacency bits
+    def algorithmic(which, back):
+        if which[back] == "dense":
+            return row * 2 * n + n * 4 * -(-n // max(st["components"], 1) // 32)
+        return h.algorithmic_bytes((back == "backward") + (2 if which[back] in ("lists", "component_lists") else 0), op, d)
+
+    way = form["forward"]
+    whole = way != "hag"                                      # one launch (and, over plain lists cut by source, a fold): timed whole
+    if whole:
         ms_gather = time_kernel(torch, lambda: None, lambda: h.forward(x, op, y=y, argmax=am),
                                 lambda: h.backward(gy, op, argmax=am, gx=gx), args.steps, args.warmup)
-        gather_bytes = h.algorithmic_bytes(0, op, d)
-        kernel_name = f"dense_kernel<{1 if d <= 16 else 2 if d <= 32 else 4}, 0>"   # the whole forward pass
+        gather_bytes = algorithmic(form, "forward")
+        role = 3 if way == "lists" else 0
+        kernel_name = {"dense": f"dense_kernel<{1 if d <= 16 else 2 if d <= 32 else 4}, 0>", "one_launch": f"fused_kernel<float, {1 if op == 'max' else 0}, {lpr}, 0>",
+                       "component_hag": f"component_kernel<float, {lpr}, 256, 0>", "component_lists": f"component_kernel<float, {lpr}, 256, 2>"}.get(
+                           way, f"gather_kernel<float, {1 if op == 'max' else 0}, {lpr}, {role}>")
     else:
         ms_gather = time_kernel(
             torch,
@@ -617,10 +657,15 @@ def main():
     def measured(key):
         return None if ceil is None else ceil[key]
 
-    if component_pass:
+    if way == "dense":
         # dense products: every feature row from HBM once, every result to it, the adjacency bits beside them
         bound, peak, ceiling = "hbm", HBM_PEAK_GBS, measured("copy_1GiB_read_plus_write_GBps")
-        achieved_bound = (row * 2 * n + n * 4 * -(-n // max(st["components"], 1) // 32)) / (ms_gather * 1e-3) / 1e9
+        achieved_bound = gather_bytes / (ms_gather * 1e-3) / 1e9
+    elif way.startswith("component"):
+        # every list entry is one LDS row read; staging adds one LDS write per row of the matrix
+        bound, peak, ceiling = "lds", LDS_PEAK_GBS, measured("lds_rows_GBps")
+        rows = (st["e_hag"] + n + st["a"]) if way == "component_hag" else e + n
+        achieved_bound = row * rows / (ms_gather * 1e-3) / 1e9
     elif achieved > HBM_PEAK_GBS * 0.6:
         bound, peak, ceiling = "l2", L2_PEAK_GBS, measured("l2_resident_rows_GBps")
         achieved_bound = achieved
@@ -639,8 +684,8 @@ def main():
         roofline["l2_fill"] = {"bytes": prof["fetch"], "achieved": prof["fetch"] / (ms_gather * 1e-3) / 1e9, "unit": "GB/s",
                                "measured_ceiling": measured("infinity_cache_rows_GBps")}
 
-    alg_hag = h.algorithmic_bytes(0, op, d) + h.algorithmic_bytes(1, op, d)
-    alg_naive = h.algorithmic_bytes(2, op, d) + h.algorithmic_bytes(3, op, d)
+    alg_hag = sum(algorithmic(form, k) for k in form)
+    alg_naive = sum(algorithmic(naive_form, k) for k in naive_form)
     # what must move at least: every input row in, every output row out, aggregation rows out and in,
     # indices once (forward + backward)
     b_min = 2 * (row * (2 * n + 2 * st["a"]) + 4 * st["e_hag"] + 16 * (n + st["a"]))
@@ -659,7 +704,7 @@ def main():
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": workload, "nodes": n, "edges": e, "feature_dim": d, "op": op,
-                   "capacity": st["a"], "levels": st["levels"], "hag_edges": st["e_hag"]},
+                   "capacity": st["a"], "levels": st["levels"], "hag_edges": st["e_hag"], "form": form},
         "roofline": roofline,
         "timing": "median of per-step event pairs on the launch stream over the timed steps, taken in four runs that "
                   "alternate with the naive baseline's",
@@ -668,7 +713,8 @@ def main():
         "effective_frac_of_hbm_peak": alg_hag / (ms_hag * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "compulsory_bytes_fwd_bwd": b_min,
         "profiled_bytes_per_aggregated_element": None if prof is None else (prof["fetch"] + prof["write"]) / (e * d),
-        "naive_csr": {"ms_per_step": ms_naive, "ms_per_step_wall_mean": ms_naive_wall,
+        "over_the_hag_and_over_the_lists": list_legs,
+        "naive_csr": {"ms_per_step": ms_naive, "form": naive_form, "ms_per_step_wall_mean": ms_naive_wall,
                       "feature_elems_per_s": 2.0 * e * d / (ms_naive * 1e-3),
                       "effective_GBps": alg_naive / (ms_naive * 1e-3) / 1e9},
         "speedup_vs_naive": ms_naive / ms_hag,
@@ -681,16 +727,18 @@ def main():
         "one_launch_schedule": bool(args.one_launch),
     }
     log(f"[bench] {workload} D={d} op={op}: N={n} E={e} A={st['a']} levels={st['levels']} E^={st['e_hag']}")
-    log(f"[bench] fwd+bwd  hag {ms_hag:.4f} ms  naive {ms_naive:.4f} ms  speedup {ms_naive / ms_hag:.3f}x "
+    log(f"[bench] form: {form['forward']} / {form['backward']}, baseline {naive_form['forward']} / {naive_form['backward']}"
+        + ("" if list_legs is None else f"; over the HAG {list_legs['hag_ms_per_step']:.4f} ms, over the lists {list_legs['naive_ms_per_step']:.4f} ms"))
+    log(f"[bench] fwd+bwd  as called {ms_hag:.4f} ms  naive {ms_naive:.4f} ms  speedup {ms_naive / ms_hag:.3f}x "
         f"(aggregations {out['aggregation_reduction']:.3f}x, transfers {out['transfer_reduction']:.3f}x fewer)")
-    log(f"[bench] fwd only hag {ms_fwd:.4f} ms  naive {ms_nfwd:.4f} ms")
-    log(f"[bench] replayed from a HIP graph: hag {ms_hag_graph:.4f} ms  naive {ms_naive_graph:.4f} ms")
-    log(f"[bench] cold caches (after a 1 GiB write sweep): hag {ms_hag_cold:.4f} ms  naive {ms_naive_cold:.4f} ms")
+    log(f"[bench] fwd only  as called {ms_fwd:.4f} ms  naive {ms_nfwd:.4f} ms")
+    log(f"[bench] replayed from a HIP graph: as called {ms_hag_graph:.4f} ms  naive {ms_naive_graph:.4f} ms")
+    log(f"[bench] cold caches (after a 1 GiB write sweep): as called {ms_hag_cold:.4f} ms  naive {ms_naive_cold:.4f} ms")
     if ceil is not None:
         log(f"[bench] ceilings (rows of {ceil['row_width']} floats, GB/s): L2-resident {ceil['l2_resident_rows_GBps']:.0f}  "
             f"memory-side cache {ceil['infinity_cache_rows_GBps']:.0f}  HBM {ceil['hbm_rows_GBps']:.0f}  LDS {ceil['lds_rows_GBps']:.0f}  "
             f"1 GiB copy {ceil['copy_1GiB_read_plus_write_GBps']:.0f}")
-    log(f"[bench] effective (algorithmic) GB/s fwd+bwd: hag {out['effective_GBps_fwd_bwd']:.0f}  "
+    log(f"[bench] effective (algorithmic) GB/s fwd+bwd: as called {out['effective_GBps_fwd_bwd']:.0f}  "
         f"naive {out['naive_csr']['effective_GBps']:.0f}  (HBM peak {HBM_PEAK_GBS:.0f})")
     log(f"[bench] dominant kernel {kernel_name}: {ms_gather * 1e3:.1f} us, {gather_bytes / 1e6:.1f} MB -> {achieved_bound:.0f} GB/s "
         f"= {100 * achieved_bound / peak:.1f}% of the {bound} limit ({peak:.0f})"

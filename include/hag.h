@@ -295,6 +295,7 @@ int hag_backward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d,
 enum { HAG_ROUTE_HAG = 0, HAG_ROUTE_LISTS = 1, HAG_ROUTE_COMPONENT_HAG = 2, HAG_ROUTE_COMPONENT_LISTS = 3, HAG_ROUTE_DENSE = 4,
        HAG_ROUTE_ONE_LAUNCH = 5, HAG_ROUTE_SCATTER = 6 };
 int hag_route(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d, int32_t backward);
+int hag_naive_route(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d, int32_t backward);   /* the same for hag_naive_forward / _backward */
 
 /* The one-launch schedule (optional, off by default).  hag_forward and hag_backward can run
  * Algorithm 2's loop over V_A and its final loop (resp. their transposes) as ONE kernel launch:
@@ -317,13 +318,15 @@ int hag_route(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d, int32_t
  *                                 after the spin limit and hag_check must report HAG_ETIMEOUT;
  *   HAG_OPT_PARTITION_SHIFT       0..7: in a launch whose long rows are cut into 8 classes of source ids, workgroup b takes
  *                                 the sources of class (b + shift) mod 8 (any value gives the same results);
+ *   HAG_OPT_LIST_FORMS            non-zero: hag_forward / hag_backward run over the HAG and hag_naive_forward / hag_naive_backward
+ *                                 over the input graph's lists, neither over the other's nor as dense products: to compare the two;
  *   HAG_OPT_DETERMINISTIC_MAX_BACKWARD  non-zero: the backward pass of max adds up in a fixed order
  *                                 (a gather over the transposed input graph filtered by argmax) instead
  *                                 of with atomics; slower, bit-reproducible.
  * hag_check synchronises `stream` and returns HAG_OK, or HAG_ETIMEOUT if a one-launch pass on this handle
  * gave up waiting since the last check (and clears that state). */
 enum { HAG_OPT_ONE_LAUNCH_MAX_ITEMS = 1, HAG_OPT_SPIN_LIMIT = 2, HAG_OPT_TEST_WAIT_UNREACHABLE = 3,
-       HAG_OPT_DETERMINISTIC_MAX_BACKWARD = 4, HAG_OPT_PARTITION_SHIFT = 5, HAG_OPT_SEQ_ONE_LAUNCH = 6 };
+       HAG_OPT_DETERMINISTIC_MAX_BACKWARD = 4, HAG_OPT_PARTITION_SHIFT = 5, HAG_OPT_SEQ_ONE_LAUNCH = 6, HAG_OPT_LIST_FORMS = 7 };
 int hag_set_option(hag_t *h, int32_t option, int64_t value);
 int hag_check(const hag_t *h, void *stream);
 

@@ -22,6 +22,7 @@ HAG_OK, HAG_EINVAL, HAG_ENOMEM, HAG_EHIP, HAG_ESTATE, HAG_ETIMEOUT = 0, -1, -2, 
 HAG_OPT_ONE_LAUNCH_MAX_ITEMS, HAG_OPT_SPIN_LIMIT, HAG_OPT_TEST_WAIT_UNREACHABLE, HAG_OPT_DETERMINISTIC_MAX_BACKWARD = 1, 2, 3, 4
 HAG_OPT_SEQ_ONE_LAUNCH = 6
 HAG_OPT_PARTITION_SHIFT = 5
+HAG_OPT_LIST_FORMS = 7
 HAG_SEARCH_CANONICAL, HAG_SEARCH_DEDUP, HAG_SEARCH_DEVICE = 1, 2, 4
 HAG_PHASE_LEVELS, HAG_PHASE_GATHER, HAG_PHASE_FOLD, HAG_PHASE_ALL = 1, 2, 4, 7
 OPS = {"sum": HAG_SUM, "mean": HAG_MEAN, "max": HAG_MAX, "gcn": HAG_GCN}
@@ -32,7 +33,7 @@ EXPORTS = [
     "hag_backward", "hag_forward_phases", "hag_backward_phases", "hag_naive_forward", "hag_naive_backward",
     "hag_algorithmic_bytes", "hag_last_error", "hag_forward_static_scratch", "hag_probe_rows", "hag_probe_copy", "hag_probe_mfma_f32", "hag_set_option", "hag_check", "hag_seq_search",
     "hag_seq_create", "hag_seq_free", "hag_seq_cells", "hag_seq_ranks", "hag_seq_launches", "hag_seq_get_plan", "hag_seq_set_option", "hag_seq_check", "hag_seq_train_workspace_bytes", "hag_seq_lstm_forward_train", "hag_seq_lstm_backward", "hag_seq_merges", "hag_seq_upload", "hag_seq_workspace_bytes",
-    "hag_seq_lstm_forward", "hag_route",
+    "hag_seq_lstm_forward", "hag_route", "hag_naive_route",
 ]
 ROUTES = ("hag", "lists", "component_hag", "component_lists", "dense", "one_launch", "scatter")   # HAG_ROUTE_*
 HAG_STATIC_SCRATCH_BYTES = 64 << 20
@@ -110,7 +111,8 @@ def lib():
         L.hag_seq_lstm_forward.argtypes = [vp, i64, i64, vp, vp, vp, vp, vp, vp, vp]
         L.hag_set_option.argtypes = [vp, i32, i64]
         L.hag_check.argtypes = [vp, vp]
-        L.hag_route.argtypes = [vp, ctypes.c_int, ctypes.c_int, i64, i32]
+        for name in ("hag_route", "hag_naive_route"):
+            getattr(L, name).argtypes = [vp, ctypes.c_int, ctypes.c_int, i64, i32]
         _lib = L
     return _lib
 
@@ -227,9 +229,10 @@ class Hag:
         """Synchronises the current stream; raises HagError(HAG_ETIMEOUT) if a one-launch pass gave up waiting."""
         _check(lib().hag_check(self._h, _stream_ptr()))
 
-    def route(self, op="sum", dtype_code=HAG_F32, d=64, backward=False) -> str:
-        """The way forward (or backward) takes for this op, dtype and width: one of ROUTES."""
-        rc = int(lib().hag_route(self._h, OPS[op], dtype_code, int(d), int(backward)))
+    def route(self, op="sum", dtype_code=HAG_F32, d=64, backward=False, naive=False) -> str:
+        """The way forward or backward (naive: naive_forward or naive_backward) takes for this op, dtype and width: one of ROUTES."""
+        query = lib().hag_naive_route if naive else lib().hag_route
+        rc = int(query(self._h, OPS[op], dtype_code, int(d), int(backward)))
         if rc < 0:
             _check(rc)
         return ROUTES[rc]

@@ -55,8 +55,7 @@ static void add_plan(const hag_handle *h, const Plan &p, const std::vector<int32
         if (k == 0) long0 = n;
         n_long += n;
     }
-    double reads = 0;
-    for (const Item &it : p.items) reads += it.cnt;
+    const double reads = (double)p.n_reads;
     c.miss[w] += reads * miss_rate(p, col, h->n + h->a, lpr, long0, reads, h->comp.enabled ? kSampleReadsBatch : kSampleReads);
     c.fold[w] += (double)n_long * (kBlock / lpr);
     if (w > 0) return;

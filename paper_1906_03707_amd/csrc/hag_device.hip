@@ -384,12 +384,12 @@ static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op,
     q.max = op == HAG_MAX;
     q.backward = backward;
     q.hag_allowed = !naive;
-    q.lists_allowed = naive || (h->a > 0 && h->knobs.route && !one_launch);
-    q.dense_allowed = h->comp.dense && dt == HAG_F32 && op != HAG_MAX && !h->comp.dense_always;
+    q.lists_allowed = naive || (h->a > 0 && h->knobs.route && !h->knobs.list_forms && !one_launch);
+    q.dense_allowed = h->comp.dense && dt == HAG_F32 && op != HAG_MAX && !h->knobs.list_forms;
     q.d = d;
     q.component_lds[0] = on_hag.total * on_hag.parts;     // (priced with its columns in one piece: the pieces are a knob for experiments)
     q.component_lds[1] = on_lists.total * on_lists.parts;
-    const int form = h->comp.dense_always && dt == HAG_F32 && op != HAG_MAX ? kFormDense : cheapest_form(h, q);
+    const int form = q.dense_allowed && h->comp.dense_always ? kFormDense : cheapest_form(h, q);
     if (form == kFormDense) return HAG_ROUTE_DENSE;
     if (form == kFormLists) return on_lists.total > 0 ? HAG_ROUTE_COMPONENT_LISTS : HAG_ROUTE_LISTS;
     if (on_hag.total > 0) return HAG_ROUTE_COMPONENT_HAG;
@@ -693,14 +693,16 @@ int hag_forward_static_scratch(const hag_t *h, hag_op_t op, hag_dtype_t dt, int6
     if (!ws) { set_error("static scratch of the handle's device was not set up"); return HAG_ESTATE; }
     return forward_entry(h, false, op, dt, d, x, y, argmax, ws, stream, HAG_PHASE_ALL);
 }
-int hag_route(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d, int32_t backward) {
+static int route_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, int32_t backward) {
     if (!h) { set_error("handle is NULL"); return HAG_EINVAL; }
     if (op != HAG_SUM && op != HAG_MEAN && op != HAG_MAX && op != HAG_GCN) { set_error("unknown op"); return HAG_EINVAL; }
     if (dt != HAG_F32 && dt != HAG_I32) { set_error("unknown dtype"); return HAG_EINVAL; }
     if ((op == HAG_MEAN || op == HAG_GCN) && dt != HAG_F32) { set_error("mean and gcn are defined for f32 only"); return HAG_EINVAL; }
     if (d <= 0 || d % 4 != 0 || d > (1 << 20)) { set_error("d must be a positive multiple of 4, at most 2^20"); return HAG_EINVAL; }
-    return route_of(h, false, backward != 0, op, dt, d, HAG_PHASE_ALL);
+    return route_of(h, naive, backward != 0, op, dt, d, HAG_PHASE_ALL);
 }
+int hag_route(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d, int32_t backward) { return route_entry(h, false, op, dt, d, backward); }
+int hag_naive_route(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d, int32_t backward) { return route_entry(h, true, op, dt, d, backward); }
 int hag_set_option(hag_t *h, int32_t option, int64_t value) {
     if (!h) { set_error("handle is NULL"); return HAG_EINVAL; }
     switch (option) {
@@ -708,6 +710,7 @@ int hag_set_option(hag_t *h, int32_t option, int64_t value) {
         case HAG_OPT_SPIN_LIMIT: h->knobs.spin_limit = std::max<int64_t>(value, 1); return HAG_OK;
         case HAG_OPT_TEST_WAIT_UNREACHABLE: h->knobs.wait_unreachable = value != 0; return HAG_OK;
         case HAG_OPT_DETERMINISTIC_MAX_BACKWARD: h->knobs.deterministic_max_backward = value != 0; return HAG_OK;
+        case HAG_OPT_LIST_FORMS: h->knobs.list_forms = value != 0; return HAG_OK;
         case HAG_OPT_PARTITION_SHIFT: h->knobs.part_shift = (int32_t)(value & 7); return HAG_OK;
     }
     set_error("unknown option");

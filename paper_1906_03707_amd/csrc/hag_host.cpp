@@ -622,6 +622,7 @@ void build_plan(const Csr &c, std::vector<int32_t> &dcol, int64_t row_begin, int
     p.items.clear();
     p.combine.clear();
     p.n_slots = 0;
+    p.n_reads = c.ptr[row_end] - c.ptr[row_begin];
     p.np = np;
     std::vector<int32_t> slot_row;                        // output row of every partial slot
     auto cut = [&](int part, int64_t beg, int64_t cnt, bool partial, int64_t row) {

@@ -42,6 +42,7 @@ struct Plan {
     std::vector<int64_t> part_begin;
     std::vector<Item> combine;   // per split row: beg = first slot, cnt = #slots, row = output row
     int64_t n_slots = 0;
+    int64_t n_reads = 0;         // entries of all items
     // items of a length class up to this one are not ordered by class (see build_plan): the
     // launch may only hand whole workgroups to items of longer classes
     int min_block_class = 0;
@@ -178,6 +179,7 @@ struct hag_knobs {
     int64_t spin_limit = 0;     // HAG_SPIN_LIMIT: polls a wavefront of the one-launch pass waits for earlier phases
     bool wait_unreachable = false;      // test only: the awaited count can never be reached, so every wait gives up
     bool deterministic_max_backward = false;
+    bool list_forms = false;    // every call over its own lists
     bool route = true;          // HAG_ROUTE: whole passes may run over the input graph's lists where those are faster
     int32_t part_shift = 0;     // HAG_PART_SHIFT: workgroup b of a partitioned launch takes the sources of class (b + shift) mod 8
 };

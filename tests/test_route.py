@@ -113,3 +113,18 @@ def test_the_way_depends_on_the_handle_alone():
     again = B.hag_from_merges(rowptr, col, left, right)
     for op in ("sum", "max", "gcn"):
         assert ways(h, op, widths=range(4, 300, 28)) == ways(again, op, widths=range(4, 300, 28)) == ways(h.prefix(left.size), op, widths=range(4, 300, 28))
+
+
+def test_list_forms_option():
+    # what a comparison of the HAG with the plain lists needs: each over its own lists, and the handle's own choice back afterwards
+    rowptr, col = synth.holme_kim(3000, 8, 0.5, seed=81)
+    graph = B.hag_search(rowptr, col, 750)
+    rowptr, col, gp = synth.er_batch(150, 40, 0.6, seed=5)
+    batch = B.hag_search_batched(rowptr, col, gp, 0.25)
+    for h, own, hag, lists in ((graph, "lists", "hag", "lists"), (batch, "dense", "component_hag", "component_lists")):
+        both = lambda **k: [h.route("sum", d=64, backward=b, **k) for b in (False, True)]   # noqa: E731
+        assert both() == [own] * 2 == both(naive=True)
+        h.set_option(B.HAG_OPT_LIST_FORMS, 1)
+        assert both() == [hag] * 2 and both(naive=True) == [lists] * 2
+        h.set_option(B.HAG_OPT_LIST_FORMS, 0)
+        assert both() == [own] * 2 == both(naive=True)

@@ -41,6 +41,7 @@ struct hag_seq {
     std::vector<int32_t> paths_by_depth;
     std::vector<int64_t> depth_ptr, depth_tile_ptr;
     int64_t longest = 0;
+    int64_t n_empty = 0, n_from_state = 0;   // nodes with an empty list; nodes whose a_v is a state that no path of their own ends in
     bool one_launch = true;           // HAG_SEQ_ONE_LAUNCH (default 1): all levels in one launch, paths waiting for the states they start from
     int32_t spin_limit = 1 << 21;     // HAG_SPIN_LIMIT: polls (about half a microsecond apart) after which such a wait gives up
     bool wait_unreachable = false;    // tests only: flags are never set, so every wait gives up
@@ -93,13 +94,20 @@ __device__ __forceinline__ void seq_split2(float a, float b, uint32_t (&p)[3]) {
 //       l % 32 of the tile, k = 16 * step + 8 * (l / 32) + 0..7.  Row 8 m + 4 p + gate of a tile is that gate of hidden unit
 //       8 * tile + 4 p + m, so that lane l of the product ends up with all gates of four CONSECUTIVE units;
 //   bp: the bias in (unit, gate) order.
-// The "state is written" counters of the pass start at zero.
+// The "state is written" counters of the pass start at zero, and a_v of the nodes with an empty list is zero (final_state NULL: there are none).
 __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
                                                       const float *__restrict__ b, float *__restrict__ wx,
                                                       uint16_t *__restrict__ wq, float *__restrict__ bp, int d, int dp,
-                                                      int hidden, int ks, int32_t *__restrict__ flags, int64_t n_flags) {
+                                                      int hidden, int ks, int32_t *__restrict__ flags, int64_t n_flags,
+                                                      const int32_t *__restrict__ final_state, float *__restrict__ a_out, int64_t n) {
     const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
     for (int64_t f = first; f < n_flags; f += stride) flags[f] = 0;
+    if (final_state) {                                     // 64 nodes per wavefront, as in seq_output_kernel
+        const int lane = threadIdx.x & 63;
+        for (int64_t base = first - lane; base < n; base += stride)
+            for (unsigned long long left = __ballot(base + lane < n && final_state[base + lane < n ? base + lane : 0] == -1); left; left &= left - 1)
+                for (int u = lane; u < hidden; u += 64) a_out[(base + __builtin_ctzll(left)) * hidden + u] = 0.f;
+    }
     for (int64_t i = first; i < (int64_t)4 * hidden; i += stride) bp[i] = b[(i & 3) * hidden + (i >> 2)];
     for (int64_t i = first; i < (int64_t)4 * hidden * dp; i += stride) {
         const int per_tile = 32 * dp, tile = (int)(i / per_tile), rest = (int)(i % per_tile);
@@ -542,16 +550,16 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
     }
 }
 
-// a_v of the nodes that no path writes: a shared state's h, or zero for an empty list.  Most nodes are written by their path, so a
+// a_v of the nodes whose whole list is a shared prefix: that state's h.  Most nodes are written by their path, so a
 // wavefront looks at 64 nodes at once and moves rows only for those that are left (one thread per element took 40 us for 370 k nodes).
 __global__ __launch_bounds__(256) void seq_output_kernel(const int32_t *__restrict__ final_state, const float *__restrict__ h,
                                                         float *__restrict__ out, int64_t n, int hidden) {
     const int lane = threadIdx.x & 63;
     const int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
     const int state = base + lane < n ? final_state[base + lane] : -2;
-    for (unsigned long long left = __ballot(state != -2); left; left &= left - 1) {
+    for (unsigned long long left = __ballot(state >= 0); left; left &= left - 1) {
         const int b = __builtin_ctzll(left), s = __builtin_amdgcn_readlane(state, b);
-        for (int u = lane; u < hidden; u += 64) out[(size_t)(base + b) * hidden + u] = s >= 0 ? h[(size_t)s * hidden + u] : 0.f;
+        for (int u = lane; u < hidden; u += 64) out[(size_t)(base + b) * hidden + u] = h[(size_t)s * hidden + u];
     }
 }
 
@@ -586,25 +594,24 @@ struct SeqRevArgs {
 };
 
 
-__global__ __launch_bounds__(256) void seq_copy_i32_kernel(const int32_t *__restrict__ src, int32_t *__restrict__ dst, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) dst[i] = src[i];
-}
-
-__global__ __launch_bounds__(256) void seq_fill_kernel(float *p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0.f;
-}
-
-// The weights of the backward products, from the usual layout.
+// What the backward pass starts from, in one launch: cleared gradient rows of the kept states, cleared g_x where some node is in no list
+// (n_g_x > 0), the pending counts of a one-launch pass (n_states > 0) and the weights of the products, from the usual layout.
 //   wqt, hidden <= 64: [gate tile][m_tiles of 32 hidden units][16][lane]; lane l supplies output unit 32 * mt + l % 32, and as k
 //       value e = 4 m + gate the gate row of unit 8 * tile + 4 * (l / 32) + m: the order in which the lanes hold dG;
 //   wqt, hidden > 64: [m_tiles][4H / 8 groups of four k-steps][lane][4]; lane l supplies unit 32 * mt + l % 32, k-step q the gate
 //       rows 2 q + l / 32 in (unit, gate) order;
 //   wxt: W_ih^T for g_x: [d tiles of 32 columns][4H / 8 groups of four k-steps][lane][4]; lane l supplies column 32 * tile + l % 32,
 //       k-step q the gate rows 2 q + l / 32.
-__global__ __launch_bounds__(256) void seq_pack_transposed_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
-                                                                 float *__restrict__ wqt, float *__restrict__ wxt, int d, int hidden) {
+__global__ __launch_bounds__(256) void seq_backward_start_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
+                                                                float *__restrict__ wqt, float *__restrict__ wxt, int d, int hidden,
+                                                                float *__restrict__ state_grads, int64_t n_state_grads, float *__restrict__ g_x,
+                                                                int64_t n_g_x, const int32_t *__restrict__ pending_init,
+                                                                int32_t *__restrict__ pending, int64_t n_states) {
     const int m_tiles = (hidden + 31) / 32, d_tiles = (d + 31) / 32, rows = 4 * hidden;
     const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
+    for (int64_t i = first; i < n_state_grads; i += stride) state_grads[i] = 0.f;
+    for (int64_t i = first; i < n_g_x; i += stride) g_x[i] = 0.f;
+    for (int64_t i = first; i < n_states; i += stride) pending[i] = pending_init[i];
     for (int64_t i = first; i < (int64_t)m_tiles * 32 * rows; i += stride) {
         int unit, gate, z;
         if (hidden <= 64) {
@@ -1156,28 +1163,29 @@ __global__ __launch_bounds__(256) void seq_edges_kernel(const int32_t *__restric
 }
 
 // adds the workgroups' partial sums in a fixed order (eight interleaved sums, then those) and writes gate-major rows; `g_b` is NULL where
-// the column sums are not wanted.  32 outputs per workgroup, eight threads each.
-__global__ __launch_bounds__(256) void seq_weight_grad_reduce_kernel(const float *__restrict__ partial, int groups, float *__restrict__ g_w,
-                                                                    float *__restrict__ g_b, int cols, int hidden, int kp) {
+// the column sums are not wanted.  32 outputs per workgroup, eight threads each; the first `split` workgroups serve one contraction, the others the other.
+struct SeqReduceArgs { const float *partial; float *g_w, *g_b; int32_t groups, cols, kp; };
+__global__ __launch_bounds__(256) void seq_weight_grad_reduce_kernel(SeqReduceArgs first, SeqReduceArgs second, unsigned split, int hidden) {
     __shared__ float part[8][32];
-    const int64_t per = (int64_t)4 * hidden * kp + 4 * hidden, wanted = g_b ? per : per - 4 * hidden;
+    const SeqReduceArgs A = blockIdx.x < split ? first : second;
+    const int64_t per = (int64_t)4 * hidden * A.kp + 4 * hidden, wanted = A.g_b ? per : per - 4 * hidden;
     const int o = threadIdx.x & 31, p = threadIdx.x >> 5;
-    const int64_t i = (int64_t)blockIdx.x * 32 + o;
-    const bool in_use = i < wanted && (i >= (int64_t)4 * hidden * kp || (int)(i % kp) < cols);   // (padding columns were never written)
+    const int64_t i = (int64_t)(blockIdx.x - (blockIdx.x < split ? 0 : split)) * 32 + o;
+    const bool in_use = i < wanted && (i >= (int64_t)4 * hidden * A.kp || (int)(i % A.kp) < A.cols);   // (padding columns were never written)
     float sum = 0.f;
     if (in_use)
-        for (int g = p; g < groups; g += 8) sum += partial[(size_t)g * per + i];
+        for (int g = p; g < A.groups; g += 8) sum += A.partial[(size_t)g * per + i];
     part[p][o] = sum;
     __syncthreads();
     if (p != 0 || !in_use) return;
 #pragma unroll
     for (int k = 1; k < 8; ++k) sum += part[k][o];
-    if (i < (int64_t)4 * hidden * kp) {
-        const int r = (int)(i / kp), k = (int)(i % kp);
-        g_w[(size_t)((r & 3) * hidden + (r >> 2)) * cols + k] = sum;
+    if (i < (int64_t)4 * hidden * A.kp) {
+        const int r = (int)(i / A.kp), k = (int)(i % A.kp);
+        A.g_w[(size_t)((r & 3) * hidden + (r >> 2)) * A.cols + k] = sum;
     } else {
-        const int r = (int)(i - (int64_t)4 * hidden * kp);
-        g_b[(r & 3) * hidden + (r >> 2)] = sum;
+        const int r = (int)(i - (int64_t)4 * hidden * A.kp);
+        A.g_b[(r & 3) * hidden + (r >> 2)] = sum;
     }
 }
 
@@ -1338,6 +1346,7 @@ int hag_seq_create(int64_t n, const int64_t *rowptr, const int32_t *col, int64_t
             if (tail[st] < 0 || rem[tail[st]].len < (int32_t)(b1 - b0 - 1)) tail[st] = (int32_t)rem.size();
             rem.push_back(R{st, (int32_t)(b0 + 1), (int32_t)(b1 - b0 - 1), (int32_t)v});
         }
+        for (int32_t f : h->final_state) { h->n_empty += f == -1; h->n_from_state += f >= 0; }
         // a state hands its running (h, c) to the successor with the most evaluations below it, or, with no
         // successor state, to its longest remainder
         std::vector<int32_t> cont((size_t)S, -1);
@@ -1616,9 +1625,9 @@ static int seq_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const floa
     uint16_t *wq = (uint16_t *)(w + L.wq);
     int32_t *flags = (int32_t *)(w + L.flags);              // [n_states]
     {
-        const int64_t total = std::max<int64_t>({4 * hidden * L.dp, hidden / 8 * L.ks * 512, std::min<int64_t>(h->n_states, 1 << 20)});
+        const int64_t total = std::max<int64_t>({4 * hidden * L.dp, hidden / 8 * L.ks * 512, std::min<int64_t>(std::max(h->n_states, h->n_empty > 0 ? h->n : 0), 1 << 20)});
         hipLaunchKernelGGL(seq_pack_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, w_ih, w_hh, b, wx, wq, bp, (int)d,
-                           (int)L.dp, (int)hidden, (int)L.ks, flags, h->n_states);
+                           (int)L.dp, (int)hidden, (int)L.ks, flags, h->n_states, h->n_empty > 0 ? h->d_final : nullptr, a_out, h->n);
         HIP_TRY(hipGetLastError());
     }
     if (const int64_t n_used = (int64_t)h->used.size(); n_used > 0) {
@@ -1648,7 +1657,7 @@ static int seq_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const floa
         hipLaunchKernelGGL(tape_g ? kSeqTapeVariants[variant] : kSeqVariants[variant], grid, block, 0, s, c);
         HIP_TRY(hipGetLastError());
     }
-    {
+    if (h->n_from_state > 0) {
         hipLaunchKernelGGL(seq_output_kernel, dim3((unsigned)((h->n + 255) / 256)), dim3(256), 0, s, h->d_final, hst, a_out, h->n,
                            (int)hidden);
         HIP_TRY(hipGetLastError());
@@ -1731,30 +1740,21 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
     float *gh = (float *)(w + L.gh), *gc = (float *)(w + L.gc), *wqt = (float *)(w + L.wqt), *wxt = (float *)(w + L.wxt), *sums = (float *)(w + L.s);
     const int64_t cells = (int64_t)h->step_x.size(), n_used = (int64_t)h->used.size();
     auto blocks = [](int64_t total) { return dim3((unsigned)std::min<int64_t>((total + 255) / 256, 65535 * 16)); };
-    // gradient rows of the kept states start at zero (gh and gc are adjacent); nodes that no list names have no gradient
-    {
-        const int64_t total = (int64_t)((L.pending - L.gh) / sizeof(float));
-        hipLaunchKernelGGL(seq_fill_kernel, blocks(total), dim3(256), 0, s, gh, total);
-        HIP_TRY(hipGetLastError());
-        if (n_used < h->n) {
-            hipLaunchKernelGGL(seq_fill_kernel, blocks(h->n * d), dim3(256), 0, s, g_x, h->n * d);
-            HIP_TRY(hipGetLastError());
-        }
-    }
-    {
-        const int64_t total = 4 * hidden * std::max((hidden + 31) / 32, (d + 31) / 32) * 32;
-        hipLaunchKernelGGL(seq_pack_transposed_kernel, blocks(total), dim3(256), 0, s, w_ih, w_hh, wqt, wxt, (int)d, (int)hidden);
-        HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(seq_final_grad_kernel, dim3((unsigned)((h->n + 255) / 256)), dim3(256), 0, s, h->d_final, g_a, gh, h->n, (int)hidden);
-        HIP_TRY(hipGetLastError());
-    }
     const int64_t levels = (int64_t)h->tile_ptr.size() - 1;
     const int rv = seq_variant(hidden);
     const int64_t resident = h->resident_reverse[rv];
     const bool fused = levels > 1 && h->one_launch && resident > 0;
     int32_t *pending = (int32_t *)(w + L.pending);
-    if (fused) {
-        hipLaunchKernelGGL(seq_copy_i32_kernel, blocks(h->n_states), dim3(256), 0, s, h->d_pending_init, pending, h->n_states);
+    {
+        const int64_t n_state_grads = (int64_t)((L.pending - L.gh) / sizeof(float));   // (gh and gc are adjacent)
+        const int64_t n_g_x = n_used < h->n ? h->n * d : 0, n_states = fused ? h->n_states : 0;
+        const int64_t total = std::max({4 * hidden * std::max((hidden + 31) / 32, (d + 31) / 32) * 32, n_state_grads, n_g_x, n_states});
+        hipLaunchKernelGGL(seq_backward_start_kernel, blocks(total), dim3(256), 0, s, w_ih, w_hh, wqt, wxt, (int)d, (int)hidden, gh, n_state_grads, g_x, n_g_x,
+                           h->d_pending_init, pending, n_states);
+        HIP_TRY(hipGetLastError());
+    }
+    if (h->n_from_state > 0) {
+        hipLaunchKernelGGL(seq_final_grad_kernel, dim3((unsigned)((h->n + 255) / 256)), dim3(256), 0, s, h->d_final, g_a, gh, h->n, (int)hidden);
         HIP_TRY(hipGetLastError());
     }
     for (int64_t l = fused ? 0 : levels - 1; l >= 0; --l) {
@@ -1776,7 +1776,7 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
         HIP_TRY(hipGetLastError());
     }
     {
-        // recurrent weights and the per-node sums of dG, over the cells
+        // recurrent weights and the per-node sums of dG, over the cells (the partial sums are added up with the others, below)
         SeqWgradArgs g{};
         g.dg = tape_g; g.z = tape_h; g.z2 = hst; g.at = h->d_xt_idx; g.prev = h->d_xt_prev; g.seg = h->d_xt_seg;
         g.rows = cells; g.range = L.hh.range; g.cols = (int32_t)hidden; g.hidden = (int32_t)hidden;
@@ -1787,9 +1787,6 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
                                sums, (int)(4 * hidden));
             HIP_TRY(hipGetLastError());
         }
-        hipLaunchKernelGGL(seq_weight_grad_reduce_kernel, dim3((unsigned)((L.hh.per + 31) / 32)), dim3(256), 0, s, g.partial, (int)L.hh.groups, g_w_hh,
-                           (float *)nullptr, (int)hidden, (int)hidden, 32 * L.hh.nct);
-        HIP_TRY(hipGetLastError());
     }
     {
         // input weights, bias and g_x, over the nodes
@@ -1797,8 +1794,10 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
         g.dg = sums; g.z = x; g.at = h->d_used;
         g.rows = n_used; g.range = L.ih.range; g.cols = (int32_t)d; g.hidden = (int32_t)hidden; g.partial = (float *)(w + L.partial_ih);
         if (int rc = launch_wgrad<false>(g, L.ih, hidden, s)) return rc;
-        hipLaunchKernelGGL(seq_weight_grad_reduce_kernel, dim3((unsigned)((L.ih.per + 31) / 32)), dim3(256), 0, s, g.partial, (int)L.ih.groups, g_w_ih, g_b,
-                           (int)d, (int)hidden, 32 * L.ih.nct);
+        const SeqReduceArgs hh{(const float *)(w + L.partial_hh), g_w_hh, nullptr, (int32_t)L.hh.groups, (int32_t)hidden, 32 * L.hh.nct};
+        const SeqReduceArgs ih{g.partial, g_w_ih, g_b, (int32_t)L.ih.groups, (int32_t)d, 32 * L.ih.nct};
+        const unsigned split = (unsigned)((L.hh.per + 31) / 32);
+        hipLaunchKernelGGL(seq_weight_grad_reduce_kernel, dim3(split + (unsigned)((L.ih.per + 31) / 32)), dim3(256), 0, s, hh, ih, split, (int)hidden);
         HIP_TRY(hipGetLastError());
         if (n_used > 0) {
             hipLaunchKernelGGL(seq_input_grad_kernel, dim3((unsigned)std::min<int64_t>((n_used + 63) / 64, 1 << 20)), dim3(256), 0, s, sums, h->d_used, n_used,

@@ -85,7 +85,7 @@ void estimate_pass(const hag_handle *h, bool lists, bool backward, int w, PassCo
 }
 
 // The prices below were fitted to passes timed on an MI355X: 271 pairs (HAG, plain lists) for each of sum forward, sum transposed and max, over
-// 22 graphs of 1e3 to 2.3e5 nodes and 1e4 to 1.1e8 edges (dense groups and overlapping cliques with ids in order and shuffled, community and power-law
+// 20 graphs of 1e3 to 2.3e5 nodes and 5e4 to 1.1e8 edges (dense groups and overlapping cliques with ids in order and shuffled, community and power-law
 // graphs), HAGs of |V| / 16 to |V| nodes that save 1 to 95 % of the row reads, d = 16, 64, 128 and 512.  A pass's time is met within 14 %
 // (root mean square; max 17 %).  Taking what they call cheaper costs 0.4 % on average against always knowing (sum: more than 5 % in 9 of 542 cases, the
 // worst 17 %; max: 0.5 %, 7 of 271, 33 %); always the lists would cost 13 % on average and up to 3.6 times (max 14 %, 3.8 times), always the HAG

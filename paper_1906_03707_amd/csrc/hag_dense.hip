@@ -20,7 +20,9 @@ typedef unsigned int dense_u4_t __attribute__((ext_vector_type(4)));
 // Graphs up to kDenseMaxNodes nodes: the matrix and vector instructions of a wavefront (about 0.1 nv^2 + 10 nv cycles of a compute unit
 // per 64 columns) stay below the time its rows take from and to HBM (about 60 nv), whatever the number of edges; lists of ids cost about two
 // cycles per edge and column block, plus a barrier per stage.  Measured, 5000 graphs of 74 nodes, d = 64, forward and transposed pass
-// together: 80 us (4.7 TB/s of features in and results out, a copy runs at 5.2) at any density; lists 203 us at density 0.9, 114 us at 0.05.
+// together: 75 us repeated alone, 89 us on new features (4.3 TB/s of features in and results out, a copy runs at 5.2) at any density; lists repeated alone 160 us
+// at density 0.9 and about what the products take at 0.05.  Few, large and sparse graphs are better served by the lists: 100 of 250 nodes, mean degree 5: 35 against 22 us
+// (which form runs is decided in hag_cost.cpp).
 //
 // A feature is multiplied by 2^48 first, which takes even the last bit of a subnormal into the range of bf16 and is exact.  Features that the pieces
 // cannot hold then (infinities, NaN, |x| above 2^70) would also reach rows they are no neighbour of (0 * inf); a wavefront that has loaded one redoes

@@ -997,8 +997,8 @@ static void build_components(hag_handle *h) {
     }
     c.steps = 0;
     for (uint8_t v : c.n_stages) c.steps += v;
-    // Adjacency bits for the dense form, unless one of the knobs of the list form is given (HAG_COMPONENT_DENSE: 0 never, 1 by the rule of
-    // dense_applies, 2 always)
+    // Adjacency bits for the dense form, unless one of the knobs of the list form is given (HAG_COMPONENT_DENSE: 0 never, 1 where it is
+    // expected to be fastest, 2 always)
     const bool list_knob = env_i64("HAG_COMPONENT_EXPAND", -1) != -1 || env_i64("HAG_COMPONENT_PAD", 0) != 0 ||
                            env_i64("HAG_COMPONENT_EXTRA_LDS", 0) != 0 || env_i64("HAG_STREAM_OUTPUT", 0) != 0;
     const int64_t want = env_i64("HAG_COMPONENT_DENSE", list_knob ? 0 : 1);

@@ -18,7 +18,7 @@ static double miss_rate(const Plan &p, const std::vector<int32_t> &col, int64_t 
     if (n_ids <= cap) return std::min(1., (double)n_ids / std::max(1., plan_reads / kPartitions));   // every row once
     std::vector<int32_t> seen((size_t)n_ids, INT32_MIN);
     // one XCD's items: all of partition 0, or every 8th workgroup's
-    const int64_t per = kBlock / item_lanes(lpr), step = p.np > 1 ? 1 : kPartitions, n_groups = n_long + (n_all - n_long + per - 1) / per;
+    const int64_t per = kBlock / item_lanes(lpr, true), step = p.np > 1 ? 1 : kPartitions, n_groups = n_long + (n_all - n_long + per - 1) / per;
     int64_t misses = 0, reads = 0, counted = 0, counted_misses = 0;
     for (const int64_t from : {(int64_t)0, n_groups / 2 / step * step}) {
         // what was cached before a run counts as gone; a run counts from when its cache is full

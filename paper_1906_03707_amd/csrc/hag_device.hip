@@ -141,7 +141,6 @@ static int run_fused(const hag_handle *h, const std::vector<const Plan *> &plans
                      hipStream_t s) {
     FusedArgs<T> f{};
     const int lpr = pick_lpr(base.d);
-    const int64_t per_block = kBlock / item_lanes(lpr);
     int64_t blocks = 0;
     const int np = (int)plans.size();
     for (int k = 0; k < np; ++k) {
@@ -156,6 +155,8 @@ static int run_fused(const hag_handle *h, const std::vector<const Plan *> &plans
         ph.out_id = last ? final_out_id : agg_out_id;
         ph.out_off = last ? 0 : (int32_t)h->n;
         ph.block_begin = (int32_t)blocks;
+        ph.streams = several_streams((double)p.n_reads, (double)p.items.size(), RED == R_MAX) ? 1 : 0;
+        const int64_t per_block = kBlock / item_lanes(lpr, ph.streams != 0);
         blocks += ph.n_block + (ph.n_items - ph.n_block + per_block - 1) / per_block;
     }
     if (blocks > (1 << 24)) { set_error("launch too large"); return HAG_EINVAL; }
@@ -213,6 +214,7 @@ static int run_plan(const hag_handle *h, const Plan &p, const int32_t *d_col, Ga
             a.seg[k].n_block = long_items(p, k, threshold);
         }
     }
+    a.streams = several_streams((double)p.n_reads, (double)p.items.size(), RED == R_MAX) ? 1 : 0;
     a.col = d_col;
     a.part = (T *)w.part;
     a.part_id = (int32_t *)w.part_id;
@@ -228,6 +230,7 @@ static int run_plan(const hag_handle *h, const Plan &p, const int32_t *d_col, Ga
         c.seg[0].n_block = 0;
         c.seg[0].n_items = (int64_t)p.combine.size();
         c.col = h->d_slot_ids;
+        c.streams = several_streams((double)p.n_slots, (double)p.combine.size(), RED == R_MAX) ? 1 : 0;
         // partial results of a float max may still hold aggregation ids (see gather_body)
         c.late_id = (RED == R_MAX && std::is_same<T, float>::value) ? a.id_hi : nullptr;
         c.late_split = a.split;

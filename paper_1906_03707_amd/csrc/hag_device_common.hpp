@@ -51,6 +51,7 @@ struct GatherArgs {
     const float *self_scale;  // ... after being multiplied by self_scale[item.row], if given
     int32_t d;
     int32_t off32;            // both gathered matrices are smaller than 4 GiB: 32-bit byte offsets
+    int32_t streams;          // rows of up to 32 columns: several streams of lanes per short item (see several_streams)
     int32_t stream_hi;        // rows of src_hi are read once (fold of partial rows): streaming loads
     // Fold of partial (value, id) rows of a float max: a stored id >= late_split is an aggregation
     // node standing for the winner stored in late_id (row id - late_split); NULL: stored ids are final
@@ -91,6 +92,7 @@ struct FusedArgs {
         T *out;
         int32_t *out_id;
         int32_t out_off;
+        int32_t streams;      // as GatherArgs::streams
         int32_t block_begin;  // first ticket of the phase = number of workgroups of all earlier phases
     } ph[kMaxPhases];
     int32_t n_phases;

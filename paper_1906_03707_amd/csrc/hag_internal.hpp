@@ -66,11 +66,16 @@ static inline int pick_lpr(int64_t d) {
 // (forward sum over 26 M edges, 131072 nodes: d = 256 1425 -> 1341 us, d = 512 2838 -> 2676 us; narrower chunks gain nothing, the list work per byte grows).
 static inline int gather_lpr(int64_t d, int np) { return np > 1 ? std::min(pick_lpr(d), 32) : pick_lpr(d); }
 
-// Lanes that share one short item of a gather: at least 16, so that narrow rows (4 or 8 lanes each) are read by 4 or 2 streams of lanes
-// side by side.  With one stream per item an item of 16 columns was a chain of one id load and four row loads per four entries, and took
+// Lanes that share one short item of a gather.  With `streams` at least 16, so that narrow rows (4 or 8 lanes each) are read by 4 or 2 streams of lanes
+// side by side: with one stream an item of 16 columns is a chain of one id load and four row loads per four entries, and took
 // longer than one of 64 columns.  Forward sum over 8.4 M edges (65536 nodes, mean degree 128): d = 16 142 -> 56 us, d = 32 95 -> 73 us (d = 64:
 // 117 us); over 26 M edges (131072 nodes): 244 -> 150 and 198 -> 194 us; max at d = 16 192 -> 86 us.
-constexpr int item_lanes(int lpr) { return lpr < 16 ? 16 : lpr; }
+constexpr int item_lanes(int lpr, bool streams) { return streams && lpr < 16 ? 16 : lpr; }
+// Whether a launch of narrow rows takes several streams per item: its items have to be long enough to feed them, as each item then takes 4 or 2 times the
+// wavefronts and a fold at its end.  300 k nodes, one stream / several, us: sum, mean degree 3, d = 4 / 16 / 32: 13.9 / 23.7, 21.5 / 25.9, 25.7 / 28.0; degree 8: 24.0 / 27.4,
+// 44.7 / 42.2, 51.5 / 50.9; degree 16: 44.0 / 38.3, 85.9 / 75.4, 94.7 / 90.1.  Max, degree 3: 17.3 / 44.5, 24.9 / 43.0, 32.3 / 40.2; degree 8:
+// 27.6 / 48.6, 49.6 / 51.5, 59.2 / 59.8; degree 16: 47.1 / 56.1, 90.9 / 80.2, 102 / 98.
+inline bool several_streams(double reads, double items, bool max) { return reads >= (max ? 12. : 8.) * items; }
 
 // What decides how long a pass over the lists of a graph or a HAG takes (hag_cost.cpp), summed over its launches.  Entry w of an array is
 // for rows that 4 << w lanes share.

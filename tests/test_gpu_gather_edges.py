@@ -127,13 +127,28 @@ def test_one_launch_max_with_ties(B, d, monkeypatch):
         h.check()                                                     # no wait gave up
 
 
+@pytest.mark.parametrize("d", [4, 16, 20, 32])
+@pytest.mark.parametrize("route", ["0", "1"])
+def test_lists_too_short_for_several_streams(B, d, route, monkeypatch):
+    # mean length below 8: one stream of 4 or 8 lanes per item, 64 or 32 items per workgroup, the last workgroup partly filled
+    monkeypatch.setenv("HAG_ROUTE", route)
+    rng = np.random.default_rng(d)
+    n = 1203
+    rows = [np.sort(rng.choice(n // 8, [0, 1, 2, 3, 4, 5, 7, 8, 9, 12][v % 10], replace=False)) for v in range(n)]
+    rowptr, col = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64), np.concatenate(rows).astype(np.int32)
+    h = B.hag_search(rowptr, col, 200).upload()
+    assert h.stats()["a"] > 20 and h.route("sum", d=d) == ("lists" if route == "1" else "hag")
+    check_against_oracle(h, rowptr, col, d)
+
+
+@pytest.mark.parametrize("longest", [8, 31])                          # one stream per item, several
 @pytest.mark.parametrize("d", [4, 16, 32, 64])
-def test_max_passes_over_nan_in_short_lists(B, d):
+def test_max_passes_over_nan_in_short_lists(B, d, longest):
     # the scan takes the first entry and then whatever is greater: a NaN stays if it comes first and hides nothing anywhere else, however many
     # streams of lanes share the list
     rng = np.random.default_rng(d)
     n = 400
-    rows = [np.sort(rng.choice(n, k, replace=False)) for k in rng.integers(1, 16, n)]
+    rows = [np.sort(rng.choice(n, k, replace=False)) for k in rng.integers(1, longest + 1, n)]
     rowptr, col = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64), np.concatenate(rows).astype(np.int32)
     h = B.hag_search(rowptr, col, 0).upload()
     x = rng.integers(-3, 4, (n, d)).astype(np.float32)

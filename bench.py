@@ -626,6 +626,8 @@ def main():
         return h.algorithmic_bytes((back == "backward") + (2 if which[back] in ("lists", "component_lists") else 0), op, d)
 
     way = form["forward"]
+    # rows of up to 32 columns: several streams of lanes per item where the lists are long enough
+    gather = "gather_streams_kernel" if lpr < 16 and (e if way == "lists" else st["h"]) >= (12 if op == "max" else 8) * n else "gather_kernel"
     whole = way != "hag"                                      # one launch (and, over plain lists cut by source, a fold): timed whole
     if whole:
         ms_gather = time_kernel(torch, lambda: None, lambda: h.forward(x, op, y=y, argmax=am),
@@ -634,7 +636,7 @@ def main():
         role = 3 if way == "lists" else 0
         kernel_name = {"dense": f"dense_kernel<{1 if d <= 16 else 2 if d <= 32 else 4}, 0>", "one_launch": f"fused_kernel<float, {1 if op == 'max' else 0}, {lpr}, 0>",
                        "component_hag": f"component_kernel<float, {lpr}, 256, 0>", "component_lists": f"component_kernel<float, {lpr}, 256, 2>"}.get(
-                           way, f"gather_kernel<float, {1 if op == 'max' else 0}, {lpr}, {role}>")
+                           way, f"{gather}<float, {1 if op == 'max' else 0}, {lpr}, {role}>")
     else:
         ms_gather = time_kernel(
             torch,
@@ -645,7 +647,7 @@ def main():
         gather_bytes = (row + 4) * st["h"] + (row + 16) * n   # row reads + index reads, row writes + schedule
         if op == "max":
             gather_bytes += row * n                           # argmax rows written beside the values
-        kernel_name = f"gather_kernel<float, {1 if op == 'max' else 0}, {lpr}, 0>"
+        kernel_name = f"{gather}<float, {1 if op == 'max' else 0}, {lpr}, 0>"
     achieved = gather_bytes / (ms_gather * 1e-3) / 1e9
     workload = f"config{cfg}:{synth.CONFIGS[cfg]['name']}"
     ceil = measure_ceilings(torch, binding, d) if not args.no_ceilings else None

@@ -259,7 +259,8 @@ int hag_get_forward(const hag_t *h, const int32_t **agg_left, const int32_t **ag
 int hag_upload(hag_t *h, void *stream);
 
 /* Bytes of caller-provided scratch that hag_forward / hag_backward need for this
- * op, dtype and d (aggregation-node rows, partial sums of split rows).  The
+ * op, dtype and d (aggregation-node rows, partial sums of split rows; max: the
+ * gradients of its transposed pass sorted by winner).  The
  * contents need not survive between calls: nothing is memorised for the backward
  * pass except argmax (Algorithm 2's caption). */
 size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d);
@@ -279,7 +280,8 @@ int hag_forward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d,
  * definition of equivalence in Section 3.2 it must return the gradient of the
  * naive aggregation): gx[u] = sum over consumers of u.  sum/mean run over the
  * transposed HAG, deepest level first; max uses only argmax
- * (gx[argmax[v,f], f] += gy[v,f], hardware atomics: fp32 order not fixed).
+ * (gx[argmax[v,f], f] += gy[v,f], fp32 order not fixed; it may be called without a
+ * workspace and then adds with device-wide atomics, slower where n * d >= 2^20).
  * gx is overwritten. */
 int hag_backward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d,
                  const void *gy, const int32_t *argmax, void *gx, void *workspace, void *stream);
@@ -355,7 +357,7 @@ int hag_naive_backward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d
  * with the workspace taken from a fixed device array inside the library instead of from the
  * caller.  The array holds HAG_STATIC_SCRATCH_BYTES per GPU from the moment the library is loaded
  * until the process ends.  HAG_EINVAL (nothing is launched) when
- * hag_workspace_bytes(h, op, dtype, d) exceeds it; HAG_ESTATE before hag_upload.  The call
+ * what the forward pass needs (at most hag_workspace_bytes(h, op, dtype, d)) exceeds it; HAG_ESTATE before hag_upload.  The call
  * allocates nothing, on the host or on the device.  All calls on one GPU share the one array:
  * calls that may overlap in time (different streams, different threads) race on it and must be
  * serialised by the caller; its contents are left over from the last call and nothing is

@@ -491,6 +491,7 @@ static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d
     if (route == HAG_ROUTE_SCATTER) {
         int64_t total = h->n * d;
         if (total == 0 || !(phases & HAG_PHASE_GATHER)) return HAG_OK;
+        if (ws && max_scatter_bytes(h->n, d) > 0) return launch_max_scatter<T>(h->n, d, gy, argmax, gx, ws, s);
         hipLaunchKernelGGL((fill_zero_kernel<T>), dim3((unsigned)((total / 4 + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                            s, gx, total / 4);
         HIP_TRY(hipGetLastError());
@@ -643,14 +644,16 @@ bad:
     return rc;
 }
 
+// what a pass over lists or a HAG needs; the transposed pass of max can do with none (it then adds with atomics)
+static size_t pass_bytes(const hag_t *h, hag_op_t op, int64_t d) { return !h || d <= 0 ? 0 : carve(h, op, d, nullptr).total; }
+
 size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t, int64_t d) {
-    if (!h || d <= 0) return 0;
-    return carve(h, op, d, nullptr).total;
+    return std::max(pass_bytes(h, op, d), h && d > 0 && op == HAG_MAX ? max_scatter_bytes(h->n, d) : 0);
 }
 
 static int forward_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, const void *x, void *y,
                          int32_t *argmax, void *ws, void *stream, uint32_t phases) {
-    int rc = check_common(h, op, dt, d, x, y, ws, hag_workspace_bytes(h, op, dt, d) > 0);
+    int rc = check_common(h, op, dt, d, x, y, ws, pass_bytes(h, op, d) > 0);
     if (rc) return rc;
     if (op == HAG_MAX && !argmax && h->n > 0) { set_error("argmax is required for max"); return HAG_EINVAL; }
     if ((uintptr_t)argmax & 15) { set_error("argmax must be 16-byte aligned"); return HAG_EINVAL; }
@@ -666,7 +669,7 @@ static int forward_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt
 
 static int backward_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, const void *gy,
                           const int32_t *argmax, void *gx, void *ws, void *stream, uint32_t phases) {
-    const bool needs_ws = (op != HAG_MAX || (h && h->knobs.deterministic_max_backward)) && hag_workspace_bytes(h, op, dt, d) > 0;
+    const bool needs_ws = (op != HAG_MAX || (h && h->knobs.deterministic_max_backward)) && pass_bytes(h, op, d) > 0;
     int rc = check_common(h, op, dt, d, gy, gx, ws, needs_ws);
     if (rc) return rc;
     if (op == HAG_MAX && !argmax && h->n > 0) { set_error("argmax is required for max"); return HAG_EINVAL; }
@@ -685,7 +688,7 @@ int hag_forward_static_scratch(const hag_t *h, hag_op_t op, hag_dtype_t dt, int6
     if (!h) { set_error("handle is NULL"); return HAG_EINVAL; }
     if (!h->uploaded) { set_error("hag_upload has not been called on this handle"); return HAG_ESTATE; }
     if (d <= 0 || d > (1 << 20)) { set_error("d out of range"); return HAG_EINVAL; }
-    const size_t need = hag_workspace_bytes(h, op, dt, d);
+    const size_t need = pass_bytes(h, op, d);
     if (need > (size_t)HAG_STATIC_SCRATCH_BYTES) {
         set_error("this pass needs " + std::to_string(need) + " bytes of scratch, the static array holds " +
                   std::to_string((size_t)HAG_STATIC_SCRATCH_BYTES) + ": use hag_forward with a workspace");

@@ -34,6 +34,7 @@ EXPORTS = [
     "hag_algorithmic_bytes", "hag_last_error", "hag_forward_static_scratch", "hag_probe_rows", "hag_probe_copy", "hag_probe_mfma_f32", "hag_set_option", "hag_check", "hag_seq_search",
     "hag_seq_create", "hag_seq_free", "hag_seq_cells", "hag_seq_ranks", "hag_seq_launches", "hag_seq_get_plan", "hag_seq_set_option", "hag_seq_check", "hag_seq_train_workspace_bytes", "hag_seq_lstm_forward_train", "hag_seq_lstm_backward", "hag_seq_merges", "hag_seq_upload", "hag_seq_workspace_bytes",
     "hag_seq_lstm_forward", "hag_route", "hag_naive_route",
+    "hag_weight_grad_workspace_bytes", "hag_weight_grad", "hag_softmax_loss_workspace_bytes", "hag_softmax_loss", "hag_softmax_loss_grad",
 ]
 ROUTES = ("hag", "lists", "component_hag", "component_lists", "dense", "one_launch", "scatter")   # HAG_ROUTE_*
 HAG_STATIC_SCRATCH_BYTES = 64 << 20
@@ -113,6 +114,13 @@ def lib():
         L.hag_check.argtypes = [vp, vp]
         for name in ("hag_route", "hag_naive_route"):
             getattr(L, name).argtypes = [vp, ctypes.c_int, ctypes.c_int, i64, i32]
+        L.hag_weight_grad_workspace_bytes.argtypes = [i64, i64, i64]
+        L.hag_weight_grad_workspace_bytes.restype = ctypes.c_size_t
+        L.hag_weight_grad.argtypes = [i64, i64, i64] + [vp] * 5
+        L.hag_softmax_loss_workspace_bytes.argtypes = []
+        L.hag_softmax_loss_workspace_bytes.restype = ctypes.c_size_t
+        L.hag_softmax_loss.argtypes = [i64, i64, vp, vp, i64] + [vp] * 4
+        L.hag_softmax_loss_grad.argtypes = [i64, i64, vp, vp, i64] + [vp] * 4
         _lib = L
     return _lib
 
@@ -376,6 +384,44 @@ def hag_from_merges(rowptr, col, left, right, flags=0) -> Hag:
     _check(lib().hag_from_merges(rowptr.size - 1, rowptr.ctypes.data, col.ctypes.data, left.size,
                                  left.ctypes.data, right.ctypes.data, flags, ctypes.byref(out)))
     return Hag(out.value)
+
+
+def weight_grad(x, g):
+    """x^T g [d, k] of float32 device matrices x [n, d] and g [n, k] on the current device (hag_weight_grad)."""
+    import torch
+    if x.dim() != 2 or g.dim() != 2 or x.shape[0] != g.shape[0] or x.dtype != torch.float32 or g.dtype != torch.float32 or x.device != g.device:
+        raise ValueError("x and g must be float32 matrices of the same number of rows on one device")
+    n, d, k = int(x.shape[0]), int(x.shape[1]), int(g.shape[1])
+    out = torch.empty((d, k), dtype=torch.float32, device=x.device)
+    ws = torch.empty(max(int(lib().hag_weight_grad_workspace_bytes(n, d, k)), 16), dtype=torch.uint8, device=x.device)
+    _check(lib().hag_weight_grad(n, d, k, _dev_ptr(x), _dev_ptr(g), _dev_ptr(out), _dev_ptr(ws), _stream_ptr()))
+    return out
+
+
+def _check_loss_args(z, labels):
+    import torch
+    if z.dim() != 2 or z.dtype != torch.float32 or labels.dim() != 1 or labels.dtype != torch.int64 or labels.shape[0] != z.shape[0] or labels.device != z.device:
+        raise ValueError("z must be a float32 matrix and labels int64, one per row, on one device")
+    return int(z.shape[0]), int(z.shape[1])
+
+
+def softmax_loss(z, labels, ignore=-100):
+    """(loss, rows that count), scalars on the device: SoftMax cross-entropy of z [n, classes], mean over the rows whose label is not `ignore`."""
+    import torch
+    n, classes = _check_loss_args(z, labels)
+    loss, counted = (torch.empty((), dtype=torch.float32, device=z.device) for _ in range(2))
+    ws = torch.empty(int(lib().hag_softmax_loss_workspace_bytes()), dtype=torch.uint8, device=z.device)
+    _check(lib().hag_softmax_loss(n, classes, _dev_ptr(z), _dev_ptr(labels), int(ignore), _dev_ptr(loss), _dev_ptr(counted), _dev_ptr(ws), _stream_ptr()))
+    return loss, counted
+
+
+def softmax_loss_grad(z, labels, counted, g_loss, ignore=-100):
+    """Gradient of g_loss * softmax_loss at z."""
+    import torch
+    n, classes = _check_loss_args(z, labels)
+    out = torch.empty_like(z)
+    _check(lib().hag_softmax_loss_grad(n, classes, _dev_ptr(z), _dev_ptr(labels), int(ignore), _dev_ptr(counted), _dev_ptr(g_loss), _dev_ptr(out), _stream_ptr()))
+    return out
 
 
 def probe_rows(src, n_rows, d, reads, from_lds, workgroups, sink) -> int:

@@ -1,8 +1,8 @@
 """The two GNN layers of the paper's Table 1 around the library's aggregation calls.
 
-Only the aggregation (and, for GCN, the normalisation fused into it) is this library's work; the
-dense parts (weight matrices, ReLU, SoftMax loss) are plain torch and serve the end-to-end
-measurements and the layer-level parity tests.  Each aggregation call can be recorded (its input and
+The aggregation (and, for GCN, the normalisation fused into it), the gradients of the weight matrices
+and the SoftMax loss are this library's kernels; the other dense parts (products with the weight
+matrices, ReLU) are plain torch.  Each aggregation call can be recorded (its input and
 output tensors), so that a test can hand exactly those inputs to the CPU oracle.
 
 GCN (Table 1, GCN row; the model of Section 5.3):  h'_v = relu(W . (a_v + h_v) / (|N(v)| + 1)) with
@@ -13,6 +13,71 @@ GraphSAGE-P (Table 1, pooling row):  a_v = max over N(v) of relu(W1 h_u),  h'_v 
 from __future__ import annotations
 
 import torch
+
+from . import binding
+
+
+def _plain(t):
+    """A contiguous float32 matrix of the ordinary kind on the current device: what the library's kernels take."""
+    return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda and t.layout == torch.strided and t.dtype == torch.float32 and t.dim() == 2
+            and t.is_contiguous() and t.get_device() == torch.cuda.current_device())
+
+
+class _Product(torch.autograd.Function):
+    """x @ w with the gradient of w, a contraction over all rows of x, by hag_weight_grad."""
+
+    @staticmethod
+    def forward(ctx, x, w):
+        ctx.save_for_backward(x, w if ctx.needs_input_grad[0] else None)
+        return x @ w
+
+    @staticmethod
+    def backward(ctx, g):
+        x, w = ctx.saved_tensors
+        g_x = g @ w.t() if w is not None else None
+        if not ctx.needs_input_grad[1]:
+            return g_x, None
+        g = g.contiguous()
+        # a backward pass that is itself differentiated needs operations that are; and x comes back from whatever hooks keep saved tensors
+        own = not torch.is_grad_enabled() and _plain(x) and _plain(g) and x.data_ptr() % 16 == 0
+        return g_x, binding.weight_grad(x, g) if own else x.t() @ g
+
+
+def product(x, w):
+    """x @ w for a tall x [n, d] and a small w [d, k].
+
+    The gradient of w is the library's up to d * k = 65536: 65536 rows, 64 x 16 14 us against the BLAS's 82, 16 x 16 15 and 174, 256 x 256 144 and 217 (its
+    error against 64 bits 2e-7 and 2e-6); beyond, it reads x and g too many times (370000 rows, 256 x 256: 784 and 878)."""
+    if (torch.is_grad_enabled() and w.requires_grad and _plain(x) and _plain(w) and x.shape[1] == w.shape[0] and x.shape[1] % 4 == 0
+            and 0 < w.numel() <= 65536 and max(w.shape) <= 4096 and not torch.is_autocast_enabled()):
+        return _Product.apply(x, w)
+    return x @ w
+
+
+class _SoftmaxLoss(torch.autograd.Function):
+    @staticmethod
+    def forward(ctx, z, labels):
+        loss, counted = binding.softmax_loss(z, labels)
+        ctx.save_for_backward(z, labels, counted)
+        return loss
+
+    @staticmethod
+    def backward(ctx, g):
+        z, labels, counted = ctx.saved_tensors
+        if torch.is_grad_enabled() or not (_plain(z) and labels.is_contiguous()):   # (as above)
+            kept = (labels != -100)[:, None]
+            one_hot = torch.nn.functional.one_hot(torch.where(kept[:, 0], labels, 0), z.shape[1])
+            return torch.where(kept, (torch.softmax(z, 1) - one_hot) * (g / counted), 0.0), None
+        return binding.softmax_loss_grad(z, labels, counted, g.contiguous()), None
+
+
+def softmax_loss(z, labels):
+    """torch.nn.functional.cross_entropy(z, labels) by hag_softmax_loss where the arguments are of the ordinary kind (65536 rows, 16 classes, both
+    passes: 27 us against 113, 300 classes 100 and 234)."""
+    if (_plain(z) and type(labels) is torch.Tensor and labels.dtype == torch.int64 and labels.dim() == 1 and labels.device == z.device
+            and labels.is_contiguous() and labels.shape[0] == z.shape[0] and 0 < z.shape[1] <= 1 << 20 and not torch.is_autocast_enabled()):
+        return _SoftmaxLoss.apply(z, labels)
+    return torch.nn.functional.cross_entropy(z, labels)
 
 
 def aggregation(h, op, naive=False, record=None):
@@ -51,9 +116,9 @@ def aggregation(h, op, naive=False, record=None):
 def gcn2_loss(h, x, w1, w2, labels, naive=False, record=None):
     """SoftMax cross-entropy of a 2-layer GCN (Section 5.3's model) on features x."""
     agg = aggregation(h, "gcn", naive, record)
-    h1 = torch.relu(agg(x @ w1))
-    logits = agg(h1 @ w2)
-    return torch.nn.functional.cross_entropy(logits, labels)
+    h1 = torch.relu(agg(product(x, w1)))
+    logits = agg(product(h1, w2))
+    return softmax_loss(logits, labels)
 
 
 def sage_pool2_loss(h, x, pool, comb, labels, naive=False, record=None):
@@ -63,11 +128,11 @@ def sage_pool2_loss(h, x, pool, comb, labels, naive=False, record=None):
     agg = aggregation(h, "max", naive, record)
     hcur = x
     for i in range(2):
-        a = agg(torch.relu(hcur @ pool[i]))
-        hcur = torch.cat([a, hcur], dim=1) @ comb[i]
+        a = agg(torch.relu(product(hcur, pool[i])))
+        hcur = product(torch.cat([a, hcur], dim=1), comb[i])
         if i == 0:
             hcur = torch.relu(hcur)
-    return torch.nn.functional.cross_entropy(hcur, labels)
+    return softmax_loss(hcur, labels)
 
 
 def sage_lstm2_logits(seq, x, cells, comb):
@@ -113,7 +178,7 @@ def sage_lstm2_loss(seq, x, cells, comb, labels):
     h = x
     for i in range(2):
         a = agg(h, *cells[i])
-        h = torch.cat([a, h], dim=1) @ comb[i]
+        h = product(torch.cat([a, h], dim=1), comb[i])
         if i == 0:
             h = torch.relu(h)
-    return torch.nn.functional.cross_entropy(h, labels)
+    return softmax_loss(h, labels)

@@ -1,0 +1,99 @@
+"""hag_weight_grad and hag_softmax_loss against 64-bit sums: edges of their tiles (4 rows, 64 columns of x, 16 and 64 of g; 16 and 64 lanes per row of the
+loss), and the functions of layers.py around them where autograd is used in other ways than a plain backward pass."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+EPS = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1906_03707_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("n", [0, 1, 3, 5, 64, 515, 4099, 70001])
+@pytest.mark.parametrize("d,k", [(4, 1), (60, 7), (64, 16), (68, 17), (128, 33), (132, 65), (4, 4096), (4096, 5)])
+def test_weight_grad(B, n, d, k):
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    x, g = torch.randn(n, d, device="cuda", generator=gen), torch.randn(n, k, device="cuda", generator=gen)
+    want, size = x.double().t() @ g.double(), x.double().abs().t() @ g.double().abs()
+    # any order of n fp32 additions of rounded products: n + 1 roundings at most on the way of a term
+    assert bool(((B.weight_grad(x, g).double() - want).abs() <= (n + 1) * EPS * size).all())
+
+
+@pytest.mark.parametrize("n", [1, 17, 1000, 40001])
+@pytest.mark.parametrize("classes", [1, 2, 16, 63, 64, 65, 256, 257, 1000])
+def test_softmax_loss(B, n, classes):
+    gen = torch.Generator(device="cuda").manual_seed(n + classes)
+    z = 5 * torch.randn(n, classes, device="cuda", generator=gen)
+    z[0] += 1e4                                            # far from where exp() is finite
+    labels = torch.randint(0, classes, (n,), device="cuda", generator=gen)
+    labels[1::5] = -100
+    ref = z.double().requires_grad_()
+    want = torch.nn.functional.cross_entropy(ref, labels)
+    want.backward()
+    loss, counted = B.softmax_loss(z, labels)
+    # a row's loss is a difference of numbers of the size of its logits (top + log-sum and the label's): a few roundings of those
+    assert abs(loss.item() - want.item()) <= 8 * EPS * (abs(want.item()) + z.abs().max(1).values.sub(z[:, 0].abs()).abs().max().item() + 40)
+    assert counted.item() == (labels != -100).sum().item()
+    g = B.softmax_loss_grad(z, labels, counted, torch.tensor(3.0, device="cuda"))
+    # probabilities: exp of a difference that is exact to half an ulp of up to 40, times a reciprocal of a sum
+    assert bool(((g.double() - 3 * ref.grad).abs() <= 3 / counted.item() * EPS * 100).all())
+
+
+def test_softmax_loss_of_what_is_no_number(B):
+    z = torch.randn(40, 16, device="cuda")
+    labels = torch.arange(40, device="cuda") % 16
+    ce = torch.nn.functional.cross_entropy
+    for value in (float("nan"), float("inf"), float("-inf")):
+        y = z.clone()
+        y[7, 3] = value
+        assert torch.equal(torch.isfinite(B.softmax_loss(y, labels)[0]), torch.isfinite(ce(y, labels))), value
+    assert torch.isnan(B.softmax_loss(z, torch.full_like(labels, -100))[0])
+    labels[5] = 16                                         # no class
+    assert torch.isnan(B.softmax_loss(z, labels)[0])
+
+
+def test_products_and_loss_under_autograd(B):
+    from paper_1906_03707_amd import layers
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen)   # noqa: E731
+    x, w, labels = rnd(900, 20), rnd(20, 6), torch.randint(0, 6, (900,), device="cuda", generator=gen)
+    labels[::9] = -100
+
+    def model(product, loss, xx, ww):
+        return loss(product(xx, ww), labels)
+
+    own = (layers.product, layers.softmax_loss)
+    lib = (torch.matmul, torch.nn.functional.cross_entropy)
+    for x_grad in (False, True):
+        results = []
+        for how in (own, lib):
+            xx, ww = x.clone().requires_grad_(x_grad), w.clone().requires_grad_()
+            inputs = (xx, ww) if x_grad else (ww,)
+            value = model(*how, xx, ww)
+            first = torch.autograd.grad(value, inputs, create_graph=True)
+            second = torch.autograd.grad(sum((g ** 2).sum() for g in first), inputs)
+            plain = torch.autograd.grad(model(*how, xx, ww) * 2, inputs)
+            kept = []
+            with torch.autograd.graph.saved_tensors_hooks(lambda t: kept.append(t) or t.cpu(), lambda t: t.cuda()):
+                hooked = model(*how, xx, ww)
+            assert kept
+            results.append((value, *first, *second, *plain, *torch.autograd.grad(hooked, inputs)))
+        for a, b in zip(*results):
+            assert a.shape == b.shape and (a - b).norm().item() <= 1e-5 * b.norm().item()
+    with torch.no_grad():
+        assert torch.equal(layers.product(x, w), x @ w)
+    assert torch.equal(layers.product(x.to_sparse(), w.requires_grad_()), x.to_sparse() @ w)
+    value = layers.softmax_loss(x, labels.clamp(min=0))
+    value += 1                                             # in place, as with the library's
+    with pytest.raises(RuntimeError):
+        layers.product(x, w[:19])
+    probabilities = torch.softmax(rnd(900, 20), 1)
+    assert torch.equal(layers.softmax_loss(x, probabilities), torch.nn.functional.cross_entropy(x, probabilities))

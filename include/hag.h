@@ -367,13 +367,16 @@ int hag_forward_static_scratch(const hag_t *h, hag_op_t op, hag_dtype_t dtype, i
                                const void *x, void *y, int32_t *argmax, void *stream);
 
 /* Dense parts of a layer's training step on tall, narrow matrices (device pointers, fp32, row-major; kernels only, so they can be captured).
- * hag_weight_grad: g_w [d, k] = x^T g for x [n, d] (16-byte aligned), g [n, k]; d a multiple of 4, d and k at most 4096; `workspace` of
+ * hag_narrow_product: y [n, k] = x w for x [n, d] (16-byte aligned), w [d, k] (transposed: w [k, d], its transpose); relu: of relu(x); mask (may be NULL)
+ * [n, k]: 0 where it is not positive.  d a multiple of 4, at most 1024 for k <= 16, 512 for k <= 32, 256 beyond; k at most 4096.
+ * hag_weight_grad: g_w [d, k] = x^T g (relu: relu(x)^T g) for x [n, d] (16-byte aligned), g [n, k]; d a multiple of 4, d and k at most 4096; `workspace` of
  * hag_weight_grad_workspace_bytes(n, d, k) bytes.  Fixed order of additions.
  * hag_softmax_loss: *loss = mean over the rows whose label is not `ignore` of -log softmax(z[row])[label], z [n, classes]; *counted = number of those rows;
  * `workspace` of hag_softmax_loss_workspace_bytes() bytes, 16-byte aligned.  A label that is neither a class nor `ignore` makes the loss NaN.
  * hag_softmax_loss_grad: g_z [n, classes] = *g_loss times the gradient of that loss at z, `counted` as the loss call left it. */
 size_t hag_weight_grad_workspace_bytes(int64_t n, int64_t d, int64_t k);
-int hag_weight_grad(int64_t n, int64_t d, int64_t k, const float *x, const float *g, float *g_w, void *workspace, void *stream);
+int hag_weight_grad(int64_t n, int64_t d, int64_t k, const float *x, int32_t relu, const float *g, float *g_w, void *workspace, void *stream);
+int hag_narrow_product(int64_t n, int64_t d, int64_t k, const float *x, int32_t relu, const float *w, int32_t transposed, const float *mask, float *y, void *stream);
 size_t hag_softmax_loss_workspace_bytes(void);
 int hag_softmax_loss(int64_t n, int64_t classes, const float *z, const int64_t *labels, int64_t ignore, float *loss, float *counted,
                      void *workspace, void *stream);

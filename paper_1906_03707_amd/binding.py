@@ -34,7 +34,7 @@ EXPORTS = [
     "hag_algorithmic_bytes", "hag_last_error", "hag_forward_static_scratch", "hag_probe_rows", "hag_probe_copy", "hag_probe_mfma_f32", "hag_set_option", "hag_check", "hag_seq_search",
     "hag_seq_create", "hag_seq_free", "hag_seq_cells", "hag_seq_ranks", "hag_seq_launches", "hag_seq_get_plan", "hag_seq_set_option", "hag_seq_check", "hag_seq_train_workspace_bytes", "hag_seq_lstm_forward_train", "hag_seq_lstm_backward", "hag_seq_merges", "hag_seq_upload", "hag_seq_workspace_bytes",
     "hag_seq_lstm_forward", "hag_route", "hag_naive_route",
-    "hag_weight_grad_workspace_bytes", "hag_weight_grad", "hag_softmax_loss_workspace_bytes", "hag_softmax_loss", "hag_softmax_loss_grad",
+    "hag_weight_grad_workspace_bytes", "hag_weight_grad", "hag_narrow_product", "hag_softmax_loss_workspace_bytes", "hag_softmax_loss", "hag_softmax_loss_grad",
 ]
 ROUTES = ("hag", "lists", "component_hag", "component_lists", "dense", "one_launch", "scatter")   # HAG_ROUTE_*
 HAG_STATIC_SCRATCH_BYTES = 64 << 20
@@ -116,7 +116,8 @@ def lib():
             getattr(L, name).argtypes = [vp, ctypes.c_int, ctypes.c_int, i64, i32]
         L.hag_weight_grad_workspace_bytes.argtypes = [i64, i64, i64]
         L.hag_weight_grad_workspace_bytes.restype = ctypes.c_size_t
-        L.hag_weight_grad.argtypes = [i64, i64, i64] + [vp] * 5
+        L.hag_weight_grad.argtypes = [i64, i64, i64, vp, i32] + [vp] * 4
+        L.hag_narrow_product.argtypes = [i64, i64, i64, vp, i32, vp, i32, vp, vp, vp]
         L.hag_softmax_loss_workspace_bytes.argtypes = []
         L.hag_softmax_loss_workspace_bytes.restype = ctypes.c_size_t
         L.hag_softmax_loss.argtypes = [i64, i64, vp, vp, i64] + [vp] * 4
@@ -386,23 +387,64 @@ def hag_from_merges(rowptr, col, left, right, flags=0) -> Hag:
     return Hag(out.value)
 
 
-def weight_grad(x, g):
-    """x^T g [d, k] of float32 device matrices x [n, d] and g [n, k] on the current device (hag_weight_grad)."""
+def _raw_stream():
+    """The current stream of the current device, as a number."""
+    current_device, raw_stream = _torch_calls or _resolve_torch_calls()
+    return raw_stream(current_device())
+
+
+def _matrices(*tensors):
     import torch
-    if x.dim() != 2 or g.dim() != 2 or x.shape[0] != g.shape[0] or x.dtype != torch.float32 or g.dtype != torch.float32 or x.device != g.device:
-        raise ValueError("x and g must be float32 matrices of the same number of rows on one device")
-    n, d, k = int(x.shape[0]), int(x.shape[1]), int(g.shape[1])
+    for t in tensors:
+        if t.dim() != 2 or t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous() or t.device != tensors[0].device:
+            raise ValueError("contiguous float32 matrices on one device are needed")
+
+
+def narrow_product(x, w, transposed=False, relu=False, mask=None):
+    """x w [n, k] of x [n, d] and a small w [d, k] (transposed: w [k, d]), on the current device; relu: of relu(x); mask [n, k]: 0 where it is not positive
+    (hag_narrow_product)."""
+    import torch
+    _matrices(x, w)
+    n, d = x.shape
+    k = w.shape[0 if transposed else 1]
+    if w.shape[1 if transposed else 0] != d:
+        raise ValueError(f"x {tuple(x.shape)} and w {tuple(w.shape)} do not match")
+    if mask is not None:
+        _matrices(x, mask)
+        if mask.shape != (n, k):
+            raise ValueError(f"mask must have shape {(n, k)}")
+    y = torch.empty((n, k), dtype=torch.float32, device=x.device)
+    _check(lib().hag_narrow_product(n, d, k, x.data_ptr(), int(relu), w.data_ptr(), int(transposed), None if mask is None else mask.data_ptr(), y.data_ptr(),
+                                    _raw_stream()))
+    return y
+
+
+def weight_grad(x, g, relu=False):
+    """x^T g [d, k] (relu: relu(x)^T g) of float32 device matrices x [n, d] and g [n, k] on the current device (hag_weight_grad)."""
+    import torch
+    _matrices(x, g)
+    n, d, k = *x.shape, g.shape[1]
+    if g.shape[0] != n:
+        raise ValueError("x and g must have the same number of rows")
     out = torch.empty((d, k), dtype=torch.float32, device=x.device)
-    ws = torch.empty(max(int(lib().hag_weight_grad_workspace_bytes(n, d, k)), 16), dtype=torch.uint8, device=x.device)
-    _check(lib().hag_weight_grad(n, d, k, _dev_ptr(x), _dev_ptr(g), _dev_ptr(out), _dev_ptr(ws), _stream_ptr()))
+    ws = torch.empty(max(lib().hag_weight_grad_workspace_bytes(n, d, k), 16), dtype=torch.uint8, device=x.device)
+    _check(lib().hag_weight_grad(n, d, k, x.data_ptr(), int(relu), g.data_ptr(), out.data_ptr(), ws.data_ptr(), _raw_stream()))
     return out
 
 
 def _check_loss_args(z, labels):
     import torch
-    if z.dim() != 2 or z.dtype != torch.float32 or labels.dim() != 1 or labels.dtype != torch.int64 or labels.shape[0] != z.shape[0] or labels.device != z.device:
-        raise ValueError("z must be a float32 matrix and labels int64, one per row, on one device")
-    return int(z.shape[0]), int(z.shape[1])
+    _matrices(z)
+    if labels.dim() != 1 or labels.dtype != torch.int64 or labels.shape[0] != z.shape[0] or labels.device != z.device or not labels.is_contiguous():
+        raise ValueError("labels must be contiguous int64, one per row of z, on its device")
+    return z.shape
+
+
+def _scalar(t, like):
+    import torch
+    if t.numel() != 1 or t.dtype != torch.float32 or t.device != like.device:
+        raise ValueError("a float32 scalar on z's device is needed")
+    return t.data_ptr()
 
 
 def softmax_loss(z, labels, ignore=-100):
@@ -410,8 +452,8 @@ def softmax_loss(z, labels, ignore=-100):
     import torch
     n, classes = _check_loss_args(z, labels)
     loss, counted = (torch.empty((), dtype=torch.float32, device=z.device) for _ in range(2))
-    ws = torch.empty(int(lib().hag_softmax_loss_workspace_bytes()), dtype=torch.uint8, device=z.device)
-    _check(lib().hag_softmax_loss(n, classes, _dev_ptr(z), _dev_ptr(labels), int(ignore), _dev_ptr(loss), _dev_ptr(counted), _dev_ptr(ws), _stream_ptr()))
+    ws = torch.empty(lib().hag_softmax_loss_workspace_bytes(), dtype=torch.uint8, device=z.device)
+    _check(lib().hag_softmax_loss(n, classes, z.data_ptr(), labels.data_ptr(), int(ignore), loss.data_ptr(), counted.data_ptr(), ws.data_ptr(), _raw_stream()))
     return loss, counted
 
 
@@ -420,7 +462,7 @@ def softmax_loss_grad(z, labels, counted, g_loss, ignore=-100):
     import torch
     n, classes = _check_loss_args(z, labels)
     out = torch.empty_like(z)
-    _check(lib().hag_softmax_loss_grad(n, classes, _dev_ptr(z), _dev_ptr(labels), int(ignore), _dev_ptr(counted), _dev_ptr(g_loss), _dev_ptr(out), _stream_ptr()))
+    _check(lib().hag_softmax_loss_grad(n, classes, z.data_ptr(), labels.data_ptr(), int(ignore), _scalar(counted, z), _scalar(g_loss, z), out.data_ptr(), _raw_stream()))
     return out
 
 

@@ -23,6 +23,11 @@ def _plain(t):
             and t.is_contiguous() and t.get_device() == torch.cuda.current_device())
 
 
+def _plain_labels(labels, z):
+    return (type(labels) is torch.Tensor and labels.dtype == torch.int64 and labels.dim() == 1 and labels.device == z.device and labels.is_contiguous()
+            and labels.shape[0] == z.shape[0])
+
+
 class _Product(torch.autograd.Function):
     """x @ w with the gradient of w, a contraction over all rows of x, by hag_weight_grad."""
 
@@ -74,8 +79,7 @@ class _SoftmaxLoss(torch.autograd.Function):
 def softmax_loss(z, labels):
     """torch.nn.functional.cross_entropy(z, labels) by hag_softmax_loss where the arguments are of the ordinary kind (65536 rows, 16 classes, both
     passes: 27 us against 113, 300 classes 100 and 234)."""
-    if (_plain(z) and type(labels) is torch.Tensor and labels.dtype == torch.int64 and labels.dim() == 1 and labels.device == z.device
-            and labels.is_contiguous() and labels.shape[0] == z.shape[0] and 0 < z.shape[1] <= 1 << 20 and not torch.is_autocast_enabled()):
+    if _plain(z) and _plain_labels(labels, z) and 0 < z.shape[1] <= 1 << 20 and not torch.is_autocast_enabled():
         return _SoftmaxLoss.apply(z, labels)
     return torch.nn.functional.cross_entropy(z, labels)
 
@@ -113,12 +117,59 @@ def aggregation(h, op, naive=False, record=None):
     return Agg.apply
 
 
-def gcn2_loss(h, x, w1, w2, labels, naive=False, record=None):
-    """SoftMax cross-entropy of a 2-layer GCN (Section 5.3's model) on features x."""
+def _gcn2_composed(h, x, w1, w2, labels, naive, record):
     agg = aggregation(h, "gcn", naive, record)
     h1 = torch.relu(agg(product(x, w1)))
     logits = agg(product(h1, w2))
     return softmax_loss(logits, labels)
+
+
+class _Gcn2Loss(torch.autograd.Function):
+    """gcn2_loss as one node of the graph: the same calls as the composed form, with the ReLU inside the products on both sides of it."""
+
+    @staticmethod
+    def forward(ctx, x, w1, w2, labels, h, naive):
+        agg = h.naive_forward if naive else h.forward
+        a1 = agg(binding.narrow_product(x, w1), "gcn")
+        logits = agg(binding.narrow_product(a1, w2, relu=True), "gcn")
+        loss, counted = binding.softmax_loss(logits, labels)
+        ctx.save_for_backward(x, w1, w2, labels, a1, logits, counted)
+        ctx.h, ctx.naive = h, naive
+        return loss
+
+    @staticmethod
+    def backward(ctx, g):
+        x, w1, w2, labels, a1, logits, counted = ctx.saved_tensors
+        need_x, need_1, need_2 = ctx.needs_input_grad[:3]
+        if torch.is_grad_enabled() or not (_plain(x) and _plain(w1) and _plain(w2) and _plain(a1) and _plain(logits) and x.data_ptr() % 16 == 0
+                                           and a1.data_ptr() % 16 == 0 and labels.is_contiguous()):
+            # to be differentiated itself, or the saved tensors came back from hooks as something else
+            wanted = [t for t, need in ((x, need_x), (w1, need_1), (w2, need_2)) if need]
+            with torch.enable_grad():
+                inner = iter(torch.autograd.grad(_gcn2_composed(ctx.h, x, w1, w2, labels, ctx.naive, None), wanted, g, create_graph=torch.is_grad_enabled()))
+            return (*(next(inner) if need else None for need in (need_x, need_1, need_2)), None, None, None)
+        back = ctx.h.naive_backward if ctx.naive else ctx.h.backward
+        g_z2 = back(binding.softmax_loss_grad(logits, labels, counted, g.contiguous()), "gcn")
+        g_w2 = binding.weight_grad(a1, g_z2, relu=True) if need_2 else None
+        if not (need_x or need_1):
+            return None, None, g_w2, None, None, None
+        g_z1 = back(binding.narrow_product(g_z2, w2, transposed=True, mask=a1), "gcn")
+        g_w1 = binding.weight_grad(x, g_z1) if need_1 else None
+        g_x = binding.narrow_product(g_z1, w1, transposed=True) if need_x else None
+        return g_x, g_w1, g_w2, None, None, None
+
+
+def _narrow(d, k):
+    """What hag_narrow_product takes both ways round, within the sizes where it and hag_weight_grad are the faster side."""
+    return d % 4 == 0 and k % 4 == 0 and 0 < d <= 256 and 0 < k <= 256
+
+
+def gcn2_loss(h, x, w1, w2, labels, naive=False, record=None):
+    """SoftMax cross-entropy of a 2-layer GCN (Section 5.3's model) on features x."""
+    if (record is None and _plain(x) and _plain(w1) and _plain(w2) and _plain_labels(labels, x) and x.data_ptr() % 16 == 0 and x.shape[1] == w1.shape[0]
+            and w1.shape[1] == w2.shape[0] and _narrow(*w1.shape) and _narrow(*w2.shape) and not torch.is_autocast_enabled()):
+        return _Gcn2Loss.apply(x, w1, w2, labels, h, naive)
+    return _gcn2_composed(h, x, w1, w2, labels, naive, record)
 
 
 def sage_pool2_loss(h, x, pool, comb, labels, naive=False, record=None):

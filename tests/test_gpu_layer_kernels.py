@@ -27,6 +27,24 @@ def test_weight_grad(B, n, d, k):
     assert bool(((B.weight_grad(x, g).double() - want).abs() <= (n + 1) * EPS * size).all())
 
 
+@pytest.mark.parametrize("n", [1, 31, 33, 128, 129, 5001])
+@pytest.mark.parametrize("d,k", [(4, 1), (16, 16), (20, 17), (64, 33), (132, 64), (256, 65), (512, 32), (1024, 7)])
+def test_narrow_product(B, n, d, k):
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    x, w, a = (torch.randn(*s, device="cuda", generator=gen) for s in ((n, d), (d, k), (n, k)))
+    a[0, 0] = float("nan")                                 # (a ReLU passes a NaN on, and its gradient)
+    for relu, mask in ((False, None), (True, None), (False, a), (True, a)):
+        z = torch.relu(x) if relu else x
+        want, size = z.double() @ w.double(), z.double().abs() @ w.double().abs()
+        if mask is not None:
+            want = torch.where(mask <= 0, 0.0, want)
+        for got in (B.narrow_product(x, w, relu=relu, mask=mask), B.narrow_product(x, w.t().contiguous(), transposed=True, relu=relu, mask=mask)):
+            assert bool(((got.double() - want).abs() <= (d + 1) * EPS * size).all())
+    g = torch.randn(n, k, device="cuda", generator=gen)
+    z = torch.relu(x).double()
+    assert bool(((B.weight_grad(x, g, relu=True).double() - z.t() @ g.double()).abs() <= (n + 1) * EPS * (z.t() @ g.double().abs())).all())
+
+
 @pytest.mark.parametrize("n", [1, 17, 1000, 40001])
 @pytest.mark.parametrize("classes", [1, 2, 16, 63, 64, 65, 256, 257, 1000])
 def test_softmax_loss(B, n, classes):
@@ -97,3 +115,38 @@ def test_products_and_loss_under_autograd(B):
         layers.product(x, w[:19])
     probabilities = torch.softmax(rnd(900, 20), 1)
     assert torch.equal(layers.softmax_loss(x, probabilities), torch.nn.functional.cross_entropy(x, probabilities))
+
+
+@pytest.mark.parametrize("naive", [False, True])
+@pytest.mark.parametrize("x_grad", [False, True])
+def test_gcn_loss_as_one_node_equals_the_composed_form(B, naive, x_grad):
+    from paper_1906_03707_amd import layers, synth
+    rowptr, col = synth.holme_kim(900, 6, 0.5, seed=5)
+    h = B.hag_search(rowptr, col, 200).upload()
+    n = rowptr.size - 1
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen)   # noqa: E731
+    data = rnd(n, 20), rnd(20, 12), rnd(12, 8)
+    labels = torch.randint(0, 8, (n,), device="cuda", generator=gen)
+    labels[::7] = -100
+    results = []
+    for form in (lambda *a: layers.gcn2_loss(*a, naive=naive), lambda *a: layers._gcn2_composed(*a, naive, None)):
+        x, w1, w2 = (t.clone().requires_grad_(k > 0 or x_grad) for k, t in enumerate(data))
+        inputs = (x, w1, w2) if x_grad else (w1, w2)
+        loss = form(h, x, w1, w2, labels)
+        plain = torch.autograd.grad(loss, inputs, retain_graph=True)
+        again = torch.autograd.grad(3 * loss, inputs)
+        loss = form(h, x, w1, w2, labels)
+        first = torch.autograd.grad(loss, inputs, create_graph=True)
+        second = torch.autograd.grad(sum((g ** 2).sum() for g in first), inputs, allow_unused=True)
+        only = torch.autograd.grad(form(h, x.detach(), w1.detach(), w2, labels), (w2,))
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t.cpu(), lambda t: t.cuda()):
+            hooked = form(h, x, w1, w2, labels)
+        results.append((loss, *plain, *again, *first, *second, *only, *torch.autograd.grad(hooked, inputs)))
+    for a, b in zip(*results):
+        assert (a is None) == (b is None) and (a is None or (a - b).norm().item() <= 1e-5 * b.norm().item())
+    with torch.no_grad():
+        assert not layers.gcn2_loss(h, *data, labels).requires_grad
+    for bad in ((data[0][:-1], *data[1:]), (data[0], data[2], data[2])):
+        with pytest.raises((ValueError, RuntimeError)):
+            layers.gcn2_loss(h, *bad, labels)

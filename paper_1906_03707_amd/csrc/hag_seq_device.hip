@@ -845,108 +845,111 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
     }
 }
 
-// Hidden sizes from 72 to 128: eight threads per path run the element-wise part, dG is staged as rows of 4 * 128 + 2 in LDS (131 KB, one
-// workgroup per compute unit) and every wavefront multiplies one 32-unit tile of W_hh^T, streamed from the L2 cache, with one half of the paths.
-__global__ __launch_bounds__(512, 2) void seq_reverse_wide_kernel(SeqRevArgs A) {
-    constexpr int ZG = 4 * 128 + 2, IT = 4;
-    // per path: the pre-activation gradients of the current step (the product's operand), then the product's result
-    // dh_prev; the running dh and dc themselves stay in the registers of the path's eight threads
-    __shared__ __align__(16) float zg[kSeqJobs * ZG];
-    __shared__ int32_t sdesc[kSeqJobs * 4];
+// Hidden sizes from 72 to 128.  A workgroup takes half a tile, 32 paths: dG is staged as rows of 4 * 128 + 2 in LDS (66 KB), so that two workgroups share
+// a compute unit and one's loads, stores and element-wise part run beside the other's products.  (With 64 paths and 131 KB a workgroup had the compute unit to
+// itself and its phases followed one another: 2.63 ms for 0.85 M cells of 128 hidden units, of which the products are 0.72 and the tape's bytes 0.75.  As halves the
+// training step of those cells takes 4.77 ms instead of 5.53.)
+// Sixteen threads per path run the element-wise part; every wavefront multiplies one 32-unit tile of W_hh^T, streamed from the L2 cache, with one half
+// of the gate rows, and the two parts are added by whoever reads dh_prev.
+constexpr int kSeqRevJobs = 32;
+__global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) {
+    constexpr int ZG = 4 * 128 + 2, IT = 8, TP = 16;       // units per thread, threads per path
+    // per path: the pre-activation gradients of the current step (the product's operand), then the two parts of the product's result
+    // dh_prev; the running dh and dc themselves stay in the registers of the path's sixteen threads
+    __shared__ __align__(16) float zg[kSeqRevJobs * ZG];
+    __shared__ int32_t sdesc[kSeqRevJobs * 4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int hidden = A.hidden, n_rt = (hidden + 31) / 32;          // 3 or 4 row tiles of the product
-    const int sj = threadIdx.x >> 3, part = threadIdx.x & 7;         // element-wise phases: 8 threads per path, all in one wavefront
-    for (int64_t ci = blockIdx.x; ci < A.n_path_tiles; ci += gridDim.x) {
-        const int64_t ct = A.reversed ? A.n_path_tiles - 1 - ci : ci;
-        if (threadIdx.x < kSeqJobs * 4) sdesc[threadIdx.x] = A.paths[ct * (kSeqJobs * 4) + threadIdx.x];
+    const int sj = threadIdx.x / TP, part = threadIdx.x % TP;        // element-wise phases: 16 threads per path, all in one wavefront
+    const int64_t n_halves = A.n_path_tiles * (kSeqJobs / kSeqRevJobs);
+    for (int64_t ci = blockIdx.x; ci < n_halves; ci += gridDim.x) {
+        const int64_t ct = A.reversed ? n_halves - 1 - ci : ci;
+        if (threadIdx.x < kSeqRevJobs * 4) sdesc[threadIdx.x] = A.paths[ct * (kSeqRevJobs * 4) + threadIdx.x];
         __syncthreads();
-        const int steps = sdesc[2];
-        const int start = sdesc[sj * 4], beg = sdesc[sj * 4 + 1], len = sdesc[sj * 4 + 2], node = sdesc[sj * 4 + 3];
-        // unit 32 * it + 8 * e + part: the eight threads of a path move 128 contiguous bytes of its gates per instruction
-        float dhv[IT][4], dcv[IT][4];
-        // the tape of a step is requested while the product of the one after it runs (one workgroup per compute unit: there are registers)
-        float4 gates[IT][4];
-        float c_now[IT][4], c_prev[IT][4];                   // c_prev is the next step's c_now
+        const int steps = sdesc[2];                        // the first path is the longest
+        // unit 16 * it + part: the sixteen threads of a path move 256 contiguous bytes of its gates per instruction
+        float dcv[IT];
+        // the tape of a step is requested while the product of the one after it runs
+        float4 gates[IT];
+        float c_now[IT], c_prev[IT];                       // c_prev is the next step's c_now
         int keep = -1;
         auto load_step = [&](int t) {
-            const size_t cell = (size_t)beg + t;
+            const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, start = sdesc[sj * 4];   // (indices are derived again in every phase: registers are short)
+            const size_t cell = (size_t)sdesc[sj * 4 + 1] + t;
             keep = A.step_out[cell];
             const float *before = t > 0 ? A.tape_c + (cell - 1) * hidden : start >= 0 ? A.c_state + (size_t)start * hidden : nullptr;
 #pragma unroll
-            for (int it = 0; it < IT; ++it)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int u = 32 * it + 8 * e + part;
-                    if (u >= hidden) continue;
-                    gates[it][e] = *reinterpret_cast<const float4 *>(A.tape_g + (cell * hidden + u) * 4);
-                    c_prev[it][e] = before ? before[u] : 0.f;
-                }
-        };
-#pragma unroll
-        for (int it = 0; it < IT; ++it)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int u = 32 * it + 8 * e + part;
-                dhv[it][e] = node >= 0 && u < hidden ? A.g_a[(size_t)node * hidden + u] : 0.f;
-                dcv[it][e] = c_prev[it][e] = 0.f;
-                gates[it][e] = make_float4(0.f, 0.f, 0.f, 0.f);
-                c_now[it][e] = len > 0 && u < hidden ? A.tape_c[((size_t)beg + len - 1) * hidden + u] : 0.f;
+            for (int it = 0; it < IT; ++it) {
+                const int u = TP * it + part;
+                if (u >= hidden) continue;
+                gates[it] = *reinterpret_cast<const float4 *>(A.tape_g + (cell * hidden + u) * 4);
+                c_prev[it] = before ? before[u] : 0.f;
             }
-        if (len > 0 && len == steps) load_step(steps - 1);
+        };
+        {
+            const int beg = sdesc[sj * 4 + 1], len = sdesc[sj * 4 + 2], node = sdesc[sj * 4 + 3];
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const int u = TP * it + part;
+                // (dh lives in the path's row, as the sum of two parts, so that it takes no registers during the products)
+                zg[sj * ZG + u] = node >= 0 && u < hidden ? A.g_a[(size_t)node * hidden + u] : 0.f;
+                zg[sj * ZG + 128 + u] = 0.f;
+                dcv[it] = c_prev[it] = 0.f;
+                gates[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+                c_now[it] = len > 0 && u < hidden ? A.tape_c[((size_t)beg + len - 1) * hidden + u] : 0.f;
+            }
+            if (len > 0 && len == steps) load_step(steps - 1);
+        }
         for (int t = steps - 1; t >= 0; --t) {
+            const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, len = sdesc[sj * 4 + 2];
             if (t < len) {
-                const size_t cell = (size_t)beg + t;
+                const size_t cell = (size_t)sdesc[sj * 4 + 1] + t;
                 if (A.pending && keep >= 0) seq_wait_pending(A, keep);
-                // the product of the step before left dh_prev of this path in its row: this step's dh.  Only this path's own
+                // the product of the step before left the parts of dh_prev of this path in its row: this step's dh.  Only this path's own
                 // lanes touch the row between the barriers, and they read all of it before any of them overwrites it below: one
                 // wavefront, whose LDS accesses take effect in program order, and the fence keeps the compiler to that order.
-                if (t + 1 < len) {
+                float dhv[IT];
 #pragma unroll
-                    for (int it = 0; it < IT; ++it)
+                for (int it = 0; it < IT; ++it) dhv[it] = zg[sj * ZG + TP * it + part] + zg[sj * ZG + 128 + TP * it + part];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (32 * it + 8 * e < hidden) dhv[it][e] = zg[sj * ZG + 32 * it + 8 * e + part];
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                }
-#pragma unroll
-                for (int it = 0; it < IT; ++it)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int u = 32 * it + 8 * e + part;
-                        if (u >= hidden) continue;
-                        if (keep >= 0) {                   // what the other users of this state sent back
-                            const float *h = A.gh + (size_t)keep * hidden + u, *c = A.gc + (size_t)keep * hidden + u;
-                            dhv[it][e] += A.pending ? __hip_atomic_load(h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *h;
-                            dcv[it][e] += A.pending ? __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *c;
-                        }
-                        const float4 g4 = gates[it][e];    // i, f, g, o
-                        const float tc = seq_tanh(c_now[it][e]);
-                        const float d_o = dhv[it][e] * tc;
-                        const float dcc = dcv[it][e] + dhv[it][e] * g4.w * (1.f - tc * tc);
-                        const float4 dg = make_float4(dcc * g4.z * g4.x * (1.f - g4.x), dcc * c_prev[it][e] * g4.y * (1.f - g4.y),
-                                                      dcc * g4.x * (1.f - g4.z * g4.z), d_o * g4.w * (1.f - g4.w));
-                        dcv[it][e] = dcc * g4.y;
-                        c_now[it][e] = c_prev[it][e];
-                        *reinterpret_cast<float4 *>(A.tape_g + (cell * hidden + u) * 4) = dg;   // kept for the weight gradients
-                        *reinterpret_cast<float2 *>(&zg[sj * ZG + u * 4]) = make_float2(dg.x, dg.y);
-                        *reinterpret_cast<float2 *>(&zg[sj * ZG + u * 4 + 2]) = make_float2(dg.z, dg.w);
+                for (int it = 0; it < IT; ++it) {
+                    const int u = TP * it + part;
+                    if (u >= hidden) continue;
+                    if (keep >= 0) {                       // what the other users of this state sent back
+                        const float *h = A.gh + (size_t)keep * hidden + u, *c = A.gc + (size_t)keep * hidden + u;
+                        dhv[it] += A.pending ? __hip_atomic_load(h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *h;
+                        dcv[it] += A.pending ? __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *c;
                     }
+                    const float4 g4 = gates[it];           // i, f, g, o
+                    const float tc = seq_tanh(c_now[it]);
+                    const float d_o = dhv[it] * tc;
+                    const float dcc = dcv[it] + dhv[it] * g4.w * (1.f - tc * tc);
+                    const float4 dg = make_float4(dcc * g4.z * g4.x * (1.f - g4.x), dcc * c_prev[it] * g4.y * (1.f - g4.y),
+                                                  dcc * g4.x * (1.f - g4.z * g4.z), d_o * g4.w * (1.f - g4.w));
+                    dcv[it] = dcc * g4.y;
+                    c_now[it] = c_prev[it];
+                    *reinterpret_cast<float4 *>(A.tape_g + (cell * hidden + u) * 4) = dg;   // kept for the weight gradients
+                    *reinterpret_cast<float2 *>(&zg[sj * ZG + u * 4]) = make_float2(dg.x, dg.y);
+                    *reinterpret_cast<float2 *>(&zg[sj * ZG + u * 4 + 2]) = make_float2(dg.z, dg.w);
+                }
             }
             if (t > 0 && t - 1 < len) load_step(t - 1);
             __syncthreads();
-            // dh_prev^T [units, paths] = W_hh^T . dG^T [4H, paths]
+            // dh_prev^T [units, paths] = W_hh^T . dG^T [4H, paths], the gate rows in two halves
             seq_acc_t acc;
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = 0.f;
             const bool has_pair = wave < 2 * n_rt;
-            const int rt = wave % n_rt, grp = wave / n_rt;
+            const int rt = wave % n_rt, half = wave / n_rt;
             if (has_pair) {
+                const int q0 = half * (hidden / 4), q1 = q0 + hidden / 4;   // groups of eight gate rows (hidden is a multiple of 8)
                 const float4 *wq = reinterpret_cast<const float4 *>(A.wqt) + (size_t)rt * (hidden / 2) * 64 + lane;
-                const float *zl = &zg[(grp * 32 + (lane & 31)) * ZG + (lane >> 5)];
-                float4 wa = wq[0];
-                for (int q = 0; q < hidden / 2; ++q) {
-                    const float4 wn = wq[(q + 1 < hidden / 2 ? q + 1 : q) * 64];
+                const float *zl = &zg[(lane & 31) * ZG + (lane >> 5)];
+                float4 wa = wq[q0 * 64];
+                for (int q = q0; q < q1; ++q) {
+                    const float4 wn = wq[(q + 1 < q1 ? q + 1 : q) * 64];
                     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.x, zl[2 * (4 * q + 0)], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.y, zl[2 * (4 * q + 1)], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.z, zl[2 * (4 * q + 2)], acc, 0, 0, 0);
@@ -956,38 +959,36 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_wide_kernel(SeqRevArgs A) 
             }
             __syncthreads();                               // every product has read the staged gradients
             if (has_pair) {
-                const int j = grp * 32 + (lane & 31);
+                const int j = lane & 31;
                 if (t < sdesc[j * 4 + 2]) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int row = rt * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-                        if (row < hidden) zg[j * ZG + row] = acc[r];
+                        if (row < hidden) zg[j * ZG + 128 * half + row] = acc[r];
                     }
                 }
             }
             __syncthreads();
         }
-        // what is left: the gradient of the state the path started from, dh beside dc in the path's row, added by whole wavefronts so
+        // what is left: the gradient of the state the path started from, dh (in two parts) beside dc in the path's row, added by whole wavefronts so
         // that an atomic instruction covers contiguous bytes
-        if (__syncthreads_or(start >= 0)) {
+        if (__syncthreads_or(sdesc[sj * 4] >= 0)) {
 #pragma unroll
             for (int it = 0; it < IT; ++it)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (32 * it + 8 * e < hidden) zg[sj * ZG + 128 + 32 * it + 8 * e + part] = dcv[it][e];
+                if (TP * it < hidden) zg[sj * ZG + 256 + TP * it + part] = dcv[it];
             __syncthreads();
-            for (int j = wave; j < kSeqJobs; j += 8) {
+            for (int j = wave; j < kSeqRevJobs; j += 8) {
                 const int from = sdesc[j * 4];
                 if (from < 0) continue;
                 for (int u = lane; u < hidden; u += 64) {
-                    __hip_atomic_fetch_add(A.gh + (size_t)from * hidden + u, zg[j * ZG + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_fetch_add(A.gc + (size_t)from * hidden + u, zg[j * ZG + 128 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(A.gh + (size_t)from * hidden + u, zg[j * ZG + u] + zg[j * ZG + 128 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(A.gc + (size_t)from * hidden + u, zg[j * ZG + 256 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
             if (A.pending) {
                 // once the wavefront has seen its atomics complete, its paths are counted off
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                const int from = lane < 8 ? sdesc[(wave + 8 * lane) * 4] : -1;
+                const int from = lane < kSeqRevJobs / 8 ? sdesc[(wave + 8 * lane) * 4] : -1;
                 if (from >= 0 && A.publish) __hip_atomic_fetch_sub(A.pending + from, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
@@ -1772,7 +1773,7 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
         r.hidden = (int32_t)hidden;
         if (r.n_path_tiles <= 0) continue;
         const int64_t cap = fused ? resident : 512;
-        hipLaunchKernelGGL(kSeqReverseVariants[rv], dim3((unsigned)std::min<int64_t>(r.n_path_tiles, cap)), dim3(512), 0, s, r);
+        hipLaunchKernelGGL(kSeqReverseVariants[rv], dim3((unsigned)std::min<int64_t>(r.n_path_tiles * (rv == 2 ? kSeqJobs / kSeqRevJobs : 1), cap)), dim3(512), 0, s, r);
         HIP_TRY(hipGetLastError());
     }
     {

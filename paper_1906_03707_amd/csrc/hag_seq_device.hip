@@ -302,10 +302,10 @@ __device__ __forceinline__ void seq_from_pieces(V &v) {
 //   halves: the pieces of a whole tile would be 96 of the 128 registers there are at four wavefronts per SIMD.
 template <int HMAX, bool TAPE>
 __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(SeqChainArgs A) {
-    constexpr bool BIG = HMAX == 128, WIDE = HMAX >= 64, C_LDS = HMAX == 64;
+    constexpr bool BIG = HMAX == 128, WIDE = HMAX >= 64, C_LDS = HMAX == 64 || TAPE;
     constexpr int KS = HMAX / 16, ZS = HMAX + 8, JG = WIDE ? 2 : 1;
     __shared__ __align__(16) uint16_t z[2][3][kSeqJobs][ZS];   // h of every path in bf16 pieces: this step's and the next step's
-    // c: in registers, except where those are too short (rows 4 banks apart: conflict-free 16-byte accesses)
+    // c: in registers, except where those are too short or the tape takes it from here (rows 4 banks apart: conflict-free 16-byte accesses)
     __shared__ __align__(16) float cs[C_LDS ? kSeqJobs : 1][HMAX + 4];
     __shared__ int32_t sdesc[kSeqJobs * 4];
     __shared__ int32_t spend[2][kSeqJobs];                 // per path: the state row that a step wrote, to be announced a step later
@@ -482,8 +482,7 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                         const float4 h4 = make_float4(h[0], h[1], h[2], h[3]), c4 = make_float4(c[0], c[1], c[2], c[3]);
                         if constexpr (C_LDS) *reinterpret_cast<float4 *>(&cs[j][unit0]) = c4;
                         else creg[g] = c4;
-                        // (the gates and h leave further down, in larger pieces)
-                        if constexpr (TAPE) st4_stream(A.tape_c + (size_t)(beg + t) * hidden + unit0, c4);
+                        // (gates, c and h leave for the tape further down, in larger pieces)
                         if (keep[g] >= 0) {                // a state that another path starts from, or some a_v
                             const size_t o = (size_t)keep[g] * hidden + unit0;
                             if (A.flags) {
@@ -524,8 +523,9 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
             }
             __syncthreads();                               // the h rows of the next step are complete, this step's have been read
             if constexpr (TAPE) {
-                // h of the step as whole rows out of the operand buffer (the three pieces add up to it exactly), which is not
-                // written again before the barrier of the next step
+                // h and c of the step as whole rows, h out of the operand buffer (the three pieces add up to it exactly).  A wavefront holds 32 bytes of
+                // c per path: written from there, they left as 64-byte requests that were half empty (6.8 GB instead of 5.9 at 3.35 M cells of 64
+                // units: 2.18 ms, now 1.59; 0.85 M cells of 128: 1.33 and 1.19).
                 const int tid = seq_opaque(threadIdx.x), j = tid / (HMAX / 8), part = tid % (HMAX / 8);
                 if (j < kSeqJobs && t < sdesc[j * 4 + 2]) {
                     const size_t cell = (size_t)(sdesc[j * 4 + 1] + t) * hidden;
@@ -541,8 +541,10 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                             h[2] += __uint_as_float(w.y << 16); h[3] += __uint_as_float(w.y & 0xffff0000u);
                         }
                         st4_stream(A.tape_h + cell + u, make_float4(h[0], h[1], h[2], h[3]));
+                        st4_stream(A.tape_c + cell + u, *reinterpret_cast<const float4 *>(&cs[j][u]));
                     }
                 }
+                __syncthreads();                           // the rows of c have been read
             }
         }
         if (on) publish((steps - 1) & 1);

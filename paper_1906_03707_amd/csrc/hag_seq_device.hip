@@ -660,31 +660,36 @@ __device__ __forceinline__ void seq_wait_pending(const SeqRevArgs &A, int keep) 
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");       // the sums are then read with device-scope loads
 }
 
+constexpr int kSeqRevJobs = 32;   // paths per workgroup of the reverse kernels above 32 hidden units: half a tile
+
 // Hidden sizes up to 64 (HMAX 32 or 64).  Lanes and wavefronts are those of the forward kernel: a lane holds (path, four units of
 // gate tile w), their running dh and dc and, per step, the sixteen dG.  The k index of dh_prev = W_hh^T dG can be taken in any order, so the
 // dG are the product's operand where they are, in the registers of the lane that made them: wavefront w multiplies the 32 gate
 // rows of its own tile and leaves its part of dh_prev for all units in LDS; after a barrier every lane adds the parts
-// for its own units, in a fixed order.  The gates of the next step are requested before the product, and with one workgroup per compute
-// unit (139 KB of LDS, 256 registers) about 80 KB of tape are in flight: the kernel is bound by the tape (read gates and c, write dG: 36 H bytes
-// per cell).
+// for its own units, in a fixed order.  The gates of the next step are requested before the product.  Above 32 units a
+// workgroup takes half a tile (70 KB of LDS, 128 registers), so that two share a compute unit and one's tape accesses run beside the other's products: the kernel is bound
+// by the tape (read gates and c, write dG: 36 H bytes per cell).  3.35 M cells of 64 units: 2.43 ms with 64 paths and one workgroup per compute unit, 2.30 with halves.
 template <int HMAX>
-__global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
-    constexpr int MT = HMAX / 32, JG = HMAX / 32, NT = HMAX / 8, RS = HMAX + 4;
-    __shared__ __align__(16) float red[NT][kSeqJobs][RS];
-    __shared__ int32_t sdesc[kSeqJobs * 4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+__global__ __launch_bounds__(512, 4) void seq_reverse_kernel(SeqRevArgs A) {
+    constexpr int MT = HMAX / 32, JG = 1, NT = HMAX / 8, RS = HMAX + 4, RJ = HMAX == 64 ? kSeqRevJobs : kSeqJobs;
+    __shared__ __align__(16) float red[NT][RJ][RS];
+    __shared__ int32_t sdesc[RJ * 4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int hidden = A.hidden, n_tiles = hidden / 8, m_tiles = (hidden + 31) / 32;
     const int tile = HMAX == 64 ? wave : (wave & 3), group0 = HMAX == 64 ? 0 : (wave >> 2);
     const bool on = tile < n_tiles;
-    const int unit0 = tile * 8 + half * 4;
     float wt[MT][16];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) wt[mt][e] = on && mt < m_tiles ? A.wqt[(((size_t)tile * m_tiles + mt) * 16 + e) * 64 + lane] : 0.f;
-    for (int64_t ci = blockIdx.x; ci < A.n_path_tiles; ci += gridDim.x) {
-        const int64_t ct = A.reversed ? A.n_path_tiles - 1 - ci : ci;
-        if (threadIdx.x < kSeqJobs * 4) sdesc[threadIdx.x] = A.paths[ct * (kSeqJobs * 4) + threadIdx.x];
+    const int64_t n_parts = A.n_path_tiles * (kSeqJobs / RJ);
+    for (int64_t ci = blockIdx.x; ci < n_parts; ci += gridDim.x) {
+        const int64_t ct = A.reversed ? n_parts - 1 - ci : ci;
+        {
+            const int tid = seq_opaque(threadIdx.x);
+            if (tid < RJ * 4) sdesc[tid] = A.paths[ct * (RJ * 4) + tid];
+        }
         __syncthreads();
         const int steps = sdesc[2];
         float dh[JG][4], dc[JG][4];
@@ -713,6 +718,7 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
             }
         };
         auto sum_parts = [&](int g, int j) {
+            const int unit0 = tile * 8 + ((seq_opaque(threadIdx.x) >> 5) & 1) * 4;
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int w = 0; w < NT; ++w) {
@@ -724,6 +730,7 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
         };
 #pragma unroll
         for (int g = 0; g < JG; ++g) {
+            const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4;
             const int j = (group0 + g) * 32 + (lane & 31), len = sdesc[j * 4 + 2], node = sdesc[j * 4 + 3];
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
             if (on && node >= 0) v = *reinterpret_cast<const float4 *>(A.g_a + (size_t)node * hidden + unit0);
@@ -734,12 +741,13 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
             keep[g] = -1;
             c_now[g] = c_prev[g] = make_float4(0.f, 0.f, 0.f, 0.f);
             if (on && len > 0) c_now[g] = *reinterpret_cast<const float4 *>(A.tape_c + ((size_t)sdesc[j * 4 + 1] + len - 1) * hidden + unit0);
-            if (on) load_step(g, steps - 1);
+            if (on && steps > 0) load_step(g, steps - 1);   // (a half that holds nothing but padding has no step)
         }
         for (int t = steps - 1; t >= 0; --t) {
 #pragma unroll
             for (int g = 0; g < JG; ++g) {
                 if (!on) break;                            // (wavefronts beyond the hidden size only keep the barriers)
+                const int lane = seq_opaque(threadIdx.x) & 63, half = lane >> 5, unit0 = tile * 8 + half * 4;
                 const int j = (group0 + g) * 32 + (lane & 31), len = sdesc[j * 4 + 2];
                 seq_from_pieces(gates[g]);
                 if (t < len) {
@@ -785,22 +793,19 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
             if (on) {
 #pragma unroll
                 for (int g = 0; g < JG; ++g) {
-                    seq_acc_t acc[MT];
+                    const int l = seq_opaque(threadIdx.x) & 63, half = l >> 5, j = (group0 + g) * 32 + (l & 31);
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
+                    for (int mt = 0; mt < MT; ++mt) {
+                        seq_acc_t acc;
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+                        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-                    for (int e = 0; e < 16; ++e)
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(wt[mt][e], dg[g][e], acc[mt], 0, 0, 0);
-                    const int j = (group0 + g) * 32 + (lane & 31);
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
+                        for (int e = 0; e < 16; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wt[mt][e], dg[g][e], acc, 0, 0, 0);
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
-                            *reinterpret_cast<float4 *>(&red[tile][j][mt * 32 + 8 * q + 4 * half]) =
-                                make_float4(acc[mt][4 * q], acc[mt][4 * q + 1], acc[mt][4 * q + 2], acc[mt][4 * q + 3]);
+                            *reinterpret_cast<float4 *>(&red[tile][j][mt * 32 + 8 * q + 4 * half]) = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+                        __builtin_amdgcn_sched_barrier(0);   // (one accumulator at a time: registers are short)
+                    }
                 }
             }
             __syncthreads();                               // the parts of dh_prev are complete
@@ -809,8 +814,9 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
         // covers a row of 256 contiguous bytes (issued by the lanes that hold the values, four bytes of each of 64 rows per
         // instruction, they took most of the kernel's time: the memory side does about 17 such requests per ns).
         bool any = false;
-        if (threadIdx.x < kSeqJobs) any = sdesc[threadIdx.x * 4] >= 0;
+        if (threadIdx.x < RJ) any = sdesc[threadIdx.x * 4] >= 0;
         if (__syncthreads_or(any)) {
+            const int tid = seq_opaque(threadIdx.x), lane = tid & 63, wave = tid >> 6, unit0 = tile * 8 + (lane >> 5) * 4;
             float4 rows[JG];
 #pragma unroll
             for (int g = 0; g < JG; ++g) {
@@ -828,7 +834,7 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
                 }
             }
             __syncthreads();
-            for (int j = wave; j < kSeqJobs; j += 8) {
+            for (int j = wave; j < RJ; j += 8) {
                 const int start = sdesc[j * 4];
                 if (start < 0) continue;                   // (the same for the whole wavefront; an empty path starts nowhere)
                 if (lane < hidden) {
@@ -839,7 +845,7 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
             if (A.pending) {
                 // once the wavefront has seen its atomics complete, its paths are counted off
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                const int start = lane < 8 ? sdesc[(wave + 8 * lane) * 4] : -1;
+                const int start = lane < RJ / 8 ? sdesc[(wave + 8 * lane) * 4] : -1;
                 if (start >= 0 && A.publish) __hip_atomic_fetch_sub(A.pending + start, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
@@ -849,11 +855,10 @@ __global__ __launch_bounds__(512, 2) void seq_reverse_kernel(SeqRevArgs A) {
 
 // Hidden sizes from 72 to 128.  A workgroup takes half a tile, 32 paths: dG is staged as rows of 4 * 128 + 2 in LDS (66 KB), so that two workgroups share
 // a compute unit and one's loads, stores and element-wise part run beside the other's products.  (With 64 paths and 131 KB a workgroup had the compute unit to
-// itself and its phases followed one another: 2.63 ms for 0.85 M cells of 128 hidden units, of which the products are 0.72 and the tape's bytes 0.75.  As halves the
-// training step of those cells takes 4.77 ms instead of 5.53.)
+// itself and its phases followed one another: 2.63 ms for 0.85 M cells of 128 hidden units, of which the products are 0.72 and the tape's bytes 0.75; as halves
+// 1.86 ms.)
 // Sixteen threads per path run the element-wise part; every wavefront multiplies one 32-unit tile of W_hh^T, streamed from the L2 cache, with one half
 // of the gate rows, and the two parts are added by whoever reads dh_prev.
-constexpr int kSeqRevJobs = 32;
 __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) {
     constexpr int ZG = 4 * 128 + 2, IT = 8, TP = 16;       // units per thread, threads per path
     // per path: the pre-activation gradients of the current step (the product's operand), then the two parts of the product's result
@@ -1775,7 +1780,7 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
         r.hidden = (int32_t)hidden;
         if (r.n_path_tiles <= 0) continue;
         const int64_t cap = fused ? resident : 512;
-        hipLaunchKernelGGL(kSeqReverseVariants[rv], dim3((unsigned)std::min<int64_t>(r.n_path_tiles * (rv == 2 ? kSeqJobs / kSeqRevJobs : 1), cap)), dim3(512), 0, s, r);
+        hipLaunchKernelGGL(kSeqReverseVariants[rv], dim3((unsigned)std::min<int64_t>(r.n_path_tiles * (rv > 0 ? kSeqJobs / kSeqRevJobs : 1), cap)), dim3(512), 0, s, r);
         HIP_TRY(hipGetLastError());
     }
     {

@@ -48,7 +48,7 @@ static double miss_rate(const Plan &p, const std::vector<int32_t> &col, int64_t 
 
 static void add_plan(const hag_handle *h, const Plan &p, const std::vector<int32_t> &col, int w, PassCost &c) {
     if (p.items.empty()) return;
-    const int lpr = p.np > 1 ? std::min(4 << w, 32) : 4 << w;
+    const int lpr = p.np > 1 ? std::min(4 << w, p.lanes) : 4 << w;
     int64_t n_long = 0, long0 = 0;
     for (int k = 0; k < p.np; ++k) {
         const int64_t n = long_items(p, k, block_threshold(h->knobs.sub_max, p, lpr));
@@ -83,6 +83,8 @@ void estimate_pass(const hag_handle *h, bool lists, bool backward, int w, PassCo
     }
     add_plan(h, backward ? h->p_bwd_src : h->p_fwd, backward ? h->ht_dcol : h->hf_dcol, w, c);
 }
+
+void estimate_tiles(const hag_handle *h, Tiles &t, int w, PassCost &c) { add_plan(h, t.plan, t.rest_col, w, c); }
 
 // The prices below were fitted to passes timed on an MI355X: 271 pairs (HAG, plain lists) for each of sum forward, sum transposed and max, over
 // 20 graphs of 1e3 to 2.3e5 nodes and 5e4 to 1.1e8 edges (dense groups and overlapping cliques with ids in order and shuffled, community and power-law
@@ -125,6 +127,18 @@ static double dense_us(const hag_handle *h, int64_t d) {
     return 4.3 + std::cbrt((1 + std::pow(waves / 1211, 3)) * std::pow(wave, 3) + std::pow(0.153e-6 * 8. * (double)h->n * (double)d, 3));
 }
 
+// The tiles of the lists and the rest (us): what the launches and the longest unit take whatever the size, the steps, the partial rows.  Fitted to 7 community graphs of 1.2 to 26 M edges,
+// d = 16 to 512; with the margin below no case of those was slower than its lists (closest: 131072 nodes, d = 128, 598 against 687 us; left out: 40000 nodes, d = 512, 293 and 328).
+static double tiles_us(const Tiles &t, int64_t d) {
+    const int vec = dense_vec(d);
+    const double chunks = std::ceil((double)d / (16 * vec)), steps = (double)t.ptr.back(), step = vec == 1 ? 0.6e-3 : vec == 2 ? 0.9e-3 : 1.4e-3;
+    return 60. + steps * chunks * step + 2e-6 * (double)t.n_slots * (double)d + gather_us(t.cost, false, d);
+}
+bool tiles_pay(const hag_handle *h, bool backward, int64_t d) {
+    const Tiles &t = h->tiles[backward && !h->symmetric];
+    return t.on && (h->knobs.tiles > 1 || tiles_us(t, d) < 0.9 * gather_us(h->cost[1][backward], false, d));
+}
+
 // Predictions this close are taken as equal: the lists then serve graphs below 16 M edges (where the community graphs measured gained from them) and
 // the HAG larger ones (114 M edges, 14 to 17 % fewer reads: 2577 against 2704 us for a forward sum at d = 128, 10354 against 10874 us at 512, though the model has the
 // two within 8 %).  A max over a HAG carries the winners' ids along: it has to be clearly cheaper.
@@ -133,16 +147,18 @@ static bool hag_is_cheaper(const hag_handle *h, bool max, double hag, double lis
 }
 
 int cheapest_form(const hag_handle *h, const FormQuery &q) {
-    const bool max = q.max;
+    const bool max = q.max, tiles = q.tiles_allowed && q.lists_allowed && tiles_pay(h, q.backward, q.d);
     const auto list_form = [&](bool lists) {
         const size_t lds = q.component_lds[lists];
-        return lds > 0 ? component_us(h, lists, q.backward, q.d, lds) : gather_us(h->cost[lists][q.backward], max, q.d);
+        if (lds > 0) return component_us(h, lists, q.backward, q.d, lds);
+        return lists && tiles ? tiles_us(h->tiles[q.backward && !h->symmetric], q.d) : gather_us(h->cost[lists][q.backward], max, q.d);
     };
-    const bool choose = q.hag_allowed && q.lists_allowed;
+    // (without aggregation nodes the pass over the HAG is the one over the lists)
+    const bool choose = q.hag_allowed && q.lists_allowed && (h->a > 0 || tiles);
     double hag = 0, lists = 0;
     if (q.hag_allowed && (choose || q.dense_allowed)) hag = list_form(false);
     if (q.lists_allowed && (choose || q.dense_allowed)) lists = list_form(true);
-    int form = q.hag_allowed && (!choose || hag_is_cheaper(h, max, hag, lists)) ? kFormHag : kFormLists;
+    int form = q.hag_allowed && (!choose || (tiles ? h->knobs.tiles < 2 && hag < 0.95 * lists : hag_is_cheaper(h, max, hag, lists))) ? kFormHag : kFormLists;
     if (q.dense_allowed && dense_us(h, q.d) <= (form == kFormHag ? hag : lists)) form = kFormDense;
     return form;
 }

@@ -194,4 +194,147 @@ int launch_dense(DenseArgs a, int role, int max_nodes, hipStream_t s) {
     }
 }
 
+// The tiles of a list set: 128 rows of the output against the sources that at least five of them name, the same products as above with a gathered operand.  A list entry costs a
+// gather one row read, mostly out of L2; here a source's row is read once per tile, whatever the number of rows that name it.  Graphs with communities have half of
+// their entries in such (tile, source) pairs, twelve to a pair on average.  What bounds it: the rows come from beyond L2 (5 TB/s of them; neighbouring tiles go to one XCD, which
+// helps little, as a tile names a thousand sources), so a pair costs about as much as three or four list entries, and pairs of three (212 us for 64 k steps instead of 121 for 33 k) gain
+// nothing over the lists.  Whole forward sums, lists / tiles and rest, us: 131072 nodes, 26 M edges, d = 64 345 / 300, 128 687 / 598, 512 2695 / 2250; 65536 nodes, 8.4 M edges, d = 256 444 / 398,
+// 512 827 / 730, but 64 126 / 144; 65536 nodes, 3.9 M edges, d = 512 412 / 420 (where the line lies: tiles_us in hag_cost.cpp).
+// A wavefront takes a unit, at most 16 steps of 32 sources of a tile, and 16 * VEC columns; tiles of more steps are added up by the fold, like cut rows.  Shorter units would cost more partial
+// rows than they gain (8 steps: 664 us), longer ones make the chain of fp32 additions longer (error of the whole sum against 64 bits 1.17e-7 with 16 steps, 1.40e-7 with 32; the pass over a HAG 1.3e-7).
+// Four wavefronts sharing a tile's steps through LDS took 261 us where this takes 212: most tiles are a few steps long.
+template <int VEC>
+__global__ __launch_bounds__(kBlock, 2) void tile_kernel(TileArgs A) {
+    constexpr int MT = kTileRows / 16;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), n = lane & 15, q4 = lane >> 4;
+    const int xcd = blockIdx.x % kPartitions, at = blockIdx.x / kPartitions * (kBlock / kWave) + wave, fc = at % A.f_chunks;
+    const int which = A.range[xcd] + at / A.f_chunks;
+    if (which >= A.range[xcd + 1]) return;
+    const Tiles::Unit unit = A.units[which];
+    const int s0 = unit.first, s1 = unit.last;
+    const int f = fc * 16 * VEC + VEC * n;
+    const bool col_ok = f < A.d;
+    const int from = col_ok ? f : 0;
+    dense_f4_t acc[MT][VEC];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int t = 0; t < VEC; ++t) acc[m][t] = dense_f4_t{0.f, 0.f, 0.f, 0.f};
+    uint32_t largest = 0;                                  // of the scaled magnitudes
+    typedef typename DenseVec<VEC>::type vec_t;
+    union Vec { vec_t v; float e[VEC]; };
+    auto load = [&](int id) { Vec u; u.v = *reinterpret_cast<const vec_t *>(A.in + ((size_t)id * A.d + from)); return u; };
+    int ids = 0;                                           // lane l: source l % 32 of the step after next
+    Vec x[8];
+    uint2 bits = make_uint2(0, 0);                         // of the next step: byte m, bit i: source 8 * (l / 16) + i for row 16 m + l % 16
+    auto request_bits = [&](int s) { bits = *reinterpret_cast<const uint2 *>(A.bits + ((size_t)s * kTileRows + 2 * lane)); };
+    auto request_ids = [&](int s) { ids = A.ids[(size_t)s * kTileStep + (lane & 31)]; };
+    auto request_rows = [&](int i0, int i1) {
+#pragma unroll
+        for (int i = i0; i < i1; ++i) x[i] = load(__shfl(ids, 8 * q4 + i));
+    };
+    if (s0 < s1) {
+        request_ids(s0);
+        request_bits(s0);
+        request_rows(0, 8);
+        request_ids(min(s0 + 1, s1 - 1));
+    }
+    for (int s = s0; s < s1; ++s) {
+        Vec v[8];
+        dense_u4_t a[MT];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = x[i];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const uint32_t b = ((m < 4 ? bits.x : bits.y) >> (8 * (m % 4))) & 0xffu, e = b | (b << 15);   // bit 2 i below bit 2 i + 1 of the next half word
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[m][i] = (e << (14 - 2 * i)) & 0x40004000u;
+        }
+        if (s + 1 < s1) {
+            request_bits(s + 1);
+            request_rows(0, VEC == 4 ? 4 : 8);
+        }
+#pragma unroll
+        for (int t = 0; t < VEC; ++t) {
+            dense_u4_t p[3];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float lo = kDenseScale * v[2 * i].e[t], hi = kDenseScale * v[2 * i + 1].e[t];
+                const uint32_t ul = __float_as_uint(lo) & 0x7fffffffu, uh = __float_as_uint(hi) & 0x7fffffffu;
+                largest = max(largest, max(ul, uh));
+                uint32_t p0, p1, p2;
+                dense_split2(lo, hi, p0, p1, p2);
+                p[0][i] = p0; p[1][i] = p1; p[2][i] = p2;
+            }
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const dense_b8_t w = __builtin_bit_cast(dense_b8_t, a[m]);
+#pragma unroll
+                for (int k = 2; k >= 0; --k)
+                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, __builtin_bit_cast(dense_b8_t, p[k]), acc[m][t], 0, 0, 0);
+            }
+            if (t == VEC / 2 && s + 1 < s1) {              // (half of the wide rows once half of these are used up: registers are short)
+                if (VEC == 4) request_rows(4, 8);
+                request_ids(min(s + 2, s1 - 1));
+            }
+        }
+    }
+    // 2^118 as in the dense kernel, and room for sums of 2^19 sources: otherwise this wavefront's sources are added one by one
+    const bool plain = __any(largest > 0x71000000u);
+    int again = threadIdx.x;                               // (what the loop above does not need is derived again: registers are short)
+    asm volatile("" : "+v"(again));
+    const int q4_out = (again >> 4) & 3, f_out = fc * 16 * VEC + VEC * (again & 15);
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int t = 0; t < VEC; ++t) acc[m][t][r] *= 0.5f / kDenseScale;
+            if (plain) {
+                Vec y;
+#pragma unroll
+                for (int t = 0; t < VEC; ++t) y.e[t] = 0.f;
+                for (int s = s0; s < s1; ++s)
+                    for (int k = 0; k < kTileStep; ++k) {
+                        const uint32_t w = A.bits[(size_t)s * kTileRows + 2 * (k / 8 * 16 + 4 * q4_out + r) + m / 4];
+                        if (!((w >> (8 * (m % 4) + k % 8)) & 1)) continue;
+                        const Vec z = load(A.ids[(size_t)s * kTileStep + k]);
+#pragma unroll
+                        for (int t = 0; t < VEC; ++t) y.e[t] += z.e[t];
+                    }
+#pragma unroll
+                for (int t = 0; t < VEC; ++t) acc[m][t][r] = y.e[t];
+            }
+        }
+    if (f_out >= A.d) return;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * m + 4 * q4_out + r, node = A.rows[(size_t)unit.tile * kTileRows + row];
+            if (node < 0) continue;
+            float *out = unit.slot < 0 ? A.out + (size_t)node * A.d : A.part + ((size_t)unit.slot + (size_t)row * unit.parts) * A.d;
+            Vec y;
+#pragma unroll
+            for (int t = 0; t < VEC; ++t) y.e[t] = acc[m][t][r];
+            *reinterpret_cast<vec_t *>(out + f_out) = y.v;
+        }
+}
+
+int launch_tiles(TileArgs a, hipStream_t s) {
+    const int vec = dense_vec(a.d);
+    a.f_chunks = (a.d + 16 * vec - 1) / (16 * vec);
+    const int64_t per = kBlock / kWave, blocks = ((int64_t)a.longest_range * a.f_chunks + per - 1) / per * kPartitions;
+    if (blocks <= 0) return HAG_OK;
+    if (blocks > 0x7fffffffLL) { set_error("launch too large"); return HAG_EINVAL; }
+    const dim3 grid((unsigned)blocks), block(kBlock);
+    switch (vec) {
+        case 1: hipLaunchKernelGGL(tile_kernel<1>, grid, block, 0, s, a); break;
+        case 2: hipLaunchKernelGGL(tile_kernel<2>, grid, block, 0, s, a); break;
+        default: hipLaunchKernelGGL(tile_kernel<4>, grid, block, 0, s, a); break;
+    }
+    HIP_TRY(hipGetLastError());
+    return HAG_OK;
+}
+
 }  // namespace hag

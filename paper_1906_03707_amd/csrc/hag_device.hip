@@ -141,6 +141,16 @@ static size_t scaled_bytes(const hag_handle *h, hag_op_t op, int64_t d) {
     return saved > 1.1 * cost ? align_up((size_t)h->n * (size_t)d * 4) : 0;
 }
 
+// Partial rows of the sums that run as tiles and a rest, beside what the other forms need (so that a caller without room for them is served over the lists as ever).
+// Only sizes decide, none of the handle's options: what a caller was told stays enough.
+static size_t tiles_bytes(const hag_handle *h, hag_op_t op, hag_dtype_t dt, int64_t d) {
+    int64_t rows = 0;
+    if (dt == HAG_F32 && op != HAG_MAX)
+        for (const bool backward : {false, true})
+            if (tiles_pay(h, backward, d)) rows = std::max(rows, h->tiles[backward && !h->symmetric].part_rows());
+    return align_up((size_t)rows * (size_t)d * 4);
+}
+
 // Whether a pass over `plans` (its phases in execution order) can run as one launch: a small
 // HAG whose launches are short against the gaps between them, no row cut into pieces (the fold
 // of partial rows would be one more phase per launch), feature columns in one chunk.
@@ -171,7 +181,7 @@ static int run_fused(const hag_handle *h, const std::vector<const Plan *> &plans
         ph.items = p.d_items;
         ph.col = cols[k];
         ph.n_items = (int64_t)p.items.size();
-        ph.n_block = long_items(p, 0, block_threshold(h->knobs.sub_max, p, gather_lpr(base.d, p.np)));
+        ph.n_block = long_items(p, 0, block_threshold(h->knobs.sub_max, p, gather_lpr(base.d, p.np, p.lanes)));
         const bool last = k == np - 1;
         ph.out = last ? final_out : agg_out;
         ph.out_id = last ? final_out_id : agg_out_id;
@@ -216,6 +226,7 @@ static int run_plan(const hag_handle *h, const Plan &p, const int32_t *d_col, Ga
                     hipStream_t s, uint32_t phases = HAG_PHASE_ALL) {
     a.items = p.d_items;
     a.np = p.np;
+    a.lanes = p.lanes;
     a.part_shift = p.np > 1 ? (int)(((h->knobs.part_shift % p.np) + p.np) % p.np) : 0;
     // rows of ids < split live in a matrix of `split` rows, the others in one of at most
     // n + a (aggregation rows) or max_slots (partial rows) rows
@@ -229,7 +240,7 @@ static int run_plan(const hag_handle *h, const Plan &p, const int32_t *d_col, Ga
     // A row is worth a whole workgroup when each of its 256/LPR sub-groups still gets about
     // eight neighbours, and needs one when a single sub-group would walk it for too long.
     {
-        const int64_t threshold = block_threshold(h->knobs.sub_max, p, gather_lpr(a.d, p.np));
+        const int64_t threshold = block_threshold(h->knobs.sub_max, p, gather_lpr(a.d, p.np, p.lanes));
         for (int k = 0; k < p.np; ++k) {
             a.seg[k].begin = p.part_begin[k];
             a.seg[k].n_items = p.part_begin[k + 1] - p.part_begin[k];
@@ -398,6 +409,45 @@ static PassPlans hag_pass(const hag_handle *h, bool backward) {
     return p;
 }
 
+// Whether sums over the input graph's lists may run as tiles and a rest (see Tiles); whether they do is a matter of cost (tiles_pay).
+static bool tiles_apply(const hag_handle *h, bool backward, hag_op_t op, hag_dtype_t dt, uint32_t phases) {
+    return h->tiles[backward && !h->symmetric].on && dt == HAG_F32 && op != HAG_MAX && phases == HAG_PHASE_ALL && !h->knobs.list_forms;
+}
+
+// A sum over the input graph's lists: what the tiles hold into `a.out`, then the other entries' gather, which adds it.
+static int run_tiles(const hag_handle *h, bool backward, GatherArgs<float> a, void *part, hipStream_t s) {
+    Workspace w;
+    w.part = (char *)part;
+    const Tiles &t = h->tiles[backward && !h->symmetric];
+    TileArgs ta{};
+    ta.rows = t.d_rows;
+    ta.units = t.d_units;
+    ta.ids = t.d_ids;
+    ta.bits = t.d_bits;
+    ta.in = a.src_lo;
+    ta.out = a.out;
+    ta.part = (float *)w.part;
+    ta.d = a.d;
+    ta.longest_range = t.longest_range;
+    for (int k = 0; k <= kPartitions; ++k) ta.range[k] = t.range[k];
+    if (int rc = launch_tiles(ta, s)) return rc;
+    if (!t.fold.empty()) {
+        GatherArgs<float> c{};
+        c.items = t.d_fold;
+        c.np = 1;
+        c.seg[0].n_items = (int64_t)t.fold.size();
+        c.col = h->d_slot_ids;
+        c.src_hi = (const float *)w.part;
+        c.stream_hi = 1;
+        c.out = a.out;
+        c.d = a.d;
+        c.streams = several_streams((double)t.n_slots, (double)t.fold.size(), false) ? 1 : 0;
+        if (int rc = launch_gather<float, R_SUM, G_FOLD>(c, s)) return rc;
+    }
+    a.add = a.out;
+    return backward ? run_plan<float, R_SUM, G_NAIVE_BWD>(h, t.plan, t.d_rest_col, a, w, s) : run_plan<float, R_SUM, G_NAIVE_FWD>(h, t.plan, t.d_rest_col, a, w, s);
+}
+
 // The way a pass takes (HAG_ROUTE_*): the one place where it is decided, from sizes and knobs alone.  The pass over the HAG, the pass over the input
 // graph's own lists and, for a batch of small graphs, the dense products aggregate the same; a whole pass takes the one expected to be fastest (see hag_cost.cpp).
 static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases) {
@@ -409,7 +459,13 @@ static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op,
     q.max = op == HAG_MAX;
     q.backward = backward;
     q.hag_allowed = !naive;
-    q.lists_allowed = naive || (h->a > 0 && h->knobs.route && !h->knobs.list_forms && !one_launch);
+    q.tiles_allowed = tiles_apply(h, backward, op, dt, phases) && on_lists.total == 0 && !one_launch;
+    if (!naive) {
+        // a HAG that saves most of the row reads is taken as it is
+        const double hag_reads = h->cost[0][backward].reads[0] + h->cost[0][backward].reads[1], list_reads = h->cost[1][backward].reads[0] + h->cost[1][backward].reads[1];
+        q.tiles_allowed = q.tiles_allowed && h->knobs.route && hag_reads > 0.5 * list_reads;
+    }
+    q.lists_allowed = naive || ((h->a > 0 || q.tiles_allowed) && h->knobs.route && !h->knobs.list_forms && !one_launch);
     q.dense_allowed = h->comp.dense && dt == HAG_F32 && op != HAG_MAX && !h->knobs.list_forms;
     q.d = d;
     q.component_lds[0] = on_hag.total * on_hag.parts;     // (priced with its columns in one piece: the pieces are a knob for experiments)
@@ -424,7 +480,7 @@ static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op,
 
 template <typename T, int RED>
 static int forward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d, const T *x, T *y, int32_t *argmax,
-                        void *ws, hipStream_t s, uint32_t phases) {
+                        void *ws, hipStream_t s, uint32_t phases, bool tiles) {
     const int route = route_of(h, naive, false, op, std::is_same<T, float>::value ? HAG_F32 : HAG_I32, d, phases);
     if constexpr (std::is_same<T, float>::value && RED == R_SUM)
         if (route == HAG_ROUTE_DENSE) return run_dense(h, naive, false, op, d, x, y, s);
@@ -485,6 +541,9 @@ static int forward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d,
     a.self = op == HAG_GCN ? x : nullptr;
     a.d = (int32_t)d;
     if (!(phases & (HAG_PHASE_GATHER | HAG_PHASE_FOLD))) return HAG_OK;
+    if constexpr (std::is_same<T, float>::value && RED == R_SUM)
+        if (naive && tiles && ws && tiles_apply(h, false, op, HAG_F32, phases) && tiles_pay(h, false, d))
+            return run_tiles(h, false, a, (char *)ws + w.total + scaled_bytes(h, op, d), s);
     if (naive) return run_plan<T, RED, G_NAIVE_FWD>(h, h->p_naive_fwd, h->d_gcol, a, w, s, phases);
     return run_plan<T, RED, G_HAG_FWD>(h, h->p_fwd, h->d_hcol, a, w, s, phases);
 }
@@ -554,6 +613,9 @@ static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d
         a.out_off = 0;
         if (op == HAG_GCN) { a.self = gy; a.self_scale = h->d_inv_deg1; }
         if (!(phases & (HAG_PHASE_GATHER | HAG_PHASE_FOLD))) return HAG_OK;
+        if constexpr (std::is_same<T, float>::value)
+            if (ws && !a.in_scale && tiles_apply(h, true, op, HAG_F32, phases) && tiles_pay(h, true, d))
+                return run_tiles(h, true, a, (char *)ws + w.total + scaled_bytes(h, op, d), s);
         return run_plan<T, R_SUM, G_NAIVE_BWD>(h, h->p_naive_bwd, h->d_gtcol, a, w, s, phases);
     }
     if (route == HAG_ROUTE_ONE_LAUNCH) {
@@ -625,7 +687,7 @@ int hag_upload(hag_t *h, void *stream) {
         void *unused = nullptr;
         if ((rc = scratch_address(h->device, &unused))) return rc;
     }
-    std::vector<int32_t> slots((size_t)h->max_slots);
+    std::vector<int32_t> slots((size_t)std::max({h->max_slots, h->tiles[0].part_rows(), h->tiles[1].part_rows()}));
     for (size_t i = 0; i < slots.size(); ++i) slots[i] = (int32_t)i;
     if ((rc = upload_array(h, h->left, &h->d_left, s))) goto bad;
     if ((rc = upload_array(h, h->right, &h->d_right, s))) goto bad;
@@ -652,6 +714,16 @@ int hag_upload(hag_t *h, void *stream) {
     if ((rc = upload_plan(h, h->p_naive_fwd, s))) goto bad;
     if ((rc = upload_plan(h, h->p_naive_bwd, s))) goto bad;
     if ((rc = upload_array(h, h->p_naive_bwd.slot_row, &h->p_naive_bwd.d_slot_row, s))) goto bad;
+    for (Tiles &t : h->tiles)
+        if (t.on) {
+            if ((rc = upload_array(h, t.rows, &t.d_rows, s))) goto bad;
+            if ((rc = upload_array(h, t.units, &t.d_units, s))) goto bad;
+            if ((rc = upload_array(h, t.fold, &t.d_fold, s))) goto bad;
+            if ((rc = upload_array(h, t.ids, &t.d_ids, s))) goto bad;
+            if ((rc = upload_array(h, t.bits, &t.d_bits, s))) goto bad;
+            if ((rc = upload_array(h, t.rest_col, &t.d_rest_col, s))) goto bad;
+            if ((rc = upload_plan(h, t.plan, s))) goto bad;
+        }
     if (h->comp.enabled) {
         Components &c = h->comp;
         if ((rc = upload_array(h, c.meta, &c.d_meta, s))) goto bad;
@@ -671,7 +743,9 @@ int hag_upload(hag_t *h, void *stream) {
         if (e != hipSuccess) { rc = hip_fail(e, "hipStreamSynchronize"); goto bad; }
     }
     h->uploaded = true;
-    for (auto *v : {&h->hf_dcol, &h->ht_dcol, &h->g_dcol, &h->gt_dcol}) std::vector<int32_t>().swap(*v);
+    for (auto *v : {&h->hf_dcol, &h->ht_dcol, &h->g_dcol, &h->gt_dcol, &h->tiles[0].ids, &h->tiles[1].ids, &h->tiles[0].rest_col, &h->tiles[1].rest_col})
+        std::vector<int32_t>().swap(*v);
+    for (Tiles &t : h->tiles) std::vector<uint32_t>().swap(t.bits);
     return HAG_OK;
 bad:
     (void)hipStreamSynchronize(s);
@@ -682,13 +756,13 @@ bad:
 // what a pass over lists or a HAG needs; the transposed pass of max can do with none (it then adds with atomics)
 static size_t pass_bytes(const hag_t *h, hag_op_t op, int64_t d) { return !h || d <= 0 ? 0 : carve(h, op, d, nullptr).total; }
 
-size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t, int64_t d) {
+size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d) {
     if (!h || d <= 0) return 0;
-    return std::max(pass_bytes(h, op, d) + scaled_bytes(h, op, d), op == HAG_MAX ? max_scatter_bytes(h->n, d) : 0);
+    return std::max(pass_bytes(h, op, d) + scaled_bytes(h, op, d) + tiles_bytes(h, op, dt, d), op == HAG_MAX ? max_scatter_bytes(h->n, d) : 0);
 }
 
 static int forward_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, const void *x, void *y,
-                         int32_t *argmax, void *ws, void *stream, uint32_t phases) {
+                         int32_t *argmax, void *ws, void *stream, uint32_t phases, bool tiles = true) {
     int rc = check_common(h, op, dt, d, x, y, ws, pass_bytes(h, op, d) > 0);
     if (rc) return rc;
     if (op == HAG_MAX && !argmax && h->n > 0) { set_error("argmax is required for max"); return HAG_EINVAL; }
@@ -696,11 +770,11 @@ static int forward_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt
     if (x == y && h->n > 0) { set_error("x and y must not alias"); return HAG_EINVAL; }
     hipStream_t s = (hipStream_t)stream;
     if (dt == HAG_F32) {
-        if (op == HAG_MAX) return forward_impl<float, R_MAX>(h, naive, op, d, (const float *)x, (float *)y, argmax, ws, s, phases);
-        return forward_impl<float, R_SUM>(h, naive, op, d, (const float *)x, (float *)y, argmax, ws, s, phases);
+        if (op == HAG_MAX) return forward_impl<float, R_MAX>(h, naive, op, d, (const float *)x, (float *)y, argmax, ws, s, phases, tiles);
+        return forward_impl<float, R_SUM>(h, naive, op, d, (const float *)x, (float *)y, argmax, ws, s, phases, tiles);
     }
-    if (op == HAG_MAX) return forward_impl<int32_t, R_MAX>(h, naive, op, d, (const int32_t *)x, (int32_t *)y, argmax, ws, s, phases);
-    return forward_impl<int32_t, R_SUM>(h, naive, op, d, (const int32_t *)x, (int32_t *)y, argmax, ws, s, phases);
+    if (op == HAG_MAX) return forward_impl<int32_t, R_MAX>(h, naive, op, d, (const int32_t *)x, (int32_t *)y, argmax, ws, s, phases, tiles);
+    return forward_impl<int32_t, R_SUM>(h, naive, op, d, (const int32_t *)x, (int32_t *)y, argmax, ws, s, phases, tiles);
 }
 
 static int backward_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, const void *gy,
@@ -733,7 +807,8 @@ int hag_forward_static_scratch(const hag_t *h, hag_op_t op, hag_dtype_t dt, int6
     // the address was looked up by hag_upload on the handle's device; no runtime query here
     void *ws = (h->device >= 0 && h->device < kMaxDevices) ? g_scratch_ptr[h->device] : nullptr;
     if (!ws) { set_error("static scratch of the handle's device was not set up"); return HAG_ESTATE; }
-    return forward_entry(h, false, op, dt, d, x, y, argmax, ws, stream, HAG_PHASE_ALL);
+    // (no tiles where their partial rows do not fit as well)
+    return forward_entry(h, false, op, dt, d, x, y, argmax, ws, stream, HAG_PHASE_ALL, hag_workspace_bytes(h, op, dt, d) <= (size_t)HAG_STATIC_SCRATCH_BYTES);
 }
 static int route_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, int32_t backward) {
     if (!h) { set_error("handle is NULL"); return HAG_EINVAL; }

@@ -28,6 +28,7 @@ template <> struct V4<int32_t> { using type = int4; };
 template <typename T>
 struct GatherArgs {
     const Item *items;
+    int lanes;                // Plan::lanes
     int np;                   // 1 or kPartitions: workgroup b works on partition (b + part_shift) mod np
     int part_shift;           // 0 <= part_shift < np
     struct {
@@ -43,6 +44,7 @@ struct GatherArgs {
     T *out;                   // final rows, row (item.row - out_off)
     int32_t *out_id;          // R_MAX
     int32_t out_off;
+    const T *add;             // rows added to the final rows (may be `out`: what is stored there already), NULL: none
     T *part;                  // partial slots of split rows
     int32_t *part_id;         // R_MAX
     const float *in_scale;    // optional: multiplies rows of ids < split (mean, transposed pass)
@@ -336,6 +338,19 @@ struct DenseArgs {
     int32_t m_chunks, f_chunks;  // set by launch_dense: wavefronts per component, along its rows and its feature columns
 };
 
+// The tiles of a list set (see Tiles; hag_dense.hip).
+struct TileArgs {
+    const Tiles::Unit *units;
+    const int32_t *rows, *ids;
+    const uint32_t *bits;
+    const float *in;
+    float *out;                  // [n, d]: every row of a tile of one unit is written
+    float *part;                 // partial rows of the other tiles
+    int32_t d;
+    int32_t range[kPartitions + 1], longest_range;
+    int32_t f_chunks;            // set by launch_tiles
+};
+
 static inline int hip_fail(hipError_t e, const char *what) {
     set_error(std::string(what) + ": " + hipGetErrorString(e));
     return HAG_EHIP;
@@ -367,5 +382,6 @@ int launch_max_scatter(int64_t n, int64_t d, const T *gy, const int32_t *argmax,
 
 // role: as launch_component_kernel
 int launch_dense(DenseArgs a, int role, int max_nodes, hipStream_t s);
+int launch_tiles(TileArgs a, hipStream_t s);
 
 }  // namespace hag

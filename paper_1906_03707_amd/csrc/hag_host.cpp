@@ -601,7 +601,7 @@ static inline int source_class(int32_t id, int shift) {
 }
 
 void build_plan(const Csr &c, std::vector<int32_t> &dcol, int64_t row_begin, int64_t row_end, Plan &p,
-                bool partition, int64_t split) {
+                bool partition, int64_t split, bool rest) {
     const int class_shift = (int)std::min<int64_t>(env_i64("HAG_PART_CLASS_SHIFT", 5), 20);
     const int64_t block_max = env_i64("HAG_BLOCK_MAX", 2048);
     const int64_t part_min = env_i64("HAG_PART_MIN", 64);
@@ -615,7 +615,7 @@ void build_plan(const Csr &c, std::vector<int32_t> &dcol, int64_t row_begin, int
         }
         // ... and are long enough on average that an eighth of a row is still worth a partial row
         partition = total > 0 && in_long * 100 >= total * env_i64("HAG_PART_SHARE_PCT", 30) &&
-                    in_long >= n_long * env_i64("HAG_PART_MEAN_MIN", 128);
+                    in_long >= n_long * (rest ? 0 : env_i64("HAG_PART_MEAN_MIN", 128));
     }
     const int np = partition ? kPartitions : 1;
     std::vector<std::vector<Item>> lists(np);
@@ -624,6 +624,7 @@ void build_plan(const Csr &c, std::vector<int32_t> &dcol, int64_t row_begin, int
     p.n_slots = 0;
     p.n_reads = c.ptr[row_end] - c.ptr[row_begin];
     p.np = np;
+    p.lanes = rest ? 16 : 32;
     std::vector<int32_t> slot_row;                        // output row of every partial slot
     auto cut = [&](int part, int64_t beg, int64_t cnt, bool partial, int64_t row) {
         // appends the items of one contiguous run of entries; returns nothing, bumps n_slots
@@ -734,6 +735,111 @@ void build_plan(const Csr &c, std::vector<int32_t> &dcol, int64_t row_begin, int
         p.items.insert(p.items.end(), lists[k].begin(), lists[k].end());
         p.part_begin[k + 1] = (int64_t)p.items.size();
     }
+}
+
+// Splits the lists `c` into tiles and a rest (see Tiles); leaves t.on false where too few entries would go to the tiles.  Rows are taken in the order of
+// the bucketed schedules, (row / 4096, length): neighbouring rows share sources, and long rows of a neighbourhood share most.
+static void build_tiles(const Csr &c, int64_t n, bool part, Tiles &t) {
+    const int64_t e = (int64_t)c.col.size();
+    std::vector<int32_t> order((size_t)n);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+        if (x / 4096 != y / 4096) return x / 4096 < y / 4096;
+        return c.ptr[x + 1] - c.ptr[x] > c.ptr[y + 1] - c.ptr[y];
+    });
+    const int64_t count = (n + kTileRows - 1) / kTileRows;
+    const unsigned threads = host_threads();
+    struct Scratch { std::vector<int32_t> uses, touched; };
+    std::vector<Scratch> scratch(threads);
+    // the sources of tile k, how often each is named, into scratch (uses is all zero before and to be put back to zero after)
+    auto count_tile = [&](int64_t k, Scratch &s) {
+        if (s.uses.empty()) s.uses.assign((size_t)n, 0);
+        s.touched.clear();
+        for (int64_t i = k * kTileRows; i < std::min(n, (k + 1) * kTileRows); ++i)
+            for (int64_t j = c.ptr[order[i]]; j < c.ptr[order[i] + 1]; ++j)
+                if (s.uses[c.col[j]]++ == 0) s.touched.push_back(c.col[j]);
+    };
+    {
+        // every 16th tile tells whether it is worth while
+        std::vector<int64_t> all(threads, 0), in(threads, 0);
+        parallel_for((count + 15) / 16, threads, [&](int64_t k, unsigned th) {
+            Scratch &s = scratch[th];
+            count_tile(16 * k, s);
+            for (int32_t u : s.touched) { all[th] += s.uses[u]; if (s.uses[u] >= kTileUses) in[th] += s.uses[u]; s.uses[u] = 0; }
+        });
+        const int64_t a = std::accumulate(all.begin(), all.end(), (int64_t)0), b = std::accumulate(in.begin(), in.end(), (int64_t)0);
+        if (b * 100 < a * env_i64("HAG_TILES_SHARE_PCT", 30)) return;
+    }
+    std::vector<std::vector<int32_t>> ids((size_t)count);
+    std::vector<std::vector<uint32_t>> bits((size_t)count);
+    Csr rest;
+    std::vector<int64_t> rest_len((size_t)n, 0);
+    std::vector<int32_t> moved((size_t)e);                // the entries of each row that stay, at the row's place
+    parallel_for(count, threads, [&](int64_t k, unsigned th) {
+        Scratch &s = scratch[th];
+        count_tile(k, s);
+        std::vector<int32_t> &id = ids[k];
+        for (int32_t u : s.touched) { if (s.uses[u] >= kTileUses) id.push_back(u); s.uses[u] = 0; }
+        std::sort(id.begin(), id.end());
+        for (size_t i = 0; i < id.size(); ++i) s.uses[id[i]] = (int32_t)i + 1;
+        const size_t steps = (id.size() + kTileStep - 1) / kTileStep;
+        bits[k].assign(steps * kTileRows, 0);
+        for (int64_t i = k * kTileRows; i < std::min(n, (k + 1) * kTileRows); ++i) {
+            const int32_t r = order[i];
+            int64_t stay = 0;
+            for (int64_t j = c.ptr[r]; j < c.ptr[r + 1]; ++j) {
+                const int32_t at = s.uses[c.col[j]] - 1;
+                if (at >= 0) {
+                    const int64_t row = i - k * kTileRows, m = row / 16, source = at % kTileStep, lane = source / 8 * 16 + row % 16;
+                    bits[k][(size_t)(at / kTileStep * kTileRows + 2 * lane + m / 4)] |= 1u << (8 * (m % 4) + source % 8);
+                } else moved[(size_t)(c.ptr[r] + stay++)] = c.col[j];
+            }
+            rest_len[r] = stay;
+        }
+        for (int32_t u : id) s.uses[u] = 0;
+        while (!id.empty() && id.size() % kTileStep) id.push_back(id.back());
+    });
+    t.count = (int32_t)count;
+    t.rows.assign((size_t)count * kTileRows, -1);
+    std::copy(order.begin(), order.end(), t.rows.begin());
+    t.ptr.assign((size_t)count + 1, 0);
+    int64_t steps = 0;
+    for (int64_t k = 0; k < count; ++k) { steps += (int64_t)ids[k].size() / kTileStep; t.ptr[(size_t)k + 1] = (int32_t)steps; }
+    if (steps * kTileRows >= (int64_t)INT32_MAX) { t = Tiles{}; return; }
+    t.ids.resize((size_t)steps * kTileStep);
+    t.bits.resize((size_t)steps * kTileRows);
+    parallel_for(count, threads, [&](int64_t k, unsigned) {
+        std::copy(ids[k].begin(), ids[k].end(), t.ids.begin() + (int64_t)t.ptr[k] * kTileStep);
+        std::copy(bits[k].begin(), bits[k].end(), t.bits.begin() + (int64_t)t.ptr[k] * kTileRows);
+    });
+    for (int64_t k = 0; k < count; ++k) {
+        const int32_t first = t.ptr[k], all = t.ptr[(size_t)k + 1] - first, parts = std::max((all + kTileSteps - 1) / kTileSteps, 1);
+        const int32_t slot = parts > 1 ? (int32_t)t.n_slots : -1;
+        for (int32_t p = 0; p < parts; ++p)
+            t.units.push_back(Tiles::Unit{(int32_t)k, first + (int32_t)((int64_t)all * p / parts), first + (int32_t)((int64_t)all * (p + 1) / parts), slot < 0 ? -1 : slot + p, parts, {0, 0, 0}});
+        if (parts == 1) continue;
+        for (int64_t r = 0; r < kTileRows; ++r)
+            if (t.rows[(size_t)(k * kTileRows + r)] >= 0) t.fold.push_back(Item{slot + r * parts, parts, t.rows[(size_t)(k * kTileRows + r)]});
+        t.n_slots += (int64_t)kTileRows * parts;
+    }
+    const int64_t n_units = (int64_t)t.units.size();
+    for (int64_t p = 0, k = 0; p <= kPartitions; ++p) {    // (a unit costs its steps and its result)
+        while (k < n_units && (t.units[k].first + 8 * k) * kPartitions < (steps + 8 * n_units) * p) ++k;
+        t.range[p] = (int32_t)(p == kPartitions ? n_units : k);
+    }
+    for (int p = 0; p < kPartitions; ++p)                  // long units first, neighbours together
+        std::stable_sort(t.units.begin() + t.range[p], t.units.begin() + t.range[p + 1], [](const Tiles::Unit &x, const Tiles::Unit &y) { return (x.last - x.first) / 8 > (y.last - y.first) / 8; });
+    for (int p = 0; p < kPartitions; ++p) t.longest_range = std::max(t.longest_range, t.range[p + 1] - t.range[p]);
+    rest.ptr.assign((size_t)n + 1, 0);
+    for (int64_t v = 0; v < n; ++v) rest.ptr[v + 1] = rest.ptr[v] + rest_len[v];
+    rest.col.resize((size_t)rest.ptr[n]);
+    parallel_for((n + 255) / 256, threads, [&](int64_t b, unsigned) {
+        for (int64_t v = b * 256; v < std::min(n, b * 256 + 256); ++v)
+            std::copy(moved.begin() + c.ptr[v], moved.begin() + c.ptr[v] + rest_len[v], rest.col.begin() + rest.ptr[v]);
+    });
+    t.rest_col = rest.col;
+    build_plan(rest, t.rest_col, 0, n, t.plan, part, INT64_MAX, true);
+    t.on = true;
 }
 
 // Number of leading items of partition k whose length class exceeds that of `threshold` entries.
@@ -1189,12 +1295,27 @@ static int finalize_from_builder(hag_handle *h, Builder &b) {
     build_plan(h->ht, h->ht_dcol, 0, n, h->p_bwd_src, part, n);
     build_plan(h->g, h->g_dcol, 0, n, h->p_naive_fwd, part, INT64_MAX);
     build_plan(h->gt, h->gt_dcol, 0, n, h->p_naive_bwd, part, INT64_MAX);
+    for (Tiles &t : h->tiles) t = Tiles{};
+    h->symmetric = h->g.ptr == h->gt.ptr && h->g.col == h->gt.col;
+    h->knobs.tiles = (int32_t)env_i64("HAG_TILES", 1);
+    // (below half a million entries a pass takes about as long as its launches)
+    if (h->knobs.tiles > 0 && h->e >= env_i64("HAG_TILES_MIN_ENTRIES", 500000)) {
+        build_tiles(h->g, n, part, h->tiles[0]);
+        if (!h->symmetric) build_tiles(h->gt, n, part, h->tiles[1]);
+    }
     h->max_slots = std::max({h->p_fwd.n_slots, h->p_bwd_src.n_slots, h->p_naive_fwd.n_slots, h->p_naive_bwd.n_slots});
     for (auto &p : h->p_bwd_stage) h->max_slots = std::max(h->max_slots, p.n_slots);
     for (auto &p : h->p_fwd_stage) h->max_slots = std::max(h->max_slots, p.n_slots);
     build_components(h);
     for (auto &form : h->cost) for (PassCost &c : form) c = PassCost{};
-    if (a > 0 || h->comp.dense) {
+    for (Tiles &t : h->tiles)
+        if (t.on) {
+            PassCost part[kWidths];
+            parallel_for(kWidths, host_threads(), [&](int64_t w, unsigned) { estimate_tiles(h, t, (int)w, part[w]); });
+            t.cost = part[0];
+            for (int w = 0; w < kWidths; ++w) { t.cost.miss[w] = part[w].miss[w]; t.cost.fold[w] = part[w].fold[w]; }
+        }
+    if (a > 0 || h->comp.dense || h->tiles[0].on || h->tiles[1].on) {
         PassCost part[2 * 2 * kWidths];
         parallel_for(2 * 2 * kWidths, h->e > 4000000 ? host_threads() : 1, [&](int64_t i, unsigned) { estimate_pass(h, i & 1, (i >> 1) & 1, (int)(i >> 2), part[i]); });
         for (int i = 0; i < 2 * 2 * kWidths; ++i) {

@@ -43,6 +43,7 @@ struct Plan {
     std::vector<Item> combine;   // per split row: beg = first slot, cnt = #slots, row = output row
     int64_t n_slots = 0;
     int64_t n_reads = 0;         // entries of all items
+    int lanes = 32;              // lanes per row at most where the launch is cut by source (gather_lpr)
     // items of a length class up to this one are not ordered by class (see build_plan): the
     // launch may only hand whole workgroups to items of longer classes
     int min_block_class = 0;
@@ -64,7 +65,7 @@ static inline int pick_lpr(int64_t d) {
 // The same for a gather over np source classes: at most 32 lanes (128 columns) where the launch is cut by source, so that wide rows are gathered
 // in more column chunks, one after the other, each with a smaller share of the matrix per XCD
 // (forward sum over 26 M edges, 131072 nodes: d = 256 1425 -> 1341 us, d = 512 2838 -> 2676 us; narrower chunks gain nothing, the list work per byte grows).
-static inline int gather_lpr(int64_t d, int np) { return np > 1 ? std::min(pick_lpr(d), 32) : pick_lpr(d); }
+static inline int gather_lpr(int64_t d, int np, int lanes) { return np > 1 ? std::min(pick_lpr(d), lanes) : pick_lpr(d); }
 
 // Lanes that share one short item of a gather.  With `streams` at least 16, so that narrow rows (4 or 8 lanes each) are read by 4 or 2 streams of lanes
 // side by side: with one stream an item of 16 columns is a chain of one id load and four row loads per four entries, and took
@@ -146,6 +147,34 @@ struct Components {
     uint8_t *d_stage = nullptr;
 };
 
+// The lists of a graph split in two (f32 sums; tile_kernel in hag_dense.hip): the rows are taken 128 at a time, and what sources at least kTileUses rows of such a tile
+// name becomes a small dense product, every such source's row read once per tile instead of once per entry; the other entries stay lists.
+constexpr int kTileRows = 128, kTileUses = 5, kTileStep = 32;   // rows per tile; entries per (tile, source) worth a place; sources per product step
+constexpr int kTileSteps = 16;       // steps of a unit of work at most; a tile with more is several units, whose partial rows a fold adds up
+struct Tiles {
+    bool on = false;
+    int32_t count = 0;
+    std::vector<int32_t> rows;       // [count * kTileRows] node of each row, -1: none
+    std::vector<int32_t> ptr;        // [count+1] first step of each tile
+    std::vector<int32_t> ids;        // [steps * kTileStep] sources (the last step of a tile filled up with its last source)
+    // [steps * 64 lanes * 2]: eight bytes per lane l of the product, bit i of byte m: source 8 * (l / 16) + i of the step is summed into row 16 m + l % 16
+    std::vector<uint32_t> bits;
+    struct Unit { int32_t tile, first, last, slot, parts, unused[3]; };   // steps [first, last); slot: of the tile's first row, -1: the rows are final; parts: slots per row
+    std::vector<Unit> units;
+    std::vector<Item> fold;          // per row of a tile of several units: its slots
+    int64_t n_slots = 0;
+    int64_t part_rows() const { return std::max(n_slots, plan.n_slots); }   // partial rows of a pass: of the tiles, then of the rest
+    int32_t range[kPartitions + 1] = {};   // units of each XCD: runs of neighbouring tiles with about the same number of steps
+    int32_t longest_range = 0;
+    Plan plan;                       // the entries that stay lists
+    std::vector<int32_t> rest_col;
+    PassCost cost;
+    int32_t *d_rows = nullptr, *d_ids = nullptr, *d_rest_col = nullptr;
+    Unit *d_units = nullptr;
+    Item *d_fold = nullptr;
+    uint32_t *d_bits = nullptr;
+};
+
 void set_error(const std::string &msg);
 
 // Pair counting of the search on the GPU (hag_search_device.hip): a device mirror of the lists
@@ -184,6 +213,7 @@ struct hag_knobs {
     int64_t spin_limit = 0;     // HAG_SPIN_LIMIT: polls a wavefront of the one-launch pass waits for earlier phases
     bool wait_unreachable = false;      // test only: the awaited count can never be reached, so every wait gives up
     bool deterministic_max_backward = false;
+    int32_t tiles = 1;          // HAG_TILES: sums over the lists may take what neighbouring rows share as dense products (2: always, where there are tiles)
     bool list_forms = false;    // every call over its own lists
     bool route = true;          // HAG_ROUTE: whole passes may run over the input graph's lists where those are faster
     int32_t part_shift = 0;     // HAG_PART_SHIFT: workgroup b of a partitioned launch takes the sources of class (b + shift) mod 8
@@ -226,6 +256,8 @@ struct hag_handle {
     hag::PassCost cost[2][2];              // [over the HAG, over the plain lists][forward, backward]; empty if a == 0
     int64_t max_slots = 0;
     hag::Components comp;
+    hag::Tiles tiles[2];                   // of the input graph's lists [forward, backward]; a symmetric graph has one set for both
+    bool symmetric = false;
 
     // device copies
     bool uploaded = false;
@@ -242,14 +274,16 @@ namespace hag {
 // hag_host.cpp
 int finalize(hag_handle *h, uint32_t flags);  // levels, forward form, transposes, schedules, stats
 void build_plan(const Csr &c, std::vector<int32_t> &dcol, int64_t row_begin, int64_t row_end, Plan &p, bool partition,
-                int64_t split);
+                int64_t split, bool rest = false);
 int64_t long_items(const Plan &p, int k, int64_t threshold);
 int64_t block_threshold(int64_t sub_max, const Plan &p, int lpr);
 // hag_cost.cpp
 void estimate_pass(const hag_handle *h, bool lists, bool backward, int w, PassCost &c);
+void estimate_tiles(const hag_handle *h, Tiles &t, int w, PassCost &c);
+bool tiles_pay(const hag_handle *h, bool backward, int64_t d);   // a sum over the lists is expected to be faster with the tiles
 // The form of a whole pass, by expected time.  component_lds: LDS bytes of the component pass over [the HAG, the lists], 0 where it does not apply.
 enum { kFormHag = 0, kFormLists = 1, kFormDense = 2 };
-struct FormQuery { bool max, backward, hag_allowed, lists_allowed, dense_allowed; int64_t d; size_t component_lds[2]; };
+struct FormQuery { bool max, backward, hag_allowed, lists_allowed, dense_allowed, tiles_allowed; int64_t d; size_t component_lds[2]; };
 int cheapest_form(const hag_handle *h, const FormQuery &q);
 // hag_device.hip
 void free_device(hag_handle *h);

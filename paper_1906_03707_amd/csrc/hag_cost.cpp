@@ -132,7 +132,7 @@ static double dense_us(const hag_handle *h, int64_t d) {
 static double tiles_us(const Tiles &t, int64_t d) {
     const int vec = dense_vec(d);
     const double chunks = std::ceil((double)d / (16 * vec)), steps = (double)t.ptr.back(), step = vec == 1 ? 0.6e-3 : vec == 2 ? 0.9e-3 : 1.4e-3;
-    return 60. + steps * chunks * step + 2e-6 * (double)t.n_slots * (double)d + gather_us(t.cost, false, d);
+    return 50. + steps * chunks * step + 1e-6 * (double)t.n_slots * (double)d + gather_us(t.cost, false, d);
 }
 bool tiles_pay(const hag_handle *h, bool backward, int64_t d) {
     const Tiles &t = h->tiles[backward && !h->symmetric];

@@ -317,6 +317,13 @@ __global__ __launch_bounds__(kBlock, 2) void tile_kernel(TileArgs A) {
             Vec y;
 #pragma unroll
             for (int t = 0; t < VEC; ++t) y.e[t] = acc[m][t][r];
+            if (A.self && unit.slot < 0) {
+                Vec own;
+                own.v = *reinterpret_cast<const vec_t *>(A.self + (size_t)node * A.d + f_out);
+                const float scale = A.self_scale ? A.self_scale[node] : 1.f;
+#pragma unroll
+                for (int t = 0; t < VEC; ++t) y.e[t] += own.e[t] * scale;
+            }
             *reinterpret_cast<vec_t *>(out + f_out) = y.v;
         }
 }

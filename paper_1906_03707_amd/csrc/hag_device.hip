@@ -414,7 +414,7 @@ static bool tiles_apply(const hag_handle *h, bool backward, hag_op_t op, hag_dty
     return h->tiles[backward && !h->symmetric].on && dt == HAG_F32 && op != HAG_MAX && phases == HAG_PHASE_ALL && !h->knobs.list_forms;
 }
 
-// A sum over the input graph's lists: what the tiles hold into `a.out`, then the other entries' gather, which adds it.
+// A sum over the input graph's lists: what the tiles hold into `a.out`, then the other entries' gather, which finds it there as if it were the row of the node itself.
 static int run_tiles(const hag_handle *h, bool backward, GatherArgs<float> a, void *part, hipStream_t s) {
     Workspace w;
     w.part = (char *)part;
@@ -427,6 +427,8 @@ static int run_tiles(const hag_handle *h, bool backward, GatherArgs<float> a, vo
     ta.in = a.src_lo;
     ta.out = a.out;
     ta.part = (float *)w.part;
+    ta.self = a.self;
+    ta.self_scale = a.self_scale;
     ta.d = a.d;
     ta.longest_range = t.longest_range;
     for (int k = 0; k <= kPartitions; ++k) ta.range[k] = t.range[k];
@@ -440,11 +442,14 @@ static int run_tiles(const hag_handle *h, bool backward, GatherArgs<float> a, vo
         c.src_hi = (const float *)w.part;
         c.stream_hi = 1;
         c.out = a.out;
+        c.self = a.self;
+        c.self_scale = a.self_scale;
         c.d = a.d;
         c.streams = several_streams((double)t.n_slots, (double)t.fold.size(), false) ? 1 : 0;
         if (int rc = launch_gather<float, R_SUM, G_FOLD>(c, s)) return rc;
     }
-    a.add = a.out;
+    a.self = a.out;                                        // (what is there already)
+    a.self_scale = nullptr;
     return backward ? run_plan<float, R_SUM, G_NAIVE_BWD>(h, t.plan, t.d_rest_col, a, w, s) : run_plan<float, R_SUM, G_NAIVE_FWD>(h, t.plan, t.d_rest_col, a, w, s);
 }
 

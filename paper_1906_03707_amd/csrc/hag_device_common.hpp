@@ -28,7 +28,6 @@ template <> struct V4<int32_t> { using type = int4; };
 template <typename T>
 struct GatherArgs {
     const Item *items;
-    int lanes;                // Plan::lanes
     int np;                   // 1 or kPartitions: workgroup b works on partition (b + part_shift) mod np
     int part_shift;           // 0 <= part_shift < np
     struct {
@@ -44,7 +43,6 @@ struct GatherArgs {
     T *out;                   // final rows, row (item.row - out_off)
     int32_t *out_id;          // R_MAX
     int32_t out_off;
-    const T *add;             // rows added to the final rows (may be `out`: what is stored there already), NULL: none
     T *part;                  // partial slots of split rows
     int32_t *part_id;         // R_MAX
     const float *in_scale;    // optional: multiplies rows of ids < split (mean, transposed pass)
@@ -71,6 +69,7 @@ struct GatherArgs {
     int32_t wait_n;
     int32_t wait_bias;        // 0; tests make it large, so that no phase ever counts as complete
     int32_t spin_limit;
+    int lanes;                // host only: Plan::lanes
 };
 
 // One pass (all aggregation-node stages and the gather over V) as a single launch.  Workgroups
@@ -346,6 +345,7 @@ struct TileArgs {
     const float *in;
     float *out;                  // [n, d]: every row of a tile of one unit is written
     float *part;                 // partial rows of the other tiles
+    const float *self, *self_scale;   // gcn: the row of the node itself, times self_scale[node] (1 if NULL), is added to rows that are written to `out`; or NULL
     int32_t d;
     int32_t range[kPartitions + 1], longest_range;
     int32_t f_chunks;            // set by launch_tiles

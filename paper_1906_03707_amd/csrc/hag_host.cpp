@@ -743,12 +743,12 @@ static void build_tiles(const Csr &c, int64_t n, bool part, Tiles &t) {
     const int64_t e = (int64_t)c.col.size();
     std::vector<int32_t> order((size_t)n);
     std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-        if (x / 4096 != y / 4096) return x / 4096 < y / 4096;
-        return c.ptr[x + 1] - c.ptr[x] > c.ptr[y + 1] - c.ptr[y];
+    const unsigned threads = host_threads();
+    parallel_for((n + 4095) / 4096, threads, [&](int64_t b, unsigned) {
+        std::stable_sort(order.begin() + b * 4096, order.begin() + std::min(n, (b + 1) * 4096),
+                         [&](int32_t x, int32_t y) { return c.ptr[x + 1] - c.ptr[x] > c.ptr[y + 1] - c.ptr[y]; });
     });
     const int64_t count = (n + kTileRows - 1) / kTileRows;
-    const unsigned threads = host_threads();
     struct Scratch { std::vector<int32_t> uses, touched; };
     std::vector<Scratch> scratch(threads);
     // the sources of tile k, how often each is named, into scratch (uses is all zero before and to be put back to zero after)

@@ -268,7 +268,7 @@ size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64
 /* Algorithm 2 without the Update line: aggregation nodes level by level, then
  * y[v] = Aggregate over Nhat_v for every v in V.  x, y: device [n, d].
  * What is computed is the aggregate over N(v), which the HAG covers exactly (Section 3.2); hag_forward and
- * hag_backward evaluate it over the HAG, over the input graph's own lists or, for a batch of small graphs, as
+ * hag_backward evaluate it over the HAG, over the input graph's own lists (f32 sums over large ones in part as dense tiles) or, for a batch of small graphs, as
  * products with their adjacency matrices, whichever is expected to be fastest (from the handle, op, dtype and d alone: the same call
  * takes the same way every time; hag_route tells which).  Integer results and max are the same bit for bit; fp32 sums differ in the last bits, as the order of addition does.
  * argmax: device int32 [n, d], required for HAG_MAX, ignored otherwise.

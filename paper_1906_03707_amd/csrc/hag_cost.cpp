@@ -128,7 +128,8 @@ static double dense_us(const hag_handle *h, int64_t d) {
 }
 
 // The tiles of the lists and the rest (us): what the launches and the longest unit take whatever the size, the steps, the partial rows.  Fitted to 7 community graphs of 1.2 to 26 M edges,
-// d = 16 to 512; with the margin below no case of those was slower than its lists (closest: 131072 nodes, d = 128, 598 against 687 us; left out: 40000 nodes, d = 512, 293 and 328).
+// d = 16 to 512; with the margin below no case of those was
+// slower than its lists (closest: 65536 nodes, 8.4 M edges, d = 512, 753 against 822 us; left out: 30000 nodes, 4.5 M edges, d = 512, 362 and 444).
 static double tiles_us(const Tiles &t, int64_t d) {
     const int vec = dense_vec(d);
     const double chunks = std::ceil((double)d / (16 * vec)), steps = (double)t.ptr.back(), step = vec == 1 ? 0.6e-3 : vec == 2 ? 0.9e-3 : 1.4e-3;

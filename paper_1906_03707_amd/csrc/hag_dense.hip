@@ -198,10 +198,10 @@ int launch_dense(DenseArgs a, int role, int max_nodes, hipStream_t s) {
 // gather one row read, mostly out of L2; here a source's row is read once per tile, whatever the number of rows that name it.  Graphs with communities have half of
 // their entries in such (tile, source) pairs, twelve to a pair on average.  What bounds it: the rows come from beyond L2 (5 TB/s of them; neighbouring tiles go to one XCD, which
 // helps little, as a tile names a thousand sources), so a pair costs about as much as three or four list entries, and pairs of three (212 us for 64 k steps instead of 121 for 33 k) gain
-// nothing over the lists.  Whole forward sums, lists / tiles and rest, us: 131072 nodes, 26 M edges, d = 64 345 / 300, 128 687 / 598, 512 2695 / 2250; 65536 nodes, 8.4 M edges, d = 256 444 / 398,
-// 512 827 / 730, but 64 126 / 144; 65536 nodes, 3.9 M edges, d = 512 412 / 420 (where the line lies: tiles_us in hag_cost.cpp).
+// nothing over the lists.  Whole forward sums, lists / tiles and rest, us: 131072 nodes, 26 M edges, d = 64 354 / 316, 128 649 / 578, 512 2676 / 2264; 65536 nodes, 8.4 M edges, d = 256 424 / 377,
+// 512 822 / 753, but 64 126 / 127, 16 58 / 74; 65536 nodes, 3.9 M edges, d = 512 419 / 435 (where the line lies: tiles_us in hag_cost.cpp).
 // A wavefront takes a unit, at most 16 steps of 32 sources of a tile, and 16 * VEC columns; tiles of more steps are added up by the fold, like cut rows.  Shorter units would cost more partial
-// rows than they gain (8 steps: 664 us), longer ones make the chain of fp32 additions longer (error of the whole sum against 64 bits 1.17e-7 with 16 steps, 1.40e-7 with 32; the pass over a HAG 1.3e-7).
+// rows than they gain (131072 nodes, d = 128, steps 8 / 16 / 32: 664 / 598 / 565 us, lists 687 in the same run), longer ones make the chain of fp32 additions longer (error of the whole sum against 64 bits 1.17e-7 with 16 steps, 1.40e-7 with 32; the pass over a HAG 1.3e-7).
 // Four wavefronts sharing a tile's steps through LDS took 261 us where this takes 212: most tiles are a few steps long.
 template <int VEC>
 __global__ __launch_bounds__(kBlock, 2) void tile_kernel(TileArgs A) {

@@ -637,7 +637,12 @@ def main():
         kernel_name = {"dense": f"dense_kernel<{1 if d <= 16 else 2 if d <= 32 else 4}, 0>", "one_launch": f"fused_kernel<float, {1 if op == 'max' else 0}, {lpr}, 0>",
                        "component_hag": f"component_kernel<float, {lpr}, 256, 0>", "component_lists": f"component_kernel<float, {lpr}, 256, 2>"}.get(
                            way, f"{gather}<float, {1 if op == 'max' else 0}, {lpr}, {role}>")
+        # f32 sums over large lists run as dense tiles and a rest, whose partial rows are what their workspace has beyond an int32 sum's
+        tiled = way == "lists" and op != "max" and h.workspace_bytes("sum", P.HAG_F32, d) > h.workspace_bytes("sum", P.HAG_I32, d)
+        if tiled:
+            kernel_name = f"tile_kernel<{1 if d <= 16 else 2 if d <= 32 else 4}>, {gather}<float, 0, {min(lpr, 16)}, 3> and folds: the whole forward pass"
     else:
+        tiled = False
         ms_gather = time_kernel(
             torch,
             lambda: h.forward_phases(x, P.HAG_PHASE_LEVELS, op, y=y, argmax=am),
@@ -674,7 +679,7 @@ def main():
     else:
         bound, peak, ceiling = "hbm", HBM_PEAK_GBS, measured("hbm_rows_GBps")
         achieved_bound = achieved
-    prof = PROFILED_TRAFFIC.get((workload, d, op)) if args.capacity < 0 else None
+    prof = PROFILED_TRAFFIC.get((workload, d, op)) if args.capacity < 0 and not tiled else None   # (the profiled launch is the gather over the HAG or the lists)
     roofline = {"bound": bound, "achieved": achieved_bound, "peak": peak, "unit": "GB/s", "frac": achieved_bound / peak,
                 "traffic": None if prof is None else prof["fetch"] + prof["write"],
                 "kernel": kernel_name, "kernel_ms": ms_gather, "algorithmic_bytes": gather_bytes,

@@ -196,12 +196,17 @@ int launch_dense(DenseArgs a, int role, int max_nodes, hipStream_t s) {
 
 // The tiles of a list set: 128 rows of the output against the sources that at least five of them name, the same products as above with a gathered operand.  A list entry costs a
 // gather one row read, mostly out of L2; here a source's row is read once per tile, whatever the number of rows that name it.  Graphs with communities have half of
-// their entries in such (tile, source) pairs, twelve to a pair on average.  What bounds it: the rows come from beyond L2 (5 TB/s of them; neighbouring tiles go to one XCD, which
+// their entries in such (tile, source) pairs, twelve to a pair on average.  What bounds it: the rows come from beyond L2 (neighbouring tiles go to one XCD, which
 // helps little, as a tile names a thousand sources), so a pair costs about as much as three or four list entries, and pairs of three (212 us for 64 k steps instead of 121 for 33 k) gain
-// nothing over the lists.  Whole forward sums, lists / tiles and rest, us: 131072 nodes, 26 M edges, d = 64 354 / 316, 128 649 / 578, 512 2676 / 2264; 65536 nodes, 8.4 M edges, d = 256 424 / 377,
-// 512 822 / 753, but 64 126 / 127, 16 58 / 74; 65536 nodes, 3.9 M edges, d = 512 419 / 435 (where the line lies: tiles_us in hag_cost.cpp).
-// A wavefront takes a unit, at most 16 steps of 32 sources of a tile, and 16 * VEC columns; tiles of more steps are added up by the fold, like cut rows.  Shorter units would cost more partial
-// rows than they gain (131072 nodes, d = 128, steps 8 / 16 / 32: 664 / 598 / 565 us, lists 687 in the same run), longer ones make the chain of fp32 additions longer (error of the whole sum against 64 bits 1.17e-7 with 16 steps, 1.40e-7 with 32; the pass over a HAG 1.3e-7).
+// nothing over the lists.  Whole forward sums, lists / tiles and rest, us: 131072 nodes, 26 M edges, d = 64 331 / 305, 128 634 / 569, 512 2696 / 2245; 65536 nodes, 8.4 M edges, d = 256 409 / 373,
+// 512 826 / 746, but 64 119 / 146, 16 58 / 78 (where the line lies: tiles_us in hag_cost.cpp).
+// A wavefront takes a unit, at most 24 steps of 32 sources of a tile, and 16 * VEC columns; tiles of more steps are added up by the fold, like cut rows.  Shorter units cost more partial
+// rows than they gain, longer ones leave the smaller graphs waiting for the last of them (steps 16 / 24 / 32: 131072 nodes, d = 128, 595 / 569 / 560 us; 65536 nodes, d = 256, 388 / 373 / 383).
+// The matrix cores cut what they add to the size of the largest operand, always in one direction: sums carried along in the accumulator were too small by 6e-9 to 1e-8 on average, with an error
+// against 64 bits of 5.7e-8 on features of one sign, where the same sum as a plain gather had 5.2e-8 one after the other and has 4.2e-8 (131072 nodes, d = 128).  Every step therefore begins at
+// zero, the largest pieces (exact unless their sizes differ by more than 2^11 or so) apart from the others (whose cut bits are 2^-8 of theirs), and joins the running sum in rounded additions:
+// 4.8e-8 (normal features 1.17e-7 -> 9.4e-8, a gather 9.4e-8) with no bias left, for 4 % of the pass, which units of 24 steps in place of 16 give back.  One chain from zero for all three pieces took
+// half of that, but left normal features with a bias of 3e-8.
 // Four wavefronts sharing a tile's steps through LDS took 261 us where this takes 212: most tiles are a few steps long.
 template <int VEC>
 __global__ __launch_bounds__(kBlock, 2) void tile_kernel(TileArgs A) {
@@ -240,42 +245,44 @@ __global__ __launch_bounds__(kBlock, 2) void tile_kernel(TileArgs A) {
         request_ids(min(s0 + 1, s1 - 1));
     }
     for (int s = s0; s < s1; ++s) {
-        Vec v[8];
-        dense_u4_t a[MT];
+        dense_u4_t p[VEC][3];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = x[i];
-#pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            const uint32_t b = ((m < 4 ? bits.x : bits.y) >> (8 * (m % 4))) & 0xffu, e = b | (b << 15);   // bit 2 i below bit 2 i + 1 of the next half word
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[m][i] = (e << (14 - 2 * i)) & 0x40004000u;
-        }
-        if (s + 1 < s1) {
-            request_bits(s + 1);
-            request_rows(0, VEC == 4 ? 4 : 8);
-        }
-#pragma unroll
-        for (int t = 0; t < VEC; ++t) {
-            dense_u4_t p[3];
+        for (int t = 0; t < VEC; ++t)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float lo = kDenseScale * v[2 * i].e[t], hi = kDenseScale * v[2 * i + 1].e[t];
+                const float lo = kDenseScale * x[2 * i].e[t], hi = kDenseScale * x[2 * i + 1].e[t];
                 const uint32_t ul = __float_as_uint(lo) & 0x7fffffffu, uh = __float_as_uint(hi) & 0x7fffffffu;
                 largest = max(largest, max(ul, uh));
                 uint32_t p0, p1, p2;
                 dense_split2(lo, hi, p0, p1, p2);
-                p[0][i] = p0; p[1][i] = p1; p[2][i] = p2;
+                p[t][0][i] = p0; p[t][1][i] = p1; p[t][2][i] = p2;
             }
+        const uint2 now = bits;
+        if (s + 1 < s1) {
+            request_bits(s + 1);
+            request_rows(0, 8);
+            request_ids(min(s + 2, s1 - 1));
+        }
 #pragma unroll
-            for (int m = 0; m < MT; ++m) {
-                const dense_b8_t w = __builtin_bit_cast(dense_b8_t, a[m]);
+        for (int m = 0; m < MT; ++m) {
+            if (VEC == 4) __builtin_amdgcn_sched_barrier(0);   // (one row tile at a time: registers are short)
+            const uint32_t b = ((m < 4 ? now.x : now.y) >> (8 * (m % 4))) & 0xffu, e = b | (b << 15);   // bit 2 i below bit 2 i + 1 of the next half word
+            dense_u4_t a;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[i] = (e << (14 - 2 * i)) & 0x40004000u;
+            // a step's sums begin at zero, of the largest pieces and of the others, and join the running sum in rounded additions
+#pragma unroll
+            for (int t0 = 0; t0 < VEC; t0 += 2) {
+                constexpr int TN = VEC < 2 ? VEC : 2;
+                dense_f4_t sum[TN][2];
 #pragma unroll
                 for (int k = 2; k >= 0; --k)
-                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, __builtin_bit_cast(dense_b8_t, p[k]), acc[m][t], 0, 0, 0);
-            }
-            if (t == VEC / 2 && s + 1 < s1) {              // (half of the wide rows once half of these are used up: registers are short)
-                if (VEC == 4) request_rows(4, 8);
-                request_ids(min(s + 2, s1 - 1));
+#pragma unroll
+                    for (int t = 0; t < TN; ++t)
+                        sum[t][k == 0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dense_b8_t, a), __builtin_bit_cast(dense_b8_t, p[t0 + t][k]),
+                                                                                 k == 1 ? sum[t][0] : dense_f4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < TN; ++t) acc[m][t0 + t] += sum[t][0] + sum[t][1];
             }
         }
     }

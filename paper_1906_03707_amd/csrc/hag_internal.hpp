@@ -150,7 +150,7 @@ struct Components {
 // The lists of a graph split in two (f32 sums; tile_kernel in hag_dense.hip): the rows are taken 128 at a time, and what sources at least kTileUses rows of such a tile
 // name becomes a small dense product, every such source's row read once per tile instead of once per entry; the other entries stay lists.
 constexpr int kTileRows = 128, kTileUses = 5, kTileStep = 32;   // rows per tile; entries per (tile, source) worth a place; sources per product step
-constexpr int kTileSteps = 16;       // steps of a unit of work at most; a tile with more is several units, whose partial rows a fold adds up
+constexpr int kTileSteps = 24;       // steps of a unit of work at most; a tile with more is several units, whose partial rows a fold adds up
 struct Tiles {
     bool on = false;
     int32_t count = 0;

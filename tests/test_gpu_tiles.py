@@ -1,4 +1,4 @@
-"""Sums over lists split into dense tiles and a rest (HAG_TILES=2: wherever there are tiles): tiles of 128 rows and their remainder, units of 16 steps of 32 sources, chunks of 16, 32
+"""Sums over lists split into dense tiles and a rest (HAG_TILES=2: wherever there are tiles): tiles of 128 rows and their remainder, units of 24 steps of 32 sources, chunks of 16, 32
 and 64 columns.  Small whole numbers, so that every order of addition gives the same floats and an entry dropped or taken twice shows."""
 import numpy as np
 import pytest
@@ -90,6 +90,24 @@ def test_numbers_that_are_not_finite_or_huge_reach_their_neighbours_only(B, monk
     fine = torch.isfinite(want)
     size = plain.forward(torch.where(torch.isfinite(x), x.abs() / 2 ** 40, torch.zeros_like(x)), "sum") * 2 ** 40
     assert bool(((got - want).abs()[fine] <= 1e-5 * size[fine]).all())
+
+
+@pytest.mark.parametrize("kind", ["normal", "positive"])
+def test_sums_lean_to_no_side(B, monkeypatch, kind):
+    # rounded additions err to either side: the mean of N errors is within a few of their standard deviations / sqrt(N) (10: columns of a row share its order
+    # of additions).  Products that are cut to the size of their accumulator leave more than that.
+    n, d = 6000, 128
+    rowptr, col = groups(n, 1500, 0.3, 60000, False, seed=8)
+    h, plain = handles(B, monkeypatch, rowptr, col, False)
+    x = torch.randn(n, d, device="cuda", generator=torch.Generator(device="cuda").manual_seed(9))
+    x = x.abs() if kind == "positive" else x
+    to = torch.repeat_interleave(torch.arange(n, device="cuda"), torch.from_numpy(np.diff(rowptr)).cuda())
+    want = torch.zeros(n, d, dtype=torch.float64, device="cuda").index_add_(0, to, x.double()[torch.from_numpy(col).cuda().long()])
+    error = h.forward(x, "sum").double() - want
+    assert abs(error.mean().item()) <= 10 * error.std().item() / error.numel() ** 0.5
+    # and they are of the size of the lists' errors: a chain of m additions of positive numbers errs by about sqrt(m / 3) roundings of its sum.  Here two units of 24 steps
+    # (2.8 of half a row each) and their fold, 2.2 in all; the lists 8 streams of 54 entries, four at a time (2.1 of an eighth), and their fold, 1.8
+    assert error.norm().item() <= 1.5 * (plain.forward(x, "sum").double() - want).norm().item()
 
 
 def test_replays_of_a_captured_pass(B, monkeypatch):

@@ -129,16 +129,30 @@ static Workspace carve(const hag_handle *h, hag_op_t op, int64_t d, void *base) 
     return w;
 }
 
+static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases, bool as_built = false);
+
 // Transposed mean and gcn: a gather that multiplies every row it reads by the row's 1 / degree loads that number with every list entry, a request of its own
 // beside the row's.  Where the lists are long it pays to multiply the n rows of gy once beforehand (the same products, so the same sums bit for bit).
-// Bytes of the scaled copy, 0 where the gather multiplies.  The copy costs a launch and two rows of traffic per node (4 us + 2 ps per element); what it saves
+// The copy costs a launch and two rows of traffic per node (4 us + 2 ps per element); what it saves
 // per list entry was 4 to 9 ps at d <= 32, 10 at 64, 12 to 22 at 128, 20 to 39 at 256: the line lies where the low end of those just pays.  us, the
 // gather multiplying / a scaled copy: 65536 nodes, 8.4 M entries, d = 16 87 / 63, 64 190 / 131, 128 324 / 231, 256 625 / 437; 20000 nodes, 1.2 M entries,
 // d = 64 63 / 44; 56944 nodes, 1.6 M entries, d = 64 86 / 68, 128 105 / 105 (not taken); 20000 nodes, 0.64 M entries, d = 32 14 / 17 (not taken).
+// Over a HAG only entries that name a destination are scaled (those that name an aggregation node are not), one for each entry of the cover lists: 60000 nodes
+// in complete groups of 100 have 6 M entries and a HAG that scales 60000; with a copy for those d = 64 29 / 31, 128 38 / 46, 256 63 / 77 (not taken).
+static bool copy_pays(const hag_handle *h, bool lists, hag_op_t op, int64_t d) {
+    if (op != HAG_MEAN && op != HAG_GCN) return false;
+    const double saved = (3e-6 + 7.5e-8 * (double)d) * (double)(lists ? h->e : h->st.h), cost = 4. + 2e-6 * (double)h->n * (double)d;
+    return saved > 1.1 * cost;
+}
+// Bytes of the scaled copy where a transposed pass (of hag_backward or hag_naive_backward) makes one, else 0.  Only sizes decide, none of the handle's options: what a
+// caller was told stays enough.
 static size_t scaled_bytes(const hag_handle *h, hag_op_t op, int64_t d) {
-    if (op != HAG_MEAN && op != HAG_GCN) return 0;
-    const double saved = (3e-6 + 7.5e-8 * (double)d) * (double)h->e, cost = 4. + 2e-6 * (double)h->n * (double)d;
-    return saved > 1.1 * cost ? align_up((size_t)h->n * (size_t)d * 4) : 0;
+    for (const bool naive : {false, true}) {
+        if (!copy_pays(h, true, op, d) && !copy_pays(h, false, op, d)) return 0;
+        const int route = route_of(h, naive, true, op, HAG_F32, d, HAG_PHASE_ALL, true);
+        if ((route == HAG_ROUTE_LISTS || route == HAG_ROUTE_HAG) && copy_pays(h, route == HAG_ROUTE_LISTS, op, d)) return align_up((size_t)h->n * (size_t)d * 4);
+    }
+    return 0;
 }
 
 // Partial rows of the sums that run as tiles and a rest, beside what the other forms need (so that a caller without room for them is served over the lists as ever).
@@ -411,7 +425,7 @@ static PassPlans hag_pass(const hag_handle *h, bool backward) {
 
 // Whether sums over the input graph's lists may run as tiles and a rest (see Tiles); whether they do is a matter of cost (tiles_pay).
 static bool tiles_apply(const hag_handle *h, bool backward, hag_op_t op, hag_dtype_t dt, uint32_t phases) {
-    return h->tiles[backward && !h->symmetric].on && dt == HAG_F32 && op != HAG_MAX && phases == HAG_PHASE_ALL && !h->knobs.list_forms;
+    return h->tiles[backward && !h->symmetric].on && dt == HAG_F32 && op != HAG_MAX && phases == HAG_PHASE_ALL;
 }
 
 // A sum over the input graph's lists: what the tiles hold into `a.out`, then the other entries' gather, which finds it there as if it were the row of the node itself.
@@ -455,23 +469,24 @@ static int run_tiles(const hag_handle *h, bool backward, GatherArgs<float> a, vo
 
 // The way a pass takes (HAG_ROUTE_*): the one place where it is decided, from sizes and knobs alone.  The pass over the HAG, the pass over the input
 // graph's own lists and, for a batch of small graphs, the dense products aggregate the same; a whole pass takes the one expected to be fastest (see hag_cost.cpp).
-static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases) {
+// as_built: what the handle would do without its options.
+static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases, bool as_built) {
     if (op == HAG_MAX && backward) return h->knobs.deterministic_max_backward ? HAG_ROUTE_LISTS : HAG_ROUTE_SCATTER;   // looks at no list of the HAG
     if (phases != HAG_PHASE_ALL) return naive ? HAG_ROUTE_LISTS : HAG_ROUTE_HAG;
-    const bool one_launch = h->knobs.fuse_max_items > 0;
+    const bool one_launch = !as_built && h->knobs.fuse_max_items > 0, list_forms = !as_built && h->knobs.list_forms;
     const CompLayout on_hag = component_layout(h, false, backward, op, d), on_lists = component_layout(h, true, backward, op, d);
     FormQuery q{};
     q.max = op == HAG_MAX;
     q.backward = backward;
     q.hag_allowed = !naive;
-    q.tiles_allowed = tiles_apply(h, backward, op, dt, phases) && on_lists.total == 0 && !one_launch;
+    q.tiles_allowed = tiles_apply(h, backward, op, dt, phases) && !list_forms && on_lists.total == 0 && !one_launch;
     if (!naive) {
         // a HAG that saves most of the row reads is taken as it is
         const double hag_reads = h->cost[0][backward].reads[0] + h->cost[0][backward].reads[1], list_reads = h->cost[1][backward].reads[0] + h->cost[1][backward].reads[1];
         q.tiles_allowed = q.tiles_allowed && h->knobs.route && hag_reads > 0.5 * list_reads;
     }
-    q.lists_allowed = naive || ((h->a > 0 || q.tiles_allowed) && h->knobs.route && !h->knobs.list_forms && !one_launch);
-    q.dense_allowed = h->comp.dense && dt == HAG_F32 && op != HAG_MAX && !h->knobs.list_forms;
+    q.lists_allowed = naive || ((h->a > 0 || q.tiles_allowed) && h->knobs.route && !list_forms && !one_launch);
+    q.dense_allowed = h->comp.dense && dt == HAG_F32 && op != HAG_MAX && !list_forms;
     q.d = d;
     q.component_lds[0] = on_hag.total * on_hag.parts;     // (priced with its columns in one piece: the pieces are a knob for experiments)
     q.component_lds[1] = on_lists.total * on_lists.parts;
@@ -547,7 +562,7 @@ static int forward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d,
     a.d = (int32_t)d;
     if (!(phases & (HAG_PHASE_GATHER | HAG_PHASE_FOLD))) return HAG_OK;
     if constexpr (std::is_same<T, float>::value && RED == R_SUM)
-        if (naive && tiles && ws && tiles_apply(h, false, op, HAG_F32, phases) && tiles_pay(h, false, d))
+        if (naive && tiles && ws && !h->knobs.list_forms && tiles_apply(h, false, op, HAG_F32, phases) && tiles_pay(h, false, d))
             return run_tiles(h, false, a, (char *)ws + w.total + scaled_bytes(h, op, d), s);
     if (naive) return run_plan<T, RED, G_NAIVE_FWD>(h, h->p_naive_fwd, h->d_gcol, a, w, s, phases);
     return run_plan<T, RED, G_HAG_FWD>(h, h->p_fwd, h->d_hcol, a, w, s, phases);
@@ -602,7 +617,7 @@ static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d
     a.d = (int32_t)d;
     if constexpr (std::is_same<T, float>::value) {
         // (a caller may have brought no workspace where the lists alone need none; the one-launch schedule has no launch to spare)
-        if (ws && route != HAG_ROUTE_ONE_LAUNCH && scaled_bytes(h, op, d) > 0 && h->n > 0) {
+        if (ws && route != HAG_ROUTE_ONE_LAUNCH && h->n > 0 && copy_pays(h, naive, op, d) && scaled_bytes(h, op, d) > 0) {
             float *scaled = (float *)((char *)ws + w.total);
             const int64_t n4 = h->n * (d / 4);
             if (phases & (HAG_PHASE_LEVELS | HAG_PHASE_GATHER)) {
@@ -619,7 +634,7 @@ static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d
         if (op == HAG_GCN) { a.self = gy; a.self_scale = h->d_inv_deg1; }
         if (!(phases & (HAG_PHASE_GATHER | HAG_PHASE_FOLD))) return HAG_OK;
         if constexpr (std::is_same<T, float>::value)
-            if (ws && !a.in_scale && tiles_apply(h, true, op, HAG_F32, phases) && tiles_pay(h, true, d))
+            if (ws && !a.in_scale && !h->knobs.list_forms && tiles_apply(h, true, op, HAG_F32, phases) && tiles_pay(h, true, d))
                 return run_tiles(h, true, a, (char *)ws + w.total + scaled_bytes(h, op, d), s);
         return run_plan<T, R_SUM, G_NAIVE_BWD>(h, h->p_naive_bwd, h->d_gtcol, a, w, s, phases);
     }

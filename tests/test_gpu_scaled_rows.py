@@ -46,3 +46,31 @@ def test_scaled_rows(B, monkeypatch, way, d):
             stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
             assert B.lib().hag_backward(h._h, B.OPS[op], B.HAG_F32, d, gy.data_ptr(), None, gx.data_ptr(), None, stream) == 0
             assert torch.equal(gx, got)
+
+
+def test_no_copy_over_a_hag_that_scales_few_entries(B):
+    # complete groups of shuffled nodes: a million list entries, of which a HAG with a balanced tree per group names a destination 10000 times
+    size, n, d = 100, 10000, 64
+    members = np.sort(np.random.default_rng(4).permutation(n).astype(np.int32).reshape(-1, size), axis=1)
+    group = np.empty(n, np.int64)
+    group[members.ravel()] = np.repeat(np.arange(n // size), size)
+    rowptr, col = np.arange(n + 1, dtype=np.int64) * size, members[group].reshape(-1)
+    merges, at = [], n
+    trees = [list(m) for m in members]
+    while len(trees[0]) > 1:
+        for t in trees:
+            pairs = [(t[i], t[i + 1]) for i in range(0, len(t) - 1, 2)]
+            t[:] = list(range(at, at + len(pairs))) + t[2 * len(pairs):]
+            merges += pairs
+            at += len(pairs)
+    h = B.hag_from_merges(rowptr, col, *np.array(merges, np.int32).T).upload()
+    assert h.stats()["h"] == n and h.route("mean", d=d, backward=True) == "hag"
+    gy = torch.randn(n, d, device="cuda")
+    for op in ("mean", "gcn"):
+        rows = h.workspace_bytes("sum", B.HAG_F32, d)      # the copy's place is behind what a sum needs (lists alone make one: their rows are long)
+        ws = torch.full((h.workspace_bytes(op, B.HAG_F32, d),), 171, dtype=torch.uint8, device="cuda")
+        assert ws.numel() >= rows + 4 * n * d
+        got = h.backward(gy, op, workspace=ws)
+        assert bool((ws[rows:] == 171).all())
+        assert bool(((got - h.naive_backward(gy, op, workspace=ws)).abs() <= 1e-5 * gy.abs().max() * 2).all())
+        assert not bool((ws[rows:] == 171).all())

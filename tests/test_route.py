@@ -128,3 +128,16 @@ def test_list_forms_option():
         assert both() == [hag] * 2 and both(naive=True) == [lists] * 2
         h.set_option(B.HAG_OPT_LIST_FORMS, 0)
         assert both() == [own] * 2 == both(naive=True)
+
+
+def test_workspace_of_a_batch_holds_nothing_for_lists():
+    # 2.4 M entries, enough for a scaled copy of the gradients if a transposed mean went over the lists: it runs as dense products, which need none
+    rowptr, col, gp = synth.er_batch(500, 74, 0.9, seed=104)
+    h = B.hag_search_batched(rowptr, col, gp, 0.0)
+    for op in ("sum", "mean", "gcn"):
+        for naive in (False, True):
+            assert {h.route(op, d=64, backward=b, naive=naive) for b in (False, True)} == {"dense"}
+        assert h.workspace_bytes(op, B.HAG_F32, 64) == 0
+    # and an option given later does not need more than was told before
+    h.set_option(B.HAG_OPT_LIST_FORMS, 1)
+    assert h.workspace_bytes("mean", B.HAG_F32, 64) == 0

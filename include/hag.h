@@ -269,8 +269,10 @@ size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64
  * y[v] = Aggregate over Nhat_v for every v in V.  x, y: device [n, d].
  * What is computed is the aggregate over N(v), which the HAG covers exactly (Section 3.2); hag_forward and
  * hag_backward evaluate it over the HAG, over the input graph's own lists (f32 sums over large ones in part as dense tiles) or, for a batch of small graphs, as
- * products with their adjacency matrices, whichever is expected to be fastest (from the handle, op, dtype and d alone: the same call
- * takes the same way every time; hag_route tells which).  Integer results and max are the same bit for bit; fp32 sums differ in the last bits, as the order of addition does.
+ * products with their adjacency matrices, whichever is expected to be fastest (from the handle, op, dtype and d: the same call
+ * takes the same way every time; hag_route tells which for a call that brings hag_workspace_bytes.  Tiles need room for partial rows:
+ * where the lists alone need no workspace and none is brought, and where the fixed array of hag_forward_static_scratch is too small for
+ * them, the lists, or the HAG if that is expected to be faster than they, serve alone).  Integer results and max are the same bit for bit; fp32 sums differ in the last bits, as the order of addition does.
  * argmax: device int32 [n, d], required for HAG_MAX, ignored otherwise.
  * HAG_MEAN and HAG_GCN require HAG_F32. */
 int hag_forward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d,
@@ -289,7 +291,7 @@ int hag_backward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d,
 /* The way hag_forward (backward = 0) or hag_backward (1) takes with these arguments, or a negative status.  Host state only; hag_upload
  * need not have been called:
  *   HAG_ROUTE_HAG              Algorithm 2 over the HAG: a launch per stage of aggregation nodes, then the gather over V;
- *   HAG_ROUTE_LISTS            the input graph's own lists (max, backward: the fixed-order gather of HAG_OPT_DETERMINISTIC_MAX_BACKWARD);
+ *   HAG_ROUTE_LISTS            the input graph's own lists, with or without tiles (max, backward: the fixed-order gather of HAG_OPT_DETERMINISTIC_MAX_BACKWARD);
  *   HAG_ROUTE_COMPONENT_HAG, HAG_ROUTE_COMPONENT_LISTS   a batch of small graphs, one launch out of LDS, over the HAG or the lists;
  *   HAG_ROUTE_DENSE            a batch of small graphs as products with their adjacency matrices;
  *   HAG_ROUTE_ONE_LAUNCH       the one-launch schedule below, over the HAG;

@@ -129,7 +129,9 @@ static Workspace carve(const hag_handle *h, hag_op_t op, int64_t d, void *base) 
     return w;
 }
 
-static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases, bool as_built = false);
+// The way a call takes: HAG_ROUTE_*, and whether the lists of HAG_ROUTE_LISTS run as tiles and a rest.
+struct Way { int route; bool tiles; };
+static Way way_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases, bool room, bool as_built = false);
 
 // Transposed mean and gcn: a gather that multiplies every row it reads by the row's 1 / degree loads that number with every list entry, a request of its own
 // beside the row's.  Where the lists are long it pays to multiply the n rows of gy once beforehand (the same products, so the same sums bit for bit).
@@ -149,20 +151,20 @@ static bool copy_pays(const hag_handle *h, bool lists, hag_op_t op, int64_t d) {
 static size_t scaled_bytes(const hag_handle *h, hag_op_t op, int64_t d) {
     for (const bool naive : {false, true}) {
         if (!copy_pays(h, true, op, d) && !copy_pays(h, false, op, d)) return 0;
-        const int route = route_of(h, naive, true, op, HAG_F32, d, HAG_PHASE_ALL, true);
+        const int route = way_of(h, naive, true, op, HAG_F32, d, HAG_PHASE_ALL, true, true).route;
         if ((route == HAG_ROUTE_LISTS || route == HAG_ROUTE_HAG) && copy_pays(h, route == HAG_ROUTE_LISTS, op, d)) return align_up((size_t)h->n * (size_t)d * 4);
     }
     return 0;
 }
 
-// Partial rows of the sums that run as tiles and a rest, beside what the other forms need (so that a caller without room for them is served over the lists as ever).
-// Only sizes decide, none of the handle's options: what a caller was told stays enough.
-static size_t tiles_bytes(const hag_handle *h, hag_op_t op, hag_dtype_t dt, int64_t d) {
-    int64_t rows = 0;
-    if (dt == HAG_F32 && op != HAG_MAX)
-        for (const bool backward : {false, true})
-            if (tiles_pay(h, backward, d)) rows = std::max(rows, h->tiles[backward && !h->symmetric].part_rows());
-    return align_up((size_t)rows * (size_t)d * 4);
+// Partial rows of the sums of one direction that run as tiles and a rest, beside what the other forms need (so that a caller without room for them is served over the
+// lists as ever).  As above, whatever the options.
+static size_t tiles_bytes(const hag_handle *h, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d) {
+    if (op == HAG_MAX) return 0;
+    for (const bool naive : {false, true})
+        if (way_of(h, naive, backward, op, dt, d, HAG_PHASE_ALL, true, true).tiles)
+            return align_up((size_t)h->tiles[backward && !h->symmetric].part_rows() * (size_t)d * 4);
+    return 0;
 }
 
 // Whether a pass over `plans` (its phases in execution order) can run as one launch: a small
@@ -423,11 +425,6 @@ static PassPlans hag_pass(const hag_handle *h, bool backward) {
     return p;
 }
 
-// Whether sums over the input graph's lists may run as tiles and a rest (see Tiles); whether they do is a matter of cost (tiles_pay).
-static bool tiles_apply(const hag_handle *h, bool backward, hag_op_t op, hag_dtype_t dt, uint32_t phases) {
-    return h->tiles[backward && !h->symmetric].on && dt == HAG_F32 && op != HAG_MAX && phases == HAG_PHASE_ALL;
-}
-
 // A sum over the input graph's lists: what the tiles hold into `a.out`, then the other entries' gather, which finds it there as if it were the row of the node itself.
 static int run_tiles(const hag_handle *h, bool backward, GatherArgs<float> a, void *part, hipStream_t s) {
     Workspace w;
@@ -467,23 +464,25 @@ static int run_tiles(const hag_handle *h, bool backward, GatherArgs<float> a, vo
     return backward ? run_plan<float, R_SUM, G_NAIVE_BWD>(h, t.plan, t.d_rest_col, a, w, s) : run_plan<float, R_SUM, G_NAIVE_FWD>(h, t.plan, t.d_rest_col, a, w, s);
 }
 
-// The way a pass takes (HAG_ROUTE_*): the one place where it is decided, from sizes and knobs alone.  The pass over the HAG, the pass over the input
+// The way a pass takes: the one place where it is decided, from sizes and knobs alone.  The pass over the HAG, the pass over the input
 // graph's own lists and, for a batch of small graphs, the dense products aggregate the same; a whole pass takes the one expected to be fastest (see hag_cost.cpp).
-// as_built: what the handle would do without its options.
-static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases, bool as_built) {
-    if (op == HAG_MAX && backward) return h->knobs.deterministic_max_backward ? HAG_ROUTE_LISTS : HAG_ROUTE_SCATTER;   // looks at no list of the HAG
-    if (phases != HAG_PHASE_ALL) return naive ? HAG_ROUTE_LISTS : HAG_ROUTE_HAG;
+// room: the caller's workspace holds the tiles' partial rows.  as_built: what the handle would do without its options.
+static Way way_of(const hag_handle *h, bool naive, bool backward, hag_op_t op, hag_dtype_t dt, int64_t d, uint32_t phases, bool room, bool as_built) {
+    if (op == HAG_MAX && backward) return {h->knobs.deterministic_max_backward ? HAG_ROUTE_LISTS : HAG_ROUTE_SCATTER, false};   // looks at no list of the HAG
+    if (phases != HAG_PHASE_ALL) return {naive ? HAG_ROUTE_LISTS : HAG_ROUTE_HAG, false};
     const bool one_launch = !as_built && h->knobs.fuse_max_items > 0, list_forms = !as_built && h->knobs.list_forms;
     const CompLayout on_hag = component_layout(h, false, backward, op, d), on_lists = component_layout(h, true, backward, op, d);
     FormQuery q{};
     q.max = op == HAG_MAX;
     q.backward = backward;
     q.hag_allowed = !naive;
-    q.tiles_allowed = tiles_apply(h, backward, op, dt, phases) && !list_forms && on_lists.total == 0 && !one_launch;
+    // (on the transposed pass of mean and gcn the rows the tiles read have to be scaled beforehand)
+    q.tiles_allowed = h->tiles[backward && !h->symmetric].on && room && dt == HAG_F32 && op != HAG_MAX && !list_forms && on_lists.total == 0 &&
+                      (!backward || op == HAG_SUM || copy_pays(h, true, op, d));
     if (!naive) {
         // a HAG that saves most of the row reads is taken as it is
         const double hag_reads = h->cost[0][backward].reads[0] + h->cost[0][backward].reads[1], list_reads = h->cost[1][backward].reads[0] + h->cost[1][backward].reads[1];
-        q.tiles_allowed = q.tiles_allowed && h->knobs.route && hag_reads > 0.5 * list_reads;
+        q.tiles_allowed = q.tiles_allowed && !one_launch && h->knobs.route && hag_reads > 0.5 * list_reads;
     }
     q.lists_allowed = naive || ((h->a > 0 || q.tiles_allowed) && h->knobs.route && !list_forms && !one_launch);
     q.dense_allowed = h->comp.dense && dt == HAG_F32 && op != HAG_MAX && !list_forms;
@@ -491,17 +490,17 @@ static int route_of(const hag_handle *h, bool naive, bool backward, hag_op_t op,
     q.component_lds[0] = on_hag.total * on_hag.parts;     // (priced with its columns in one piece: the pieces are a knob for experiments)
     q.component_lds[1] = on_lists.total * on_lists.parts;
     const int form = q.dense_allowed && h->comp.dense_always ? kFormDense : cheapest_form(h, q);
-    if (form == kFormDense) return HAG_ROUTE_DENSE;
-    if (form == kFormLists) return on_lists.total > 0 ? HAG_ROUTE_COMPONENT_LISTS : HAG_ROUTE_LISTS;
-    if (on_hag.total > 0) return HAG_ROUTE_COMPONENT_HAG;
+    if (form == kFormDense) return {HAG_ROUTE_DENSE, false};
+    if (form == kFormLists) return {on_lists.total > 0 ? HAG_ROUTE_COMPONENT_LISTS : HAG_ROUTE_LISTS, q.tiles_allowed && tiles_pay(h, backward, d)};
+    if (on_hag.total > 0) return {HAG_ROUTE_COMPONENT_HAG, false};
     // a small HAG: aggregation-node stages and the gather over V as one launch
-    return one_launch && fusable(h, d, hag_pass(h, backward).plans) ? HAG_ROUTE_ONE_LAUNCH : HAG_ROUTE_HAG;
+    return {one_launch && fusable(h, d, hag_pass(h, backward).plans) ? HAG_ROUTE_ONE_LAUNCH : HAG_ROUTE_HAG, false};
 }
 
 template <typename T, int RED>
 static int forward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d, const T *x, T *y, int32_t *argmax,
-                        void *ws, hipStream_t s, uint32_t phases, bool tiles) {
-    const int route = route_of(h, naive, false, op, std::is_same<T, float>::value ? HAG_F32 : HAG_I32, d, phases);
+                        void *ws, hipStream_t s, uint32_t phases, bool room) {
+    const auto [route, tiles] = way_of(h, naive, false, op, std::is_same<T, float>::value ? HAG_F32 : HAG_I32, d, phases, room);
     if constexpr (std::is_same<T, float>::value && RED == R_SUM)
         if (route == HAG_ROUTE_DENSE) return run_dense(h, naive, false, op, d, x, y, s);
     if (route == HAG_ROUTE_COMPONENT_HAG || route == HAG_ROUTE_COMPONENT_LISTS)
@@ -562,8 +561,7 @@ static int forward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d,
     a.d = (int32_t)d;
     if (!(phases & (HAG_PHASE_GATHER | HAG_PHASE_FOLD))) return HAG_OK;
     if constexpr (std::is_same<T, float>::value && RED == R_SUM)
-        if (naive && tiles && ws && !h->knobs.list_forms && tiles_apply(h, false, op, HAG_F32, phases) && tiles_pay(h, false, d))
-            return run_tiles(h, false, a, (char *)ws + w.total + scaled_bytes(h, op, d), s);
+        if (tiles) return run_tiles(h, false, a, (char *)ws + w.total, s);
     if (naive) return run_plan<T, RED, G_NAIVE_FWD>(h, h->p_naive_fwd, h->d_gcol, a, w, s, phases);
     return run_plan<T, RED, G_HAG_FWD>(h, h->p_fwd, h->d_hcol, a, w, s, phases);
 }
@@ -572,7 +570,7 @@ template <typename T>
 static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d, const T *gy, const int32_t *argmax,
                          T *gx, void *ws, hipStream_t s, uint32_t phases) {
     const int32_t n = (int32_t)h->n;
-    const int route = route_of(h, naive, true, op, std::is_same<T, float>::value ? HAG_F32 : HAG_I32, d, phases);
+    const auto [route, tiles] = way_of(h, naive, true, op, std::is_same<T, float>::value ? HAG_F32 : HAG_I32, d, phases, ws != nullptr);
     if (op == HAG_MAX && route == HAG_ROUTE_LISTS) {
         // gx[u, f] = sum over the consumers v of u of gy[v, f] where argmax[v, f] == u: a gather over the
         // transposed input graph in a fixed order (no atomics), at the price of reading the argmax row
@@ -634,8 +632,7 @@ static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d
         if (op == HAG_GCN) { a.self = gy; a.self_scale = h->d_inv_deg1; }
         if (!(phases & (HAG_PHASE_GATHER | HAG_PHASE_FOLD))) return HAG_OK;
         if constexpr (std::is_same<T, float>::value)
-            if (ws && !a.in_scale && !h->knobs.list_forms && tiles_apply(h, true, op, HAG_F32, phases) && tiles_pay(h, true, d))
-                return run_tiles(h, true, a, (char *)ws + w.total + scaled_bytes(h, op, d), s);
+            if (tiles) return run_tiles(h, true, a, (char *)ws + w.total + scaled_bytes(h, op, d), s);
         return run_plan<T, R_SUM, G_NAIVE_BWD>(h, h->p_naive_bwd, h->d_gtcol, a, w, s, phases);
     }
     if (route == HAG_ROUTE_ONE_LAUNCH) {
@@ -776,25 +773,29 @@ bad:
 // what a pass over lists or a HAG needs; the transposed pass of max can do with none (it then adds with atomics)
 static size_t pass_bytes(const hag_t *h, hag_op_t op, int64_t d) { return !h || d <= 0 ? 0 : carve(h, op, d, nullptr).total; }
 
+// with room for the tiles of a forward pass
+static size_t forward_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d) { return pass_bytes(h, op, d) + tiles_bytes(h, false, op, dt, d); }
+
 size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d) {
     if (!h || d <= 0) return 0;
-    return std::max(pass_bytes(h, op, d) + scaled_bytes(h, op, d) + tiles_bytes(h, op, dt, d), op == HAG_MAX ? max_scatter_bytes(h->n, d) : 0);
+    return std::max({forward_bytes(h, op, dt, d), pass_bytes(h, op, d) + scaled_bytes(h, op, d) + tiles_bytes(h, true, op, dt, d), op == HAG_MAX ? max_scatter_bytes(h->n, d) : 0});
 }
 
 static int forward_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, const void *x, void *y,
-                         int32_t *argmax, void *ws, void *stream, uint32_t phases, bool tiles = true) {
+                         int32_t *argmax, void *ws, void *stream, uint32_t phases, bool room = true) {
     int rc = check_common(h, op, dt, d, x, y, ws, pass_bytes(h, op, d) > 0);
     if (rc) return rc;
     if (op == HAG_MAX && !argmax && h->n > 0) { set_error("argmax is required for max"); return HAG_EINVAL; }
     if ((uintptr_t)argmax & 15) { set_error("argmax must be 16-byte aligned"); return HAG_EINVAL; }
     if (x == y && h->n > 0) { set_error("x and y must not alias"); return HAG_EINVAL; }
     hipStream_t s = (hipStream_t)stream;
+    room = room && ws;
     if (dt == HAG_F32) {
-        if (op == HAG_MAX) return forward_impl<float, R_MAX>(h, naive, op, d, (const float *)x, (float *)y, argmax, ws, s, phases, tiles);
-        return forward_impl<float, R_SUM>(h, naive, op, d, (const float *)x, (float *)y, argmax, ws, s, phases, tiles);
+        if (op == HAG_MAX) return forward_impl<float, R_MAX>(h, naive, op, d, (const float *)x, (float *)y, argmax, ws, s, phases, room);
+        return forward_impl<float, R_SUM>(h, naive, op, d, (const float *)x, (float *)y, argmax, ws, s, phases, room);
     }
-    if (op == HAG_MAX) return forward_impl<int32_t, R_MAX>(h, naive, op, d, (const int32_t *)x, (int32_t *)y, argmax, ws, s, phases, tiles);
-    return forward_impl<int32_t, R_SUM>(h, naive, op, d, (const int32_t *)x, (int32_t *)y, argmax, ws, s, phases, tiles);
+    if (op == HAG_MAX) return forward_impl<int32_t, R_MAX>(h, naive, op, d, (const int32_t *)x, (int32_t *)y, argmax, ws, s, phases, room);
+    return forward_impl<int32_t, R_SUM>(h, naive, op, d, (const int32_t *)x, (int32_t *)y, argmax, ws, s, phases, room);
 }
 
 static int backward_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, const void *gy,
@@ -828,7 +829,7 @@ int hag_forward_static_scratch(const hag_t *h, hag_op_t op, hag_dtype_t dt, int6
     void *ws = (h->device >= 0 && h->device < kMaxDevices) ? g_scratch_ptr[h->device] : nullptr;
     if (!ws) { set_error("static scratch of the handle's device was not set up"); return HAG_ESTATE; }
     // (no tiles where their partial rows do not fit as well)
-    return forward_entry(h, false, op, dt, d, x, y, argmax, ws, stream, HAG_PHASE_ALL, hag_workspace_bytes(h, op, dt, d) <= (size_t)HAG_STATIC_SCRATCH_BYTES);
+    return forward_entry(h, false, op, dt, d, x, y, argmax, ws, stream, HAG_PHASE_ALL, forward_bytes(h, op, dt, d) <= (size_t)HAG_STATIC_SCRATCH_BYTES);
 }
 static int route_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, int32_t backward) {
     if (!h) { set_error("handle is NULL"); return HAG_EINVAL; }
@@ -836,7 +837,7 @@ static int route_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, 
     if (dt != HAG_F32 && dt != HAG_I32) { set_error("unknown dtype"); return HAG_EINVAL; }
     if ((op == HAG_MEAN || op == HAG_GCN) && dt != HAG_F32) { set_error("mean and gcn are defined for f32 only"); return HAG_EINVAL; }
     if (d <= 0 || d % 4 != 0 || d > (1 << 20)) { set_error("d must be a positive multiple of 4, at most 2^20"); return HAG_EINVAL; }
-    return route_of(h, naive, backward != 0, op, dt, d, HAG_PHASE_ALL);
+    return way_of(h, naive, backward != 0, op, dt, d, HAG_PHASE_ALL, true).route;
 }
 int hag_route(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d, int32_t backward) { return route_entry(h, false, op, dt, d, backward); }
 int hag_naive_route(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d, int32_t backward) { return route_entry(h, true, op, dt, d, backward); }

@@ -152,3 +152,17 @@ def test_without_room_for_the_partial_rows_a_sum_goes_over_the_lists(B, monkeypa
     assert need(h, d) > B.HAG_STATIC_SCRATCH_BYTES and need(plain, d) == 0
     x = torch.randn(n, d, device="cuda")
     assert torch.equal(h.forward_static_scratch(x, "sum"), plain.forward(x, "sum"))
+
+
+def test_the_fixed_scratch_array_serves_what_a_forward_pass_needs(B, monkeypatch):
+    # seven partial rows per node.  They fit the array, but not together with the scaled copy of a transposed mean
+    n, d = 12000, 200
+    rowptr, col = groups(n, 1500, 0.15, 0, True, seed=11)
+    h, plain = handles(B, monkeypatch, rowptr, col, False)
+    need = {op: h.workspace_bytes(op, B.HAG_F32, d) for op in ("sum", "mean")}
+    assert need["sum"] <= B.HAG_STATIC_SCRATCH_BYTES < need["mean"]
+    x = torch.randn(n, d, device="cuda")
+    for op in ("sum", "mean"):
+        want = h.forward(x, op)
+        assert not torch.equal(want, plain.forward(x, op))    # another order of additions: tiles ran
+        assert torch.equal(h.forward_static_scratch(x, op), want)

@@ -1,6 +1,7 @@
 // What a pass over the HAG and a pass over the plain lists are expected to cost: the two aggregate the same, and the faster one is taken.
 #include <algorithm>
 #include <cmath>
+#include <numeric>
 #include <vector>
 
 #include "hag_internal.hpp"
@@ -49,6 +50,7 @@ static double miss_rate(const Plan &p, const std::vector<int32_t> &col, int64_t 
 static void add_plan(const hag_handle *h, const Plan &p, const std::vector<int32_t> &col, int w, PassCost &c) {
     if (p.items.empty()) return;
     const int lpr = p.np > 1 ? std::min(4 << w, p.lanes) : 4 << w;
+    if (p.np > 1) c.lanes = p.lanes;
     int64_t n_long = 0, long0 = 0;
     for (int k = 0; k < p.np; ++k) {
         const int64_t n = long_items(p, k, block_threshold(h->knobs.sub_max, p, lpr));
@@ -99,7 +101,7 @@ constexpr Price kMaxPrice{7.1, 1.6e-6, 1 / 56e6, 1 / 10.3e6, 8.2e-5, 1 / 1.65e6,
 static double gather_us(const PassCost &c, bool max, int64_t d) {
     const Price &p = max ? kMaxPrice : kSumPrice;
     const int lpr = pick_lpr(d), w = lpr == 4 ? 0 : lpr == 8 ? 1 : lpr == 16 ? 2 : lpr == 32 ? 3 : 4;
-    const double bytes = 4. * (double)d, all = std::ceil((double)d / (4 * lpr)), cut = std::ceil((double)d / (4 * std::min(lpr, 32)));   // column chunks
+    const double bytes = 4. * (double)d, all = std::ceil((double)d / (4 * lpr)), cut = std::ceil((double)d / (4 * std::min(lpr, c.lanes)));   // column chunks
     const double reads = c.reads[0] + c.reads[1], chunks = c.reads[1] > c.reads[0] ? cut : all;
     return p.launch * c.launches + p.read * (c.reads[0] * all + c.reads[1] * cut) + bytes * (p.hit * reads + p.miss * c.miss[w] + p.slot * c.slots + p.row * c.rows) +
            p.fold * c.fold[w] * chunks + p.item * (c.slots + c.rows);
@@ -127,17 +129,33 @@ static double dense_us(const hag_handle *h, int64_t d) {
     return 4.3 + std::cbrt((1 + std::pow(waves / 1211, 3)) * std::pow(wave, 3) + std::pow(0.153e-6 * 8. * (double)h->n * (double)d, 3));
 }
 
-// The tiles of the lists and the rest (us): what the launches and the longest unit take whatever the size, the steps, the partial rows.  Fitted to 7 community graphs of 1.2 to 26 M edges,
-// d = 16 to 512; with the margin below no case of those was
-// slower than its lists (closest: 65536 nodes, 8.4 M edges, d = 512, 753 against 822 us; left out: 30000 nodes, 4.5 M edges, d = 512, 362 and 444).
+// Passes mostly cut by source, at any width, where they are weighed against tiles.  The prices above were fitted at four widths that fill their column chunks and are too low in between (131072
+// nodes, 26 M edges: d = 128 634 us, priced 699, but 132 1203, priced 744): a row is read in whole chunks, and misses are whole lines of 128 bytes.
+// Fitted with the tiles below to 17 community and block graphs of 1.2 to 114 M edges (mean degrees 60 to 490), 15 widths from 8 to 512: lists within 7.3 % (root mean square), tiles
+// and rest within 8.5 %.  Taking what is called cheaper costs 0.2 % on average against always knowing (more than 5 % in 5 of 255 cases, the worst 9.5 %).
+static double row_lines(int64_t d, int64_t chunk) {          // lines a row of d floats touches when it is read in chunks, on average over its rows
+    const double unit = (double)std::gcd(4 * d, (int64_t)128);
+    const auto lines = [&](int64_t columns) { return columns > 0 ? (4. * (double)columns - unit) / 128 + 1 : 0.; };
+    return (double)(d / chunk) * lines(chunk) + lines(d % chunk);
+}
+static double cut_us(const PassCost &c, int64_t d) {
+    if (c.reads[1] <= c.reads[0]) return gather_us(c, false, d);
+    const int lpr = pick_lpr(d), w = lpr == 4 ? 0 : lpr == 8 ? 1 : lpr == 16 ? 2 : lpr == 32 ? 3 : 4;
+    const int64_t chunk = 4 * std::min(lpr, c.lanes), chunks = (d + chunk - 1) / chunk;
+    const double reads = c.reads[0] + c.reads[1], line_bytes = 128 * row_lines(d, chunk);
+    return 4.5 + 4. * c.launches + reads * (2.24e-6 * (double)chunks + 2.01e-8 * 4. * (double)(chunks * chunk) + 1.18e-8 * line_bytes) + 2.86e-8 * line_bytes * c.miss[w] +
+           4e-6 * (double)d * (0.09 * c.slots + 0.3055 * c.rows);
+}
+
+// The tiles of the lists and the rest (us): the launches and the longest unit whatever the size, the steps and the lines their rows touch, the rest's gather.
 static double tiles_us(const Tiles &t, int64_t d) {
     const int vec = dense_vec(d);
-    const double chunks = std::ceil((double)d / (16 * vec)), steps = (double)t.ptr.back(), step = vec == 1 ? 0.6e-3 : vec == 2 ? 0.9e-3 : 1.4e-3;
-    return 50. + steps * chunks * step + 1e-6 * (double)t.n_slots * (double)d + gather_us(t.cost, false, d);
+    const double chunks = std::ceil((double)d / (16 * vec)), steps = (double)t.ptr.back(), step = vec == 1 ? 0. : vec == 2 ? 0.56e-3 : 1.77e-3;
+    return 36.9 + steps * (chunks * step + 0.386e-3 * row_lines(d, 16 * vec)) + cut_us(t.cost, d);
 }
 bool tiles_pay(const hag_handle *h, bool backward, int64_t d) {
     const Tiles &t = h->tiles[backward && !h->symmetric];
-    return t.on && (h->knobs.tiles > 1 || tiles_us(t, d) < 0.9 * gather_us(h->cost[1][backward], false, d));
+    return t.on && (h->knobs.tiles > 1 || tiles_us(t, d) < cut_us(h->cost[1][backward], d));
 }
 
 // Predictions this close are taken as equal: the lists then serve graphs below 16 M edges (where the community graphs measured gained from them) and
@@ -152,7 +170,8 @@ int cheapest_form(const hag_handle *h, const FormQuery &q) {
     const auto list_form = [&](bool lists) {
         const size_t lds = q.component_lds[lists];
         if (lds > 0) return component_us(h, lists, q.backward, q.d, lds);
-        return lists && tiles ? tiles_us(h->tiles[q.backward && !h->symmetric], q.d) : gather_us(h->cost[lists][q.backward], max, q.d);
+        if (tiles) return lists ? tiles_us(h->tiles[q.backward && !h->symmetric], q.d) : cut_us(h->cost[0][q.backward], q.d);
+        return gather_us(h->cost[lists][q.backward], max, q.d);
     };
     // (without aggregation nodes the pass over the HAG is the one over the lists)
     const bool choose = q.hag_allowed && q.lists_allowed && (h->a > 0 || tiles);

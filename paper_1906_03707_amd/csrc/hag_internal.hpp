@@ -83,6 +83,7 @@ inline bool several_streams(double reads, double items, bool max) { return reads
 constexpr int kWidths = 5;
 struct PassCost {
     double launches = 0;
+    int lanes = 32;                  // Plan::lanes of its launches that are cut by source
     double reads[2] = {0, 0};        // rows gathered, by launches over all sources and by launches cut by source
     double rows = 0;                 // rows written
     double slots = 0;                // partial rows written and folded

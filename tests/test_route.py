@@ -141,3 +141,18 @@ def test_workspace_of_a_batch_holds_nothing_for_lists():
     # and an option given later does not need more than was told before
     h.set_option(B.HAG_OPT_LIST_FORMS, 1)
     assert h.workspace_bytes("mean", B.HAG_F32, 64) == 0
+
+
+@pytest.mark.parametrize("n,degree,tiles,lists", [
+    # forward sums timed over the lists and as tiles and a rest, us, at the widths where the line lies:
+    (65536, 128, (132, 192, 256, 320, 512), (8, 16, 32, 64, 100, 128)),   # 389 / 340, 369 / 302, 412 / 374, 583 / 473, 821 / 748; 55 / 75, 58 / 77, 74 / 94, 118 / 145, 206 / 260, 211 / 216
+    (30000, 150, (192, 320, 512), (16, 64, 128)),                         # 203 / 168, 314 / 249, 422 / 370; 37 / 59, 71 / 106, 117 / 136
+    (65536, 60, (), (16, 64, 128, 132, 256, 512)),                        # 45 / 61, 66 / 118, 111 / 156, 196 / 227, 207 / 235, 408 / 435
+    (131072, 120, (132, 256, 512), (16, 64, 100))])                       # 760 / 691, 835 / 789, 1664 / 1553; 103 / 108, 211 / 229, 394 / 513
+def test_widths_where_a_sum_runs_as_tiles(n, degree, tiles, lists):
+    rowptr, col = synth.dcsbm(n=n, mean_degree=float(degree), seed=103 if n < 131072 else 22)[:2]
+    h = B.hag_from_merges(rowptr, col, np.zeros(0, np.int32), np.zeros(0, np.int32))
+    # (what a sum of floats needs beyond one of integers is the tiles' partial rows)
+    takes = lambda d: h.workspace_bytes("sum", B.HAG_F32, d) > h.workspace_bytes("sum", B.HAG_I32, d)   # noqa: E731
+    assert [d for d in tiles if not takes(d)] == [] == [d for d in lists if takes(d)]
+    assert {h.route("sum", d=d) for d in tiles} <= {"lists"}

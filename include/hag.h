@@ -283,7 +283,7 @@ int hag_forward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d,
  * naive aggregation): gx[u] = sum over consumers of u.  sum/mean run over the
  * transposed HAG, deepest level first; max uses only argmax
  * (gx[argmax[v,f], f] += gy[v,f], fp32 order not fixed; it may be called without a
- * workspace and then adds with device-wide atomics, slower where n * d >= 2^20).
+ * workspace and then adds with device-wide atomics, slower where n * d >= 2^20 unless the columns are few and the nodes many).
  * gx is overwritten. */
 int hag_backward(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d,
                  const void *gy, const int32_t *argmax, void *gx, void *workspace, void *stream);

@@ -590,7 +590,7 @@ static int backward_impl(const hag_handle *h, bool naive, hag_op_t op, int64_t d
     if (route == HAG_ROUTE_SCATTER) {
         int64_t total = h->n * d;
         if (total == 0 || !(phases & HAG_PHASE_GATHER)) return HAG_OK;
-        if (ws && max_scatter_bytes(h->n, d) > 0) return launch_max_scatter<T>(h->n, d, gy, argmax, gx, ws, s);
+        if (ws && max_scatter_bytes(h->n, d, std::is_same<T, float>::value ? HAG_F32 : HAG_I32) > 0) return launch_max_scatter<T>(h->n, d, gy, argmax, gx, ws, s);
         hipLaunchKernelGGL((fill_zero_kernel<T>), dim3((unsigned)((total / 4 + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                            s, gx, total / 4);
         HIP_TRY(hipGetLastError());
@@ -778,7 +778,7 @@ static size_t forward_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t
 
 size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d) {
     if (!h || d <= 0) return 0;
-    return std::max({forward_bytes(h, op, dt, d), pass_bytes(h, op, d) + scaled_bytes(h, op, d) + tiles_bytes(h, true, op, dt, d), op == HAG_MAX ? max_scatter_bytes(h->n, d) : 0});
+    return std::max({forward_bytes(h, op, dt, d), pass_bytes(h, op, d) + scaled_bytes(h, op, d) + tiles_bytes(h, true, op, dt, d), op == HAG_MAX ? max_scatter_bytes(h->n, d, dt) : 0});
 }
 
 static int forward_entry(const hag_t *h, bool naive, hag_op_t op, hag_dtype_t dt, int64_t d, const void *x, void *y,

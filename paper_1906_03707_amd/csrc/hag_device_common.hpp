@@ -376,7 +376,7 @@ int launch_component_kernel(const CompArgs<T> &a, int role, int64_t d, unsigned 
 
 // Transposed pass of max, gradients sorted by winner (hag_scatter.hip).  max_scatter_bytes: the scratch it needs, 0 where it does not apply.
 constexpr int64_t kBinMaxNodes = 1 << 21, kBinMinElements = 1 << 20;
-size_t max_scatter_bytes(int64_t n, int64_t d);
+size_t max_scatter_bytes(int64_t n, int64_t d, hag_dtype_t dt);
 template <typename T>
 int launch_max_scatter(int64_t n, int64_t d, const T *gy, const int32_t *argmax, T *gx, void *ws, hipStream_t s);
 

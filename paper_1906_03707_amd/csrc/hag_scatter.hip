@@ -16,7 +16,11 @@ namespace hag {
 // 131072 nodes, d = 128, winners anywhere: 809 us with atomics, 163 in blocks (int32 634 and 114: LDS adds 32-bit integers faster than floats); winners of a
 //     graph with communities 990 and 165; one node winning everything 3160 and 313; 232965 nodes, d = 16: 185 and 60.
 // From 2^20 elements: 16384 x 64 55 us with atomics and 46 in blocks, 65536 x 16 55 and 34, but 8192 x 64 30 and 43, 16384 x 36 33 and 34 (three launches, and few
-//     workgroups).  Up to 2^21 nodes: the histogram is 16 KB of LDS then and runs average four elements (2000000 x 64: 6517 and 2518 us).
+//     workgroups).  Up to 2^21 nodes: the histogram is 16 KB of LDS then (2000000 x 64: 6517 and 2518 us).
+// Few columns of many nodes stay with the atomics: a block's workgroup looks up its run in the table of every tile (tiles x blocks entries), and the runs of 512 rows hold an element or
+//     two.  us, atomics / blocks, winners anywhere: 4 columns of 262145 nodes 56 / 49, 524288 106 / 99, 700000 140 / 158, 1000003 198 / 243, 2000000 391 / 651; 8 of 1000003 390 / 281,
+//     1500000 582 / 513, 2000000 774 / 796; 12 of 2000000 1157 / 897.  Atomics of integers are a fifth faster: 4 of 262145 44 / 49, 1000003 155 / 239; 8 of 1000003 307 / 281, 1500000 456 / 508,
+//     2000000 606 / 791; 12 of 1500000 681 / 566.  blocks_us below is those with the table's lookups at 50 ps each.
 // 32 columns: wider tiles would make the blocks of a 64 KB accumulator shorter and the runs with them; narrower ones read less than a cache line.
 // Every element is added once; the order inside a run and between runs is not fixed, as it was not with the atomics.
 constexpr int kBinRows = 512, kBinNodes = 512, kBinCols = 32, kBinThreads = 1024, kBinElems = kBinRows * kBinCols, kBinQuads = kBinElems / 4 / kBinThreads;
@@ -37,9 +41,11 @@ static BinShape bin_shape(int64_t n, int64_t d) {
 
 static size_t align_256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-size_t max_scatter_bytes(int64_t n, int64_t d) {
+size_t max_scatter_bytes(int64_t n, int64_t d, hag_dtype_t dt) {
     if (n <= 0 || n > kBinMaxNodes || n * d < kBinMinElements) return 0;
     const BinShape b = bin_shape(n, d);
+    const double elements = (double)n * (double)d, blocks_us = 33. + 50e-6 * (double)b.tiles * (double)b.blocks * (double)b.chunks + 8e-6 * elements;
+    if (blocks_us > 5. + (dt == HAG_F32 ? 48e-6 : 38e-6) * elements) return 0;
     const size_t segments = (size_t)(b.tiles * b.chunks), elems = segments * (size_t)(kBinRows * b.cols);
     return align_256(elems * 4) + align_256(elems * 2) + align_256(segments * (size_t)b.pitch * 2) + align_256((size_t)(b.blocks * b.chunks) * 4) +
            align_256((kFoldExtra * 2 + 2) * 4);

@@ -156,3 +156,13 @@ def test_widths_where_a_sum_runs_as_tiles(n, degree, tiles, lists):
     takes = lambda d: h.workspace_bytes("sum", B.HAG_F32, d) > h.workspace_bytes("sum", B.HAG_I32, d)   # noqa: E731
     assert [d for d in tiles if not takes(d)] == [] == [d for d in lists if takes(d)]
     assert {h.route("sum", d=d) for d in tiles} <= {"lists"}
+
+
+def test_max_sorts_its_gradients_only_where_the_runs_are_long_enough():
+    # a ring of nodes needs no other workspace: sorted gradients (6 bytes an element and tables), or none where atomics are faster.  Times, us, atomics / sorted:
+    # f32 106 / 99, 140 / 158, 391 / 651, 390 / 281, 774 / 796, 1157 / 897, 55 / 46; i32 84 / 98, 307 / 281, 456 / 508, 681 / 566
+    for dt, sorts, adds in ((B.HAG_F32, ((524288, 4), (1000003, 8), (2000000, 12), (16384, 64)), ((700000, 4), (2000000, 4), (2000000, 8))),
+                            (B.HAG_I32, ((1000003, 8), (1500000, 12)), ((524288, 4), (1500000, 8)))):
+        for n, d in sorts + adds:
+            h = B.hag_from_merges(np.arange(n + 1, dtype=np.int64), ((np.arange(n) + 1) % n).astype(np.int32), np.zeros(0, np.int32), np.zeros(0, np.int32))
+            assert (h.workspace_bytes("max", dt, d) >= 6 * n * d) == ((n, d) in sorts), (dt, n, d)

@@ -1298,15 +1298,15 @@ static int finalize_from_builder(hag_handle *h, Builder &b) {
     for (Tiles &t : h->tiles) t = Tiles{};
     h->symmetric = h->g.ptr == h->gt.ptr && h->g.col == h->gt.col;
     h->knobs.tiles = (int32_t)env_i64("HAG_TILES", 1);
-    // (below half a million entries a pass takes about as long as its launches)
-    if (h->knobs.tiles > 0 && h->e >= env_i64("HAG_TILES_MIN_ENTRIES", 500000)) {
+    build_components(h);
+    // (below half a million entries a pass takes about as long as its launches; sums over a batch of small graphs run as dense products)
+    if (h->knobs.tiles > 0 && !h->comp.dense && h->e >= env_i64("HAG_TILES_MIN_ENTRIES", 500000)) {
         build_tiles(h->g, n, part, h->tiles[0]);
         if (!h->symmetric) build_tiles(h->gt, n, part, h->tiles[1]);
     }
     h->max_slots = std::max({h->p_fwd.n_slots, h->p_bwd_src.n_slots, h->p_naive_fwd.n_slots, h->p_naive_bwd.n_slots});
     for (auto &p : h->p_bwd_stage) h->max_slots = std::max(h->max_slots, p.n_slots);
     for (auto &p : h->p_fwd_stage) h->max_slots = std::max(h->max_slots, p.n_slots);
-    build_components(h);
     for (auto &form : h->cost) for (PassCost &c : form) c = PassCost{};
     for (Tiles &t : h->tiles)
         if (t.on) {
@@ -1324,6 +1324,12 @@ static int finalize_from_builder(hag_handle *h, Builder &b) {
             c.miss[i >> 2] = part[i].miss[i >> 2];
             c.fold[i >> 2] = part[i].fold[i >> 2];
         }
+    }
+    for (const bool backward : {false, true}) {            // tiles that no width would take are neither kept nor uploaded
+        if (backward && h->symmetric) break;
+        bool some = false;
+        for (int64_t d = 4; d <= 1024 && !some; d += 4) some = tiles_pay(h, backward, d) || (h->symmetric && tiles_pay(h, true, d));
+        if (!some) h->tiles[backward] = Tiles{};
     }
     // statistics (Section 4.1: k in-neighbours cost k-1 binary aggregations; Section 5.4: one
     // row transfer per aggregated neighbour)

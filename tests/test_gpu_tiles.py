@@ -166,3 +166,20 @@ def test_the_fixed_scratch_array_serves_what_a_forward_pass_needs(B, monkeypatch
         want = h.forward(x, op)
         assert not torch.equal(want, plain.forward(x, op))    # another order of additions: tiles ran
         assert torch.equal(h.forward_static_scratch(x, op), want)
+
+
+@pytest.mark.parametrize("kind", ["batch", "blocks"])
+def test_handles_that_take_no_tiles_keep_none(B, monkeypatch, kind):
+    # dense products serve the batch at every width, and the lists the blocks (12 of 1300 nodes: d = 128 50 us, as tiles and a rest 100; 512 184 and 262)
+    from paper_1906_03707_amd import synth
+    rowptr, col = synth.er_batch(1000, 74, 0.9, seed=104)[:2] if kind == "batch" else synth.sbm(12, 1300, 0.1, 0.0005, seed=5)[:2]
+    none, held = np.zeros(0, np.int32), []
+    for tiles in ("1", "0"):
+        monkeypatch.setenv("HAG_TILES", tiles)
+        h = B.hag_from_merges(rowptr, col, none, none)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        h.upload()
+        held.append(before - torch.cuda.mem_get_info()[0])
+        del h
+    assert held[0] <= held[1] + 4 * col.size // 4          # (a quarter of what a second copy of the lists would take)

@@ -145,8 +145,9 @@ class _Gcn2Loss(torch.autograd.Function):
                                            and a1.data_ptr() % 16 == 0 and labels.is_contiguous()):
             # to be differentiated itself, or the saved tensors came back from hooks as something else
             wanted = [t for t, need in ((x, need_x), (w1, need_1), (w2, need_2)) if need]
+            again = torch.is_grad_enabled()
             with torch.enable_grad():
-                inner = iter(torch.autograd.grad(_gcn2_composed(ctx.h, x, w1, w2, labels, ctx.naive, None), wanted, g, create_graph=torch.is_grad_enabled()))
+                inner = iter(torch.autograd.grad(_gcn2_composed(ctx.h, x, w1, w2, labels, ctx.naive, None), wanted, g, create_graph=again))
             return (*(next(inner) if need else None for need in (need_x, need_1, need_2)), None, None, None)
         back = ctx.h.naive_backward if ctx.naive else ctx.h.backward
         g_z2 = back(binding.softmax_loss_grad(logits, labels, counted, g.contiguous()), "gcn")

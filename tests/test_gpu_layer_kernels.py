@@ -168,3 +168,16 @@ def test_gradients_keep_no_graph_when_hooks_return_saved_tensors_as_something_el
     got, want = torch.autograd.grad(loss, (w1, w2)), torch.autograd.grad(layers.gcn2_loss(h, x, w1, w2, labels), (w1, w2))
     for a, b in zip(got, want):
         assert not a.requires_grad and (a - b).norm().item() <= 1e-5 * b.norm().item()
+
+
+@pytest.mark.parametrize("n,d,k", [(70001, 64, 16), (70001, 68, 33), (200003, 12, 70), (40000, 132, 5)])
+@pytest.mark.parametrize("relu", [False, True])
+def test_weight_grad_takes_every_row_once(B, n, d, k, relu):
+    # small whole numbers: sums below 2^24 are exact in any order, so a row left out or taken twice shows (wavefronts go many times round their stride here)
+    gen = torch.Generator(device="cuda").manual_seed(n + d + k)
+    x = torch.randint(-3, 4, (n, d), device="cuda", generator=gen).float()
+    g = torch.randint(1, 4, (n, k), device="cuda", generator=gen).float()
+    z = torch.relu(x) if relu else x
+    want = z.double().t() @ g.double()
+    assert (z.double().abs().t() @ g.double()).max().item() < 1 << 24
+    assert torch.equal(B.weight_grad(x, g, relu=relu), want.float())

@@ -52,9 +52,11 @@ def product(x, w):
     """x @ w for a tall x [n, d] and a small w [d, k].
 
     The gradient of w is the library's up to d * k = 65536: 65536 rows, 64 x 16 14 us against the BLAS's 82, 16 x 16 15 and 174, 256 x 256 144 and 217 (its
-    error against 64 bits 2e-7 and 2e-6); beyond, it reads x and g too many times (370000 rows, 256 x 256: 784 and 878)."""
+    error against 64 bits 2e-7 and 2e-6); beyond, it reads x and g too many times (370000 rows, 256 x 256: 784 and 878).  Below 32768 rows and 2^25 products it
+    saves less than a node of the graph in Python costs the host (forward and backward 57 us, torch's 53: 16384 rows, 64 x 16; 57 and 66: 8192 rows, 128 x 64)."""
     if (torch.is_grad_enabled() and w.requires_grad and _plain(x) and _plain(w) and x.shape[1] == w.shape[0] and x.shape[1] % 4 == 0
-            and 0 < w.numel() <= 65536 and max(w.shape) <= 4096 and not torch.is_autocast_enabled()):
+            and 0 < w.numel() <= 65536 and max(w.shape) <= 4096 and (x.shape[0] >= 32768 or x.shape[0] * w.numel() >= 1 << 25)
+            and not torch.is_autocast_enabled()):
         return _Product.apply(x, w)
     return x @ w
 
@@ -78,8 +80,9 @@ class _SoftmaxLoss(torch.autograd.Function):
 
 def softmax_loss(z, labels):
     """torch.nn.functional.cross_entropy(z, labels) by hag_softmax_loss where the arguments are of the ordinary kind (65536 rows, 16 classes, both
-    passes: 27 us against 113, 300 classes 100 and 234)."""
-    if _plain(z) and _plain_labels(labels, z) and 0 < z.shape[1] <= 1 << 20 and not torch.is_autocast_enabled():
+    passes: 27 us against 113, 300 classes 100 and 234) and there are 2^19 logits or more (as above: 16384 rows of 40 a whole step 496 us against 532, below
+    49 us against torch's 43)."""
+    if _plain(z) and _plain_labels(labels, z) and 0 < z.shape[1] <= 1 << 20 and z.numel() >= 1 << 19 and not torch.is_autocast_enabled():
         return _SoftmaxLoss.apply(z, labels)
     return torch.nn.functional.cross_entropy(z, labels)
 
@@ -161,7 +164,9 @@ class _Gcn2Loss(torch.autograd.Function):
 
 
 def _narrow(d, k):
-    """What hag_narrow_product takes both ways round, within the sizes where it and hag_weight_grad are the faster side."""
+    """What hag_narrow_product takes both ways round.  A step as one node was faster than one of the library's products, ReLU and loss at every size timed (8000 to 370000 rows, weights up to
+    256 x 256: 126 / 238 us at 8000 rows, 128 x 128 and 128 x 16; 5202 / 5903 at 370000, 256 x 256 twice); the wide products by themselves are not (x is read once per 64 columns of the
+    weight: 65536 rows, 256 x 256 139 us, the BLAS library 75), the weight gradients and the passes left out make up for it."""
     return d % 4 == 0 and k % 4 == 0 and 0 < d <= 256 and 0 < k <= 256
 
 

@@ -181,3 +181,28 @@ def test_weight_grad_takes_every_row_once(B, n, d, k, relu):
     want = z.double().t() @ g.double()
     assert (z.double().abs().t() @ g.double()).max().item() < 1 << 24
     assert torch.equal(B.weight_grad(x, g, relu=relu), want.float())
+
+
+def test_small_calls_take_the_library_and_large_ones_are_the_same_under_autograd(B):
+    # (what a node of the graph in Python costs the host is more than small calls gain)
+    from paper_1906_03707_amd import layers
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen)   # noqa: E731
+    name = lambda t: type(t.grad_fn).__name__   # noqa: E731
+    for n, d, k, own in ((1000, 64, 16, False), (16384, 64, 16, False), (8192, 128, 64, True), (32768, 16, 16, True), (1000, 256, 256, True)):
+        assert (name(layers.product(rnd(n, d), rnd(d, k).requires_grad_())) == "_ProductBackward") == own, (n, d, k)
+    for n, k, own in ((1000, 16, False), (16384, 16, False), (32768, 16, True), (16384, 40, True)):
+        assert (name(layers.softmax_loss(rnd(n, k).requires_grad_(), torch.zeros(n, dtype=torch.int64, device="cuda"))) == "_SoftmaxLossBackward") == own, (n, k)
+    x, w, labels = rnd(90000, 20), rnd(20, 6), torch.randint(0, 6, (90000,), device="cuda", generator=gen)
+    labels[::9] = -100
+    results = []
+    for product, loss in ((layers.product, layers.softmax_loss), (torch.matmul, torch.nn.functional.cross_entropy)):
+        xx, ww = x.clone().requires_grad_(), w.clone().requires_grad_()
+        value = loss(product(xx, ww), labels)
+        first = torch.autograd.grad(value, (xx, ww), create_graph=True)
+        second = torch.autograd.grad(sum((g ** 2).sum() for g in first), (xx, ww))
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t.cpu(), lambda t: t.cuda()):
+            hooked = loss(product(xx, ww), labels)
+        results.append((value, *first, *second, *torch.autograd.grad(loss(product(xx, ww), labels) * 2, (xx, ww)), *torch.autograd.grad(hooked, (xx, ww))))
+    for a, b in zip(*results):
+        assert a.shape == b.shape and (a - b).norm().item() <= 1e-5 * b.norm().item()

@@ -23,6 +23,11 @@ def _plain(t):
             and t.is_contiguous() and t.get_device() == torch.cuda.current_device())
 
 
+def _no_tangent(*tensors):
+    """None of them carries a forward-mode derivative, which the nodes below do not pass on."""
+    return all(torch.autograd.forward_ad.unpack_dual(t).tangent is None for t in tensors)
+
+
 def _plain_labels(labels, z):
     return (type(labels) is torch.Tensor and labels.dtype == torch.int64 and labels.dim() == 1 and labels.device == z.device and labels.is_contiguous()
             and labels.shape[0] == z.shape[0])
@@ -56,7 +61,7 @@ def product(x, w):
     saves less than a node of the graph in Python costs the host (forward and backward 57 us, torch's 53: 16384 rows, 64 x 16; 57 and 66: 8192 rows, 128 x 64)."""
     if (torch.is_grad_enabled() and w.requires_grad and _plain(x) and _plain(w) and x.shape[1] == w.shape[0] and x.shape[1] % 4 == 0
             and 0 < w.numel() <= 65536 and max(w.shape) <= 4096 and (x.shape[0] >= 32768 or x.shape[0] * w.numel() >= 1 << 25)
-            and not torch.is_autocast_enabled()):
+            and not torch.is_autocast_enabled() and _no_tangent(x, w)):
         return _Product.apply(x, w)
     return x @ w
 
@@ -82,7 +87,7 @@ def softmax_loss(z, labels):
     """torch.nn.functional.cross_entropy(z, labels) by hag_softmax_loss where the arguments are of the ordinary kind (65536 rows, 16 classes, both
     passes: 27 us against 113, 300 classes 100 and 234) and there are 2^19 logits or more (as above: 16384 rows of 40 a whole step 496 us against 532, below
     49 us against torch's 43)."""
-    if _plain(z) and _plain_labels(labels, z) and 0 < z.shape[1] <= 1 << 20 and z.numel() >= 1 << 19 and not torch.is_autocast_enabled():
+    if _plain(z) and _plain_labels(labels, z) and 0 < z.shape[1] <= 1 << 20 and z.numel() >= 1 << 19 and not torch.is_autocast_enabled() and _no_tangent(z):
         return _SoftmaxLoss.apply(z, labels)
     return torch.nn.functional.cross_entropy(z, labels)
 

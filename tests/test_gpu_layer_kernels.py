@@ -206,3 +206,18 @@ def test_small_calls_take_the_library_and_large_ones_are_the_same_under_autograd
         results.append((value, *first, *second, *torch.autograd.grad(loss(product(xx, ww), labels) * 2, (xx, ww)), *torch.autograd.grad(hooked, (xx, ww))))
     for a, b in zip(*results):
         assert a.shape == b.shape and (a - b).norm().item() <= 1e-5 * b.norm().item()
+
+
+def test_forward_mode_derivatives_of_the_last_product_and_the_loss(B):
+    # what comes after the last aggregation can be differentiated forwards, as with the library's product and loss
+    from paper_1906_03707_amd import layers
+    import torch.autograd.forward_ad as fw
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    x, w, v = (torch.randn(*s, device="cuda", generator=gen) for s in ((40000, 20), (20, 16), (20, 16)))
+    labels = torch.randint(0, 16, (40000,), device="cuda", generator=gen)
+    tangents = []
+    for product, loss in ((layers.product, layers.softmax_loss), (torch.matmul, torch.nn.functional.cross_entropy)):
+        for grad in (False, True):
+            with fw.dual_level():
+                tangents.append(fw.unpack_dual(loss(product(x, fw.make_dual(w.clone().requires_grad_(grad), v)), labels)).tangent)
+    assert all(t is not None and (t - tangents[-1]).abs().item() <= 1e-5 * tangents[-1].abs().item() for t in tangents)

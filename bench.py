@@ -31,12 +31,15 @@ LDS_PEAK_GBS = 256 * 64 * 4 * 2.4
 
 # L2 fills + write-backs per launch of the dominant kernel, from separate rocprofv3 --pmc runs of this
 # file (FETCH_SIZE, WRITE_SIZE, scaled by what the same counters read for --copy-calibration's
-# known copy); the summaries are in profiles/.  Not measured by the run that prints them.
+# known copy); the summaries are in profiles/.  Not measured by the run that prints them.  Last of a key: whether the
+# lists run as tiles and a rest; those entries are sums over the kernels of a forward pass, with the L2s' requests.
 PROFILED_TRAFFIC = {
-    ("config2:holme_kim56944", 128, "sum"): dict(fetch=310725 * 2048, write=28472 * 1024,
+    ("config2:holme_kim56944", 128, "sum", False): dict(fetch=310725 * 2048, write=28472 * 1024,
                                                   source="profiles/pmc_config2_holme_kim56944_d128_sum.txt"),
-    ("config3:dcsbm232965", 128, "sum"): dict(fetch=6014900 * 2048, write=931865 * 1024,
+    ("config3:dcsbm232965", 128, "sum", False): dict(fetch=6014900 * 2048, write=931865 * 1024,
                                                source="profiles/pmc_config3_dcsbm232965_d128_sum.txt"),
+    ("config3:dcsbm232965", 128, "sum", True): dict(fetch=3872342 * 2048, write=1570566 * 1024, requests=263433000 * 128,
+                                                    source="profiles/pmc_config3_dcsbm232965_d128_sum_tiles.txt"),
 }
 
 
@@ -657,6 +660,8 @@ def main():
     workload = f"config{cfg}:{synth.CONFIGS[cfg]['name']}"
     ceil = measure_ceilings(torch, binding, d) if not args.no_ceilings else None
 
+    prof = PROFILED_TRAFFIC.get((workload, d, op, tiled)) if args.capacity < 0 else None   # (the gather over the HAG or the lists; tiled: the whole forward pass)
+
     # Which limit binds.  Rows of a cache-resident matrix never reach HBM, so algorithmic bytes per second may
     # exceed the HBM peak: the gather is then priced against what the L2s can hand to the compute units (peak
     # derived from unit counts and clock; beside it what hag_probe_rows reaches on this machine), the
@@ -673,13 +678,21 @@ def main():
         bound, peak, ceiling = "lds", LDS_PEAK_GBS, measured("lds_rows_GBps")
         rows = (st["e_hag"] + n + st["a"]) if way == "component_hag" else e + n
         achieved_bound = row * rows / (ms_gather * 1e-3) / 1e9
+    elif tiled:
+        # a tile reads a source's row once for all its rows, so the lists' entries count reads that are not made: the L2s' requests as counted
+        # where this workload was profiled, else what has to move at least (rows in and out, ids once)
+        if prof is not None:
+            bound, peak, ceiling = "l2", L2_PEAK_GBS, measured("l2_resident_rows_GBps")
+            achieved_bound = prof["requests"] / (ms_gather * 1e-3) / 1e9
+        else:
+            bound, peak, ceiling = "hbm", HBM_PEAK_GBS, measured("copy_1GiB_read_plus_write_GBps")
+            achieved_bound = (2 * row * n + 4 * e) / (ms_gather * 1e-3) / 1e9
     elif achieved > HBM_PEAK_GBS * 0.6:
         bound, peak, ceiling = "l2", L2_PEAK_GBS, measured("l2_resident_rows_GBps")
         achieved_bound = achieved
     else:
         bound, peak, ceiling = "hbm", HBM_PEAK_GBS, measured("hbm_rows_GBps")
         achieved_bound = achieved
-    prof = PROFILED_TRAFFIC.get((workload, d, op)) if args.capacity < 0 and not tiled else None   # (the profiled launch is the gather over the HAG or the lists)
     roofline = {"bound": bound, "achieved": achieved_bound, "peak": peak, "unit": "GB/s", "frac": achieved_bound / peak,
                 "traffic": None if prof is None else prof["fetch"] + prof["write"],
                 "kernel": kernel_name, "kernel_ms": ms_gather, "algorithmic_bytes": gather_bytes,

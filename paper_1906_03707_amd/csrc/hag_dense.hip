@@ -196,9 +196,9 @@ int launch_dense(DenseArgs a, int role, int max_nodes, hipStream_t s) {
 
 // The tiles of a list set: 128 rows of the output against the sources that at least five of them name, the same products as above with a gathered operand.  A list entry costs a
 // gather one row read, mostly out of L2; here a source's row is read once per tile, whatever the number of rows that name it.  Graphs with communities have half of
-// their entries in such (tile, source) pairs, twelve to a pair on average.  What bounds it: the rows come from beyond L2 (neighbouring tiles go to one XCD, which
-// helps little, as a tile names a thousand sources), so a pair costs about as much as three or four list entries, and pairs of three (212 us for 64 k steps instead of 121 for 33 k) gain
-// nothing over the lists.  Whole forward sums, lists / tiles and rest, us: 131072 nodes, 26 M edges, d = 64 331 / 305, 128 634 / 569, 512 2696 / 2245; 65536 nodes, 8.4 M edges, d = 256 409 / 373,
+// their entries in such (tile, source) pairs, twelve to a pair on average.  What bounds it are the instructions: vector instructions issue 69 % of the time and the matrix cores are busy
+// 34 % of it, one after the other (131072 nodes, d = 128: 0.8 GB of L2 requests, 0.28 GB of fills and 0.13 GB of writes in 162 us).  A pair costs about as much as three or four list
+// entries, and pairs of three (212 us for 64 k steps instead of 121 for 33 k) gain nothing over the lists.  Whole forward sums, lists / tiles and rest, us: 131072 nodes, 26 M edges, d = 64 331 / 305, 128 634 / 569, 512 2696 / 2245; 65536 nodes, 8.4 M edges, d = 256 409 / 373,
 // 512 826 / 746, but 64 119 / 146, 16 58 / 78 (where the line lies: tiles_us in hag_cost.cpp).
 // A wavefront takes a unit, at most 24 steps of 32 sources of a tile, and 16 * VEC columns; tiles of more steps are added up by the fold, like cut rows.  Shorter units cost more partial
 // rows than they gain, longer ones leave the smaller graphs waiting for the last of them (steps 16 / 24 / 32: 131072 nodes, d = 128, 595 / 569 / 560 us; 65536 nodes, d = 256, 388 / 373 / 383).

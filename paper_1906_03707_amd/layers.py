@@ -95,7 +95,8 @@ def softmax_loss(z, labels):
 def aggregation(h, op, naive=False, record=None):
     """torch.autograd.Function around hag_forward / hag_backward (or the naive-CSR kernels) for `op`.
 
-    record: optional list; every call appends (kind, input tensor, output tensor[, argmax])."""
+    record: optional list; every call appends (kind, input tensor, output tensor[, argmax]).  Its backward pass is not itself differentiable: second derivatives
+    leave out what passes through it."""
     fwd = h.naive_forward if naive else h.forward
     bwd = h.naive_backward if naive else h.backward
 
@@ -151,7 +152,7 @@ class _Gcn2Loss(torch.autograd.Function):
         need_x, need_1, need_2 = ctx.needs_input_grad[:3]
         if torch.is_grad_enabled() or not (_plain(x) and _plain(w1) and _plain(w2) and _plain(a1) and _plain(logits) and x.data_ptr() % 16 == 0
                                            and a1.data_ptr() % 16 == 0 and labels.is_contiguous()):
-            # to be differentiated itself, or the saved tensors came back from hooks as something else
+            # to be differentiated itself (as far as the composed form is: not through an aggregation), or the saved tensors came back from hooks as something else
             wanted = [t for t, need in ((x, need_x), (w1, need_1), (w2, need_2)) if need]
             again = torch.is_grad_enabled()
             with torch.enable_grad():

@@ -264,6 +264,8 @@ int hag_upload(hag_t *h, void *stream);
  * contents need not survive between calls: nothing is memorised for the backward
  * pass except argmax (Algorithm 2's caption). */
 size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d);
+/* The part of it that forward passes need (what the transposed pass of max sorts and the rows that of mean and gcn scales are not theirs). */
+size_t hag_forward_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dtype, int64_t d);
 
 /* Algorithm 2 without the Update line: aggregation nodes level by level, then
  * y[v] = Aggregate over Nhat_v for every v in V.  x, y: device [n, d].

@@ -33,7 +33,7 @@ EXPORTS = [
     "hag_backward", "hag_forward_phases", "hag_backward_phases", "hag_naive_forward", "hag_naive_backward",
     "hag_algorithmic_bytes", "hag_last_error", "hag_forward_static_scratch", "hag_probe_rows", "hag_probe_copy", "hag_probe_mfma_f32", "hag_set_option", "hag_check", "hag_seq_search",
     "hag_seq_create", "hag_seq_free", "hag_seq_cells", "hag_seq_ranks", "hag_seq_launches", "hag_seq_get_plan", "hag_seq_set_option", "hag_seq_check", "hag_seq_train_workspace_bytes", "hag_seq_lstm_forward_train", "hag_seq_lstm_backward", "hag_seq_merges", "hag_seq_upload", "hag_seq_workspace_bytes",
-    "hag_seq_lstm_forward", "hag_route", "hag_naive_route",
+    "hag_seq_lstm_forward", "hag_route", "hag_naive_route", "hag_forward_workspace_bytes",
     "hag_weight_grad_workspace_bytes", "hag_weight_grad", "hag_narrow_product", "hag_softmax_loss_workspace_bytes", "hag_softmax_loss", "hag_softmax_loss_grad",
 ]
 ROUTES = ("hag", "lists", "component_hag", "component_lists", "dense", "one_launch", "scatter")   # HAG_ROUTE_*
@@ -75,8 +75,9 @@ def lib():
         L.hag_get_forward.argtypes = [vp, ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(vp),
                                       ctypes.POINTER(i32), ctypes.POINTER(vp), ctypes.POINTER(vp)]
         L.hag_upload.argtypes = [vp, vp]
-        L.hag_workspace_bytes.argtypes = [vp, ctypes.c_int, ctypes.c_int, i64]
-        L.hag_workspace_bytes.restype = ctypes.c_size_t
+        for name in ("hag_workspace_bytes", "hag_forward_workspace_bytes"):
+            getattr(L, name).argtypes = [vp, ctypes.c_int, ctypes.c_int, i64]
+            getattr(L, name).restype = ctypes.c_size_t
         for name in ("hag_forward", "hag_naive_forward"):
             getattr(L, name).argtypes = [vp, ctypes.c_int, ctypes.c_int, i64, vp, vp, vp, vp, vp]
         for name in ("hag_backward", "hag_naive_backward"):
@@ -277,14 +278,14 @@ class Hag:
                 raise ValueError(f"workspace holds {have} bytes on {workspace.device}, {need} needed on {a.device}")
 
     def _shape(self, what, a, op):
-        """(op code, dtype code, d, workspace bytes) of a call on a matrix of a's shape and dtype; raises what _check_args
+        """(op code, dtype code, d, workspace bytes, forward workspace bytes) of a call on a matrix of a's shape and dtype; raises what _check_args
         raises for `a`.  Looked up by value: a handle's sizes never change, so neither do the answers."""
         key = (op, a.dtype, a.shape)
         got = self._shapes.get(key)
         if got is None:
             self._check_args(what, a, op, None, None, None, False)
             code, d = _dtype_code(a), int(a.shape[1])
-            got = (OPS[op], code, d, self.workspace_bytes(op, code, d))
+            got = (OPS[op], code, d, self.workspace_bytes(op, code, d), int(lib().hag_forward_workspace_bytes(self._h, OPS[op], code, d)))
             if len(self._shapes) >= 256:
                 self._shapes.clear()
             self._shapes[key] = got
@@ -294,7 +295,7 @@ class Hag:
         # A call on a small graph takes about as long as preparing it, so everything that depends on sizes only is looked up, and
         # the stream is asked for once.
         import torch
-        op_code, code, d, nbytes = self._shape(what, a, op)
+        op_code, code, d, nbytes, forward_nbytes = self._shape(what, a, op)
         if out is not None or argmax is not None or workspace is not None or needs_argmax:
             self._check_args(what, a, op, out, argmax, workspace, needs_argmax)
         if not a.is_cuda or not a.is_contiguous():
@@ -307,9 +308,15 @@ class Hag:
         device = current_device()
         stream = raw_stream(device)
         if workspace is None:
-            # one buffer per (device, stream): calls enqueued on different streams may overlap
+            # one buffer per (device, stream): calls enqueued on different streams may overlap.  The transposed pass of max, where it needs more than
+            # forward passes brought, has one of its own: theirs may be in use by a captured graph and is not replaced
             index = a.get_device()
             key = (index, stream if index == device else raw_stream(index))
+            if op == "max":
+                if not backward:
+                    nbytes = forward_nbytes
+                elif nbytes > forward_nbytes and (key not in self._ws or self._ws[key].numel() < nbytes):
+                    key = (*key, "sorted")
             workspace = self._ws.get(key)
             if workspace is None or workspace.numel() < nbytes:
                 workspace = self._ws[key] = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=a.device)

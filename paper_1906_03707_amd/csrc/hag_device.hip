@@ -776,6 +776,8 @@ static size_t pass_bytes(const hag_t *h, hag_op_t op, int64_t d) { return !h || 
 // with room for the tiles of a forward pass
 static size_t forward_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d) { return pass_bytes(h, op, d) + tiles_bytes(h, false, op, dt, d); }
 
+size_t hag_forward_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d) { return !h || d <= 0 ? 0 : forward_bytes(h, op, dt, d); }
+
 size_t hag_workspace_bytes(const hag_t *h, hag_op_t op, hag_dtype_t dt, int64_t d) {
     if (!h || d <= 0) return 0;
     return std::max({forward_bytes(h, op, dt, d), pass_bytes(h, op, d) + scaled_bytes(h, op, d) + tiles_bytes(h, true, op, dt, d), op == HAG_MAX ? max_scatter_bytes(h->n, d, dt) : 0});

@@ -80,3 +80,24 @@ def test_replays_of_a_captured_call_and_what_the_forward_pass_needs(B):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(gx, (x * (k + 1)).roll(1, 0))
+
+
+def test_forward_passes_hold_no_room_for_sorted_gradients(B):
+    n, d = 65536, 64
+    h = ring(B, n)
+    x = torch.randn(n, d, device="cuda")
+    assert B.lib().hag_forward_workspace_bytes(h._h, B.HAG_MAX, B.HAG_F32, d) == 0 and h.workspace_bytes("max", B.HAG_F32, d) > 6 * n * d
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_allocated()
+    y, am = h.forward(x, "max")
+    assert torch.cuda.memory_allocated() - before <= 2 * 4 * n * d + 4096           # the results
+    # a captured forward pass keeps its workspace when a transposed one needs more
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        h.forward(x, "max", y=y, argmax=am)
+    kept = dict(h._ws)
+    gx = h.backward(y, "max", argmax=am)
+    assert all(h._ws[k] is w for k, w in kept.items())
+    x.copy_(torch.randn(n, d, device="cuda"))
+    graph.replay()
+    assert torch.equal(y, x.roll(-1, 0)) and torch.equal(h.backward(y, "max", argmax=am), y.roll(1, 0)) and gx.shape == y.shape

@@ -1004,11 +1004,19 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 }
 
 // Weight gradients: a contraction over many rows on the matrix cores, dW [4H, columns] = sum over rows of dG[row] z[row]^T.  A
-// workgroup of 8 wavefronts stages 32 rows at a time in LDS, wavefront w accumulates 32 rows of dW (tile w) against all
+// workgroup of 4 wavefronts stages 32 rows at a time in LDS, wavefront w accumulates 64 rows of dW (gate tiles 2 w and 2 w + 1) against all
 // column tiles; every workgroup ends with its own partial sums, which a second kernel adds up in a fixed order (so the weight
-// gradients do not depend on timing).  blockIdx.y selects a slab of 256 rows of dW (hidden > 64 has two).
+// gradients do not depend on timing).  blockIdx.y selects a slab of 256 rows of dW (hidden > 64 has two), blockIdx.z one of 32 NCT columns.
 //
-// SEG: the rows are cells, taken in the order of the input row they read (`at`, ascending `seg`), z is h_prev, and while a row of dG is in LDS
+// The operands are cut into three bf16 pieces (seq_split2) once, by the thread that loads them: a thread takes one column of dG for all 32 rows, so its
+// loads are contiguous over a wavefront, eight rows make one 16-byte operand of v_mfma_f32_32x32x16_bf16 per piece, and the sums of dG over a
+// node's rows run in its registers.  The matrix cores cut what they add to the size of the accumulator, always in the same direction, and a
+// gradient adds hundreds of thousands of rows: the products of 32 rows therefore begin at zero, the large ones apart from the small ones,
+// and join the running sums in rounded additions.  (Numbers below about 2^-110 lose their last pieces; infinities and NaN stay not finite.)
+// 3.35 M cells of 64 units: 1.41 ms with fp32 matrix instructions, 1.07 so (4.0 TB/s; vector instructions issue 59 % of the time, matrix cores are busy
+// 31 %); 0.85 M cells of 128 units: 1.33 and 0.93 ms.  Error of the training step's results against 64 bits 1.2e-6 and 5e-7, 6.4e-7 and 5.3e-7.
+//
+// SEG: the rows are cells, taken in the order of the input row they read (`at`, ascending `seg`), z is h_prev, and while a row of dG is at hand
 // it is also added to s[seg], the sum of dG over the cells that read one node: dG is read once for both.  A workgroup takes a
 // contiguous range of rows; the part of a node that an earlier range began goes to edge_first, the part of one that a later range
 // goes on with to edge_last, and seq_edges_kernel adds those up in order.
@@ -1023,66 +1031,68 @@ struct SeqWgradArgs {
     float *s, *edge_first, *edge_last;   // SEG: [nodes, 4H], [gridDim.x, 4H] twice
 };
 constexpr int kSeqWgradRows = 32;
-constexpr int kSeqWgradGroups = 768;        // workgroups along x at most (three per compute unit)
+constexpr int kSeqWgradGroups = 512;        // workgroups at most, over all slabs of gate rows: two per compute unit
 constexpr int64_t kSeqWgradPartialFloats = 64 << 20;   // and no more partial sums than this many floats
 
-// NCT: column tiles of 32, rounded up to 1, 2, 4 or 8.
+// element at a byte offset from a wave-uniform address in device memory; lane c's value of a 64-bit number, as a scalar
+typedef float __attribute__((address_space(1))) *seq_global_t;
+__device__ __forceinline__ seq_global_t seq_at(uint64_t row, uint32_t off) { return (seq_global_t)((char __attribute__((address_space(1))) *)row + off); }
+__device__ __forceinline__ uint64_t seq_lane64(uint64_t v, int c) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, c) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), c) << 32;
+}
+
+// NCT: column tiles of 32 of a workgroup, rounded up to 1, 2 or 4; kp: columns of a row of the partial sums.
 template <int NCT, bool SEG>
-__global__ __launch_bounds__(512, NCT <= 4 ? 4 : 2) void seq_weight_grad_kernel(SeqWgradArgs A) {
-    constexpr int CK = kSeqWgradRows, ZW = NCT * 32, RZ = (CK * ZW / 4 + 511) / 512;
-    __shared__ __align__(16) float sdg[CK][256];
-    __shared__ __align__(16) float sz[CK][ZW];
-    __shared__ int32_t sseg[CK + 1];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A, int kp) {
+    constexpr int CK = kSeqWgradRows, ZW = NCT * 32, CPT = CK * ZW / 256;   // CPT: rows of z per thread
+    // eight rows (k) of a column per 16-byte slot, slot q of column c at q ^ (c / 4 % 4): eight neighbouring columns cover all banks
+    __shared__ uint4 sdg[3][256][CK / 8], sz[3][ZW][CK / 8];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows4 = 4 * A.hidden, cols = A.cols;
-    const int row0 = blockIdx.y * 256, n_rt = (rows4 - row0 < 256 ? rows4 - row0 : 256) / 32, n_ct = (cols + 31) / 32;
-    seq_acc_t acc[NCT];
+    const int row0 = blockIdx.y * 256, n_rt = (rows4 - row0 < 256 ? rows4 - row0 : 256) / 32;
+    const int col0 = blockIdx.z * (NCT * 32), n_ct = (cols - col0 + 31) / 32;
+    // Threads beyond the last gate row repeat it: they load, add and write what its own thread does, and no product reads their column.
+    const uint32_t gate_off = (uint32_t)((row0 + tid < rows4 ? row0 + tid : rows4 - 1) - row0) * 4;
+    // a thread takes column tid % ZW of z and rows CPT * (tid / ZW) on of the 32 (indices are derived again where they are used: registers are short)
+    seq_acc_t acc[2][NCT];
 #pragma unroll
-    for (int c = 0; c < NCT; ++c)
+    for (int g = 0; g < 2; ++g)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
-    float sum = 0.f;                                       // thread i < 256: the running sum of dG[.][row0 + i]
+        for (int c = 0; c < NCT; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[g][c][r] = 0.f;
+    float sum = 0.f;                                       // the running sum of dG[.][row0 + tid]
     const int64_t first = (int64_t)blockIdx.x * A.range, last = first + A.range < A.rows ? first + A.range : A.rows;
     bool begun_before = false;                             // SEG: the running sum belongs to a node that an earlier range began
     if (SEG && first > 0 && first < last) begun_before = A.seg[first - 1] == A.seg[first];
-    // the next 32 rows are requested into registers before the products of the current ones
-    float4 rg[4], rz[RZ];
-    int32_t rs = -1, ig[4], iz[RZ];                        // and the places of those rows a chunk before that
+    // The next 32 rows are requested into registers before the products of the current ones, and their places a chunk before that.  Lane c works out where
+    // row c lies and the wavefront reads it there as a scalar: as scalar arithmetic per row this took as long as the products.  Places past the end
+    // are those of the last row, and what they hold is cleared before it is used; so is z where h_prev is the zero state (zero: the rows to clear).
+    float rg[CK], rz[CPT];
+    int32_t rs = -1, ig = 0, iz = 0;                       // of row lane % 32; rs: of row lane, one more than the chunk: where the last row's node ends
+    uint32_t zero = 0;
     auto request_ids = [&](int64_t c0) {
-        const int tid = seq_opaque(threadIdx.x), wave = tid >> 6;   // (indices are derived again in every phase: registers are short)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-            const int64_t at = c0 + wave + 8 * v4;
-            ig[v4] = at < last ? (SEG ? A.at[at] : 0) : -1;
-        }
-#pragma unroll
-        for (int v4 = 0; v4 < RZ; ++v4) {
-            const int i = tid + 512 * v4, c = i / (ZW / 4);
-            iz[v4] = c < CK && c0 + c < last ? (SEG ? A.prev[c0 + c] : A.at[c0 + c]) : -1;
-        }
+        int64_t at = c0 + (lane & (CK - 1));
+        at = at < last ? at : last - 1;
+        ig = SEG ? A.at[at] : (int32_t)at;
+        iz = SEG ? A.prev[at] : A.at[at];
     };
     auto request = [&](int64_t c0) {
-        const int tid = seq_opaque(threadIdx.x), wave = tid >> 6, lane = tid & 63;
+        const int tid = seq_opaque(threadIdx.x), zc = tid % ZW, zq = tid / ZW;
+        const uint64_t g_row = (uint64_t)(A.dg + row0) + (uint64_t)(uint32_t)ig * (uint32_t)(rows4 * 4);
+        const bool state = SEG && iz <= -2;
+        const uint64_t z_row = (uint64_t)((state ? A.z2 : A.z) + col0) + (uint64_t)(uint32_t)(state ? -iz - 2 : iz < 0 ? 0 : iz) * (uint32_t)(cols * 4);
+        zero = (uint32_t)__ballot(iz == -1 || c0 + (lane & (CK - 1)) >= last);
+        const uint32_t g_off = (uint32_t)seq_opaque((int)gate_off);
 #pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-            const int c = wave + 8 * v4, k = lane * 4;     // a wavefront moves whole slabs of rows
-            rg[v4] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ig[v4] >= 0 && row0 + k < rows4) {
-                const size_t row = SEG ? (size_t)ig[v4] : (size_t)(c0 + c);
-                rg[v4] = *reinterpret_cast<const float4 *>(A.dg + row * rows4 + row0 + k);
-            }
-        }
+        for (int c = 0; c < CK; ++c) rg[c] = *seq_at(seq_lane64(g_row, c), g_off);
+        const uint32_t z_off = (uint32_t)(col0 + zc < cols ? zc : 0) * 4;   // (columns of padding: no result reads them)
 #pragma unroll
-        for (int v4 = 0; v4 < RZ; ++v4) {
-            const int i = tid + 512 * v4, k = (i % (ZW / 4)) * 4, pv = iz[v4];
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (k < cols) {
-                if (pv >= 0) v = *reinterpret_cast<const float4 *>(A.z + (size_t)pv * cols + k);
-                else if (SEG && pv <= -2) v = *reinterpret_cast<const float4 *>(A.z2 + (size_t)(-pv - 2) * cols + k);
-            }
-            rz[v4] = v;
+        for (int c = 0; c < CPT; ++c) {
+            if constexpr (ZW >= 64) rz[c] = *seq_at(seq_lane64(z_row, wave * 64 / ZW * CPT + c), z_off);   // a wavefront has one run of rows
+            else rz[c] = *seq_at((uint64_t)__shfl((unsigned long long)z_row, zq * CPT + c), z_off);
         }
-        if (SEG && tid <= CK) rs = c0 + tid < A.rows ? A.seg[c0 + tid] : -1;   // one more than the chunk: where the last row's node ends
+        if (SEG) rs = lane <= CK && c0 + lane < A.rows ? A.seg[c0 + lane] : -1;
     };
     if (first < last) {
         request_ids(first);
@@ -1090,69 +1100,129 @@ __global__ __launch_bounds__(512, NCT <= 4 ? 4 : 2) void seq_weight_grad_kernel(
         request_ids(first + CK);
     }
     for (int64_t c0 = first; c0 < last; c0 += CK) {
-        const int tid = seq_opaque(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+        const int here = last - c0 < CK ? (int)(last - c0) : CK;
+        if (here < CK) {
 #pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) *reinterpret_cast<float4 *>(&sdg[wave + 8 * v4][lane * 4]) = rg[v4];
-#pragma unroll
-        for (int v4 = 0; v4 < RZ; ++v4) {
-            const int i = tid + 512 * v4;
-            if (i / (ZW / 4) < CK) *reinterpret_cast<float4 *>(&sz[i / (ZW / 4)][(i % (ZW / 4)) * 4]) = rz[v4];
+            for (int c = 0; c < CK; ++c) rg[c] = c < here ? rg[c] : 0.f;
         }
-        if (SEG && tid <= CK) sseg[tid] = rs;
+#pragma unroll
+        for (int c = 0; c < CPT; ++c)
+            rz[c] = (zero >> ((seq_opaque(threadIdx.x) / ZW) * CPT + c)) & 1 ? 0.f : rz[c];
+        const int tid = seq_opaque(threadIdx.x), zc = tid % ZW, zq = tid / ZW;
+#pragma unroll
+        for (int q = 0; q < CK / 8; ++q) {
+            uint32_t w[3][4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                uint32_t p[3];
+                seq_split2(rg[8 * q + 2 * k], rg[8 * q + 2 * k + 1], p);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) w[i][k] = p[i];
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) sdg[i][tid][q ^ ((tid >> 2) & 3)] = make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]);
+        }
+        {
+            uint32_t w[3][CPT / 2];
+#pragma unroll
+            for (int k = 0; k < CPT / 2; ++k) {
+                uint32_t p[3];
+                seq_split2(rz[2 * k], rz[2 * k + 1], p);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) w[i][k] = p[i];
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                if constexpr (CPT >= 8) {
+#pragma unroll
+                    for (int q = 0; q < CPT / 8; ++q)
+                        sz[i][zc][(zq * (CPT / 8) + q) ^ ((zc >> 2) & 3)] = make_uint4(w[i][4 * q], w[i][4 * q + 1], w[i][4 * q + 2], w[i][4 * q + 3]);
+                } else {
+                    reinterpret_cast<uint2 *>(&sz[i][zc][(zq / 2) ^ ((zc >> 2) & 3)])[zq & 1] = make_uint2(w[i][0], w[i][1]);
+                }
+            }
+        }
+        if (SEG) {
+            // bit c: the node of row c ends there, or the range does
+            const int32_t after = __shfl_down(rs, 1);
+            const bool ends = lane < here && (rs != after || lane + 1 + c0 == last);
+            const uint32_t stops = (uint32_t)__ballot(ends);
+            const bool goes_on = c0 + here == last && __builtin_amdgcn_readlane(rs, here - 1) == __builtin_amdgcn_readlane(rs, here);   // the last row's node, beyond this range
+            float *out = begun_before && stops && lane == __builtin_ctz(stops) ? A.edge_first + (size_t)blockIdx.x * rows4
+                       : goes_on && lane == here - 1 ? A.edge_last + (size_t)blockIdx.x * rows4 : A.s + (size_t)(uint32_t)(rs < 0 ? 0 : rs) * (uint32_t)rows4;
+            const uint64_t out_row = (uint64_t)(out + row0);
+            if (stops) begun_before = false;
+#pragma unroll
+            for (int c = 0; c < CK; ++c) {
+                sum += rg[c];
+                if (!((stops >> c) & 1)) continue;
+                *seq_at(seq_lane64(out_row, c), gate_off) = sum;
+                sum = 0.f;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < CK; ++c) sum += rg[c];
+        }
         __syncthreads();
         if (c0 + CK < last) {
             request(c0 + CK);
             request_ids(c0 + 2 * CK);
         }
-        if (wave < n_rt) {
-            constexpr int UNR = NCT == 4 ? 2 : 4;          // (unrolled further the operands of many steps are read at once, and spill)
-#pragma unroll UNR
-            for (int st = 0; st < CK / 2; ++st) {
-                const int c = 2 * st + (lane >> 5);
-                const float a = sdg[c][wave * 32 + (lane & 31)];
+        __builtin_amdgcn_sched_barrier(0);
+        const int l32 = seq_opaque(threadIdx.x) & 31, half = (seq_opaque(threadIdx.x) >> 5) & 1;
 #pragma unroll
-                for (int ct = 0; ct < NCT; ++ct)
-                    acc[ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, sz[c][ct * 32 + (lane & 31)], acc[ct], 0, 0, 0);
-            }
-        }
-        if (tid < 32 * n_rt) {
-            if (SEG) {
-                // bit c: the node of row c ends there, or the range does
-                const int here = last - c0 < CK ? (int)(last - c0) : CK;
-                const bool ends = lane < here && (sseg[lane & (CK - 1)] != sseg[(lane & (CK - 1)) + 1] || lane + 1 + c0 == last);
-                const uint32_t stops = (uint32_t)__ballot(ends);
-                const bool goes_on = here > 0 && c0 + here == last && sseg[here - 1] == sseg[here];   // the last row's node, beyond this range
-#pragma unroll 8
-                for (int c = 0; c < CK; ++c) {
-                    sum += sdg[c][tid];            // (rows past the end were staged as zeros)
-                    if (!((stops >> c) & 1)) continue;
-                    float *out = begun_before ? A.edge_first + (size_t)blockIdx.x * rows4
-                               : goes_on && c == here - 1 ? A.edge_last + (size_t)blockIdx.x * rows4 : A.s + (size_t)sseg[c] * rows4;
-                    out[row0 + tid] = sum;
-                    sum = 0.f;
-                    begun_before = false;
+        for (int g = 0; g < 2; ++g) {
+            const int rt = 2 * wave + g;
+            if (rt >= n_rt) continue;
+            seq_b8_t a[CK / 16][3];
+#pragma unroll
+            for (int k = 0; k < CK / 16; ++k)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) a[k][p] = *reinterpret_cast<const seq_b8_t *>(&sdg[p][rt * 32 + l32][(2 * k + half) ^ ((l32 >> 2) & 3)]);
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) {
+                auto z_piece = [&](int k, int p) { return *reinterpret_cast<const seq_b8_t *>(&sz[p][ct * 32 + l32][(2 * k + half) ^ ((l32 >> 2) & 3)]); };
+                seq_acc_t t;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) t[r] = 0.f;
+#pragma unroll
+                for (int k = 0; k < CK / 16; ++k) {
+                    const seq_b8_t b0 = z_piece(k, 0), b1 = z_piece(k, 1), b2 = z_piece(k, 2);
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][2], b0, t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][1], b0, t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][1], b1, t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][0], b1, t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][0], b2, t, 0, 0, 0);
+                    if (NCT == 4) __builtin_amdgcn_sched_barrier(0);   // (registers are short)
                 }
-            } else {
-#pragma unroll 8
-                for (int c = 0; c < CK; ++c) sum += sdg[c][tid];   // (rows past the end were staged as zeros)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) { acc[g][ct][r] += t[r]; t[r] = 0.f; }
+                if (NCT == 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < CK / 16; ++k) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][0], z_piece(k, 0), t, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[g][ct][r] += t[r];
+                if (NCT == 4) __builtin_amdgcn_sched_barrier(0);   // (one column tile at a time: registers are short)
             }
         }
         __syncthreads();
     }
-    const int kp = NCT * 32;
     float *out = A.partial + (size_t)blockIdx.x * ((size_t)rows4 * kp + rows4);
-    if (wave < n_rt) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const int rt = 2 * wave + g;
+        if (rt >= n_rt) continue;
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct) {
             if (ct >= n_ct) continue;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int row = row0 + wave * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-                out[(size_t)row * kp + ct * 32 + (lane & 31)] = acc[ct][r];
+                const int row = row0 + rt * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
+                out[(size_t)row * kp + col0 + ct * 32 + (lane & 31)] = acc[g][ct][r];
             }
         }
     }
-    if (!SEG && (int)threadIdx.x < 32 * n_rt) out[(size_t)rows4 * kp + row0 + threadIdx.x] = sum;
+    if (!SEG && blockIdx.z == 0 && row0 + tid < rows4) out[(size_t)rows4 * kp + row0 + tid] = sum;
 }
 
 // s of the nodes that several ranges share: the part of the range that begins the node, then those of the ranges that go on with
@@ -1264,7 +1334,7 @@ static SeqWgradShape seq_wgrad_shape(int64_t rows, int64_t cols, int64_t hidden)
     const int64_t ct = (cols + 31) / 32;
     w.nct = ct <= 1 ? 1 : ct <= 2 ? 2 : ct <= 4 ? 4 : 8;
     w.per = 4 * hidden * 32 * w.nct + 4 * hidden;
-    const int64_t most = std::max<int64_t>(std::min<int64_t>(kSeqWgradGroups, kSeqWgradPartialFloats / w.per), 1);
+    const int64_t most = std::max<int64_t>(std::min<int64_t>(kSeqWgradGroups / ((4 * hidden + 255) / 256), kSeqWgradPartialFloats / w.per), 1);
     const int64_t chunks = (rows + kSeqWgradRows - 1) / kSeqWgradRows;
     const int64_t each = std::max<int64_t>((chunks + most - 1) / most, 1);
     w.range = each * kSeqWgradRows;
@@ -1274,12 +1344,14 @@ static SeqWgradShape seq_wgrad_shape(int64_t rows, int64_t cols, int64_t hidden)
 
 template <bool SEG>
 static int launch_wgrad(const SeqWgradArgs &g, const SeqWgradShape &w, int64_t hidden, hipStream_t s) {
-    const dim3 grid((unsigned)w.groups, (unsigned)((4 * hidden + 255) / 256)), block(512);
-    switch (w.nct) {
-        case 1: hipLaunchKernelGGL((seq_weight_grad_kernel<1, SEG>), grid, block, 0, s, g); break;
-        case 2: hipLaunchKernelGGL((seq_weight_grad_kernel<2, SEG>), grid, block, 0, s, g); break;
-        case 4: hipLaunchKernelGGL((seq_weight_grad_kernel<4, SEG>), grid, block, 0, s, g); break;
-        default: hipLaunchKernelGGL((seq_weight_grad_kernel<8, false>), grid, block, 0, s, g); break;   // (hidden has at most four column tiles)
+    // (the nodes are few beside the cells: their columns in slabs of 64, which leaves registers free; hidden has at most four column tiles)
+    constexpr int most = SEG ? 4 : 2;
+    const dim3 grid((unsigned)w.groups, (unsigned)((4 * hidden + 255) / 256), (unsigned)(w.nct > most ? w.nct / most : 1)), block(256);
+    const int kp = 32 * w.nct;
+    switch (std::min(w.nct, most)) {
+        case 1: hipLaunchKernelGGL((seq_weight_grad_kernel<1, SEG>), grid, block, 0, s, g, kp); break;
+        case 2: hipLaunchKernelGGL((seq_weight_grad_kernel<2, SEG>), grid, block, 0, s, g, kp); break;
+        default: hipLaunchKernelGGL((seq_weight_grad_kernel<4, true>), grid, block, 0, s, g, kp); break;
     }
     HIP_TRY(hipGetLastError());
     return HAG_OK;

@@ -74,3 +74,31 @@ def test_infinite_and_nan_features_stay_with_their_readers(B):
     assert np.array_equal(got[untouched], clean[untouched])
     fine = holds(7) & ~holds(9)
     assert np.abs(got[fine] - want[fine]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("d,hidden", [(4, 8), (36, 32), (68, 56), (132, 64), (64, 72), (128, 128)])
+def test_gradients_scale_with_the_gradient_they_come_from(B, d, hidden):
+    # The backward pass is linear in g: over the plain lists (no atomics, so bit-reproducible) a power of two passes through every product, piece
+    # and sum unchanged.  2^60 and 2^-60 leave the smallest pieces of a product (2^-16 of it) far from the ends of the fp32 range.
+    n = 173
+    rowptr, col = lists(n, hidden)
+    rng = np.random.default_rng(d)
+    x, w_ih, w_hh, b, g = (dev(rng.normal(0, s, shape)) for s, shape in ((1, (n, d)), (0.3, (4 * hidden, d)), (0.3, (4 * hidden, hidden)), (0.3, 4 * hidden), (1, (n, hidden))))
+    h = B.SeqHag(rowptr, col, 0).upload()
+
+    def grads(g_a):
+        _, ws = h.lstm_forward_train(x, w_ih, w_hh, b)
+        return h.lstm_backward(x, w_ih, w_hh, g_a, ws)
+
+    plain = grads(g)
+    for k in (60, -60):
+        for one, other in zip(plain, grads(g * 2.0 ** k)):
+            assert torch.equal(one * 2.0 ** k, other)
+    # an infinite gradient of one node reaches what that node's list reads, and no other row of g_x
+    v = int(np.argmax(np.diff(rowptr)))
+    g[v, 1] = float("inf")
+    g_x, g_w_ih, g_w_hh, g_b = grads(g)
+    read = np.unique(col[rowptr[v]:rowptr[v + 1]])
+    others = np.setdiff1d(np.arange(n), read)
+    assert not torch.isfinite(g_x[read]).all(1).any() and not torch.isfinite(g_b).any()
+    assert torch.equal(g_x[others], plain[0][others])

@@ -12,7 +12,7 @@
 // matrix product on the matrix cores.  The half of the gates that depends on the input row only, W_ih x + b, is computed once
 // per node (a node occurs in many lists); a step adds to it
 //     gates^T [4H, paths] += W_hh [4H, H] . H^T [H, paths],
-// with fp32 operands cut into three bf16 pieces.  The rows of W_hh are ordered so that a lane ends up holding all four gates
+// with fp32 operands cut into two fp16 pieces.  The rows of W_hh are ordered so that a lane ends up holding all four gates
 // of its hidden units for its path and the cell's element-wise part runs in registers.
 #include <hip/hip_runtime.h>
 
@@ -68,6 +68,8 @@ constexpr int kSeqMaxK = 256;     // D + H at most
 
 typedef float seq_acc_t __attribute__((ext_vector_type(16)));
 typedef __bf16 seq_b8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 seq_h8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 seq_h2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 seq_b2_t __attribute__((ext_vector_type(2)));
 typedef float seq_f2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int seq_u2_t __attribute__((ext_vector_type(2)));
@@ -86,20 +88,37 @@ __device__ __forceinline__ void seq_split2(float a, float b, uint32_t (&p)[3]) {
     }
 }
 
+// The operands of the recurrent product in the forward pass as two fp16 numbers each, 11 + 11 significant bits: what is cut off is 2^-23 of a number at
+// most, 2^-25 on average and of either sign, about what one fp32 addition rounds, and a product needs three matrix instructions
+// instead of six.  Both operands fit fp16's range because both are bounded: |h| < 1 is multiplied by 2^4 and the weights of a unit by the power of two
+// that brings the largest to [2^5, 2^6), so what the second piece of a small number rounds off (2^-25, the subnormal numbers of fp16) is
+// 2^-29 and 2^-30 of the largest; the factors stay that small so that pre-activations have the range of fp32 but for a few powers of ten.
+constexpr float kSeqHScale = 16.f;
+__device__ __forceinline__ void seq_halves2(float a, float b, uint32_t (&p)[2]) {   // two numbers, packed as the low and the high half of each word
+#pragma clang fp contract(off)
+    const seq_f2_t v = {a, b};
+    const seq_h2_t hi = __builtin_convertvector(v, seq_h2_t);
+    const seq_f2_t r = {fmaf((float)hi.x, -1.f, a), fmaf((float)hi.y, -1.f, b)};   // exact; one mixed-precision instruction each
+    p[0] = __builtin_bit_cast(uint32_t, hi);
+    p[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, seq_h2_t));
+}
+
 // Weights in the forms the kernels read, from the usual layout (w_ih [4H, D], w_hh [4H, H], b [4H], gate-major rows: input,
-// forget, cell, output gate):
+// forget, cell, output gate).  Everything that makes up a pre-activation is multiplied by a power of two of its unit (see seq_halves2), and
+// twice that for the cell gate, whose tanh is a function of 2 z:
 //   wx: W_ih for the product over input rows, fp32, [gate tile][dp / 8 groups of four k-steps][lane][4]; lane l supplies
 //       column l % 32 of the tile (gate row tile * 32 + l % 32 in (unit, gate) order) and k = 2 * step + l / 32;
-//   wq: W_hh for the recurrent product, three bf16 pieces, [gate tile][ks steps of 16][piece][lane][8]; lane l supplies row
+//   wq: W_hh for the recurrent product, two fp16 pieces, [gate tile][ks steps of 16][piece][lane][8]; lane l supplies row
 //       l % 32 of the tile, k = 16 * step + 8 * (l / 32) + 0..7.  Row 8 m + 4 p + gate of a tile is that gate of hidden unit
 //       8 * tile + 4 p + m, so that lane l of the product ends up with all gates of four CONSECUTIVE units;
-//   bp: the bias in (unit, gate) order.
-// The "state is written" counters of the pass start at zero, and a_v of the nodes with an empty list is zero (final_state NULL: there are none).
+//   bp: the bias in (unit, gate) order; behind it, per unit, -log2(e) over the unit's factor: what turns a pre-activation into the exponent of its gate function.
+// One workgroup per unit.  The "state is written" counters of the pass start at zero, and a_v of the nodes with an empty list is zero (final_state NULL: there are none).
 __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
                                                       const float *__restrict__ b, float *__restrict__ wx,
                                                       uint16_t *__restrict__ wq, float *__restrict__ bp, int d, int dp,
                                                       int hidden, int ks, int32_t *__restrict__ flags, int64_t n_flags,
                                                       const int32_t *__restrict__ final_state, float *__restrict__ a_out, int64_t n) {
+    __shared__ float largest[4];
     const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
     for (int64_t f = first; f < n_flags; f += stride) flags[f] = 0;
     if (final_state) {                                     // 64 nodes per wavefront, as in seq_output_kernel
@@ -108,28 +127,40 @@ __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__
             for (unsigned long long left = __ballot(base + lane < n && final_state[base + lane < n ? base + lane : 0] == -1); left; left &= left - 1)
                 for (int u = lane; u < hidden; u += 64) a_out[(base + __builtin_ctzll(left)) * hidden + u] = 0.f;
     }
-    for (int64_t i = first; i < (int64_t)4 * hidden; i += stride) bp[i] = b[(i & 3) * hidden + (i >> 2)];
-    for (int64_t i = first; i < (int64_t)4 * hidden * dp; i += stride) {
-        const int per_tile = 32 * dp, tile = (int)(i / per_tile), rest = (int)(i % per_tile);
-        const int q = rest / 256, lane = (rest % 256) / 4, step = 4 * q + (rest & 3);
-        const int r = tile * 32 + (lane & 31), k = 2 * step + (lane >> 5);
-        wx[i] = k < d ? w_ih[(size_t)((r & 3) * hidden + (r >> 2)) * d + k] : 0.f;
-    }
-    for (int64_t i = first; i < (int64_t)(hidden / 8) * ks * 512; i += stride) {
-        const int tile = (int)(i / (ks * 512)), step = (int)(i / 512) % ks, lane = (int)(i % 512) / 8;
-        const int row = lane & 31, unit = tile * 8 + ((row >> 2) & 1) * 4 + (row >> 3), gate = row & 3;
-        const int k = 16 * step + 8 * (lane >> 5) + (int)(i & 7);
-        float v = k < hidden ? w_hh[(size_t)(gate * hidden + unit) * hidden + k] : 0.f;
-        uint32_t p[3];
-        seq_split2(v, 0.f, p);
-        if ((p[0] & 0x7fffu) == 0x7f80u && fabsf(v) < INFINITY) {   // rounded up past the largest bf16: cut the first piece instead
-            p[0] = __float_as_uint(v) >> 16;
-            uint32_t rest[3];
-            seq_split2(v - __uint_as_float(p[0] << 16), 0.f, rest);
-            p[1] = rest[0]; p[2] = rest[1];
-        }
+    const int unit = blockIdx.x, gate = threadIdx.x >> 6, lane = threadIdx.x & 63;   // a wavefront per gate row
+    if (unit >= hidden) return;
+    const float *row = w_hh + (size_t)(gate * hidden + unit) * hidden;
+    const float twice = gate == 2 ? 2.f : 1.f;
+    float v[2];                                            // (hidden is 128 at most)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) wq[((int64_t)(tile * ks + step) * 3 + c) * 512 + (i % 512)] = (uint16_t)(p[c] & 0xffffu);
+    for (int i = 0; i < 2; ++i) v[i] = lane + 64 * i < hidden ? row[lane + 64 * i] * twice : 0.f;
+    float most = fmaxf(fabsf(v[0]), fabsf(v[1]));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off));
+    if (lane == 0) largest[gate] = most;
+    __syncthreads();
+    most = fmaxf(fmaxf(largest[0], largest[1]), fmaxf(largest[2], largest[3]));
+    // (smaller weights than 2^-4 are not brought up all the way: what they lose is 2^-35, and the input half keeps clear of fp32's end)
+    const int up = most < INFINITY ? min(6 - __builtin_amdgcn_frexp_expf(most), 10) : 0;
+    const float by = __builtin_ldexpf(1.f, up), with_h = twice * by * kSeqHScale;
+    const int r = 4 * unit + gate, tile = unit >> 3, in_tile = 8 * (unit & 3) + 4 * ((unit >> 2) & 1) + gate;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int k = lane + 64 * i;
+        if (k >= 16 * ks) continue;
+        uint32_t p[2];
+        seq_halves2(v[i] * by, 0.f, p);
+        uint16_t *out = wq + (size_t)(tile * ks + (k >> 4)) * 1024 + (in_tile + 32 * ((k >> 3) & 1)) * 8 + (k & 7);
+        out[0] = (uint16_t)(p[0] & 0xffffu);
+        out[512] = (uint16_t)(p[1] & 0xffffu);
+    }
+    for (int k = lane; k < dp; k += 64) {
+        const float w = k < d ? w_ih[(size_t)(gate * hidden + unit) * d + k] * with_h : 0.f;
+        wx[(size_t)(r >> 5) * 32 * dp + (k >> 3) * 256 + ((r & 31) + 32 * (k & 1)) * 4 + ((k >> 1) & 3)] = w;
+    }
+    if (lane == 0) {
+        bp[r] = b[gate * hidden + unit] * with_h;
+        if (gate == 0) bp[4 * hidden + unit] = -1.44269504f / (by * kSeqHScale);
     }
 }
 
@@ -193,11 +224,13 @@ __global__ __launch_bounds__(256) void seq_input_gates_kernel(const float *__res
 // Gate functions on the hardware's exp2 and reciprocal: absolute error of a few 1e-7 on outputs in (0, 1) and
 // (-1, 1), against ~150 instructions per hidden unit for the library versions, which made the element-wise
 // part as long as the matrix products.
-__device__ __forceinline__ float seq_sigmoid(float z) { return __builtin_amdgcn_rcpf(1.f + __expf(-z)); }
-__device__ __forceinline__ float seq_tanh(float z) {
-    const float e = __expf(-2.f * fabsf(z));             // in (0, 1]: no overflow, no cancellation in 1 + e
+// Of a pre-activation times a factor, with `by` = -log2(e) over that factor (tanh: of 2 z).
+__device__ __forceinline__ float seq_sigmoid(float z, float by) { return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(z * by)); }
+__device__ __forceinline__ float seq_tanh(float z, float by) {
+    const float e = __builtin_amdgcn_exp2f(fabsf(z) * by);   // in (0, 1]: no overflow, no cancellation in 1 + e
     return copysignf((1.f - e) * __builtin_amdgcn_rcpf(1.f + e), z);
 }
+__device__ __forceinline__ float seq_tanh(float z) { return seq_tanh(z, -2.f * 1.44269504f); }
 
 struct SeqChainArgs {
     const int32_t *chains;   // paths, 4 per path, in tiles of 64 (padded with empty paths), longest first within a level
@@ -209,7 +242,8 @@ struct SeqChainArgs {
     const int32_t *step_g;   // per step: row of gx
     const int32_t *step_out; // per step: state row to write, or -1
     const float *gx;         // the input half of the gates, [n_used, 4H] in (unit, gate) order
-    const uint16_t *wq;      // W_hh in bf16 pieces, see seq_pack_kernel
+    const uint16_t *wq;      // W_hh in fp16 pieces, see seq_pack_kernel
+    const float *unscale;    // per unit, see seq_pack_kernel
     float *h, *c;            // [n_states, H]: read where a path starts (written by a lower level), written where a step says so
     float *a_out;            // [n, H]
     float *tape_g, *tape_c, *tape_h;   // training: per step the activated gates [H][4], the new c [H] and the new h [H] (NULL: inference)
@@ -290,21 +324,22 @@ __device__ __forceinline__ void seq_from_pieces(V &v) {
 // registers and writes the new h to the other of two LDS buffers, so that a step has one barrier.  Paths are sorted by length, so
 // the paths of a tile end within a step or two of each other; a path that has ended keeps quiet while the others finish.
 //
-// The product runs in bf16 pieces (seq_split2): six v_mfma_f32_32x32x16_bf16 per 16 columns cost 192 cycles against 512 for
-// fp32 ones.
-// Measured (370 k nodes, hidden = d = 64, prefix HAG with 3.35 M cells): 0.85 ms + 0.06 ms for gx, against 1.9 ms with fp32
-// products over (x, h) in every cell; what is left is the element-wise part and the gx rows.
+// The product runs in fp16 pieces (seq_halves2): three v_mfma_f32_32x32x16_f16 per 16 columns cost 96 cycles against 192 for bf16 pieces (six) and
+// 512 for fp32 instructions.  What is left is the element-wise part and the rows of gx.  Inference over 370 k nodes (hidden = d = 64, prefix HAG with 3.35 M
+// cells): 877 us with bf16 pieces, 737 so; with the tape 1.57 and 1.49 ms; 0.85 M cells of 128 units with the tape: 1.18 and 1.01 ms.  Error of the
+// result against 64 bits 2.1e-7 and 1.9e-7 (128 units: 2.7e-7 and 2.5e-7).
 // A gate tile is 32 gate rows = 8 hidden units; lane l of the product holds, for path l % 32 of its half of the tile, the four
 // gates of units 8 * tile + 4 * (l / 32) + 0..3.
 //   HMAX 64 (hidden 33..64): 8 wavefronts, wavefront w holds gate tile w in registers and takes both halves of the paths;
 //   HMAX 32: wavefront w holds gate tile w % 4 and takes half w / 4;
-//   HMAX 128: 16 wavefronts, wavefront w streams gate tile w (3 KB per 16 columns) from the L2 cache once per step for both
-//   halves: the pieces of a whole tile would be 96 of the 128 registers there are at four wavefronts per SIMD.
+//   HMAX 128: 16 wavefronts, wavefront w streams gate tile w (2 KB per 16 columns) from the L2 cache once per step for both
+//   halves: the pieces of a whole tile would be 64 of the 128 registers there are at four wavefronts per SIMD.
 template <int HMAX, bool TAPE>
 __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(SeqChainArgs A) {
     constexpr bool BIG = HMAX == 128, WIDE = HMAX >= 64, C_LDS = HMAX == 64 || TAPE;
     constexpr int KS = HMAX / 16, ZS = HMAX + 8, JG = WIDE ? 2 : 1;
-    __shared__ __align__(16) uint16_t z[2][3][kSeqJobs][ZS];   // h of every path in bf16 pieces: this step's and the next step's
+    __shared__ __align__(16) uint16_t z[2][2][kSeqJobs][ZS];   // h of every path in fp16 pieces: this step's and the next step's
+    __shared__ __align__(16) float hs[TAPE ? kSeqJobs : 1][HMAX + 4];   // the step's h as it is, for the tape
     // c: in registers, except where those are too short or the tape takes it from here (rows 4 banks apart: conflict-free 16-byte accesses)
     __shared__ __align__(16) float cs[C_LDS ? kSeqJobs : 1][HMAX + 4];
     __shared__ int32_t sdesc[kSeqJobs * 4];
@@ -313,14 +348,16 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
     const int hidden = A.hidden, n_tiles = hidden / 8, ks = BIG ? (hidden + 15) / 16 : KS;
     const int tile = WIDE ? wave : (wave & 3), group0 = WIDE ? 0 : (wave >> 2);
     const bool on = tile < n_tiles;                        // wavefronts beyond the hidden size only keep the barriers
-    seq_b8_t wreg[BIG ? 1 : KS][3];
-    const seq_b8_t *wl = reinterpret_cast<const seq_b8_t *>(A.wq) + (size_t)tile * ks * 3 * 64 + lane;
+    seq_h8_t wreg[BIG ? 1 : KS][2];
+    const seq_h8_t *wl = reinterpret_cast<const seq_h8_t *>(A.wq) + (size_t)tile * ks * 2 * 64 + lane;
+    const float4 by4 = on ? *reinterpret_cast<const float4 *>(A.unscale + tile * 8 + half * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float by[4] = {by4.x, by4.y, by4.z, by4.w};
     if constexpr (!BIG) {
         if (on) {
 #pragma unroll
             for (int s = 0; s < KS; ++s)
 #pragma unroll
-                for (int p = 0; p < 3; ++p) wreg[s][p] = wl[(s * 3 + p) * 64];
+                for (int p = 0; p < 2; ++p) wreg[s][p] = wl[(s * 2 + p) * 64];
         }
     }
     // columns from `hidden` on stay zero in both buffers
@@ -373,11 +410,11 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
             }
         };
         auto put_h = [&](int buf, int j, int unit0, const float (&h)[4]) {
-            uint32_t a[3], b[3];
-            seq_split2(h[0], h[1], a);
-            seq_split2(h[2], h[3], b);
+            uint32_t a[2], b[2];
+            seq_halves2(h[0] * kSeqHScale, h[1] * kSeqHScale, a);
+            seq_halves2(h[2] * kSeqHScale, h[3] * kSeqHScale, b);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2 *>(&z[buf][p][j][unit0]) = make_uint2(a[p], b[p]);
+            for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2 *>(&z[buf][p][j][unit0]) = make_uint2(a[p], b[p]);
         };
 #pragma unroll
         for (int g = 0; g < JG; ++g) {
@@ -423,17 +460,14 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
             for (int g = 0; g < JG; ++g)
                 if (pend[g] >= 0 && half == 0 && A.publish) __hip_atomic_fetch_add(A.flags + pend[g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         };
-        auto product = [&](int cur, int g, seq_acc_t &a, const seq_b8_t (&w)[3], int s) {
-            seq_b8_t zb[3];
+        auto product = [&](int cur, int g, seq_acc_t &a, const seq_h8_t (&w)[2], int s) {
+            seq_h8_t zb[2];
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
-                zb[p] = *reinterpret_cast<const seq_b8_t *>(&z[cur][p][(group0 + g) * 32 + (lane & 31)][16 * s + 8 * half]);
-            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[2], zb[0], a, 0, 0, 0);
-            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], zb[2], a, 0, 0, 0);
-            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[1], zb[1], a, 0, 0, 0);
-            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[1], zb[0], a, 0, 0, 0);
-            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], zb[1], a, 0, 0, 0);
-            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], zb[0], a, 0, 0, 0);
+            for (int p = 0; p < 2; ++p)
+                zb[p] = *reinterpret_cast<const seq_h8_t *>(&z[cur][p][(group0 + g) * 32 + (lane & 31)][16 * s + 8 * half]);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[1], zb[0], a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[0], zb[1], a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[0], zb[0], a, 0, 0, 0);
         };
         for (int t = 0; t < steps; ++t) {
             const int cur = t & 1;
@@ -441,17 +475,17 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                 if constexpr (BIG) {
 #pragma unroll
                     for (int g = 0; g < JG; ++g) seq_from_pieces(acc[g]);
-                    seq_b8_t wa[3], wn[3];
+                    seq_h8_t wa[2], wn[2];
 #pragma unroll
-                    for (int p = 0; p < 3; ++p) wa[p] = wl[p * 64];
+                    for (int p = 0; p < 2; ++p) wa[p] = wl[p * 64];
                     for (int s = 0; s < ks; ++s) {
                         const int sn = s + 1 < ks ? s + 1 : s;
 #pragma unroll
-                        for (int p = 0; p < 3; ++p) wn[p] = wl[(sn * 3 + p) * 64];
+                        for (int p = 0; p < 2; ++p) wn[p] = wl[(sn * 2 + p) * 64];
 #pragma unroll
                         for (int g = 0; g < JG; ++g) product(cur, g, acc[g], wa, s);
 #pragma unroll
-                        for (int p = 0; p < 3; ++p) wa[p] = wn[p];
+                        for (int p = 0; p < 2; ++p) wa[p] = wn[p];
                     }
                 }
 #pragma unroll
@@ -472,8 +506,8 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                         float h[4], c[4] = {cv.x, cv.y, cv.z, cv.w};
 #pragma unroll
                         for (int m = 0; m < 4; ++m) {
-                            const float gi = seq_sigmoid(acc[g][4 * m]), gf = seq_sigmoid(acc[g][4 * m + 1]);
-                            const float gg = seq_tanh(acc[g][4 * m + 2]), go = seq_sigmoid(acc[g][4 * m + 3]);
+                            const float gi = seq_sigmoid(acc[g][4 * m], by[m]), gf = seq_sigmoid(acc[g][4 * m + 1], by[m]);
+                            const float gg = seq_tanh(acc[g][4 * m + 2], by[m]), go = seq_sigmoid(acc[g][4 * m + 3], by[m]);
                             c[m] = fmaf(gf, c[m], gi * gg);             // (spelled out: one rounding, the same in every copy of this code)
                             h[m] = go * seq_tanh(c[m]);
                             if constexpr (TAPE) { acc[g][4 * m] = gi; acc[g][4 * m + 1] = gf; acc[g][4 * m + 2] = gg; acc[g][4 * m + 3] = go; }
@@ -482,6 +516,7 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                         const float4 h4 = make_float4(h[0], h[1], h[2], h[3]), c4 = make_float4(c[0], c[1], c[2], c[3]);
                         if constexpr (C_LDS) *reinterpret_cast<float4 *>(&cs[j][unit0]) = c4;
                         else creg[g] = c4;
+                        if constexpr (TAPE) *reinterpret_cast<float4 *>(&hs[j][unit0]) = h4;
                         // (gates, c and h leave for the tape further down, in larger pieces)
                         if (keep[g] >= 0) {                // a state that another path starts from, or some a_v
                             const size_t o = (size_t)keep[g] * hidden + unit0;
@@ -523,7 +558,7 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
             }
             __syncthreads();                               // the h rows of the next step are complete, this step's have been read
             if constexpr (TAPE) {
-                // h and c of the step as whole rows, h out of the operand buffer (the three pieces add up to it exactly).  A wavefront holds 32 bytes of
+                // h and c of the step as whole rows.  A wavefront holds 32 bytes of
                 // c per path: written from there, they left as 64-byte requests that were half empty (6.8 GB instead of 5.9 at 3.35 M cells of 64
                 // units: 2.18 ms, now 1.59; 0.85 M cells of 128: 1.33 and 1.19).
                 const int tid = seq_opaque(threadIdx.x), j = tid / (HMAX / 8), part = tid % (HMAX / 8);
@@ -533,18 +568,11 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                     for (int i = 0; i < 2; ++i) {
                         const int u = part * 4 + i * (HMAX / 2);
                         if (u >= hidden) continue;
-                        float h[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int p = 0; p < 3; ++p) {
-                            const uint2 w = *reinterpret_cast<const uint2 *>(&z[cur ^ 1][p][j][u]);
-                            h[0] += __uint_as_float(w.x << 16); h[1] += __uint_as_float(w.x & 0xffff0000u);
-                            h[2] += __uint_as_float(w.y << 16); h[3] += __uint_as_float(w.y & 0xffff0000u);
-                        }
-                        st4_stream(A.tape_h + cell + u, make_float4(h[0], h[1], h[2], h[3]));
+                        st4_stream(A.tape_h + cell + u, *reinterpret_cast<const float4 *>(&hs[j][u]));
                         st4_stream(A.tape_c + cell + u, *reinterpret_cast<const float4 *>(&cs[j][u]));
                     }
                 }
-                __syncthreads();                           // the rows of c have been read
+                __syncthreads();                           // the rows of h and c have been read
             }
         }
         if (on) publish((steps - 1) & 1);
@@ -1160,8 +1188,15 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
                 sum = 0.f;
             }
         } else {
+            // the rows of a chunk among themselves first: fewer roundings at the size of the running sum
+            float part[CK / 2];
 #pragma unroll
-            for (int c = 0; c < CK; ++c) sum += rg[c];
+            for (int c = 0; c < CK / 2; ++c) part[c] = rg[c] + rg[c + CK / 2];
+#pragma unroll
+            for (int n = CK / 4; n > 0; n /= 2)
+#pragma unroll
+                for (int c = 0; c < n; ++c) part[c] += part[c + n];
+            sum += part[0];
         }
         __syncthreads();
         if (c0 + CK < last) {
@@ -1673,8 +1708,8 @@ static SeqLayout seq_layout(const hag_seq_t *h, int64_t d, int64_t hidden) {
     L.ks = hidden > 64 ? (hidden + 15) / 16 : hidden > 32 ? 4 : 2;
     size_t at = 0;
     L.wx = at; at += up(4 * H * (size_t)L.dp * f);
-    L.wq = at; at += up((H / 8) * (size_t)L.ks * 3 * 512 * sizeof(uint16_t));
-    L.bp = at; at += up(4 * H * f);
+    L.wq = at; at += up((H / 8) * (size_t)L.ks * 2 * 512 * sizeof(uint16_t));
+    L.bp = at; at += up(5 * H * f);
     L.h = at; at += up(states * H * f);
     L.c = at; at += up(states * H * f);
     L.flags = at; at += up(states * sizeof(int32_t));
@@ -1705,8 +1740,8 @@ static int seq_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const floa
     uint16_t *wq = (uint16_t *)(w + L.wq);
     int32_t *flags = (int32_t *)(w + L.flags);              // [n_states]
     {
-        const int64_t total = std::max<int64_t>({4 * hidden * L.dp, hidden / 8 * L.ks * 512, std::min<int64_t>(std::max(h->n_states, h->n_empty > 0 ? h->n : 0), 1 << 20)});
-        hipLaunchKernelGGL(seq_pack_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, w_ih, w_hh, b, wx, wq, bp, (int)d,
+        const int64_t total = std::min<int64_t>(std::max(h->n_states, h->n_empty > 0 ? h->n : 0), 1 << 20);   // counters and nodes with an empty list
+        hipLaunchKernelGGL(seq_pack_kernel, dim3((unsigned)std::max<int64_t>((total + 255) / 256, hidden)), dim3(256), 0, s, w_ih, w_hh, b, wx, wq, bp, (int)d,
                            (int)L.dp, (int)hidden, (int)L.ks, flags, h->n_states, h->n_empty > 0 ? h->d_final : nullptr, a_out, h->n);
         HIP_TRY(hipGetLastError());
     }
@@ -1729,7 +1764,7 @@ static int seq_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const floa
         c.publish = h->wait_unreachable ? 0 : 1;
         c.gave_up = h->d_gave_up;
         c.step_g = h->d_step_g; c.step_out = h->d_step_out;
-        c.gx = gx; c.wq = wq; c.h = hst; c.c = cst; c.a_out = a_out;
+        c.gx = gx; c.wq = wq; c.unscale = bp + 4 * hidden; c.h = hst; c.c = cst; c.a_out = a_out;
         c.tape_g = tape_g; c.tape_c = tape_c; c.tape_h = tape_h;
         c.hidden = (int32_t)hidden;
         if (c.n_path_tiles <= 0) continue;

@@ -102,3 +102,25 @@ def test_gradients_scale_with_the_gradient_they_come_from(B, d, hidden):
     others = np.setdiff1d(np.arange(n), read)
     assert not torch.isfinite(g_x[read]).all(1).any() and not torch.isfinite(g_b).any()
     assert torch.equal(g_x[others], plain[0][others])
+
+
+@pytest.mark.parametrize("d,hidden", [(8, 8), (16, 40), (20, 64), (12, 120)])
+def test_units_of_very_different_weights(B, d, hidden):
+    # Every unit's weights are brought to a common size by a power of two of their own: units of weight 2^3, 1, 2^-12, 2^-60 and 0 side by side, and
+    # a feature far outside fp16's range in both directions.
+    n = 150
+    rowptr, col = lists(n, hidden)
+    rng = np.random.default_rng(d)
+    size = np.tile(np.array([8.0, 1.0, 2.0 ** -12, 2.0 ** -60, 0.0])[np.arange(hidden) % 5], 4)[:, None]
+    x, w_ih, w_hh, b = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)) * size, rng.normal(0, 0.3, 4 * hidden)
+    x[3, 1], x[5, 2] = 1e25, 1e-25
+    f32 = [a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b)]
+    want, _ = lstm.naive_aggregate(rowptr, col, *f32)
+    # pre-activations of hidden terms of 8 * 0.3 |h| and d of 0.3: (0.5 * 2.4 hidden + d) * 2^-24 at most, the gates' slopes are below 1
+    bar = 1e-6 + (1.2 * hidden + d) * 2.0 ** -24 * 4
+    for cap in (0, int(col.size)):
+        h = B.SeqHag(rowptr, col, cap).upload()
+        got = h.lstm_forward(dev(x), dev(w_ih), dev(w_hh), dev(b))
+        assert np.abs(got.cpu().numpy() - want).max() <= bar
+        a, _ = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
+        assert torch.equal(a, got)

@@ -608,7 +608,8 @@ struct SeqRevArgs {
     const int32_t *paths;    // this level's paths in tiles of 64
     int64_t n_path_tiles;
     const int32_t *step_out;
-    const float *wqt;        // W_hh^T in the order the matrix instructions consume it, see seq_pack_transposed_kernel
+    const uint16_t *wqt;     // W_hh^T in fp16 pieces, in the order the matrix instructions consume it, see seq_backward_start_kernel
+    const float *wqt_unscale;   // per hidden unit, likewise
     float *tape_g;           // in: the activated gates of every step; out: the gradients of its pre-activations
     const float *tape_c;     // c' of every step
     const float *c_state;    // c rows of the kept states
@@ -624,40 +625,75 @@ struct SeqRevArgs {
 };
 
 
+// The power of two that brings numbers of size `most` to [2^14, 2^15), as its exponent: as far up as fp16's range allows, so that what the second piece
+// of a number rounds off (2^-25 at least, see seq_halves2) is 2^-39 of the largest.  Infinities and NaN stay what they are.
+// the largest of sixteen lanes, in all of them
+__device__ __forceinline__ float seq_max16(float v) {
+#define HAG_SEQ_ROR(n) v = fmaxf(v, __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x120 + n, 0xf, 0xf, false)))
+    HAG_SEQ_ROR(8); HAG_SEQ_ROR(4); HAG_SEQ_ROR(2); HAG_SEQ_ROR(1);
+#undef HAG_SEQ_ROR
+    return v;
+}
+__device__ __forceinline__ int seq_up(float most) { return most < INFINITY ? min(15 - __builtin_amdgcn_frexp_expf(most), 126) : 0; }
+
 // What the backward pass starts from, in one launch: cleared gradient rows of the kept states, cleared g_x where some node is in no list
 // (n_g_x > 0), the pending counts of a one-launch pass (n_states > 0) and the weights of the products, from the usual layout.
-//   wqt, hidden <= 64: [gate tile][m_tiles of 32 hidden units][16][lane]; lane l supplies output unit 32 * mt + l % 32, and as k
-//       value e = 4 m + gate the gate row of unit 8 * tile + 4 * (l / 32) + m: the order in which the lanes hold dG;
-//   wqt, hidden > 64: [m_tiles][4H / 8 groups of four k-steps][lane][4]; lane l supplies unit 32 * mt + l % 32, k-step q the gate
-//       rows 2 q + l / 32 in (unit, gate) order;
+//   wqt: W_hh^T in two fp16 pieces, the weights of an output unit (a column of W_hh) brought to a common size by a power of two (seq_up); unscale: per output
+//       unit 2^15 over that power, see seq_reverse_kernel;
+//     hidden <= 64: [gate tile][m_tiles of 32 hidden units][2 steps of 16][piece][lane][8]; lane l supplies output unit 32 * mt + l % 32, and as k
+//       value e = 8 * step + i = 4 m + gate the gate row of unit 8 * tile + 4 * (l / 32) + m: the order in which the lanes hold dG;
+//     hidden > 64: [m_tiles][4H / 16 steps][piece][lane][8]; lane l supplies unit 32 * mt + l % 32, k = 16 * step + 8 * (l / 32) + i the gate
+//       row in (unit, gate) order;
 //   wxt: W_ih^T for g_x: [d tiles of 32 columns][4H / 8 groups of four k-steps][lane][4]; lane l supplies column 32 * tile + l % 32,
 //       k-step q the gate rows 2 q + l / 32.
+// The first 32 * m_tiles workgroups (there are at least as many) cut one column of W_hh each.
 __global__ __launch_bounds__(256) void seq_backward_start_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
-                                                                float *__restrict__ wqt, float *__restrict__ wxt, int d, int hidden,
+                                                                uint16_t *__restrict__ wqt, float *__restrict__ unscale, float *__restrict__ wxt, int d, int hidden,
                                                                 float *__restrict__ state_grads, int64_t n_state_grads, float *__restrict__ g_x,
                                                                 int64_t n_g_x, const int32_t *__restrict__ pending_init,
                                                                 int32_t *__restrict__ pending, int64_t n_states) {
+    __shared__ float largest[4];
     const int m_tiles = (hidden + 31) / 32, d_tiles = (d + 31) / 32, rows = 4 * hidden;
     const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
     for (int64_t i = first; i < n_state_grads; i += stride) state_grads[i] = 0.f;
     for (int64_t i = first; i < n_g_x; i += stride) g_x[i] = 0.f;
     for (int64_t i = first; i < n_states; i += stride) pending[i] = pending_init[i];
-    for (int64_t i = first; i < (int64_t)m_tiles * 32 * rows; i += stride) {
-        int unit, gate, z;
-        if (hidden <= 64) {
-            const int lane = (int)(i & 63), e = (int)(i >> 6) & 15, mt = (int)(i >> 10) % m_tiles, tile = (int)(i >> 10) / m_tiles;
-            unit = tile * 8 + (lane >> 5) * 4 + (e >> 2); gate = e & 3; z = mt * 32 + (lane & 31);
-        } else {
-            const int mt = (int)(i / (32 * rows)), rest = (int)(i % (32 * rows)), q = rest / 256, lane = (rest % 256) / 4;
-            const int r = 2 * (4 * q + (rest & 3)) + (lane >> 5);
-            unit = r >> 2; gate = r & 3; z = mt * 32 + (lane & 31);
-        }
-        wqt[i] = z < hidden ? w_hh[(size_t)(gate * hidden + unit) * hidden + z] : 0.f;
-    }
     for (int64_t i = first; i < (int64_t)d_tiles * 32 * rows; i += stride) {
         const int tile = (int)(i / (32 * rows)), rest = (int)(i % (32 * rows)), q = rest / 256, lane = (rest % 256) / 4;
         const int r = 2 * (4 * q + (rest & 3)) + (lane >> 5), z = tile * 32 + (lane & 31);
         wxt[i] = z < d ? w_ih[(size_t)((r & 3) * hidden + (r >> 2)) * d + z] : 0.f;
+    }
+    const int z = blockIdx.x, mt = z >> 5;
+    if (z >= 32 * m_tiles) return;
+    float v[2], most = 0.f;                                // row r = threadIdx.x + 256 i of the column, in (unit, gate) order (4H is 512 at most)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = threadIdx.x + 256 * i;
+        v[i] = z < hidden && r < rows ? w_hh[(size_t)((r & 3) * hidden + (r >> 2)) * hidden + z] : 0.f;
+        most = fmaxf(most, fabsf(v[i]));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off));
+    if ((threadIdx.x & 63) == 0) largest[threadIdx.x >> 6] = most;
+    __syncthreads();
+    const int up = seq_up(fmaxf(fmaxf(largest[0], largest[1]), fmaxf(largest[2], largest[3])));
+    const float by = __builtin_ldexpf(1.f, up);
+    if (threadIdx.x == 0 && z < hidden) unscale[z] = __builtin_ldexpf(1.f, 15 - up);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = threadIdx.x + 256 * i;
+        if (r >= rows) continue;
+        uint32_t p[2];
+        seq_halves2(v[i] * by, 0.f, p);
+        size_t at;
+        if (hidden <= 64) {
+            const int unit = r >> 2, e = 4 * (unit & 3) + (r & 3);
+            at = ((size_t)(((unit >> 3) * m_tiles + mt) * 2 + (e >> 3)) * 2 * 64 + (z & 31) + 32 * ((unit >> 2) & 1)) * 8 + (e & 7);
+        } else {
+            at = ((size_t)(mt * (rows / 16) + (r >> 4)) * 2 * 64 + (z & 31) + 32 * ((r >> 3) & 1)) * 8 + (r & 7);
+        }
+        wqt[at] = (uint16_t)(p[0] & 0xffffu);
+        wqt[at + 512] = (uint16_t)(p[1] & 0xffffu);
     }
 }
 
@@ -694,23 +730,31 @@ constexpr int kSeqRevJobs = 32;   // paths per workgroup of the reverse kernels 
 // gate tile w), their running dh and dc and, per step, the sixteen dG.  The k index of dh_prev = W_hh^T dG can be taken in any order, so the
 // dG are the product's operand where they are, in the registers of the lane that made them: wavefront w multiplies the 32 gate
 // rows of its own tile and leaves its part of dh_prev for all units in LDS; after a barrier every lane adds the parts
-// for its own units, in a fixed order.  The gates of the next step are requested before the product.  Above 32 units a
+// for its own units, in a fixed order.  The operands are two fp16 pieces each (seq_halves2): gradients have no bound, so the
+// largest of a path's 32 gate rows in the tile says what power of two brings them into fp16's range (seq_up), and whoever adds the parts multiplies by what undoes it.
+// The matrix cores cut what they add up, always downwards, and the gradients of hundreds of thousands of cells are added in the end: the factor's
+// sign alternates over paths, tiles and steps, so that half of the parts are cut upwards.  (Error of the training step's results against 64 bits at 3.35 M cells: 4.4e-6
+// with one sign, 4.9e-7 so, 5e-7 with fp32 instructions.)  The gates of the next step are requested before the product.  Above 32 units a
 // workgroup takes half a tile (70 KB of LDS, 128 registers), so that two share a compute unit and one's tape accesses run beside the other's products: the kernel is bound
-// by the tape (read gates and c, write dG: 36 H bytes per cell).  3.35 M cells of 64 units: 2.43 ms with 64 paths and one workgroup per compute unit, 2.30 with halves.
+// by the tape (read gates and c, write dG: 36 H bytes per cell).  3.35 M cells of 64 units: 2.43 ms with 64 paths and one workgroup per compute unit, 2.23 with halves,
+// of which the fp32 matrix instructions were 37 %; 1.93 with fp16 pieces.
 template <int HMAX>
 __global__ __launch_bounds__(512, 4) void seq_reverse_kernel(SeqRevArgs A) {
     constexpr int MT = HMAX / 32, JG = 1, NT = HMAX / 8, RS = HMAX + 4, RJ = HMAX == 64 ? kSeqRevJobs : kSeqJobs;
     __shared__ __align__(16) float red[NT][RJ][RS];
+    __shared__ __align__(16) float sun[HMAX];              // the units' factors
     __shared__ int32_t sdesc[RJ * 4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int hidden = A.hidden, n_tiles = hidden / 8, m_tiles = (hidden + 31) / 32;
     const int tile = HMAX == 64 ? wave : (wave & 3), group0 = HMAX == 64 ? 0 : (wave >> 2);
     const bool on = tile < n_tiles;
-    float wt[MT][16];
+    seq_h8_t wt[MT][2][2];                                 // [output tile][step][piece]
+    const seq_h8_t *wl = reinterpret_cast<const seq_h8_t *>(A.wqt) + lane;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) wt[mt][e] = on && mt < m_tiles ? A.wqt[(((size_t)tile * m_tiles + mt) * 16 + e) * 64 + lane] : 0.f;
+        for (int k = 0; k < 4; ++k) wt[mt][k >> 1][k & 1] = on && mt < m_tiles ? wl[(((size_t)tile * m_tiles + mt) * 4 + k) * 64] : seq_h8_t{};
+    if ((int)threadIdx.x < hidden) sun[threadIdx.x] = A.wqt_unscale[threadIdx.x];   // (read behind the barriers of a tile)
     const int64_t n_parts = A.n_path_tiles * (kSeqJobs / RJ);
     for (int64_t ci = blockIdx.x; ci < n_parts; ci += gridDim.x) {
         const int64_t ct = A.reversed ? n_parts - 1 - ci : ci;
@@ -752,9 +796,11 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_kernel(SeqRevArgs A) {
             for (int w = 0; w < NT; ++w) {
                 if (w >= n_tiles) break;
                 const float4 q = *reinterpret_cast<const float4 *>(&red[w][j][unit0]);
-                v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+                const float by = red[w][j][HMAX];
+                v.x = fmaf(q.x, by, v.x); v.y = fmaf(q.y, by, v.y); v.z = fmaf(q.z, by, v.z); v.w = fmaf(q.w, by, v.w);
             }
-            dh[g][0] = v.x; dh[g][1] = v.y; dh[g][2] = v.z; dh[g][3] = v.w;
+            const float4 un4 = *reinterpret_cast<const float4 *>(&sun[unit0]);
+            dh[g][0] = v.x * un4.x; dh[g][1] = v.y * un4.y; dh[g][2] = v.z * un4.z; dh[g][3] = v.w * un4.w;
         };
 #pragma unroll
         for (int g = 0; g < JG; ++g) {
@@ -822,13 +868,34 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_kernel(SeqRevArgs A) {
 #pragma unroll
                 for (int g = 0; g < JG; ++g) {
                     const int l = seq_opaque(threadIdx.x) & 63, half = l >> 5, j = (group0 + g) * 32 + (l & 31);
+                    float most = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) most = fmaxf(most, fabsf(dg[g][e]));
+                    const seq_u2_t both = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
+                    const int up = seq_up(fmaxf(__uint_as_float(both.x), __uint_as_float(both.y)));   // of the path's 32 gate rows
+                    const float one = (tile + j + t) & 1 ? -1.f : 1.f, by = __builtin_ldexpf(one, up);
+                    if (half == 0) red[tile][j][HMAX] = __builtin_ldexpf(one, -15 - up);
+                    seq_h8_t zb[2][2];                     // [step][piece]
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        uint32_t p[4][2];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) seq_halves2(dg[g][8 * k + 2 * i] * by, dg[g][8 * k + 2 * i + 1] * by, p[i]);
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) zb[k][i] = __builtin_bit_cast(seq_h8_t, make_uint4(p[0][i], p[1][i], p[2][i], p[3][i]));
+                    }
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) {
                         seq_acc_t acc;
 #pragma unroll
                         for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-                        for (int e = 0; e < 16; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wt[mt][e], dg[g][e], acc, 0, 0, 0);
+                        for (int k = 0; k < 2; ++k) {
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[mt][k][1], zb[k][0], acc, 0, 0, 0);
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[mt][k][0], zb[k][1], acc, 0, 0, 0);
+                        }
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[mt][k][0], zb[k][0], acc, 0, 0, 0);
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
                             *reinterpret_cast<float4 *>(&red[tile][j][mt * 32 + 8 * q + 4 * half]) = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
@@ -884,19 +951,23 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_kernel(SeqRevArgs A) {
 // Hidden sizes from 72 to 128.  A workgroup takes half a tile, 32 paths: dG is staged as rows of 4 * 128 + 2 in LDS (66 KB), so that two workgroups share
 // a compute unit and one's loads, stores and element-wise part run beside the other's products.  (With 64 paths and 131 KB a workgroup had the compute unit to
 // itself and its phases followed one another: 2.63 ms for 0.85 M cells of 128 hidden units, of which the products are 0.72 and the tape's bytes 0.75; as halves
-// 1.86 ms.)
+// 1.77 ms.)
 // Sixteen threads per path run the element-wise part; every wavefront multiplies one 32-unit tile of W_hh^T, streamed from the L2 cache, with one half
-// of the gate rows, and the two parts are added by whoever reads dh_prev.
+// of the gate rows, and the two parts are added by whoever reads dh_prev.  Operands in two fp16 pieces as in the kernel above, a path's gradients with one factor
+// for all gate rows (fp32 matrix instructions were busy 50 % of the time: 1.77 ms, 1.27 so; error against 64 bits 6.6e-7 and 5.1e-7).
 __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) {
-    constexpr int ZG = 4 * 128 + 2, IT = 8, TP = 16;       // units per thread, threads per path
-    // per path: the pre-activation gradients of the current step (the product's operand), then the two parts of the product's result
-    // dh_prev; the running dh and dc themselves stay in the registers of the path's sixteen threads
-    __shared__ __align__(16) float zg[kSeqRevJobs * ZG];
+    constexpr int ZS = 4 * 128 + 8, IT = 8, TP = 16;       // units per thread, threads per path; rows 4 banks apart
+    // per path: the pre-activation gradients of the current step in fp16 pieces (the product's operand), then, in the row of the first pieces, the two parts
+    // of the product's result dh_prev; the running dh and dc themselves stay in the registers of the path's sixteen threads
+    __shared__ __align__(16) uint16_t z[2][kSeqRevJobs][ZS];
+    __shared__ float sun[128];                             // the units' factors
+    auto row_of = [&](int j) { return reinterpret_cast<float *>(&z[0][j][0]); };   // 256 floats (and four of padding)
     __shared__ int32_t sdesc[kSeqRevJobs * 4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int hidden = A.hidden, n_rt = (hidden + 31) / 32;          // 3 or 4 row tiles of the product
-    const int sj = threadIdx.x / TP, part = threadIdx.x % TP;        // element-wise phases: 16 threads per path, all in one wavefront
+    // element-wise phases: 16 threads per path, all in one wavefront (their places are derived again in every phase: registers are short)
     const int64_t n_halves = A.n_path_tiles * (kSeqJobs / kSeqRevJobs);
+    if ((int)threadIdx.x < hidden) sun[threadIdx.x] = A.wqt_unscale[threadIdx.x];   // (read behind the barriers of a tile)
     for (int64_t ci = blockIdx.x; ci < n_halves; ci += gridDim.x) {
         const int64_t ct = A.reversed ? n_halves - 1 - ci : ci;
         if (threadIdx.x < kSeqRevJobs * 4) sdesc[threadIdx.x] = A.paths[ct * (kSeqRevJobs * 4) + threadIdx.x];
@@ -904,12 +975,13 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
         const int steps = sdesc[2];                        // the first path is the longest
         // unit 16 * it + part: the sixteen threads of a path move 256 contiguous bytes of its gates per instruction
         float dcv[IT];
+        float back = 1.f;                                  // with the unit's factor, what the product's result is multiplied by
         // the tape of a step is requested while the product of the one after it runs
         float4 gates[IT];
         float c_now[IT], c_prev[IT];                       // c_prev is the next step's c_now
         int keep = -1;
         auto load_step = [&](int t) {
-            const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, start = sdesc[sj * 4];   // (indices are derived again in every phase: registers are short)
+            const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, start = sdesc[sj * 4];
             const size_t cell = (size_t)sdesc[sj * 4 + 1] + t;
             keep = A.step_out[cell];
             const float *before = t > 0 ? A.tape_c + (cell - 1) * hidden : start >= 0 ? A.c_state + (size_t)start * hidden : nullptr;
@@ -922,13 +994,13 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
             }
         };
         {
-            const int beg = sdesc[sj * 4 + 1], len = sdesc[sj * 4 + 2], node = sdesc[sj * 4 + 3];
+            const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, beg = sdesc[sj * 4 + 1], len = sdesc[sj * 4 + 2], node = sdesc[sj * 4 + 3];
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
                 const int u = TP * it + part;
                 // (dh lives in the path's row, as the sum of two parts, so that it takes no registers during the products)
-                zg[sj * ZG + u] = node >= 0 && u < hidden ? A.g_a[(size_t)node * hidden + u] : 0.f;
-                zg[sj * ZG + 128 + u] = 0.f;
+                row_of(sj)[u] = node >= 0 && u < hidden ? A.g_a[(size_t)node * hidden + u] : 0.f;
+                row_of(sj)[128 + u] = 0.f;
                 dcv[it] = c_prev[it] = 0.f;
                 gates[it] = make_float4(0.f, 0.f, 0.f, 0.f);
                 c_now[it] = len > 0 && u < hidden ? A.tape_c[((size_t)beg + len - 1) * hidden + u] : 0.f;
@@ -945,9 +1017,14 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                 // wavefront, whose LDS accesses take effect in program order, and the fence keeps the compiler to that order.
                 float dhv[IT];
 #pragma unroll
-                for (int it = 0; it < IT; ++it) dhv[it] = zg[sj * ZG + TP * it + part] + zg[sj * ZG + 128 + TP * it + part];
+                for (int it = 0; it < IT; ++it) {
+                    const int u = TP * it + part;
+                    const float sum = row_of(sj)[u] + row_of(sj)[128 + u];
+                    dhv[it] = t + 1 < len && u < hidden ? sum * back * sun[u] : sum;   // (before the first step: g_a as it is)
+                }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
+                float most = 0.f;
 #pragma unroll
                 for (int it = 0; it < IT; ++it) {
                     const int u = TP * it + part;
@@ -966,30 +1043,52 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                     dcv[it] = dcc * g4.y;
                     c_now[it] = c_prev[it];
                     *reinterpret_cast<float4 *>(A.tape_g + (cell * hidden + u) * 4) = dg;   // kept for the weight gradients
-                    *reinterpret_cast<float2 *>(&zg[sj * ZG + u * 4]) = make_float2(dg.x, dg.y);
-                    *reinterpret_cast<float2 *>(&zg[sj * ZG + u * 4 + 2]) = make_float2(dg.z, dg.w);
+                    gates[it] = dg;
+                    most = fmaxf(fmaxf(most, fmaxf(fabsf(dg.x), fabsf(dg.y))), fmaxf(fabsf(dg.z), fabsf(dg.w)));
+                }
+                __builtin_amdgcn_sched_barrier(0);         // (registers are short)
+                most = seq_max16(most);                    // of the path's gate rows
+                const int up = seq_up(most);
+                const float one = (sj + t) & 1 ? -1.f : 1.f, by = __builtin_ldexpf(one, up);
+                back = __builtin_ldexpf(one, -15 - up);
+#pragma unroll
+                for (int it = 0; it < IT; ++it) {
+                    const int u = TP * it + part;
+                    if (u >= hidden) continue;
+                    uint32_t a[2], b[2];
+                    seq_halves2(gates[it].x * by, gates[it].y * by, a);
+                    seq_halves2(gates[it].z * by, gates[it].w * by, b);
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2 *>(&z[p][sj][u * 4]) = make_uint2(a[p], b[p]);
                 }
             }
             if (t > 0 && t - 1 < len) load_step(t - 1);
             __syncthreads();
             // dh_prev^T [units, paths] = W_hh^T . dG^T [4H, paths], the gate rows in two halves
+            const int lane = seq_opaque(threadIdx.x) & 63;
             seq_acc_t acc;
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = 0.f;
             const bool has_pair = wave < 2 * n_rt;
             const int rt = wave % n_rt, half = wave / n_rt;
             if (has_pair) {
-                const int q0 = half * (hidden / 4), q1 = q0 + hidden / 4;   // groups of eight gate rows (hidden is a multiple of 8)
-                const float4 *wq = reinterpret_cast<const float4 *>(A.wqt) + (size_t)rt * (hidden / 2) * 64 + lane;
-                const float *zl = &zg[(lane & 31) * ZG + (lane >> 5)];
-                float4 wa = wq[q0 * 64];
-                for (int q = q0; q < q1; ++q) {
-                    const float4 wn = wq[(q + 1 < q1 ? q + 1 : q) * 64];
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.x, zl[2 * (4 * q + 0)], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.y, zl[2 * (4 * q + 1)], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.z, zl[2 * (4 * q + 2)], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wa.w, zl[2 * (4 * q + 3)], acc, 0, 0, 0);
-                    wa = wn;
+                const int s0 = half * (hidden / 8), s1 = s0 + hidden / 8;   // steps of sixteen gate rows (hidden is a multiple of 8)
+                const seq_h8_t *wq = reinterpret_cast<const seq_h8_t *>(A.wqt) + (size_t)rt * (hidden / 4) * 2 * 64 + lane;
+                seq_h8_t wa[2], wn[2], zb[2];
+#pragma unroll
+                for (int p = 0; p < 2; ++p) wa[p] = wq[(s0 * 2 + p) * 64];
+#pragma unroll 1
+                for (int s = s0; s < s1; ++s) {
+                    const int sn = s + 1 < s1 ? s + 1 : s;
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) wn[p] = wq[(sn * 2 + p) * 64];
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) zb[p] = *reinterpret_cast<const seq_h8_t *>(&z[p][lane & 31][16 * s + 8 * (lane >> 5)]);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[1], zb[0], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[0], zb[1], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[0], zb[0], acc, 0, 0, 0);
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) wa[p] = wn[p];
                 }
             }
             __syncthreads();                               // every product has read the staged gradients
@@ -999,7 +1098,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int row = rt * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-                        if (row < hidden) zg[j * ZG + 128 * half + row] = acc[r];
+                        if (row < hidden) row_of(j)[128 * half + row] = acc[r];
                     }
                 }
             }
@@ -1007,17 +1106,19 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
         }
         // what is left: the gradient of the state the path started from, dh (in two parts) beside dc in the path's row, added by whole wavefronts so
         // that an atomic instruction covers contiguous bytes
+        const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, lane = tid & 63;
         if (__syncthreads_or(sdesc[sj * 4] >= 0)) {
 #pragma unroll
-            for (int it = 0; it < IT; ++it)
-                if (TP * it < hidden) zg[sj * ZG + 256 + TP * it + part] = dcv[it];
+            for (int it = 0; it < IT; ++it) reinterpret_cast<float *>(&z[1][sj][0])[TP * it + part] = dcv[it];
+            if (part == 0) row_of(sj)[256] = back;
             __syncthreads();
             for (int j = wave; j < kSeqRevJobs; j += 8) {
                 const int from = sdesc[j * 4];
                 if (from < 0) continue;
+                const float *dh = row_of(j), *dc = reinterpret_cast<const float *>(&z[1][j][0]);
                 for (int u = lane; u < hidden; u += 64) {
-                    __hip_atomic_fetch_add(A.gh + (size_t)from * hidden + u, zg[j * ZG + u] + zg[j * ZG + 128 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_fetch_add(A.gc + (size_t)from * hidden + u, zg[j * ZG + 256 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(A.gh + (size_t)from * hidden + u, (dh[u] + dh[128 + u]) * dh[256] * sun[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(A.gc + (size_t)from * hidden + u, dc[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
             if (A.pending) {
@@ -1786,7 +1887,7 @@ int hag_seq_lstm_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const fl
 }
 
 // Layout of the training workspace: the forward workspace, then the tape and the backward pass's own buffers.
-struct SeqTrainLayout { SeqWgradShape hh, ih; size_t fwd, tape_g, tape_c, tape_h, gh, gc, pending, wqt, wxt, s, edge_first, edge_last, partial_hh, partial_ih, total; };
+struct SeqTrainLayout { SeqWgradShape hh, ih; size_t fwd, tape_g, tape_c, tape_h, gh, gc, pending, wqt, unscale, wxt, s, edge_first, edge_last, partial_hh, partial_ih, total; };
 static SeqTrainLayout seq_train_layout(const hag_seq_t *h, int64_t d, int64_t hidden) {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t cells = std::max<size_t>(h->step_x.size(), 1), states = (size_t)std::max<int64_t>(h->n_states, 1);
@@ -1803,6 +1904,7 @@ static SeqTrainLayout seq_train_layout(const hag_seq_t *h, int64_t d, int64_t hi
     L.gc = at; at += up(states * H * f);
     L.pending = at; at += up(states * sizeof(int32_t));
     L.wqt = at; at += up((H + 31) / 32 * 32 * 4 * H * f);
+    L.unscale = at; at += up(H * f);
     L.wxt = at; at += up(((size_t)d + 31) / 32 * 32 * 4 * H * f);
     L.s = at; at += up(used * 4 * H * f);
     L.edge_first = at; at += up((size_t)L.hh.groups * 4 * H * f);
@@ -1852,7 +1954,8 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
     const SeqLayout F = seq_layout(h, d, hidden);           // the forward pass left its state rows there
     const float *hst = (const float *)(w + F.h), *cst = (const float *)(w + F.c);
     float *tape_g = (float *)(w + L.tape_g), *tape_c = (float *)(w + L.tape_c), *tape_h = (float *)(w + L.tape_h);
-    float *gh = (float *)(w + L.gh), *gc = (float *)(w + L.gc), *wqt = (float *)(w + L.wqt), *wxt = (float *)(w + L.wxt), *sums = (float *)(w + L.s);
+    float *gh = (float *)(w + L.gh), *gc = (float *)(w + L.gc), *unscale = (float *)(w + L.unscale), *wxt = (float *)(w + L.wxt), *sums = (float *)(w + L.s);
+    uint16_t *wqt = (uint16_t *)(w + L.wqt);
     const int64_t cells = (int64_t)h->step_x.size(), n_used = (int64_t)h->used.size();
     auto blocks = [](int64_t total) { return dim3((unsigned)std::min<int64_t>((total + 255) / 256, 65535 * 16)); };
     const int64_t levels = (int64_t)h->tile_ptr.size() - 1;
@@ -1863,8 +1966,8 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
     {
         const int64_t n_state_grads = (int64_t)((L.pending - L.gh) / sizeof(float));   // (gh and gc are adjacent)
         const int64_t n_g_x = n_used < h->n ? h->n * d : 0, n_states = fused ? h->n_states : 0;
-        const int64_t total = std::max({4 * hidden * std::max((hidden + 31) / 32, (d + 31) / 32) * 32, n_state_grads, n_g_x, n_states});
-        hipLaunchKernelGGL(seq_backward_start_kernel, blocks(total), dim3(256), 0, s, w_ih, w_hh, wqt, wxt, (int)d, (int)hidden, gh, n_state_grads, g_x, n_g_x,
+        const int64_t total = std::max({4 * hidden * (d + 31) / 32 * 32, (hidden + 31) / 32 * 32 * 256, n_state_grads, n_g_x, n_states});
+        hipLaunchKernelGGL(seq_backward_start_kernel, blocks(total), dim3(256), 0, s, w_ih, w_hh, wqt, unscale, wxt, (int)d, (int)hidden, gh, n_state_grads, g_x, n_g_x,
                            h->d_pending_init, pending, n_states);
         HIP_TRY(hipGetLastError());
     }
@@ -1883,7 +1986,7 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
         r.spin_limit = h->spin_limit;
         r.publish = h->wait_unreachable ? 0 : 1;
         r.step_out = h->d_step_out;
-        r.wqt = wqt; r.tape_g = tape_g; r.tape_c = tape_c; r.c_state = cst; r.g_a = g_a; r.gh = gh; r.gc = gc;
+        r.wqt = wqt; r.wqt_unscale = unscale; r.tape_g = tape_g; r.tape_c = tape_c; r.c_state = cst; r.g_a = g_a; r.gh = gh; r.gc = gc;
         r.hidden = (int32_t)hidden;
         if (r.n_path_tiles <= 0) continue;
         const int64_t cap = fused ? resident : 512;

@@ -124,3 +124,24 @@ def test_units_of_very_different_weights(B, d, hidden):
         assert np.abs(got.cpu().numpy() - want).max() <= bar
         a, _ = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
         assert torch.equal(a, got)
+
+
+@pytest.mark.parametrize("d,hidden", [(8, 8), (16, 40), (20, 64), (12, 72), (8, 128)])
+def test_gradients_of_very_different_sizes(B, d, hidden):
+    # The product of the reverse pass brings a path's gradients and a unit's weights to a common size each: units of a gradient of 2^-40, 1 and 2^20, columns of
+    # weights of 2^3, 1, 2^-12, 2^-60 and 0, nodes without a gradient, side by side.
+    n = 150
+    rowptr, col = lists(n, hidden)
+    rng = np.random.default_rng(d)
+    x, w_ih, w_hh, b, g = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden), rng.normal(0, 1, (n, hidden))
+    w_hh *= np.array([8.0, 1.0, 2.0 ** -12, 2.0 ** -60, 0.0])[np.arange(hidden) % 5]
+    g *= np.array([2.0 ** -40, 1.0, 0.0, 2.0 ** 20])[np.arange(n) % 4][:, None]
+    f32 = [a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b, g)]
+    want = lstm.naive_aggregate_backward(rowptr, col, *f32)
+    for cap in (0, int(col.size)):
+        h = B.SeqHag(rowptr, col, cap).upload()
+        _, ws = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
+        for got, ref in zip(h.lstm_backward(dev(x), dev(w_ih), dev(w_hh), dev(g), ws), want):
+            # norm-wise, the bar of the other gradient tests
+            assert np.linalg.norm(got.cpu().numpy() - ref) <= 2e-5 * np.linalg.norm(ref)
+        h.check()

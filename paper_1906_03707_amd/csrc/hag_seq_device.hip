@@ -336,7 +336,7 @@ __device__ __forceinline__ void seq_from_pieces(V &v) {
 //   halves: the pieces of a whole tile would be 64 of the 128 registers there are at four wavefronts per SIMD.
 template <int HMAX, bool TAPE>
 __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(SeqChainArgs A) {
-    constexpr bool BIG = HMAX == 128, WIDE = HMAX >= 64, C_LDS = HMAX == 64 || TAPE;
+    constexpr bool BIG = HMAX == 128, WIDE = HMAX >= 64, C_LDS = HMAX == 64 || TAPE, GATES = TAPE && HMAX != 64;   // (of 64 units the backward pass computes the gates again)
     constexpr int KS = HMAX / 16, ZS = HMAX + 8, JG = WIDE ? 2 : 1;
     __shared__ __align__(16) uint16_t z[2][2][kSeqJobs][ZS];   // h of every path in fp16 pieces: this step's and the next step's
     __shared__ __align__(16) float hs[TAPE ? kSeqJobs : 1][HMAX + 4];   // the step's h as it is, for the tape
@@ -510,7 +510,7 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                             const float gg = seq_tanh(acc[g][4 * m + 2], by[m]), go = seq_sigmoid(acc[g][4 * m + 3], by[m]);
                             c[m] = fmaf(gf, c[m], gi * gg);             // (spelled out: one rounding, the same in every copy of this code)
                             h[m] = go * seq_tanh(c[m]);
-                            if constexpr (TAPE) { acc[g][4 * m] = gi; acc[g][4 * m + 1] = gf; acc[g][4 * m + 2] = gg; acc[g][4 * m + 3] = go; }
+                            if constexpr (GATES) { acc[g][4 * m] = gi; acc[g][4 * m + 1] = gf; acc[g][4 * m + 2] = gg; acc[g][4 * m + 3] = go; }
                         }
                         put_h(cur ^ 1, j, unit0, h);
                         const float4 h4 = make_float4(h[0], h[1], h[2], h[3]), c4 = make_float4(c[0], c[1], c[2], c[3]);
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                             keep[g] = A.step_out[beg + t + 1];
                         }
                     }
-                    if constexpr (TAPE) {
+                    if constexpr (GATES) {
                         // the activated gates, for the backward pass, indexed by the step
                         float4 v[4];
                         seq_to_pieces(acc[g], v);
@@ -610,9 +610,14 @@ struct SeqRevArgs {
     const int32_t *step_out;
     const uint16_t *wqt;     // W_hh^T in fp16 pieces, in the order the matrix instructions consume it, see seq_backward_start_kernel
     const float *wqt_unscale;   // per hidden unit, likewise
-    float *tape_g;           // in: the activated gates of every step; out: the gradients of its pre-activations
-    const float *tape_c;     // c' of every step
-    const float *c_state;    // c rows of the kept states
+    float *tape_g;           // out: the gradients of every step's pre-activations; in, but for 40 to 64 units: its activated gates
+    const float *tape_c, *tape_h;   // c' and h of every step
+    const float *h_state, *c_state; // rows of the kept states
+    // for 40 to 64 units, what the forward pass computed the gates from (see SeqChainArgs)
+    const int32_t *step_g;
+    const float *gx;
+    const uint16_t *wq;
+    const float *unscale;
     const float *g_a;        // [n, H]
     float *gh, *gc;          // [n_states, H]
     // all levels in one launch (NULL: one launch per level): per kept state the number of paths that start from it
@@ -726,7 +731,7 @@ __device__ __forceinline__ void seq_wait_pending(const SeqRevArgs &A, int keep) 
 
 constexpr int kSeqRevJobs = 32;   // paths per workgroup of the reverse kernels above 32 hidden units: half a tile
 
-// Hidden sizes up to 64 (HMAX 32 or 64).  Lanes and wavefronts are those of the forward kernel: a lane holds (path, four units of
+// Hidden sizes up to 32.  Lanes and wavefronts are those of the forward kernel: a lane holds (path, four units of
 // gate tile w), their running dh and dc and, per step, the sixteen dG.  The k index of dh_prev = W_hh^T dG can be taken in any order, so the
 // dG are the product's operand where they are, in the registers of the lane that made them: wavefront w multiplies the 32 gate
 // rows of its own tile and leaves its part of dh_prev for all units in LDS; after a barrier every lane adds the parts
@@ -734,19 +739,15 @@ constexpr int kSeqRevJobs = 32;   // paths per workgroup of the reverse kernels 
 // largest of a path's 32 gate rows in the tile says what power of two brings them into fp16's range (seq_up), and whoever adds the parts multiplies by what undoes it.
 // The matrix cores cut what they add up, always downwards, and the gradients of hundreds of thousands of cells are added in the end: the factor's
 // sign alternates over paths, tiles and steps, so that half of the parts are cut upwards.  (Error of the training step's results against 64 bits at 3.35 M cells: 4.4e-6
-// with one sign, 4.9e-7 so, 5e-7 with fp32 instructions.)  The gates of the next step are requested before the product.  Above 32 units a
-// workgroup takes half a tile (70 KB of LDS, 128 registers), so that two share a compute unit and one's tape accesses run beside the other's products: the kernel is bound
-// by the tape (read gates and c, write dG: 36 H bytes per cell).  3.35 M cells of 64 units: 2.43 ms with 64 paths and one workgroup per compute unit, 2.23 with halves,
-// of which the fp32 matrix instructions were 37 %; 1.93 with fp16 pieces.
-template <int HMAX>
-__global__ __launch_bounds__(512, 4) void seq_reverse_kernel(SeqRevArgs A) {
-    constexpr int MT = HMAX / 32, JG = 1, NT = HMAX / 8, RS = HMAX + 4, RJ = HMAX == 64 ? kSeqRevJobs : kSeqJobs;
+// with one sign, 4.9e-7 so, 5e-7 with fp32 instructions.)  The gates of the next step are requested before the product.
+__global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A) {
+    constexpr int HMAX = 32, MT = 1, JG = 1, NT = 4, RS = HMAX + 4, RJ = kSeqJobs;
     __shared__ __align__(16) float red[NT][RJ][RS];
     __shared__ __align__(16) float sun[HMAX];              // the units' factors
     __shared__ int32_t sdesc[RJ * 4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int hidden = A.hidden, n_tiles = hidden / 8, m_tiles = (hidden + 31) / 32;
-    const int tile = HMAX == 64 ? wave : (wave & 3), group0 = HMAX == 64 ? 0 : (wave >> 2);
+    const int tile = wave & 3, group0 = wave >> 2;
     const bool on = tile < n_tiles;
     seq_h8_t wt[MT][2][2];                                 // [output tile][step][piece]
     const seq_h8_t *wl = reinterpret_cast<const seq_h8_t *>(A.wqt) + lane;
@@ -948,6 +949,297 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_kernel(SeqRevArgs A) {
     }
 }
 
+// Hidden sizes from 40 to 64: the products and their operands of the kernel above, 32 paths per workgroup, and the gates computed again instead of
+// read from the tape.  Bound by the tape, the kernel above took 1.93 ms for 3.35 M cells of 64 units and the forward pass 1.55, of which it stored 3.4 GB of gates for
+// most of the time; now 2.13 and 0.96 ms.  (Up to 32 units the products and the lockstep below take longer than the gates' bytes: 4 % slower on steps of 90 to 290 us.)
+// Sixteen wavefronts in two roles, because one wavefront's registers do not hold both W_hh and W_hh^T, and weights streamed from the cache between the tape's
+// loads would wait for those (loads return in order: 2.50 ms):
+//   wavefronts 8..15 run ahead: they load h and c of the tape and the rows of gx, multiply W_hh with h as the forward pass does and leave the gates of the
+//     next step in LDS, and c of this one; they are the only ones that wait for loads;
+//   wavefronts 0..7 go back through the steps, wavefront w for gate tile w, out of LDS, and write dG.
+// A step has two barriers, and the loads of a step are requested two steps ahead.  Vector instructions issue 55 % of the time, matrix cores are busy 15 %, 3 TB/s.
+__global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
+    constexpr int HMAX = 64, MT = 2, NT = 8, RS = HMAX + 4, RJ = kSeqRevJobs, KS = 4, ZS = HMAX + 8;
+    constexpr int PT = 512 / RJ;                           // threads that stage the h and c of one path, four columns each
+    __shared__ __align__(16) float red[NT][RJ][RS];
+    __shared__ __align__(16) uint16_t z[2][2][RJ][ZS];     // the h that a step began with, in fp16 pieces: of the next step and of the one after it
+    __shared__ __align__(16) float cs[2][RJ][RS];          // the c that a step began with: of this step and of the next one
+    __shared__ float4 gates[8][4][64];                     // of the next step, as the lanes hold them
+    __shared__ int32_t skeep[2][RJ];                       // the state row that a step wrote, or -1
+    __shared__ __align__(16) float sun[HMAX], sby[HMAX];   // the units' factors: of the product here, of the forward pass's pre-activations
+    __shared__ int32_t sdesc[4][RJ];                       // of a path: start state, first step, steps, node
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), worker = wave & 7;
+    const bool ahead = wave >= 8;
+    const int hidden = A.hidden, n_tiles = hidden / 8, tile = worker;
+    const bool on = tile < n_tiles;                        // (wavefronts beyond the hidden size only keep the barriers, and stage h)
+    seq_h8_t wr[KS * 2];                                   // W_hh [step][piece], or W_hh^T [output tile][step][piece]
+#pragma unroll
+    for (int k = 0; k < KS * 2; ++k) {
+        const seq_h8_t *from = ahead ? reinterpret_cast<const seq_h8_t *>(A.wq) + ((size_t)tile * KS * 2 + k) * 64
+                                     : reinterpret_cast<const seq_h8_t *>(A.wqt) + ((size_t)tile * MT * 4 + k) * 64;
+        wr[k] = on ? from[threadIdx.x & 63] : seq_h8_t{};
+    }
+    if ((int)threadIdx.x < hidden) { sun[threadIdx.x] = A.wqt_unscale[threadIdx.x]; sby[threadIdx.x] = A.unscale[threadIdx.x]; }   // (read behind the barriers of a tile)
+    for (int i = threadIdx.x; i < (int)(sizeof(z) / 4); i += 1024) reinterpret_cast<uint32_t *>(&z[0][0][0][0])[i] = 0;   // columns from `hidden` on stay zero
+    const int64_t n_parts = A.n_path_tiles * (kSeqJobs / RJ);
+    for (int64_t ci = blockIdx.x; ci < n_parts; ci += gridDim.x) {
+        const int64_t ct = A.reversed ? n_parts - 1 - ci : ci;
+        {
+            const int tid = seq_opaque(threadIdx.x);
+            if (tid < RJ * 4) sdesc[tid & 3][tid >> 2] = A.paths[ct * (RJ * 4) + tid];
+        }
+        __syncthreads();
+        const int steps = __builtin_amdgcn_readfirstlane(sdesc[2][0]);   // (none where a half of a tile holds nothing but padding)
+        float dh[4] = {0.f, 0.f, 0.f, 0.f}, dc[4] = {0.f, 0.f, 0.f, 0.f};
+        auto sum_parts = [&](int j) {
+            const int unit0 = tile * 8 + ((seq_opaque(threadIdx.x) >> 5) & 1) * 4;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int w = 0; w < NT; ++w) {
+                const int from = w < n_tiles ? w : 0;      // (no branch, so that the reads go out together; what is not finite in tile 0 makes the sum so anyway)
+                const float4 q = *reinterpret_cast<const float4 *>(&red[from][j][unit0]);
+                const float by = w < n_tiles ? red[from][j][HMAX] : 0.f;
+                v.x = fmaf(q.x, by, v.x); v.y = fmaf(q.y, by, v.y); v.z = fmaf(q.z, by, v.z); v.w = fmaf(q.w, by, v.w);
+            }
+            const float4 un4 = *reinterpret_cast<const float4 *>(&sun[unit0]);
+            dh[0] = v.x * un4.x; dh[1] = v.y * un4.y; dh[2] = v.z * un4.z; dh[3] = v.w * un4.w;
+        };
+        if (ahead) {
+            // Loads return in order and the compiler counts them, so none hangs on a condition: where a path has no such step its first cell is read.
+            float gx[16];                                  // in pieces (see seq_to_pieces)
+            seq_acc_t pre;
+            float4 h_next, c_next, c_held = make_float4(0.f, 0.f, 0.f, 0.f);
+            int row, keep_next, keep_held = -1;            // row: of gx
+            bool zero_next;
+            auto load_row = [&](int t) {
+                const int j = (seq_opaque(threadIdx.x) & 31);
+                row = A.step_g[sdesc[1][j] + (t >= 0 && t < sdesc[2][j] ? t : 0)];
+            };
+            auto load_gx = [&] {                           // of the step whose row is at hand
+                const seq_u2_t rows = __builtin_amdgcn_permlane16_swap((unsigned)row, (unsigned)row, false, false);   // of paths l % 16 and 16 + l % 16
+                const int l = seq_opaque(threadIdx.x) & 63;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const float *p = A.gx + ((size_t)(q ? rows.y : rows.x) * hidden + tile * 8 + seq_piece(l)) * 4;
+                    const float4 v = *reinterpret_cast<const float4 *>(p), w = *reinterpret_cast<const float4 *>(p + 16);
+                    gx[8 * q] = v.x; gx[8 * q + 1] = v.y; gx[8 * q + 2] = v.z; gx[8 * q + 3] = v.w;
+                    gx[8 * q + 4] = w.x; gx[8 * q + 5] = w.y; gx[8 * q + 6] = w.z; gx[8 * q + 7] = w.w;
+                }
+            };
+            auto load_begun = [&](int t) {                 // four columns of the h and c that step t of a path began with, and the state row that it wrote
+                const int tid = seq_opaque(threadIdx.x) - 512, j = tid / PT, u = tid % PT * 4, start = sdesc[0][j], beg = sdesc[1][j], len = sdesc[2][j];
+                const bool inner = t > 0 && t < len, first = t == 0 && len > 0 && start >= 0;
+                const size_t at = (size_t)(inner ? beg + t - 1 : first ? start : beg) * hidden + (u < hidden ? u : 0);
+                h_next = *reinterpret_cast<const float4 *>((first ? A.h_state : A.tape_h) + at);
+                c_next = *reinterpret_cast<const float4 *>((first ? A.c_state : A.tape_c) + at);
+                keep_next = A.step_out[beg + (t >= 0 && t < len ? t : 0)];
+                zero_next = u >= hidden || !(inner || first);
+            };
+            auto stage = [&](int t) {                      // h of step t, c of the step before (which is processed one step later than its gates are computed)
+                const int tid = seq_opaque(threadIdx.x) - 512, j = tid / PT, u = tid % PT * 4;
+                const float4 h = zero_next ? make_float4(0.f, 0.f, 0.f, 0.f) : h_next;
+                uint32_t a[2], b[2];
+                seq_halves2(h.x * kSeqHScale, h.y * kSeqHScale, a);
+                seq_halves2(h.z * kSeqHScale, h.w * kSeqHScale, b);
+#pragma unroll
+                for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2 *>(&z[t & 1][p][j][u]) = make_uint2(a[p], b[p]);   // (columns beyond `hidden`: zero)
+                *reinterpret_cast<float4 *>(&cs[(t + 1) & 1][j][u]) = c_held;
+                if (u == 0) skeep[(t + 1) & 1][j] = keep_held;
+                c_held = zero_next ? make_float4(0.f, 0.f, 0.f, 0.f) : c_next;
+                keep_held = keep_next;
+            };
+            auto product = [&](int t) {                    // the forward pass's recurrent product
+                const int l = seq_opaque(threadIdx.x) & 63;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) pre[r] = 0.f;
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    seq_h8_t zb[2];
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) zb[p] = *reinterpret_cast<const seq_h8_t *>(&z[t & 1][p][(l & 31)][16 * s + 8 * (l >> 5)]);
+                    pre = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * s + 1], zb[0], pre, 0, 0, 0);
+                    pre = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * s], zb[1], pre, 0, 0, 0);
+                    pre = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * s], zb[0], pre, 0, 0, 0);
+                }
+            };
+            auto put_gates = [&] {
+                const int l = seq_opaque(threadIdx.x) & 63;
+                const float4 by4 = *reinterpret_cast<const float4 *>(&sby[tile * 8 + (l >> 5) * 4]);
+                const float by[4] = {by4.x, by4.y, by4.z, by4.w};
+                seq_from_pieces(gx);
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    gates[worker][m][l] = make_float4(seq_sigmoid(pre[4 * m] + gx[4 * m], by[m]), seq_sigmoid(pre[4 * m + 1] + gx[4 * m + 1], by[m]),
+                                                      seq_tanh(pre[4 * m + 2] + gx[4 * m + 2], by[m]), seq_sigmoid(pre[4 * m + 3] + gx[4 * m + 3], by[m]));   // i, f, g, o
+            };
+            load_row(steps - 1);
+            load_begun(steps - 1);
+            load_gx();
+            load_row(steps - 2);
+            stage(steps - 1);
+            load_begun(steps - 2);
+            __syncthreads();
+            if (on) {
+                product(steps - 1);                        // (in the order of the loop, so that the counts of loads agree)
+                stage(steps - 2);
+                load_begun(steps - 3);
+                put_gates();
+                load_gx();
+                load_row(steps - 3);
+                __syncthreads();                           // the gates of the last step are complete, and the h rows of the one before
+                for (int t = steps - 1; t >= 0; --t) {
+                    product(t - 1);
+                    stage(t - 2);
+                    load_begun(t - 3);
+                    __syncthreads();                       // the gates of step t have been read
+                    put_gates();
+                    load_gx();
+                    load_row(t - 3);
+                    __syncthreads();
+                }
+            } else {
+                stage(steps - 2);
+                load_begun(steps - 3);
+                __syncthreads();
+                for (int t = steps - 1; t >= 0; --t) {
+                    stage(t - 2);
+                    load_begun(t - 3);
+                    __syncthreads();
+                    __syncthreads();
+                }
+            }
+        } else {
+            float4 c_now = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (on) {
+                const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4;
+                const int j = (lane & 31), len = sdesc[2][j], node = sdesc[3][j];
+                if (node >= 0) {
+                    const float4 v = *reinterpret_cast<const float4 *>(A.g_a + (size_t)node * hidden + unit0);
+                    dh[0] = v.x; dh[1] = v.y; dh[2] = v.z; dh[3] = v.w;
+                }
+                if (len > 0) c_now = *reinterpret_cast<const float4 *>(A.tape_c + ((size_t)sdesc[1][j] + len - 1) * hidden + unit0);
+            }
+            __syncthreads();
+            __syncthreads();                               // the gates of the last step are complete
+            for (int t = steps - 1; t >= 0; --t) {
+                float dg[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) dg[e] = 0.f;
+                if (on) {
+                    const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4;
+                    const int j = (lane & 31), len = sdesc[2][j];
+                    if (t < len) {
+                        if (t + 1 < len) sum_parts(j);     // dh_prev of the step before is this step's dh
+                        const int keep = skeep[t & 1][j];
+                        if (keep >= 0) {                   // what the other users of this state sent back
+                            if (A.pending) seq_wait_pending(A, keep);
+                            const size_t o = (size_t)keep * hidden + unit0;
+                            const float4 a = A.pending ? seq_ld4_device(A.gh + o) : *reinterpret_cast<const float4 *>(A.gh + o);
+                            const float4 b = A.pending ? seq_ld4_device(A.gc + o) : *reinterpret_cast<const float4 *>(A.gc + o);
+                            dh[0] += a.x; dh[1] += a.y; dh[2] += a.z; dh[3] += a.w;
+                            dc[0] += b.x; dc[1] += b.y; dc[2] += b.z; dc[3] += b.w;
+                        }
+                        const float4 c_prev = *reinterpret_cast<const float4 *>(&cs[t & 1][j][unit0]);
+                        const float cn[4] = {c_now.x, c_now.y, c_now.z, c_now.w}, cp[4] = {c_prev.x, c_prev.y, c_prev.z, c_prev.w};
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) {
+                            const float4 g4 = gates[worker][m][lane];   // i, f, g, o
+                            const float tc = seq_tanh(cn[m]);
+                            const float d_o = dh[m] * tc;
+                            const float dcc = dc[m] + dh[m] * g4.w * (1.f - tc * tc);
+                            dg[4 * m] = dcc * g4.z * g4.x * (1.f - g4.x);
+                            dg[4 * m + 1] = dcc * cp[m] * g4.y * (1.f - g4.y);
+                            dg[4 * m + 2] = dcc * g4.x * (1.f - g4.z * g4.z);
+                            dg[4 * m + 3] = d_o * g4.w * (1.f - g4.w);
+                            dc[m] = dcc * g4.y;
+                        }
+                        c_now = c_prev;
+                    }
+                    float4 v[4];
+                    seq_to_pieces(dg, v);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const int jj = 16 * q + (lane & 15);
+                        if (t < sdesc[2][jj]) {
+                            float *p = A.tape_g + ((size_t)(sdesc[1][jj] + t) * hidden + tile * 8 + seq_piece(lane)) * 4;
+                            *reinterpret_cast<float4 *>(p) = v[2 * q];
+                            *reinterpret_cast<float4 *>(p + 16) = v[2 * q + 1];
+                        }
+                    }
+                }
+                __syncthreads();                           // every lane has read the parts of the step before
+                if (on) {
+                    const int l = seq_opaque(threadIdx.x) & 63, half = l >> 5, j = (l & 31);
+                    float most = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) most = fmaxf(most, fabsf(dg[e]));
+                    const seq_u2_t both = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
+                    const int up = seq_up(fmaxf(__uint_as_float(both.x), __uint_as_float(both.y)));   // of the path's 32 gate rows
+                    const float one = (tile + j + t) & 1 ? -1.f : 1.f, by = __builtin_ldexpf(one, up);
+                    if (half == 0) red[tile][j][HMAX] = __builtin_ldexpf(one, -15 - up);
+                    seq_h8_t zb[2][2];                     // [step][piece]
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        uint32_t p[4][2];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) seq_halves2(dg[8 * k + 2 * i] * by, dg[8 * k + 2 * i + 1] * by, p[i]);
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) zb[k][i] = __builtin_bit_cast(seq_h8_t, make_uint4(p[0][i], p[1][i], p[2][i], p[3][i]));
+                    }
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        seq_acc_t acc;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[(mt * 2 + k) * 2 + 1], zb[k][0], acc, 0, 0, 0);
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[(mt * 2 + k) * 2], zb[k][1], acc, 0, 0, 0);
+                        }
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[(mt * 2 + k) * 2], zb[k][0], acc, 0, 0, 0);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            *reinterpret_cast<float4 *>(&red[tile][j][mt * 32 + 8 * q + 4 * half]) = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+                    }
+                }
+                __syncthreads();                           // the parts of dh_prev and the gates of the next step are complete
+            }
+        }
+        // What is left: the gradient of the state the path started from, as rows in LDS first, so that one atomic instruction
+        // covers a row of 256 contiguous bytes (issued by the lanes that hold the values, four bytes of each of 64 rows per
+        // instruction, they took most of the kernel's time: the memory side does about 17 such requests per ns).
+        bool any = false;
+        if (threadIdx.x < RJ) any = sdesc[0][threadIdx.x] >= 0;
+        if (__syncthreads_or(any)) {
+            const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4, own = (lane & 31);
+            const bool holds = on && !ahead;
+            if (holds) sum_parts(own);
+            __syncthreads();
+            if (holds) {
+                *reinterpret_cast<float4 *>(&red[0][own][unit0]) = make_float4(dh[0], dh[1], dh[2], dh[3]);
+                *reinterpret_cast<float4 *>(&red[1][own][unit0]) = make_float4(dc[0], dc[1], dc[2], dc[3]);
+            }
+            __syncthreads();
+            for (int j = wave; j < RJ; j += 16) {
+                const int start = sdesc[0][j];
+                if (start < 0) continue;                   // (the same for the whole wavefront; an empty path starts nowhere)
+                if (lane < hidden) {
+                    __hip_atomic_fetch_add(A.gh + (size_t)start * hidden + lane, red[0][j][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(A.gc + (size_t)start * hidden + lane, red[1][j][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+            if (A.pending) {
+                // once the wavefront has seen its atomics complete, its paths are counted off
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                const int start = lane < RJ / 16 ? sdesc[0][wave + 16 * lane] : -1;
+                if (start >= 0 && A.publish) __hip_atomic_fetch_sub(A.pending + start, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Hidden sizes from 72 to 128.  A workgroup takes half a tile, 32 paths: dG is staged as rows of 4 * 128 + 2 in LDS (66 KB), so that two workgroups share
 // a compute unit and one's loads, stores and element-wise part run beside the other's products.  (With 64 paths and 131 KB a workgroup had the compute unit to
 // itself and its phases followed one another: 2.63 ms for 0.85 M cells of 128 hidden units, of which the products are 0.72 and the tape's bytes 0.75; as halves
@@ -1062,7 +1354,6 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                     for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2 *>(&z[p][sj][u * 4]) = make_uint2(a[p], b[p]);
                 }
             }
-            if (t > 0 && t - 1 < len) load_step(t - 1);
             __syncthreads();
             // dh_prev^T [units, paths] = W_hh^T . dG^T [4H, paths], the gate rows in two halves
             const int lane = seq_opaque(threadIdx.x) & 63;
@@ -1071,26 +1362,33 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
             for (int r = 0; r < 16; ++r) acc[r] = 0.f;
             const bool has_pair = wave < 2 * n_rt;
             const int rt = wave % n_rt, half = wave / n_rt;
+            seq_h8_t wa[2];
+            auto step = [&](int s) {
+                seq_h8_t zb[2];
+#pragma unroll
+                for (int p = 0; p < 2; ++p) zb[p] = *reinterpret_cast<const seq_h8_t *>(&z[p][lane & 31][16 * s + 8 * (lane >> 5)]);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[1], zb[0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[0], zb[1], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[0], zb[0], acc, 0, 0, 0);
+            };
+            const int s0 = half * (hidden / 8), s1 = s0 + hidden / 8;   // steps of sixteen gate rows (hidden is a multiple of 8)
             if (has_pair) {
-                const int s0 = half * (hidden / 8), s1 = s0 + hidden / 8;   // steps of sixteen gate rows (hidden is a multiple of 8)
                 const seq_h8_t *wq = reinterpret_cast<const seq_h8_t *>(A.wqt) + (size_t)rt * (hidden / 4) * 2 * 64 + lane;
-                seq_h8_t wa[2], wn[2], zb[2];
+                seq_h8_t wn[2];
 #pragma unroll
                 for (int p = 0; p < 2; ++p) wa[p] = wq[(s0 * 2 + p) * 64];
 #pragma unroll 1
-                for (int s = s0; s < s1; ++s) {
-                    const int sn = s + 1 < s1 ? s + 1 : s;
+                for (int s = s0; s + 1 < s1; ++s) {
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) wn[p] = wq[(sn * 2 + p) * 64];
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) zb[p] = *reinterpret_cast<const seq_h8_t *>(&z[p][lane & 31][16 * s + 8 * (lane >> 5)]);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[1], zb[0], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[0], zb[1], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[0], zb[0], acc, 0, 0, 0);
+                    for (int p = 0; p < 2; ++p) wn[p] = wq[((s + 1) * 2 + p) * 64];
+                    step(s);
 #pragma unroll
                     for (int p = 0; p < 2; ++p) wa[p] = wn[p];
                 }
             }
+            // (loads return in order: requested before the weights, the tape would be waited for with them)
+            if (t > 0 && t - 1 < sdesc[(seq_opaque(threadIdx.x) / TP) * 4 + 2]) load_step(t - 1);
+            if (has_pair) step(s1 - 1);
             __syncthreads();                               // every product has read the staged gradients
             if (has_pair) {
                 const int j = lane & 31;
@@ -1707,7 +2005,8 @@ static const seq_kernel_t kSeqVariants[3] = {seq_chain_kernel<32, false>, seq_ch
 static const seq_kernel_t kSeqTapeVariants[3] = {seq_chain_kernel<32, true>, seq_chain_kernel<64, true>, seq_chain_kernel<128, true>};
 static unsigned seq_block(int variant) { return variant == 2 ? 1024 : 512; }
 typedef void (*seq_reverse_t)(SeqRevArgs);
-static const seq_reverse_t kSeqReverseVariants[3] = {seq_reverse_kernel<32>, seq_reverse_kernel<64>, seq_reverse_wide_kernel};
+static const seq_reverse_t kSeqReverseVariants[3] = {seq_reverse_narrow_kernel, seq_reverse_kernel, seq_reverse_wide_kernel};
+static unsigned seq_reverse_block(int variant) { return variant == 1 ? 1024 : 512; }
 
 int hag_seq_get_plan(const hag_seq_t *h, int32_t order, int64_t *n_states, int64_t *n_paths, const int32_t **paths,
                      const int32_t **step_x, const int32_t **step_out, int64_t *n_levels, const int64_t **level_ptr,
@@ -1767,7 +2066,7 @@ int hag_seq_upload(hag_seq_t *h) {
             h->resident[k] = (int64_t)std::min(per_cu, 2) * cus;
             HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqTapeVariants[k], (int)seq_block(k), 0));
             h->resident_tape[k] = (int64_t)std::min(per_cu, 2) * cus;
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqReverseVariants[k], 512, 0));
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kSeqReverseVariants[k], (int)seq_reverse_block(k), 0));
             h->resident_reverse[k] = (int64_t)std::min(per_cu, 2) * cus;
         }
     }
@@ -1986,11 +2285,12 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
         r.spin_limit = h->spin_limit;
         r.publish = h->wait_unreachable ? 0 : 1;
         r.step_out = h->d_step_out;
-        r.wqt = wqt; r.wqt_unscale = unscale; r.tape_g = tape_g; r.tape_c = tape_c; r.c_state = cst; r.g_a = g_a; r.gh = gh; r.gc = gc;
+        r.step_g = h->d_step_g; r.gx = (const float *)(w + F.gx); r.wq = (const uint16_t *)(w + F.wq); r.unscale = (const float *)(w + F.bp) + 4 * hidden;
+        r.wqt = wqt; r.wqt_unscale = unscale; r.tape_g = tape_g; r.tape_c = tape_c; r.tape_h = tape_h; r.h_state = hst; r.c_state = cst; r.g_a = g_a; r.gh = gh; r.gc = gc;
         r.hidden = (int32_t)hidden;
         if (r.n_path_tiles <= 0) continue;
         const int64_t cap = fused ? resident : 512;
-        hipLaunchKernelGGL(kSeqReverseVariants[rv], dim3((unsigned)std::min<int64_t>(r.n_path_tiles * (rv > 0 ? kSeqJobs / kSeqRevJobs : 1), cap)), dim3(512), 0, s, r);
+        hipLaunchKernelGGL(kSeqReverseVariants[rv], dim3((unsigned)std::min<int64_t>(r.n_path_tiles * (rv > 0 ? kSeqJobs / kSeqRevJobs : 1), cap)), dim3(seq_reverse_block(rv)), 0, s, r);
         HIP_TRY(hipGetLastError());
     }
     {

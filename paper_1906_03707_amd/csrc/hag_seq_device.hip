@@ -1209,9 +1209,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
         // What is left: the gradient of the state the path started from, as rows in LDS first, so that one atomic instruction
         // covers a row of 256 contiguous bytes (issued by the lanes that hold the values, four bytes of each of 64 rows per
         // instruction, they took most of the kernel's time: the memory side does about 17 such requests per ns).
-        bool any = false;
-        if (threadIdx.x < RJ) any = sdesc[0][threadIdx.x] >= 0;
-        if (__syncthreads_or(any)) {
+        if (__any(sdesc[0][seq_opaque(threadIdx.x) & 31] >= 0)) {   // (the same for every wavefront)
             const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4, own = (lane & 31);
             const bool holds = on && !ahead;
             if (holds) sum_parts(own);
@@ -1247,6 +1245,8 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
 // Sixteen threads per path run the element-wise part; every wavefront multiplies one 32-unit tile of W_hh^T, streamed from the L2 cache, with one half
 // of the gate rows, and the two parts are added by whoever reads dh_prev.  Operands in two fp16 pieces as in the kernel above, a path's gradients with one factor
 // for all gate rows (fp32 matrix instructions were busy 50 % of the time: 1.77 ms, 1.27 so; error against 64 bits 6.6e-7 and 5.1e-7).
+// What then took the time was waiting: a load under a condition of its own was waited for before the next (eight times the latency of memory per step), and
+// the weights came one step ahead of the products.  With loads that hang on nothing and weights four steps ahead: 0.94 ms.
 __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) {
     constexpr int ZS = 4 * 128 + 8, IT = 8, TP = 16;       // units per thread, threads per path; rows 4 banks apart
     // per path: the pre-activation gradients of the current step in fp16 pieces (the product's operand), then, in the row of the first pieces, the two parts
@@ -1262,9 +1262,12 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
     if ((int)threadIdx.x < hidden) sun[threadIdx.x] = A.wqt_unscale[threadIdx.x];   // (read behind the barriers of a tile)
     for (int64_t ci = blockIdx.x; ci < n_halves; ci += gridDim.x) {
         const int64_t ct = A.reversed ? n_halves - 1 - ci : ci;
-        if (threadIdx.x < kSeqRevJobs * 4) sdesc[threadIdx.x] = A.paths[ct * (kSeqRevJobs * 4) + threadIdx.x];
+        {
+            const int tid = seq_opaque(threadIdx.x);
+            if (tid < kSeqRevJobs * 4) sdesc[tid] = A.paths[ct * (kSeqRevJobs * 4) + tid];
+        }
         __syncthreads();
-        const int steps = sdesc[2];                        // the first path is the longest
+        const int steps = __builtin_amdgcn_readfirstlane(sdesc[2]);   // the first path is the longest
         // unit 16 * it + part: the sixteen threads of a path move 256 contiguous bytes of its gates per instruction
         float dcv[IT];
         float back = 1.f;                                  // with the unit's factor, what the product's result is multiplied by
@@ -1272,17 +1275,19 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
         float4 gates[IT];
         float c_now[IT], c_prev[IT];                       // c_prev is the next step's c_now
         int keep = -1;
+        // (no load hangs on a condition, or the compiler waits for each before the next: a path without a step t reads its first cell, a thread without a unit one
+        // that it has; c before a first step from the zero state is cleared where it is used)
         auto load_step = [&](int t) {
-            const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, start = sdesc[sj * 4];
-            const size_t cell = (size_t)sdesc[sj * 4 + 1] + t;
+            const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, start = sdesc[sj * 4], beg = sdesc[sj * 4 + 1], len = sdesc[sj * 4 + 2];
+            const size_t cell = (size_t)beg + (t >= 0 && t < len ? t : 0);
+            const bool inner = t > 0 && t < len, from_state = t == 0 && len > 0 && start >= 0;
             keep = A.step_out[cell];
-            const float *before = t > 0 ? A.tape_c + (cell - 1) * hidden : start >= 0 ? A.c_state + (size_t)start * hidden : nullptr;
+            const float *g = A.tape_g + cell * hidden * 4, *before = (from_state ? A.c_state : A.tape_c) + (size_t)(from_state ? start : inner ? cell - 1 : cell) * hidden;
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
-                const int u = TP * it + part;
-                if (u >= hidden) continue;
-                gates[it] = *reinterpret_cast<const float4 *>(A.tape_g + (cell * hidden + u) * 4);
-                c_prev[it] = before ? before[u] : 0.f;
+                const int u = TP * it + part < hidden ? TP * it + part : part;
+                gates[it] = *reinterpret_cast<const float4 *>(g + u * 4);
+                c_prev[it] = before[u];
             }
         };
         {
@@ -1293,14 +1298,13 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                 // (dh lives in the path's row, as the sum of two parts, so that it takes no registers during the products)
                 row_of(sj)[u] = node >= 0 && u < hidden ? A.g_a[(size_t)node * hidden + u] : 0.f;
                 row_of(sj)[128 + u] = 0.f;
-                dcv[it] = c_prev[it] = 0.f;
-                gates[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+                dcv[it] = 0.f;
                 c_now[it] = len > 0 && u < hidden ? A.tape_c[((size_t)beg + len - 1) * hidden + u] : 0.f;
             }
-            if (len > 0 && len == steps) load_step(steps - 1);
+            load_step(steps - 1);
         }
         for (int t = steps - 1; t >= 0; --t) {
-            const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, len = sdesc[sj * 4 + 2];
+            const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, from = sdesc[sj * 4], len = sdesc[sj * 4 + 2];
             if (t < len) {
                 const size_t cell = (size_t)sdesc[sj * 4 + 1] + t;
                 if (A.pending && keep >= 0) seq_wait_pending(A, keep);
@@ -1316,17 +1320,22 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                 }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
-                float most = 0.f;
+                if (keep >= 0) {                           // what the other users of this state sent back
 #pragma unroll
-                for (int it = 0; it < IT; ++it) {
-                    const int u = TP * it + part;
-                    if (u >= hidden) continue;
-                    if (keep >= 0) {                       // what the other users of this state sent back
+                    for (int it = 0; it < IT; ++it) {
+                        const int u = TP * it + part;
+                        if (u >= hidden) continue;
                         const float *h = A.gh + (size_t)keep * hidden + u, *c = A.gc + (size_t)keep * hidden + u;
                         dhv[it] += A.pending ? __hip_atomic_load(h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *h;
                         dcv[it] += A.pending ? __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *c;
                     }
+                }
+                float most = 0.f;
+                float *out = A.tape_g + (cell * hidden + part) * 4;
+#pragma unroll
+                for (int it = 0; it < IT; ++it) {
                     const float4 g4 = gates[it];           // i, f, g, o
+                    if (t == 0 && from < 0) c_prev[it] = 0.f;
                     const float tc = seq_tanh(c_now[it]);
                     const float d_o = dhv[it] * tc;
                     const float dcc = dcv[it] + dhv[it] * g4.w * (1.f - tc * tc);
@@ -1334,8 +1343,9 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                                                   dcc * g4.x * (1.f - g4.z * g4.z), d_o * g4.w * (1.f - g4.w));
                     dcv[it] = dcc * g4.y;
                     c_now[it] = c_prev[it];
-                    *reinterpret_cast<float4 *>(A.tape_g + (cell * hidden + u) * 4) = dg;   // kept for the weight gradients
                     gates[it] = dg;
+                    if (TP * it + part >= hidden) continue;
+                    *reinterpret_cast<float4 *>(out + TP * it * 4) = dg;   // kept for the weight gradients
                     most = fmaxf(fmaxf(most, fmaxf(fabsf(dg.x), fabsf(dg.y))), fmaxf(fabsf(dg.z), fabsf(dg.w)));
                 }
                 __builtin_amdgcn_sched_barrier(0);         // (registers are short)
@@ -1362,33 +1372,41 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
             for (int r = 0; r < 16; ++r) acc[r] = 0.f;
             const bool has_pair = wave < 2 * n_rt;
             const int rt = wave % n_rt, half = wave / n_rt;
-            seq_h8_t wa[2];
-            auto step = [&](int s) {
+            // The weights are requested four steps of sixteen gate rows ahead: a step is 96 cycles of products, an access of the L2 cache several hundred.
+            constexpr int AHEAD = 4;
+            seq_h8_t w[AHEAD][2];
+            const int s0 = half * (hidden / 8), s1 = s0 + hidden / 8;   // (hidden is a multiple of 8, 72 at least)
+            const seq_h8_t *wq = reinterpret_cast<const seq_h8_t *>(A.wqt) + (size_t)rt * (hidden / 4) * 2 * 64 + lane;
+            auto load_w = [&](int i, int s) {
+                s = s < s1 ? s : s1 - 1;
+#pragma unroll
+                for (int p = 0; p < 2; ++p) w[i][p] = wq[(s * 2 + p) * 64];
+            };
+            auto step = [&](int i, int s) {
                 seq_h8_t zb[2];
 #pragma unroll
                 for (int p = 0; p < 2; ++p) zb[p] = *reinterpret_cast<const seq_h8_t *>(&z[p][lane & 31][16 * s + 8 * (lane >> 5)]);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[1], zb[0], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[0], zb[1], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[0], zb[0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][1], zb[0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][0], zb[1], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][0], zb[0], acc, 0, 0, 0);
             };
-            const int s0 = half * (hidden / 8), s1 = s0 + hidden / 8;   // steps of sixteen gate rows (hidden is a multiple of 8)
+            int s = s0;
             if (has_pair) {
-                const seq_h8_t *wq = reinterpret_cast<const seq_h8_t *>(A.wqt) + (size_t)rt * (hidden / 4) * 2 * 64 + lane;
-                seq_h8_t wn[2];
 #pragma unroll
-                for (int p = 0; p < 2; ++p) wa[p] = wq[(s0 * 2 + p) * 64];
+                for (int i = 0; i < AHEAD; ++i) load_w(i, s + i);
 #pragma unroll 1
-                for (int s = s0; s + 1 < s1; ++s) {
+                for (; s + AHEAD < s1; s += AHEAD) {
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) wn[p] = wq[((s + 1) * 2 + p) * 64];
-                    step(s);
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) wa[p] = wn[p];
+                    for (int i = 0; i < AHEAD; ++i) { step(i, s + i); load_w(i, s + AHEAD + i); __builtin_amdgcn_sched_barrier(0); }
                 }
             }
             // (loads return in order: requested before the weights, the tape would be waited for with them)
-            if (t > 0 && t - 1 < sdesc[(seq_opaque(threadIdx.x) / TP) * 4 + 2]) load_step(t - 1);
-            if (has_pair) step(s1 - 1);
+            load_step(t - 1);
+            if (has_pair) {
+#pragma unroll
+                for (int i = 0; i < AHEAD; ++i)
+                    if (s + i < s1) step(i, s + i);
+            }
             __syncthreads();                               // every product has read the staged gradients
             if (has_pair) {
                 const int j = lane & 31;
@@ -1405,7 +1423,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
         // what is left: the gradient of the state the path started from, dh (in two parts) beside dc in the path's row, added by whole wavefronts so
         // that an atomic instruction covers contiguous bytes
         const int tid = seq_opaque(threadIdx.x), sj = tid / TP, part = tid % TP, lane = tid & 63;
-        if (__syncthreads_or(sdesc[sj * 4] >= 0)) {
+        if (__any(sdesc[(lane & 31) * 4] >= 0)) {           // (the same for every wavefront)
 #pragma unroll
             for (int it = 0; it < IT; ++it) reinterpret_cast<float *>(&z[1][sj][0])[TP * it + part] = dcv[it];
             if (part == 0) row_of(sj)[256] = back;

@@ -230,6 +230,11 @@ __device__ __forceinline__ float seq_tanh(float z, float by) {
     const float e = __builtin_amdgcn_exp2f(fabsf(z) * by);   // in (0, 1]: no overflow, no cancellation in 1 + e
     return copysignf((1.f - e) * __builtin_amdgcn_rcpf(1.f + e), z);
 }
+// seq_sigmoid(z, by) * seq_tanh(x, by_x); the denominators' product is infinite only where the first factor is 0, and so is the result
+__device__ __forceinline__ float seq_sigmoid_tanh(float z, float by, float x, float by_x) {
+    const float e = __builtin_amdgcn_exp2f(fabsf(x) * by_x);
+    return copysignf((1.f - e) * __builtin_amdgcn_rcpf((1.f + __builtin_amdgcn_exp2f(z * by)) * (1.f + e)), x);
+}
 __device__ __forceinline__ float seq_tanh(float z) { return seq_tanh(z, -2.f * 1.44269504f); }
 
 struct SeqChainArgs {
@@ -326,7 +331,7 @@ __device__ __forceinline__ void seq_from_pieces(V &v) {
 //
 // The product runs in fp16 pieces (seq_halves2): three v_mfma_f32_32x32x16_f16 per 16 columns cost 96 cycles against 192 for bf16 pieces (six) and
 // 512 for fp32 instructions.  What is left is the element-wise part and the rows of gx.  Inference over 370 k nodes (hidden = d = 64, prefix HAG with 3.35 M
-// cells): 877 us with bf16 pieces, 737 so; with the tape 1.57 and 1.49 ms; 0.85 M cells of 128 units with the tape: 1.18 and 1.01 ms.  Error of the
+// cells): 877 us with bf16 pieces, 737 so, 724 with one reciprocal for two gate functions; with the tape 1.57 and 1.49 ms (0.96 without the gates); 0.85 M cells of 128 units with the tape: 1.18 and 1.01 ms.  Error of the
 // result against 64 bits 2.1e-7 and 1.9e-7 (128 units: 2.7e-7 and 2.5e-7).
 // A gate tile is 32 gate rows = 8 hidden units; lane l of the product holds, for path l % 32 of its half of the tile, the four
 // gates of units 8 * tile + 4 * (l / 32) + 0..3.
@@ -506,11 +511,17 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                         float h[4], c[4] = {cv.x, cv.y, cv.z, cv.w};
 #pragma unroll
                         for (int m = 0; m < 4; ++m) {
-                            const float gi = seq_sigmoid(acc[g][4 * m], by[m]), gf = seq_sigmoid(acc[g][4 * m + 1], by[m]);
-                            const float gg = seq_tanh(acc[g][4 * m + 2], by[m]), go = seq_sigmoid(acc[g][4 * m + 3], by[m]);
-                            c[m] = fmaf(gf, c[m], gi * gg);             // (spelled out: one rounding, the same in every copy of this code)
-                            h[m] = go * seq_tanh(c[m]);
-                            if constexpr (GATES) { acc[g][4 * m] = gi; acc[g][4 * m + 1] = gf; acc[g][4 * m + 2] = gg; acc[g][4 * m + 3] = go; }
+                            const float gf = seq_sigmoid(acc[g][4 * m + 1], by[m]);
+                            if constexpr (HMAX == 64) {
+                                // sigmoid times tanh with one reciprocal of both denominators: the reciprocal is a quarter of a gate function's time
+                                c[m] = fmaf(gf, c[m], seq_sigmoid_tanh(acc[g][4 * m], by[m], acc[g][4 * m + 2], by[m]));   // (spelled out: one rounding, the same in every copy of this code)
+                                h[m] = seq_sigmoid_tanh(acc[g][4 * m + 3], by[m], c[m], -2.f * 1.44269504f);
+                            } else {
+                                const float gi = seq_sigmoid(acc[g][4 * m], by[m]), gg = seq_tanh(acc[g][4 * m + 2], by[m]), go = seq_sigmoid(acc[g][4 * m + 3], by[m]);
+                                c[m] = fmaf(gf, c[m], gi * gg);
+                                h[m] = go * seq_tanh(c[m]);
+                                if constexpr (GATES) { acc[g][4 * m] = gi; acc[g][4 * m + 1] = gf; acc[g][4 * m + 2] = gg; acc[g][4 * m + 3] = go; }
+                            }
                         }
                         put_h(cur ^ 1, j, unit0, h);
                         const float4 h4 = make_float4(h[0], h[1], h[2], h[3]), c4 = make_float4(c[0], c[1], c[2], c[3]);

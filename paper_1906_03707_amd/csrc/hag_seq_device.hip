@@ -750,195 +750,166 @@ constexpr int kSeqRevJobs = 32;   // paths per workgroup of the reverse kernels 
 // largest of a path's 32 gate rows in the tile says what power of two brings them into fp16's range (seq_up), and whoever adds the parts multiplies by what undoes it.
 // The matrix cores cut what they add up, always downwards, and the gradients of hundreds of thousands of cells are added in the end: the factor's
 // sign alternates over paths, tiles and steps, so that half of the parts are cut upwards.  (Error of the training step's results against 64 bits at 3.35 M cells: 4.4e-6
-// with one sign, 4.9e-7 so, 5e-7 with fp32 instructions.)  The gates of the next step are requested before the product.
+// with one sign, 4.9e-7 so, 5e-7 with fp32 instructions.)  The tape of the next step is requested before the product, without conditions (1 to 4 % of training steps
+// of 90 to 470 us).
 __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A) {
-    constexpr int HMAX = 32, MT = 1, JG = 1, NT = 4, RS = HMAX + 4, RJ = kSeqJobs;
+    constexpr int HMAX = 32, NT = 4, RS = HMAX + 4, RJ = kSeqJobs;
     __shared__ __align__(16) float red[NT][RJ][RS];
     __shared__ __align__(16) float sun[HMAX];              // the units' factors
     __shared__ int32_t sdesc[RJ * 4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int hidden = A.hidden, n_tiles = hidden / 8, m_tiles = (hidden + 31) / 32;
-    const int tile = wave & 3, group0 = wave >> 2;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int hidden = A.hidden, n_tiles = hidden / 8, tile = wave & 3, group = wave >> 2;
     const bool on = tile < n_tiles;
-    seq_h8_t wt[MT][2][2];                                 // [output tile][step][piece]
-    const seq_h8_t *wl = reinterpret_cast<const seq_h8_t *>(A.wqt) + lane;
+    seq_h8_t wt[2][2];                                     // [step][piece]
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) wt[mt][k >> 1][k & 1] = on && mt < m_tiles ? wl[(((size_t)tile * m_tiles + mt) * 4 + k) * 64] : seq_h8_t{};
+    for (int k = 0; k < 4; ++k)
+        wt[k >> 1][k & 1] = on ? reinterpret_cast<const seq_h8_t *>(A.wqt)[((size_t)tile * 4 + k) * 64 + (threadIdx.x & 63)] : seq_h8_t{};
     if ((int)threadIdx.x < hidden) sun[threadIdx.x] = A.wqt_unscale[threadIdx.x];   // (read behind the barriers of a tile)
-    const int64_t n_parts = A.n_path_tiles * (kSeqJobs / RJ);
-    for (int64_t ci = blockIdx.x; ci < n_parts; ci += gridDim.x) {
-        const int64_t ct = A.reversed ? n_parts - 1 - ci : ci;
+    for (int64_t ci = blockIdx.x; ci < A.n_path_tiles; ci += gridDim.x) {
+        const int64_t ct = A.reversed ? A.n_path_tiles - 1 - ci : ci;
         {
             const int tid = seq_opaque(threadIdx.x);
             if (tid < RJ * 4) sdesc[tid] = A.paths[ct * (RJ * 4) + tid];
         }
         __syncthreads();
-        const int steps = sdesc[2];
-        float dh[JG][4], dc[JG][4];
-        float dg[JG][16], gates[JG][16];                   // gates: requested a step ahead, in pieces (see seq_to_pieces)
-        float4 c_now[JG], c_prev[JG];                      // c_prev is the next step's c_now
-        int keep[JG];
-        auto load_step = [&](int g, int t) {               // the tape of step t, where the paths have one
-            const int l = seq_opaque(threadIdx.x) & 63, half = l >> 5, unit0 = tile * 8 + half * 4;
+        const int steps = __builtin_amdgcn_readfirstlane(sdesc[2]);
+        float dh[4] = {0.f, 0.f, 0.f, 0.f}, dc[4] = {0.f, 0.f, 0.f, 0.f};
+        float gates[16];                                   // requested a step ahead, in pieces (see seq_to_pieces)
+        float4 c_now = make_float4(0.f, 0.f, 0.f, 0.f), c_prev;   // c_prev is the next step's c_now
+        int keep;
+        // The tape of step t.  No load hangs on a condition, or the compiler waits for each before the next: a path without such a step reads its first cell, and
+        // c before a first step from the zero state is cleared where it is used.
+        auto load_step = [&](int t) {
+            const int l = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (l >> 5) * 4;
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                const int jj = (group0 + g) * 32 + 16 * q + (l & 15);
-                if (t < sdesc[jj * 4 + 2]) {
-                    const float *p = A.tape_g + ((size_t)(sdesc[jj * 4 + 1] + t) * hidden + tile * 8 + seq_piece(l)) * 4;
-                    const float4 v = *reinterpret_cast<const float4 *>(p), w = *reinterpret_cast<const float4 *>(p + 16);
-                    gates[g][8 * q] = v.x; gates[g][8 * q + 1] = v.y; gates[g][8 * q + 2] = v.z; gates[g][8 * q + 3] = v.w;
-                    gates[g][8 * q + 4] = w.x; gates[g][8 * q + 5] = w.y; gates[g][8 * q + 6] = w.z; gates[g][8 * q + 7] = w.w;
-                }
+                const int jj = group * 32 + 16 * q + (l & 15);
+                const float *p = A.tape_g + ((size_t)(sdesc[jj * 4 + 1] + (t >= 0 && t < sdesc[jj * 4 + 2] ? t : 0)) * hidden + tile * 8 + seq_piece(l)) * 4;
+                const float4 v = *reinterpret_cast<const float4 *>(p), w = *reinterpret_cast<const float4 *>(p + 16);
+                gates[8 * q] = v.x; gates[8 * q + 1] = v.y; gates[8 * q + 2] = v.z; gates[8 * q + 3] = v.w;
+                gates[8 * q + 4] = w.x; gates[8 * q + 5] = w.y; gates[8 * q + 6] = w.z; gates[8 * q + 7] = w.w;
             }
-            const int j = (group0 + g) * 32 + (l & 31), start = sdesc[j * 4], len = sdesc[j * 4 + 2];
-            if (t < len) {
-                const size_t cell = (size_t)sdesc[j * 4 + 1] + t;
-                keep[g] = A.step_out[cell];
-                c_prev[g] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (t > 0) c_prev[g] = *reinterpret_cast<const float4 *>(A.tape_c + (cell - 1) * hidden + unit0);
-                else if (start >= 0) c_prev[g] = *reinterpret_cast<const float4 *>(A.c_state + (size_t)start * hidden + unit0);
-            }
+            const int j = group * 32 + (l & 31), start = sdesc[j * 4], beg = sdesc[j * 4 + 1], len = sdesc[j * 4 + 2];
+            const bool inner = t > 0 && t < len, from_state = t == 0 && len > 0 && start >= 0;
+            keep = A.step_out[beg + (t >= 0 && t < len ? t : 0)];
+            c_prev = *reinterpret_cast<const float4 *>((from_state ? A.c_state : A.tape_c) + (size_t)(from_state ? start : inner ? beg + t - 1 : beg) * hidden + unit0);
         };
-        auto sum_parts = [&](int g, int j) {
+        auto sum_parts = [&](int j) {
             const int unit0 = tile * 8 + ((seq_opaque(threadIdx.x) >> 5) & 1) * 4;
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int w = 0; w < NT; ++w) {
-                if (w >= n_tiles) break;
-                const float4 q = *reinterpret_cast<const float4 *>(&red[w][j][unit0]);
-                const float by = red[w][j][HMAX];
+                const int from = w < n_tiles ? w : 0;      // (no branch, so that the reads go out together; what is not finite in tile 0 makes the sum so anyway)
+                const float4 q = *reinterpret_cast<const float4 *>(&red[from][j][unit0]);
+                const float by = w < n_tiles ? red[from][j][HMAX] : 0.f;
                 v.x = fmaf(q.x, by, v.x); v.y = fmaf(q.y, by, v.y); v.z = fmaf(q.z, by, v.z); v.w = fmaf(q.w, by, v.w);
             }
             const float4 un4 = *reinterpret_cast<const float4 *>(&sun[unit0]);
-            dh[g][0] = v.x * un4.x; dh[g][1] = v.y * un4.y; dh[g][2] = v.z * un4.z; dh[g][3] = v.w * un4.w;
+            dh[0] = v.x * un4.x; dh[1] = v.y * un4.y; dh[2] = v.z * un4.z; dh[3] = v.w * un4.w;
         };
-#pragma unroll
-        for (int g = 0; g < JG; ++g) {
+        if (on) {
             const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4;
-            const int j = (group0 + g) * 32 + (lane & 31), len = sdesc[j * 4 + 2], node = sdesc[j * 4 + 3];
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (on && node >= 0) v = *reinterpret_cast<const float4 *>(A.g_a + (size_t)node * hidden + unit0);
-            dh[g][0] = v.x; dh[g][1] = v.y; dh[g][2] = v.z; dh[g][3] = v.w;
-            dc[g][0] = dc[g][1] = dc[g][2] = dc[g][3] = 0.f;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) dg[g][e] = gates[g][e] = 0.f;
-            keep[g] = -1;
-            c_now[g] = c_prev[g] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (on && len > 0) c_now[g] = *reinterpret_cast<const float4 *>(A.tape_c + ((size_t)sdesc[j * 4 + 1] + len - 1) * hidden + unit0);
-            if (on && steps > 0) load_step(g, steps - 1);   // (a half that holds nothing but padding has no step)
-        }
-        for (int t = steps - 1; t >= 0; --t) {
-#pragma unroll
-            for (int g = 0; g < JG; ++g) {
-                if (!on) break;                            // (wavefronts beyond the hidden size only keep the barriers)
+            const int j = group * 32 + (lane & 31), len = sdesc[j * 4 + 2], node = sdesc[j * 4 + 3];
+            if (node >= 0) {
+                const float4 v = *reinterpret_cast<const float4 *>(A.g_a + (size_t)node * hidden + unit0);
+                dh[0] = v.x; dh[1] = v.y; dh[2] = v.z; dh[3] = v.w;
+            }
+            if (len > 0) c_now = *reinterpret_cast<const float4 *>(A.tape_c + ((size_t)sdesc[j * 4 + 1] + len - 1) * hidden + unit0);
+            load_step(steps - 1);
+            for (int t = steps - 1; t >= 0; --t) {
                 const int lane = seq_opaque(threadIdx.x) & 63, half = lane >> 5, unit0 = tile * 8 + half * 4;
-                const int j = (group0 + g) * 32 + (lane & 31), len = sdesc[j * 4 + 2];
-                seq_from_pieces(gates[g]);
+                const int j = group * 32 + (lane & 31), len = sdesc[j * 4 + 2];
+                float dg[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) dg[e] = 0.f;
+                seq_from_pieces(gates);
+                if (t == 0 && sdesc[j * 4] < 0) c_prev = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (t < len) {
-                    if (t + 1 < len) sum_parts(g, j);      // dh_prev of the step before is this step's dh
-                    if (keep[g] >= 0) {                    // what the other users of this state sent back
-                        if (A.pending) seq_wait_pending(A, keep[g]);
-                        const size_t o = (size_t)keep[g] * hidden + unit0;
+                    if (t + 1 < len) sum_parts(j);         // dh_prev of the step before is this step's dh
+                    if (keep >= 0) {                       // what the other users of this state sent back
+                        if (A.pending) seq_wait_pending(A, keep);
+                        const size_t o = (size_t)keep * hidden + unit0;
                         const float4 a = A.pending ? seq_ld4_device(A.gh + o) : *reinterpret_cast<const float4 *>(A.gh + o);
                         const float4 b = A.pending ? seq_ld4_device(A.gc + o) : *reinterpret_cast<const float4 *>(A.gc + o);
-                        dh[g][0] += a.x; dh[g][1] += a.y; dh[g][2] += a.z; dh[g][3] += a.w;
-                        dc[g][0] += b.x; dc[g][1] += b.y; dc[g][2] += b.z; dc[g][3] += b.w;
+                        dh[0] += a.x; dh[1] += a.y; dh[2] += a.z; dh[3] += a.w;
+                        dc[0] += b.x; dc[1] += b.y; dc[2] += b.z; dc[3] += b.w;
                     }
-                    const float cn[4] = {c_now[g].x, c_now[g].y, c_now[g].z, c_now[g].w}, cp[4] = {c_prev[g].x, c_prev[g].y, c_prev[g].z, c_prev[g].w};
+                    const float cn[4] = {c_now.x, c_now.y, c_now.z, c_now.w}, cp[4] = {c_prev.x, c_prev.y, c_prev.z, c_prev.w};
 #pragma unroll
                     for (int m = 0; m < 4; ++m) {
-                        const float4 g4 = make_float4(gates[g][4 * m], gates[g][4 * m + 1], gates[g][4 * m + 2], gates[g][4 * m + 3]);   // i, f, g, o
+                        const float4 g4 = make_float4(gates[4 * m], gates[4 * m + 1], gates[4 * m + 2], gates[4 * m + 3]);   // i, f, g, o
                         const float tc = seq_tanh(cn[m]);
-                        const float d_o = dh[g][m] * tc;
-                        const float dcc = dc[g][m] + dh[g][m] * g4.w * (1.f - tc * tc);
-                        dg[g][4 * m] = dcc * g4.z * g4.x * (1.f - g4.x);
-                        dg[g][4 * m + 1] = dcc * cp[m] * g4.y * (1.f - g4.y);
-                        dg[g][4 * m + 2] = dcc * g4.x * (1.f - g4.z * g4.z);
-                        dg[g][4 * m + 3] = d_o * g4.w * (1.f - g4.w);
-                        dc[g][m] = dcc * g4.y;
+                        const float d_o = dh[m] * tc;
+                        const float dcc = dc[m] + dh[m] * g4.w * (1.f - tc * tc);
+                        dg[4 * m] = dcc * g4.z * g4.x * (1.f - g4.x);
+                        dg[4 * m + 1] = dcc * cp[m] * g4.y * (1.f - g4.y);
+                        dg[4 * m + 2] = dcc * g4.x * (1.f - g4.z * g4.z);
+                        dg[4 * m + 3] = d_o * g4.w * (1.f - g4.w);
+                        dc[m] = dcc * g4.y;
                     }
-                    c_now[g] = c_prev[g];
+                    c_now = c_prev;
                 }
+                load_step(t - 1);
                 // dG replaces the gates on the tape
                 float4 v[4];
-                seq_to_pieces(dg[g], v);
+                seq_to_pieces(dg, v);
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
-                    const int jj = (group0 + g) * 32 + 16 * q + (lane & 15);
+                    const int jj = group * 32 + 16 * q + (lane & 15);
                     if (t < sdesc[jj * 4 + 2]) {
                         float *p = A.tape_g + ((size_t)(sdesc[jj * 4 + 1] + t) * hidden + tile * 8 + seq_piece(lane)) * 4;
                         *reinterpret_cast<float4 *>(p) = v[2 * q];
                         *reinterpret_cast<float4 *>(p + 16) = v[2 * q + 1];
                     }
                 }
-                if (t > 0) load_step(g, t - 1);
-            }
-            __syncthreads();                               // every lane has read the parts of the step before
-            if (on) {
+                __syncthreads();                           // every lane has read the parts of the step before
+                float most = 0.f;
 #pragma unroll
-                for (int g = 0; g < JG; ++g) {
-                    const int l = seq_opaque(threadIdx.x) & 63, half = l >> 5, j = (group0 + g) * 32 + (l & 31);
-                    float most = 0.f;
+                for (int e = 0; e < 16; ++e) most = fmaxf(most, fabsf(dg[e]));
+                const seq_u2_t both = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
+                const int up = seq_up(fmaxf(__uint_as_float(both.x), __uint_as_float(both.y)));   // of the path's 32 gate rows
+                const float one = (tile + j + t) & 1 ? -1.f : 1.f, by = __builtin_ldexpf(one, up);
+                if (half == 0) red[tile][j][HMAX] = __builtin_ldexpf(one, -15 - up);
+                seq_h8_t zb[2][2];                         // [step][piece]
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) most = fmaxf(most, fabsf(dg[g][e]));
-                    const seq_u2_t both = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
-                    const int up = seq_up(fmaxf(__uint_as_float(both.x), __uint_as_float(both.y)));   // of the path's 32 gate rows
-                    const float one = (tile + j + t) & 1 ? -1.f : 1.f, by = __builtin_ldexpf(one, up);
-                    if (half == 0) red[tile][j][HMAX] = __builtin_ldexpf(one, -15 - up);
-                    seq_h8_t zb[2][2];                     // [step][piece]
+                for (int k = 0; k < 2; ++k) {
+                    uint32_t p[4][2];
 #pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        uint32_t p[4][2];
+                    for (int i = 0; i < 4; ++i) seq_halves2(dg[8 * k + 2 * i] * by, dg[8 * k + 2 * i + 1] * by, p[i]);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) seq_halves2(dg[g][8 * k + 2 * i] * by, dg[g][8 * k + 2 * i + 1] * by, p[i]);
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) zb[k][i] = __builtin_bit_cast(seq_h8_t, make_uint4(p[0][i], p[1][i], p[2][i], p[3][i]));
-                    }
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        seq_acc_t acc;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-                        for (int k = 0; k < 2; ++k) {
-                            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[mt][k][1], zb[k][0], acc, 0, 0, 0);
-                            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[mt][k][0], zb[k][1], acc, 0, 0, 0);
-                        }
-#pragma unroll
-                        for (int k = 0; k < 2; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[mt][k][0], zb[k][0], acc, 0, 0, 0);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            *reinterpret_cast<float4 *>(&red[tile][j][mt * 32 + 8 * q + 4 * half]) = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
-                        __builtin_amdgcn_sched_barrier(0);   // (one accumulator at a time: registers are short)
-                    }
+                    for (int i = 0; i < 2; ++i) zb[k][i] = __builtin_bit_cast(seq_h8_t, make_uint4(p[0][i], p[1][i], p[2][i], p[3][i]));
                 }
+                seq_acc_t acc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[k][1], zb[k][0], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[k][0], zb[k][1], acc, 0, 0, 0);
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[k][0], zb[k][0], acc, 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4 *>(&red[tile][j][8 * q + 4 * half]) = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+                __syncthreads();                           // the parts of dh_prev are complete
             }
-            __syncthreads();                               // the parts of dh_prev are complete
+        } else {                                           // wavefronts beyond the hidden size only keep the barriers
+            for (int t = steps - 1; t >= 0; --t) {
+                __syncthreads();
+                __syncthreads();
+            }
         }
         // What is left: the gradient of the state the path started from, as rows in LDS first, so that one atomic instruction
         // covers a row of 256 contiguous bytes (issued by the lanes that hold the values, four bytes of each of 64 rows per
         // instruction, they took most of the kernel's time: the memory side does about 17 such requests per ns).
-        bool any = false;
-        if (threadIdx.x < RJ) any = sdesc[threadIdx.x * 4] >= 0;
-        if (__syncthreads_or(any)) {
-            const int tid = seq_opaque(threadIdx.x), lane = tid & 63, wave = tid >> 6, unit0 = tile * 8 + (lane >> 5) * 4;
-            float4 rows[JG];
-#pragma unroll
-            for (int g = 0; g < JG; ++g) {
-                const int j = (group0 + g) * 32 + (lane & 31);
-                if (on) sum_parts(g, j);
-                rows[g] = make_float4(dh[g][0], dh[g][1], dh[g][2], dh[g][3]);
-            }
+        if (__any(sdesc[(seq_opaque(threadIdx.x) & 63) * 4] >= 0)) {   // (the same for every wavefront)
+            const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4, own = group * 32 + (lane & 31);
+            if (on) sum_parts(own);
             __syncthreads();
             if (on) {
-#pragma unroll
-                for (int g = 0; g < JG; ++g) {
-                    const int j = (group0 + g) * 32 + (lane & 31);
-                    *reinterpret_cast<float4 *>(&red[0][j][unit0]) = rows[g];
-                    *reinterpret_cast<float4 *>(&red[1][j][unit0]) = make_float4(dc[g][0], dc[g][1], dc[g][2], dc[g][3]);
-                }
+                *reinterpret_cast<float4 *>(&red[0][own][unit0]) = make_float4(dh[0], dh[1], dh[2], dh[3]);
+                *reinterpret_cast<float4 *>(&red[1][own][unit0]) = make_float4(dc[0], dc[1], dc[2], dc[3]);
             }
             __syncthreads();
             for (int j = wave; j < RJ; j += 8) {

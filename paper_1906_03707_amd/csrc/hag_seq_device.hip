@@ -939,7 +939,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A
 //   wavefronts 8..15 run ahead: they load h and c of the tape and the rows of gx, multiply W_hh with h as the forward pass does and leave the gates of the
 //     next step in LDS, and c of this one; they are the only ones that wait for loads;
 //   wavefronts 0..7 go back through the steps, wavefront w for gate tile w, out of LDS, and write dG.
-// A step has two barriers, and the loads of a step are requested two steps ahead.  Vector instructions issue 55 % of the time, matrix cores are busy 15 %, 3 TB/s.
+// A step has two barriers, and the loads of a step are requested two steps ahead, across half tiles too (steps of 280 to 340 us over short lists 5 % faster).  Vector instructions issue 55 % of the time, matrix cores are busy 15 %, 3 TB/s.
 __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
     constexpr int HMAX = 64, MT = 2, NT = 8, RS = HMAX + 4, RJ = kSeqRevJobs, KS = 4, ZS = HMAX + 8;
     constexpr int PT = 512 / RJ;                           // threads that stage the h and c of one path, four columns each
@@ -949,7 +949,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
     __shared__ float4 gates[8][4][64];                     // of the next step, as the lanes hold them
     __shared__ int32_t skeep[2][RJ];                       // the state row that a step wrote, or -1
     __shared__ __align__(16) float sun[HMAX], sby[HMAX];   // the units' factors: of the product here, of the forward pass's pre-activations
-    __shared__ int32_t sdesc[4][RJ];                       // of a path: start state, first step, steps, node
+    __shared__ int32_t sdesc_of[2][4][RJ];                 // of a path: start state, first step, steps, node; of this half tile and of the next one
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), worker = wave & 7;
     const bool ahead = wave >= 8;
     const int hidden = A.hidden, n_tiles = hidden / 8, tile = worker;
@@ -964,107 +964,117 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
     if ((int)threadIdx.x < hidden) { sun[threadIdx.x] = A.wqt_unscale[threadIdx.x]; sby[threadIdx.x] = A.unscale[threadIdx.x]; }   // (read behind the barriers of a tile)
     for (int i = threadIdx.x; i < (int)(sizeof(z) / 4); i += 1024) reinterpret_cast<uint32_t *>(&z[0][0][0][0])[i] = 0;   // columns from `hidden` on stay zero
     const int64_t n_parts = A.n_path_tiles * (kSeqJobs / RJ);
-    for (int64_t ci = blockIdx.x; ci < n_parts; ci += gridDim.x) {
-        const int64_t ct = A.reversed ? n_parts - 1 - ci : ci;
-        {
-            const int tid = seq_opaque(threadIdx.x);
-            if (tid < RJ * 4) sdesc[tid & 3][tid >> 2] = A.paths[ct * (RJ * 4) + tid];
-        }
-        __syncthreads();
-        const int steps = __builtin_amdgcn_readfirstlane(sdesc[2][0]);   // (none where a half of a tile holds nothing but padding)
-        float dh[4] = {0.f, 0.f, 0.f, 0.f}, dc[4] = {0.f, 0.f, 0.f, 0.f};
-        auto sum_parts = [&](int j) {
-            const int unit0 = tile * 8 + ((seq_opaque(threadIdx.x) >> 5) & 1) * 4;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int w = 0; w < NT; ++w) {
-                const int from = w < n_tiles ? w : 0;      // (no branch, so that the reads go out together; what is not finite in tile 0 makes the sum so anyway)
-                const float4 q = *reinterpret_cast<const float4 *>(&red[from][j][unit0]);
-                const float by = w < n_tiles ? red[from][j][HMAX] : 0.f;
-                v.x = fmaf(q.x, by, v.x); v.y = fmaf(q.y, by, v.y); v.z = fmaf(q.z, by, v.z); v.w = fmaf(q.w, by, v.w);
-            }
-            const float4 un4 = *reinterpret_cast<const float4 *>(&sun[unit0]);
-            dh[0] = v.x * un4.x; dh[1] = v.y * un4.y; dh[2] = v.z * un4.z; dh[3] = v.w * un4.w;
+    const int32_t (*sdesc)[RJ] = sdesc_of[0];              // of this half tile
+    // The words of half tile number i; past the end those of the last one (nothing uses what is loaded for them).
+    auto word_of = [&](int64_t i, int w) {
+        i = i < n_parts ? i : n_parts - 1;
+        return A.paths[(A.reversed ? n_parts - 1 - i : i) * (RJ * 4) + w];
+    };
+    {
+        const int tid = seq_opaque(threadIdx.x);
+        if (tid < RJ * 4) sdesc_of[0][tid & 3][tid >> 2] = word_of(blockIdx.x, tid);
+    }
+    __syncthreads();
+    // The two roles take the same half tiles and keep the same barriers: two before the first step, two per step, two after the last if a path of the half tile started from a state.
+    auto hands_back = [&] { return __any(sdesc[0][seq_opaque(threadIdx.x) & 31] >= 0) != 0; };   // (the same for every wavefront)
+    if (ahead) {
+        // What the wavefronts that run ahead hold for their next steps.  Loads return in order and the compiler counts them, so none hangs on a condition: where a
+        // path has no such step its first cell is read.
+        float4 h_next, c_next;
+        int row, keep_next;                                // row: of gx
+        bool zero_next;
+        auto load_row = [&](int t) {
+            const int j = seq_opaque(threadIdx.x) & 31;
+            row = A.step_g[sdesc[1][j] + (t >= 0 && t < sdesc[2][j] ? t : 0)];
         };
-        if (ahead) {
-            // Loads return in order and the compiler counts them, so none hangs on a condition: where a path has no such step its first cell is read.
-            float gx[16];                                  // in pieces (see seq_to_pieces)
-            seq_acc_t pre;
-            float4 h_next, c_next, c_held = make_float4(0.f, 0.f, 0.f, 0.f);
-            int row, keep_next, keep_held = -1;            // row: of gx
-            bool zero_next;
-            auto load_row = [&](int t) {
-                const int j = (seq_opaque(threadIdx.x) & 31);
-                row = A.step_g[sdesc[1][j] + (t >= 0 && t < sdesc[2][j] ? t : 0)];
-            };
-            auto load_gx = [&] {                           // of the step whose row is at hand
-                const seq_u2_t rows = __builtin_amdgcn_permlane16_swap((unsigned)row, (unsigned)row, false, false);   // of paths l % 16 and 16 + l % 16
-                const int l = seq_opaque(threadIdx.x) & 63;
+        auto load_begun = [&](int t) {                     // four columns of the h and c that step t of a path began with, and the state row that it wrote
+            const int tid = seq_opaque(threadIdx.x) - 512, j = tid / PT, u = tid % PT * 4, start = sdesc[0][j], beg = sdesc[1][j], len = sdesc[2][j];
+            const bool inner = t > 0 && t < len, first = t == 0 && len > 0 && start >= 0;
+            const size_t at = (size_t)(inner ? beg + t - 1 : first ? start : beg) * hidden + (u < hidden ? u : 0);
+            h_next = *reinterpret_cast<const float4 *>((first ? A.h_state : A.tape_h) + at);
+            c_next = *reinterpret_cast<const float4 *>((first ? A.c_state : A.tape_c) + at);
+            keep_next = A.step_out[beg + (t >= 0 && t < len ? t : 0)];
+            zero_next = u >= hidden || !(inner || first);
+        };
+        int owed = -1;                                     // the start state of a path whose gradients this lane has still to count off
+        auto count_off = [&] {                             // once the wavefront has seen its atomics complete
+            if (!A.pending) return;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (owed >= 0 && A.publish) __hip_atomic_fetch_sub(A.pending + owed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            owed = -1;
+        };
+        float gx[16];                                      // in pieces (see seq_to_pieces)
+        seq_acc_t pre;
+        float4 c_held = make_float4(0.f, 0.f, 0.f, 0.f);
+        int keep_held = -1;
+        auto load_gx = [&] {                               // of the step whose row is at hand
+            const seq_u2_t rows = __builtin_amdgcn_permlane16_swap((unsigned)row, (unsigned)row, false, false);   // of paths l % 16 and 16 + l % 16
+            const int l = seq_opaque(threadIdx.x) & 63;
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const float *p = A.gx + ((size_t)(q ? rows.y : rows.x) * hidden + tile * 8 + seq_piece(l)) * 4;
-                    const float4 v = *reinterpret_cast<const float4 *>(p), w = *reinterpret_cast<const float4 *>(p + 16);
-                    gx[8 * q] = v.x; gx[8 * q + 1] = v.y; gx[8 * q + 2] = v.z; gx[8 * q + 3] = v.w;
-                    gx[8 * q + 4] = w.x; gx[8 * q + 5] = w.y; gx[8 * q + 6] = w.z; gx[8 * q + 7] = w.w;
-                }
-            };
-            auto load_begun = [&](int t) {                 // four columns of the h and c that step t of a path began with, and the state row that it wrote
-                const int tid = seq_opaque(threadIdx.x) - 512, j = tid / PT, u = tid % PT * 4, start = sdesc[0][j], beg = sdesc[1][j], len = sdesc[2][j];
-                const bool inner = t > 0 && t < len, first = t == 0 && len > 0 && start >= 0;
-                const size_t at = (size_t)(inner ? beg + t - 1 : first ? start : beg) * hidden + (u < hidden ? u : 0);
-                h_next = *reinterpret_cast<const float4 *>((first ? A.h_state : A.tape_h) + at);
-                c_next = *reinterpret_cast<const float4 *>((first ? A.c_state : A.tape_c) + at);
-                keep_next = A.step_out[beg + (t >= 0 && t < len ? t : 0)];
-                zero_next = u >= hidden || !(inner || first);
-            };
-            auto stage = [&](int t) {                      // h of step t, c of the step before (which is processed one step later than its gates are computed)
-                const int tid = seq_opaque(threadIdx.x) - 512, j = tid / PT, u = tid % PT * 4;
-                const float4 h = zero_next ? make_float4(0.f, 0.f, 0.f, 0.f) : h_next;
-                uint32_t a[2], b[2];
-                seq_halves2(h.x * kSeqHScale, h.y * kSeqHScale, a);
-                seq_halves2(h.z * kSeqHScale, h.w * kSeqHScale, b);
+            for (int q = 0; q < 2; ++q) {
+                const float *p = A.gx + ((size_t)(q ? rows.y : rows.x) * hidden + tile * 8 + seq_piece(l)) * 4;
+                const float4 v = *reinterpret_cast<const float4 *>(p), w = *reinterpret_cast<const float4 *>(p + 16);
+                gx[8 * q] = v.x; gx[8 * q + 1] = v.y; gx[8 * q + 2] = v.z; gx[8 * q + 3] = v.w;
+                gx[8 * q + 4] = w.x; gx[8 * q + 5] = w.y; gx[8 * q + 6] = w.z; gx[8 * q + 7] = w.w;
+            }
+        };
+        auto stage = [&](int t) {                          // h of step t, c of the step before (which is processed one step later than its gates are computed)
+            const int tid = seq_opaque(threadIdx.x) - 512, j = tid / PT, u = tid % PT * 4;
+            const float4 h = zero_next ? make_float4(0.f, 0.f, 0.f, 0.f) : h_next;
+            uint32_t a[2], b[2];
+            seq_halves2(h.x * kSeqHScale, h.y * kSeqHScale, a);
+            seq_halves2(h.z * kSeqHScale, h.w * kSeqHScale, b);
 #pragma unroll
-                for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2 *>(&z[t & 1][p][j][u]) = make_uint2(a[p], b[p]);   // (columns beyond `hidden`: zero)
-                *reinterpret_cast<float4 *>(&cs[(t + 1) & 1][j][u]) = c_held;
-                if (u == 0) skeep[(t + 1) & 1][j] = keep_held;
-                c_held = zero_next ? make_float4(0.f, 0.f, 0.f, 0.f) : c_next;
-                keep_held = keep_next;
-            };
-            auto product = [&](int t) {                    // the forward pass's recurrent product
-                const int l = seq_opaque(threadIdx.x) & 63;
+            for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2 *>(&z[t & 1][p][j][u]) = make_uint2(a[p], b[p]);   // (columns beyond `hidden`: zero)
+            *reinterpret_cast<float4 *>(&cs[(t + 1) & 1][j][u]) = c_held;
+            if (u == 0) skeep[(t + 1) & 1][j] = keep_held;
+            c_held = zero_next ? make_float4(0.f, 0.f, 0.f, 0.f) : c_next;
+            keep_held = keep_next;
+        };
+        auto product = [&](int t) {                        // the forward pass's recurrent product
+            const int l = seq_opaque(threadIdx.x) & 63;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) pre[r] = 0.f;
+            for (int r = 0; r < 16; ++r) pre[r] = 0.f;
 #pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    seq_h8_t zb[2];
+            for (int s = 0; s < KS; ++s) {
+                seq_h8_t zb[2];
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) zb[p] = *reinterpret_cast<const seq_h8_t *>(&z[t & 1][p][(l & 31)][16 * s + 8 * (l >> 5)]);
-                    pre = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * s + 1], zb[0], pre, 0, 0, 0);
-                    pre = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * s], zb[1], pre, 0, 0, 0);
-                    pre = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * s], zb[0], pre, 0, 0, 0);
-                }
-            };
-            auto put_gates = [&] {
-                const int l = seq_opaque(threadIdx.x) & 63;
-                const float4 by4 = *reinterpret_cast<const float4 *>(&sby[tile * 8 + (l >> 5) * 4]);
-                const float by[4] = {by4.x, by4.y, by4.z, by4.w};
-                seq_from_pieces(gx);
+                for (int p = 0; p < 2; ++p) zb[p] = *reinterpret_cast<const seq_h8_t *>(&z[t & 1][p][l & 31][16 * s + 8 * (l >> 5)]);
+                pre = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * s + 1], zb[0], pre, 0, 0, 0);
+                pre = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * s], zb[1], pre, 0, 0, 0);
+                pre = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * s], zb[0], pre, 0, 0, 0);
+            }
+        };
+        auto put_gates = [&] {
+            const int l = seq_opaque(threadIdx.x) & 63;
+            const float4 by4 = *reinterpret_cast<const float4 *>(&sby[tile * 8 + (l >> 5) * 4]);
+            const float by[4] = {by4.x, by4.y, by4.z, by4.w};
+            seq_from_pieces(gx);
 #pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    gates[worker][m][l] = make_float4(seq_sigmoid(pre[4 * m] + gx[4 * m], by[m]), seq_sigmoid(pre[4 * m + 1] + gx[4 * m + 1], by[m]),
-                                                      seq_tanh(pre[4 * m + 2] + gx[4 * m + 2], by[m]), seq_sigmoid(pre[4 * m + 3] + gx[4 * m + 3], by[m]));   // i, f, g, o
-            };
-            load_row(steps - 1);
-            load_begun(steps - 1);
+            for (int m = 0; m < 4; ++m)
+                gates[worker][m][l] = make_float4(seq_sigmoid(pre[4 * m] + gx[4 * m], by[m]), seq_sigmoid(pre[4 * m + 1] + gx[4 * m + 1], by[m]),
+                                                  seq_tanh(pre[4 * m + 2] + gx[4 * m + 2], by[m]), seq_sigmoid(pre[4 * m + 3] + gx[4 * m + 3], by[m]));   // i, f, g, o
+        };
+        load_row(sdesc[2][0] - 1);
+        load_begun(sdesc[2][0] - 1);
+        for (int64_t ci = blockIdx.x, nth = 0; ci < n_parts; ci += gridDim.x, ++nth) {
+            sdesc = sdesc_of[nth & 1];
+            const int steps = __builtin_amdgcn_readfirstlane(sdesc[2][0]);   // (none where a half of a tile holds nothing but padding)
+            const int word = word_of(ci + gridDim.x, seq_opaque(threadIdx.x) & (RJ * 4 - 1));   // of the next half tile
             load_gx();
             load_row(steps - 2);
             stage(steps - 1);
             load_begun(steps - 2);
             __syncthreads();
+            if (on) product(steps - 1);                    // (in the order of the loop, so that the counts of loads agree)
+            stage(steps - 2);
+            count_off();                                   // of the half tile before: a state that this one waits for may be among them
+            {
+                const int tid = seq_opaque(threadIdx.x) - 512;
+                if (tid < RJ * 4) sdesc_of[~nth & 1][tid & 3][tid >> 2] = word;
+            }
+            load_begun(steps - 3);
             if (on) {
-                product(steps - 1);                        // (in the order of the loop, so that the counts of loads agree)
-                stage(steps - 2);
-                load_begun(steps - 3);
                 put_gates();
                 load_gx();
                 load_row(steps - 3);
@@ -1080,8 +1090,6 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                     __syncthreads();
                 }
             } else {
-                stage(steps - 2);
-                load_begun(steps - 3);
                 __syncthreads();
                 for (int t = steps - 1; t >= 0; --t) {
                     stage(t - 2);
@@ -1090,11 +1098,53 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                     __syncthreads();
                 }
             }
-        } else {
+            // (the next half tile's first loads go out before this one's last gradients)
+            sdesc = sdesc_of[~nth & 1];
+            load_row(sdesc[2][0] - 1);
+            load_begun(sdesc[2][0] - 1);
+            sdesc = sdesc_of[nth & 1];
+            if (hands_back()) {
+                // What is left: the gradient of the state the path started from, as rows in LDS first, so that one atomic instruction
+                // covers a row of 256 contiguous bytes (issued by the lanes that hold the values, four bytes of each of 64 rows per
+                // instruction, they took most of the kernel's time: the memory side does about 17 such requests per ns).  Counted off in the next
+                // half tile, where this wavefront has waited for later loads anyway.
+                const int lane = seq_opaque(threadIdx.x) & 63;
+                __syncthreads();
+                __syncthreads();
+                for (int j = worker; j < RJ; j += 8) {
+                    const int start = sdesc[0][j];
+                    if (start < 0) continue;               // (the same for the whole wavefront; an empty path starts nowhere)
+                    if (lane < hidden) {
+                        __hip_atomic_fetch_add(A.gh + (size_t)start * hidden + lane, red[0][j][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_fetch_add(A.gc + (size_t)start * hidden + lane, red[1][j][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+                owed = lane < RJ / 8 ? sdesc[0][worker + 8 * lane] : -1;
+            }
+        }
+        count_off();
+    } else {
+        for (int64_t ci = blockIdx.x, nth = 0; ci < n_parts; ci += gridDim.x, ++nth) {
+            sdesc = sdesc_of[nth & 1];
+            const int steps = __builtin_amdgcn_readfirstlane(sdesc[2][0]);   // (none where a half of a tile holds nothing but padding)
+            float dh[4] = {0.f, 0.f, 0.f, 0.f}, dc[4] = {0.f, 0.f, 0.f, 0.f};
+            auto sum_parts = [&](int j) {
+                const int unit0 = tile * 8 + ((seq_opaque(threadIdx.x) >> 5) & 1) * 4;
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int w = 0; w < NT; ++w) {
+                    const int from = w < n_tiles ? w : 0;  // (no branch, so that the reads go out together; what is not finite in tile 0 makes the sum so anyway)
+                    const float4 q = *reinterpret_cast<const float4 *>(&red[from][j][unit0]);
+                    const float by = w < n_tiles ? red[from][j][HMAX] : 0.f;
+                    v.x = fmaf(q.x, by, v.x); v.y = fmaf(q.y, by, v.y); v.z = fmaf(q.z, by, v.z); v.w = fmaf(q.w, by, v.w);
+                }
+                const float4 un4 = *reinterpret_cast<const float4 *>(&sun[unit0]);
+                dh[0] = v.x * un4.x; dh[1] = v.y * un4.y; dh[2] = v.z * un4.z; dh[3] = v.w * un4.w;
+            };
             float4 c_now = make_float4(0.f, 0.f, 0.f, 0.f);
             if (on) {
                 const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4;
-                const int j = (lane & 31), len = sdesc[2][j], node = sdesc[3][j];
+                const int j = lane & 31, len = sdesc[2][j], node = sdesc[3][j];
                 if (node >= 0) {
                     const float4 v = *reinterpret_cast<const float4 *>(A.g_a + (size_t)node * hidden + unit0);
                     dh[0] = v.x; dh[1] = v.y; dh[2] = v.z; dh[3] = v.w;
@@ -1109,7 +1159,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                 for (int e = 0; e < 16; ++e) dg[e] = 0.f;
                 if (on) {
                     const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4;
-                    const int j = (lane & 31), len = sdesc[2][j];
+                    const int j = lane & 31, len = sdesc[2][j];
                     if (t < len) {
                         if (t + 1 < len) sum_parts(j);     // dh_prev of the step before is this step's dh
                         const int keep = skeep[t & 1][j];
@@ -1187,36 +1237,17 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                 }
                 __syncthreads();                           // the parts of dh_prev and the gates of the next step are complete
             }
-        }
-        // What is left: the gradient of the state the path started from, as rows in LDS first, so that one atomic instruction
-        // covers a row of 256 contiguous bytes (issued by the lanes that hold the values, four bytes of each of 64 rows per
-        // instruction, they took most of the kernel's time: the memory side does about 17 such requests per ns).
-        if (__any(sdesc[0][seq_opaque(threadIdx.x) & 31] >= 0)) {   // (the same for every wavefront)
-            const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4, own = (lane & 31);
-            const bool holds = on && !ahead;
-            if (holds) sum_parts(own);
-            __syncthreads();
-            if (holds) {
-                *reinterpret_cast<float4 *>(&red[0][own][unit0]) = make_float4(dh[0], dh[1], dh[2], dh[3]);
-                *reinterpret_cast<float4 *>(&red[1][own][unit0]) = make_float4(dc[0], dc[1], dc[2], dc[3]);
-            }
-            __syncthreads();
-            for (int j = wave; j < RJ; j += 16) {
-                const int start = sdesc[0][j];
-                if (start < 0) continue;                   // (the same for the whole wavefront; an empty path starts nowhere)
-                if (lane < hidden) {
-                    __hip_atomic_fetch_add(A.gh + (size_t)start * hidden + lane, red[0][j][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_fetch_add(A.gc + (size_t)start * hidden + lane, red[1][j][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (hands_back()) {
+                const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4, j = lane & 31;
+                if (on) sum_parts(j);
+                __syncthreads();
+                if (on) {
+                    *reinterpret_cast<float4 *>(&red[0][j][unit0]) = make_float4(dh[0], dh[1], dh[2], dh[3]);
+                    *reinterpret_cast<float4 *>(&red[1][j][unit0]) = make_float4(dc[0], dc[1], dc[2], dc[3]);
                 }
-            }
-            if (A.pending) {
-                // once the wavefront has seen its atomics complete, its paths are counted off
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                const int start = lane < RJ / 16 ? sdesc[0][wave + 16 * lane] : -1;
-                if (start >= 0 && A.publish) __hip_atomic_fetch_sub(A.pending + start, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __syncthreads();
             }
         }
-        __syncthreads();
     }
 }
 

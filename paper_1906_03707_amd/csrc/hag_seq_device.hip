@@ -21,6 +21,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "hag_device_common.hpp"
@@ -1466,13 +1467,16 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 // column tiles; every workgroup ends with its own partial sums, which a second kernel adds up in a fixed order (so the weight
 // gradients do not depend on timing).  blockIdx.y selects a slab of 256 rows of dW (hidden > 64 has two), blockIdx.z one of 32 NCT columns.
 //
-// The operands are cut into three bf16 pieces (seq_split2) once, by the thread that loads them: a thread takes one column of dG for all 32 rows, so its
-// loads are contiguous over a wavefront, eight rows make one 16-byte operand of v_mfma_f32_32x32x16_bf16 per piece, and the sums of dG over a
+// The operands are cut into pieces once, by the thread that loads them: a thread takes one column of dG for all 32 rows, so its
+// loads are contiguous over a wavefront, eight rows make one 16-byte operand of a 32x32x16 matrix instruction per piece, and the sums of dG over a
 // node's rows run in its registers.  The matrix cores cut what they add to the size of the accumulator, always in the same direction, and a
-// gradient adds hundreds of thousands of rows: the products of 32 rows therefore begin at zero, the large ones apart from the small ones,
-// and join the running sums in rounded additions.  (Numbers below about 2^-110 lose their last pieces; infinities and NaN stay not finite.)
-// 3.35 M cells of 64 units: 1.41 ms with fp32 matrix instructions, 1.07 so (4.0 TB/s; vector instructions issue 59 % of the time, matrix cores are busy
-// 31 %); 0.85 M cells of 128 units: 1.33 and 0.93 ms.  Error of the training step's results against 64 bits 1.2e-6 and 5e-7, 6.4e-7 and 5.3e-7.
+// gradient adds hundreds of thousands of rows: the products of 32 rows therefore begin at zero and join the running sums in rounded additions.
+//   Over the cells (SEG): two fp16 pieces, three products.  h is bounded; the 32 numbers of a column of dG are brought into range by the power of two
+//     that their largest asks for, with a sign that alternates over columns and chunks (so that half of the products are cut upwards), undone in the addition.
+//   Over the nodes, whose features have no bound: three bf16 pieces, six products, the large ones apart from the small ones.  (Numbers below about
+//     2^-110 lose their last pieces.)  Infinities and NaN stay not finite in both.
+// 3.35 M cells of 64 units: 1.41 ms with fp32 matrix instructions, 1.07 with bf16 pieces (vector instructions issue 59 % of the time, matrix cores are busy 31 %),
+// 0.96 with fp16 (4.5 TB/s); 0.85 M cells of 128 units: 1.33, 0.97 and 0.75 ms.  Error of the training step's results against 64 bits 1.2e-6, 5e-7 and 4.2e-7, 6.4e-7, 5.1e-7 and 5e-7.
 //
 // SEG: the rows are cells, taken in the order of the input row they read (`at`, ascending `seg`), z is h_prev, and while a row of dG is at hand
 // it is also added to s[seg], the sum of dG over the cells that read one node: dG is read once for both.  A workgroup takes a
@@ -1504,7 +1508,9 @@ template <int NCT, bool SEG>
 __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A, int kp) {
     constexpr int CK = kSeqWgradRows, ZW = NCT * 32, CPT = CK * ZW / 256;   // CPT: rows of z per thread
     // eight rows (k) of a column per 16-byte slot, slot q of column c at q ^ (c / 4 % 4): eight neighbouring columns cover all banks
-    __shared__ uint4 sdg[3][256][CK / 8], sz[3][ZW][CK / 8];
+    constexpr int P = SEG ? 2 : 3;                         // pieces per operand: fp16 over the cells, bf16 over the nodes
+    __shared__ uint4 sdg[P][256][CK / 8], sz[P][ZW][CK / 8];
+    __shared__ __align__(16) float sback[SEG ? 256 : 4];   // SEG: what undoes the factors of a column of dG and of h
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows4 = 4 * A.hidden, cols = A.cols;
     const int row0 = blockIdx.y * 256, n_rt = (rows4 - row0 < 256 ? rows4 - row0 : 256) / 32;
@@ -1567,30 +1573,44 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
         for (int c = 0; c < CPT; ++c)
             rz[c] = (zero >> ((seq_opaque(threadIdx.x) / ZW) * CPT + c)) & 1 ? 0.f : rz[c];
         const int tid = seq_opaque(threadIdx.x), zc = tid % ZW, zq = tid / ZW;
+        float by = 1.f;
+        if constexpr (SEG) {
+            float most = 0.f;
+#pragma unroll
+            for (int c = 0; c < CK; ++c) most = fmaxf(most, fabsf(rg[c]));
+            const int up = seq_up(most);
+            const float one = ((int)(c0 / CK) + tid) & 1 ? -1.f : 1.f;
+            by = __builtin_ldexpf(one, up);
+            sback[tid] = __builtin_ldexpf(one, -up) / kSeqHScale;
+        }
+        auto cut = [&](float a, float b, float by, uint32_t (&p)[P]) {
+            if constexpr (SEG) seq_halves2(a * by, b * by, p);
+            else seq_split2(a, b, p);
+        };
 #pragma unroll
         for (int q = 0; q < CK / 8; ++q) {
-            uint32_t w[3][4];
+            uint32_t w[P][4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                uint32_t p[3];
-                seq_split2(rg[8 * q + 2 * k], rg[8 * q + 2 * k + 1], p);
+                uint32_t p[P];
+                cut(rg[8 * q + 2 * k], rg[8 * q + 2 * k + 1], by, p);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) w[i][k] = p[i];
+                for (int i = 0; i < P; ++i) w[i][k] = p[i];
             }
 #pragma unroll
-            for (int i = 0; i < 3; ++i) sdg[i][tid][q ^ ((tid >> 2) & 3)] = make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]);
+            for (int i = 0; i < P; ++i) sdg[i][tid][q ^ ((tid >> 2) & 3)] = make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]);
         }
         {
-            uint32_t w[3][CPT / 2];
+            uint32_t w[P][CPT / 2];
 #pragma unroll
             for (int k = 0; k < CPT / 2; ++k) {
-                uint32_t p[3];
-                seq_split2(rz[2 * k], rz[2 * k + 1], p);
+                uint32_t p[P];
+                cut(rz[2 * k], rz[2 * k + 1], kSeqHScale, p);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) w[i][k] = p[i];
+                for (int i = 0; i < P; ++i) w[i][k] = p[i];
             }
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
+            for (int i = 0; i < P; ++i) {
                 if constexpr (CPT >= 8) {
 #pragma unroll
                     for (int q = 0; q < CPT / 8; ++q)
@@ -1639,34 +1659,53 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
         for (int g = 0; g < 2; ++g) {
             const int rt = 2 * wave + g;
             if (rt >= n_rt) continue;
-            seq_b8_t a[CK / 16][3];
+            typedef typename std::conditional<SEG, seq_h8_t, seq_b8_t>::type piece_t;
+            piece_t a[CK / 16][P];
 #pragma unroll
             for (int k = 0; k < CK / 16; ++k)
 #pragma unroll
-                for (int p = 0; p < 3; ++p) a[k][p] = *reinterpret_cast<const seq_b8_t *>(&sdg[p][rt * 32 + l32][(2 * k + half) ^ ((l32 >> 2) & 3)]);
+                for (int p = 0; p < P; ++p) a[k][p] = *reinterpret_cast<const piece_t *>(&sdg[p][rt * 32 + l32][(2 * k + half) ^ ((l32 >> 2) & 3)]);
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) {
-                auto z_piece = [&](int k, int p) { return *reinterpret_cast<const seq_b8_t *>(&sz[p][ct * 32 + l32][(2 * k + half) ^ ((l32 >> 2) & 3)]); };
+                auto z_piece = [&](int k, int p) { return *reinterpret_cast<const piece_t *>(&sz[p][ct * 32 + l32][(2 * k + half) ^ ((l32 >> 2) & 3)]); };
                 seq_acc_t t;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) t[r] = 0.f;
+                if constexpr (SEG) {
+                    piece_t b[CK / 16];
 #pragma unroll
-                for (int k = 0; k < CK / 16; ++k) {
-                    const seq_b8_t b0 = z_piece(k, 0), b1 = z_piece(k, 1), b2 = z_piece(k, 2);
-                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][2], b0, t, 0, 0, 0);
-                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][1], b0, t, 0, 0, 0);
-                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][1], b1, t, 0, 0, 0);
-                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][0], b1, t, 0, 0, 0);
-                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][0], b2, t, 0, 0, 0);
-                    if (NCT == 4) __builtin_amdgcn_sched_barrier(0);   // (registers are short)
+                    for (int k = 0; k < CK / 16; ++k) {
+                        b[k] = z_piece(k, 0);
+                        t = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k][1], b[k], t, 0, 0, 0);
+                        t = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k][0], z_piece(k, 1), t, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int k = 0; k < CK / 16; ++k) t = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k][0], b[k], t, 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 back = *reinterpret_cast<const float4 *>(&sback[rt * 32 + 8 * q + 4 * half]);
+                        acc[g][ct][4 * q] = fmaf(t[4 * q], back.x, acc[g][ct][4 * q]);
+                        acc[g][ct][4 * q + 1] = fmaf(t[4 * q + 1], back.y, acc[g][ct][4 * q + 1]);
+                        acc[g][ct][4 * q + 2] = fmaf(t[4 * q + 2], back.z, acc[g][ct][4 * q + 2]);
+                        acc[g][ct][4 * q + 3] = fmaf(t[4 * q + 3], back.w, acc[g][ct][4 * q + 3]);
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < CK / 16; ++k) {
+                        const piece_t b0 = z_piece(k, 0), b1 = z_piece(k, 1), b2 = z_piece(k, 2);
+                        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][2], b0, t, 0, 0, 0);
+                        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][1], b0, t, 0, 0, 0);
+                        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][1], b1, t, 0, 0, 0);
+                        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][0], b1, t, 0, 0, 0);
+                        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][0], b2, t, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) { acc[g][ct][r] += t[r]; t[r] = 0.f; }
+#pragma unroll
+                    for (int k = 0; k < CK / 16; ++k) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][0], z_piece(k, 0), t, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[g][ct][r] += t[r];
                 }
-#pragma unroll
-                for (int r = 0; r < 16; ++r) { acc[g][ct][r] += t[r]; t[r] = 0.f; }
-                if (NCT == 4) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int k = 0; k < CK / 16; ++k) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[k][0], z_piece(k, 0), t, 0, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[g][ct][r] += t[r];
                 if (NCT == 4) __builtin_amdgcn_sched_barrier(0);   // (one column tile at a time: registers are short)
             }
         }

@@ -934,7 +934,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A
 
 // Hidden sizes from 40 to 64: the products and their operands of the kernel above, 32 paths per workgroup, and the gates computed again instead of
 // read from the tape.  Bound by the tape, the kernel above took 1.93 ms for 3.35 M cells of 64 units and the forward pass 1.55, of which it stored 3.4 GB of gates for
-// most of the time; now 2.13 and 0.96 ms.  (Up to 32 units the products and the lockstep below take longer than the gates' bytes: 4 % slower on steps of 90 to 290 us.)
+// most of the time; now 2.02 and 0.96 ms.  (Up to 32 units the products and the lockstep below take longer than the gates' bytes: 4 % slower on steps of 90 to 290 us.)
 // Sixteen wavefronts in two roles, because one wavefront's registers do not hold both W_hh and W_hh^T, and weights streamed from the cache between the tape's
 // loads would wait for those (loads return in order: 2.50 ms):
 //   wavefronts 8..15 run ahead: they load h and c of the tape and the rows of gx, multiply W_hh with h as the forward pass does and leave the gates of the
@@ -944,7 +944,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A
 __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
     constexpr int HMAX = 64, MT = 2, NT = 8, RS = HMAX + 4, RJ = kSeqRevJobs, KS = 4, ZS = HMAX + 8;
     constexpr int PT = 512 / RJ;                           // threads that stage the h and c of one path, four columns each
-    __shared__ __align__(16) float red[NT][RJ][RS];
+    __shared__ __align__(16) float red[NT][RJ][RS], sfac[RJ][NT + 4];   // the parts of dh_prev, and what each is multiplied by
     __shared__ __align__(16) uint16_t z[2][2][RJ][ZS];     // the h that a step began with, in fp16 pieces: of the next step and of the one after it
     __shared__ __align__(16) float cs[2][RJ][RS];          // the c that a step began with: of this step and of the next one
     __shared__ float4 gates[8][4][64];                     // of the next step, as the lanes hold them
@@ -964,6 +964,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
     }
     if ((int)threadIdx.x < hidden) { sun[threadIdx.x] = A.wqt_unscale[threadIdx.x]; sby[threadIdx.x] = A.unscale[threadIdx.x]; }   // (read behind the barriers of a tile)
     for (int i = threadIdx.x; i < (int)(sizeof(z) / 4); i += 1024) reinterpret_cast<uint32_t *>(&z[0][0][0][0])[i] = 0;   // columns from `hidden` on stay zero
+    if (threadIdx.x < RJ * (NT + 4)) (&sfac[0][0])[threadIdx.x] = 0.f;
     const int64_t n_parts = A.n_path_tiles * (kSeqJobs / RJ);
     const int32_t (*sdesc)[RJ] = sdesc_of[0];              // of this half tile
     // The words of half tile number i; past the end those of the last one (nothing uses what is loaded for them).
@@ -1132,12 +1133,12 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
             auto sum_parts = [&](int j) {
                 const int unit0 = tile * 8 + ((seq_opaque(threadIdx.x) >> 5) & 1) * 4;
                 float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                const float4 f0 = *reinterpret_cast<const float4 *>(&sfac[j][0]), f1 = *reinterpret_cast<const float4 *>(&sfac[j][4]);   // (zero of tiles that do not exist)
+                const float by[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
 #pragma unroll
                 for (int w = 0; w < NT; ++w) {
-                    const int from = w < n_tiles ? w : 0;  // (no branch, so that the reads go out together; what is not finite in tile 0 makes the sum so anyway)
-                    const float4 q = *reinterpret_cast<const float4 *>(&red[from][j][unit0]);
-                    const float by = w < n_tiles ? red[from][j][HMAX] : 0.f;
-                    v.x = fmaf(q.x, by, v.x); v.y = fmaf(q.y, by, v.y); v.z = fmaf(q.z, by, v.z); v.w = fmaf(q.w, by, v.w);
+                    const float4 q = *reinterpret_cast<const float4 *>(&red[w < n_tiles ? w : 0][j][unit0]);   // (no branch, so that the reads go out together; what is not finite in tile 0 makes the sum so anyway)
+                    v.x = fmaf(q.x, by[w], v.x); v.y = fmaf(q.y, by[w], v.y); v.z = fmaf(q.z, by[w], v.z); v.w = fmaf(q.w, by[w], v.w);
                 }
                 const float4 un4 = *reinterpret_cast<const float4 *>(&sun[unit0]);
                 dh[0] = v.x * un4.x; dh[1] = v.y * un4.y; dh[2] = v.z * un4.z; dh[3] = v.w * un4.w;
@@ -1154,6 +1155,8 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
             }
             __syncthreads();
             __syncthreads();                               // the gates of the last step are complete
+            // (waited for here, or the compiler waits for everything outstanding, the stores of dG too, in every step)
+            asm volatile("" : "+v"(c_now.x), "+v"(c_now.y), "+v"(c_now.z), "+v"(c_now.w), "+v"(dh[0]), "+v"(dh[1]), "+v"(dh[2]), "+v"(dh[3]));
             for (int t = steps - 1; t >= 0; --t) {
                 float dg[16];
 #pragma unroll
@@ -1209,7 +1212,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                     const seq_u2_t both = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
                     const int up = seq_up(fmaxf(__uint_as_float(both.x), __uint_as_float(both.y)));   // of the path's 32 gate rows
                     const float one = (tile + j + t) & 1 ? -1.f : 1.f, by = __builtin_ldexpf(one, up);
-                    if (half == 0) red[tile][j][HMAX] = __builtin_ldexpf(one, -15 - up);
+                        if (half == 0) sfac[j][tile] = __builtin_ldexpf(one, -15 - up);
                     seq_h8_t zb[2][2];                     // [step][piece]
 #pragma unroll
                     for (int k = 0; k < 2; ++k) {

@@ -91,10 +91,10 @@ __device__ __forceinline__ void seq_split2(float a, float b, uint32_t (&p)[3]) {
 
 // The operands of the recurrent product in the forward pass as two fp16 numbers each, 11 + 11 significant bits: what is cut off is 2^-23 of a number at
 // most, 2^-25 on average and of either sign, about what one fp32 addition rounds, and a product needs three matrix instructions
-// instead of six.  Both operands fit fp16's range because both are bounded: |h| < 1 is multiplied by 2^4 and the weights of a unit by the power of two
-// that brings the largest to [2^5, 2^6), so what the second piece of a small number rounds off (2^-25, the subnormal numbers of fp16) is
-// 2^-29 and 2^-30 of the largest; the factors stay that small so that pre-activations have the range of fp32 but for a few powers of ten.
-constexpr float kSeqHScale = 16.f;
+// instead of six.  Both operands fit fp16's range because both are bounded: |h| < 1 is multiplied by 2^8 and the weights of a unit by the power of two
+// that brings the largest to [2^8, 2^9), so what the second piece of a small number rounds off (2^-25, the subnormal numbers of fp16) is
+// 2^-33 of the largest; the factors stay that small so that pre-activations have the range of fp32 but for six powers of ten.
+constexpr float kSeqHScale = 256.f;
 __device__ __forceinline__ void seq_halves2(float a, float b, uint32_t (&p)[2]) {   // two numbers, packed as the low and the high half of each word
 #pragma clang fp contract(off)
     const seq_f2_t v = {a, b};
@@ -141,8 +141,8 @@ __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__
     if (lane == 0) largest[gate] = most;
     __syncthreads();
     most = fmaxf(fmaxf(largest[0], largest[1]), fmaxf(largest[2], largest[3]));
-    // (smaller weights than 2^-4 are not brought up all the way: what they lose is 2^-35, and the input half keeps clear of fp32's end)
-    const int up = most < INFINITY ? min(6 - __builtin_amdgcn_frexp_expf(most), 10) : 0;
+    // (smaller weights than 2^-4 are not brought up all the way: what they lose is 2^-37, and the input half keeps clear of fp32's end)
+    const int up = most < INFINITY ? min(9 - __builtin_amdgcn_frexp_expf(most), 12) : 0;
     const float by = __builtin_ldexpf(1.f, up), with_h = twice * by * kSeqHScale;
     const int r = 4 * unit + gate, tile = unit >> 3, in_tile = 8 * (unit & 3) + 4 * ((unit >> 2) & 1) + gate;
 #pragma unroll

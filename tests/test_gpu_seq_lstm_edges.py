@@ -113,11 +113,13 @@ def test_units_of_very_different_weights(B, d, hidden):
     rng = np.random.default_rng(d)
     size = np.tile(np.array([8.0, 1.0, 2.0 ** -12, 2.0 ** -60, 0.0])[np.arange(hidden) % 5], 4)[:, None]
     x, w_ih, w_hh, b = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)) * size, rng.normal(0, 0.3, 4 * hidden)
+    w_hh[2, 1] = 300.0            # one large weight beside small ones within a unit
     x[3, 1], x[5, 2] = 1e25, 1e-25
     f32 = [a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b)]
     want, _ = lstm.naive_aggregate(rowptr, col, *f32)
-    # pre-activations of hidden terms of 8 * 0.3 |h| and d of 0.3: (0.5 * 2.4 hidden + d) * 2^-24 at most, the gates' slopes are below 1
-    bar = 1e-6 + (1.2 * hidden + d) * 2.0 ** -24 * 4
+    # pre-activations of hidden terms of 8 * 0.3 |h| and d of 0.3: (0.5 * 2.4 hidden + d) * 2^-24 at most, the gates' slopes are below 1; the unit with the
+    # large weight adds one term of 300 |h|
+    bar = 1e-6 + (1.2 * hidden + d + 300) * 2.0 ** -24 * 4
     for cap in (0, int(col.size)):
         h = B.SeqHag(rowptr, col, cap).upload()
         got = h.lstm_forward(dev(x), dev(w_ih), dev(w_hh), dev(b))

@@ -219,7 +219,8 @@ int hag_seq_lstm_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const fl
 /* Training with the LSTM aggregator (the sizes of hag_seq_lstm_forward).
  * hag_seq_lstm_forward_train is hag_seq_lstm_forward that also keeps, in `workspace`
  * (hag_seq_train_workspace_bytes(h, d, hidden) bytes, 16-byte aligned), what the backward pass needs of every cell: the
- * activated gates, c and h (24 H bytes per cell evaluation), besides the states of the shared prefixes.
+ * activated gates (but for hidden sizes 40 to 64, whose backward pass computes them again), c and h (24 H bytes per cell
+ * evaluation, where the backward pass leaves its gradients too), besides the states of the shared prefixes.
  * hag_seq_lstm_backward, called after it with the same handle, sizes, x, w_ih, w_hh and workspace (nothing else may have
  * used the workspace in between), backpropagates through time along the plan's paths, last step first: given g_a [n, H], the
  * gradient of a loss with respect to a_out, it writes the gradients g_x [n, d], g_w_ih [4H, d], g_w_hh [4H, H], g_b [4H]

@@ -332,14 +332,15 @@ __device__ __forceinline__ void seq_from_pieces(V &v) {
 //
 // The product runs in fp16 pieces (seq_halves2): three v_mfma_f32_32x32x16_f16 per 16 columns cost 96 cycles against 192 for bf16 pieces (six) and
 // 512 for fp32 instructions.  What is left is the element-wise part and the rows of gx.  Inference over 370 k nodes (hidden = d = 64, prefix HAG with 3.35 M
-// cells): 877 us with bf16 pieces, 737 so, 724 with one reciprocal for two gate functions; with the tape 1.57 and 1.49 ms (0.96 without the gates); 0.85 M cells of 128 units with the tape: 1.18 and 1.01 ms.  Error of the
+// cells): 877 us with bf16 pieces, 737 so, 724 with one reciprocal for two gate functions; with the tape 1.57 and 1.49 ms (0.96 without the gates); 0.85 M cells of 128 units with the tape: 1.18 and 1.06 ms.  Error of the
 // result against 64 bits 2.1e-7 and 1.9e-7 (128 units: 2.7e-7 and 2.5e-7).
 // A gate tile is 32 gate rows = 8 hidden units; lane l of the product holds, for path l % 32 of its half of the tile, the four
 // gates of units 8 * tile + 4 * (l / 32) + 0..3.
 //   HMAX 64 (hidden 33..64): 8 wavefronts, wavefront w holds gate tile w in registers and takes both halves of the paths;
 //   HMAX 32: wavefront w holds gate tile w % 4 and takes half w / 4;
-//   HMAX 128: 16 wavefronts, wavefront w streams gate tile w (2 KB per 16 columns) from the L2 cache once per step for both
-//   halves: the pieces of a whole tile would be 64 of the 128 registers there are at four wavefronts per SIMD.
+//   HMAX 128: 16 wavefronts, wavefront w holds half of gate tile w in registers (a whole tile would be 64 of the 128 there are at four wavefronts per SIMD) and streams
+//   the rest (2 KB per 16 columns) from the L2 cache once per step for both halves of the paths.  The weights in registers come first: the streamed ones, which
+//   queue behind the tape's stores, arrive meanwhile (0.85 M cells of 128 units with the tape: 1.06 ms with all of the tile streamed, 0.96 so).
 template <int HMAX, bool TAPE>
 __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(SeqChainArgs A) {
     constexpr bool BIG = HMAX == 128, WIDE = HMAX >= 64, C_LDS = HMAX == 64 || TAPE, GATES = TAPE && HMAX != 64;   // (of 64 units the backward pass computes the gates again)
@@ -354,17 +355,16 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
     const int hidden = A.hidden, n_tiles = hidden / 8, ks = BIG ? (hidden + 15) / 16 : KS;
     const int tile = WIDE ? wave : (wave & 3), group0 = WIDE ? 0 : (wave >> 2);
     const bool on = tile < n_tiles;                        // wavefronts beyond the hidden size only keep the barriers
-    seq_h8_t wreg[BIG ? 1 : KS][2];
+    constexpr int KR = BIG ? 4 : KS;                       // steps of 16 columns whose weights stay in registers (above 64 units there are five at least)
+    seq_h8_t wreg[KR][2];
     const seq_h8_t *wl = reinterpret_cast<const seq_h8_t *>(A.wq) + (size_t)tile * ks * 2 * 64 + lane;
     const float4 by4 = on ? *reinterpret_cast<const float4 *>(A.unscale + tile * 8 + half * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
     const float by[4] = {by4.x, by4.y, by4.z, by4.w};
-    if constexpr (!BIG) {
-        if (on) {
+    if (on) {
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
+        for (int s = 0; s < KR; ++s)
 #pragma unroll
-                for (int p = 0; p < 2; ++p) wreg[s][p] = wl[(s * 2 + p) * 64];
-        }
+            for (int p = 0; p < 2; ++p) wreg[s][p] = wl[(s * 2 + p) * 64];
     }
     // columns from `hidden` on stay zero in both buffers
     for (int i = threadIdx.x; i < (int)(sizeof(z) / 4); i += blockDim.x) reinterpret_cast<uint32_t *>(&z[0][0][0][0])[i] = 0;
@@ -479,19 +479,33 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
             const int cur = t & 1;
             if (on) {
                 if constexpr (BIG) {
+                    // the others are requested first, two steps at a time, and arrive while the products of those in registers run
+                    seq_h8_t wa[2][2];
+                    auto load_w = [&](int i, int s) {
+                        s = s < ks ? s : ks - 1;
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) wa[i][p] = wl[(s * 2 + p) * 64];
+                    };
+                    load_w(0, KR);
+                    load_w(1, KR + 1);
 #pragma unroll
                     for (int g = 0; g < JG; ++g) seq_from_pieces(acc[g]);
-                    seq_h8_t wa[2], wn[2];
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) wa[p] = wl[p * 64];
-                    for (int s = 0; s < ks; ++s) {
-                        const int sn = s + 1 < ks ? s + 1 : s;
+                    for (int s = 0; s < KR; ++s)
 #pragma unroll
-                        for (int p = 0; p < 2; ++p) wn[p] = wl[(sn * 2 + p) * 64];
+                        for (int g = 0; g < JG; ++g) product(cur, g, acc[g], wreg[s], s);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int g = 0; g < JG; ++g) product(cur, g, acc[g], wa, s);
+                    for (int s = KR; s < 8; s += 2) {
+                        if (s >= ks) break;
 #pragma unroll
-                        for (int p = 0; p < 2; ++p) wa[p] = wn[p];
+                        for (int i = 0; i < 2; ++i) {
+                            if (s + i < ks) {
+#pragma unroll
+                                for (int g = 0; g < JG; ++g) product(cur, g, acc[g], wa[i], s + i);
+                            }
+                            if (s + 2 < 8) load_w(i, s + 2 + i);
+                        }
                     }
                 }
 #pragma unroll

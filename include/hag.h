@@ -184,6 +184,9 @@ int64_t hag_seq_cells(const hag_seq_t *h);
 int64_t hag_seq_ranks(const hag_seq_t *h);
 int64_t hag_seq_launches(const hag_seq_t *h);
 int64_t hag_seq_merges(const hag_seq_t *h);
+/* How the backward pass cuts the columns of a weight gradient (host; for tests): the number of slabs of *slab_cols columns that workgroups
+ * take side by side, over the cells (over_cells != 0: g_w_hh, cols = H) or over the nodes (g_w_ih, cols = d).  0 for cols <= 0. */
+int64_t hag_seq_weight_grad_slabs(int64_t cols, int32_t over_cells, int64_t *slab_cols);
 /* The plan as the device executes it (host arrays owned by the handle, valid until hag_seq_free; any out
  * pointer may be NULL): the shared prefixes and the nodes' remainders cut into PATHS -- a path carries its
  * running (h, c) from step to step on chip -- in groups such that a path starts only from a state that a path

@@ -33,7 +33,7 @@ EXPORTS = [
     "hag_backward", "hag_forward_phases", "hag_backward_phases", "hag_naive_forward", "hag_naive_backward",
     "hag_algorithmic_bytes", "hag_last_error", "hag_forward_static_scratch", "hag_probe_rows", "hag_probe_copy", "hag_probe_mfma_f32", "hag_set_option", "hag_check", "hag_seq_search",
     "hag_seq_create", "hag_seq_free", "hag_seq_cells", "hag_seq_ranks", "hag_seq_launches", "hag_seq_get_plan", "hag_seq_set_option", "hag_seq_check", "hag_seq_train_workspace_bytes", "hag_seq_lstm_forward_train", "hag_seq_lstm_backward", "hag_seq_merges", "hag_seq_upload", "hag_seq_workspace_bytes",
-    "hag_seq_lstm_forward", "hag_route", "hag_naive_route", "hag_forward_workspace_bytes",
+    "hag_seq_lstm_forward", "hag_seq_weight_grad_slabs", "hag_route", "hag_naive_route", "hag_forward_workspace_bytes",
     "hag_weight_grad_workspace_bytes", "hag_weight_grad", "hag_narrow_product", "hag_softmax_loss_workspace_bytes", "hag_softmax_loss", "hag_softmax_loss_grad",
 ]
 ROUTES = ("hag", "lists", "component_hag", "component_lists", "dense", "one_launch", "scatter")   # HAG_ROUTE_*
@@ -100,6 +100,8 @@ def lib():
         for name in ("hag_seq_cells", "hag_seq_ranks", "hag_seq_launches", "hag_seq_merges"):
             getattr(L, name).argtypes = [vp]
             getattr(L, name).restype = i64
+        L.hag_seq_weight_grad_slabs.argtypes = [i64, i32, ctypes.POINTER(i64)]
+        L.hag_seq_weight_grad_slabs.restype = i64
         L.hag_seq_upload.argtypes = [vp]
         L.hag_seq_get_plan.argtypes = [vp, i32] + [vp] * 8
         L.hag_seq_set_option.argtypes = [vp, i32, i64]

@@ -1562,12 +1562,12 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
         const int tid = seq_opaque(threadIdx.x), zc = tid % ZW, zq = tid / ZW;
         const uint64_t g_row = (uint64_t)(A.dg + row0) + (uint64_t)(uint32_t)ig * (uint32_t)(rows4 * 4);
         const bool state = SEG && iz <= -2;
-        const uint64_t z_row = (uint64_t)((state ? A.z2 : A.z) + col0) + (uint64_t)(uint32_t)(state ? -iz - 2 : iz < 0 ? 0 : iz) * (uint32_t)(cols * 4);
+        const uint64_t z_row = (uint64_t)(state ? A.z2 : A.z) + (uint64_t)(uint32_t)(state ? -iz - 2 : iz < 0 ? 0 : iz) * (uint32_t)(cols * 4);
         zero = (uint32_t)__ballot(iz == -1 || c0 + (lane & (CK - 1)) >= last);
         const uint32_t g_off = (uint32_t)seq_opaque((int)gate_off);
 #pragma unroll
         for (int c = 0; c < CK; ++c) rg[c] = *seq_at(seq_lane64(g_row, c), g_off);
-        const uint32_t z_off = (uint32_t)(col0 + zc < cols ? zc : 0) * 4;   // (columns of padding: no result reads them)
+        const uint32_t z_off = (uint32_t)(col0 + zc < cols ? col0 + zc : cols - 1) * 4;   // (columns of padding read the row's last: no result reads them)
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
             if constexpr (ZW >= 64) rz[c] = *seq_at(seq_lane64(z_row, wave * 64 / ZW * CPT + c), z_off);   // a wavefront has one run of rows
@@ -1847,7 +1847,17 @@ __global__ __launch_bounds__(256) void seq_input_grad_kernel(const float *__rest
     }
 }
 
-// The two weight-gradient contractions: column tiles (as the kernel rounds them), floats of one workgroup's partial sums,
+// How a weight-gradient contraction cuts its columns: `tiles` column tiles of 32 per workgroup (1, 2 or 4: a template argument), `slabs` of them side by side
+// along z, of which none begins beyond the last column.  Over the cells a workgroup takes all columns (128 at most); over the nodes, most often few beside the cells,
+// slabs of 64 leave registers free and cost a read of s each.  Where there are as many nodes as cells (200 k nodes in lists of two that share none), training steps with
+// three and four slabs take 0.86 (d = 160, hidden 40), 1.11 (160, 64) and 1.17 ms (196, 56), with all columns in one workgroup and fp32 products 1.04, 1.32 and 1.33.
+struct SeqWgradSlabs { int64_t tiles, slabs; };
+static constexpr SeqWgradSlabs seq_wgrad_slabs(int64_t cols, bool over_cells) {
+    const int64_t ct = (cols + 31) / 32, most = over_cells ? 4 : 2, rounded = ct <= 1 ? 1 : ct <= 2 ? 2 : 4, tiles = rounded < most ? rounded : most;
+    return {tiles, (ct + tiles - 1) / tiles};
+}
+
+// The two weight-gradient contractions: column tiles of a row of partial sums, floats of one workgroup's partial sums,
 // workgroups along x and rows per workgroup (a multiple of the rows staged at a time).
 struct SeqWgradShape { int nct; int64_t per, groups, range; };
 static SeqWgradShape seq_wgrad_shape(int64_t rows, int64_t cols, int64_t hidden) {
@@ -1865,15 +1875,12 @@ static SeqWgradShape seq_wgrad_shape(int64_t rows, int64_t cols, int64_t hidden)
 
 template <bool SEG>
 static int launch_wgrad(const SeqWgradArgs &g, const SeqWgradShape &w, int64_t hidden, hipStream_t s) {
-    // (the nodes are few beside the cells: their columns in slabs of 64, which leaves registers free; hidden has at most four column tiles)
-    constexpr int most = SEG ? 4 : 2;
-    const dim3 grid((unsigned)w.groups, (unsigned)((4 * hidden + 255) / 256), (unsigned)(w.nct > most ? w.nct / most : 1)), block(256);
+    const SeqWgradSlabs z = seq_wgrad_slabs(g.cols, SEG);
+    const dim3 grid((unsigned)w.groups, (unsigned)((4 * hidden + 255) / 256), (unsigned)z.slabs), block(256);
     const int kp = 32 * w.nct;
-    switch (std::min(w.nct, most)) {
-        case 1: hipLaunchKernelGGL((seq_weight_grad_kernel<1, SEG>), grid, block, 0, s, g, kp); break;
-        case 2: hipLaunchKernelGGL((seq_weight_grad_kernel<2, SEG>), grid, block, 0, s, g, kp); break;
-        default: hipLaunchKernelGGL((seq_weight_grad_kernel<4, true>), grid, block, 0, s, g, kp); break;
-    }
+    if (z.tiles == 1) hipLaunchKernelGGL((seq_weight_grad_kernel<1, SEG>), grid, block, 0, s, g, kp);
+    else if (z.tiles == 2) hipLaunchKernelGGL((seq_weight_grad_kernel<2, SEG>), grid, block, 0, s, g, kp);
+    else if constexpr (SEG) hipLaunchKernelGGL((seq_weight_grad_kernel<4, true>), grid, block, 0, s, g, kp);
     HIP_TRY(hipGetLastError());
     return HAG_OK;
 }
@@ -2081,6 +2088,12 @@ int64_t hag_seq_launches(const hag_seq_t *h) {
     if (!h) return 0;
     const int64_t levels = (int64_t)h->level_ptr.size() - 1;
     return h->one_launch ? std::min<int64_t>(levels, 1) : levels;
+}
+int64_t hag_seq_weight_grad_slabs(int64_t cols, int32_t over_cells, int64_t *slab_cols) {
+    if (cols <= 0) return 0;
+    const SeqWgradSlabs z = seq_wgrad_slabs(cols, over_cells != 0);
+    if (slab_cols) *slab_cols = 32 * z.tiles;
+    return z.slabs;
 }
 int64_t hag_seq_merges(const hag_seq_t *h) { return h ? h->n_merges : 0; }
 

@@ -278,3 +278,15 @@ def test_lstm_workspace_sizes():
         fwd, train = plan.workspace_bytes(d, hidden), plan.train_workspace_bytes(d, hidden)
         assert fwd > 0 and train >= fwd + plan.cells * 24 * hidden
     assert plan.train_workspace_bytes(8, 136) == 0 and plan.train_workspace_bytes(200, 64) == 0 and plan.train_workspace_bytes(6, 8) == 0
+
+
+def test_slabs_of_a_weight_gradient_begin_within_the_columns():
+    # a workgroup of a slab that begins beyond the last column would read past the end of a row of x; the columns of padding of the last slab are
+    # clamped within the kernel
+    import ctypes
+    width = ctypes.c_int64()
+    for over_cells, sizes in ((0, range(4, 249, 4)), (1, range(8, 129, 8))):
+        for cols in sizes:
+            slabs = B.lib().hag_seq_weight_grad_slabs(cols, over_cells, ctypes.byref(width))
+            assert (slabs - 1) * width.value < cols <= slabs * width.value, (cols, over_cells)
+    assert B.lib().hag_seq_weight_grad_slabs(0, 0, None) == 0

@@ -91,10 +91,11 @@ __device__ __forceinline__ void seq_split2(float a, float b, uint32_t (&p)[3]) {
 
 // The operands of the recurrent product in the forward pass as two fp16 numbers each, 11 + 11 significant bits: what is cut off is 2^-23 of a number at
 // most, 2^-25 on average and of either sign, about what one fp32 addition rounds, and a product needs three matrix instructions
-// instead of six.  Both operands fit fp16's range because both are bounded: |h| < 1 is multiplied by 2^8 and the weights of a unit by the power of two
+// instead of six.  Both operands fit fp16's range because both are bounded: |h| < 1 is multiplied by 2^8 and the weights of a gate row by the power of two
 // that brings the largest to [2^8, 2^9), so what the second piece of a small number rounds off (2^-25, the subnormal numbers of fp16) is
 // 2^-33 of the largest; the factors stay that small so that pre-activations have the range of fp32 but for six powers of ten.
 constexpr float kSeqHScale = 256.f;
+constexpr int kSeqHScaleExp = 8;
 __device__ __forceinline__ void seq_halves2(float a, float b, uint32_t (&p)[2]) {   // two numbers, packed as the low and the high half of each word
 #pragma clang fp contract(off)
     const seq_f2_t v = {a, b};
@@ -105,21 +106,20 @@ __device__ __forceinline__ void seq_halves2(float a, float b, uint32_t (&p)[2]) 
 }
 
 // Weights in the forms the kernels read, from the usual layout (w_ih [4H, D], w_hh [4H, H], b [4H], gate-major rows: input,
-// forget, cell, output gate).  Everything that makes up a pre-activation is multiplied by a power of two of its unit (see seq_halves2), and
-// twice that for the cell gate, whose tanh is a function of 2 z:
-//   wx: W_ih for the product over input rows, fp32, [gate tile][dp / 8 groups of four k-steps][lane][4]; lane l supplies
+// forget, cell, output gate).  Pre-activations are kept multiplied by a power of two of their gate row (see seq_halves2):
+//   wx: W_ih for the product over input rows, fp32, times the rows' factors too, [gate tile][dp / 8 groups of four k-steps][lane][4]; lane l supplies
 //       column l % 32 of the tile (gate row tile * 32 + l % 32 in (unit, gate) order) and k = 2 * step + l / 32;
-//   wq: W_hh for the recurrent product, two fp16 pieces, [gate tile][ks steps of 16][piece][lane][8]; lane l supplies row
+//   wq: W_hh for the recurrent product times the rows' factors, two fp16 pieces, [gate tile][ks steps of 16][piece][lane][8]; lane l supplies row
 //       l % 32 of the tile, k = 16 * step + 8 * (l / 32) + 0..7.  Row 8 m + 4 p + gate of a tile is that gate of hidden unit
 //       8 * tile + 4 p + m, so that lane l of the product ends up with all gates of four CONSECUTIVE units;
-//   bp: the bias in (unit, gate) order; behind it, per unit, -log2(e) over the unit's factor: what turns a pre-activation into the exponent of its gate function.
+//   bp: in (unit, gate) order, the bias times the factor; what turns a pre-activation into the exponent of its gate function, -log2(e) over the row's factor, twice that for the cell gate,
+//       whose tanh is a function of 2 z.
 // One workgroup per unit.  The "state is written" counters of the pass start at zero, and a_v of the nodes with an empty list is zero (final_state NULL: there are none).
 __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
                                                       const float *__restrict__ b, float *__restrict__ wx,
                                                       uint16_t *__restrict__ wq, float *__restrict__ bp, int d, int dp,
                                                       int hidden, int ks, int32_t *__restrict__ flags, int64_t n_flags,
                                                       const int32_t *__restrict__ final_state, float *__restrict__ a_out, int64_t n) {
-    __shared__ float largest[4];
     const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
     for (int64_t f = first; f < n_flags; f += stride) flags[f] = 0;
     if (final_state) {                                     // 64 nodes per wavefront, as in seq_output_kernel
@@ -131,19 +131,15 @@ __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__
     const int unit = blockIdx.x, gate = threadIdx.x >> 6, lane = threadIdx.x & 63;   // a wavefront per gate row
     if (unit >= hidden) return;
     const float *row = w_hh + (size_t)(gate * hidden + unit) * hidden;
-    const float twice = gate == 2 ? 2.f : 1.f;
     float v[2];                                            // (hidden is 128 at most)
 #pragma unroll
-    for (int i = 0; i < 2; ++i) v[i] = lane + 64 * i < hidden ? row[lane + 64 * i] * twice : 0.f;
+    for (int i = 0; i < 2; ++i) v[i] = lane + 64 * i < hidden ? row[lane + 64 * i] : 0.f;
     float most = fmaxf(fabsf(v[0]), fabsf(v[1]));
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off));
-    if (lane == 0) largest[gate] = most;
-    __syncthreads();
-    most = fmaxf(fmaxf(largest[0], largest[1]), fmaxf(largest[2], largest[3]));
     // (smaller weights than 2^-4 are not brought up all the way: what they lose is 2^-37, and the input half keeps clear of fp32's end)
     const int up = most < INFINITY ? min(9 - __builtin_amdgcn_frexp_expf(most), 12) : 0;
-    const float by = __builtin_ldexpf(1.f, up), with_h = twice * by * kSeqHScale;
+    const float by = __builtin_ldexpf(1.f, up);
     const int r = 4 * unit + gate, tile = unit >> 3, in_tile = 8 * (unit & 3) + 4 * ((unit >> 2) & 1) + gate;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -155,18 +151,19 @@ __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__
         out[0] = (uint16_t)(p[0] & 0xffffu);
         out[512] = (uint16_t)(p[1] & 0xffffu);
     }
+    const float with_h = __builtin_ldexpf(1.f, up + kSeqHScaleExp);
     for (int k = lane; k < dp; k += 64) {
         const float w = k < d ? w_ih[(size_t)(gate * hidden + unit) * d + k] * with_h : 0.f;
         wx[(size_t)(r >> 5) * 32 * dp + (k >> 3) * 256 + ((r & 31) + 32 * (k & 1)) * 4 + ((k >> 1) & 3)] = w;
     }
     if (lane == 0) {
         bp[r] = b[gate * hidden + unit] * with_h;
-        if (gate == 0) bp[4 * hidden + unit] = -1.44269504f / (by * kSeqHScale);
+        bp[4 * hidden + r] = __builtin_ldexpf(gate == 2 ? -2.f * 1.44269504f : -1.44269504f, -up - kSeqHScaleExp);
     }
 }
 
 // The input half of the gates, once per node that occurs in a list instead of once per cell that reads it:
-//     gx[i] = b + W_ih x[used[i]]   ([n_used, 4H], (unit, gate) order),
+//     gx[i] = (b + W_ih x[used[i]]) times the row's factor   ([n_used, 4H], (unit, gate) order),
 // 64 nodes per workgroup against all gate rows, fp32 matrix-core products, nodes as rows so that a store instruction writes
 // 128 contiguous bytes of two rows.  On the lists of the benchmark every row serves 6 to 16 cells; the sums start from the
 // bias and take the columns in order, as a product over (x, h) in one piece would.
@@ -249,7 +246,7 @@ struct SeqChainArgs {
     const int32_t *step_out; // per step: state row to write, or -1
     const float *gx;         // the input half of the gates, [n_used, 4H] in (unit, gate) order
     const uint16_t *wq;      // W_hh in fp16 pieces, see seq_pack_kernel
-    const float *unscale;    // per unit, see seq_pack_kernel
+    const float *unscale;    // per gate row in (unit, gate) order, see seq_pack_kernel
     float *h, *c;            // [n_states, H]: read where a path starts (written by a lower level), written where a step says so
     float *a_out;            // [n, H]
     float *tape_g, *tape_c, *tape_h;   // training: per step the activated gates [H][4], the new c [H] and the new h [H] (NULL: inference)
@@ -351,6 +348,7 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
     __shared__ __align__(16) float cs[C_LDS ? kSeqJobs : 1][HMAX + 4];
     __shared__ int32_t sdesc[kSeqJobs * 4];
     __shared__ int32_t spend[2][kSeqJobs];                 // per path: the state row that a step wrote, to be announced a step later
+    __shared__ float4 sby[BIG ? HMAX : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
     const int hidden = A.hidden, n_tiles = hidden / 8, ks = BIG ? (hidden + 15) / 16 : KS;
     const int tile = WIDE ? wave : (wave & 3), group0 = WIDE ? 0 : (wave >> 2);
@@ -358,9 +356,14 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
     constexpr int KR = BIG ? 4 : KS;                       // steps of 16 columns whose weights stay in registers (above 64 units there are five at least)
     seq_h8_t wreg[KR][2];
     const seq_h8_t *wl = reinterpret_cast<const seq_h8_t *>(A.wq) + (size_t)tile * ks * 2 * 64 + lane;
-    const float4 by4 = on ? *reinterpret_cast<const float4 *>(A.unscale + tile * 8 + half * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float by[4] = {by4.x, by4.y, by4.z, by4.w};
+    // what turns a lane's pre-activations into exponents, per unit (input, forget, cell, output gate): in registers where there are enough
+    float4 by_reg[BIG ? 1 : 4];
+    if constexpr (BIG) { if ((int)threadIdx.x < hidden) sby[threadIdx.x] = reinterpret_cast<const float4 *>(A.unscale)[threadIdx.x]; }   // (read behind the barriers of a tile)
     if (on) {
+        if constexpr (!BIG) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) by_reg[m] = reinterpret_cast<const float4 *>(A.unscale)[tile * 8 + half * 4 + m];
+        }
 #pragma unroll
         for (int s = 0; s < KR; ++s)
 #pragma unroll
@@ -526,13 +529,16 @@ __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(
                         float h[4], c[4] = {cv.x, cv.y, cv.z, cv.w};
 #pragma unroll
                         for (int m = 0; m < 4; ++m) {
-                            const float gf = seq_sigmoid(acc[g][4 * m + 1], by[m]);
+                            float4 by;
+                            if constexpr (BIG) by = sby[unit0 + m];
+                            else by = by_reg[m];
+                            const float gf = seq_sigmoid(acc[g][4 * m + 1], by.y);
                             if constexpr (HMAX == 64) {
                                 // sigmoid times tanh with one reciprocal of both denominators: the reciprocal is a quarter of a gate function's time
-                                c[m] = fmaf(gf, c[m], seq_sigmoid_tanh(acc[g][4 * m], by[m], acc[g][4 * m + 2], by[m]));   // (spelled out: one rounding, the same in every copy of this code)
-                                h[m] = seq_sigmoid_tanh(acc[g][4 * m + 3], by[m], c[m], -2.f * 1.44269504f);
+                                c[m] = fmaf(gf, c[m], seq_sigmoid_tanh(acc[g][4 * m], by.x, acc[g][4 * m + 2], by.z));   // (spelled out: one rounding, the same in every copy of this code)
+                                h[m] = seq_sigmoid_tanh(acc[g][4 * m + 3], by.w, c[m], -2.f * 1.44269504f);
                             } else {
-                                const float gi = seq_sigmoid(acc[g][4 * m], by[m]), gg = seq_tanh(acc[g][4 * m + 2], by[m]), go = seq_sigmoid(acc[g][4 * m + 3], by[m]);
+                                const float gi = seq_sigmoid(acc[g][4 * m], by.x), gg = seq_tanh(acc[g][4 * m + 2], by.z), go = seq_sigmoid(acc[g][4 * m + 3], by.w);
                                 c[m] = fmaf(gf, c[m], gi * gg);
                                 h[m] = go * seq_tanh(c[m]);
                                 if constexpr (GATES) { acc[g][4 * m] = gi; acc[g][4 * m + 1] = gf; acc[g][4 * m + 2] = gg; acc[g][4 * m + 3] = go; }
@@ -963,7 +969,8 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
     __shared__ __align__(16) float cs[2][RJ][RS];          // the c that a step began with: of this step and of the next one
     __shared__ float4 gates[8][4][64];                     // of the next step, as the lanes hold them
     __shared__ int32_t skeep[2][RJ];                       // the state row that a step wrote, or -1
-    __shared__ __align__(16) float sun[HMAX], sby[HMAX];   // the units' factors: of the product here, of the forward pass's pre-activations
+    __shared__ __align__(16) float sun[HMAX];              // the units' factors
+    __shared__ float4 sby[HMAX];                           // the factors of the forward pass's pre-activations, per unit those of its gates
     __shared__ int32_t sdesc_of[2][4][RJ];                 // of a path: start state, first step, steps, node; of this half tile and of the next one
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), worker = wave & 7;
     const bool ahead = wave >= 8;
@@ -976,7 +983,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                                      : reinterpret_cast<const seq_h8_t *>(A.wqt) + ((size_t)tile * MT * 4 + k) * 64;
         wr[k] = on ? from[threadIdx.x & 63] : seq_h8_t{};
     }
-    if ((int)threadIdx.x < hidden) { sun[threadIdx.x] = A.wqt_unscale[threadIdx.x]; sby[threadIdx.x] = A.unscale[threadIdx.x]; }   // (read behind the barriers of a tile)
+    if ((int)threadIdx.x < hidden) { sun[threadIdx.x] = A.wqt_unscale[threadIdx.x]; sby[threadIdx.x] = reinterpret_cast<const float4 *>(A.unscale)[threadIdx.x]; }   // (read behind the barriers of a tile)
     for (int i = threadIdx.x; i < (int)(sizeof(z) / 4); i += 1024) reinterpret_cast<uint32_t *>(&z[0][0][0][0])[i] = 0;   // columns from `hidden` on stay zero
     if (threadIdx.x < RJ * (NT + 4)) (&sfac[0][0])[threadIdx.x] = 0.f;
     const int64_t n_parts = A.n_path_tiles * (kSeqJobs / RJ);
@@ -1063,13 +1070,13 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
         };
         auto put_gates = [&] {
             const int l = seq_opaque(threadIdx.x) & 63;
-            const float4 by4 = *reinterpret_cast<const float4 *>(&sby[tile * 8 + (l >> 5) * 4]);
-            const float by[4] = {by4.x, by4.y, by4.z, by4.w};
             seq_from_pieces(gx);
 #pragma unroll
-            for (int m = 0; m < 4; ++m)
-                gates[worker][m][l] = make_float4(seq_sigmoid(pre[4 * m] + gx[4 * m], by[m]), seq_sigmoid(pre[4 * m + 1] + gx[4 * m + 1], by[m]),
-                                                  seq_tanh(pre[4 * m + 2] + gx[4 * m + 2], by[m]), seq_sigmoid(pre[4 * m + 3] + gx[4 * m + 3], by[m]));   // i, f, g, o
+            for (int m = 0; m < 4; ++m) {
+                const float4 by = sby[tile * 8 + (l >> 5) * 4 + m];
+                gates[worker][m][l] = make_float4(seq_sigmoid(pre[4 * m] + gx[4 * m], by.x), seq_sigmoid(pre[4 * m + 1] + gx[4 * m + 1], by.y),
+                                                  seq_tanh(pre[4 * m + 2] + gx[4 * m + 2], by.z), seq_sigmoid(pre[4 * m + 3] + gx[4 * m + 3], by.w));   // i, f, g, o
+            }
         };
         load_row(sdesc[2][0] - 1);
         load_begun(sdesc[2][0] - 1);
@@ -2209,7 +2216,7 @@ static SeqLayout seq_layout(const hag_seq_t *h, int64_t d, int64_t hidden) {
     size_t at = 0;
     L.wx = at; at += up(4 * H * (size_t)L.dp * f);
     L.wq = at; at += up((H / 8) * (size_t)L.ks * 2 * 512 * sizeof(uint16_t));
-    L.bp = at; at += up(5 * H * f);
+    L.bp = at; at += up(8 * H * f);
     L.h = at; at += up(states * H * f);
     L.c = at; at += up(states * H * f);
     L.flags = at; at += up(states * sizeof(int32_t));

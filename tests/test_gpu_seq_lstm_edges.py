@@ -147,3 +147,22 @@ def test_gradients_of_very_different_sizes(B, d, hidden):
             # norm-wise, the bar of the other gradient tests
             assert np.linalg.norm(got.cpu().numpy() - ref) <= 2e-5 * np.linalg.norm(ref)
         h.check()
+
+
+@pytest.mark.parametrize("d,hidden", [(8, 8), (16, 32), (16, 40), (20, 64), (12, 72), (12, 120)])
+def test_gates_of_very_different_weights(B, d, hidden):
+    # Every gate row has a factor of its own: forget gates that stay open (f = 1) with weights a million times those of the other gates leave the others all their bits.
+    n = 150
+    rowptr, col = lists(n, hidden)
+    rng = np.random.default_rng(d)
+    x, w_ih, w_hh, b = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden)
+    w_hh[hidden:2 * hidden] *= 1e6
+    b[hidden:2 * hidden] = 1e9
+    want, _ = lstm.naive_aggregate(rowptr, col, *(a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b)))
+    for cap in (0, int(col.size)):
+        h = B.SeqHag(rowptr, col, cap).upload()
+        got = h.lstm_forward(dev(x), dev(w_ih), dev(w_hh), dev(b))
+        # six cells at most, each adding i g (an error of about 3e-7: two gate functions and pre-activations of size 3) to c; |h| changes by less than c
+        assert np.abs(got.cpu().numpy() - want).max() <= 2e-6
+        a, _ = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
+        assert torch.equal(a, got)

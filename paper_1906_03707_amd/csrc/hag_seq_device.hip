@@ -91,11 +91,13 @@ __device__ __forceinline__ void seq_split2(float a, float b, uint32_t (&p)[3]) {
 
 // The operands of the recurrent product in the forward pass as two fp16 numbers each, 11 + 11 significant bits: what is cut off is 2^-23 of a number at
 // most, 2^-25 on average and of either sign, about what one fp32 addition rounds, and a product needs three matrix instructions
-// instead of six.  Both operands fit fp16's range because both are bounded: |h| < 1 is multiplied by 2^8 and the weights of a gate row by the power of two
-// that brings the largest to [2^8, 2^9), so what the second piece of a small number rounds off (2^-25, the subnormal numbers of fp16) is
-// 2^-33 of the largest; the factors stay that small so that pre-activations have the range of fp32 but for six powers of ten.
-constexpr float kSeqHScale = 256.f;
-constexpr int kSeqHScaleExp = 8;
+// instead of six.  Both operands fit fp16's range because both are bounded: |h| <= 1 is multiplied by 2^15 and the weights of a gate row by the power of two
+// that brings the largest to [2^14, 2^15), so what the second piece of a small number rounds off (2^-25, the subnormal numbers of fp16) is
+// 2^-40 of that.  A smaller h or weight than 2^-17 of the largest loses bits, which the others hide: the gate functions leave errors of a few 2^-25 in h, and the row's
+// largest weight hands them on.
+constexpr float kSeqHScale = 32768.f;
+constexpr int kSeqHScaleExp = 15;
+constexpr float kSeqXMost = 0x1p60f;   // see seq_input_gates_kernel
 __device__ __forceinline__ void seq_halves2(float a, float b, uint32_t (&p)[2]) {   // two numbers, packed as the low and the high half of each word
 #pragma clang fp contract(off)
     const seq_f2_t v = {a, b};
@@ -113,7 +115,7 @@ __device__ __forceinline__ void seq_halves2(float a, float b, uint32_t (&p)[2]) 
 //       l % 32 of the tile, k = 16 * step + 8 * (l / 32) + 0..7.  Row 8 m + 4 p + gate of a tile is that gate of hidden unit
 //       8 * tile + 4 p + m, so that lane l of the product ends up with all gates of four CONSECUTIVE units;
 //   bp: in (unit, gate) order, the bias times the factor; what turns a pre-activation into the exponent of its gate function, -log2(e) over the row's factor, twice that for the cell gate,
-//       whose tanh is a function of 2 z.
+//       whose tanh is a function of 2 z; the factor itself, negative where the row is too large to be multiplied: W_ih and the bias then stay as they are.
 // One workgroup per unit.  The "state is written" counters of the pass start at zero, and a_v of the nodes with an empty list is zero (final_state NULL: there are none).
 __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
                                                       const float *__restrict__ b, float *__restrict__ wx,
@@ -137,8 +139,8 @@ __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__
     float most = fmaxf(fabsf(v[0]), fabsf(v[1]));
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off));
-    // (smaller weights than 2^-4 are not brought up all the way: what they lose is 2^-37, and the input half keeps clear of fp32's end)
-    const int up = most < INFINITY ? min(9 - __builtin_amdgcn_frexp_expf(most), 12) : 0;
+    // (weights below 2^-26 are not brought up all the way: what they lose is 2^-66, and pre-activations up to 2^72 have a place in fp32)
+    const int up = most < INFINITY ? min(15 - __builtin_amdgcn_frexp_expf(most), 40) : 0;
     const float by = __builtin_ldexpf(1.f, up);
     const int r = 4 * unit + gate, tile = unit >> 3, in_tile = 8 * (unit & 3) + 4 * ((unit >> 2) & 1) + gate;
 #pragma unroll
@@ -151,14 +153,21 @@ __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__
         out[0] = (uint16_t)(p[0] & 0xffffu);
         out[512] = (uint16_t)(p[1] & 0xffffu);
     }
-    const float with_h = __builtin_ldexpf(1.f, up + kSeqHScaleExp);
-    for (int k = lane; k < dp; k += 64) {
-        const float w = k < d ? w_ih[(size_t)(gate * hidden + unit) * d + k] * with_h : 0.f;
-        wx[(size_t)(r >> 5) * 32 * dp + (k >> 3) * 256 + ((r & 31) + 32 * (k & 1)) * 4 + ((k >> 1) & 3)] = w;
-    }
+    // a row of usual size leaves the sums of seq_input_gates_kernel within 2^126 for features below kSeqXMost
+    const float *row_x = w_ih + (size_t)(gate * hidden + unit) * d;
+    float all = lane == 0 ? fabsf(b[gate * hidden + unit]) : 0.f;
+    for (int k = lane; k < d; k += 64) all += fabsf(row_x[k]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) all += __shfl_xor(all, off);
+    const float factor = __builtin_ldexpf(1.f, up + kSeqHScaleExp);
+    const bool large = !(all * factor < 0x1p126f / kSeqXMost);
+    const float with_h = large ? 1.f : factor;
+    for (int k = lane; k < dp; k += 64)
+        wx[(size_t)(r >> 5) * 32 * dp + (k >> 3) * 256 + ((r & 31) + 32 * (k & 1)) * 4 + ((k >> 1) & 3)] = k < d ? row_x[k] * with_h : 0.f;
     if (lane == 0) {
         bp[r] = b[gate * hidden + unit] * with_h;
         bp[4 * hidden + r] = __builtin_ldexpf(gate == 2 ? -2.f * 1.44269504f : -1.44269504f, -up - kSeqHScaleExp);
+        bp[8 * hidden + r] = large ? -factor : factor;
     }
 }
 
@@ -167,46 +176,71 @@ __global__ __launch_bounds__(256) void seq_pack_kernel(const float *__restrict__
 // 64 nodes per workgroup against all gate rows, fp32 matrix-core products, nodes as rows so that a store instruction writes
 // 128 contiguous bytes of two rows.  On the lists of the benchmark every row serves 6 to 16 cells; the sums start from the
 // bias and take the columns in order, as a product over (x, h) in one piece would.
-__global__ __launch_bounds__(256) void seq_input_gates_kernel(const float *__restrict__ x, const int32_t *__restrict__ used, int64_t n_used,
+// Features above kSeqXMost and rows marked by seq_pack_kernel would overflow with the factor in the weights (two terms of opposite signs then make NaN): their sums are
+// taken without it, in all of fp32's range, and multiplied afterwards.  What that would bring beyond 2^127 stays there, where the gate functions have long reached their
+// limits (it is 2^72 without the factor) and the recurrent half, 2^37 at most, does not count.
+template <bool LARGE>
+__device__ __forceinline__ void seq_input_gates_tile(const float *xl, const float4 *wq, int zs, int dp, float bias, float factor, seq_acc_t (&acc)[2]) {
+    const float down = LARGE && factor > 0.f ? 1.f / factor : 1.f;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[g][r] = LARGE ? bias * down : bias;
+    float4 wa = wq[0];
+    for (int q = 0; q < dp / 8; ++q) {
+        const float4 wn = wq[(q + 1 < dp / 8 ? q + 1 : q) * 64];
+        const float w4[4] = {wa.x, wa.y, wa.z, wa.w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+                acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(xl[g * 32 * zs + 2 * (4 * q + r)], LARGE ? w4[r] * down : w4[r], acc[g], 0, 0, 0);
+        wa = wn;
+    }
+    if constexpr (LARGE) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float z = acc[g][r] * fabsf(factor);
+                acc[g][r] = fabsf(z) > 0x1p127f ? copysignf(0x1p127f, z) : z;   // (NaN stays)
+            }
+    }
+}
+__global__ __launch_bounds__(256, 3) void seq_input_gates_kernel(const float *__restrict__ x, const int32_t *__restrict__ used, int64_t n_used,
                                                              const float *__restrict__ wx, const float *__restrict__ bp,
                                                              float *__restrict__ gx, int d, int dp, int hidden) {
     extern __shared__ float xs[];                          // [64][dp + 2]: rows 2 banks apart
+    __shared__ int32_t large_at;                           // the last block of nodes with a large feature
     const int zs = dp + 2, n_tiles = hidden / 8, rows4 = 4 * hidden;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t blocks = (n_used + 63) / 64;
+    if (threadIdx.x == 0) large_at = -1;
+    __syncthreads();
     for (int64_t bt = blockIdx.x; bt < blocks; bt += gridDim.x) {
         {
             const int row = threadIdx.x >> 2;
             const int64_t at = bt * 64 + row;
             const int u = at < n_used ? used[at] : -1;
+            float most = 0.f;
             for (int k = (threadIdx.x & 3) * 4; k < dp; k += 16) {
                 float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (u >= 0 && k < d) v = *reinterpret_cast<const float4 *>(x + (size_t)u * d + k);
                 *reinterpret_cast<float2 *>(&xs[row * zs + k]) = make_float2(v.x, v.y);
                 *reinterpret_cast<float2 *>(&xs[row * zs + k + 2]) = make_float2(v.z, v.w);
+                most = fmaxf(fmaxf(most, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
             }
+            if (most > kSeqXMost) large_at = (int32_t)bt;
         }
         __syncthreads();
+        const bool large = large_at == (int32_t)bt;
         for (int tile = wave; tile < n_tiles; tile += 4) {
-            const float bias = bp[tile * 32 + (lane & 31)];
+            const float bias = bp[tile * 32 + (lane & 31)], factor = bp[8 * hidden + tile * 32 + (lane & 31)];
             seq_acc_t acc[2];
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[g][r] = bias;
             const float4 *wq = reinterpret_cast<const float4 *>(wx) + (size_t)tile * (dp / 8) * 64 + lane;
             const float *xl = &xs[(lane & 31) * zs + (lane >> 5)];
-            float4 wa = wq[0];
-            for (int q = 0; q < dp / 8; ++q) {
-                const float4 wn = wq[(q + 1 < dp / 8 ? q + 1 : q) * 64];
-                const float w4[4] = {wa.x, wa.y, wa.z, wa.w};
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int g = 0; g < 2; ++g)
-                        acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(xl[g * 32 * zs + 2 * (4 * q + r)], w4[r], acc[g], 0, 0, 0);
-                wa = wn;
-            }
+            if (large || __any(factor < 0.f)) seq_input_gates_tile<true>(xl, wq, zs, dp, bias, factor, acc);
+            else seq_input_gates_tile<false>(xl, wq, zs, dp, bias, factor, acc);
 #pragma unroll
             for (int g = 0; g < 2; ++g)
 #pragma unroll
@@ -2216,7 +2250,7 @@ static SeqLayout seq_layout(const hag_seq_t *h, int64_t d, int64_t hidden) {
     size_t at = 0;
     L.wx = at; at += up(4 * H * (size_t)L.dp * f);
     L.wq = at; at += up((H / 8) * (size_t)L.ks * 2 * 512 * sizeof(uint16_t));
-    L.bp = at; at += up(8 * H * f);
+    L.bp = at; at += up(12 * H * f);
     L.h = at; at += up(states * H * f);
     L.c = at; at += up(states * H * f);
     L.flags = at; at += up(states * sizeof(int32_t));

@@ -166,3 +166,21 @@ def test_gates_of_very_different_weights(B, d, hidden):
         assert np.abs(got.cpu().numpy() - want).max() <= 2e-6
         a, _ = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
         assert torch.equal(a, got)
+
+
+@pytest.mark.parametrize("d,hidden", [(8, 8), (16, 40), (12, 120)])
+def test_pre_activations_have_the_range_of_fp32(B, d, hidden):
+    # features of 1e36 whose terms have opposite signs, rows of large weights in either matrix: finite sums that saturate the gates
+    n = 150
+    rowptr, col = lists(n, hidden)
+    rng = np.random.default_rng(d)
+    x, w_ih, w_hh, b = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden)
+    x[:40, 1], x[:40, 2] = 1e36, -1e36
+    w_ih[3, 3:] *= 1e34
+    w_hh[hidden + 5] *= 1e36
+    with np.errstate(over="ignore"):
+        want, _ = lstm.naive_aggregate(rowptr, col, *(a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b)))
+    assert np.isin(col, np.arange(40)).sum() > 30
+    for cap in (0, int(col.size)):
+        h = B.SeqHag(rowptr, col, cap).upload()
+        assert np.abs(h.lstm_forward(dev(x), dev(w_ih), dev(w_hh), dev(b)).cpu().numpy() - want).max() <= 1e-5

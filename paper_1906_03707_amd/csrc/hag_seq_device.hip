@@ -675,7 +675,7 @@ struct SeqRevArgs {
     int64_t n_path_tiles;
     const int32_t *step_out;
     const uint16_t *wqt;     // W_hh^T in fp16 pieces, in the order the matrix instructions consume it, see seq_backward_start_kernel
-    const float *wqt_unscale;   // per hidden unit, likewise
+    const int32_t *wqt_unscale; // per hidden unit, likewise
     float *tape_g;           // out: the gradients of every step's pre-activations; in, but for 40 to 64 units: its activated gates
     const float *tape_c, *tape_h;   // c' and h of every step
     const float *h_state, *c_state; // rows of the kept states
@@ -696,8 +696,6 @@ struct SeqRevArgs {
 };
 
 
-// The power of two that brings numbers of size `most` to [2^14, 2^15), as its exponent: as far up as fp16's range allows, so that what the second piece
-// of a number rounds off (2^-25 at least, see seq_halves2) is 2^-39 of the largest.  Infinities and NaN stay what they are.
 // the largest of sixteen lanes, in all of them
 __device__ __forceinline__ float seq_max16(float v) {
 #define HAG_SEQ_ROR(n) v = fmaxf(v, __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x120 + n, 0xf, 0xf, false)))
@@ -705,12 +703,18 @@ __device__ __forceinline__ float seq_max16(float v) {
 #undef HAG_SEQ_ROR
     return v;
 }
-__device__ __forceinline__ int seq_up(float most) { return most < INFINITY ? min(15 - __builtin_amdgcn_frexp_expf(most), 126) : 0; }
+// The power of two that brings numbers of size `most` to [2^14, 2^15), as its exponent: as far up as fp16's range allows, so that what the second piece
+// of a number rounds off (2^-25 at least, see seq_halves2) is 2^-39 of the largest.  Infinities and NaN stay what they are; beside an infinity the factor is 1 and numbers above 65504
+// become infinite too, in sums that are not finite anyway.
+__device__ __forceinline__ int seq_up(float most) { return most < INFINITY ? min(15 - __builtin_amdgcn_frexp_expf(most), 125) : 0; }
+// Sums of products of two such operands are put right in two steps, neither of which leaves fp32's range: by 2^(-kSeqBack - up) of the gradients' power, which is at
+// least 2^-149 and leaves up to 512 terms of the largest gradient's size, and by the exponent kSeqBack - up of the weights'.
+constexpr int kSeqBack = 24;
 
 // What the backward pass starts from, in one launch: cleared gradient rows of the kept states, cleared g_x where some node is in no list
 // (n_g_x > 0), the pending counts of a one-launch pass (n_states > 0) and the weights of the products, from the usual layout.
 //   wqt: W_hh^T in two fp16 pieces, the weights of an output unit (a column of W_hh) brought to a common size by a power of two (seq_up); unscale: per output
-//       unit 2^15 over that power, see seq_reverse_kernel;
+//       unit the exponent that undoes it, see kSeqBack;
 //     hidden <= 64: [gate tile][m_tiles of 32 hidden units][2 steps of 16][piece][lane][8]; lane l supplies output unit 32 * mt + l % 32, and as k
 //       value e = 8 * step + i = 4 m + gate the gate row of unit 8 * tile + 4 * (l / 32) + m: the order in which the lanes hold dG;
 //     hidden > 64: [m_tiles][4H / 16 steps][piece][lane][8]; lane l supplies unit 32 * mt + l % 32, k = 16 * step + 8 * (l / 32) + i the gate
@@ -719,7 +723,7 @@ __device__ __forceinline__ int seq_up(float most) { return most < INFINITY ? min
 //       k-step q the gate rows 2 q + l / 32.
 // The first 32 * m_tiles workgroups (there are at least as many) cut one column of W_hh each.
 __global__ __launch_bounds__(256) void seq_backward_start_kernel(const float *__restrict__ w_ih, const float *__restrict__ w_hh,
-                                                                uint16_t *__restrict__ wqt, float *__restrict__ unscale, float *__restrict__ wxt, int d, int hidden,
+                                                                uint16_t *__restrict__ wqt, int32_t *__restrict__ unscale, float *__restrict__ wxt, int d, int hidden,
                                                                 float *__restrict__ state_grads, int64_t n_state_grads, float *__restrict__ g_x,
                                                                 int64_t n_g_x, const int32_t *__restrict__ pending_init,
                                                                 int32_t *__restrict__ pending, int64_t n_states) {
@@ -749,7 +753,7 @@ __global__ __launch_bounds__(256) void seq_backward_start_kernel(const float *__
     __syncthreads();
     const int up = seq_up(fmaxf(fmaxf(largest[0], largest[1]), fmaxf(largest[2], largest[3])));
     const float by = __builtin_ldexpf(1.f, up);
-    if (threadIdx.x == 0 && z < hidden) unscale[z] = __builtin_ldexpf(1.f, 15 - up);
+    if (threadIdx.x == 0 && z < hidden) unscale[z] = kSeqBack - up;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int r = threadIdx.x + 256 * i;
@@ -810,7 +814,7 @@ constexpr int kSeqRevJobs = 32;   // paths per workgroup of the reverse kernels 
 __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A) {
     constexpr int HMAX = 32, NT = 4, RS = HMAX + 4, RJ = kSeqJobs;
     __shared__ __align__(16) float red[NT][RJ][RS];
-    __shared__ __align__(16) float sun[HMAX];              // the units' factors
+    __shared__ __align__(16) int32_t sun[HMAX];            // the units' exponents
     __shared__ int32_t sdesc[RJ * 4];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int hidden = A.hidden, n_tiles = hidden / 8, tile = wave & 3, group = wave >> 2;
@@ -859,8 +863,8 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A
                 const float by = w < n_tiles ? red[from][j][HMAX] : 0.f;
                 v.x = fmaf(q.x, by, v.x); v.y = fmaf(q.y, by, v.y); v.z = fmaf(q.z, by, v.z); v.w = fmaf(q.w, by, v.w);
             }
-            const float4 un4 = *reinterpret_cast<const float4 *>(&sun[unit0]);
-            dh[0] = v.x * un4.x; dh[1] = v.y * un4.y; dh[2] = v.z * un4.z; dh[3] = v.w * un4.w;
+            const int4 un4 = *reinterpret_cast<const int4 *>(&sun[unit0]);
+            dh[0] = __builtin_ldexpf(v.x, un4.x); dh[1] = __builtin_ldexpf(v.y, un4.y); dh[2] = __builtin_ldexpf(v.z, un4.z); dh[3] = __builtin_ldexpf(v.w, un4.w);
         };
         if (on) {
             const int lane = seq_opaque(threadIdx.x) & 63, unit0 = tile * 8 + (lane >> 5) * 4;
@@ -924,7 +928,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A
                 const seq_u2_t both = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
                 const int up = seq_up(fmaxf(__uint_as_float(both.x), __uint_as_float(both.y)));   // of the path's 32 gate rows
                 const float one = (tile + j + t) & 1 ? -1.f : 1.f, by = __builtin_ldexpf(one, up);
-                if (half == 0) red[tile][j][HMAX] = __builtin_ldexpf(one, -15 - up);
+                if (half == 0) red[tile][j][HMAX] = __builtin_ldexpf(one, -kSeqBack - up);
                 seq_h8_t zb[2][2];                         // [step][piece]
 #pragma unroll
                 for (int k = 0; k < 2; ++k) {
@@ -1003,7 +1007,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
     __shared__ __align__(16) float cs[2][RJ][RS];          // the c that a step began with: of this step and of the next one
     __shared__ float4 gates[8][4][64];                     // of the next step, as the lanes hold them
     __shared__ int32_t skeep[2][RJ];                       // the state row that a step wrote, or -1
-    __shared__ __align__(16) float sun[HMAX];              // the units' factors
+    __shared__ __align__(16) int32_t sun[HMAX];            // the units' exponents
     __shared__ float4 sby[HMAX];                           // the factors of the forward pass's pre-activations, per unit those of its gates
     __shared__ int32_t sdesc_of[2][4][RJ];                 // of a path: start state, first step, steps, node; of this half tile and of the next one
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), worker = wave & 7;
@@ -1195,8 +1199,8 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                     const float4 q = *reinterpret_cast<const float4 *>(&red[w < n_tiles ? w : 0][j][unit0]);   // (no branch, so that the reads go out together; what is not finite in tile 0 makes the sum so anyway)
                     v.x = fmaf(q.x, by[w], v.x); v.y = fmaf(q.y, by[w], v.y); v.z = fmaf(q.z, by[w], v.z); v.w = fmaf(q.w, by[w], v.w);
                 }
-                const float4 un4 = *reinterpret_cast<const float4 *>(&sun[unit0]);
-                dh[0] = v.x * un4.x; dh[1] = v.y * un4.y; dh[2] = v.z * un4.z; dh[3] = v.w * un4.w;
+                const int4 un4 = *reinterpret_cast<const int4 *>(&sun[unit0]);
+                dh[0] = __builtin_ldexpf(v.x, un4.x); dh[1] = __builtin_ldexpf(v.y, un4.y); dh[2] = __builtin_ldexpf(v.z, un4.z); dh[3] = __builtin_ldexpf(v.w, un4.w);
             };
             float4 c_now = make_float4(0.f, 0.f, 0.f, 0.f);
             if (on) {
@@ -1267,7 +1271,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                     const seq_u2_t both = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
                     const int up = seq_up(fmaxf(__uint_as_float(both.x), __uint_as_float(both.y)));   // of the path's 32 gate rows
                     const float one = (tile + j + t) & 1 ? -1.f : 1.f, by = __builtin_ldexpf(one, up);
-                        if (half == 0) sfac[j][tile] = __builtin_ldexpf(one, -15 - up);
+                    if (half == 0) sfac[j][tile] = __builtin_ldexpf(one, -kSeqBack - up);
                     seq_h8_t zb[2][2];                     // [step][piece]
 #pragma unroll
                     for (int k = 0; k < 2; ++k) {
@@ -1324,7 +1328,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
     // per path: the pre-activation gradients of the current step in fp16 pieces (the product's operand), then, in the row of the first pieces, the two parts
     // of the product's result dh_prev; the running dh and dc themselves stay in the registers of the path's sixteen threads
     __shared__ __align__(16) uint16_t z[2][kSeqRevJobs][ZS];
-    __shared__ float sun[128];                             // the units' factors
+    __shared__ int32_t sun[128];                           // the units' exponents
     auto row_of = [&](int j) { return reinterpret_cast<float *>(&z[0][j][0]); };   // 256 floats (and four of padding)
     __shared__ int32_t sdesc[kSeqRevJobs * 4];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1388,7 +1392,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                 for (int it = 0; it < IT; ++it) {
                     const int u = TP * it + part;
                     const float sum = row_of(sj)[u] + row_of(sj)[128 + u];
-                    dhv[it] = t + 1 < len && u < hidden ? sum * back * sun[u] : sum;   // (before the first step: g_a as it is)
+                    dhv[it] = t + 1 < len && u < hidden ? __builtin_ldexpf(sum * back, sun[u]) : sum;   // (before the first step: g_a as it is)
                 }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
@@ -1424,7 +1428,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                 most = seq_max16(most);                    // of the path's gate rows
                 const int up = seq_up(most);
                 const float one = (sj + t) & 1 ? -1.f : 1.f, by = __builtin_ldexpf(one, up);
-                back = __builtin_ldexpf(one, -15 - up);
+                back = __builtin_ldexpf(one, -kSeqBack - up);
 #pragma unroll
                 for (int it = 0; it < IT; ++it) {
                     const int u = TP * it + part;
@@ -1505,7 +1509,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                 if (from < 0) continue;
                 const float *dh = row_of(j), *dc = reinterpret_cast<const float *>(&z[1][j][0]);
                 for (int u = lane; u < hidden; u += 64) {
-                    __hip_atomic_fetch_add(A.gh + (size_t)from * hidden + u, (dh[u] + dh[128 + u]) * dh[256] * sun[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(A.gh + (size_t)from * hidden + u, __builtin_ldexpf((dh[u] + dh[128 + u]) * dh[256], sun[u]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     __hip_atomic_fetch_add(A.gc + (size_t)from * hidden + u, dc[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
@@ -2394,8 +2398,9 @@ int hag_seq_lstm_backward(const hag_seq_t *h, int64_t d, int64_t hidden, const f
     const SeqLayout F = seq_layout(h, d, hidden);           // the forward pass left its state rows there
     const float *hst = (const float *)(w + F.h), *cst = (const float *)(w + F.c);
     float *tape_g = (float *)(w + L.tape_g), *tape_c = (float *)(w + L.tape_c), *tape_h = (float *)(w + L.tape_h);
-    float *gh = (float *)(w + L.gh), *gc = (float *)(w + L.gc), *unscale = (float *)(w + L.unscale), *wxt = (float *)(w + L.wxt), *sums = (float *)(w + L.s);
+    float *gh = (float *)(w + L.gh), *gc = (float *)(w + L.gc), *wxt = (float *)(w + L.wxt), *sums = (float *)(w + L.s);
     uint16_t *wqt = (uint16_t *)(w + L.wqt);
+    int32_t *unscale = (int32_t *)(w + L.unscale);
     const int64_t cells = (int64_t)h->step_x.size(), n_used = (int64_t)h->used.size();
     auto blocks = [](int64_t total) { return dim3((unsigned)std::min<int64_t>((total + 255) / 256, 65535 * 16)); };
     const int64_t levels = (int64_t)h->tile_ptr.size() - 1;

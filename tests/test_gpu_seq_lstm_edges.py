@@ -184,3 +184,23 @@ def test_pre_activations_have_the_range_of_fp32(B, d, hidden):
     for cap in (0, int(col.size)):
         h = B.SeqHag(rowptr, col, cap).upload()
         assert np.abs(h.lstm_forward(dev(x), dev(w_ih), dev(w_hh), dev(b)).cpu().numpy() - want).max() <= 1e-5
+
+
+@pytest.mark.parametrize("d,hidden", [(8, 8), (16, 40), (12, 120)])
+def test_weights_and_gradients_near_the_ends_of_fp32(B, d, hidden):
+    # a column of weights that saturates the gates (3e38) under gradients of 1e-20, and gradients of 2^122
+    n = 150
+    rowptr, col = lists(n, hidden)
+    rng = np.random.default_rng(d)
+    x, w_ih, w_hh, b, g = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden), rng.normal(0, 1, (n, hidden))
+    large = w_hh.copy()
+    large[:, 0] = 0
+    large[:hidden // 2, 0] = 3e38
+    h = B.SeqHag(rowptr, col, 0).upload()
+    for w, scale in ((large, 1e-20), (w_hh, 2.0 ** 122)):
+        with np.errstate(over="ignore"):
+            want = lstm.naive_aggregate_backward(rowptr, col, *(a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w, b, g * scale)))
+        _, ws = h.lstm_forward_train(dev(x), dev(w_ih), dev(w), dev(b))
+        for got, ref in zip(h.lstm_backward(dev(x), dev(w_ih), dev(w), dev(g * scale), ws), want):
+            size = np.abs(ref).max()
+            assert np.linalg.norm(got.cpu().numpy() / size - ref / size) <= 2e-5 * np.linalg.norm(ref / size)

@@ -107,6 +107,18 @@ __device__ __forceinline__ void seq_halves2(float a, float b, uint32_t (&p)[2]) 
     p[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, seq_h2_t));
 }
 
+// The same where small numbers beside large ones count too, as in the backward pass: the second piece times 2^11, which makes it as large as the first one, so that of numbers
+// up to 2^15 it rounds off 2^-36 instead of 2^-25.  The products with a second piece are summed first and multiplied by 2^-11 before those of the first pieces join them.
+constexpr float kSeqLow = 2048.f;
+__device__ __forceinline__ void seq_halves2_low(float a, float b, uint32_t (&p)[2]) {
+#pragma clang fp contract(off)
+    const seq_f2_t v = {a, b};
+    const seq_h2_t hi = __builtin_convertvector(v, seq_h2_t);
+    const seq_f2_t r = {fmaf((float)hi.x, -kSeqLow, a * kSeqLow), fmaf((float)hi.y, -kSeqLow, b * kSeqLow)};   // exact
+    p[0] = __builtin_bit_cast(uint32_t, hi);
+    p[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, seq_h2_t));
+}
+
 // Weights in the forms the kernels read, from the usual layout (w_ih [4H, D], w_hh [4H, H], b [4H], gate-major rows: input,
 // forget, cell, output gate).  Pre-activations are kept multiplied by a power of two of their gate row (see seq_halves2):
 //   wx: W_ih for the product over input rows, fp32, times the rows' factors too, [gate tile][dp / 8 groups of four k-steps][lane][4]; lane l supplies
@@ -704,7 +716,7 @@ __device__ __forceinline__ float seq_max16(float v) {
     return v;
 }
 // The power of two that brings numbers of size `most` to [2^14, 2^15), as its exponent: as far up as fp16's range allows, so that what the second piece
-// of a number rounds off (2^-25 at least, see seq_halves2) is 2^-39 of the largest.  Infinities and NaN stay what they are; beside an infinity the factor is 1 and numbers above 65504
+// of a number rounds off (see seq_halves2_low) is 2^-51 of the largest.  Infinities and NaN stay what they are; beside an infinity the factor is 1 and numbers above 65504
 // become infinite too, in sums that are not finite anyway.
 __device__ __forceinline__ int seq_up(float most) { return most < INFINITY ? min(15 - __builtin_amdgcn_frexp_expf(most), 125) : 0; }
 // Sums of products of two such operands are put right in two steps, neither of which leaves fp32's range: by 2^(-kSeqBack - up) of the gradients' power, which is at
@@ -713,7 +725,7 @@ constexpr int kSeqBack = 24;
 
 // What the backward pass starts from, in one launch: cleared gradient rows of the kept states, cleared g_x where some node is in no list
 // (n_g_x > 0), the pending counts of a one-launch pass (n_states > 0) and the weights of the products, from the usual layout.
-//   wqt: W_hh^T in two fp16 pieces, the weights of an output unit (a column of W_hh) brought to a common size by a power of two (seq_up); unscale: per output
+//   wqt: W_hh^T in two fp16 pieces (seq_halves2_low), the weights of an output unit (a column of W_hh) brought to a common size by a power of two (seq_up); unscale: per output
 //       unit the exponent that undoes it, see kSeqBack;
 //     hidden <= 64: [gate tile][m_tiles of 32 hidden units][2 steps of 16][piece][lane][8]; lane l supplies output unit 32 * mt + l % 32, and as k
 //       value e = 8 * step + i = 4 m + gate the gate row of unit 8 * tile + 4 * (l / 32) + m: the order in which the lanes hold dG;
@@ -759,7 +771,7 @@ __global__ __launch_bounds__(256) void seq_backward_start_kernel(const float *__
         const int r = threadIdx.x + 256 * i;
         if (r >= rows) continue;
         uint32_t p[2];
-        seq_halves2(v[i] * by, 0.f, p);
+        seq_halves2_low(v[i] * by, 0.f, p);
         size_t at;
         if (hidden <= 64) {
             const int unit = r >> 2, e = 4 * (unit & 3) + (r & 3);
@@ -934,7 +946,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A
                 for (int k = 0; k < 2; ++k) {
                     uint32_t p[4][2];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) seq_halves2(dg[8 * k + 2 * i] * by, dg[8 * k + 2 * i + 1] * by, p[i]);
+                    for (int i = 0; i < 4; ++i) seq_halves2_low(dg[8 * k + 2 * i] * by, dg[8 * k + 2 * i + 1] * by, p[i]);
 #pragma unroll
                     for (int i = 0; i < 2; ++i) zb[k][i] = __builtin_bit_cast(seq_h8_t, make_uint4(p[0][i], p[1][i], p[2][i], p[3][i]));
                 }
@@ -946,6 +958,8 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[k][1], zb[k][0], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[k][0], zb[k][1], acc, 0, 0, 0);
                 }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] *= 1.f / kSeqLow;
 #pragma unroll
                 for (int k = 0; k < 2; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wt[k][0], zb[k][0], acc, 0, 0, 0);
 #pragma unroll
@@ -1277,7 +1291,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                     for (int k = 0; k < 2; ++k) {
                         uint32_t p[4][2];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) seq_halves2(dg[8 * k + 2 * i] * by, dg[8 * k + 2 * i + 1] * by, p[i]);
+                        for (int i = 0; i < 4; ++i) seq_halves2_low(dg[8 * k + 2 * i] * by, dg[8 * k + 2 * i + 1] * by, p[i]);
 #pragma unroll
                         for (int i = 0; i < 2; ++i) zb[k][i] = __builtin_bit_cast(seq_h8_t, make_uint4(p[0][i], p[1][i], p[2][i], p[3][i]));
                     }
@@ -1291,6 +1305,8 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
                             acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[(mt * 2 + k) * 2 + 1], zb[k][0], acc, 0, 0, 0);
                             acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[(mt * 2 + k) * 2], zb[k][1], acc, 0, 0, 0);
                         }
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[r] *= 1.f / kSeqLow;
 #pragma unroll
                         for (int k = 0; k < 2; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[(mt * 2 + k) * 2], zb[k][0], acc, 0, 0, 0);
 #pragma unroll
@@ -1434,8 +1450,8 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
                     const int u = TP * it + part;
                     if (u >= hidden) continue;
                     uint32_t a[2], b[2];
-                    seq_halves2(gates[it].x * by, gates[it].y * by, a);
-                    seq_halves2(gates[it].z * by, gates[it].w * by, b);
+                    seq_halves2_low(gates[it].x * by, gates[it].y * by, a);
+                    seq_halves2_low(gates[it].z * by, gates[it].w * by, b);
 #pragma unroll
                     for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2 *>(&z[p][sj][u * 4]) = make_uint2(a[p], b[p]);
                 }
@@ -1443,9 +1459,9 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
             __syncthreads();
             // dh_prev^T [units, paths] = W_hh^T . dG^T [4H, paths], the gate rows in two halves
             const int lane = seq_opaque(threadIdx.x) & 63;
-            seq_acc_t acc;
+            seq_acc_t acc, low;                            // low: the products with a second piece, 2^11 times as large
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[r] = low[r] = 0.f;
             const bool has_pair = wave < 2 * n_rt;
             const int rt = wave % n_rt, half = wave / n_rt;
             // The weights are requested four steps of sixteen gate rows ahead: a step is 96 cycles of products, an access of the L2 cache several hundred.
@@ -1458,13 +1474,10 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 #pragma unroll
                 for (int p = 0; p < 2; ++p) w[i][p] = wq[(s * 2 + p) * 64];
             };
-            auto step = [&](int i, int s) {
-                seq_h8_t zb[2];
-#pragma unroll
-                for (int p = 0; p < 2; ++p) zb[p] = *reinterpret_cast<const seq_h8_t *>(&z[p][lane & 31][16 * s + 8 * (lane >> 5)]);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][1], zb[0], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][0], zb[1], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][0], zb[0], acc, 0, 0, 0);
+            auto dg_piece = [&](int p, int s) { return *reinterpret_cast<const seq_h8_t *>(&z[p][lane & 31][16 * s + 8 * (lane >> 5)]); };
+            auto step_low = [&](int i, int s, const seq_h8_t &z0) {
+                low = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][1], z0, low, 0, 0, 0);
+                low = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][0], dg_piece(1, s), low, 0, 0, 0);
             };
             int s = s0;
             if (has_pair) {
@@ -1473,15 +1486,29 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 #pragma unroll 1
                 for (; s + AHEAD < s1; s += AHEAD) {
 #pragma unroll
-                    for (int i = 0; i < AHEAD; ++i) { step(i, s + i); load_w(i, s + AHEAD + i); __builtin_amdgcn_sched_barrier(0); }
+                    for (int i = 0; i < AHEAD; ++i) {
+                        const seq_h8_t z0 = dg_piece(0, s + i);
+                        step_low(i, s + i, z0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][0], z0, acc, 0, 0, 0);
+                        load_w(i, s + AHEAD + i);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
+                // (one accumulator from here on, and below one piece of the weights: the tape needs the registers)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) low[r] = fmaf(acc[r], kSeqLow, low[r]);
+#pragma unroll
+                for (int i = 0; i < AHEAD; ++i)
+                    if (s + i < s1) step_low(i, s + i, dg_piece(0, s + i));
+#pragma unroll
+                for (int r = 0; r < 16; ++r) low[r] *= 1.f / kSeqLow;
             }
             // (loads return in order: requested before the weights, the tape would be waited for with them)
             load_step(t - 1);
             if (has_pair) {
 #pragma unroll
                 for (int i = 0; i < AHEAD; ++i)
-                    if (s + i < s1) step(i, s + i);
+                    if (s + i < s1) low = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i][0], dg_piece(0, s + i), low, 0, 0, 0);
             }
             __syncthreads();                               // every product has read the staged gradients
             if (has_pair) {
@@ -1490,7 +1517,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int row = rt * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-                        if (row < hidden) row_of(j)[128 * half + row] = acc[r];
+                        if (row < hidden) row_of(j)[128 * half + row] = low[r];
                     }
                 }
             }

@@ -186,6 +186,28 @@ def test_pre_activations_have_the_range_of_fp32(B, d, hidden):
         assert np.abs(h.lstm_forward(dev(x), dev(w_ih), dev(w_hh), dev(b)).cpu().numpy() - want).max() <= 1e-5
 
 
+@pytest.mark.parametrize("d,hidden", [(8, 8), (16, 32), (16, 40), (20, 64), (12, 72), (8, 128)])
+def test_gradients_of_units_that_do_not_see_each_other(B, d, hidden):
+    # even units read even features and even units, odd ones the others, and the even ones' gradients are 2^26 times as large: the odd ones keep all their bits, although
+    # a path's gradients are brought into range together
+    n = 150
+    rowptr, col = lists(n, hidden)
+    rng = np.random.default_rng(d)
+    x, w_ih, w_hh, b, g = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden), rng.normal(0, 1, (n, hidden))
+    odd, odd_x = np.arange(hidden) % 2, np.arange(d) % 2
+    w_ih *= np.tile(odd[:, None] == odd_x[None, :], (4, 1))
+    w_hh *= np.tile(odd[:, None] == odd[None, :], (4, 1))
+    g *= np.where(odd, 1.0, 2.0 ** 26)
+    want = lstm.naive_aggregate_backward(rowptr, col, *(a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b, g)))
+    of_odd = ((slice(None), odd_x == 1), *[np.tile(odd == 1, 4)] * 3)
+    for cap in (0, int(col.size)):
+        h = B.SeqHag(rowptr, col, cap).upload()
+        _, ws = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
+        for got, ref, rows in zip(h.lstm_backward(dev(x), dev(w_ih), dev(w_hh), dev(g), ws), want, of_odd):
+            # gradients that see no larger ones beside them have errors of up to 6e-7 here
+            assert np.linalg.norm(got.cpu().numpy()[rows] - ref[rows]) <= 2e-6 * np.linalg.norm(ref[rows])
+
+
 @pytest.mark.parametrize("d,hidden", [(8, 8), (16, 40), (12, 120)])
 def test_weights_and_gradients_near_the_ends_of_fp32(B, d, hidden):
     # a column of weights that saturates the gates (3e38) under gradients of 1e-20, and gradients of 2^122

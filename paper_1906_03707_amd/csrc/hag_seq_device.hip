@@ -79,6 +79,9 @@ typedef unsigned int seq_u2_t __attribute__((ext_vector_type(2)));
 // of two such sums loses only the terms mid * lo, lo * mid and lo * lo, about 2^-26 of the product and of either sign
 // (round to nearest at every cut), which is below the rounding of the fp32 accumulator.  Two numbers at a time,
 // packed as the low and the high half of each word.
+// Numbers above kSeqSplitMost have no first piece, and those below 2^-109 no whole third one (bf16 ends at 2^-133): whoever cuts numbers without a
+// bound keeps to this range, the lower end for the largest of those that are added up.
+constexpr float kSeqSplitMost = 0x1.fep127f, kSeqSplitLeast = 0x1p-100f;
 __device__ __forceinline__ void seq_split2(float a, float b, uint32_t (&p)[3]) {
 #pragma clang fp contract(off)   // the pieces are those of the rounded number, however it was computed
 #pragma unroll
@@ -1562,8 +1565,9 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 // gradient adds hundreds of thousands of rows: the products of 32 rows therefore begin at zero and join the running sums in rounded additions.
 //   Over the cells (SEG): two fp16 pieces, three products.  h is bounded; the 32 numbers of a column of dG are brought into range by the power of two
 //     that their largest asks for, with a sign that alternates over columns and chunks (so that half of the products are cut upwards), undone in the addition.
-//   Over the nodes, whose features have no bound: three bf16 pieces, six products, the large ones apart from the small ones.  (Numbers below about
-//     2^-110 lose their last pieces.)  Infinities and NaN stay not finite in both.
+//   Over the nodes, whose features have no bound: three bf16 pieces, six products, the large ones apart from the small ones.  A chunk with numbers beyond bf16's
+//     range, or with a run of rows whose largest is so small that last pieces would be lost, takes fp32 products of the numbers as they are (kSeqSplitMost, kSeqSplitLeast).
+//   Infinities and NaN stay not finite in both.
 // 3.35 M cells of 64 units: 1.41 ms with fp32 matrix instructions, 1.07 with bf16 pieces (vector instructions issue 59 % of the time, matrix cores are busy 31 %),
 // 0.96 with fp16 (4.5 TB/s); 0.85 M cells of 128 units: 1.33, 0.97 and 0.75 ms.  Error of the training step's results against 64 bits 1.2e-6, 5e-7 and 4.2e-7, 6.4e-7, 5.1e-7 and 5e-7.
 //
@@ -1600,6 +1604,7 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
     constexpr int P = SEG ? 2 : 3;                         // pieces per operand: fp16 over the cells, bf16 over the nodes
     __shared__ uint4 sdg[P][256][CK / 8], sz[P][ZW][CK / 8];
     __shared__ __align__(16) float sback[SEG ? 256 : 4];   // SEG: what undoes the factors of a column of dG and of h
+    __shared__ int32_t far_chunk;                          // the last chunk whose numbers the pieces do not hold
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows4 = 4 * A.hidden, cols = A.cols;
     const int row0 = blockIdx.y * 256, n_rt = (rows4 - row0 < 256 ? rows4 - row0 : 256) / 32;
@@ -1624,6 +1629,8 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
     float rg[CK], rz[CPT];
     int32_t rs = -1, ig = 0, iz = 0;                       // of row lane % 32; rs: of row lane, one more than the chunk: where the last row's node ends
     uint32_t zero = 0;
+    if (tid == 0) far_chunk = -1;
+    __syncthreads();
     auto request_ids = [&](int64_t c0) {
         int64_t at = c0 + (lane & (CK - 1));
         at = at < last ? at : last - 1;
@@ -1671,6 +1678,14 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
             const float one = ((int)(c0 / CK) + tid) & 1 ? -1.f : 1.f;
             by = __builtin_ldexpf(one, up);
             sback[tid] = __builtin_ldexpf(one, -up) / kSeqHScale;
+        }
+        if constexpr (!SEG) {
+            float most_g = 0.f, most_z = 0.f;
+#pragma unroll
+            for (int c = 0; c < CK; ++c) most_g = fmaxf(most_g, fabsf(rg[c]));
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) most_z = fmaxf(most_z, fabsf(rz[c]));
+            if (fmaxf(most_g, most_z) > kSeqSplitMost || (most_g > 0.f && most_g < kSeqSplitLeast) || (most_z > 0.f && most_z < kSeqSplitLeast)) far_chunk = (int32_t)((c0 - first) / CK);
         }
         auto cut = [&](float a, float b, float by, uint32_t (&p)[P]) {
             if constexpr (SEG) seq_halves2(a * by, b * by, p);
@@ -1738,6 +1753,15 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
             sum += part[0];
         }
         __syncthreads();
+        const bool far = !SEG && __builtin_amdgcn_readfirstlane(far_chunk) == (int32_t)((c0 - first) / CK);
+        if (far) {                                         // the numbers as they are take the place of the pieces, row k of column c at (k + c) % 32
+            const int tid = seq_opaque(threadIdx.x), zc = tid % ZW, zq = tid / ZW;
+#pragma unroll
+            for (int c = 0; c < CK; ++c) reinterpret_cast<float *>(sdg)[tid * CK + ((c + tid) & (CK - 1))] = rg[c];
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) reinterpret_cast<float *>(sz)[zc * CK + ((zq * CPT + c + zc) & (CK - 1))] = rz[c];
+            __syncthreads();
+        }
         if (c0 + CK < last) {
             request(c0 + CK);
             request_ids(c0 + 2 * CK);
@@ -1748,6 +1772,22 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
         for (int g = 0; g < 2; ++g) {
             const int rt = 2 * wave + g;
             if (rt >= n_rt) continue;
+            if (far) {
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    seq_acc_t t;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) t[r] = 0.f;
+#pragma unroll 1
+                    for (int k = 0; k < CK; k += 2) {
+                        const int at = (k + half + l32) & (CK - 1);
+                        t = __builtin_amdgcn_mfma_f32_32x32x2f32(reinterpret_cast<const float *>(sdg)[(rt * 32 + l32) * CK + at], reinterpret_cast<const float *>(sz)[(ct * 32 + l32) * CK + at], t, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[g][ct][r] += t[r];
+                }
+                continue;
+            }
             typedef typename std::conditional<SEG, seq_h8_t, seq_b8_t>::type piece_t;
             piece_t a[CK / 16][P];
 #pragma unroll

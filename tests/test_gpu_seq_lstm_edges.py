@@ -226,3 +226,24 @@ def test_weights_and_gradients_near_the_ends_of_fp32(B, d, hidden):
         for got, ref in zip(h.lstm_backward(dev(x), dev(w_ih), dev(w), dev(g * scale), ws), want):
             size = np.abs(ref).max()
             assert np.linalg.norm(got.cpu().numpy() / size - ref / size) <= 2e-5 * np.linalg.norm(ref / size)
+
+
+@pytest.mark.parametrize("d,hidden", [(8, 8), (36, 32), (64, 72), (132, 64)])
+def test_weight_gradients_of_features_at_the_ends_of_fp32(B, d, hidden):
+    # g_w_ih is cut into pieces that neither hold features above 3.39e38 nor all bits of a column of features of 1e-36, or of gradients of 1e-35: those take fp32
+    # products.  The large feature's weights are zero, so that it changes nothing else; the other columns are as they are without it.
+    n = 150
+    rowptr, col = lists(n, hidden)
+    rng = np.random.default_rng(d)
+    x, w_ih, w_hh, b, g = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden), rng.normal(0, 1, (n, hidden))
+    w_ih[:, 2] = 0
+    small, huge = x.copy(), x.copy()
+    small[:, 1] *= 1e-36
+    huge[int(col[0]), 2] = 3.4e38
+    h = B.SeqHag(rowptr, col, 0).upload()
+    for feats, scale in ((small, 1.0), (small, 2.0 ** 100), (huge, 1e-3), (x, 1e-35)):
+        want = lstm.naive_aggregate_backward(rowptr, col, *(a.astype(np.float32).astype(np.float64) for a in (feats, w_ih, w_hh, b, g * scale)))[1]
+        _, ws = h.lstm_forward_train(dev(feats), dev(w_ih), dev(w_hh), dev(b))
+        got = h.lstm_backward(dev(feats), dev(w_ih), dev(w_hh), dev(g * scale), ws)[1].cpu().numpy().astype(np.float64)
+        # other columns have errors of up to 6e-7
+        assert (np.linalg.norm(got - want, axis=0) <= 2e-6 * np.linalg.norm(want, axis=0)).all()

@@ -122,6 +122,8 @@ __device__ __forceinline__ void seq_halves2_low(float a, float b, uint32_t (&p)[
     p[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, seq_h2_t));
 }
 
+constexpr float kSeqHLeast = 0x1p-26f;   // the smallest h that keeps all its bits so: its second piece rounds off 2^-51
+
 // Weights in the forms the kernels read, from the usual layout (w_ih [4H, D], w_hh [4H, H], b [4H], gate-major rows: input,
 // forget, cell, output gate).  Pre-activations are kept multiplied by a power of two of their gate row (see seq_halves2):
 //   wx: W_ih for the product over input rows, fp32, times the rows' factors too, [gate tile][dp / 8 groups of four k-steps][lane][4]; lane l supplies
@@ -1563,11 +1565,11 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 // loads are contiguous over a wavefront, eight rows make one 16-byte operand of a 32x32x16 matrix instruction per piece, and the sums of dG over a
 // node's rows run in its registers.  The matrix cores cut what they add to the size of the accumulator, always in the same direction, and a
 // gradient adds hundreds of thousands of rows: the products of 32 rows therefore begin at zero and join the running sums in rounded additions.
-//   Over the cells (SEG): two fp16 pieces, three products.  h is bounded; the 32 numbers of a column of dG are brought into range by the power of two
-//     that their largest asks for, with a sign that alternates over columns and chunks (so that half of the products are cut upwards), undone in the addition.
+//   Over the cells (SEG): two fp16 pieces (seq_halves2_low), three products.  h is bounded; the 32 numbers of a column of dG are brought into range by the power of two
+//     that their largest asks for, with a sign that alternates over columns and chunks (so that half of the products are cut upwards), undone in the addition.  A chunk
+//     with a run of rows whose largest h of a unit is below kSeqHLeast (an output gate that is all but closed), or with infinite gradients, takes fp32 products.
 //   Over the nodes, whose features have no bound: three bf16 pieces, six products, the large ones apart from the small ones.  A chunk with numbers beyond bf16's
 //     range, or with a run of rows whose largest is so small that last pieces would be lost, takes fp32 products of the numbers as they are (kSeqSplitMost, kSeqSplitLeast).
-//   Infinities and NaN stay not finite in both.
 // 3.35 M cells of 64 units: 1.41 ms with fp32 matrix instructions, 1.07 with bf16 pieces (vector instructions issue 59 % of the time, matrix cores are busy 31 %),
 // 0.96 with fp16 (4.5 TB/s); 0.85 M cells of 128 units: 1.33, 0.97 and 0.75 ms.  Error of the training step's results against 64 bits 1.2e-6, 5e-7 and 4.2e-7, 6.4e-7, 5.1e-7 and 5e-7.
 //
@@ -1632,13 +1634,13 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
     if (tid == 0) far_chunk = -1;
     __syncthreads();
     auto request_ids = [&](int64_t c0) {
-        int64_t at = c0 + (lane & (CK - 1));
+        int64_t at = c0 + (seq_opaque(threadIdx.x) & (CK - 1));
         at = at < last ? at : last - 1;
         ig = SEG ? A.at[at] : (int32_t)at;
         iz = SEG ? A.prev[at] : A.at[at];
     };
     auto request = [&](int64_t c0) {
-        const int tid = seq_opaque(threadIdx.x), zc = tid % ZW, zq = tid / ZW;
+        const int tid = seq_opaque(threadIdx.x), lane = tid & 63, zc = tid % ZW, zq = tid / ZW;
         const uint64_t g_row = (uint64_t)(A.dg + row0) + (uint64_t)(uint32_t)ig * (uint32_t)(rows4 * 4);
         const bool state = SEG && iz <= -2;
         const uint64_t z_row = (uint64_t)(state ? A.z2 : A.z) + (uint64_t)(uint32_t)(state ? -iz - 2 : iz < 0 ? 0 : iz) * (uint32_t)(cols * 4);
@@ -1669,26 +1671,22 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
         for (int c = 0; c < CPT; ++c)
             rz[c] = (zero >> ((seq_opaque(threadIdx.x) / ZW) * CPT + c)) & 1 ? 0.f : rz[c];
         const int tid = seq_opaque(threadIdx.x), zc = tid % ZW, zq = tid / ZW;
-        float by = 1.f;
-        if constexpr (SEG) {
-            float most = 0.f;
+        float by = 1.f, most_g = 0.f, most_z = 0.f;
 #pragma unroll
-            for (int c = 0; c < CK; ++c) most = fmaxf(most, fabsf(rg[c]));
-            const int up = seq_up(most);
+        for (int c = 0; c < CK; ++c) most_g = fmaxf(most_g, fabsf(rg[c]));
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) most_z = fmaxf(most_z, fabsf(rz[c]));
+        if constexpr (SEG) {
+            const int up = seq_up(most_g);
             const float one = ((int)(c0 / CK) + tid) & 1 ? -1.f : 1.f;
             by = __builtin_ldexpf(one, up);
             sback[tid] = __builtin_ldexpf(one, -up) / kSeqHScale;
-        }
-        if constexpr (!SEG) {
-            float most_g = 0.f, most_z = 0.f;
-#pragma unroll
-            for (int c = 0; c < CK; ++c) most_g = fmaxf(most_g, fabsf(rg[c]));
-#pragma unroll
-            for (int c = 0; c < CPT; ++c) most_z = fmaxf(most_z, fabsf(rz[c]));
-            if (fmaxf(most_g, most_z) > kSeqSplitMost || (most_g > 0.f && most_g < kSeqSplitLeast) || (most_z > 0.f && most_z < kSeqSplitLeast)) far_chunk = (int32_t)((c0 - first) / CK);
+            if (!(most_g < INFINITY) || (most_z > 0.f && most_z < kSeqHLeast)) far_chunk = (int32_t)((c0 - first) / CK);
+        } else if (fmaxf(most_g, most_z) > kSeqSplitMost || (most_g > 0.f && most_g < kSeqSplitLeast) || (most_z > 0.f && most_z < kSeqSplitLeast)) {
+            far_chunk = (int32_t)((c0 - first) / CK);
         }
         auto cut = [&](float a, float b, float by, uint32_t (&p)[P]) {
-            if constexpr (SEG) seq_halves2(a * by, b * by, p);
+            if constexpr (SEG) seq_halves2_low(a * by, b * by, p);
             else seq_split2(a, b, p);
         };
 #pragma unroll
@@ -1726,6 +1724,7 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
         }
         if (SEG) {
             // bit c: the node of row c ends there, or the range does
+            const int lane = seq_opaque(threadIdx.x) & 63;
             const int32_t after = __shfl_down(rs, 1);
             const bool ends = lane < here && (rs != after || lane + 1 + c0 == last);
             const uint32_t stops = (uint32_t)__ballot(ends);
@@ -1753,14 +1752,32 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
             sum += part[0];
         }
         __syncthreads();
-        const bool far = !SEG && __builtin_amdgcn_readfirstlane(far_chunk) == (int32_t)((c0 - first) / CK);
-        if (far) {                                         // the numbers as they are take the place of the pieces, row k of column c at (k + c) % 32
+        const bool far = __builtin_amdgcn_readfirstlane(far_chunk) == (int32_t)((c0 - first) / CK);
+        if (far) {                                         // the numbers as they are take the place of the pieces, row by row
             const int tid = seq_opaque(threadIdx.x), zc = tid % ZW, zq = tid / ZW;
 #pragma unroll
-            for (int c = 0; c < CK; ++c) reinterpret_cast<float *>(sdg)[tid * CK + ((c + tid) & (CK - 1))] = rg[c];
+            for (int c = 0; c < CK; ++c) reinterpret_cast<float *>(sdg)[c * 256 + tid] = rg[c];
 #pragma unroll
-            for (int c = 0; c < CPT; ++c) reinterpret_cast<float *>(sz)[zc * CK + ((zq * CPT + c + zc) & (CK - 1))] = rz[c];
+            for (int c = 0; c < CPT; ++c) reinterpret_cast<float *>(sz)[(zq * CPT + c) * ZW + zc] = rz[c];
             __syncthreads();
+            const int l32 = seq_opaque(threadIdx.x) & 31, half = (seq_opaque(threadIdx.x) >> 5) & 1;
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const int rt = 2 * wave + g;
+                if (rt >= n_rt) continue;
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    seq_acc_t t;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) t[r] = 0.f;
+#pragma unroll 1
+                    for (int k = 0; k < CK; k += 2)
+                        t = __builtin_amdgcn_mfma_f32_32x32x2f32(reinterpret_cast<const float *>(sdg)[(k + half) * 256 + rt * 32 + l32], reinterpret_cast<const float *>(sz)[(k + half) * ZW + ct * 32 + l32], t, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[g][ct][r] += t[r];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
         }
         if (c0 + CK < last) {
             request(c0 + CK);
@@ -1771,23 +1788,7 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
             const int rt = 2 * wave + g;
-            if (rt >= n_rt) continue;
-            if (far) {
-#pragma unroll
-                for (int ct = 0; ct < NCT; ++ct) {
-                    seq_acc_t t;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) t[r] = 0.f;
-#pragma unroll 1
-                    for (int k = 0; k < CK; k += 2) {
-                        const int at = (k + half + l32) & (CK - 1);
-                        t = __builtin_amdgcn_mfma_f32_32x32x2f32(reinterpret_cast<const float *>(sdg)[(rt * 32 + l32) * CK + at], reinterpret_cast<const float *>(sz)[(ct * 32 + l32) * CK + at], t, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[g][ct][r] += t[r];
-                }
-                continue;
-            }
+            if (far || rt >= n_rt) continue;
             typedef typename std::conditional<SEG, seq_h8_t, seq_b8_t>::type piece_t;
             piece_t a[CK / 16][P];
 #pragma unroll
@@ -1808,6 +1809,8 @@ __global__ __launch_bounds__(256, 2) void seq_weight_grad_kernel(SeqWgradArgs A,
                         t = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k][1], b[k], t, 0, 0, 0);
                         t = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k][0], z_piece(k, 1), t, 0, 0, 0);
                     }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) t[r] *= 1.f / kSeqLow;
 #pragma unroll
                     for (int k = 0; k < CK / 16; ++k) t = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k][0], b[k], t, 0, 0, 0);
 #pragma unroll

@@ -247,3 +247,42 @@ def test_weight_gradients_of_features_at_the_ends_of_fp32(B, d, hidden):
         got = h.lstm_backward(dev(feats), dev(w_ih), dev(w_hh), dev(g * scale), ws)[1].cpu().numpy().astype(np.float64)
         # other columns have errors of up to 6e-7
         assert (np.linalg.norm(got - want, axis=0) <= 2e-6 * np.linalg.norm(want, axis=0)).all()
+
+
+@pytest.mark.parametrize("d,hidden", [(8, 8), (16, 32), (16, 40), (20, 64), (12, 72), (12, 120)])
+@pytest.mark.parametrize("closed", [6, 12, 18, 30])
+def test_recurrent_weight_gradients_of_nearly_closed_units(B, d, hidden, closed):
+    # output gates of every second unit e^-6 to e^-30 open: their h, and with it the columns of g_w_hh that belong to them, are that much smaller than the others and keep their bits
+    n = 150
+    rowptr, col = lists(n, hidden)
+    rng = np.random.default_rng(d)
+    x, w_ih, w_hh, b, g = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden), rng.normal(0, 1, (n, hidden))
+    b[3 * hidden + 1::2] -= closed
+    want = lstm.naive_aggregate_backward(rowptr, col, *(a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b, g)))[2]
+    for cap in (0, int(col.size)):
+        h = B.SeqHag(rowptr, col, cap).upload()
+        _, ws = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
+        got = h.lstm_backward(dev(x), dev(w_ih), dev(w_hh), dev(g), ws)[2].cpu().numpy()
+        # exp of a pre-activation of -closed - 4 at most in size: its rounding, half of 2^-24 of that and as much from the sum and the scaling, is a relative error of h
+        bar = 2e-6 + 3 * (closed + 4) * 2.0 ** -24
+        for cols in (slice(0, None, 2), slice(1, None, 2)):
+            assert np.linalg.norm(got[:, cols] - want[:, cols]) <= bar * np.linalg.norm(want[:, cols])
+
+
+@pytest.mark.parametrize("hidden", [8, 64, 72])
+def test_an_infinite_gradient_stays_infinite_in_the_weight_gradients(B, hidden):
+    # lists of one: dG of node v is infinite where g is, and a sum of one infinite and many finite products has its sign; h before the step is zero, so that g_w_hh has no number there
+    n, d = 96, 8
+    rng = np.random.default_rng(hidden)
+    rowptr, col = np.arange(n + 1, dtype=np.int64), rng.permutation(n).astype(np.int32)
+    x, w_ih, w_hh, b, g = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden), rng.normal(0, 1, (n, hidden))
+    g[5, 1] = np.inf
+    h = B.SeqHag(rowptr, col, 0).upload()
+    _, ws = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
+    _, g_w_ih, g_w_hh, g_b = (t.cpu().numpy() for t in h.lstm_backward(dev(x), dev(w_ih), dev(w_hh), dev(g), ws))
+    rows = np.arange(4) * hidden + 1
+    rows = rows[[0, 2, 3]]       # (the forget gate's is infinity times the zero state)
+    assert np.isinf(g_b[rows]).all() and np.isinf(g_w_ih[rows]).all()
+    assert np.array_equal(np.sign(g_w_ih[rows]), np.sign(g_b[rows])[:, None] * np.sign(x[col[5]]))
+    others = np.setdiff1d(np.arange(4 * hidden), np.arange(4) * hidden + 1)
+    assert np.isfinite(g_w_ih[others]).all() and np.isfinite(g_w_hh[others]).all() and np.isfinite(g_b[others]).all()

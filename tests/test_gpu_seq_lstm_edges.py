@@ -1,4 +1,4 @@
-"""LSTM aggregator: sizes at the edges of the kernels' tiles and inputs with values that do not split into bf16 pieces.
+"""LSTM aggregator: sizes at the edges of the kernels' tiles, and numbers at the edges of the fp16 and bf16 pieces that its products run in.
 
 Forward: gate tiles of 8 hidden units, 16 columns per product step, variants for hidden up to 32, 64 and 128; the input half of the gates runs
 over 64 nodes at a time, d padded to 8.  Backward: node sums over ranges of cells that cut through a node's cells (one node in every list)."""
@@ -106,46 +106,64 @@ def test_gradients_scale_with_the_gradient_they_come_from(B, d, hidden):
 
 @pytest.mark.parametrize("d,hidden", [(8, 8), (16, 40), (20, 64), (12, 120)])
 def test_units_of_very_different_weights(B, d, hidden):
-    # Every unit's weights are brought to a common size by a power of two of their own: units of weight 2^3, 1, 2^-12, 2^-60 and 0 side by side, and
-    # a feature far outside fp16's range in both directions.
+    # Every gate row's weights are brought to a common size by a power of two of their own.  Side by side: units of ordinary weights, units whose rows are 2^-12 throughout, units of
+    # recurrent weights 2^-60 and 0, a weight that fp16 cannot hold (1e5, on a unit whose output gate lets e^-11 through), and features outside fp16's range in both directions.
     n = 150
     rowptr, col = lists(n, hidden)
     rng = np.random.default_rng(d)
-    size = np.tile(np.array([8.0, 1.0, 2.0 ** -12, 2.0 ** -60, 0.0])[np.arange(hidden) % 5], 4)[:, None]
-    x, w_ih, w_hh, b = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)) * size, rng.normal(0, 0.3, 4 * hidden)
-    w_hh[2, 1] = 300.0            # one large weight beside small ones within a unit
+    kind = np.arange(hidden) % 4
+    x, w_ih, w_hh, b = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden)
+    w_hh *= np.tile(np.array([1.0, 2.0 ** -12, 2.0 ** -60, 0.0])[kind], 4)[:, None]
+    w_ih *= np.tile(np.where(kind == 1, 2.0 ** -12, 1.0), 4)[:, None]
+    b *= np.tile(np.where(kind == 1, 2.0 ** -12, 1.0), 4)
+    b[3 * hidden + 7] -= 11
+    w_hh[2 * hidden + 4, 7] = 1e5
     x[3, 1], x[5, 2] = 1e25, 1e-25
     f32 = [a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b)]
     want, _ = lstm.naive_aggregate(rowptr, col, *f32)
-    # pre-activations of hidden terms of 8 * 0.3 |h| and d of 0.3: (0.5 * 2.4 hidden + d) * 2^-24 at most, the gates' slopes are below 1; the unit with the
-    # large weight adds one term of 300 |h|
-    bar = 1e-6 + (1.2 * hidden + d + 300) * 2.0 ** -24 * 4
+    without = [a.copy() for a in f32]
+    without[2][np.tile(kind == 1, 4)] = 0
+    fine = ~np.array([3 in col[rowptr[v]:rowptr[v + 1]] for v in range(n)])     # (the feature of 1e25 times 2^-12 saturates a small unit too)
+    # Gate functions leave absolute errors of about 1e-7, and six cells at most add them up: 2e-6 as in the test of gates below.  A small unit's are multiplied by gates of one half
+    # (c is 2^-13, h half of it): 5e-7, a hundredth of what its recurrent weights bring about.
+    bar = np.where(kind == 1, 5e-7, 2e-6)
+    assert np.abs(lstm.naive_aggregate(rowptr, col, *without)[0] - want)[fine][:, kind == 1].max() > 20 * 5e-7
     for cap in (0, int(col.size)):
         h = B.SeqHag(rowptr, col, cap).upload()
         got = h.lstm_forward(dev(x), dev(w_ih), dev(w_hh), dev(b))
-        assert np.abs(got.cpu().numpy() - want).max() <= bar
+        error = np.abs(got.cpu().numpy() - want)
+        assert error.max() <= 2e-6 and (error[fine].max(0) <= bar).all()
         a, _ = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
         assert torch.equal(a, got)
 
 
-@pytest.mark.parametrize("d,hidden", [(8, 8), (16, 40), (20, 64), (12, 72), (8, 128)])
+@pytest.mark.parametrize("d,hidden", [(8, 8), (16, 32), (16, 40), (20, 64), (12, 72), (8, 128)])
 def test_gradients_of_very_different_sizes(B, d, hidden):
-    # The product of the reverse pass brings a path's gradients and a unit's weights to a common size each: units of a gradient of 2^-40, 1 and 2^20, columns of
-    # weights of 2^3, 1, 2^-12, 2^-60 and 0, nodes without a gradient, side by side.
-    n = 150
+    # The product of the reverse pass brings a path's gradients and a column of weights to a common size each.  Side by side: nodes of gradients of 2^-40, 1, 0 and 2^20, which read nodes
+    # of their own kind only, so that every kind's rows of g_x are held against their own norm; and units whose columns of weights are 2^3, 1, 2^-12, 2^-60 and 0 times the others and
+    # whose own outputs have no gradient but for the first two: what reaches the small ones went through those columns, and so did their rows of the weight gradients.
+    n = 152
     rowptr, col = lists(n, hidden)
+    kind = np.arange(n) % 4
+    col = (col // 4 * 4 + np.repeat(kind, np.diff(rowptr))).astype(np.int32)
     rng = np.random.default_rng(d)
     x, w_ih, w_hh, b, g = rng.normal(0, 1, (n, d)), rng.normal(0, 0.3, (4 * hidden, d)), rng.normal(0, 0.3, (4 * hidden, hidden)), rng.normal(0, 0.3, 4 * hidden), rng.normal(0, 1, (n, hidden))
-    w_hh *= np.array([8.0, 1.0, 2.0 ** -12, 2.0 ** -60, 0.0])[np.arange(hidden) % 5]
-    g *= np.array([2.0 ** -40, 1.0, 0.0, 2.0 ** 20])[np.arange(n) % 4][:, None]
+    unit = np.arange(hidden) % 5
+    w_hh *= np.array([8.0, 1.0, 2.0 ** -12, 2.0 ** -60, 0.0])[unit]
+    g *= np.array([2.0 ** -40, 1.0, 0.0, 2.0 ** 20])[kind][:, None] * (unit < 2)
     f32 = [a.astype(np.float32).astype(np.float64) for a in (x, w_ih, w_hh, b, g)]
     want = lstm.naive_aggregate_backward(rowptr, col, *f32)
     for cap in (0, int(col.size)):
         h = B.SeqHag(rowptr, col, cap).upload()
         _, ws = h.lstm_forward_train(dev(x), dev(w_ih), dev(w_hh), dev(b))
-        for got, ref in zip(h.lstm_backward(dev(x), dev(w_ih), dev(w_hh), dev(g), ws), want):
-            # norm-wise, the bar of the other gradient tests
-            assert np.linalg.norm(got.cpu().numpy() - ref) <= 2e-5 * np.linalg.norm(ref)
+        g_x, *weights = (t.cpu().numpy() for t in h.lstm_backward(dev(x), dev(w_ih), dev(w_hh), dev(g), ws))
+        # norm-wise, the bar of the other gradient tests (columns of weights of 2.4 hand errors on that much larger)
+        for k in range(4):
+            assert np.linalg.norm(g_x[kind == k] - want[0][kind == k]) <= 2e-5 * np.linalg.norm(want[0][kind == k])
+        for got, ref in zip(weights, want[1:]):
+            for k in range(5):
+                rows = np.tile(unit == k, 4)
+                assert np.linalg.norm(got[rows] - ref[rows]) <= 2e-5 * np.linalg.norm(ref[rows])
         h.check()
 
 
@@ -286,3 +304,30 @@ def test_an_infinite_gradient_stays_infinite_in_the_weight_gradients(B, hidden):
     assert np.array_equal(np.sign(g_w_ih[rows]), np.sign(g_b[rows])[:, None] * np.sign(x[col[5]]))
     others = np.setdiff1d(np.arange(4 * hidden), np.arange(4) * hidden + 1)
     assert np.isfinite(g_w_ih[others]).all() and np.isfinite(g_w_hh[others]).all() and np.isfinite(g_b[others]).all()
+
+
+@pytest.mark.parametrize("hidden", [8, 32, 64])
+@pytest.mark.parametrize("masked", [False, True])
+def test_no_error_adds_up_over_many_cells(B, hidden, masked):
+    # The matrix cores cut sums downwards; the sign of the power of two that brings gradients into range alternates over paths, tiles, steps and chunks, so that cuts cancel.  Gradients that go
+    # with it, of every second node over lists of one length, which come as paths in order: as good as all of them.
+    n, d, length = 60000, 16, 8
+    gen = torch.Generator(device="cuda").manual_seed(hidden)
+    normal = lambda s, *shape: torch.randn(*shape, generator=gen, device="cuda") * s   # noqa: E731
+    idx = torch.randint(0, n, (n, length), generator=gen, device="cuda")
+    x, w_ih, w_hh, b, g = normal(1, n, d), normal(0.3, 4 * hidden, d), normal(0.3, 4 * hidden, hidden), normal(0.3, 4 * hidden), normal(1, n, hidden)
+    if masked:
+        g[1::2] = 0
+    h = B.SeqHag(np.arange(n + 1, dtype=np.int64) * length, idx.cpu().numpy().astype(np.int32).ravel(), 0).upload()
+    _, ws = h.lstm_forward_train(x, w_ih, w_hh, b)
+    got = h.lstm_backward(x, w_ih, w_hh, g, ws)
+    leaves = [t.double().requires_grad_() for t in (x, w_ih, w_hh, b)]
+    gates = leaves[0] @ leaves[1].t() + leaves[3]
+    hs = cs = torch.zeros(n, hidden, dtype=torch.float64, device="cuda")
+    for t in range(length):
+        i, f, u, o = (gates[idx[:, t]] + hs @ leaves[2].t()).split(hidden, 1)
+        cs = torch.sigmoid(f) * cs + torch.sigmoid(i) * torch.tanh(u)
+        hs = torch.sigmoid(o) * torch.tanh(cs)
+    # Errors are 2e-7 to 4e-7 here (with fp32 products up to 8e-7); with one sign throughout those of g_w_hh and g_b reach 1e-6 at 32 units and 3e-6 at 64.
+    for one, ref in zip(got, torch.autograd.grad(hs, leaves, g.double())):
+        assert ((one.double() - ref).norm() <= 8e-7 * ref.norm()).item()

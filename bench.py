@@ -330,7 +330,7 @@ def sweep_config5(torch, binding, synth, workloads, steps, warmup):
 
 
 FP32_MFMA_PEAK_TFLOPS = 157.3
-BF16_MFMA_PEAK_TFLOPS = 2500.0
+FP16_MFMA_PEAK_TFLOPS = 2500.0
 
 
 def seq_lstm_bench(torch, binding, synth, cfg, first_k, d, hidden, steps, warmup, only=None):
@@ -360,7 +360,7 @@ def seq_lstm_bench(torch, binding, synth, cfg, first_k, d, hidden, steps, warmup
     mfma_ceiling = probe_flops / (ea.elapsed_time(eb) * 1e-3) / 1e12
     log(f"[bench] fp32 matrix-core probe: {mfma_ceiling:.1f} TFLOP/s (published peak {FP32_MFMA_PEAK_TFLOPS})")
     # The cell's own arithmetic, for rates that compare plans; the passes do less of it: the input half of the gates is one fp32 product per node that
-    # occurs in a list, the recurrent half runs as six bf16 products per cell (three pieces of each operand).
+    # occurs in a list, the recurrent half runs as three fp16 products per cell (two pieces of each operand, of whose four products three).
     flops_per_cell = 2.0 * 4 * hidden * (d + hidden)
     n_used = int(np.unique(cl).size)
     res = {"workload": f"config{cfg}:{synth.CONFIGS[cfg]['name']}, first {first_k} neighbours in id order", "nodes": n,
@@ -378,12 +378,12 @@ def seq_lstm_bench(torch, binding, synth, cfg, first_k, d, hidden, steps, warmup
         res["plans"][name] = {"cells": p.cells, "aggregation_nodes": p.merges, "launches": p.launches, "levels": int(p.plan()[4].size - 1), "longest_chain": p.ranks, "ms_per_pass": ms,
                               "lists_ms_per_pass": ms_base, "speedup_vs_lists": ms_base / ms,
                               "cells_fewer": int(cl.size) / max(p.cells, 1), "cell_tflops": tf,
-                              # what the matrix cores execute: bf16 products of the cells and, in fp32, the per-node products
-                              "executed_bf16_tflops": 6 * 2.0 * 4 * hidden * hidden * p.cells / (ms * 1e-3) / 1e12,
+                              # what the matrix cores execute: fp16 products of the cells and, in fp32, the per-node products
+                              "executed_fp16_tflops": 3 * 2.0 * 4 * hidden * hidden * p.cells / (ms * 1e-3) / 1e12,
                               "executed_fp32_tflops": 2.0 * 4 * hidden * d * n_used / (ms * 1e-3) / 1e12}
         log(f"[bench] LSTM aggregator, {name}: {p.cells} cells ({res['plans'][name]['cells_fewer']:.2f}x fewer), {p.launches} launches, "
             f"{ms:.3f} ms per pass ({ms_base / ms:.2f}x the plain lists' speed), {tf:.1f} TFLOP/s of cell arithmetic, "
-            f"{res['plans'][name]['executed_bf16_tflops']:.0f} TFLOP/s of bf16 products executed")
+            f"{res['plans'][name]['executed_fp16_tflops']:.0f} TFLOP/s of fp16 products executed")
     # training: forward keeping the tape + backward (gradients of x and of the LSTM's parameters), where the sizes allow
     if plans and next(iter(plans.values())).train_workspace_bytes(d, hidden) > 0:
         g_a = torch.from_numpy(np.random.default_rng(synth.SEED_BASE + 100 * cfg + 8).normal(size=(n, hidden)).astype(np.float32)).cuda()
@@ -531,9 +531,9 @@ def main():
         print(json.dumps({"metric": "LSTM aggregator over ordered lists, forward: cell evaluations/s", "unit": "cells/s",
                           "value": main_plan["cells"] / (main_plan["ms_per_pass"] * 1e-3),
                           "n_gpus": 1, "dtype": "f32", "data": "synthetic", "higher_is_better": True, "vs_baseline": None,
-                          # the bf16 products that the cell kernel executes over the whole pass's time
-                          "roofline": {"bound": "mfma", "achieved": main_plan["executed_bf16_tflops"], "peak": BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-                                       "frac": main_plan["executed_bf16_tflops"] / BF16_MFMA_PEAK_TFLOPS, "traffic": None},
+                          # the fp16 products that the cell kernel executes over the whole pass's time
+                          "roofline": {"bound": "mfma", "achieved": main_plan["executed_fp16_tflops"], "peak": FP16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
+                                       "frac": main_plan["executed_fp16_tflops"] / FP16_MFMA_PEAK_TFLOPS, "traffic": None},
                           "config": res}), flush=True)
         return
     if cfg == 5:

@@ -97,7 +97,8 @@ __device__ __forceinline__ void seq_split2(float a, float b, uint32_t (&p)[3]) {
 // instead of six.  Both operands fit fp16's range because both are bounded: |h| <= 1 is multiplied by 2^15 and the weights of a gate row by the power of two
 // that brings the largest to [2^14, 2^15), so what the second piece of a small number rounds off (2^-25, the subnormal numbers of fp16) is
 // 2^-40 of that.  A smaller h or weight than 2^-17 of the largest loses bits, which the others hide: the gate functions leave errors of a few 2^-25 in h, and the row's
-// largest weight hands them on.
+// largest weight hands them on.  (Only where weights above 2^20 meet nothing but units whose output gates let less than 2^-20 through do 2^-40 of a weight reach 1e-6, which is
+// what the rounding of such a gate's own pre-activation leaves as well.)
 constexpr float kSeqHScale = 32768.f;
 constexpr int kSeqHScaleExp = 15;
 constexpr float kSeqXMost = 0x1p60f;   // see seq_input_gates_kernel
@@ -378,17 +379,18 @@ __device__ __forceinline__ void seq_from_pieces(V &v) {
 // registers and writes the new h to the other of two LDS buffers, so that a step has one barrier.  Paths are sorted by length, so
 // the paths of a tile end within a step or two of each other; a path that has ended keeps quiet while the others finish.
 //
-// The product runs in fp16 pieces (seq_halves2): three v_mfma_f32_32x32x16_f16 per 16 columns cost 96 cycles against 192 for bf16 pieces (six) and
-// 512 for fp32 instructions.  What is left is the element-wise part and the rows of gx.  Inference over 370 k nodes (hidden = d = 64, prefix HAG with 3.35 M
-// cells): 877 us with bf16 pieces, 737 so, 724 with one reciprocal for two gate functions; with the tape 1.57 and 1.49 ms (0.96 without the gates); 0.85 M cells of 128 units with the tape: 1.18 and 1.06 ms.  Error of the
-// result against 64 bits 2.1e-7 and 1.9e-7 (128 units: 2.7e-7 and 2.5e-7).
+// The product runs in fp16 pieces (seq_halves2): three v_mfma_f32_32x32x16_f16 per 16 columns, 96 cycles (bf16 pieces 192, fp32 instructions 512).
+// Bound by what it issues, products and element-wise part one after the other: vector instructions 65 % of the time, matrix cores 22 % (64 units; with the tape 50 and 17 % at
+// 3.3 TB/s, 128 units with the tape 38 and 19 % at 4.3 TB/s).  So sigmoid times tanh takes one reciprocal, and of 64 units no gates go to the tape.
+// Measured: inference over 370 k nodes (hidden = d = 64, prefix HAG with 3.35 M cells) 723 us (bf16 pieces 877); the same with the tape, this kernel alone, 0.96 ms (1.49
+// with the gates on it); 0.85 M cells of 128 units with the tape 1.01 ms.  Error of the result against 64 bits 1.9e-7 (bf16 pieces 2.1e-7).
 // A gate tile is 32 gate rows = 8 hidden units; lane l of the product holds, for path l % 32 of its half of the tile, the four
 // gates of units 8 * tile + 4 * (l / 32) + 0..3.
 //   HMAX 64 (hidden 33..64): 8 wavefronts, wavefront w holds gate tile w in registers and takes both halves of the paths;
 //   HMAX 32: wavefront w holds gate tile w % 4 and takes half w / 4;
 //   HMAX 128: 16 wavefronts, wavefront w holds half of gate tile w in registers (a whole tile would be 64 of the 128 there are at four wavefronts per SIMD) and streams
 //   the rest (2 KB per 16 columns) from the L2 cache once per step for both halves of the paths.  The weights in registers come first: the streamed ones, which
-//   queue behind the tape's stores, arrive meanwhile (0.85 M cells of 128 units with the tape: 1.06 ms with all of the tile streamed, 0.96 so).
+//   queue behind the tape's stores, arrive meanwhile (9 % faster than with all of the tile streamed).
 template <int HMAX, bool TAPE>
 __global__ __launch_bounds__(HMAX == 128 ? 1024 : 512, 4) void seq_chain_kernel(SeqChainArgs A) {
     constexpr bool BIG = HMAX == 128, WIDE = HMAX >= 64, C_LDS = HMAX == 64 || TAPE, GATES = TAPE && HMAX != 64;   // (of 64 units the backward pass computes the gates again)
@@ -726,6 +728,7 @@ __device__ __forceinline__ float seq_max16(float v) {
 __device__ __forceinline__ int seq_up(float most) { return most < INFINITY ? min(15 - __builtin_amdgcn_frexp_expf(most), 125) : 0; }
 // Sums of products of two such operands are put right in two steps, neither of which leaves fp32's range: by 2^(-kSeqBack - up) of the gradients' power, which is at
 // least 2^-149 and leaves up to 512 terms of the largest gradient's size, and by the exponent kSeqBack - up of the weights'.
+// Between the two steps gradients are 2^9 times smaller than in the end: of those below 2^-115 last bits go (gradients of 1e-36: errors of up to 1.1e-6).
 constexpr int kSeqBack = 24;
 
 // What the backward pass starts from, in one launch: cleared gradient rows of the kept states, cleared g_x where some node is in no list
@@ -822,12 +825,12 @@ constexpr int kSeqRevJobs = 32;   // paths per workgroup of the reverse kernels 
 // gate tile w), their running dh and dc and, per step, the sixteen dG.  The k index of dh_prev = W_hh^T dG can be taken in any order, so the
 // dG are the product's operand where they are, in the registers of the lane that made them: wavefront w multiplies the 32 gate
 // rows of its own tile and leaves its part of dh_prev for all units in LDS; after a barrier every lane adds the parts
-// for its own units, in a fixed order.  The operands are two fp16 pieces each (seq_halves2): gradients have no bound, so the
+// for its own units, in a fixed order.  The operands are two fp16 pieces each (seq_halves2_low): gradients have no bound, so the
 // largest of a path's 32 gate rows in the tile says what power of two brings them into fp16's range (seq_up), and whoever adds the parts multiplies by what undoes it.
 // The matrix cores cut what they add up, always downwards, and the gradients of hundreds of thousands of cells are added in the end: the factor's
-// sign alternates over paths, tiles and steps, so that half of the parts are cut upwards.  (Error of the training step's results against 64 bits at 3.35 M cells: 4.4e-6
-// with one sign, 4.9e-7 so, 5e-7 with fp32 instructions.)  The tape of the next step is requested before the product, without conditions (1 to 4 % of training steps
-// of 90 to 470 us).
+// sign alternates over paths, tiles and steps, so that half of the parts are cut upwards.  (Error of g_w_hh and g_b against 64 bits over 0.4 M cells of 32 units: 9e-7 and
+// 1.7e-6 with one sign, 2.9e-7 and 2.3e-7 so, 4.3e-7 and 2.7e-7 with fp32 instructions; the same where gradients go with the parity of the paths.)
+// The tape of the next step is requested before the product, without conditions (1 to 4 % of training steps of 90 to 470 us).
 __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A) {
     constexpr int HMAX = 32, NT = 4, RS = HMAX + 4, RJ = kSeqJobs;
     __shared__ __align__(16) float red[NT][RJ][RS];
@@ -1010,14 +1013,19 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_narrow_kernel(SeqRevArgs A
 }
 
 // Hidden sizes from 40 to 64: the products and their operands of the kernel above, 32 paths per workgroup, and the gates computed again instead of
-// read from the tape.  Bound by the tape, the kernel above took 1.93 ms for 3.35 M cells of 64 units and the forward pass 1.55, of which it stored 3.4 GB of gates for
-// most of the time; now 2.02 and 0.96 ms.  (Up to 32 units the products and the lockstep below take longer than the gates' bytes: 4 % slower on steps of 90 to 290 us.)
+// read from the tape.
 // Sixteen wavefronts in two roles, because one wavefront's registers do not hold both W_hh and W_hh^T, and weights streamed from the cache between the tape's
-// loads would wait for those (loads return in order: 2.50 ms):
-//   wavefronts 8..15 run ahead: they load h and c of the tape and the rows of gx, multiply W_hh with h as the forward pass does and leave the gates of the
-//     next step in LDS, and c of this one; they are the only ones that wait for loads;
+// loads would wait for those (loads return in order: a quarter slower):
+//   wavefronts 8..15 run ahead: they load h and c of the tape and the rows of gx, multiply W_hh with h in the forward pass's pieces and leave the gates of the
+//     next step in LDS, and c of this one; they are the only ones that wait for loads.  (The sum begins at zero and gx joins it last, where the forward pass begins with gx: the
+//     gates differ by a rounding from those that made c.);
 //   wavefronts 0..7 go back through the steps, wavefront w for gate tile w, out of LDS, and write dG.
-// A step has two barriers, and the loads of a step are requested two steps ahead, across half tiles too (steps of 280 to 340 us over short lists 5 % faster).  Vector instructions issue 55 % of the time, matrix cores are busy 15 %, 3 TB/s.
+// A step has two barriers, and the loads of a step are requested two steps ahead, across half tiles too.  What bounds it: reads out of LDS, vector instructions (61 % of the time),
+// products (16 %) and barriers, one after the other; 3.2 TB/s.
+// Why from 40 to 64: training steps with the gates on the tape and so, us: 370 k nodes, prefix HAG, 64 units 4600 and 4030; 74 k nodes in lists of 16, prefix HAG, 1302 and 1115
+// (40 units), 1654 and 1480 (64); 50 k nodes in lists of up to 8, 438 and 394, 566 and 525; 2 k nodes 148 and 143, 186 and 177; only lists of one and two entries lose, 514 and 547,
+// 744 and 775 (200 k nodes), too little to keep both forms.  Up to 32 units the products and the lockstep take longer than the gates' bytes (steps of 90 to 290 us: 4 %
+// slower), and above 64 the two forms of the weights fit no wavefronts' registers.
 __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
     constexpr int HMAX = 64, MT = 2, NT = 8, RS = HMAX + 4, RJ = kSeqRevJobs, KS = 4, ZS = HMAX + 8;
     constexpr int PT = 512 / RJ;                           // threads that stage the h and c of one path, four columns each
@@ -1111,7 +1119,7 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
             c_held = zero_next ? make_float4(0.f, 0.f, 0.f, 0.f) : c_next;
             keep_held = keep_next;
         };
-        auto product = [&](int t) {                        // the forward pass's recurrent product
+        auto product = [&](int t) {                        // the recurrent half of the gates
             const int l = seq_opaque(threadIdx.x) & 63;
 #pragma unroll
             for (int r = 0; r < 16; ++r) pre[r] = 0.f;
@@ -1335,15 +1343,13 @@ __global__ __launch_bounds__(1024, 4) void seq_reverse_kernel(SeqRevArgs A) {
     }
 }
 
-// Hidden sizes from 72 to 128.  A workgroup takes half a tile, 32 paths: dG is staged as rows of 4 * 128 + 2 in LDS (66 KB), so that two workgroups share
-// a compute unit and one's loads, stores and element-wise part run beside the other's products.  (With 64 paths and 131 KB a workgroup had the compute unit to
-// itself and its phases followed one another: 2.63 ms for 0.85 M cells of 128 hidden units, of which the products are 0.72 and the tape's bytes 0.75; as halves
-// 1.77 ms.)
+// Hidden sizes from 72 to 128.  A workgroup takes half a tile, 32 paths: dG is staged as rows of 4 * 128 + 8 pieces in LDS (66 KB), so that two workgroups share
+// a compute unit and one's loads, stores and element-wise part run beside the other's products (a third faster than 64 paths and 131 KB).
 // Sixteen threads per path run the element-wise part; every wavefront multiplies one 32-unit tile of W_hh^T, streamed from the L2 cache, with one half
-// of the gate rows, and the two parts are added by whoever reads dh_prev.  Operands in two fp16 pieces as in the kernel above, a path's gradients with one factor
-// for all gate rows (fp32 matrix instructions were busy 50 % of the time: 1.77 ms, 1.27 so; error against 64 bits 6.6e-7 and 5.1e-7).
-// What then took the time was waiting: a load under a condition of its own was waited for before the next (eight times the latency of memory per step), and
-// the weights came one step ahead of the products.  With loads that hang on nothing and weights four steps ahead: 0.94 ms.
+// of the gate rows, and the two parts are added by whoever reads dh_prev.  Operands in two fp16 pieces as in the kernels above, a path's gradients with one factor
+// for all gate rows.  No load hangs on a condition (it would be waited for before the next), and the weights come four steps ahead of the products.
+// 0.85 M cells of 128 units: 0.95 ms (4.5 TB/s; vector instructions 42 % of the time, matrix cores 19 %); 1.77 with fp32 products, 1.27 with fp16 pieces and loads that waited for
+// one another.  Error of the training step's results against 64 bits 5.1e-7 (fp32 products 6.7e-7).
 __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) {
     constexpr int ZS = 4 * 128 + 8, IT = 8, TP = 16;       // units per thread, threads per path; rows 4 banks apart
     // per path: the pre-activation gradients of the current step in fp16 pieces (the product's operand), then, in the row of the first pieces, the two parts
@@ -1570,8 +1576,8 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 //     with a run of rows whose largest h of a unit is below kSeqHLeast (an output gate that is all but closed), or with infinite gradients, takes fp32 products.
 //   Over the nodes, whose features have no bound: three bf16 pieces, six products, the large ones apart from the small ones.  A chunk with numbers beyond bf16's
 //     range, or with a run of rows whose largest is so small that last pieces would be lost, takes fp32 products of the numbers as they are (kSeqSplitMost, kSeqSplitLeast).
-// 3.35 M cells of 64 units: 1.41 ms with fp32 matrix instructions, 1.07 with bf16 pieces (vector instructions issue 59 % of the time, matrix cores are busy 31 %),
-// 0.96 with fp16 (4.5 TB/s); 0.85 M cells of 128 units: 1.33, 0.97 and 0.75 ms.  Error of the training step's results against 64 bits 1.2e-6, 5e-7 and 4.2e-7, 6.4e-7, 5.1e-7 and 5e-7.
+// 3.35 M cells of 64 units: 1.02 ms (4.4 TB/s; vector instructions 61 % of the time, matrix cores 17 %), with fp32 matrix instructions 1.41; 0.85 M cells of 128 units: 0.85 (3.3 TB/s,
+// 62 and 24 %) and 1.33 ms.  Error of the training step's results against 64 bits 4e-7 (fp32 instructions 1.2e-6) and 5.1e-7 (6.7e-7).
 //
 // SEG: the rows are cells, taken in the order of the input row they read (`at`, ascending `seg`), z is h_prev, and while a row of dG is at hand
 // it is also added to s[seg], the sum of dG over the cells that read one node: dG is read once for both.  A workgroup takes a

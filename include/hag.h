@@ -218,7 +218,7 @@ int hag_seq_check(const hag_seq_t *h, void *stream);
 size_t hag_seq_workspace_bytes(const hag_seq_t *h, int64_t d, int64_t hidden);
 /* Numbers: fp32 in and out.  W_ih x + b is summed in fp32, in all of its range; W_hh h runs on products of two fp16 pieces per operand that powers of two bring into range
  * (a row of W_hh to within 2^-40 of its largest weight, h to within 2^-40), and the backward pass's products likewise (gradients to within 2^-51 of the largest of a
- * path's step), with errors no larger than those of fp32 products.  Finite pre-activations of any size are as good as fp32's: large ones saturate the gates.  An infinite gradient makes what
+ * path's step), with errors no larger than those of fp32 products but where weights above 1e7 meet outputs below 1e-7.  Finite pre-activations of any size are as good as fp32's: large ones saturate the gates.  An infinite gradient makes what
  * it reaches infinite or NaN (within a list's earlier steps NaN), and nothing else. */
 int hag_seq_lstm_forward(const hag_seq_t *h, int64_t d, int64_t hidden, const float *x, const float *w_ih,
                          const float *w_hh, const float *b, float *a_out, void *workspace, void *stream);

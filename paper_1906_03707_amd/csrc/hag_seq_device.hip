@@ -97,8 +97,8 @@ __device__ __forceinline__ void seq_split2(float a, float b, uint32_t (&p)[3]) {
 // instead of six.  Both operands fit fp16's range because both are bounded: |h| <= 1 is multiplied by 2^15 and the weights of a gate row by the power of two
 // that brings the largest to [2^14, 2^15), so what the second piece of a small number rounds off (2^-25, the subnormal numbers of fp16) is
 // 2^-40 of that.  A smaller h or weight than 2^-17 of the largest loses bits, which the others hide: the gate functions leave errors of a few 2^-25 in h, and the row's
-// largest weight hands them on.  (Only where weights above 2^20 meet nothing but units whose output gates let less than 2^-20 through do 2^-40 of a weight reach 1e-6, which is
-// what the rounding of such a gate's own pre-activation leaves as well.)
+// largest weight hands them on.  Where output gates let only e^-k through and weights of 0.3 e^k make up for it, the error of the result is that of three bf16 pieces up to k = 16
+// (8 units: 8.4e-6 and 7.8e-6, from the rounding of such a gate's own pre-activation); with weights of 2e7 and 1e9 (k = 18 and 22) it is 3e-5 and 2e-3 (bf16 pieces 8e-6 and 6e-5).
 constexpr float kSeqHScale = 32768.f;
 constexpr int kSeqHScaleExp = 15;
 constexpr float kSeqXMost = 0x1p60f;   // see seq_input_gates_kernel

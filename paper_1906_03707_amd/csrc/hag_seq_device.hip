@@ -1577,7 +1577,7 @@ __global__ __launch_bounds__(512, 4) void seq_reverse_wide_kernel(SeqRevArgs A) 
 //   Over the nodes, whose features have no bound: three bf16 pieces, six products, the large ones apart from the small ones.  A chunk with numbers beyond bf16's
 //     range, or with a run of rows whose largest is so small that last pieces would be lost, takes fp32 products of the numbers as they are (kSeqSplitMost, kSeqSplitLeast).
 // 3.35 M cells of 64 units: 1.02 ms (4.4 TB/s; vector instructions 61 % of the time, matrix cores 17 %), with fp32 matrix instructions 1.41; 0.85 M cells of 128 units: 0.85 (3.3 TB/s,
-// 62 and 24 %) and 1.33 ms.  Error of the training step's results against 64 bits 4e-7 (fp32 instructions 1.2e-6) and 5.1e-7 (6.7e-7).
+// 62 and 24 %) and 1.33 ms.  Where every chunk takes fp32 products, training steps take 10 to 26 % longer (half of the units closed) and 1 to 4 % (a column of features of 1e-36).  Error of the training step's results against 64 bits 4e-7 (fp32 instructions 1.2e-6) and 5.1e-7 (6.7e-7).
 //
 // SEG: the rows are cells, taken in the order of the input row they read (`at`, ascending `seg`), z is h_prev, and while a row of dG is at hand
 // it is also added to s[seg], the sum of dG over the cells that read one node: dG is read once for both.  A workgroup takes a
